@@ -668,8 +668,48 @@ __device__ __forceinline__ bool ap_ht_has(const int32_t *ht, int32_t v) {
     }
 }
 
+// What a construction knows beyond the lists of a round and ap_stage_refine's callers do not: all NULL for a round on
+// arbitrary lists, in which every candidate is scored in full.
+struct ApRefineHints {
+    // [nn]: no document outside the node's exact dense seed list has a dense part above this (the seed stage's K-th score, in
+    // that stage's arithmetic); -inf where the seed list holds every other document
+    const float *tau;
+    // first round only: the scores the seed stage gave the lists' members
+    const float *seed_sc;
+    // later rounds: the fused scores of the lists, and per node one bit for each of the first S list entries, set if the entry
+    // was among the first S of the node's list one round ago
+    const float *knn_sc;
+    const uint32_t *known;
+    uint32_t *known_out;   // the same bits for the lists this round returns
+};
+
 #define AP_RT_SPB 10   // look-up tables of the node's own lists: 1024 + 512 slots, at most a quarter full
 #define AP_RT_TXB 9
+// Records and dense rows a wave has on their way at once (three rounds on 200,000 bf16 documents: 2 and 1: 165 ms, 4 and 1:
+// 153 ms, 4 and 2: 150 ms, 4 and 4: 150 ms, 8 and 2: 151 ms).
+#define AP_RF_G 4
+#define AP_RF_GD 2
+#define AP_RF_TOP 0x40000000   // bit of a candidate that is among the first S entries of the node's own list (ids have 30 bits)
+
+// One refinement round for one node.  What bounds it: the candidates' bytes (record and dense row) and the instructions
+// of their look-ups, so the work is to touch fewer of them.  With the hints of a construction three things need no
+// reading, and the lists stay what scoring everything gives, bit for bit:
+//  - a candidate scored for this node before.  Lists only improve: whatever a round scored and did not keep ranks after K
+//    documents that the list still holds or has exchanged for better ones, so it cannot enter again, and the per-path
+//    lists were offered it.  That is the node's own list (its scores are at hand), and every neighbour's neighbour
+//    w = N(v)[j] whose v was already among the first S of N(u) one round ago and w among the first S of N(v): both are
+//    bits of `known`.
+//  - the dense row of a candidate whose sparse and lexical parts leave it out of reach.  The seed lists are the exact
+//    dense neighbours, so a document outside the node's list has a dense part of at most tau (plus the rounding of two
+//    differently ordered sums, eps |u||w|) -- 0.1 where the norms alone would allow 1.  It is read only if that bound lifts
+//    the candidate to the threshold T of the fused list or to the last entry of the per-path list by the dense part.
+//    T is the list's last score in later rounds.  In the first round, whose list carries no fused scores, the K candidates
+//    with the best sparse and lexical parts are scored first, and T is the least of their scores.
+// Phases: records of all candidates (a wave each, two on their way at a time), a thread per candidate decides about the
+// dense rows, dense rows of those that need one (a wave each), sort, lists.  Measured on 200,000 documents of 1,024 bf16
+// columns, three rounds: 308 ms with every candidate
+// scored in full, 150 ms now (7 TB/s of traffic in the first round: what a read-mostly kernel reaches here); 768 f32 columns,
+// 100,000 documents: 202 -> 81 ms.
 template <int DT, int NV>
 __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restrict__ rec, const uint4 *__restrict__ meta, float wd,
                                                 float ws, float wf, int32_t K, int32_t S, int32_t P,
@@ -677,19 +717,32 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
                                                 const float *__restrict__ sp_sc, const int32_t *__restrict__ node_ids,
                                                 int64_t nn, int64_t x0, int32_t *__restrict__ out_ids, float *__restrict__ out_sc,
                                                 int32_t *__restrict__ out_sp_ids, float *__restrict__ out_sp_sc,
-                                                unsigned long long *__restrict__ n_sims) {
-    __shared__ int32_t ht[AP_HT];
+                                                unsigned long long *__restrict__ n_sims, ApRefineHints hint) {
+    __shared__ __attribute__((aligned(16))) int32_t ht[AP_HT];
     __shared__ int32_t cand[AP_MAXC];
-    __shared__ uint64_t keys[2048];   // the candidates' fused keys, sorted in place afterwards (AP_MAXC padded to a power of two)
+    __shared__ uint64_t keys[2048];   // fused keys of the candidates that can enter the list, sorted in place afterwards (AP_MAXC padded to a power of two)
+    // per candidate: before it is scored, where its record lies, the two lengths and the dense norm; then the norm and the
+    // two list parts; then the three component scores (dense part -inf: not needed, not computed)
     __shared__ float comp[3][AP_MAXC];
     __shared__ int32_t l_sp_idx[AP_A_CAP], l_tx_idx[AP_A_CAP];
     __shared__ float l_sp_val[AP_A_CAP], l_tx_val[AP_A_CAP];
     __shared__ uint64_t oldk[3][32];
     __shared__ __attribute__((aligned(16))) uint64_t qtab[(1 << AP_RT_SPB) + (1 << AP_RT_TXB)];
-    __shared__ int32_t s_cnt, s_seed[2];
+    __shared__ uint16_t need[AP_MAXC];        // candidates whose dense row is to be read
+    __shared__ int32_t misc[4];
+    __shared__ uint64_t pre;
+    __shared__ int32_t s_cnt, s_seed[2], s_nk, s_need;
+    __shared__ uint32_t s_T;
+    __shared__ float s_dP;
+    // with hints the hash set is done with once the candidates are known, and its space serves again
+    uint64_t *sel = reinterpret_cast<uint64_t *>(ht);               // [256] first round: the K best by sparse and lexical parts
+    uint32_t *hist = reinterpret_cast<uint32_t *>(ht) + 512;        // [256]
+    uint64_t (*better)[64] = reinterpret_cast<uint64_t (*)[64]>(ht + 768);   // [3][64] candidates that beat a full per-path list's last entry
     const int64_t x = x0 + blockIdx.x;   // the launch covers nodes x0 .. x0 + gridDim.x of the nn
     const int64_t u = node_ids ? (int64_t)node_ids[x] : x;
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
+    constexpr int NW = 8;
+    const bool fast = hint.tau != nullptr, later = hint.knn_sc != nullptr;   // uniform
     const ApLists a = ap_stage_lists(D, u, l_sp_idx, l_sp_val, l_tx_idx, l_tx_val, AP_A_CAP);
     float qa[NV * ApDense<DT>::EPC];
     ap_load_aside<DT, NV, DT>(D.dense, u, D.dim, qa);
@@ -698,12 +751,24 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
     // look-up, as in the search); lists that are longer, or that no multiplier fits, are searched where they lie
     bool use_tab = a.sp_n <= (1 << AP_RT_SPB) / 4 && a.tx_n <= (1 << AP_RT_TXB) / 4;   // uniform
     uint32_t msp = 0, mtx = 0;
-    if (threadIdx.x == 0) s_cnt = 0;
+    if (threadIdx.x == 0) { s_cnt = 0; s_nk = 0; s_need = 0; s_T = 0xffffffffu; }
     __syncthreads();
     if (use_tab && wave == 0) {
         const int32_t s0 = ap_bucket_build<4>(a.sp_idx, a.sp_val, a.sp_n, qtab, AP_RT_SPB);
         const int32_t s1 = ap_bucket_build<2>(a.tx_idx, a.tx_val, a.tx_n, qtab + (1 << AP_RT_SPB), AP_RT_TXB);
         if (lane == 0) { s_seed[0] = s0; s_seed[1] = s1; }
+    }
+    // candidates: the node's own list ...
+    const int32_t sl = S < K ? S : K;
+    for (int32_t s = threadIdx.x; s < K; s += blockDim.x) {
+        const int32_t v = knn[u * K + s];
+        if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v)) {
+            if (later) keys[atomicAdd(&s_nk, 1)] = ap_make_key(hint.knn_sc[u * K + s], v, s < sl ? 1u : 0u);   // scored in an earlier round
+            else {
+                const int32_t at = atomicAdd(&s_cnt, 1);
+                cand[fast ? s : at] = v | (s < sl ? AP_RF_TOP : 0);   // a seed list's members are distinct and lead the list: candidate s is member s
+            }
+        }
     }
     __syncthreads();
     if (use_tab) {
@@ -711,93 +776,213 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
         use_tab = seed0 >= 0 && seed1 >= 0;
         if (use_tab) { msp = ap_seed_mult(seed0); mtx = ap_seed_mult(seed1); }
     }
-    // candidates: own list, and the first S neighbours of the first S neighbours
-    const int32_t sl = S < K ? S : K;
-    const int32_t slots = K + sl * sl;
-    for (int32_t s = threadIdx.x; s < slots; s += blockDim.x) {
-        int32_t v;
-        if (s < K) v = knn[u * K + s];
-        else {
-            const int32_t i = (s - K) / sl, j = (s - K) % sl;
+    const int32_t n_own = ap_uniform_i32(s_cnt);   // candidates of the node's own list (0 in later rounds)
+    __syncthreads();
+    // ... and the first S neighbours of the first S neighbours
+    {
+        const uint32_t mine = later ? hint.known[u] : 0u;
+        for (int32_t s = threadIdx.x; s < sl * sl; s += blockDim.x) {
+            const int32_t i = s / sl, j = s % sl;
             const int32_t p = knn[u * K + i];
-            v = p < 0 ? -1 : knn[(int64_t)p * K + j];
+            if (p < 0) continue;
+            if ((mine >> i) & 1u && (hint.known[p] >> j) & 1u) continue;   // scored for this node in an earlier round
+            const int32_t v = knn[(int64_t)p * K + j];
+            if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v)) cand[atomicAdd(&s_cnt, 1)] = v;
         }
-        if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v)) cand[atomicAdd(&s_cnt, 1)] = v;
     }
     __syncthreads();
     const int32_t cnt = ap_uniform_i32(s_cnt);
     if (threadIdx.x == 0 && n_sims) atomicAdd(n_sims, (unsigned long long)cnt);   // measurement: similarities of this node and round
-    // where each candidate's record lies and how long it is: fetched for all candidates at once, and parked in the space
-    // the candidates' component scores take later, so that the scoring loop starts its loads without a round trip of its own
-    if (use_tab) {
-        for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
-            const uint4 m = meta[cand[t]];
-            comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y);
-        }
-        __syncthreads();
+    // where each candidate's record lies and how long it is, fetched for all candidates at once, so that the scoring loop
+    // starts its loads without a round trip of its own
+    for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
+        const uint4 m = meta[cand[t] & ~AP_RF_TOP];
+        comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y); comp[2][t] = __uint_as_float(m.z);
     }
-    for (int32_t i = wave; i < cnt; i += (int32_t)(blockDim.x >> 6)) {
-        const int32_t v = ap_uniform_i32(cand[i]);
-        float sd, ss, sf;
-        if (use_tab) {
-            uint4 raw[NV];
-            ap_dense_load_raw<DT, NV>(D, v, raw);   // the dense row is always needed here: its loads go first
-            const uint32_t mx = ap_uniform_u32(__float_as_uint(comp[0][i])), my = ap_uniform_u32(__float_as_uint(comp[1][i]));
-            const uint2 *r = rec + mx;
-            const int32_t spn = (int32_t)(my & 0xffffu), txn = (int32_t)(my >> 16);
-            int32_t si[2], ti[1];
-            float sv[2], tv[1];
-            ap_rec_load<2, 1>(r, spn, txn, si, sv, ti, tv);
-            sd = ap_dense_dot_raw<DT, NV>(D, qa, raw);
-            ap_rec_reduce_bucket<2, 1, AP_RT_SPB, AP_RT_TXB>(r, (const AP_LDS uint64_t *)qtab, (const AP_LDS uint64_t *)(qtab + (1 << AP_RT_SPB)),
-                                                             msp, mtx, spn, txn, si, sv, ti, tv, ss, sf);
-        } else {
-            ap_hybrid_wave<DT, NV>(D, qa, a, v, sd, ss, sf);
-        }
-        if (lane == 0) {
-            keys[i] = ap_make_key(ap_fuse(wd, ws, wf, sd, ss, sf), v, 1u);
-            comp[0][i] = sd; comp[1][i] = ss; comp[2][i] = sf;
-        }
-    }
-    // top-K under the fused score: the keys (all different: a key carries its id) sorted in LDS.  Ranking every key
-    // against every other took a third of the kernel's vector instructions.
-    int32_t n2 = 64;
-    while (n2 < cnt) n2 <<= 1;   // uniform; cnt <= AP_MAXC <= 2048
-    for (int32_t t = cnt + threadIdx.x; t < n2; t += blockDim.x) keys[t] = 0ull;
-    ap_bitonic_desc(keys, n2);   // begins and ends with a barrier
-    for (int32_t t = threadIdx.x; t < K; t += blockDim.x) {
-        const uint64_t key = t < cnt ? keys[t] : 0ull;
-        out_ids[x * K + t] = t < cnt ? ap_key_id(key) : -1;
-        out_sc[x * K + t] = t < cnt ? ap_key_score(key) : -INFINITY;
-    }
-    // per-path lists: the best P by each single similarity among this round's candidates and the previous list (entries
-    // scored again this round excepted).  One wave per path, on its own: every lane keeps its share of the keys in
-    // registers and the P best are drawn one after the other by wave-wide maxima (no block-wide pass, no barrier).
+    // the per-path lists so far, in keys (entries scored again in a round that scores everything are left out: there the
+    // caller's scores need not be this kernel's)
     if (wave < 3) {
-        const int p = wave;
         uint64_t ok = 0;
         bool have = false;
         if (lane < P) {
-            const int32_t id = sp_ids[((int64_t)p * D.n + u) * P + lane];
-            if (id >= 0 && !ap_ht_has(ht, id)) { have = true; ok = ap_make_key(sp_sc[((int64_t)p * D.n + u) * P + lane], id, 1u); }
+            const int32_t id = sp_ids[((int64_t)wave * D.n + u) * P + lane];
+            if (id >= 0 && (fast || !ap_ht_has(ht, id))) { have = true; ok = ap_make_key(sp_sc[((int64_t)wave * D.n + u) * P + lane], id, 1u); }
         }
         const uint64_t hm = __ballot(have);
-        const int32_t nold = (int32_t)__popcll(hm);
-        if (have) oldk[p][__popcll(hm & ((1ull << lane) - 1ull))] = ok;
+        if (lane < 32) oldk[wave][lane] = 0ull;
         ap_wave_sync();
-        constexpr int PER = (AP_MAXC + 32 + 63) / 64;
-        uint64_t mine[PER];
+        if (have) oldk[wave][__popcll(hm & ((1ull << lane) - 1ull))] = ok;
+    }
+    __syncthreads();
+    // the sparse and lexical parts of all candidates
+    if (use_tab) {
+        constexpr int G = AP_RF_G;
+        for (int32_t i0 = wave; i0 < cnt; i0 += G * NW) {
+            uint2 xs[G][2], xt[G][1];
+            const uint2 *r[G];
+            int32_t spn[G], txn[G];
+            float norm[G];
 #pragma unroll
-        for (int j = 0; j < PER; j++) {
-            const int32_t t = j * 64 + lane;
-            mine[j] = t < cnt ? ap_make_key(comp[p][t], cand[t], 1u) : (t < cnt + nold ? oldk[p][t - cnt] : 0ull);
+            for (int g = 0; g < G; g++) {
+                const int32_t i = i0 + NW * g < cnt ? i0 + NW * g : i0;   // past the end: the first one again, for nothing
+                const uint32_t my = ap_uniform_u32(__float_as_uint(comp[1][i]));
+                r[g] = rec + ap_uniform_u32(__float_as_uint(comp[0][i]));
+                norm[g] = comp[2][i];
+                spn[g] = (int32_t)(my & 0xffffu); txn[g] = (int32_t)(my >> 16);
+                ap_rec_load_raw<2, 1>(r[g], spn[g], txn[g], xs[g], xt[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                if (i0 + NW * g >= cnt) break;   // uniform
+                int32_t si[2], ti[1];
+                float sv[2], tv[1], ss, sf;
+                ap_rec_decode<2, 1>(xs[g], xt[g], spn[g], txn[g], si, sv, ti, tv);
+                ap_rec_reduce_bucket<2, 1, AP_RT_SPB, AP_RT_TXB>(r[g], (const AP_LDS uint64_t *)qtab, (const AP_LDS uint64_t *)(qtab + (1 << AP_RT_SPB)),
+                                                                 msp, mtx, spn[g], txn[g], si, sv, ti, tv, ss, sf);
+                const int32_t i = i0 + NW * g;
+                if (lane == 0) { comp[0][i] = norm[g]; comp[1][i] = ss; comp[2][i] = sf; }
+            }
         }
-        uint64_t prev = ~0ull;
-        for (int32_t r = 0; r < P; r++) {
-            uint64_t best = 0;
+    } else {
+        for (int32_t i = wave; i < cnt; i += NW) {
+            const uint32_t my = ap_uniform_u32(__float_as_uint(comp[1][i]));
+            const uint2 *r = rec + ap_uniform_u32(__float_as_uint(comp[0][i]));
+            const float norm = comp[2][i];
+            const int32_t spn = (int32_t)(my & 0xffffu), txn = (int32_t)(my >> 16);
+            int32_t si[2], ti[1];
+            float sv[2], tv[1], ss, sf;
+            ap_rec_load<2, 1>(r, spn, txn, si, sv, ti, tv);
+            ap_rec_reduce_lists<2, 1>(r, a, spn, txn, si, sv, ti, tv, ss, sf);
+            if (lane == 0) { comp[0][i] = norm; comp[1][i] = ss; comp[2][i] = sf; }
+        }
+    }
+    __syncthreads();
+
+    // dense rows of the candidates need[d0 .. d1): a wave each; the first n_t of them (from 0) set the threshold T
+    auto dense_rows = [&](int32_t d0, int32_t d1, int32_t n_t) {
+        constexpr int G = AP_RF_GD;
+        for (int32_t e0 = d0 + wave; e0 < d1; e0 += G * NW) {
+            uint4 raw[G][NV];
+            int32_t cand_i[G], cv[G];
 #pragma unroll
-            for (int j = 0; j < PER; j++)
-                if (mine[j] < prev && mine[j] > best) best = mine[j];
+            for (int g = 0; g < G; g++) {
+                const int32_t d = e0 + NW * g < d1 ? e0 + NW * g : e0;
+                cand_i[g] = ap_uniform_i32(need[d]);
+                cv[g] = ap_uniform_i32(cand[cand_i[g]]);
+                ap_dense_load_raw<DT, NV>(D, cv[g] & ~AP_RF_TOP, raw[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                if (e0 + NW * g >= d1) break;   // uniform
+                const int32_t i = cand_i[g];
+                const float ss = comp[1][i], sf = comp[2][i];
+                const float sd = ap_dense_dot_raw<DT, NV>(D, qa, raw[g]);
+                if (lane == 0) {
+                    const float f = ap_fuse(wd, ws, wf, sd, ss, sf);
+                    comp[0][i] = sd;
+                    keys[atomicAdd(&s_nk, 1)] = ap_make_key(f, cv[g] & ~AP_RF_TOP, cv[g] & AP_RF_TOP ? 1u : 0u);
+                    if (e0 + NW * g < n_t) atomicMin(&s_T, ap_f2ord(f));
+                }
+            }
+        }
+    };
+    if (!fast) {
+        for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) need[t] = (uint16_t)t;
+        __syncthreads();
+        dense_rows(0, cnt, 0);
+    } else {
+        // Bounds of the dense part of candidate t with norm |w|: the seed stage's score (members of the seed list, whose
+        // scores the first round has) or its K-th score (documents outside it), plus eps |u||w|: each of the two differently
+        // ordered fp32 sums is off by at most dim 2^-24 |u||w| from the exact product; twice that for each is allowed.
+        const float un = __uint_as_float(meta[u].z), eps = 4.f * (float)D.dim * 5.9604645e-8f;
+        const float tau = hint.tau[u];
+        // the last entry of the per-path list by the dense part, or a lower bound of it
+        float dP = -INFINITY;
+        if (later) {
+            const uint64_t last = oldk[0][P - 1];
+            if (last) dP = ap_key_score(last);
+        } else if (P <= K && n_own >= P) {   // the P best of the seed list by their seed scores are at least this good
+            if (wave == 0) {
+                float lo = INFINITY;
+                if (lane < P) {
+                    const int32_t v = knn[u * K + lane];
+                    lo = v >= 0 ? hint.seed_sc[u * K + lane] - eps * un * __uint_as_float(meta[v].z) * 1.0001f : -INFINITY;
+                }
+                for (int o = 32; o > 0; o >>= 1) lo = fminf(lo, __shfl_xor(lo, o, 64));
+                if (lane == 0) s_dP = lo;
+            }
+            __syncthreads();
+            dP = s_dP;
+        }
+        auto bound = [&](int32_t t, float &bd, float &bf) {   // upper bounds of the dense part and of the fused score
+            const float nb = un * comp[0][t] * 1.0001f, ss = comp[1][t], sf = comp[2][t];
+            const float most = t < n_own ? hint.seed_sc[u * K + t] : tau;   // n_own is 0 in later rounds
+            bd = most - most == 0.f ? fminf(nb, most + eps * nb) : nb;
+            const float lift = wd >= 0.f ? wd * bd : -wd * nb;
+            bf = fmaf(wf, sf, ws * ss) + lift + 1e-5f * (fabsf(ws * ss) + fabsf(wf * sf) + fabsf(wd) * nb);
+        };
+        float T = -INFINITY;
+        int32_t n_first = 0;
+        if (later) {
+            if (s_nk == K) T = hint.knn_sc[u * K + K - 1];   // nothing was added to the keys since
+        } else {
+            // the K best by sparse and lexical parts, and whatever the dense list may want of the node's own list
+            for (int32_t i = threadIdx.x; i < 256; i += blockDim.x) sel[i] = 0ull;
+            __syncthreads();
+            const int32_t got = ap_radix_select_keys([&](int64_t t) -> uint64_t { return ap_make_key(fmaf(wf, comp[2][t], ws * comp[1][t]), (int32_t)t, 1u); },
+                                                     cnt, cnt, K, hist, sel, misc, &pre);
+            for (int32_t i = threadIdx.x; i < got; i += blockDim.x) {
+                const int32_t t = ap_key_id(sel[i]);
+                need[i] = (uint16_t)t;
+            }
+            n_first = got;
+            __syncthreads();
+            dense_rows(0, got, got);
+            __syncthreads();
+            if (got == K) T = ap_ord2f(s_T);
+        }
+        if (threadIdx.x == 0) s_need = n_first;
+        __syncthreads();
+        if (!later) {   // the K scored already are marked by a bit of their candidate word
+            for (int32_t i = threadIdx.x; i < n_first; i += blockDim.x) cand[need[i]] |= (int32_t)0x80000000;
+            __syncthreads();
+        }
+        for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
+            if (cand[t] < 0) { cand[t] &= 0x7fffffff; continue; }
+            float bd, bf;
+            bound(t, bd, bf);
+            if (!(bf < T) || !(bd < dP)) need[atomicAdd(&s_need, 1)] = (uint16_t)t;
+            else comp[0][t] = -INFINITY;
+        }
+        __syncthreads();
+        dense_rows(n_first, ap_uniform_i32(s_need), 0);
+    }
+    __syncthreads();
+    // top-K under the fused score: the keys (all different: a key carries its id) sorted in LDS.  What was left out above
+    // ranks after K of them.
+    const int32_t nk = ap_uniform_i32(s_nk);
+    int32_t n2 = 64;
+    while (n2 < nk) n2 <<= 1;   // uniform; nk <= K + S*S <= AP_MAXC <= 2048
+    for (int32_t t = nk + threadIdx.x; t < n2; t += blockDim.x) keys[t] = 0ull;
+    ap_bitonic_desc(keys, n2);   // begins and ends with a barrier
+    for (int32_t t = threadIdx.x; t < K; t += blockDim.x) {
+        const uint64_t key = t < nk ? keys[t] : 0ull;
+        out_ids[x * K + t] = t < nk ? ap_key_id(key) : -1;
+        out_sc[x * K + t] = t < nk ? ap_key_score(key) : -INFINITY;
+    }
+    if (hint.known_out && wave == NW - 1) {
+        const uint64_t m = __ballot(lane < sl && lane < nk && (keys[lane < n2 ? lane : 0] & 1ull));
+        if (lane == 0) hint.known_out[x] = (uint32_t)m;
+    }
+    // per-path lists: the best P by each single similarity among this round's candidates and the previous list.  One wave
+    // per path, on its own: every lane keeps its share of the keys in registers and the P best are drawn one after the
+    // other by wave-wide maxima (no block-wide pass, no barrier).
+    if (wave < 3) {
+        const int p = wave;
+        const int32_t nold = (int32_t)__popcll(__ballot(lane < 32 && oldk[p][lane & 31] != 0ull));
+        auto cand_key = [&](int32_t t) { return comp[p][t] == -INFINITY ? 0ull : ap_make_key(comp[p][t], cand[t] & ~AP_RF_TOP, 1u); };
+        uint64_t prev = ~0ull;
+        auto put = [&](int32_t r, uint64_t best) {
             for (int o = 32; o > 0; o >>= 1) {
                 const uint64_t other = __shfl_xor(best, o, 64);
                 best = other > best ? other : best;
@@ -807,8 +992,84 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
                 out_sp_sc[((int64_t)p * nn + x) * P + r] = best ? ap_key_score(best) : -INFINITY;
             }
             prev = best;   // 0 once exhausted: nothing ranks after it
+        };
+        if (fast && nold == P) {
+            // a full list: what can enter is what beats its last entry, usually few enough for one key a lane
+            const uint64_t last = oldk[p][P - 1];
+            int32_t nb = 0;
+            for (int32_t t0 = 0; t0 < cnt; t0 += 64) {
+                const uint64_t key = t0 + lane < cnt ? cand_key(t0 + lane) : 0ull;
+                const uint64_t m = __ballot(key > last);
+                const int32_t at = nb + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+                if (key > last && at < 64) better[p][at] = key;
+                nb += (int32_t)__popcll(m);
+            }
+            ap_wave_sync();
+            if (nb + nold <= 64) {
+                const uint64_t key = lane < nb ? better[p][lane] : lane < nb + nold ? oldk[p][lane - nb] : 0ull;
+                for (int32_t r = 0; r < P; r++) put(r, key < prev ? key : 0ull);
+                return;
+            }
+        }
+        constexpr int PER = (AP_MAXC + 32 + 63) / 64;
+        uint64_t mine[PER];
+#pragma unroll
+        for (int j = 0; j < PER; j++) {
+            const int32_t t = j * 64 + lane;
+            mine[j] = t < cnt ? cand_key(t) : (t < cnt + nold ? oldk[p][t - cnt] : 0ull);
+        }
+        for (int32_t r = 0; r < P; r++) {
+            uint64_t best = 0;
+#pragma unroll
+            for (int j = 0; j < PER; j++)
+                if (mine[j] < prev && mine[j] > best) best = mine[j];
+            put(r, best);
         }
     }
+}
+
+// One round for the nn listed nodes; see k_refine for what the hints are.
+int ap_refine_round(const ap_index *ix, int32_t K, int32_t S, int32_t P, const int32_t *knn_ids, const int32_t *sp_ids, const float *sp_sc,
+                    const int32_t *node_ids, int64_t nn, int32_t *out_ids, float *out_sc, int32_t *out_sp_ids, float *out_sp_sc,
+                    const ApRefineHints &hint, hipStream_t st) {
+    const float *w = ix->params.build_w;
+    const int64_t slice = AP_MAX_LAUNCH_THREADS / 512;   // a launch holds fewer than 2^32 threads
+    for (int64_t x0 = 0; x0 < nn; x0 += slice) {
+        const int64_t cn = std::min<int64_t>(slice, nn - x0);
+        AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim,
+                          hipLaunchKernelGGL((k_refine<DT, NV>), dim3((unsigned)cn), dim3(512), 0, st, ix->docs, ix->rec, ix->meta, w[0], w[1],
+                                             w[2], K, S, P, knn_ids, sp_ids, sp_sc, node_ids, nn, x0, out_ids, out_sc, out_sp_ids, out_sp_sc,
+                                             ix->counters, hint));
+        AP_CHECK_HIP(hipGetLastError());
+    }
+    return AP_OK;
+}
+
+// The refinement rounds of a construction: from the exact dense seed lists (ids[0], sc[0]) of all n = ix->docs.n documents
+// and empty per-path lists (spi[0], sps[0]).  Returns in *cur which of the two buffers holds the result.
+int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
+                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st) {
+    const int64_t n = ix->docs.n;
+    *cur = 0;
+    if (rounds <= 0) return AP_OK;
+    float *tau = nullptr;
+    uint32_t *known[2] = {nullptr, nullptr};
+    int rc = ap_dev_alloc(&tau, (size_t)n);
+    for (int i = 0; i < 2 && rc == AP_OK; i++) rc = ap_dev_alloc(&known[i], (size_t)n);
+    if (rc == AP_OK) {
+        hipLaunchKernelGGL(k_take_tau, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc[0], n, K, 0u, tau);
+        if (hipGetLastError() != hipSuccess) { ap_set_error("refinement failed to start"); rc = AP_EHIP; }
+    }
+    for (int32_t t = 0; t < rounds && rc == AP_OK; t++) {
+        const int c = *cur;
+        const ApRefineHints hint = t == 0 ? ApRefineHints{tau, sc[c], nullptr, nullptr, known[0]}
+                                          : ApRefineHints{tau, nullptr, sc[c], known[(t - 1) & 1], known[t & 1]};
+        rc = ap_refine_round(ix, K, S, P, ids[c], spi[c], sps[c], nullptr, n, ids[1 - c], sc[1 - c], spi[1 - c], sps[1 - c], hint, st);
+        *cur = 1 - c;
+    }
+    void *ptrs[] = {tau, known[0], known[1]};
+    for (void *p : ptrs) if (p) (void)hipFree(p);   // waits for the rounds
+    return rc;
 }
 
 extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t P, const int32_t *knn_ids,
@@ -818,17 +1079,8 @@ extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t
     AP_REQUIRE(K >= 1 && K <= 256 && S >= 0 && S <= 32 && P >= 1 && P <= 32, "need 1<=K<=256, 0<=S<=32, 1<=P<=32");
     if (!node_ids) nn = ix->docs.n;
     if (nn <= 0) return AP_OK;
-    const float *w = ix->params.build_w;
-    const int64_t slice = AP_MAX_LAUNCH_THREADS / 512;   // a launch holds fewer than 2^32 threads
-    for (int64_t x0 = 0; x0 < nn; x0 += slice) {
-        const int64_t cn = std::min<int64_t>(slice, nn - x0);
-        AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim,
-                          hipLaunchKernelGGL((k_refine<DT, NV>), dim3((unsigned)cn), dim3(512), 0, (hipStream_t)stream, ix->docs,
-                                             ix->rec, ix->meta, w[0], w[1], w[2], K, S, P, knn_ids, sp_ids, sp_sc, node_ids, nn, x0, out_ids,
-                                             out_sc, out_sp_ids, out_sp_sc, ix->counters));
-        AP_CHECK_HIP(hipGetLastError());
-    }
-    return AP_OK;
+    return ap_refine_round(ix, K, S, P, knn_ids, sp_ids, sp_sc, node_ids, nn, out_ids, out_sc, out_sp_ids, out_sp_sc,
+                           ApRefineHints{nullptr, nullptr, nullptr, nullptr, nullptr}, (hipStream_t)stream);
 }
 
 // =================================================================== S4: neighbourhood similarities
@@ -1396,11 +1648,7 @@ static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
     AP_TRY(ap_fill_u32(b.spi[0], (size_t)3 * n * P, 0xffffffffu, st));          // id -1
     AP_TRY(ap_fill_u32(b.sps[0], (size_t)3 * n * P, 0xff800000u, st));          // -inf
     int cur = 0;
-    for (int32_t t = 0; t < p.nd_rounds; t++) {
-        AP_TRY(ap_stage_refine(ix, K, p.nd_sample, P, b.knn[cur], b.spi[cur], b.sps[cur], nullptr, n, b.knn[1 - cur],
-                               b.knn_sc[1 - cur], b.spi[1 - cur], b.sps[1 - cur], st));
-        cur = 1 - cur;
-    }
+    AP_TRY(ap_refine_rounds(ix, p.nd_rounds, K, p.nd_sample, P, b.knn, b.knn_sc, b.spi, b.sps, &cur, st));
     if (p.nd_rounds == 0) AP_TRY(ap_rescore_lists(ix, n, K, b.knn[cur], b.knn_sc[cur], st));
     AP_CHECK_HIP(mark(3));
     AP_TRY(ap_prune_impl(ix, K, R, b.knn[cur], b.knn_sc[cur], nullptr, n, nullptr, nullptr, b.sorted, b.se, ix->kw, ix->kw_count,

@@ -166,6 +166,8 @@ int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_i
                   int32_t *flag, hipStream_t st);
 int ap_assemble_impl(const ap_index *ix, int32_t R, int32_t K, int32_t P, const int32_t *se, const int32_t *sorted_ids,
                      const int32_t *sp_ids, int32_t *out_graph, hipStream_t st);
+int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
+                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st);
 int ap_rescore_lists(const ap_index *ix, int64_t nn, int32_t K, const int32_t *knn, float *sc, hipStream_t st);
 // The visited-set workspace of a search call: `slab` queries are in flight at a time, each with a bitset of one bit
 // per document.  `counts` (nq x 3) and the two events belong to the index's measurement surface and may be absent.

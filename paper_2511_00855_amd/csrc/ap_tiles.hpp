@@ -407,15 +407,24 @@ __device__ __forceinline__ int32_t ap_radix_select_keys(KeyOf key_of, int64_t n,
                 if (key != 0 && (key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
             }
             __syncthreads();
-            if (threadIdx.x == 0) {
-                int32_t cum = 0, b = 255;
-                for (; b > 0; b--) {
-                    if (cum + (int32_t)hist[b] >= krem) break;
-                    cum += (int32_t)hist[b];
+            if (threadIdx.x < 64) {   // one wave finds the bucket of the krem-th key: four buckets a lane, the highest in lane 0
+                const int32_t b0 = 252 - 4 * (int32_t)threadIdx.x;
+                uint32_t h[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) h[j] = hist[b0 + j];
+                const uint32_t own = h[0] + h[1] + h[2] + h[3];
+                uint32_t upto = own;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t up = __shfl_up(upto, o, 64);
+                    if ((int)threadIdx.x >= o) upto += up;
                 }
-                s_misc[0] = krem - cum;
-                s_misc[1] = ((int32_t)hist[b] == krem - cum) ? 1 : 0;
-                *s_prefix = prefix | ((uint64_t)b << shift);
+                if ((int64_t)(upto - own) < krem && (int64_t)upto >= krem) {   // exactly one lane
+                    int32_t cum = (int32_t)(upto - own), b = 3;
+                    while (b > 0 && cum + (int32_t)h[b] < krem) { cum += (int32_t)h[b]; b--; }
+                    s_misc[0] = krem - cum;
+                    s_misc[1] = ((int32_t)h[b] == krem - cum) ? 1 : 0;
+                    *s_prefix = prefix | ((uint64_t)(uint32_t)(b0 + b) << shift);
+                }
             }
             __syncthreads();
             krem = s_misc[0];
