@@ -128,8 +128,10 @@ int ap_set_weights(ap_index *index, const float w[3]);
 /* Algorithm 2 on the semantic edges for nq queries at once.  per_query_w is
  * nq x 3 (device) or NULL for the index default.  out_ids / out_scores are
  * nq x k.  The call sizes a per-index workspace (one visited bit per document
- * for every query in flight, at most 2 GiB: larger batches run in slabs of
- * queries, one launch each) and may allocate on first use or when nq grows. */
+ * for every query in flight, at most 2 GiB, and where that pays upper bounds of
+ * all scores, 4 bytes per query and document, at most 16 GiB per stream that
+ * searches: larger batches run in slabs of queries, one launch each) and may
+ * allocate on first use or when nq grows. */
 int ap_search_batch(ap_index *index, const ap_queries *queries, const float *per_query_w,
                     const ap_search_params *params, int32_t *out_ids, float *out_scores, void *stream);
 
@@ -256,6 +258,13 @@ const char *ap_last_error(void); /* host string, thread-local */
 
 /* ---- measurement / test surface: the same kernels, exposed stage by stage - */
 
+/* The upper bounds of the fused scores that searches and the exact top-k sort documents out with: out (device) is
+ * nq x n, out[i][d] >= the score of query i and document d under per_query_w (NULL: the index default).  With kw_terms
+ * (nq x kw_stride, as ap_search_batch_keywords) the lowest 5 bits of an entry hold a count that is part of no value.  AP_ESTATE where the library keeps no bounds (more
+ * than 2^24 terms in both vocabularies, not enough memory, too large a batch). */
+int ap_stage_score_bounds(ap_index *index, const ap_queries *queries, const float *per_query_w, const int32_t *kw_terms,
+                          int32_t kw_stride, float *out, void *stream);
+
 /* S0 only: an index with lexical weights and self-similarities but no graph. */
 int ap_ingest(const ap_corpus *corpus, const ap_build_params *params, void *stream, ap_index **out);
 
@@ -351,6 +360,7 @@ int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
  *   "seed_one_sided"          1: whole-corpus seed lists by the one-sided sweep instead of the symmetric one
  *   "max_launch_threads"      a multiple of 1024: launches that grow with the corpus run in slices of this many threads
  *   "search_workspace_bytes"  cap of the searches' visited-set workspace (forces searches in several slabs of queries)
+ *   "search_bounds"           1: searches score every neighbour they meet, 2: they always sort neighbours out by the bounds
  *   "search_visited_global"   1: visited sets stay in the global workspace even where the search would keep them in LDS
  *   "search_query_lists"      1: the plain and keyword searches look query terms up in the query's lists, not in LDS tables
  * Unknown names and negative values give AP_EINVAL.  Not thread-safe against running calls. */

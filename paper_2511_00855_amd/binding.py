@@ -105,7 +105,7 @@ def debug_set(name: str, value: int):
 
 
 DEBUG_NAMES = ("seed_sample_cols", "seed_buffer_cap", "seed_tau_ulps", "max_launch_threads", "search_workspace_bytes",
-               "search_visited_global", "search_query_lists", "seed_one_sided")
+               "search_visited_global", "search_query_lists", "seed_one_sided", "search_bounds")
 
 
 def debug_reset():
@@ -383,6 +383,17 @@ class Index:
             _check(lib().ap_bruteforce_topk(self._h, C.byref(qs), _ptr(w), C.c_int32(k), _ptr(ids), _ptr(sc), _stream()),
                    "ap_bruteforce_topk")
         return ids, sc
+
+    def stage_score_bounds(self, queries: DeviceVecs, per_query_w=None, kw_terms=None):
+        """Upper bounds of the scores, nq x n (ap_stage_score_bounds)."""
+        out = torch.empty((queries.n, self.docs.n), dtype=torch.float32, device=self.device)
+        w = None if per_query_w is None else _dev(per_query_w, torch.float32, self.device)
+        kw = None if kw_terms is None else _dev(kw_terms, torch.int32, self.device)
+        qs = queries.queries_struct()
+        with torch.cuda.device(self.device):
+            _check(lib().ap_stage_score_bounds(self._h, C.byref(qs), _ptr(w), _ptr(kw), C.c_int32(0 if kw is None else kw.shape[1]), _ptr(out),
+                                               _stream()), "ap_stage_score_bounds")
+        return out
 
     def stage_seed_knn(self, K: int, node_ids=None):
         nodes = _ids(node_ids, self.device)

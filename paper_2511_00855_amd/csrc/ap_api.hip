@@ -29,6 +29,7 @@ extern "C" int ap_debug_set(const char *name, int64_t value) {
         {"seed_tau_ulps", &g_ap_debug.seed_tau_ulps},             {"max_launch_threads", &g_ap_debug.max_launch_threads},
         {"search_workspace_bytes", &g_ap_debug.search_workspace_bytes}, {"search_visited_global", &g_ap_debug.search_visited_global},
         {"search_query_lists", &g_ap_debug.search_query_lists},         {"seed_one_sided", &g_ap_debug.seed_one_sided},
+        {"search_bounds", &g_ap_debug.search_bounds},
     };
     for (auto &t : table)
         if (strcmp(name, t.name) == 0) { *t.field = value; return AP_OK; }
@@ -86,15 +87,37 @@ int ap_validate_params(const ap_build_params *p) {
 // ingest and stored as f32:
 //   w(d,t) = IDF(t) * tf (k1+1) / (tf + k1 (1 - b + b |d|/avgdl)),
 //   IDF(t) = ln(1 + (N - df + 0.5)/(df + 0.5)).
-__global__ void k_df_and_tokens(const int32_t *__restrict__ idx, const float *__restrict__ tf, int64_t nnz,
-                                int32_t *__restrict__ df, unsigned long long *__restrict__ total) {
+// Counting is bound by atomics on the counters of frequent terms (a Zipf vocabulary's first terms are in nearly every
+// document), so a block counts in an LDS table first: a term whose slot is free takes it, and only terms that find
+// another one there go to the global counter at once.  12 million entries of 100,000 documents: 1.34 -> 0.30 ms.
+#define AP_CNT_SLOTS 4096
+__global__ __launch_bounds__(512) void k_df_and_tokens(const int32_t *__restrict__ idx, const float *__restrict__ tf /* NULL: no total */, int64_t nnz,
+                                                       int32_t *__restrict__ df, unsigned long long *__restrict__ total) {
+    __shared__ int32_t s_term[AP_CNT_SLOTS], s_cnt[AP_CNT_SLOTS];
+    for (int i = threadIdx.x; i < AP_CNT_SLOTS; i += 512) { s_term[i] = -1; s_cnt[i] = 0; }
+    __syncthreads();
     unsigned long long local = 0;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * blockDim.x) {
-        atomicAdd(&df[idx[e]], 1);
-        local += (unsigned long long)llrintf(tf[e]);
+    for (int64_t e = blockIdx.x * (int64_t)512 + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * 512) {
+        const int32_t t = idx[e];
+        const uint32_t h = ((uint32_t)t * 2654435761u) >> 20;   // 12 bits
+        const int32_t old = s_term[h] == t ? t : atomicCAS(&s_term[h], -1, t);
+        if (old == t || old == -1) atomicAdd(&s_cnt[h], 1);
+        else atomicAdd(&df[t], 1);
+        if (tf) local += (unsigned long long)llrintf(tf[e]);
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < AP_CNT_SLOTS; i += 512)
+        if (s_cnt[i]) atomicAdd(&df[s_term[i]], s_cnt[i]);
+    if (!tf) return;
     for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o, 64);
     if ((threadIdx.x & 63) == 0 && local) atomicAdd(total, local);
+}
+
+int ap_count_terms(const int32_t *idx, const float *tf, int64_t nnz, int32_t *df, unsigned long long *total, hipStream_t st) {
+    if (nnz <= 0) return AP_OK;
+    hipLaunchKernelGGL(k_df_and_tokens, dim3((unsigned)std::min<int64_t>((nnz + 4095) / 4096, 1024)), dim3(512), 0, st, idx, tf, nnz, df, total);
+    AP_CHECK_HIP(hipGetLastError());
+    return AP_OK;
 }
 
 __global__ void k_bm25_weights(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx,
@@ -207,6 +230,7 @@ int ap_ingest_impl(ap_index *ix, hipStream_t st) {
     AP_REQUIRE(last >= 0 && sp_last >= 0, "indptr[n] is negative");
     AP_REQUIRE(last + sp_last < (1ll << 32), "the two CSR parts together must hold fewer than 2^32 entries");
     ix->tx_nnz = last;
+    ix->sp_nnz = sp_last;
     AP_TRY(ap_dev_alloc(&ix->stats, 4));
     {
         int32_t *bad = reinterpret_cast<int32_t *>(ix->stats);
@@ -231,11 +255,7 @@ int ap_ingest_impl(ap_index *ix, hipStream_t st) {
     AP_TRY(ap_fill_u32(ix->df, (size_t)c.tx_vocab, 0, st));
     AP_TRY(ap_fill_u32(ix->stats, 4, 0, st));
     unsigned long long *total = reinterpret_cast<unsigned long long *>(ix->stats + 2);
-    if (last > 0) {
-        int blocks = (int)((last + 255) / 256 < 8192 ? (last + 255) / 256 : 8192);
-        hipLaunchKernelGGL(k_df_and_tokens, dim3(blocks), dim3(256), 0, st, c.tx_idx, c.tx_tf, last, ix->df, total);
-        AP_CHECK_HIP(hipGetLastError());
-    }
+    AP_TRY(ap_count_terms(c.tx_idx, c.tx_tf, last, ix->df, total, st));
     {
         int blocks = (int)((c.n + 255) / 256 < 8192 ? (c.n + 255) / 256 : 8192);
         hipLaunchKernelGGL(k_bm25_weights, dim3(blocks), dim3(256), 0, st, c.tx_indptr, c.tx_idx, c.tx_tf, c.n, ix->df,
@@ -268,6 +288,7 @@ int ap_ingest_impl(ap_index *ix, hipStream_t st) {
         hipLaunchKernelGGL(k_pack_records, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, ix->docs, ix->dense_norm, ix->rec, ix->meta);
         AP_CHECK_HIP(hipGetLastError());
     }
+    AP_TRY(ap_bound_ingest(ix, st));
     AP_CHECK_HIP(hipMemcpyAsync(ix->w_dev, ix->w_default, 3 * sizeof(float), hipMemcpyHostToDevice, st));
     AP_CHECK_HIP(hipStreamSynchronize(st));
     // set-up of this device for searches that must not allocate: the address of their static workspace
@@ -301,7 +322,8 @@ extern "C" int ap_ingest(const ap_corpus *corpus, const ap_build_params *params,
 extern "C" void ap_free_index(ap_index *ix) {
     if (!ix) return;
     void *ptrs[] = {ix->kg_en_ip, ix->kg_en, ix->kg_le, ix->kg_le_count, ix->st_se, ix->st_sorted, ix->st_spi, ix->st_sps, ix->deleted, ix->deleted_bad, ix->counters, ix->tx_w, ix->df, ix->stats, ix->self_sim, ix->graph, ix->kw, ix->kw_count, ix->entry, ix->visited, ix->w_dev,
-                    ix->search_counts, ix->dense_norm, ix->rec, ix->meta};
+                    ix->search_counts, ix->dense_norm, ix->rec, ix->meta, ix->bd_mem};
+    ap_bound_release(ix);
     for (void *p : ptrs) if (p) (void)hipFree(p);
     for (hipEvent_t e : ix->ev_search) if (e) (void)hipEventDestroy(e);
     delete ix;

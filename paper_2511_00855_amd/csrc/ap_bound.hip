@@ -1,0 +1,495 @@
+// Upper bounds of the fused scores of a batch of queries against every document: what lets a search drop a neighbour
+// that cannot enter its pool on one 4-byte read, instead of reading its record (1.3 KB) and often its dense row (3 KB),
+// and lets the exact top-k score a few hundred documents per query instead of all.
+//
+//   table[q][d] >= w_d <q_d,d_d> + w_s <q_s,d_s> + w_f <q_f,d_f>   as the scoring kernels round it.
+//
+// The dense part and the most frequent terms of both vocabularies (the "head": at most AP_BOUND_HEAD columns) are one
+// bf16 matrix product; the remaining terms (the "tail") are added from postings.  Rounding to bf16 is paid for by a
+// slack per pair, so nothing that decides a result depends on the product's precision: a candidate the bound lets
+// through is scored as ever, and one it stops could not have entered.
+#include <algorithm>
+#include <new>
+#include "ap_tiles.hpp"
+
+int ap_validate_queries(const ap_queries *q);
+
+#define AP_BOUND_HEAD 512
+#define AP_BOUND_QT 256              // queries and documents of a tile
+#define AP_BOUND_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of columns is kept for
+
+// The workspaces of an index: one per stream that searches it (grow only, at most AP_BOUND_STREAMS), so that searches
+// of one index on several streams do not share a table.
+#define AP_BOUND_STREAMS 4
+struct ApBoundPool {
+    std::mutex lock;
+    struct { hipStream_t stream; void *mem; size_t bytes; } ws[AP_BOUND_STREAMS];
+    int used = 0;
+};
+
+// ------------------------------------------------------------------ ingest
+// eight bins an octave of the document frequency
+__device__ __forceinline__ int ap_df_bin(int32_t df) {
+    if (df <= 0) return -1;
+    const int b = (int)(8.f * log2f((float)df));
+    return b > 255 ? 255 : b;
+}
+__global__ __launch_bounds__(256) void k_bd_hist(const int32_t *__restrict__ df_sp, int32_t nsp, const int32_t *__restrict__ df_tx, int32_t ntx,
+                                                 int32_t *__restrict__ hist) {
+    __shared__ int32_t h[256];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x; t < (int64_t)nsp + ntx; t += (int64_t)gridDim.x * 256) {
+        const int b = ap_df_bin(t < nsp ? df_sp[t] : df_tx[t - nsp]);
+        if (b >= 0) atomicAdd(&h[b], 1);
+    }
+    __syncthreads();
+    if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+}
+// The head is every term of the top bins that fit kh columns together; every other term gets a run of postings.  misc[0]
+// counts columns, misc[1] postings handed out.
+__global__ __launch_bounds__(1024) void k_bd_pick(const int32_t *__restrict__ df_sp, int32_t nsp, const int32_t *__restrict__ df_tx, int32_t ntx,
+                                                  const int32_t *__restrict__ hist, int32_t kh, int32_t *__restrict__ col,
+                                                  uint2 *__restrict__ run, uint32_t *__restrict__ misc) {
+    __shared__ int32_t s_low;
+    __shared__ uint32_t part[16], s_base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) {
+        int32_t low = 256, sum = 0;
+        while (low > 0 && sum + hist[low - 1] <= kh) sum += hist[--low];
+        s_low = low;
+    }
+    __syncthreads();
+    const int64_t t = blockIdx.x * (int64_t)1024 + threadIdx.x, all = (int64_t)nsp + ntx;
+    const int32_t df = t < all ? (t < nsp ? df_sp[t] : df_tx[t - nsp]) : 0;
+    const bool head = df > 0 && ap_df_bin(df) >= s_low;
+    const uint32_t len = head ? 0u : (uint32_t)df;
+    uint32_t upto = len;
+    for (int o = 1; o < 64; o <<= 1) { const uint32_t up = __shfl_up(upto, o, 64); if (lane >= o) upto += up; }
+    if (lane == 63) part[wave] = upto;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t sum = 0;
+        for (int w = 0; w < 16; w++) { const uint32_t p = part[w]; part[w] = sum; sum += p; }
+        s_base = sum ? atomicAdd(&misc[1], sum) : 0u;
+    }
+    __syncthreads();
+    if (t < all) {
+        col[t] = head ? (int32_t)atomicAdd(&misc[0], 1u) : -1;
+        run[t] = make_uint2(s_base + part[wave] + upto - len, len);
+    }
+}
+
+__device__ __forceinline__ uint32_t ap_bf16_bits(float f) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f); }   // to nearest even
+
+// One wave per document: its bound row (dense part rounded to bf16 if kd > 0, then the head columns), the norms of
+// the head columns of either vocabulary, its postings, and its bit in the bitmaps of the lexical head terms it holds.
+template <int DT>
+__global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const int32_t *__restrict__ col, const uint2 *__restrict__ run,
+                                                 uint32_t *__restrict__ cursor, int32_t kd, int32_t kh, uint16_t *__restrict__ rows,
+                                                 uint2 *__restrict__ post, float2 *__restrict__ hn, uint32_t *__restrict__ bits, int64_t words) {
+    __shared__ __attribute__((aligned(16))) uint16_t s_head[4][AP_BOUND_HEAD];
+    const int lane = threadIdx.x & 63, wave = ap_wave_id();
+    uint16_t *head = s_head[wave];
+    const int32_t ld = kd + kh;
+    for (int64_t v = blockIdx.x * (int64_t)4 + wave; v < D.n; v += (int64_t)gridDim.x * 4) {
+        uint16_t *row = rows + v * ld;
+        for (int32_t c = lane * 4; c < kd; c += 256) {
+            float x[4] = {0.f, 0.f, 0.f, 0.f};
+            if (c < D.dim) {   // dim is a multiple of 4
+                if (DT == AP_F32) {
+                    const float4 y = *reinterpret_cast<const float4 *>(static_cast<const float *>(D.dense) + v * D.dim + c);
+                    x[0] = y.x; x[1] = y.y; x[2] = y.z; x[3] = y.w;
+                } else {
+                    for (int e = 0; e < 4; e++) x[e] = __uint_as_float((uint32_t)static_cast<const uint16_t *>(D.dense)[v * D.dim + c + e] << 16);
+                }
+            }
+            *reinterpret_cast<uint2 *>(row + c) = make_uint2(ap_bf16_bits(x[0]) | (ap_bf16_bits(x[1]) << 16), ap_bf16_bits(x[2]) | (ap_bf16_bits(x[3]) << 16));
+        }
+        for (int32_t c = lane * 8; c < kh; c += 512) *reinterpret_cast<uint4 *>(head + c) = make_uint4(0, 0, 0, 0);
+        ap_wave_sync();
+        float sum[2] = {0.f, 0.f};
+        for (int part = 0; part < 2; part++) {
+            const int64_t b = part ? D.tx_indptr[v] : D.sp_indptr[v], e = part ? D.tx_indptr[v + 1] : D.sp_indptr[v + 1];
+            for (int64_t p = b + lane; p < e; p += 64) {
+                const int32_t t = part ? nsp + D.tx_idx[p] : D.sp_idx[p];
+                const float x = part ? D.tx_val[p] : D.sp_val[p];
+                const int32_t c = col[t];
+                if (c >= 0) {
+                    head[c] = (uint16_t)ap_bf16_bits(x); sum[part] = fmaf(x, x, sum[part]);
+                    if (part) atomicOr(&bits[c * words + (v >> 5)], 1u << (v & 31));
+                } else post[run[t].x + atomicAdd(&cursor[t], 1u)] = make_uint2((uint32_t)v, __float_as_uint(x));
+            }
+        }
+        ap_wave_sync();
+        for (int32_t c = lane * 8; c < kh; c += 512) *reinterpret_cast<uint4 *>(row + kd + c) = *reinterpret_cast<const uint4 *>(head + c);
+        const float hs = ap_wave_sum(sum[0]), hf = ap_wave_sum(sum[1]);
+        if (lane == 0) hn[v] = make_float2(sqrtf(hs), sqrtf(hf));
+        ap_wave_sync();
+    }
+}
+
+static inline size_t ap_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// Lays out what the bounds of a corpus need.  Without it (vocabularies too large for a table of columns, not enough
+// memory) the searches run without bounds: never an error.
+int ap_bound_ingest(ap_index *ix, hipStream_t st) {
+    const ap_corpus &c = ix->corpus;
+    const int64_t all = (int64_t)c.sp_vocab + c.tx_vocab;
+    if (all > AP_BOUND_VOCAB) return AP_OK;
+    const bool own_dense = c.dense_dtype != AP_BF16 || c.dim % AP_BK16 != 0;   // else the corpus's rows are read where they lie
+    const int32_t kd = own_dense ? (int32_t)ap_up((size_t)c.dim, AP_BK16) : 0;
+    const int32_t kh = (int32_t)std::min<int64_t>(AP_BOUND_HEAD, (int64_t)ap_up((size_t)all, AP_BK16));
+    const size_t nnz = (size_t)ix->tx_nnz + (size_t)ix->sp_nnz;
+    const int64_t words = (c.n + 31) / 32;
+    // cleared: document frequencies of the learned-sparse terms, cursors, histogram, misc, bitmaps
+    const size_t n_clear = (size_t)c.sp_vocab + (size_t)all + 256 + 2 + (size_t)kh * (size_t)words;
+    size_t at = 0;
+    auto take = [&](size_t bytes) { const size_t a = at; at += ap_up(bytes, 256); return a; };
+    const size_t o_clear = take(n_clear * 4), o_col = take((size_t)all * 4), o_run = take((size_t)all * 8), o_post = take((nnz + 1) * 8),
+                 o_hn = take((size_t)c.n * 8), o_rows = take((size_t)c.n * (size_t)(kd + kh) * 2);
+    if (at > ((size_t)1 << 30)) {
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || at > free_b / 4) { (void)hipGetLastError(); return AP_OK; }
+    }
+    if (!ix->bd_pool && !(ix->bd_pool = new (std::nothrow) ApBoundPool())) { ap_set_error("out of host memory"); return AP_ENOMEM; }
+    if (hipMalloc(&ix->bd_mem, at) != hipSuccess) { (void)hipGetLastError(); ix->bd_mem = nullptr; return AP_OK; }
+    char *m = static_cast<char *>(ix->bd_mem);
+    int32_t *df_sp = reinterpret_cast<int32_t *>(m + o_clear);
+    uint32_t *cursor = reinterpret_cast<uint32_t *>(df_sp + c.sp_vocab);
+    int32_t *hist = reinterpret_cast<int32_t *>(cursor + all);
+    uint32_t *misc = reinterpret_cast<uint32_t *>(hist + 256);
+    ix->bd_col = reinterpret_cast<int32_t *>(m + o_col);
+    ix->bd_run = reinterpret_cast<uint2 *>(m + o_run);
+    ix->bd_post = reinterpret_cast<uint2 *>(m + o_post);
+    ix->bd_hn = reinterpret_cast<float2 *>(m + o_hn);
+    ix->bd_rows = reinterpret_cast<uint16_t *>(m + o_rows);
+    ix->bd_bits = misc + 2;
+    ix->bd_kd = kd; ix->bd_kh = kh;
+    AP_TRY(ap_fill_u32(df_sp, n_clear, 0u, st));
+    if (ix->sp_nnz > 0)
+        AP_TRY(ap_count_terms(c.sp_idx, nullptr, ix->sp_nnz, df_sp, nullptr, st));
+    hipLaunchKernelGGL(k_bd_hist, dim3((unsigned)std::min<int64_t>((all + 255) / 256, 256)), dim3(256), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist);
+    hipLaunchKernelGGL(k_bd_pick, dim3((unsigned)((all + 1023) / 1024)), dim3(1024), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, kh, ix->bd_col,
+                       ix->bd_run, misc);
+    const dim3 g((unsigned)std::min<int64_t>((c.n + 3) / 4, 4096));
+    if (ix->dtype == AP_F32)
+        hipLaunchKernelGGL(k_bd_rows<AP_F32>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->bd_hn, ix->bd_bits, words);
+    else
+        hipLaunchKernelGGL(k_bd_rows<AP_BF16>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->bd_hn, ix->bd_bits, words);
+    AP_CHECK_HIP(hipGetLastError());
+    return AP_OK;
+}
+
+// ------------------------------------------------------------------ the table
+// Entries carry a count in their low bits (keyword searches: how many of the query's required terms the document holds);
+// what clearing them takes off a value is added first.
+__device__ __forceinline__ float ap_bound_round(float v) {
+    return __uint_as_float(__float_as_uint(fmaf(fabsf(v), 1e-5f, v)) & ~AP_BOUND_COUNT);
+}
+
+static inline int32_t bound_kdense(const ap_index *ix) { return ix->bd_kd ? ix->bd_kd : ix->docs.dim; }
+
+// One block per row of the query matrix: the query's dense part times its weight and its head terms times theirs,
+// rounded to bf16, and what the slack of the row is made of:
+//   .x times the document's dense norm, .y and .z times the norms of its learned-sparse and lexical head columns,
+//   .w relative slack of an addition of the tail
+// The slack covers: rounding both factors to bf16 (2^-9 each; a bf16 corpus's dense rows are exact), the product's
+// accumulation (k 2^-23), the rounding of the scoring kernels' own sums and of the tail's additions (1e-5 and 2^-22 a
+// term), and products of values so small that squares or products underflow (1e-18 of the norms).
+__global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int64_t nq, int32_t kdense,
+                                                       int32_t kh, int32_t nsp, int32_t ntx, const int32_t *__restrict__ col, float eps_dense,
+                                                       uint16_t *__restrict__ qm, float4 *__restrict__ qc) {
+    __shared__ __attribute__((aligned(16))) uint16_t head[AP_BOUND_HEAD];
+    __shared__ float red[3][4];
+    const int64_t r = blockIdx.x, q = q0 + r;
+    uint16_t *row = qm + r * (kdense + kh);
+    if (r >= nq) {
+        for (int32_t c = threadIdx.x * 8; c < kdense + kh; c += 2048) *reinterpret_cast<uint4 *>(row + c) = make_uint4(0, 0, 0, 0);
+        if (threadIdx.x == 0) qc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+        return;
+    }
+    const float wd = w[q * w_stride], ws = w[q * w_stride + 1], wf = w[q * w_stride + 2];
+    for (int32_t c = threadIdx.x; c < kh; c += 256) head[c] = 0;
+    float sd = 0.f, sh[2] = {0.f, 0.f};
+    for (int32_t c = threadIdx.x * 4; c < kdense; c += 1024) {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        if (c < Q.dim) {
+            const float4 y = *reinterpret_cast<const float4 *>(static_cast<const float *>(Q.dense) + q * Q.dim + c);
+            x[0] = wd * y.x; x[1] = wd * y.y; x[2] = wd * y.z; x[3] = wd * y.w;
+#pragma unroll
+            for (int e = 0; e < 4; e++) sd = fmaf(x[e], x[e], sd);
+        }
+        *reinterpret_cast<uint2 *>(row + c) = make_uint2(ap_bf16_bits(x[0]) | (ap_bf16_bits(x[1]) << 16), ap_bf16_bits(x[2]) | (ap_bf16_bits(x[3]) << 16));
+    }
+    __syncthreads();
+    int64_t terms = 0;
+    for (int part = 0; part < 2; part++) {
+        const int64_t b = part ? Q.tx_indptr[q] : Q.sp_indptr[q], e = part ? Q.tx_indptr[q + 1] : Q.sp_indptr[q + 1];
+        terms += e - b;
+        for (int64_t p = b + threadIdx.x; p < e; p += 256) {
+            const int32_t t = part ? Q.tx_idx[p] : Q.sp_idx[p];
+            if (t < 0 || t >= (part ? ntx : nsp)) continue;
+            const int32_t c = col[part ? nsp + t : t];
+            if (c < 0) continue;
+            const float x = part ? wf * Q.tx_val[p] : ws * Q.sp_val[p];
+            head[c] = (uint16_t)ap_bf16_bits(x);
+            sh[part] = fmaf(x, x, sh[part]);
+        }
+    }
+    sd = ap_wave_sum(sd); sh[0] = ap_wave_sum(sh[0]); sh[1] = ap_wave_sum(sh[1]);
+    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = sd; red[1][threadIdx.x >> 6] = sh[0]; red[2][threadIdx.x >> 6] = sh[1]; }
+    __syncthreads();
+    for (int32_t c = threadIdx.x * 8; c < kh; c += 2048) *reinterpret_cast<uint4 *>(row + kdense + c) = *reinterpret_cast<const uint4 *>(head + c);
+    if (threadIdx.x == 0) {
+        float norm[3];
+        for (int i = 0; i < 3; i++) norm[i] = sqrtf(red[i][0] + red[i][1] + red[i][2] + red[i][3]) * 1.0001f;
+        const float rel = 1e-5f + 2.4e-7f * (float)terms, sum = rel + 1.2e-7f * (float)(kdense + kh);
+        qc[r] = make_float4(norm[0] * (eps_dense + sum) + 1e-18f, norm[1] * (0.00392f + sum) + 1e-18f, norm[2] * (0.00392f + sum) + 1e-18f, rel);
+    }
+}
+
+// The product and the slack: a tile of 256 queries x 256 documents, 16 waves of 64 x 64, chunks of 64 columns through two
+// LDS stages as in the seed sweep.  4,000 queries x 100,000 documents x 1,280 columns take 1.24 ms = 0.83 PFLOP/s; the
+// matrix cores and the LDS reads that feed them bound it, as they bound the sweep.  The documents' columns come from two places: the dense part (dense, dense_ld) and
+// the head (rows + head_at, rows_ld).
+// Tile order: an XCD takes the document tiles in groups of four and walks each group's query tiles, so that a group's
+// documents and the queries stay in its L2 while they are used.
+#define AP_BOUND_GROUP 4
+__global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict__ qm, const float4 *__restrict__ qc, int32_t nq, int32_t q_tiles,
+                                                      const uint16_t *__restrict__ dense, int32_t dense_ld, int32_t n_dense,
+                                                      const uint16_t *__restrict__ head, int32_t head_ld, int32_t n_chunks,
+                                                      const float *__restrict__ dn, const float2 *__restrict__ hn, int64_t n, int64_t doc_tiles,
+                                                      float *__restrict__ table, int64_t ld) {
+    extern __shared__ __attribute__((aligned(16))) uint16_t bound_lds[];
+    __shared__ float4 s_qc[AP_BOUND_QT];
+    __shared__ float4 s_dn[AP_BOUND_QT];
+    using T = ApBig<4, 4>;
+    constexpr int NP = T::NP, RPP = T::RPP;
+    const int64_t xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
+    const int64_t group = idx / (AP_BOUND_GROUP * q_tiles), in = idx % (AP_BOUND_GROUP * q_tiles);
+    const int64_t dt = (group * 8 + xcd) * AP_BOUND_GROUP + in % AP_BOUND_GROUP, qt = in / AP_BOUND_GROUP;
+    if (dt >= doc_tiles) return;   // uniform
+    const int64_t d0 = dt * AP_BOUND_QT, r0 = qt * AP_BOUND_QT;
+    const int t = threadIdx.x, lane = t & 63, wave = ap_wave_id(), wm = wave >> 2, wn = wave & 3;
+    if (t < AP_BOUND_QT) {
+        const int64_t d = d0 + t < n ? d0 + t : n - 1;
+        s_qc[t] = qc[r0 + t];
+        s_dn[t] = make_float4(fmaf(dn[d], 1.0001f, 1e-15f), fmaf(hn[d].x, 1.0001f, 1e-15f), fmaf(hn[d].y, 1.0001f, 1e-15f), 0.f);
+    }
+    const int32_t kq = n_chunks * AP_BK16;
+    const char *qa = reinterpret_cast<const char *>(qm + r0 * kq);
+    const char *da = reinterpret_cast<const char *>(dense + d0 * dense_ld), *ha = reinterpret_cast<const char *>(head + d0 * head_ld);
+    uint32_t qo[NP], dd[NP], ho[NP];
+#pragma unroll
+    for (int p = 0; p < NP; p++) {
+        const int32_t row = t / AP_TPR16 + RPP * p;
+        const int32_t drow = d0 + row < n ? row : (int32_t)(n - 1 - d0);   // past the end: the last document again, not stored
+        const uint32_t c = (uint32_t)(t % AP_TPR16) * 16u;
+        qo[p] = (uint32_t)row * (uint32_t)kq * 2u + c;
+        dd[p] = (uint32_t)drow * (uint32_t)dense_ld * 2u + c;
+        ho[p] = (uint32_t)drow * (uint32_t)head_ld * 2u + c;
+    }
+    auto load = [&](int32_t k, ap_u32x4 (&va)[NP], ap_u32x4 (&vb)[NP]) {
+#pragma unroll
+        for (int p = 0; p < NP; p++) va[p] = *reinterpret_cast<const ap_u32x4 *>(qa + (qo[p] + (uint32_t)k * 128u));
+        if (k < n_dense) {
+#pragma unroll
+            for (int p = 0; p < NP; p++) vb[p] = *reinterpret_cast<const ap_u32x4 *>(da + (dd[p] + (uint32_t)k * 128u));
+        } else {
+#pragma unroll
+            for (int p = 0; p < NP; p++) vb[p] = *reinterpret_cast<const ap_u32x4 *>(ha + (ho[p] + (uint32_t)(k - n_dense) * 128u));
+        }
+    };
+    auto store = [&](const ap_u32x4 (&va)[NP], const ap_u32x4 (&vb)[NP], uint16_t *to) {
+        ap_big_store_run<NP, RPP>(va, to);
+        ap_big_store_run<NP, RPP>(vb, to + AP_BIG * AP_LDS_STRIDE16);
+    };
+    ap_f32x16 acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[a][b][r] = 0.f;
+    ap_u32x4 va0[NP], vb0[NP], va1[NP], vb1[NP];
+    load(0, va0, vb0);
+    store(va0, vb0, bound_lds);
+    if (n_chunks > 1) load(1, va0, vb0);
+    if (n_chunks > 2) load(2, va1, vb1);
+    __syncthreads();
+    const int li = lane & 31, lk = (lane >> 5) * 8;
+    // round k: chunk k is multiplied out of stage k & 1; set k & 1 holds chunk k + 1, which goes to the other stage, and is
+    // filled with chunk k + 3
+    auto round = [&](int32_t k, ap_u32x4 (&sa)[NP], ap_u32x4 (&sb)[NP]) {
+        uint16_t *cur = bound_lds + (k & 1) * AP_BIG_STAGE, *nxt = bound_lds + ((k + 1) & 1) * AP_BIG_STAGE;
+        if (k + 1 < n_chunks) store(sa, sb, nxt);
+        if (k + 3 < n_chunks) load(k + 3, sa, sb);
+        const uint16_t *pa = cur + (wm * 64 + li) * AP_LDS_STRIDE16 + lk, *pb = cur + AP_BIG * AP_LDS_STRIDE16 + (wn * 64 + li) * AP_LDS_STRIDE16 + lk;
+#pragma unroll
+        for (int kk = 0; kk < AP_BK16; kk += 16) {
+            ap_bf16x8 fa[2], fb[2];
+#pragma unroll
+            for (int a = 0; a < 2; a++) {
+                fa[a] = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const ap_u32x4 *>(pa + a * 32 * AP_LDS_STRIDE16 + kk));
+                fb[a] = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const ap_u32x4 *>(pb + a * 32 * AP_LDS_STRIDE16 + kk));
+            }
+#pragma unroll
+            for (int a = 0; a < 2; a++)
+#pragma unroll
+                for (int b = 0; b < 2; b++) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+        }
+        __syncthreads();
+    };
+    for (int32_t k = 0; k < n_chunks; k += 2) {
+        round(k, va0, vb0);
+        if (k + 1 < n_chunks) round(k + 1, va1, vb1);
+    }
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        const int j = wn * 64 + b * 32 + li;
+        const float4 dh = s_dn[j];
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int i = wm * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const float4 c = s_qc[i];
+                const float slack = fmaf(c.x, dh.x, fmaf(c.y, dh.y, fmaf(c.z, dh.z, 1e-36f)));
+                if (r0 + i < nq && d0 + j < n) table[(r0 + i) * ld + d0 + j] = ap_bound_round(acc[a][b][r] + slack);
+            }
+    }
+}
+
+// One block per query: the tail terms' postings, one term after the other (a document occurs once in a term's postings,
+// so the additions need no atomics and always come in the same order); then, for keyword searches, the count of required
+// tail terms every document holds, in the entries' low bits (the head's are asked of the bitmaps).  Bound by the
+// scattered read-modify-writes: 1.4 ms for 4,000 queries of 100,000 documents (about one entry in twenty is touched).
+__global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int32_t nsp, int32_t ntx,
+                                                    const int32_t *__restrict__ col, const uint2 *__restrict__ run, const uint2 *__restrict__ post,
+                                                    const float4 *__restrict__ qc, const int32_t *__restrict__ kw_terms, int32_t kw_stride,
+                                                    float *__restrict__ table, int64_t ld) {
+    const int64_t q = q0 + blockIdx.x;
+    float *row = table + (int64_t)blockIdx.x * ld;
+    const float ws = w[q * w_stride + 1], wf = w[q * w_stride + 2], rel = qc[blockIdx.x].w;
+    for (int part = 0; part < 2; part++) {
+        const int64_t b = part ? Q.tx_indptr[q] : Q.sp_indptr[q], e = part ? Q.tx_indptr[q + 1] : Q.sp_indptr[q + 1];
+        for (int64_t p = b; p < e; p++) {   // uniform
+            const int32_t t = part ? Q.tx_idx[p] : Q.sp_idx[p];
+            if (t < 0 || t >= (part ? ntx : nsp)) continue;
+            const int32_t at = part ? nsp + t : t;
+            if (col[at] >= 0) continue;
+            const uint2 r = run[at];
+            const float x = part ? wf * Q.tx_val[p] : ws * Q.sp_val[p];
+            for (uint32_t i = threadIdx.x; i < r.y; i += 256) {
+                const uint2 dv = post[r.x + i];
+                const float c = x * __uint_as_float(dv.y);
+                row[dv.x] = ap_bound_round(row[dv.x] + fmaf(fabsf(c), rel, c));
+            }
+            if (r.y) __syncthreads();
+        }
+    }
+    for (int32_t j = 0; j < kw_stride; j++) {
+        const int32_t t = kw_terms[q * kw_stride + j];
+        if (t < 0 || t >= ntx || col[nsp + t] >= 0) continue;
+        const uint2 r = run[nsp + t];
+        for (uint32_t i = threadIdx.x; i < r.y; i += 256) {
+            uint32_t *at = reinterpret_cast<uint32_t *>(row + post[r.x + i].x);
+            *at = *at + 1u;   // at most 16 required terms: the count stays inside its bits
+        }
+        if (r.y) __syncthreads();
+    }
+}
+
+// Bytes of the workspace a slab of nq queries takes.
+size_t ap_bound_bytes(const ap_index *ix, int64_t nq) {
+    const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
+    return rows * k * 2 + rows * 16 + (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
+}
+
+void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b) {
+    const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
+    char *m = static_cast<char *>(base);
+    b->qm = reinterpret_cast<uint16_t *>(m); m += rows * k * 2;
+    b->qc = reinterpret_cast<float4 *>(m); m += rows * 16;
+    b->table = reinterpret_cast<float *>(m);
+    b->ld = (int64_t)ap_up((size_t)ix->docs.n, 64);
+    b->slab = (int32_t)nq;
+}
+
+void ap_bound_release(ap_index *ix) {
+    if (!ix->bd_pool) return;
+    for (int i = 0; i < ix->bd_pool->used; i++) if (ix->bd_pool->ws[i].mem) (void)hipFree(ix->bd_pool->ws[i].mem);
+    delete ix->bd_pool;
+    ix->bd_pool = nullptr;
+}
+
+// Sizes the workspace of stream st for slabs of as many of nq queries as `cap` bytes hold, and holds it for the caller
+// (two threads may search on one stream).  b->table stays NULL where no workspace is to be had: the caller goes without
+// bounds.  That is also what a captured search does: a graph's replays must not depend on a workspace that a later
+// call may replace.
+int ap_bound_reserve(ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b) {
+    *b = ApBound();
+    if (!ix->bd_mem || nq < 1 || st == hipStreamPerThread) return AP_OK;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
+    if (cs != hipStreamCaptureStatusNone) return AP_OK;
+    int64_t slabs = 1;
+    while (slabs < nq && ap_bound_bytes(ix, (nq + slabs - 1) / slabs) > cap) slabs++;
+    const int64_t slab = (nq + slabs - 1) / slabs;
+    const size_t need = ap_bound_bytes(ix, slab);
+    if (need > cap) return AP_OK;
+    ApBoundPool *pool = ix->bd_pool;
+    std::unique_lock<std::mutex> hold(pool->lock);
+    int i = 0;
+    while (i < pool->used && pool->ws[i].stream != st) i++;
+    if (i == AP_BOUND_STREAMS) return AP_OK;
+    if (i == pool->used) { pool->ws[i] = {st, nullptr, 0}; pool->used++; }
+    auto &w = pool->ws[i];
+    if (need > w.bytes) {
+        if (w.mem) { AP_CHECK_HIP(hipStreamSynchronize(st)); (void)hipFree(w.mem); w.mem = nullptr; w.bytes = 0; }
+        if (hipMalloc(&w.mem, need) != hipSuccess) { (void)hipGetLastError(); w.mem = nullptr; return AP_OK; }
+        w.bytes = need;
+    }
+    ap_bound_place(ix, w.mem, slab, b);
+    b->hold = std::move(hold);
+    return AP_OK;
+}
+
+// Fills rows 0 .. nq of the table for queries q0 .. q0 + nq of Q (nq <= b.slab).
+int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
+                  const int32_t *kw_terms, int32_t kw_stride, hipStream_t st) {
+    const int32_t kdense = bound_kdense(ix), kh = ix->bd_kh, nsp = ix->corpus.sp_vocab, ntx = ix->corpus.tx_vocab;
+    const int64_t n = ix->docs.n, q_tiles = (nq + AP_BOUND_QT - 1) / AP_BOUND_QT, doc_tiles = (n + AP_BOUND_QT - 1) / AP_BOUND_QT;
+    const int64_t groups = (doc_tiles + 8 * AP_BOUND_GROUP - 1) / (8 * AP_BOUND_GROUP);
+    const bool own = ix->bd_kd != 0;
+    const float eps = ix->dtype == AP_BF16 ? 0.00196f : 0.00392f;
+    hipLaunchKernelGGL(k_bound_queries, dim3((unsigned)(q_tiles * AP_BOUND_QT)), dim3(256), 0, st, Q, w, w_stride, q0, nq, kdense, kh, nsp, ntx, ix->bd_col, eps,
+                       b.qm, b.qc);
+    AP_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bound_table), hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES));
+    const int32_t ld = ix->bd_kd + kh;
+    hipLaunchKernelGGL(k_bound_table, dim3((unsigned)(groups * 8 * AP_BOUND_GROUP * q_tiles)), dim3(1024), AP_BIG_LDS_BYTES, st, b.qm, b.qc, (int32_t)nq,
+                       (int32_t)q_tiles, own ? ix->bd_rows : static_cast<const uint16_t *>(ix->docs.dense), own ? ld : ix->docs.dim, kdense / AP_BK16,
+                       ix->bd_rows + ix->bd_kd, ld, (kdense + kh) / AP_BK16, ix->dense_norm, ix->bd_hn, n, doc_tiles, b.table, b.ld);
+    hipLaunchKernelGGL(k_bound_tail, dim3((unsigned)nq), dim3(256), 0, st, Q, w, w_stride, q0, nsp, ntx, ix->bd_col, ix->bd_run, ix->bd_post, b.qc, kw_terms,
+                       kw_terms ? kw_stride : 0, b.table, b.ld);
+    AP_CHECK_HIP(hipGetLastError());
+    return AP_OK;
+}
+
+// The table itself, for tests: rows of the nq queries' bounds, n entries each.
+extern "C" int ap_stage_score_bounds(ap_index *ix, const ap_queries *q, const float *per_query_w, const int32_t *kw_terms, int32_t kw_stride,
+                                     float *out, void *stream) {
+    AP_REQUIRE(ix && out, "NULL argument");
+    AP_TRY(ap_validate_queries(q));
+    AP_REQUIRE(!kw_terms || (kw_stride >= 1 && kw_stride <= 16), "kw_stride = %d must be in [1, 16]", kw_stride);
+    if (q->nq == 0) return AP_OK;
+    hipStream_t st = (hipStream_t)stream;
+    const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
+    ApBound b;
+    AP_TRY(ap_bound_reserve(ix, q->nq, (size_t)4 << 30, st, &b));
+    if (!b.table || b.slab != q->nq) { ap_set_error("no bounds for this index and batch"); return AP_ESTATE; }
+    AP_TRY(ap_bound_fill(ix, b, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, 0, q->nq, kw_terms, kw_stride, st));
+    AP_CHECK_HIP(hipMemcpy2DAsync(out, (size_t)ix->docs.n * 4, b.table, (size_t)b.ld * 4, (size_t)ix->docs.n * 4, (size_t)q->nq, hipMemcpyDeviceToDevice, st));
+    return AP_OK;
+}

@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <mutex>
 #include <stdio.h>
 #include "../../include/allanpoe.h"
 
@@ -59,7 +60,7 @@ struct ap_index {
     ap_build_params params;
     ApVecs docs;               // device view with tx_val = owned BM25 weights
     int32_t dtype;
-    int64_t tx_nnz;
+    int64_t tx_nnz, sp_nnz;
     float *tx_w = nullptr;     // owned: BM25 weight per lexical entry
     int32_t *df = nullptr;     // owned: document frequency per term
     unsigned long long *counters = nullptr;   // owned: [0] hybrid similarities evaluated by refinement rounds on this index
@@ -84,6 +85,16 @@ struct ap_index {
     uint32_t *visited = nullptr;
     size_t visited_words = 0;
     float *w_dev = nullptr;    // 3 floats: device copy of w_default
+    // what the upper bounds of the scores are computed from (ap_bound.hip): one allocation, the parts below point into it
+    void *bd_mem = nullptr;
+    uint16_t *bd_rows = nullptr;       // n x (bd_kd + bd_kh) bf16: dense part where bd_kd > 0, then the head columns
+    int32_t bd_kd = 0, bd_kh = 0;      // columns of a copied dense part (0: the corpus's own rows serve), head columns
+    int32_t *bd_col = nullptr;         // per term (learned-sparse vocabulary, then lexical): its head column or -1
+    uint2 *bd_run = nullptr;           // per term: first posting, number of postings (0 for head terms)
+    uint2 *bd_post = nullptr;          // (document, weight bits)
+    float2 *bd_hn = nullptr;           // per document: norms of its learned-sparse and lexical head columns
+    uint32_t *bd_bits = nullptr;       // per head column a bit per document: it holds that lexical term
+    struct ApBoundPool *bd_pool = nullptr;   // search-time workspaces
     int32_t *search_counts = nullptr;  // nq x 2 of the last search: similarities evaluated, iterations
     size_t search_counts_cap = 0;
     int32_t last_nq = 0;
@@ -125,6 +136,7 @@ struct ApDebug {
     int64_t max_launch_threads = 0;      // a multiple of 1024: launches that grow with the corpus are cut into slices of this many threads
     int64_t search_visited_global = 0;   // 1: the searches' visited sets stay in global memory even where they would fit LDS
     int64_t search_query_lists = 0;      // 1: the searches look the query's terms up in its lists (the path of queries too long for the LDS tables)
+    int64_t search_bounds = 0;           // 1: searches without the table of upper bounds, 2: with it whatever it costs
     int64_t search_workspace_bytes = 0;  // cap of the search's visited-set workspace (forces searches in several slabs of queries)
 };
 extern ApDebug g_ap_debug;
@@ -156,6 +168,7 @@ struct ApStageEvents {
 int ap_validate_corpus(const ap_corpus *c);
 int ap_validate_params(const ap_build_params *p);
 int ap_ingest_impl(ap_index *ix, hipStream_t st);
+int ap_count_terms(const int32_t *idx, const float *tf, int64_t nnz, int32_t *df, unsigned long long *total, hipStream_t st);
 int ap_alloc_graph(ap_index *ix);
 int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
 // stage bodies shared by the whole build and by insertion (ap_build.hip)
@@ -169,6 +182,15 @@ int ap_assemble_impl(const ap_index *ix, int32_t R, int32_t K, int32_t P, const 
 int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
                      int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st);
 int ap_rescore_lists(const ap_index *ix, int64_t nn, int32_t K, const int32_t *knn, float *sc, hipStream_t st);
+// Upper bounds of the fused scores of a slab of queries against every document (ap_bound.hip).
+struct ApBound {
+    float *table = nullptr;    // slab x ld; NULL: not used in this call
+    int64_t ld = 0;            // documents, padded
+    uint16_t *qm = nullptr;    // the slab's queries as bf16 rows
+    float4 *qc = nullptr;      // per query: what the slack of its row is made of
+    int32_t slab = 0;          // queries the workspace holds
+    std::unique_lock<std::mutex> hold;   // of the index's workspaces, until everything that uses this one is enqueued
+};
 // The visited-set workspace of a search call: `slab` queries are in flight at a time, each with a bitset of one bit
 // per document.  `counts` (nq x 3) and the two events belong to the index's measurement surface and may be absent.
 struct ApSearchWs {
@@ -176,9 +198,19 @@ struct ApSearchWs {
     int32_t slab = 0;
     int32_t *counts = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    ApBound bound;
 };
+#define AP_BOUND_COUNT 31u     // low bits of a table entry: keyword searches count the required tail terms a document holds there
+int ap_bound_ingest(ap_index *ix, hipStream_t st);
+size_t ap_bound_bytes(const ap_index *ix, int64_t nq);
+void ap_bound_release(ap_index *ix);
+void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b);
+int ap_bound_reserve(ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b);
+int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
+                  const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);
 // sizes the workspace an index owns (grow only, capped) for a call of nq queries (ap_search.hip)
-int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws);
+int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds);
+bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters);
 // address, on the current device, of the static workspace of ap_search_batch_noalloc (looked up once per device)
 int ap_static_scratch(void **out);
 // the plain search with an arbitrary query view and device weights (ap_search.hip); big_tables: the queries are as long

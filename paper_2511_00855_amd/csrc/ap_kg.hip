@@ -476,7 +476,7 @@ extern "C" int ap_search_batch_entities(ap_index *ix, const ap_queries *q, const
     g.cmax = std::max(g.E, g.R + ix->kg_le_cap);
     g.words = ((size_t)ix->docs.n + 31) / 32;
     ApSearchWs ws;
-    AP_TRY(ap_search_reserve(ix, nq, st, &ws));
+    AP_TRY(ap_search_reserve(ix, nq, st, &ws, false));
     g.visited = ws.visited; g.out_ids = out_ids; g.out_scores = out_scores; g.counts = ws.counts;
     g.rec = ix->rec; g.meta = ix->meta;
     g.de_ip = ix->kg_de_ip; g.de = ix->kg_de; g.kg_ip = ix->kg_ip; g.kg = ix->kg_idx; g.en_ip = ix->kg_en_ip; g.en = ix->kg_en;

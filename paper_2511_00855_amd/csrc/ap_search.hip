@@ -11,6 +11,7 @@
 // dense slice stays in registers.  The visited set is an exact bitset (one bit
 // per document): in LDS for small pools on small corpora, else in a global
 // workspace of bounded size (large batches run in slabs of queries).
+#include <math.h>
 #include <stdlib.h>
 #include <algorithm>
 #include <mutex>
@@ -57,6 +58,11 @@ struct ApSearchArgs {
     const uint2 *rec;   // packed (term, weight) records of the documents' two sparse parts
     const uint4 *meta;  // per document: first entry, counts, |d_dense|
     const uint32_t *deleted;   // one bit per document, NULL = nothing is mark-deleted: left out of the answers only
+    const float *bound;        // upper bounds of the scores, a row of bound_ld documents per query of the slab; NULL: none
+    int64_t bound_ld;
+    const int32_t *bound_col;  // keyword searches with bounds: head column of every lexical term (-1: the entry's count tells), bitmaps of the columns
+    const uint32_t *bound_bits;
+    int32_t tx_vocab;
     // keyword-constrained search only
     const int32_t *kw_edges;   // n x KR keyword edges, kw_count[u] of them valid
     const int32_t *kw_count;
@@ -273,9 +279,9 @@ void k_search(ApSearchArgs g) {
     uint64_t *xk = PIPE ? reinterpret_cast<uint64_t *>(s_meta) : nxt + g.nxtw;   // cmax words.  KW: satisfying keys the pool did not keep in this iteration; PIPE: entering keys, unordered
     uint64_t *kwc = nxt + g.nxtw + (KW ? g.cmax : 0);   // KW: the secondary pool, k keys, best first
     uint64_t *umask = kwc + (KW ? g.k : 0);   // PIPE: one bit per pool entry; after it the visited set when it lives in LDS
-    __shared__ int32_t s_cnt, s_np, s_skip, s_xn, s_kc, s_nin, s_rmin;
+    __shared__ int32_t s_cnt, s_np, s_skip, s_drop, s_xn, s_kc, s_nin, s_rmin;
     __shared__ int32_t s_par[16], s_psat[16];
-    __shared__ int32_t s_kw[AP_KW_MAX_TERMS];
+    __shared__ int32_t s_kw[AP_KW_MAX_TERMS], s_kwcol[AP_KW_MAX_TERMS];
     __shared__ int32_t s_seed[2];
 
     const int64_t q = (int64_t)g.q0 + blockIdx.x;
@@ -317,13 +323,16 @@ void k_search(ApSearchArgs g) {
         vis.l = (AP_LDS uint32_t *)reinterpret_cast<uint32_t *>(umask + (PIPE ? (g.L + 63) / 64 : 0));
         for (size_t i = threadIdx.x; i < g.words; i += blockDim.x) vis.l[i] = 0u;
     }
-    if (threadIdx.x == 0) { s_cnt = 0; s_skip = 0; s_xn = 0; s_kc = 0; s_nin = 0; }
+    if (threadIdx.x == 0) { s_cnt = 0; s_skip = 0; s_drop = 0; s_xn = 0; s_kc = 0; s_nin = 0; }
     // the query's required terms, unused slots squeezed out (uniform)
     int32_t n_kw = 0;
     if (KW) {
         for (int32_t j = 0; j < g.kw_stride; j++) {
             const int32_t t = g.kw_terms[q * g.kw_stride + j];
-            if (t >= 0) { if (threadIdx.x == 0) s_kw[n_kw] = t; n_kw++; }
+            if (t >= 0) {
+                if (threadIdx.x == 0) { s_kw[n_kw] = t; s_kwcol[n_kw] = g.bound && t < g.tx_vocab ? g.bound_col[t] : -1; }
+                n_kw++;
+            }
         }
     }
     const bool kw_on = KW && n_kw > 0;
@@ -342,6 +351,8 @@ void k_search(ApSearchArgs g) {
     __syncthreads();
     int32_t len = 0, it = 0, nscored = 0, nskipped = 0;
     int32_t fu = 0;   // every pool entry before this position has been expanded
+    int32_t ndropped = 0;   // per lane: neighbours its bound kept out
+    const uint32_t *bound = reinterpret_cast<const uint32_t *>(g.bound) + (g.bound ? (int64_t)blockIdx.x * g.bound_ld : 0);
     AP_PROF_DECL;
     for (;;) {
         AP_PROF(0);
@@ -627,7 +638,14 @@ void k_search(ApSearchArgs g) {
         if (np == 0) break;
         // neighbours of the parents that were never seen before; a parent that satisfies the keyword
         // constraint also brings its keyword edges
+        // The bounds of all documents, where the call has them, are looked at first: while the pool is full, a neighbour
+        // whose bound lies below the pool's last score cannot enter (nor, with keywords, the secondary pool) and is only
+        // marked visited: its descriptor, record and dense row are not read.
         const int32_t per = g.R + (KW ? g.KR : 0);
+        const bool bound_on = g.bound && len == g.L;   // uniform
+        const float b_worst = bound_on ? ap_key_score(ap_uniform_u64(cur[g.L - 1])) : 0.f;
+        const bool b_second_full = kw_on && s_kc == g.k;
+        const float b_second = b_second_full ? ap_key_score(kwc[g.k - 1]) : 0.f;
         for (int32_t i = threadIdx.x; i < np * per; i += blockDim.x) {
             int32_t v;
             if (KW) {
@@ -641,6 +659,22 @@ void k_search(ApSearchArgs g) {
             if (v >= 0) {
                 // the descriptor (where the record is, how long, the dense norm) is fetched along with the visited
                 // test, not after it: one memory round trip less per iteration for 16 bytes per neighbour already seen
+                if (bound_on) {
+                    if (vis.test_and_set(v)) continue;
+                    const uint32_t e = bound[v];
+                    const float ub = __uint_as_float(e & ~AP_BOUND_COUNT);
+                    bool out = ub < b_worst;
+                    if (kw_on && out) {
+                        int32_t held = (int32_t)(e & AP_BOUND_COUNT);
+                        for (int32_t j = 0; j < n_kw; j++)
+                            if (s_kwcol[j] >= 0) held += (int32_t)((g.bound_bits[(int64_t)s_kwcol[j] * (int64_t)g.words + (v >> 5)] >> (v & 31)) & 1u);
+                        if (g.kw_all ? held == n_kw : held > 0) out = b_second_full && ub < b_second;
+                    }
+                    if (out) { ndropped++; continue; }
+                    const uint4 m = g.meta[v];
+                    s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
+                    continue;
+                }
                 const bool seen = vis.test_and_set(v);
                 const uint4 m = g.meta[v];
                 if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
@@ -652,8 +686,10 @@ void k_search(ApSearchArgs g) {
     }
     AP_PROF_FLUSH;
     if (lane == 0) atomicAdd(&s_skip, nskipped);
+    if (g.bound && ndropped) atomicAdd(&s_drop, ndropped);
     __syncthreads();
-    if (threadIdx.x == 0 && g.counts) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = s_skip; }
+    nscored += s_drop;   // a dropped neighbour counts like any other that was decided without its dense row
+    if (threadIdx.x == 0 && g.counts) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = s_skip + s_drop; }
     // S9
     if (kw_on) {
         // Everything in the secondary pool ranked after the pool's last entry when it was handed over, and that
@@ -710,6 +746,29 @@ void k_search(ApSearchArgs g) {
 // Default cap of the index-owned workspace: 2 GiB of visited bits (16,384 queries of a million documents at a time).
 #define AP_SEARCH_WS_BYTES ((size_t)2 << 30)
 
+// ... and of the bounds: 16 GiB (40,000 queries of 100,000 documents, 480 of 8.8 million).
+#define AP_BOUND_WS_BYTES ((size_t)16 << 30)
+
+// Whether the bounds of all documents cost less than they save, by what was measured (microseconds):
+//  - the table: a document's columns are read once (0.4 ns), a tile of 256 queries takes 3.1 ps a pair at 1,280 columns, the
+//    tail's postings 3.5 ps a pair;
+//  - a search that does without: at least 0.15 ns more for every document it reaches while the chip is full (100,000
+//    documents, beam 128: 22.1 ms for 10,000 queries without bounds, 13.3 ms with them, 2.9 of which are the table), and
+//    8 us more an iteration when it is not (one query, 128 iterations: 2.35 ms and 0.89 ms).
+// On 100,000 documents the line lies near a pool of 40 entries at degree 64; searches below it run without.
+bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters) {
+    if (!ix->bd_mem || g_ap_debug.search_bounds == 1 || nq < 1) return false;
+    const double n = (double)ix->docs.n;
+    if ((double)AP_BOUND_WS_BYTES / (4.0 * n) < (double)std::min<int64_t>(nq, 256)) return false;   // slabs too small to fill the chip
+    if (g_ap_debug.search_bounds == 2) return true;
+    double iters = (double)beam / width;
+    if (max_iters > 0) iters = std::min(iters, (double)max_iters);
+    const double reached = n * (1.0 - exp(-iters * width * (double)ix->params.degree / n));
+    const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256);
+    const double cost = 15.0 + n * (0.4e-3 * cols + tiles * 256.0 * 3.1e-6 * cols + (double)nq * 3.5e-6);
+    return std::max((double)nq * reached * 0.15e-3, iters * 8.0) > cost;
+}
+
 // Queries per slab when `cap_words` words are available: as many as fit, then evened out over the slabs.
 static int32_t ap_slab_size(int32_t nq, size_t words, size_t cap_words) {
     size_t fit = std::max<size_t>(1, cap_words / std::max<size_t>(words, 1));
@@ -720,10 +779,14 @@ static int32_t ap_slab_size(int32_t nq, size_t words, size_t cap_words) {
 }
 
 // Sizes the workspace an index owns (grow only) for a call of nq queries.
-int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws) {
+int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds) {
     const size_t words = ((size_t)ix->docs.n + 31) / 32;
     const size_t cap_bytes = g_ap_debug.search_workspace_bytes > 0 ? (size_t)g_ap_debug.search_workspace_bytes : AP_SEARCH_WS_BYTES;
     ws->slab = ap_slab_size(nq, words, cap_bytes / 4);
+    if (bounds) {
+        AP_TRY(ap_bound_reserve(ix, ws->slab, AP_BOUND_WS_BYTES, st, &ws->bound));
+        if (ws->bound.table) ws->slab = ws->bound.slab;
+    }
     const size_t need = words * (size_t)ws->slab;
     if (need > ix->visited_words) {
         if (ix->visited) { AP_CHECK_HIP(hipStreamSynchronize(st)); (void)hipFree(ix->visited); ix->visited = nullptr; ix->visited_words = 0; }
@@ -782,6 +845,11 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     g.rec = ix->rec;
     g.meta = ix->meta;
     g.deleted = ix->deleted;
+    g.bound = ws.bound.table;
+    g.bound_ld = ws.bound.ld;
+    g.bound_col = ix->bd_mem ? ix->bd_col + ix->corpus.sp_vocab : nullptr;
+    g.bound_bits = ix->bd_bits;
+    g.tx_vocab = ix->corpus.tx_vocab;
     auto lds_bytes = [&](int32_t nt) {
         const bool pipe = !kw && !big_tables && nt >= 512;   // the large-pool path: entering keys in the candidates' space, a bitmap of the pool
         const int32_t nxtw = !pipe && g.cmax > nt ? g.cmax : 0;
@@ -826,6 +894,7 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
         // every slab starts from empty visited sets (a fill kernel, not a memset: callers may capture the stream)
         if (!g.vis_lds) AP_TRY(ap_fill_u32(ws.visited, g.words * (size_t)qn, 0u, st));
         if (q0 == 0 && ws.ev0) AP_CHECK_HIP(hipEventRecord(ws.ev0, st));
+        if (ws.bound.table) AP_TRY(ap_bound_fill(ix, ws.bound, Q, w_dev, w_stride, q0, qn, kw_terms, kw_stride, st));
         if (kw) AP_LAUNCH_SEARCH(true, false, 256);
         else if (big_tables) AP_LAUNCH_SEARCH(false, true, 256);
         else if (nt == 256) AP_LAUNCH_SEARCH(false, false, 256);
@@ -857,7 +926,7 @@ int ap_search_core(ap_index *ix, const ApVecs &Q, const float *w_dev, int32_t w_
     AP_TRY(ap_search_check(ix, (int32_t)Q.n, k, beam, max_iters, width, false, out_ids, out_scores));
     if (Q.n == 0) return AP_OK;
     ApSearchWs ws;
-    AP_TRY(ap_search_reserve(ix, (int32_t)Q.n, st, &ws));
+    AP_TRY(ap_search_reserve(ix, (int32_t)Q.n, st, &ws, ap_bound_pays(ix, Q.n, beam, width, max_iters)));
     return ap_search_launch(ix, ws, Q, w_dev, w_stride, k, beam, max_iters, width, nullptr, 0, 0u, big_tables, out_ids, out_scores, st);
 }
 
@@ -870,7 +939,7 @@ static int ap_search_impl(ap_index *ix, const ap_queries *q, const float *per_qu
     if (q->nq == 0) return AP_OK;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApSearchWs ws;
-    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws));
+    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters)));
     return ap_search_launch(ix, ws, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, p->k, p->beam, p->max_iters,
                             p->search_width, kw_terms, kw_stride, kw_flags, false, out_ids, out_scores, (hipStream_t)stream);
 }

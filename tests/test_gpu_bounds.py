@@ -1,0 +1,98 @@
+"""The table of upper bounds: never below a score that the scoring kernels give, no further above it than its rounding
+allows, and searches that use it return the same ids, scores and counts of scored documents, bit for bit, as searches
+that score every neighbour."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00855_amd import binding as B
+from paper_2511_00855_amd.synth import make_keywords, make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(base, **kw):
+    w = make_workload(base, seed=11, **kw)
+    bf16 = getattr(w.docs, "dense_bf16", None) is not None
+    return w, B.DeviceVecs(w.docs, bf16=bf16), B.DeviceVecs(w.queries)
+
+
+# tiles of 256 x 256, chunks of 64 columns, at most 512 head columns: below, at and above their edges; a vocabulary that is
+# all head, one of which nearly nothing is
+@pytest.mark.parametrize("base,n,nq,dim,vocab", [("tiny", 1, 1, 4, 50), ("tiny", 255, 257, 64, 300), ("tiny", 257, 255, 260, 10_000),
+                                                 ("cfg2", 1300, 40, 768, 30_522), ("cfg3", 513, 20, 520, 5_000),
+                                                 ("cfg3", 512, 256, 1024, 250_002), ("cfg3", 700, 3, 8, 1_000)])
+def test_bounds_hold_and_are_tight(base, n, nq, dim, vocab):
+    w, docs, qs = _workload(base, n=n, nq=nq, dim=dim, vocab=vocab, **({} if vocab > 400 else dict(sp=("fixed", 12), tx=("fixed", 10))))
+    ix = B.Index.ingest(docs, B.build_params(8))
+    rng = np.random.default_rng(3)
+    cand = np.tile(np.arange(n, dtype=np.int32), (nq, 1))
+    for weights in (rng.uniform(0.05, 1.0, (nq, 3)), rng.uniform(-1.0, 1.0, (nq, 3)), np.tile([0.0, 0.0, 1.0], (nq, 1)), np.tile([1e-6, 3e4, 0.0], (nq, 1))):
+        pw = weights.astype(np.float32)
+        sc = ix.hybrid_scores(qs, cand, pw).double()
+        up = ix.stage_score_bounds(qs, pw).double()
+        torch.cuda.synchronize()
+        wd, ws, wf = [torch.from_numpy(np.abs(weights[:, i])).to(sc.device)[:, None] for i in range(3)]
+        assert (up >= sc[:, :, 3]).all()
+        # two roundings to bf16 (2^-9 each) of norm-bounded parts, once in the product and once in the slack, and 1e-3 for all sums
+        q, d = w.queries, w.docs
+        qn = torch.from_numpy(np.linalg.norm(q.dense, axis=1)).to(sc.device)[:, None]
+        dn = torch.from_numpy(np.linalg.norm(d.dense, axis=1)).to(sc.device)[None, :]
+        rows = lambda ip, v: torch.from_numpy(np.array([np.linalg.norm(v[a:b]) for a, b in zip(ip[:-1], ip[1:])])).to(sc.device)
+        txw = ix.export_ingest()[0].cpu().numpy()
+        parts = wd * qn * dn + ws * rows(q.sp_indptr, q.sp_val)[:, None] * rows(d.sp_indptr, d.sp_val)[None, :] \
+            + wf * rows(q.tx_indptr, q.tx_val)[:, None] * rows(d.tx_indptr, txw)[None, :]
+        assert (up - sc[:, :, 3] <= (4 * 2.0 ** -9 + 1e-3) * parts + 1e-12).all()
+    ix.close()
+
+
+@pytest.mark.parametrize("base,n,dim,vocab", [("tiny", 1500, 128, 10_000), ("cfg2", 2100, 260, 30_522), ("cfg3", 1100, 520, 5_000), ("cfg3", 900, 128, 250_002)])
+def test_searches_with_and_without_bounds_are_the_same(debug_knobs, base, n, dim, vocab):
+    w, docs, qs = _workload(base, n=n, nq=70, dim=dim, vocab=vocab)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=2, n_entry=16))
+    pw = np.random.default_rng(5).uniform(-0.3, 1.0, (qs.n, 3)).astype(np.float32)
+    kw = make_keywords(w.queries, seed=6, max_terms=3, stride=4, p_none=0.1)
+    kw[3] = [-1, 2 ** 30, w.docs.tx_vocab, -5]     # terms that no document can hold
+    for k, beam, width, iters in ((10, 16, 1, 0), (5, 64, 3, 0), (10, 200, 16, 7), (1, 1, 1, 0), (10, n + 50, 16, 0)):
+        got = {}
+        for mode in (1, 2):
+            debug_knobs("search_bounds", mode)
+            out = []
+            for weights in (pw, np.abs(pw)):
+                out += list(ix.search_batch(qs, k, beam, weights, search_width=width, max_iters=iters))
+                out.append(ix.search_stats(qs.n)[0][:, :2].clone())
+                for kw_all in (False, True):
+                    out += list(ix.search_batch_keywords(qs, k, beam, kw, weights, kw_all=kw_all, search_width=min(width, 4), max_iters=iters))
+                    out.append(ix.search_stats(qs.n)[0][:, :2].clone())
+            got[mode] = [t.clone() for t in out]
+        debug_knobs("search_bounds", 0)
+        assert all(torch.equal(a, b) for a, b in zip(got[1], got[2])), (k, beam, width, iters)
+    # slabs of queries, each with a table of its own
+    debug_knobs("search_bounds", 2)
+    ref = [t.clone() for t in ix.search_batch(qs, 10, 64, pw)]
+    debug_knobs("search_workspace_bytes", 9 * 4 * ((n + 31) // 32))
+    for _ in range(2):
+        assert all(torch.equal(a, b) for a, b in zip(ref, ix.search_batch(qs, 10, 64, pw)))
+    ix.close()
+
+
+def test_two_streams_search_one_index_with_tables_of_their_own(debug_knobs):
+    w, docs, qs = _workload("tiny", n=3000, nq=60)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=2, n_entry=16))
+    rng = np.random.default_rng(8)
+    pws = [torch.from_numpy(rng.uniform(0.1, 1.0, (qs.n, 3)).astype(np.float32)).to(docs.device) for _ in range(2)]
+    debug_knobs("search_bounds", 1)
+    ref = [[t.clone() for t in ix.search_batch(qs, 10, 96, p)] for p in pws]
+    debug_knobs("search_bounds", 2)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    outs = [[], []]
+    for _ in range(5):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                outs[i].append(ix.search_batch(qs, 10, 96, pws[i]))
+    torch.cuda.synchronize()
+    for i in range(2):
+        for o in outs[i]:
+            assert all(torch.equal(a, b) for a, b in zip(o, ref[i]))
+    ix.close()
