@@ -428,7 +428,7 @@ void ap_bound_release(ap_index *ix) {
 // (two threads may search on one stream).  b->table stays NULL where no workspace is to be had: the caller goes without
 // bounds.  That is also what a captured search does: a graph's replays must not depend on a workspace that a later
 // call may replace.
-int ap_bound_reserve(ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b) {
+int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b) {
     *b = ApBound();
     if (!ix->bd_mem || nq < 1 || st == hipStreamPerThread) return AP_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -487,7 +487,7 @@ extern "C" int ap_stage_score_bounds(ap_index *ix, const ap_queries *q, const fl
     hipStream_t st = (hipStream_t)stream;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApBound b;
-    AP_TRY(ap_bound_reserve(ix, q->nq, (size_t)4 << 30, st, &b));
+    AP_TRY(ap_bound_reserve(ix, q->nq, AP_BOUND_WS_BYTES, st, &b));
     if (!b.table || b.slab != q->nq) { ap_set_error("no bounds for this index and batch"); return AP_ESTATE; }
     AP_TRY(ap_bound_fill(ix, b, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, 0, q->nq, kw_terms, kw_stride, st));
     AP_CHECK_HIP(hipMemcpy2DAsync(out, (size_t)ix->docs.n * 4, b.table, (size_t)b.ld * 4, (size_t)ix->docs.n * 4, (size_t)q->nq, hipMemcpyDeviceToDevice, st));

@@ -1,6 +1,9 @@
 // S1 as stand-alone calls: hybrid similarities of explicit (a, candidate)
 // pairs, and the exhaustive scorer + exact top-k used as ground truth.
-#include "ap_common.hpp"
+#include <algorithm>
+#include <new>
+#include <vector>
+#include "ap_tiles.hpp"
 
 #define AP_LIST_CAP 512  // a-side list entries staged in LDS; longer lists are read from global memory
 
@@ -199,29 +202,102 @@ __global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ score
     }
 }
 
-extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const float *per_query_w, int32_t k,
-                                  int32_t *out_ids, float *out_scores, void *stream) {
-    AP_REQUIRE(ix && out_ids && out_scores, "NULL argument");
-    AP_TRY(ap_validate_queries(q));
-    AP_REQUIRE(k >= 1, "k must be positive");
-    if (q->nq == 0) return AP_OK;
-    hipStream_t st = (hipStream_t)stream;
-    const ApVecs Q = query_view(q, ix->docs.dim);
+// The exact top-k out of the table of upper bounds: one workgroup per query.  Every thread's best bound of its share of
+// the row gives 1,024 documents; the k best of them are scored, and the least of their scores, T, is one that the k-th
+// result reaches at least, so only documents whose bound is not below T have to be scored (some fifty for k = 10 on
+// 100,000 documents).  Two passes over the row, bound by reading it.  A query with more than AP_BT_CAND of them is left to
+// the exhaustive scorer.  1,000 queries of 100,000 documents (768 f32 columns), k = 10: 74.9 ms with the exhaustive scorer,
+// 0.98 ms with the table, which takes 0.72 ms of it.
+#define AP_BT_CAND 4096
+template <int DT, int NV>
+__global__ __launch_bounds__(1024) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
+                                                     const float *__restrict__ table, int64_t ld, int32_t k, int32_t *__restrict__ out_ids,
+                                                     float *__restrict__ out_scores, int32_t *__restrict__ over /* [0] count, then queries */) {
+    __shared__ uint64_t keys[AP_BT_CAND];
+    __shared__ int32_t cand[AP_BT_CAND];
+    __shared__ int32_t l_sp_idx[AP_BF_QCAP], l_tx_idx[AP_BF_QCAP];
+    __shared__ float l_sp_val[AP_BF_QCAP], l_tx_val[AP_BF_QCAP];
+    __shared__ int32_t s_n;
+    __shared__ uint32_t s_T;
+    const int64_t q = q0 + blockIdx.x;
+    const float *row = table + (int64_t)blockIdx.x * ld;
+    const int lane = threadIdx.x & 63, wave = ap_wave_id();
+    const ApLists a = ap_stage_lists(Q, q, l_sp_idx, l_sp_val, l_tx_idx, l_tx_val, AP_BF_QCAP);
+    float qa[NV * ApDense<DT>::EPC];
+    ap_load_aside<DT, NV, AP_F32>(Q.dense, q, D.dim, qa);
+    const float wd = w[q * w_stride], ws = w[q * w_stride + 1], wf = w[q * w_stride + 2];
+    auto score = [&](int32_t v) -> float {   // a wave
+        float sd, ss, sf;
+        ap_hybrid_wave<DT, NV>(D, qa, a, v, sd, ss, sf);
+        return ap_fuse(wd, ws, wf, sd, ss, sf);
+    };
+    const int64_t n4 = (D.n + 3) / 4;
+    float best = -INFINITY;
+    int32_t best_id = -1;
+    for (int64_t j = threadIdx.x; j < n4; j += 1024) {
+        const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
+        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            if (j * 4 + e < D.n && (best_id < 0 || !(x[e] <= best))) { best = x[e]; best_id = (int32_t)(j * 4 + e); }
+    }
+    keys[threadIdx.x] = best_id >= 0 ? ap_make_key(best == best ? best : INFINITY, best_id, 1u) : 0ull;
+    if (threadIdx.x == 0) { s_n = 0; s_T = 0xffffffffu; }
+    ap_bitonic_desc(keys, 1024);
+    for (int32_t i = wave; i < k; i += 16) {
+        const uint64_t key = ap_uniform_u64(keys[i]);
+        const float s = key ? score(ap_key_id(key)) : -INFINITY;
+        if (lane == 0) atomicMin(&s_T, ap_f2ord(s));
+    }
+    __syncthreads();
+    const float T = ap_ord2f(s_T);
+    for (int64_t j = threadIdx.x; j < n4; j += 1024) {
+        const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
+        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            if (j * 4 + e < D.n && !(x[e] < T)) {
+                const int32_t pos = atomicAdd(&s_n, 1);
+                if (pos < AP_BT_CAND) cand[pos] = (int32_t)(j * 4 + e);
+            }
+    }
+    __syncthreads();
+    const int32_t c = ap_uniform_i32(s_n);
+    if (c > AP_BT_CAND || c < k) {   // uniform (fewer than k: scores that compare with nothing)
+        if (threadIdx.x == 0) over[1 + atomicAdd(over, 1)] = (int32_t)q;
+        return;
+    }
+    for (int32_t i = wave; i < c; i += 16) {
+        const int32_t v = ap_uniform_i32(cand[i]);
+        const float s = score(v);
+        if (lane == 0) keys[i] = ap_make_key(s, v, 1u);
+    }
+    int32_t n2 = 64;
+    while (n2 < c) n2 <<= 1;
+    for (int32_t i = c + (int32_t)threadIdx.x; i < n2; i += 1024) keys[i] = 0ull;
+    ap_bitonic_desc(keys, n2);
+    for (int32_t i = threadIdx.x; i < k; i += 1024) {
+        out_ids[q * k + i] = ap_key_id(keys[i]);
+        out_scores[q * k + i] = ap_key_score(keys[i]);
+    }
+}
+
+// Every document scored, for queries [first, first + count).
+static int bf_exhaustive(const ap_index *ix, const ApVecs &Q, const float *w, int32_t ws, int32_t first, int32_t count, int32_t k, int32_t *out_ids,
+                         float *out_scores, hipStream_t st) {
     const int64_t n = ix->docs.n;
-    const float *w = per_query_w ? per_query_w : ix->w_dev;
-    const int32_t ws = per_query_w ? 3 : 0;
     // queries are processed in slabs so that the score scratch stays <= 2 GiB
     int64_t slab = (int64_t)(1ull << 29) / n;
     slab = slab / AP_BF_QB * AP_BF_QB;
     if (slab < AP_BF_QB) slab = AP_BF_QB;
-    if (slab > q->nq) slab = (q->nq + AP_BF_QB - 1) / AP_BF_QB * AP_BF_QB;
+    if (slab > count) slab = (count + AP_BF_QB - 1) / AP_BF_QB * AP_BF_QB;
     float *scratch = nullptr;
     AP_TRY(ap_dev_alloc(&scratch, (size_t)slab * (size_t)n));
     const size_t smem = (size_t)AP_BF_QB * ((size_t)ix->docs.dim + 4 * AP_BF_QCAP) * 4;
     int rc = AP_OK;
     hipError_t e = hipSuccess;
-    for (int32_t q0 = 0; q0 < q->nq && e == hipSuccess; q0 += (int32_t)slab) {
-        const int32_t nqb = (q->nq - q0) < slab ? (q->nq - q0) : (int32_t)slab;
+    for (int32_t q0 = first; q0 < first + count && e == hipSuccess; q0 += (int32_t)slab) {
+        const int32_t nqb = (first + count - q0) < slab ? (first + count - q0) : (int32_t)slab;
         int64_t xb = (n + 3) / 4;
         if (xb > 256) xb = 256;
         dim3 grid((unsigned)xb, (unsigned)((nqb + AP_BF_QB - 1) / AP_BF_QB));
@@ -241,4 +317,54 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     (void)hipFree(scratch);
     if (e != hipSuccess) { ap_set_error("ap_bruteforce_topk failed: %s", hipGetErrorString(e)); rc = AP_EHIP; }
     return rc;
+}
+
+extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const float *per_query_w, int32_t k,
+                                  int32_t *out_ids, float *out_scores, void *stream) {
+    AP_REQUIRE(ix && out_ids && out_scores, "NULL argument");
+    AP_TRY(ap_validate_queries(q));
+    AP_REQUIRE(k >= 1, "k must be positive");
+    if (q->nq == 0) return AP_OK;
+    hipStream_t st = (hipStream_t)stream;
+    const ApVecs Q = query_view(q, ix->docs.dim);
+    const float *w = per_query_w ? per_query_w : ix->w_dev;
+    const int32_t ws = per_query_w ? 3 : 0;
+    // Out of the table of bounds where that leaves most documents unscored: k well below the 1,024 documents the
+    // threshold comes from, and a corpus well above them (below, the exhaustive scorer has little to do).
+    ApBound b;
+    if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, AP_BOUND_WS_BYTES, st, &b));
+    if (!b.table) return bf_exhaustive(ix, Q, w, ws, 0, q->nq, k, out_ids, out_scores, st);
+    int32_t *over = nullptr;
+    AP_TRY(ap_dev_alloc(&over, (size_t)q->nq + 1));
+    int rc = ap_fill_u32(over, 1, 0u, st);
+    for (int32_t q0 = 0; q0 < q->nq && rc == AP_OK; q0 += b.slab) {
+        const int32_t nqb = std::min(b.slab, q->nq - q0);
+        rc = ap_bound_fill(ix, b, Q, w, ws, q0, nqb, nullptr, 0, st);
+        if (rc != AP_OK) break;
+        AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV>), dim3((unsigned)nqb), dim3(1024), 0, st, Q, ix->docs, (int64_t)q0, w,
+                                                                      ws, b.table, b.ld, k, out_ids, out_scores, over));
+        if (hipGetLastError() != hipSuccess) { ap_set_error("ap_bruteforce_topk failed to launch"); rc = AP_EHIP; }
+    }
+    int32_t n_over = 0;
+    std::vector<int32_t> list;
+    hipError_t e = hipSuccess;
+    if (rc == AP_OK) {
+        e = hipMemcpyAsync(&n_over, over, sizeof(n_over), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess && n_over > 0) {
+            try { list.resize((size_t)n_over); } catch (const std::bad_alloc &) { ap_set_error("out of host memory"); rc = AP_ENOMEM; }
+            if (rc == AP_OK) e = hipMemcpy(list.data(), over + 1, (size_t)n_over * sizeof(int32_t), hipMemcpyDeviceToHost);
+        }
+    }
+    (void)hipFree(over);
+    if (rc != AP_OK) return rc;
+    if (e != hipSuccess) { ap_set_error("ap_bruteforce_topk failed: %s", hipGetErrorString(e)); return AP_EHIP; }
+    std::sort(list.begin(), list.end());
+    for (size_t i = 0; i < list.size();) {   // runs of queries the bounds left undecided
+        size_t j = i + 1;
+        while (j < list.size() && list[j] == list[j - 1] + 1) j++;
+        AP_TRY(bf_exhaustive(ix, Q, w, ws, list[i], (int32_t)(j - i), k, out_ids, out_scores, st));
+        i = j;
+    }
+    return AP_OK;
 }

@@ -746,9 +746,6 @@ void k_search(ApSearchArgs g) {
 // Default cap of the index-owned workspace: 2 GiB of visited bits (16,384 queries of a million documents at a time).
 #define AP_SEARCH_WS_BYTES ((size_t)2 << 30)
 
-// ... and of the bounds: 16 GiB (40,000 queries of 100,000 documents, 480 of 8.8 million).
-#define AP_BOUND_WS_BYTES ((size_t)16 << 30)
-
 // Whether the bounds of all documents cost less than they save, by what was measured (microseconds):
 //  - the table: a document's columns are read once (0.4 ns), a tile of 256 queries takes 3.1 ps a pair at 1,280 columns, the
 //    tail's postings 3.5 ps a pair;

@@ -96,3 +96,22 @@ def test_two_streams_search_one_index_with_tables_of_their_own(debug_knobs):
         for o in outs[i]:
             assert all(torch.equal(a, b) for a, b in zip(o, ref[i]))
     ix.close()
+
+
+@pytest.mark.parametrize("base,n,dim,k", [("tiny", 4096, 128, 1), ("tiny", 4097, 100, 10), ("cfg2", 4500, 768, 100), ("cfg3", 5000, 1024, 256),
+                                          ("cfg3", 4200, 520, 10), ("tiny", 9001, 64, 37)])
+def test_exact_topk_out_of_the_bounds(base, n, dim, k):
+    """Against a sort of the scores of all documents (hybrid_scores): the same ids and the same bits."""
+    w, docs, qs = _workload(base, n=n, nq=19, dim=dim, **({} if n < 9000 else dict(sp=("fixed", 1), tx=("fixed", 1))))
+    if n >= 9000:   # every document the same: thousands of candidates tie, more than a workgroup lists
+        docs.dense[:] = docs.dense[0]
+        docs.sp_idx[:] = 7; docs.sp_val[:] = 1.0
+        docs.tx_idx[:] = 3; docs.tx_val[:] = 1.0
+    ix = B.Index.ingest(docs, B.build_params(8))
+    for pw in (np.random.default_rng(1).uniform(0.1, 1.0, (qs.n, 3)), np.random.default_rng(2).uniform(-1.0, 1.0, (qs.n, 3)), np.zeros((qs.n, 3))):
+        pw = pw.astype(np.float32)
+        ids, sc = ix.bruteforce_topk(qs, k, pw)
+        all_sc = ix.hybrid_scores(qs, np.tile(np.arange(n, dtype=np.int32), (qs.n, 1)), pw)[:, :, 3]
+        want, at = torch.sort(all_sc, dim=1, descending=True, stable=True)    # equal scores: smaller id first
+        assert torch.equal(sc, want[:, :k]) and torch.equal(ids, at[:, :k].to(torch.int32))
+    ix.close()
