@@ -118,17 +118,19 @@ template <bool BIG> struct ApQTab {
 // G: candidates a wave keeps on their way at once.  Their records are loaded together, then reduced one by one;
 // then the dense rows of those that still need one are loaded together and multiplied one by one.  G = 1 is the
 // plain order (record, sums, dense row); larger G trades registers for memory requests in flight, which pays where
-// a large pool leaves a CU with few waves.  The order of the additions inside a candidate does not depend on G.
+// a large pool leaves a CU with few waves.  pre: the candidates' dense rows are requested along with their records (they
+// got past their bounds, so nearly all of them need theirs).  The order of the additions inside a candidate does not depend on G.
 template <int DT, int NV, bool TAB, bool KW, bool BIG, int NW, int G>
 __device__ __forceinline__ int32_t ap_score_candidates(const ApVecs &D, const uint2 *rec, const float *qa, const uint64_t *qtab,
                                                        const ApLists &a, float wd, float ws, float wf, float qnorm, bool pool_full,
                                                        float worst_score, const uint4 *s_meta, int32_t c,
                                                        uint64_t *newk, const int32_t *s_kw, int32_t n_kw, bool kw_all,
-                                                       bool second_full, float second_worst, uint32_t msp, uint32_t mtx) {
+                                                       bool second_full, float second_worst, uint32_t msp, uint32_t mtx, bool pre) {
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
     int32_t skipped = 0;
     for (int32_t i0 = wave; i0 < c; i0 += NW * G) {
         uint2 xs[G][2], xt[G][1];
+        uint4 raw[G][NV];
         const uint2 *r[G];
         int32_t spn[G], txn[G], v[G];
         float dn[G];
@@ -144,6 +146,7 @@ __device__ __forceinline__ int32_t ap_score_candidates(const ApVecs &D, const ui
                 dn[gi] = __uint_as_float(ap_uniform_u32(m.z));
                 v[gi] = (int32_t)ap_uniform_u32(m.w);
                 ap_rec_load_raw<2, 1>(r[gi], spn[gi], txn[gi], xs[gi], xt[gi]);
+                if (pre) ap_dense_load_raw<DT, NV>(D, v[gi], raw[gi]);
             }
         }
         float ss[G], sf[G];
@@ -185,10 +188,9 @@ __device__ __forceinline__ int32_t ap_score_candidates(const ApVecs &D, const ui
                 need[gi] = true;
             }
         }
-        uint4 raw[G][NV];
 #pragma unroll
         for (int gi = 0; gi < G; gi++)
-            if (need[gi]) ap_dense_load_raw<DT, NV>(D, v[gi], raw[gi]);
+            if (need[gi] && !pre) ap_dense_load_raw<DT, NV>(D, v[gi], raw[gi]);
 #pragma unroll
         for (int gi = 0; gi < G; gi++) {
             if (need[gi]) {
@@ -216,6 +218,7 @@ __device__ __forceinline__ int32_t ap_score_candidates(const ApVecs &D, const ui
 #ifndef AP_RANK_LANES
 #define AP_RANK_LANES 16        // lanes that rank one entering key of a large pool (16, 32 or 64)
 #endif
+#define AP_RANK_SORT 128        // entering keys of a large pool beyond which they are sorted instead of ranked one against the other
 #ifndef AP_SEARCH_WAVES_512
 #define AP_SEARCH_WAVES_512 6
 #endif
@@ -351,6 +354,7 @@ void k_search(ApSearchArgs g) {
     __syncthreads();
     int32_t len = 0, it = 0, nscored = 0, nskipped = 0;
     int32_t fu = 0;   // every pool entry before this position has been expanded
+    bool bound_on = false;  // the candidates of this iteration got past their bounds (uniform)
     int32_t ndropped = 0;   // per lane: neighbours its bound kept out
     const uint32_t *bound = reinterpret_cast<const uint32_t *>(g.bound) + (g.bound ? (int64_t)blockIdx.x * g.bound_ld : 0);
     AP_PROF_DECL;
@@ -366,10 +370,10 @@ void k_search(ApSearchArgs g) {
         constexpr int G = ApSearchG<NT>::G;
         if (use_tab)
             nskipped += ap_score_candidates<DT, NV, true, KW, BIG, NT / 64, G>(g.D, g.rec, qa, qtab, a, wd, ws, wf, qnorm, pool_full, worst_score,
-                                                                 s_meta, c, newk, s_kw, n_kw, g.kw_all != 0, second_full, second_worst, msp, mtx);
+                                                                 s_meta, c, newk, s_kw, n_kw, g.kw_all != 0, second_full, second_worst, msp, mtx, bound_on);
         else
             nskipped += ap_score_candidates<DT, NV, false, KW, BIG, NT / 64, G>(g.D, g.rec, qa, qtab, a, wd, ws, wf, qnorm, pool_full, worst_score,
-                                                                  s_meta, c, newk, s_kw, n_kw, g.kw_all != 0, second_full, second_worst, 0u, 0u);
+                                                                  s_meta, c, newk, s_kw, n_kw, g.kw_all != 0, second_full, second_worst, 0u, 0u, bound_on);
         AP_PROF(1);
         __syncthreads();
         AP_PROF(2);
@@ -399,12 +403,36 @@ void k_search(ApSearchArgs g) {
                 return (int32_t)__popc((uint32_t)(m >> (grp * GL)) & (GL == 32 ? 0xffffffffu : 0xffffu));
             };
             int32_t *rr = reinterpret_cast<int32_t *>(newk);
+            // Many keys enter while the pool fills: from AP_RANK_SORT on they are sorted where they lie (the squared number of
+            // compares is what costs there: 1,024 keys took 93 us of ranking; the array and newS behind it hold them padded
+            // to a power of two).
+            const bool sorted = cin > AP_RANK_SORT;   // uniform
+            if (sorted) {
+                int32_t n2 = AP_RANK_SORT;
+                while (n2 < cin) n2 <<= 1;
+                for (int32_t t = cin + (int32_t)threadIdx.x; t < n2; t += NT) xk[t] = 0ull;
+                for (int32_t size = 2; size <= n2; size <<= 1)
+                    for (int32_t stride = size >> 1; stride > 0; stride >>= 1) {
+                        // pairs closer than 64 keys lie inside one wave's 128 keys: no barrier between those steps
+                        if (stride >= 64 || stride == size >> 1) __syncthreads(); else ap_wave_sync();
+                        for (int32_t t = threadIdx.x; t < (n2 >> 1); t += NT) {
+                            const int32_t x = 2 * t - (t & (stride - 1)), y = x + stride;
+                            const uint64_t kx = xk[x], ky = xk[y];
+                            if ((kx < ky) == ((x & size) == 0)) { xk[x] = ky; xk[y] = kx; }
+                        }
+                    }
+                __syncthreads();
+                newS = xk;
+            } else newS = reinterpret_cast<uint64_t *>(s_meta) + g.cmax;
             for (int32_t j0 = wave * GPW; j0 < cin; j0 += NT / 64 * GPW) {
                 const int32_t j = j0 + grp;
                 const bool on = j < cin;
                 const uint64_t key = on ? xk[j] : 0ull;
-                int32_t e = 0;
-                for (int32_t i0 = 0; i0 < cin; i0 += GL) e += group_count(on && i0 + gl < cin && xk[i0 + gl] > key);
+                int32_t e = j;
+                if (!sorted) {
+                    e = 0;
+                    for (int32_t i0 = 0; i0 < cin; i0 += GL) e += group_count(on && i0 + gl < cin && xk[i0 + gl] > key);
+                }
                 int32_t lo = 0, hi = on ? len : 0;   // the rank (number of pool entries that rank before the key) lies in [lo, hi]
                 while (__any(hi > lo)) {
                     const int32_t step = (hi - lo + GL - 1) >> GSH;
@@ -413,7 +441,7 @@ void k_search(ApSearchArgs g) {
                     const int32_t nlo = lo + n_before * step, nhi = lo + (n_before + 1) * step - 1;
                     if (hi > lo) { lo = nlo; hi = nhi < hi ? nhi : hi; }
                 }
-                if (on && gl == 0) { newS[e] = key; rr[e] = lo; }
+                if (on && gl == 0) { if (!sorted) newS[e] = key; rr[e] = lo; }
             }
             __syncthreads();
             if (threadIdx.x == 0) s_nin = 0;   // next touched after the barriers of the merge or the pick
@@ -642,42 +670,57 @@ void k_search(ApSearchArgs g) {
         // whose bound lies below the pool's last score cannot enter (nor, with keywords, the secondary pool) and is only
         // marked visited: its descriptor, record and dense row are not read.
         const int32_t per = g.R + (KW ? g.KR : 0);
-        const bool bound_on = g.bound && len == g.L;   // uniform
+        bound_on = g.bound && len == g.L;
         const float b_worst = bound_on ? ap_key_score(ap_uniform_u64(cur[g.L - 1])) : 0.f;
         const bool b_second_full = kw_on && s_kc == g.k;
         const float b_second = b_second_full ? ap_key_score(kwc[g.k - 1]) : 0.f;
-        for (int32_t i = threadIdx.x; i < np * per; i += blockDim.x) {
-            int32_t v;
+        auto neighbour = [&](int32_t i) -> int32_t {
             if (KW) {
                 const int32_t pi = i / per, sl = i % per, u = s_par[pi];
-                v = -1;
-                if (sl < g.R) v = g.graph[(int64_t)u * g.R + sl];
-                else if (g.kw_use_edges && s_psat[pi] && sl - g.R < g.kw_count[u]) v = g.kw_edges[(int64_t)u * g.KR + (sl - g.R)];
-            } else {
-                v = g.graph[(int64_t)s_par[i / g.R] * g.R + (i % g.R)];
+                if (sl < g.R) return g.graph[(int64_t)u * g.R + sl];
+                return g.kw_use_edges && s_psat[pi] && sl - g.R < g.kw_count[u] ? g.kw_edges[(int64_t)u * g.KR + (sl - g.R)] : -1;
             }
-            if (v >= 0) {
-                // the descriptor (where the record is, how long, the dense norm) is fetched along with the visited
-                // test, not after it: one memory round trip less per iteration for 16 bytes per neighbour already seen
-                if (bound_on) {
-                    if (vis.test_and_set(v)) continue;
-                    const uint32_t e = bound[v];
-                    const float ub = __uint_as_float(e & ~AP_BOUND_COUNT);
+            return g.graph[(int64_t)s_par[i / g.R] * g.R + (i % g.R)];
+        };
+        if (bound_on) {
+            // two neighbours a thread at a time, step by step, so that the round trips of one run beside the other's
+            constexpr int GU = 2;
+            for (int32_t i0 = threadIdx.x; i0 < np * per; i0 += GU * NT) {
+                int32_t v[GU];
+                uint32_t e[GU];
+#pragma unroll
+                for (int j = 0; j < GU; j++) v[j] = i0 + j * NT < np * per ? neighbour(i0 + j * NT) : -1;
+#pragma unroll
+                for (int j = 0; j < GU; j++)
+                    if (v[j] >= 0 && vis.test_and_set(v[j])) v[j] = -1;
+#pragma unroll
+                for (int j = 0; j < GU; j++) e[j] = v[j] >= 0 ? bound[v[j]] : 0u;
+#pragma unroll
+                for (int j = 0; j < GU; j++) {
+                    if (v[j] < 0) continue;
+                    const float ub = __uint_as_float(e[j] & ~AP_BOUND_COUNT);
                     bool out = ub < b_worst;
                     if (kw_on && out) {
-                        int32_t held = (int32_t)(e & AP_BOUND_COUNT);
-                        for (int32_t j = 0; j < n_kw; j++)
-                            if (s_kwcol[j] >= 0) held += (int32_t)((g.bound_bits[(int64_t)s_kwcol[j] * (int64_t)g.words + (v >> 5)] >> (v & 31)) & 1u);
+                        int32_t held = (int32_t)(e[j] & AP_BOUND_COUNT);
+                        for (int32_t t = 0; t < n_kw; t++)
+                            if (s_kwcol[t] >= 0) held += (int32_t)((g.bound_bits[(int64_t)s_kwcol[t] * (int64_t)g.words + (v[j] >> 5)] >> (v[j] & 31)) & 1u);
                         if (g.kw_all ? held == n_kw : held > 0) out = b_second_full && ub < b_second;
                     }
                     if (out) { ndropped++; continue; }
-                    const uint4 m = g.meta[v];
-                    s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
-                    continue;
+                    const uint4 m = g.meta[v[j]];
+                    s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v[j]);
                 }
-                const bool seen = vis.test_and_set(v);
-                const uint4 m = g.meta[v];
-                if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
+            }
+        } else {
+            for (int32_t i = threadIdx.x; i < np * per; i += NT) {
+                const int32_t v = neighbour(i);
+                if (v >= 0) {
+                    // the descriptor (where the record is, how long, the dense norm) is fetched along with the visited
+                    // test, not after it: one memory round trip less per iteration for 16 bytes per neighbour already seen
+                    const bool seen = vis.test_and_set(v);
+                    const uint4 m = g.meta[v];
+                    if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
+                }
             }
         }
         __syncthreads();
