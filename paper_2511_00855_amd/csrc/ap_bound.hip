@@ -8,6 +8,7 @@
 // bf16 matrix product; the remaining terms (the "tail") are added from postings.  Rounding to bf16 is paid for by a
 // slack per pair, so nothing that decides a result depends on the product's precision: a candidate the bound lets
 // through is scored as ever, and one it stops could not have entered.
+#include <math.h>
 #include <algorithm>
 #include <new>
 #include "ap_tiles.hpp"
@@ -401,10 +402,42 @@ __global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__res
     }
 }
 
+// One block per query: the bound that `share` of the documents reach, from a sample of at most 4,096 (64 runs spread over the
+// corpus, 256 bytes each).
+#define AP_FLOOR_SAMPLE 4096
+__global__ __launch_bounds__(256) void k_bound_floor(const float *__restrict__ table, int64_t ld, int64_t n, float share, float *__restrict__ out) {
+    __shared__ uint64_t keys[AP_FLOOR_SAMPLE];
+    const float *row = table + (int64_t)blockIdx.x * ld;
+    const int32_t m = n < AP_FLOOR_SAMPLE ? (int32_t)n : AP_FLOOR_SAMPLE;
+    for (int32_t i = threadIdx.x; i < AP_FLOOR_SAMPLE; i += 256) {
+        const int64_t d = n <= AP_FLOOR_SAMPLE ? i : (i >> 6) * ((n - 64) / 63) + (i & 63);
+        float x = i < m ? row[d] : -INFINITY;
+        if (!(x < INFINITY)) x = -INFINITY;   // says nothing about the scores
+        keys[i] = i < m ? ((uint64_t)ap_f2ord(x) << 32) | (uint32_t)(i + 1) : 0ull;
+    }
+    int32_t n2 = 64;
+    while (n2 < m) n2 <<= 1;
+    ap_bitonic_desc(keys, n2);
+    if (threadIdx.x == 0) {
+        const int32_t at = (int32_t)(share * (float)m);
+        out[blockIdx.x] = at < m ? ap_key_score(keys[at]) : -INFINITY;
+    }
+}
+
+// The floors of the slab's queries for a pool of `beam` entries: as if the documents a search meets were drawn at random,
+// with a quarter of the pool on top; they are better than that, so the pool's last score usually ends above it.
+int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st) {
+    const double n = (double)ix->docs.n, met = n * (1.0 - exp(-(double)beam * ix->params.degree / n));
+    const double share = g_ap_debug.search_floor == 2 ? 0.002 : std::min(1.0, 1.25 * beam / met);
+    hipLaunchKernelGGL(k_bound_floor, dim3((unsigned)nq), dim3(256), 0, st, b.table, b.ld, ix->docs.n, (float)share, b.floor);
+    AP_CHECK_HIP(hipGetLastError());
+    return AP_OK;
+}
+
 // Bytes of the workspace a slab of nq queries takes.
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq) {
     const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
-    return rows * k * 2 + rows * 16 + (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
+    return rows * k * 2 + rows * 16 + rows * 4 + (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
 }
 
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b) {
@@ -412,6 +445,7 @@ void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b) {
     char *m = static_cast<char *>(base);
     b->qm = reinterpret_cast<uint16_t *>(m); m += rows * k * 2;
     b->qc = reinterpret_cast<float4 *>(m); m += rows * 16;
+    b->floor = reinterpret_cast<float *>(m); m += rows * 4;
     b->table = reinterpret_cast<float *>(m);
     b->ld = (int64_t)ap_up((size_t)ix->docs.n, 64);
     b->slab = (int32_t)nq;

@@ -137,6 +137,7 @@ struct ApDebug {
     int64_t search_visited_global = 0;   // 1: the searches' visited sets stay in global memory even where they would fit LDS
     int64_t search_query_lists = 0;      // 1: the searches look the query's terms up in its lists (the path of queries too long for the LDS tables)
     int64_t search_bounds = 0;           // 1: searches without the table of upper bounds, 2: with it whatever it costs
+    int64_t search_floor = 0;            // 1: no neighbour waits below a floor, 2: the floor is far too high (forces the scan of what waits)
     int64_t search_workspace_bytes = 0;  // cap of the search's visited-set workspace (forces searches in several slabs of queries)
 };
 extern ApDebug g_ap_debug;
@@ -188,6 +189,7 @@ struct ApBound {
     int64_t ld = 0;            // documents, padded
     uint16_t *qm = nullptr;    // the slab's queries as bf16 rows
     float4 *qc = nullptr;      // per query: what the slack of its row is made of
+    float *floor = nullptr;    // per query: an estimate of the last score of a pool (ap_bound_floors)
     int32_t slab = 0;          // queries the workspace holds
     std::unique_lock<std::mutex> hold;   // of the index's workspaces, until everything that uses this one is enqueued
 };
@@ -210,6 +212,7 @@ void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b);
 int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b);
 int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
                   const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);
+int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st);
 // sizes the workspace an index owns (grow only, capped) for a call of nq queries (ap_search.hip)
 int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds);
 bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters);

@@ -53,7 +53,7 @@ def test_searches_with_and_without_bounds_are_the_same(debug_knobs, base, n, dim
     pw = np.random.default_rng(5).uniform(-0.3, 1.0, (qs.n, 3)).astype(np.float32)
     kw = make_keywords(w.queries, seed=6, max_terms=3, stride=4, p_none=0.1)
     kw[3] = [-1, 2 ** 30, w.docs.tx_vocab, -5]     # terms that no document can hold
-    for k, beam, width, iters in ((10, 16, 1, 0), (5, 64, 3, 0), (10, 200, 16, 7), (1, 1, 1, 0), (10, n + 50, 16, 0)):
+    for k, beam, width, iters in ((10, 16, 1, 0), (5, 64, 3, 0), (10, 200, 16, 7), (1, 1, 1, 0), (10, 150, 2, 0), (10, n + 50, 16, 0)):
         got = {}
         for mode in (1, 2):
             debug_knobs("search_bounds", mode)
@@ -73,6 +73,27 @@ def test_searches_with_and_without_bounds_are_the_same(debug_knobs, base, n, dim
     debug_knobs("search_workspace_bytes", 9 * 4 * ((n + 31) // 32))
     for _ in range(2):
         assert all(torch.equal(a, b) for a, b in zip(ref, ix.search_batch(qs, 10, 64, pw)))
+    ix.close()
+
+
+@pytest.mark.parametrize("base,n,dim", [("tiny", 6007, 96), ("cfg3", 6100, 256)])
+def test_large_pools_with_a_floor_are_the_same(debug_knobs, base, n, dim):
+    """Workgroups of 512 and 1,024 threads: without bounds; with them and a floor; no neighbour waits; the floor is so high
+    that everything that waits has to be scanned for (in several rounds: more waits than the candidates' array holds)."""
+    w, docs, qs = _workload(base, n=n, nq=33, dim=dim, vocab=5_000)
+    ix = B.Index.build(docs, B.build_params(64, nd_rounds=1, n_entry=16))
+    pw = np.random.default_rng(5).uniform(-0.2, 1.0, (qs.n, 3)).astype(np.float32)
+    for k, beam, width, iters in ((10, 800, 16, 0), (10, 900, 16, 9), (1, 4300, 2, 0), (50, 5900, 16, 0), (10, 9000, 16, 0), (10, 12000, 1, 0)):
+        got = {}
+        for mode, floor in ((1, 0), (2, 0), (2, 1), (2, 2)):
+            debug_knobs("search_bounds", mode)
+            debug_knobs("search_floor", floor)
+            out = list(ix.search_batch(qs, k, beam, pw, search_width=width, max_iters=iters))
+            got[mode, floor] = [t.clone() for t in out] + [ix.search_stats(qs.n)[0][:, :2].clone()]
+        debug_knobs("search_bounds", 0)
+        debug_knobs("search_floor", 0)
+        for key in got:
+            assert all(torch.equal(a, b) for a, b in zip(got[1, 0], got[key])), (key, k, beam, width, iters)
     ix.close()
 
 
