@@ -215,6 +215,8 @@ struct ApKgArgs {
     int32_t ent_stride, max_hops, n_ent;
     float w_k;
     const uint32_t *deleted;   // one bit per document, NULL when nothing was ever deleted
+    const float *bound;        // upper bounds of the scores (without rewards), a row of bound_ld documents per query of the slab; NULL: none
+    int64_t bound_ld;
 };
 
 // annotation of a pool entry: (entity + 1) << 8 | hop; 0 = no entity
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(256) void k_search_kg(ApKgArgs g) {
     uint32_t *cura = reinterpret_cast<uint32_t *>(s_meta + g.cmax);   // annotations of the pool entries
     uint32_t *canda = cura + g.L;                                      // annotations of the candidates
     int32_t *cand = reinterpret_cast<int32_t *>(canda + g.cmax);
-    __shared__ int32_t s_cnt, s_par, s_pann, s_seed[2], s_len, s_skip;
+    __shared__ int32_t s_cnt, s_par, s_pann, s_seed[2], s_len, s_skip, s_drop;
     const int64_t q = (int64_t)g.q0 + blockIdx.x;
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
     ApLists a;
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(256) void k_search_kg(ApKgArgs g) {
         qnorm = sqrtf(ap_wave_sum(p));
     }
     uint32_t *vis = g.visited + (size_t)blockIdx.x * g.words;
-    if (threadIdx.x == 0) { s_len = 0; s_skip = 0; }
+    if (threadIdx.x == 0) { s_len = 0; s_skip = 0; s_drop = 0; }
     if (threadIdx.x == 0) {
         // the documents that mention the query's entities, in the order of the entities then ascending id, at most E
         int32_t c = 0;
@@ -310,6 +312,8 @@ __global__ __launch_bounds__(256) void k_search_kg(ApKgArgs g) {
     int32_t len = 0, it = 0, nscored = 0;   // len is kept by wave 0, the only one that touches the pool
     int32_t fu = 0;                          // (wave 0) every pool entry before this position has been expanded
     int32_t nskipped = 0;
+    int32_t ndropped = 0;                    // per lane: neighbours their bound kept out
+    const uint32_t *bound = reinterpret_cast<const uint32_t *>(g.bound) + (g.bound ? (int64_t)blockIdx.x * g.bound_ld : 0);
     for (;;) {
         const int32_t c = s_cnt;
         nscored += c;
@@ -403,6 +407,12 @@ __global__ __launch_bounds__(256) void k_search_kg(ApKgArgs g) {
         const int32_t eu = pann ? (int32_t)(pann >> 8) - 1 : -1, hu = (int32_t)(pann & 0xffu);
         const bool logical = eu >= 0 && hu < g.max_hops;
         const int32_t nle = logical ? g.le_count[u] : 0;
+        // While the pool is full, a neighbour whose bound and the largest reward its parent can hand on do not reach the
+        // pool's last score is only marked visited: its entities, record and dense row are not read.
+        const bool bound_on = g.bound && s_len == g.L;   // uniform
+        const float b_worst = bound_on ? ap_key_score(cur[g.L - 1]) : 0.f;
+        const float most = eu >= 0 && hu < 255 ? fabsf(g.w_k) / (float)(hu + 1) : fabsf(g.w_k);
+        const float b_reward = eu >= 0 ? most : 0.f;
         for (int32_t i = threadIdx.x; i < g.R + nle; i += blockDim.x) {
             int32_t v = -1;
             if (i < g.R) v = g.graph[(int64_t)u * g.R + i];
@@ -414,6 +424,10 @@ __global__ __launch_bounds__(256) void k_search_kg(ApKgArgs g) {
                 const uint32_t bit = 1u << (v & 31);
                 const uint32_t old = atomicOr(&vis[v >> 5], bit);
                 if (!(old & bit)) {
+                    if (bound_on) {
+                        const float ub = __uint_as_float(bound[v] & ~AP_BOUND_COUNT);
+                        if (ub + b_reward + 1e-5f * (fabsf(ub) + b_reward) < b_worst) { ndropped++; continue; }
+                    }
                     uint32_t an = 0u;
                     if (eu >= 0) { const int32_t t = ap_related_entity(g, v, eu); if (t >= 0) an = ap_ann(t, hu + 1); }
                     const int32_t pos = atomicAdd(&s_cnt, 1);
@@ -425,8 +439,9 @@ __global__ __launch_bounds__(256) void k_search_kg(ApKgArgs g) {
         it++;
     }
     if (lane == 0) atomicAdd(&s_skip, nskipped);
+    if (ndropped) atomicAdd(&s_drop, ndropped);
     __syncthreads();
-    if (threadIdx.x == 0) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = s_skip; }
+    if (threadIdx.x == 0) { g.counts[q * 3] = nscored + s_drop; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = s_skip + s_drop; }
     // the best k pool entries; mark-deleted documents were searched through like any other and are left out here
     if (wave == 0) {
         int32_t o = 0;
@@ -476,13 +491,14 @@ extern "C" int ap_search_batch_entities(ap_index *ix, const ap_queries *q, const
     g.cmax = std::max(g.E, g.R + ix->kg_le_cap);
     g.words = ((size_t)ix->docs.n + 31) / 32;
     ApSearchWs ws;
-    AP_TRY(ap_search_reserve(ix, nq, st, &ws, false));
+    AP_TRY(ap_search_reserve(ix, nq, st, &ws, ap_bound_pays(ix, nq, p->beam, 1, p->max_iters)));
     g.visited = ws.visited; g.out_ids = out_ids; g.out_scores = out_scores; g.counts = ws.counts;
     g.rec = ix->rec; g.meta = ix->meta;
     g.de_ip = ix->kg_de_ip; g.de = ix->kg_de; g.kg_ip = ix->kg_ip; g.kg = ix->kg_idx; g.en_ip = ix->kg_en_ip; g.en = ix->kg_en;
     g.le = ix->kg_le; g.le_count = ix->kg_le_count; g.le_cap = ix->kg_le_cap;
     g.q_ent = q_ent; g.ent_stride = ent_stride; g.max_hops = max_hops; g.w_k = w_k;
     g.n_ent = ix->kg_n_ent; g.deleted = ix->deleted;
+    g.bound = ws.bound.table; g.bound_ld = ws.bound.ld;
     const size_t smem = (size_t)(g.L + g.cmax) * 8 + ((1 << AP_KG_SPB) + (1 << AP_KG_TXB)) * 8 + 8 + (size_t)g.cmax * 16 +
                         (size_t)(g.L + 2 * g.cmax) * 4;
     AP_REQUIRE(smem <= 160 * 1024, "beam needs %zu bytes of LDS (limit 160 KiB)", smem);
@@ -491,6 +507,7 @@ extern "C" int ap_search_batch_entities(ap_index *ix, const ap_queries *q, const
         g.q0 = q0;
         AP_TRY(ap_fill_u32(ws.visited, g.words * (size_t)qn, 0u, st));
         if (q0 == 0) AP_CHECK_HIP(hipEventRecord(ws.ev0, st));
+        if (ws.bound.table) AP_TRY(ap_bound_fill(ix, ws.bound, g.Q, g.w, g.w_stride, q0, qn, nullptr, 0, st));
         hipError_t le = hipSuccess;
         AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, {
             if (smem > 48 * 1024)

@@ -136,3 +136,20 @@ def test_exact_topk_out_of_the_bounds(base, n, dim, k):
         want, at = torch.sort(all_sc, dim=1, descending=True, stable=True)    # equal scores: smaller id first
         assert torch.equal(sc, want[:, :k]) and torch.equal(ids, at[:, :k].to(torch.int32))
     ix.close()
+
+
+@pytest.mark.parametrize("w_k", [0.5, -0.4, 0.0])
+def test_entity_searches_with_and_without_bounds_are_the_same(debug_knobs, w_k):
+    from paper_2511_00855_amd.synth import make_entity_graph
+    w, docs, qs = _workload("tiny", n=2500, nq=60)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=2, n_entry=16))
+    kgs = make_entity_graph(2500, 60, seed=9, n_ent=300)
+    ix.set_knowledge_graph(kgs, le_cap=16)
+    pw = np.random.default_rng(5).uniform(-0.2, 1.0, (qs.n, 3)).astype(np.float32)
+    for k, beam, hops in ((10, 16, 2), (5, 200, 0), (1, 64, 255)):
+        got = []
+        for mode in (1, 2):
+            debug_knobs("search_bounds", mode)
+            got.append([t.clone() for t in ix.search_batch_entities(qs, k, beam, kgs.q_ent, w_k, hops, pw)] + [ix.search_stats(qs.n)[0][:, :2].clone()])
+        assert all(torch.equal(a, b) for a, b in zip(*got)), (k, beam, hops)
+    ix.close()
