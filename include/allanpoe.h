@@ -358,6 +358,7 @@ int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
  *   "seed_buffer_cap"         capacity of a row's candidate buffer in that sweep (forces the overflow fallback)
  *   "seed_tau_ulps"           raises every row's threshold by this many ulps (forces the short-row fallback)
  *   "seed_one_sided"          1: whole-corpus seed lists by the one-sided sweep instead of the symmetric one
+ *   "prune_walks"             1: neighbourhood similarities by list walks even where the matrix product applies
  *   "max_launch_threads"      a multiple of 1024: launches that grow with the corpus run in slices of this many threads
  *   "search_workspace_bytes"  cap of the searches' visited-set workspace (forces searches in several slabs of queries)
  *   "search_bounds"           1: searches score every neighbour they meet, 2: they always sort neighbours out by the bounds

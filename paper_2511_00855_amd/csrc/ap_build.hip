@@ -1247,6 +1247,192 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
     out[(int64_t)j * K + i] = val;
 }
 
+// The same products as matrix products.  What bounds the walks above is instruction issue: some 330 steps of 13
+// instructions per pair, nearly all of them over terms the other list does not hold.  Here the K lists of a neighbourhood
+// are turned into columns instead: a term that only one of the K documents holds contributes to no pair and is dropped; the
+// others (some 2,000 of a neighbourhood of 128) are numbered in ascending order, and the K x T matrix of their weights is
+// multiplied with its transpose by f32 MFMAs, 64 columns at a time.  Same f32 products and sums (an absent term adds exactly
+// 0); only the order of a sum's terms differs.
+//
+// One workgroup of 16 waves per node; per vocabulary:
+//  - a wave loads the lists of its 8 documents into registers (3 entries a lane: 192 a list; what a longer list holds beyond
+//    that is read again for every chunk);
+//  - two bitmaps over the vocabulary in LDS mark terms met and terms met twice; the number of set bits before a term's in
+//    the second is its column;
+//  - a wave writes its 8 rows of a chunk (cleared, then the entries whose column falls into it), into one of two stages,
+//    while the other stage is multiplied: one barrier a chunk.
+// The lower triangle of the result is 36 blocks of 16 x 16 (K = 128): two a wave and four more on the first four waves, nine
+// on every SIMD.
+#define AP_GL_WORDS 8192          // words of a bitmap: vocabularies up to 2^18 terms
+#define AP_GL_C 64                // columns of a chunk
+#define AP_GL_STRIDE (AP_GL_C + 4)   // rows 16-byte aligned; 16 rows x 4 groups of 4 columns fall into distinct banks
+#define AP_GL_SLOTS 3             // list entries a lane holds in registers
+#define AP_GL_LDS (2 * AP_GL_WORDS * 4 + 2 * 128 * AP_GL_STRIDE * 4)
+typedef float ap_f32x4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ rec, const uint4 *__restrict__ meta, float wd, float ws, float wf,
+                                                     int32_t sp_words, int32_t tx_words, int32_t K, const int32_t *__restrict__ knn,
+                                                     const int32_t *__restrict__ node_ids, int64_t x0, float *__restrict__ pm) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t gl_lds[];
+    uint32_t *seen = gl_lds, *twice = gl_lds + AP_GL_WORDS;   // seen: afterwards the columns before each word's terms
+    float *X = reinterpret_cast<float *>(gl_lds + 2 * AP_GL_WORDS);   // two stages of 128 x AP_GL_STRIDE
+    __shared__ int32_t s_id[128], s_sn[128], s_tn[128];
+    __shared__ uint32_t s_first[128], s_part[16], s_total;
+    __shared__ float s_diag[2][128];
+    const int64_t x = blockIdx.x;
+    const int64_t u = node_ids ? (int64_t)node_ids[x0 + x] : x0 + x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = ap_wave_id();
+    if (tid < 128) {
+        const int32_t id = tid < K ? knn[u * K + tid] : -1;
+        uint4 m = make_uint4(0, 0, 0, 0);
+        if (id >= 0) m = meta[id];
+        s_id[tid] = id; s_first[tid] = m.x; s_sn[tid] = (int32_t)(m.y & 0xffffu); s_tn[tid] = (int32_t)(m.y >> 16);
+    }
+    const int32_t blocks = (K + 15) / 16, n_tasks = blocks * (blocks + 1) / 2;
+    // this wave's blocks of the lower triangle: tasks wave, wave + 16, wave + 32
+    int32_t bi[3], bj[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        int32_t p = wave + 16 * a, i = 0;
+        while (p > i) { p -= i + 1; i++; }
+        bi[a] = i; bj[a] = p;
+    }
+    ap_f32x4 acc[2][3];
+#pragma unroll
+    for (int part = 0; part < 2; part++)
+#pragma unroll
+        for (int a = 0; a < 3; a++) acc[part][a] = ap_f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+    for (int part = 0; part < 2; part++) {
+        const int32_t words = part ? tx_words : sp_words;
+        for (int32_t i = tid * 4; i < words; i += 4096) {   // words is a multiple of 4
+            *reinterpret_cast<uint4 *>(seen + i) = make_uint4(0, 0, 0, 0);
+            *reinterpret_cast<uint4 *>(twice + i) = make_uint4(0, 0, 0, 0);
+        }
+        uint2 ent[8][AP_GL_SLOTS];   // (term, then column; weight)
+#pragma unroll
+        for (int d = 0; d < 8; d++) {
+            const int32_t row = wave * 8 + d, len = part ? s_tn[row] : s_sn[row];
+            const uint2 *r = rec + s_first[row] + (part ? s_sn[row] : 0);
+#pragma unroll
+            for (int k = 0; k < AP_GL_SLOTS; k++) ent[d][k] = lane + 64 * k < len ? r[lane + 64 * k] : make_uint2(0xffffffffu, 0u);
+        }
+        __syncthreads();   // the bitmaps are clear
+        auto mark = [&](uint32_t t) {
+            const uint32_t bit = 1u << (t & 31);
+            if (atomicOr(&seen[t >> 5], bit) & bit) atomicOr(&twice[t >> 5], bit);
+        };
+#pragma unroll
+        for (int d = 0; d < 8; d++) {
+            const int32_t row = wave * 8 + d, len = part ? s_tn[row] : s_sn[row];
+            float own = 0.f;
+#pragma unroll
+            for (int k = 0; k < AP_GL_SLOTS; k++) {
+                const float v = __uint_as_float(ent[d][k].y);
+                own = fmaf(v, v, own);
+                if (ent[d][k].x != 0xffffffffu) mark(ent[d][k].x);
+            }
+            const uint2 *r = rec + s_first[row] + (part ? s_sn[row] : 0);
+            for (int32_t e = 64 * AP_GL_SLOTS + lane; e < len; e += 64) {
+                const uint2 y = r[e];
+                own = fmaf(__uint_as_float(y.y), __uint_as_float(y.y), own);
+                mark(y.x);
+            }
+            own = ap_wave_sum(own);
+            if (lane == 0) s_diag[part][row] = own;
+        }
+        __syncthreads();
+        // columns before each word: eight words a thread
+        {
+            uint32_t cnt[8], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 8; k++) { cnt[k] = tid * 8 + k < words ? (uint32_t)__popc(twice[tid * 8 + k]) : 0u; sum += cnt[k]; }
+            uint32_t upto = sum;
+            for (int o = 1; o < 64; o <<= 1) { const uint32_t up = __shfl_up(upto, o, 64); if (lane >= o) upto += up; }
+            if (lane == 63) s_part[wave] = upto;
+            __syncthreads();
+            uint32_t base = 0;
+            for (int w = 0; w < wave; w++) base += s_part[w];
+            base += upto - sum;
+#pragma unroll
+            for (int k = 0; k < 8; k++) { if (tid * 8 + k < words) seen[tid * 8 + k] = base; base += cnt[k]; }
+            if (tid == 1023) s_total = base;
+        }
+        __syncthreads();
+        auto column = [&](uint32_t t) -> uint32_t {
+            const uint32_t m = twice[t >> 5], bit = 1u << (t & 31);
+            return m & bit ? seen[t >> 5] + (uint32_t)__popc(m & (bit - 1u)) : 0xffffffffu;
+        };
+#pragma unroll
+        for (int d = 0; d < 8; d++)
+#pragma unroll
+            for (int k = 0; k < AP_GL_SLOTS; k++)
+                if (ent[d][k].x != 0xffffffffu) ent[d][k].x = column(ent[d][k].x);
+        const int32_t n_chunks = ((int32_t)ap_uniform_u32(s_total) + AP_GL_C - 1) / AP_GL_C;
+        auto scatter = [&](int32_t c) {
+            float *rows = X + (c & 1) * 128 * AP_GL_STRIDE + wave * 8 * AP_GL_STRIDE;
+            for (int32_t i = lane * 4; i < 8 * AP_GL_STRIDE; i += 256) *reinterpret_cast<float4 *>(rows + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+            ap_wave_sync();
+            const uint32_t c0 = (uint32_t)c * AP_GL_C;
+#pragma unroll
+            for (int d = 0; d < 8; d++) {
+#pragma unroll
+                for (int k = 0; k < AP_GL_SLOTS; k++) {
+                    const uint32_t at = ent[d][k].x - c0;   // no column (2^32 - 1): beyond every chunk
+                    if (at < AP_GL_C) rows[d * AP_GL_STRIDE + at] = __uint_as_float(ent[d][k].y);
+                }
+                const int32_t row = wave * 8 + d, len = part ? s_tn[row] : s_sn[row];
+                if (len > 64 * AP_GL_SLOTS) {   // uniform
+                    const uint2 *r = rec + s_first[row] + (part ? s_sn[row] : 0);
+                    for (int32_t e = 64 * AP_GL_SLOTS + lane; e < len; e += 64) {
+                        const uint2 y = r[e];
+                        const uint32_t at = column(y.x) - c0;
+                        if (at < AP_GL_C) rows[d * AP_GL_STRIDE + at] = __uint_as_float(y.y);
+                    }
+                }
+            }
+        };
+        if (n_chunks > 0) scatter(0);
+        __syncthreads();
+        for (int32_t c = 0; c < n_chunks; c++) {
+            if (c + 1 < n_chunks) scatter(c + 1);
+            // lane l feeds column 16 kk + 4 (l / 16) + m of row l % 16 to the m-th of four MFMAs
+            const float *stage = X + (c & 1) * 128 * AP_GL_STRIDE + (lane & 15) * AP_GL_STRIDE + (lane >> 4) * 4;
+#pragma unroll
+            for (int kk = 0; kk < AP_GL_C / 16; kk++)
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    if (wave + 16 * a >= n_tasks) continue;   // uniform
+                    const ap_f32x4 va = *reinterpret_cast<const ap_f32x4 *>(stage + bi[a] * 16 * AP_GL_STRIDE + kk * 16);
+                    const ap_f32x4 vb = *reinterpret_cast<const ap_f32x4 *>(stage + bj[a] * 16 * AP_GL_STRIDE + kk * 16);
+#pragma unroll
+                    for (int m = 0; m < 4; m++) {
+                        if (part) acc[1][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[m], vb[m], acc[1][a], 0, 0, 0);
+                        else acc[0][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[m], vb[m], acc[0][a], 0, 0, 0);
+                    }
+                }
+            __syncthreads();
+        }
+    }
+    // element r of a lane's four: row 4 (l / 16) + r, column l % 16 of its block
+    float *out = pm + x * (int64_t)K * K;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        if (wave + 16 * a >= n_tasks) continue;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int32_t i = bi[a] * 16 + 4 * (lane >> 4) + r, j = bj[a] * 16 + (lane & 15);
+            if (i >= K || j > i) continue;
+            float val = -INFINITY;
+            if (s_id[i] >= 0 && s_id[j] >= 0) {
+                const float qs = i == j ? s_diag[0][i] : acc[0][a][r], qt = i == j ? s_diag[1][i] : acc[1][a][r];
+                val = fmaf(wd, out[(int64_t)i * K + j], fmaf(wf, qt, ws * qs));
+            }
+            out[(int64_t)i * K + j] = val;
+            out[(int64_t)j * K + i] = val;
+        }
+    }
+}
+
 // =================================================================== S4 + S5: detour sort, IP prune, keyword flags
 // Detourable routes (Section 3.3): A -> X -> Y detours A -> Y iff
 // min(sim(A,X), sim(X,Y)) > sim(A,Y).  Neighbours are stably sorted by their
@@ -1420,6 +1606,10 @@ int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_i
     const float *w = ix->params.build_w;
     const int32_t tiles = (K + AP_TILE - 1) / AP_TILE;
     hipError_t e = hipSuccess;
+    // By columns where a workgroup can hold the neighbourhood's rows and both bitmaps; the walks for longer lists of
+    // neighbours and larger vocabularies.
+    const bool by_columns = K <= 128 && std::max(ix->corpus.sp_vocab, ix->corpus.tx_vocab) <= AP_GL_WORDS * 32 && !g_ap_debug.prune_walks;
+    if (by_columns) e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gram_lists), hipFuncAttributeMaxDynamicSharedMemorySize, AP_GL_LDS);
     for (int64_t x0 = 0; x0 < nn && e == hipSuccess; x0 += chunk) {
         const int64_t cn = std::min(chunk, nn - x0);
         float *pm = pm_out ? pm_out + x0 * per : scratch;
@@ -1432,6 +1622,12 @@ int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_i
                 hipLaunchKernelGGL(k_gram_dense<AP_BF16>, g1, dim3(256), 0, st, ix->docs.dense, ix->docs.dim, K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
             e = hipGetLastError();
             if (e != hipSuccess) break;
+            if (by_columns) {
+                hipLaunchKernelGGL(k_gram_lists, dim3((unsigned)yn), dim3(1024), AP_GL_LDS, st, ix->rec, ix->meta, w[0], w[1], w[2],
+                                   (ix->corpus.sp_vocab + 127) / 128 * 4, (ix->corpus.tx_vocab + 127) / 128 * 4, K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
+                e = hipGetLastError();
+                continue;
+            }
             const int32_t tb = (K + AP_GT - 1) / AP_GT;
             dim3 g2((unsigned)(tb * (tb + 1) / 2), (unsigned)yn);
             hipLaunchKernelGGL(k_gram_merge, g2, dim3(256), 0, st, ix->rec, ix->meta, w[0], w[1], w[2], K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
