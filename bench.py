@@ -381,16 +381,23 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
     n_dist, n_iter, n_skip = int(counts[:, 0].sum()), int(counts[:, 1].sum()), int(counts[:, 2].sum())
 
     # ---- roofline of the search kernel: algorithmic bytes / measured kernel time.  Units per launch: full similarities
-    # (descriptor + lists + dense row), partial ones (the candidate provably cannot enter the pool: no dense row), and
-    # one adjacency row per iteration (at least one parent is expanded in every iteration).
-    bytes_per_launch = (n_dist - n_skip) * bytes_per_dist + n_skip * partial_bytes + n_iter * w.degree * 4.0
+    # (descriptor + lists + dense row), partial ones (the document provably cannot enter the pool: its 4-byte bound), one
+    # adjacency row per iteration (at least one parent is expanded in every iteration), and the table of bounds itself, which
+    # the kernel time includes: every document once, every bound written.
+    partial_bytes = 4.0
+    bytes_per_launch = (n_dist - n_skip) * bytes_per_dist + n_skip * partial_bytes + n_iter * w.degree * 4.0 + N * bytes_per_dist + 4.0 * N * nq
     bytes_if_all_full = n_dist * bytes_per_dist + n_iter * w.degree * 4.0
     k_ms = float(np.mean(kernel_ms))
     achieved = bytes_per_launch / (k_ms * 1e-3) / 1e9
     traffic = None
     tfile = os.path.join(ROOT, "profiles", f"k_search_{name}_beam{beam}_w{width}_traffic.json")
     if os.path.exists(tfile) and N == cfg["n"] and nq == cfg["nq"]:
-        t = json.load(open(tfile))     # HBM-side bytes per launch from the committed rocprofv3 --pmc summary of this same configuration
+        t = json.load(open(tfile))
+        if not t.get("with_bounds"):   # counters of the search that scores every neighbour say nothing about this one
+            t = None
+    else:
+        t = None
+    if t is not None:   # HBM-side bytes per launch from the committed rocprofv3 --pmc summary of this same configuration
         traffic = round(t["fetch_bytes_per_launch"] + t["write_bytes_per_launch"])
     roofline = dict(bound="hbm", kernel="k_search", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic, kernel_ms=round(k_ms, 3),
