@@ -6,7 +6,7 @@
 //
 // The dense part and the most frequent terms of both vocabularies (the "head": at most AP_BOUND_HEAD columns) are one
 // bf16 matrix product; the remaining terms (the "tail") are added from postings.  Rounding to bf16 is paid for by a
-// slack per pair, so nothing that decides a result depends on the product's precision: a candidate the bound lets
+// slack per pair, made of what it took off the two sides, so nothing that decides a result depends on the product's precision: a candidate the bound lets
 // through is scored as ever, and one it stops could not have entered.
 #include <math.h>
 #include <algorithm>
@@ -83,20 +83,27 @@ __global__ __launch_bounds__(1024) void k_bd_pick(const int32_t *__restrict__ df
 
 __device__ __forceinline__ uint32_t ap_bf16_bits(float f) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f); }   // to nearest even
 
-// One wave per document: its bound row (dense part rounded to bf16 if kd > 0, then the head columns), the norms of
-// the head columns of either vocabulary, its postings, and its bit in the bitmaps of the lexical head terms it holds.
+__device__ __forceinline__ float ap_bf16_value(uint32_t bits) { return __uint_as_float(bits << 16); }
+
+// One wave per document: its bound row (dense part rounded to bf16 if kd > 0, then the head columns), what the slack of its
+// column is made of, its postings, and its bit in the bitmaps of the lexical head terms it holds.  norms: planes of n
+// entries for the dense part and the head columns of either vocabulary, each the norm of what rounding to bf16 took off the
+// part (exact differences: a value and its rounding lie within a factor of two) and the part's own norm.
 template <int DT>
 __global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const int32_t *__restrict__ col, const uint2 *__restrict__ run,
                                                  uint32_t *__restrict__ cursor, int32_t kd, int32_t kh, uint16_t *__restrict__ rows,
-                                                 uint2 *__restrict__ post, float2 *__restrict__ hn, uint32_t *__restrict__ bits, int64_t words) {
+                                                 uint2 *__restrict__ post, const float *__restrict__ dnorm, float2 *__restrict__ norms, uint32_t *__restrict__ bits,
+                                                 int64_t words) {
     __shared__ __attribute__((aligned(16))) uint16_t s_head[4][AP_BOUND_HEAD];
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
     uint16_t *head = s_head[wave];
     const int32_t ld = kd + kh;
     for (int64_t v = blockIdx.x * (int64_t)4 + wave; v < D.n; v += (int64_t)gridDim.x * 4) {
         uint16_t *row = rows + v * ld;
+        float sum[2] = {0.f, 0.f}, lost[3] = {0.f, 0.f, 0.f};
         for (int32_t c = lane * 4; c < kd; c += 256) {
             float x[4] = {0.f, 0.f, 0.f, 0.f};
+            uint32_t y16[4];
             if (c < D.dim) {   // dim is a multiple of 4
                 if (DT == AP_F32) {
                     const float4 y = *reinterpret_cast<const float4 *>(static_cast<const float *>(D.dense) + v * D.dim + c);
@@ -105,11 +112,16 @@ __global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const in
                     for (int e = 0; e < 4; e++) x[e] = __uint_as_float((uint32_t)static_cast<const uint16_t *>(D.dense)[v * D.dim + c + e] << 16);
                 }
             }
-            *reinterpret_cast<uint2 *>(row + c) = make_uint2(ap_bf16_bits(x[0]) | (ap_bf16_bits(x[1]) << 16), ap_bf16_bits(x[2]) | (ap_bf16_bits(x[3]) << 16));
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                y16[e] = ap_bf16_bits(x[e]);
+                const float off = x[e] - ap_bf16_value(y16[e]);
+                lost[0] = fmaf(off, off, lost[0]);
+            }
+            *reinterpret_cast<uint2 *>(row + c) = make_uint2(y16[0] | (y16[1] << 16), y16[2] | (y16[3] << 16));
         }
         for (int32_t c = lane * 8; c < kh; c += 512) *reinterpret_cast<uint4 *>(head + c) = make_uint4(0, 0, 0, 0);
         ap_wave_sync();
-        float sum[2] = {0.f, 0.f};
         for (int part = 0; part < 2; part++) {
             const int64_t b = part ? D.tx_indptr[v] : D.sp_indptr[v], e = part ? D.tx_indptr[v + 1] : D.sp_indptr[v + 1];
             for (int64_t p = b + lane; p < e; p += 64) {
@@ -117,7 +129,9 @@ __global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const in
                 const float x = part ? D.tx_val[p] : D.sp_val[p];
                 const int32_t c = col[t];
                 if (c >= 0) {
-                    head[c] = (uint16_t)ap_bf16_bits(x); sum[part] = fmaf(x, x, sum[part]);
+                    const uint32_t h = ap_bf16_bits(x);
+                    const float off = x - ap_bf16_value(h);
+                    head[c] = (uint16_t)h; sum[part] = fmaf(x, x, sum[part]); lost[1 + part] = fmaf(off, off, lost[1 + part]);
                     if (part) atomicOr(&bits[c * words + (v >> 5)], 1u << (v & 31));
                 } else post[run[t].x + atomicAdd(&cursor[t], 1u)] = make_uint2((uint32_t)v, __float_as_uint(x));
             }
@@ -125,7 +139,12 @@ __global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const in
         ap_wave_sync();
         for (int32_t c = lane * 8; c < kh; c += 512) *reinterpret_cast<uint4 *>(row + kd + c) = *reinterpret_cast<const uint4 *>(head + c);
         const float hs = ap_wave_sum(sum[0]), hf = ap_wave_sum(sum[1]);
-        if (lane == 0) hn[v] = make_float2(sqrtf(hs), sqrtf(hf));
+        for (int p = 0; p < 3; p++) lost[p] = ap_wave_sum(lost[p]);
+        if (lane == 0) {
+            norms[v] = make_float2(sqrtf(lost[0]), dnorm[v]);
+            norms[D.n + v] = make_float2(sqrtf(lost[1]), sqrtf(hs));
+            norms[2 * D.n + v] = make_float2(sqrtf(lost[2]), sqrtf(hf));
+        }
         ap_wave_sync();
     }
 }
@@ -148,7 +167,7 @@ int ap_bound_ingest(ap_index *ix, hipStream_t st) {
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t a = at; at += ap_up(bytes, 256); return a; };
     const size_t o_clear = take(n_clear * 4), o_col = take((size_t)all * 4), o_run = take((size_t)all * 8), o_post = take((nnz + 1) * 8),
-                 o_hn = take((size_t)c.n * 8), o_rows = take((size_t)c.n * (size_t)(kd + kh) * 2);
+                 o_norms = take((size_t)c.n * 24), o_rows = take((size_t)c.n * (size_t)(kd + kh) * 2);
     if (at > ((size_t)1 << 30)) {
         size_t free_b = 0, total_b = 0;
         if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || at > free_b / 4) { (void)hipGetLastError(); return AP_OK; }
@@ -163,7 +182,7 @@ int ap_bound_ingest(ap_index *ix, hipStream_t st) {
     ix->bd_col = reinterpret_cast<int32_t *>(m + o_col);
     ix->bd_run = reinterpret_cast<uint2 *>(m + o_run);
     ix->bd_post = reinterpret_cast<uint2 *>(m + o_post);
-    ix->bd_hn = reinterpret_cast<float2 *>(m + o_hn);
+    ix->bd_norms = reinterpret_cast<float2 *>(m + o_norms);
     ix->bd_rows = reinterpret_cast<uint16_t *>(m + o_rows);
     ix->bd_bits = misc + 2;
     ix->bd_kd = kd; ix->bd_kh = kh;
@@ -175,9 +194,9 @@ int ap_bound_ingest(ap_index *ix, hipStream_t st) {
                        ix->bd_run, misc);
     const dim3 g((unsigned)std::min<int64_t>((c.n + 3) / 4, 4096));
     if (ix->dtype == AP_F32)
-        hipLaunchKernelGGL(k_bd_rows<AP_F32>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->bd_hn, ix->bd_bits, words);
+        hipLaunchKernelGGL(k_bd_rows<AP_F32>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->dense_norm, ix->bd_norms, ix->bd_bits, words);
     else
-        hipLaunchKernelGGL(k_bd_rows<AP_BF16>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->bd_hn, ix->bd_bits, words);
+        hipLaunchKernelGGL(k_bd_rows<AP_BF16>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->dense_norm, ix->bd_norms, ix->bd_bits, words);
     AP_CHECK_HIP(hipGetLastError());
     return AP_OK;
 }
@@ -191,37 +210,46 @@ __device__ __forceinline__ float ap_bound_round(float v) {
 
 static inline int32_t bound_kdense(const ap_index *ix) { return ix->bd_kd ? ix->bd_kd : ix->docs.dim; }
 
-// One block per row of the query matrix: the query's dense part times its weight and its head terms times theirs,
-// rounded to bf16, and what the slack of the row is made of:
-//   .x times the document's dense norm, .y and .z times the norms of its learned-sparse and lexical head columns,
-//   .w relative slack of an addition of the tail
-// The slack covers: rounding both factors to bf16 (2^-9 each; a bf16 corpus's dense rows are exact), the product's
-// accumulation (k 2^-23), the rounding of the scoring kernels' own sums and of the tail's additions (1e-5 and 2^-22 a
-// term), and products of values so small that squares or products underflow (1e-18 of the norms).
+// One block per row of the query matrix: the query's dense part times its weight and its head terms times theirs, rounded to
+// bf16, and what the slack of the row is made of.  With x^ for x rounded, part by part (dense, learned-sparse head, lexical
+// head),  q d - q^ d^ = (q - q^) d + q^ (d - d^),  so by Cauchy-Schwarz the product is off by at most
+//   |q - q^| |d| + |q^| |d - d^|,
+// with the norms as they are: rounding to bf16 (8 significant bits) may take 2^-8 off a value, and on a short list or a row of
+// like values it does, but over many values it takes about 0.0017 of the norm.  qc[8 r ..]: per part |q^| and the factor of
+// |d|, then (6) the relative slack of an addition of the tail.  The factor of |d| is |q - q^| and, times |q|, what everything
+// else takes: the product's accumulation (k 2^-23), the rounding of the scoring kernels' own sums and of the tail's additions
+// (1e-5 and 2^-22 a term); 1e-18 of the norms for squares and products of values so small that they underflow.
 __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int64_t nq, int32_t kdense,
-                                                       int32_t kh, int32_t nsp, int32_t ntx, const int32_t *__restrict__ col, float eps_dense,
-                                                       uint16_t *__restrict__ qm, float4 *__restrict__ qc) {
+                                                       int32_t kh, int32_t nsp, int32_t ntx, const int32_t *__restrict__ col,
+                                                       uint16_t *__restrict__ qm, float *__restrict__ qc) {
     __shared__ __attribute__((aligned(16))) uint16_t head[AP_BOUND_HEAD];
-    __shared__ float red[3][4];
+    __shared__ float red[9][4];
     const int64_t r = blockIdx.x, q = q0 + r;
     uint16_t *row = qm + r * (kdense + kh);
     if (r >= nq) {
         for (int32_t c = threadIdx.x * 8; c < kdense + kh; c += 2048) *reinterpret_cast<uint4 *>(row + c) = make_uint4(0, 0, 0, 0);
-        if (threadIdx.x == 0) qc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (threadIdx.x < 8) qc[r * 8 + threadIdx.x] = 0.f;
         return;
     }
     const float wd = w[q * w_stride], ws = w[q * w_stride + 1], wf = w[q * w_stride + 2];
     for (int32_t c = threadIdx.x; c < kh; c += 256) head[c] = 0;
-    float sd = 0.f, sh[2] = {0.f, 0.f};
+    float sum[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // per part: squares of the values, of the rounded values, of the differences
+    auto add = [&](int part, float x) -> uint32_t {
+        const uint32_t y16 = ap_bf16_bits(x);
+        const float y = ap_bf16_value(y16), off = x - y;
+        sum[3 * part] = fmaf(x, x, sum[3 * part]); sum[3 * part + 1] = fmaf(y, y, sum[3 * part + 1]); sum[3 * part + 2] = fmaf(off, off, sum[3 * part + 2]);
+        return y16;
+    };
     for (int32_t c = threadIdx.x * 4; c < kdense; c += 1024) {
         float x[4] = {0.f, 0.f, 0.f, 0.f};
         if (c < Q.dim) {
             const float4 y = *reinterpret_cast<const float4 *>(static_cast<const float *>(Q.dense) + q * Q.dim + c);
             x[0] = wd * y.x; x[1] = wd * y.y; x[2] = wd * y.z; x[3] = wd * y.w;
-#pragma unroll
-            for (int e = 0; e < 4; e++) sd = fmaf(x[e], x[e], sd);
         }
-        *reinterpret_cast<uint2 *>(row + c) = make_uint2(ap_bf16_bits(x[0]) | (ap_bf16_bits(x[1]) << 16), ap_bf16_bits(x[2]) | (ap_bf16_bits(x[3]) << 16));
+        uint32_t y16[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) y16[e] = add(0, x[e]);
+        *reinterpret_cast<uint2 *>(row + c) = make_uint2(y16[0] | (y16[1] << 16), y16[2] | (y16[3] << 16));
     }
     __syncthreads();
     int64_t terms = 0;
@@ -234,19 +262,26 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
             const int32_t c = col[part ? nsp + t : t];
             if (c < 0) continue;
             const float x = part ? wf * Q.tx_val[p] : ws * Q.sp_val[p];
-            head[c] = (uint16_t)ap_bf16_bits(x);
-            sh[part] = fmaf(x, x, sh[part]);
+            head[c] = (uint16_t)(part ? add(2, x) : add(1, x));
         }
     }
-    sd = ap_wave_sum(sd); sh[0] = ap_wave_sum(sh[0]); sh[1] = ap_wave_sum(sh[1]);
-    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = sd; red[1][threadIdx.x >> 6] = sh[0]; red[2][threadIdx.x >> 6] = sh[1]; }
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+        sum[i] = ap_wave_sum(sum[i]);
+        if ((threadIdx.x & 63) == 0) red[i][threadIdx.x >> 6] = sum[i];
+    }
     __syncthreads();
     for (int32_t c = threadIdx.x * 8; c < kh; c += 2048) *reinterpret_cast<uint4 *>(row + kdense + c) = *reinterpret_cast<const uint4 *>(head + c);
     if (threadIdx.x == 0) {
-        float norm[3];
-        for (int i = 0; i < 3; i++) norm[i] = sqrtf(red[i][0] + red[i][1] + red[i][2] + red[i][3]) * 1.0001f;
-        const float rel = 1e-5f + 2.4e-7f * (float)terms, sum = rel + 1.2e-7f * (float)(kdense + kh);
-        qc[r] = make_float4(norm[0] * (eps_dense + sum) + 1e-18f, norm[1] * (0.00392f + sum) + 1e-18f, norm[2] * (0.00392f + sum) + 1e-18f, rel);
+        float norm[9];
+        for (int i = 0; i < 9; i++) norm[i] = sqrtf(red[i][0] + red[i][1] + red[i][2] + red[i][3]) * 1.0001f;
+        const float rel = 1e-5f + 2.4e-7f * (float)terms, other = rel + 1.2e-7f * (float)(kdense + kh);
+        for (int p = 0; p < 3; p++) {
+            qc[r * 8 + 2 * p] = norm[3 * p + 1] + 1e-18f;
+            qc[r * 8 + 2 * p + 1] = norm[3 * p + 2] + norm[3 * p] * other + 1e-18f;
+        }
+        qc[r * 8 + 6] = rel;
+        qc[r * 8 + 7] = 0.f;
     }
 }
 
@@ -257,14 +292,13 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
 // Tile order: an XCD takes the document tiles in groups of four and walks each group's query tiles, so that a group's
 // documents and the queries stay in its L2 while they are used.
 #define AP_BOUND_GROUP 4
-__global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict__ qm, const float4 *__restrict__ qc, int32_t nq, int32_t q_tiles,
+__global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict__ qm, const float *__restrict__ qc, int32_t nq, int32_t q_tiles,
                                                       const uint16_t *__restrict__ dense, int32_t dense_ld, int32_t n_dense,
                                                       const uint16_t *__restrict__ head, int32_t head_ld, int32_t n_chunks,
-                                                      const float *__restrict__ dn, const float2 *__restrict__ hn, int64_t n, int64_t doc_tiles,
+                                                      const float2 *__restrict__ norms, int64_t n, int64_t doc_tiles,
                                                       float *__restrict__ table, int64_t ld) {
     extern __shared__ __attribute__((aligned(16))) uint16_t bound_lds[];
-    __shared__ float4 s_qc[AP_BOUND_QT];
-    __shared__ float4 s_dn[AP_BOUND_QT];
+    __shared__ float2 s_qc[3][AP_BOUND_QT], s_dn[3][AP_BOUND_QT];   // per part: |q^| and the factor of |d|; |d - d^| and |d|
     using T = ApBig<4, 4>;
     constexpr int NP = T::NP, RPP = T::RPP;
     const int64_t xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
@@ -273,10 +307,11 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
     if (dt >= doc_tiles) return;   // uniform
     const int64_t d0 = dt * AP_BOUND_QT, r0 = qt * AP_BOUND_QT;
     const int t = threadIdx.x, lane = t & 63, wave = ap_wave_id(), wm = wave >> 2, wn = wave & 3;
-    if (t < AP_BOUND_QT) {
-        const int64_t d = d0 + t < n ? d0 + t : n - 1;
-        s_qc[t] = qc[r0 + t];
-        s_dn[t] = make_float4(fmaf(dn[d], 1.0001f, 1e-15f), fmaf(hn[d].x, 1.0001f, 1e-15f), fmaf(hn[d].y, 1.0001f, 1e-15f), 0.f);
+    if (t < 3 * AP_BOUND_QT) {
+        const int p = t / AP_BOUND_QT, j = t % AP_BOUND_QT;
+        const float2 dn = norms[p * n + (d0 + j < n ? d0 + j : n - 1)];
+        s_qc[p][j] = *reinterpret_cast<const float2 *>(qc + (r0 + j) * 8 + 2 * p);
+        s_dn[p][j] = make_float2(fmaf(dn.x, 1.0001f, 1e-15f), fmaf(dn.y, 1.0001f, 1e-15f));
     }
     const int32_t kq = n_chunks * AP_BK16;
     const char *qa = reinterpret_cast<const char *>(qm + r0 * kq);
@@ -346,20 +381,29 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
         round(k, va0, vb0);
         if (k + 1 < n_chunks) round(k + 1, va1, vb1);
     }
+    float2 dn[2][3];
 #pragma unroll
-    for (int b = 0; b < 2; b++) {
-        const int j = wn * 64 + b * 32 + li;
-        const float4 dh = s_dn[j];
+    for (int b = 0; b < 2; b++)
 #pragma unroll
-        for (int a = 0; a < 2; a++)
+        for (int p = 0; p < 3; p++) dn[b][p] = s_dn[p][wn * 64 + b * 32 + li];
 #pragma unroll
-            for (int r = 0; r < 16; r++) {
-                const int i = wm * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const float4 c = s_qc[i];
-                const float slack = fmaf(c.x, dh.x, fmaf(c.y, dh.y, fmaf(c.z, dh.z, 1e-36f)));
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const int i = wm * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            const float2 c0 = s_qc[0][i], c1 = s_qc[1][i], c2 = s_qc[2][i];
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                const int j = wn * 64 + b * 32 + li;
+                float slack = fmaf(c0.x, dn[b][0].x, 1e-36f);
+                slack = fmaf(c0.y, dn[b][0].y, slack);
+                slack = fmaf(c1.x, dn[b][1].x, slack);
+                slack = fmaf(c1.y, dn[b][1].y, slack);
+                slack = fmaf(c2.x, dn[b][2].x, slack);
+                slack = fmaf(c2.y, dn[b][2].y, slack);
                 if (r0 + i < nq && d0 + j < n) table[(r0 + i) * ld + d0 + j] = ap_bound_round(acc[a][b][r] + slack);
             }
-    }
+        }
 }
 
 // One block per query: the tail terms' postings, one term after the other (a document occurs once in a term's postings,
@@ -368,11 +412,11 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
 // scattered read-modify-writes: 1.4 ms for 4,000 queries of 100,000 documents (about one entry in twenty is touched).
 __global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int32_t nsp, int32_t ntx,
                                                     const int32_t *__restrict__ col, const uint2 *__restrict__ run, const uint2 *__restrict__ post,
-                                                    const float4 *__restrict__ qc, const int32_t *__restrict__ kw_terms, int32_t kw_stride,
+                                                    const float *__restrict__ qc, const int32_t *__restrict__ kw_terms, int32_t kw_stride,
                                                     float *__restrict__ table, int64_t ld) {
     const int64_t q = q0 + blockIdx.x;
     float *row = table + (int64_t)blockIdx.x * ld;
-    const float ws = w[q * w_stride + 1], wf = w[q * w_stride + 2], rel = qc[blockIdx.x].w;
+    const float ws = w[q * w_stride + 1], wf = w[q * w_stride + 2], rel = qc[blockIdx.x * (int64_t)8 + 6];
     for (int part = 0; part < 2; part++) {
         const int64_t b = part ? Q.tx_indptr[q] : Q.sp_indptr[q], e = part ? Q.tx_indptr[q + 1] : Q.sp_indptr[q + 1];
         for (int64_t p = b; p < e; p++) {   // uniform
@@ -437,14 +481,14 @@ int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t be
 // Bytes of the workspace a slab of nq queries takes.
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq) {
     const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
-    return rows * k * 2 + rows * 16 + rows * 4 + (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
+    return rows * k * 2 + rows * 32 + rows * 4 + (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
 }
 
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b) {
     const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
     char *m = static_cast<char *>(base);
     b->qm = reinterpret_cast<uint16_t *>(m); m += rows * k * 2;
-    b->qc = reinterpret_cast<float4 *>(m); m += rows * 16;
+    b->qc = reinterpret_cast<float *>(m); m += rows * 32;
     b->floor = reinterpret_cast<float *>(m); m += rows * 4;
     b->table = reinterpret_cast<float *>(m);
     b->ld = (int64_t)ap_up((size_t)ix->docs.n, 64);
@@ -497,14 +541,13 @@ int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const f
     const int64_t n = ix->docs.n, q_tiles = (nq + AP_BOUND_QT - 1) / AP_BOUND_QT, doc_tiles = (n + AP_BOUND_QT - 1) / AP_BOUND_QT;
     const int64_t groups = (doc_tiles + 8 * AP_BOUND_GROUP - 1) / (8 * AP_BOUND_GROUP);
     const bool own = ix->bd_kd != 0;
-    const float eps = ix->dtype == AP_BF16 ? 0.00196f : 0.00392f;
-    hipLaunchKernelGGL(k_bound_queries, dim3((unsigned)(q_tiles * AP_BOUND_QT)), dim3(256), 0, st, Q, w, w_stride, q0, nq, kdense, kh, nsp, ntx, ix->bd_col, eps,
-                       b.qm, b.qc);
+    hipLaunchKernelGGL(k_bound_queries, dim3((unsigned)(q_tiles * AP_BOUND_QT)), dim3(256), 0, st, Q, w, w_stride, q0, nq, kdense, kh, nsp, ntx, ix->bd_col, b.qm,
+                       b.qc);
     AP_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bound_table), hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES));
     const int32_t ld = ix->bd_kd + kh;
     hipLaunchKernelGGL(k_bound_table, dim3((unsigned)(groups * 8 * AP_BOUND_GROUP * q_tiles)), dim3(1024), AP_BIG_LDS_BYTES, st, b.qm, b.qc, (int32_t)nq,
                        (int32_t)q_tiles, own ? ix->bd_rows : static_cast<const uint16_t *>(ix->docs.dense), own ? ld : ix->docs.dim, kdense / AP_BK16,
-                       ix->bd_rows + ix->bd_kd, ld, (kdense + kh) / AP_BK16, ix->dense_norm, ix->bd_hn, n, doc_tiles, b.table, b.ld);
+                       ix->bd_rows + ix->bd_kd, ld, (kdense + kh) / AP_BK16, ix->bd_norms, n, doc_tiles, b.table, b.ld);
     hipLaunchKernelGGL(k_bound_tail, dim3((unsigned)nq), dim3(256), 0, st, Q, w, w_stride, q0, nsp, ntx, ix->bd_col, ix->bd_run, ix->bd_post, b.qc, kw_terms,
                        kw_terms ? kw_stride : 0, b.table, b.ld);
     AP_CHECK_HIP(hipGetLastError());

@@ -92,7 +92,7 @@ struct ap_index {
     int32_t *bd_col = nullptr;         // per term (learned-sparse vocabulary, then lexical): its head column or -1
     uint2 *bd_run = nullptr;           // per term: first posting, number of postings (0 for head terms)
     uint2 *bd_post = nullptr;          // (document, weight bits)
-    float2 *bd_hn = nullptr;           // per document: norms of its learned-sparse and lexical head columns
+    float2 *bd_norms = nullptr;        // 3 planes of n (dense part, learned-sparse and lexical head columns): norm of the rounding's loss, norm
     uint32_t *bd_bits = nullptr;       // per head column a bit per document: it holds that lexical term
     struct ApBoundPool *bd_pool = nullptr;   // search-time workspaces
     int32_t *search_counts = nullptr;  // nq x 2 of the last search: similarities evaluated, iterations
@@ -189,7 +189,7 @@ struct ApBound {
     float *table = nullptr;    // slab x ld; NULL: not used in this call
     int64_t ld = 0;            // documents, padded
     uint16_t *qm = nullptr;    // the slab's queries as bf16 rows
-    float4 *qc = nullptr;      // per query: what the slack of its row is made of
+    float *qc = nullptr;       // per query 8 floats: what the slack of its row is made of
     float *floor = nullptr;    // per query: an estimate of the last score of a pool (ap_bound_floors)
     int32_t slab = 0;          // queries the workspace holds
     std::unique_lock<std::mutex> hold;   // of the index's workspaces, until everything that uses this one is enqueued

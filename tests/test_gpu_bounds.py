@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2511_00855_amd import binding as B
-from paper_2511_00855_amd.synth import make_keywords, make_workload
+from paper_2511_00855_amd.synth import VecSet, make_keywords, make_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -15,6 +15,33 @@ def _workload(base, **kw):
     w = make_workload(base, seed=11, **kw)
     bf16 = getattr(w.docs, "dense_bf16", None) is not None
     return w, B.DeviceVecs(w.docs, bf16=bf16), B.DeviceVecs(w.queries)
+
+
+def _slack(ix, q, d, weights, bf16):
+    """The most a bound may lie above its score, per query and document.  Rounding x to x^ in bf16 takes |x - x^| off a part; a
+    product of two rounded parts is off by |q - q^| |d| + |q^| |d - d^| at most, the bound adds as much again, and 1e-3 of the
+    norms is more than all sums in 32 bits take (the parts here are whole lists, of which the head is rounded)."""
+    dev = ix.device
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float32, device=dev)
+    txw = ix.export_ingest()[0]
+    out = 0.0
+    for p, (qi, qv, di, dv) in enumerate(((None, q.dense, None, d.dense), (q.sp_indptr, q.sp_val, d.sp_indptr, d.sp_val),
+                                          (q.tx_indptr, q.tx_val, d.tx_indptr, txw))):
+        def norms(ip, v, w):   # of the values, of the rounded ones, of the difference
+            rows = torch.arange(v.shape[0], device=dev) if ip is None else \
+                torch.repeat_interleave(torch.arange(len(ip) - 1, device=dev), torch.as_tensor(np.diff(ip), device=dev))
+            n = v.shape[0] if ip is None else len(ip) - 1
+            x = v if w is None else (v * (w[:, None] if ip is None else w[rows]))
+            y = x.bfloat16().float()
+            sq = [(z.double() ** 2).sum(1) if ip is None else torch.zeros(n, dtype=torch.float64, device=dev).index_add_(0, rows, z.double() ** 2)
+                  for z in (x, y, x - y)]
+            return [z.sqrt() for z in sq]
+        qn, qr, qd = [z[:, None] for z in norms(qi, t(qv), t(weights[:, p]))]
+        dn, _, dd = [z[None, :] for z in norms(di, dv if torch.is_tensor(dv) else t(dv), None)]
+        if p == 0 and bf16:
+            dd = torch.zeros_like(dd)
+        out = out + 2 * (qd * dn + qr * dd) + 1e-3 * qn * dn
+    return out + 1e-12
 
 
 # tiles of 256 x 256, chunks of 64 columns, at most 512 head columns: below, at and above their edges; a vocabulary that is
@@ -32,17 +59,55 @@ def test_bounds_hold_and_are_tight(base, n, nq, dim, vocab):
         sc = ix.hybrid_scores(qs, cand, pw).double()
         up = ix.stage_score_bounds(qs, pw).double()
         torch.cuda.synchronize()
-        wd, ws, wf = [torch.from_numpy(np.abs(weights[:, i])).to(sc.device)[:, None] for i in range(3)]
         assert (up >= sc[:, :, 3]).all()
-        # two roundings to bf16 (2^-9 each) of norm-bounded parts, once in the product and once in the slack, and 1e-3 for all sums
-        q, d = w.queries, w.docs
-        qn = torch.from_numpy(np.linalg.norm(q.dense, axis=1)).to(sc.device)[:, None]
-        dn = torch.from_numpy(np.linalg.norm(d.dense, axis=1)).to(sc.device)[None, :]
-        rows = lambda ip, v: torch.from_numpy(np.array([np.linalg.norm(v[a:b]) for a, b in zip(ip[:-1], ip[1:])])).to(sc.device)
-        txw = ix.export_ingest()[0].cpu().numpy()
-        parts = wd * qn * dn + ws * rows(q.sp_indptr, q.sp_val)[:, None] * rows(d.sp_indptr, d.sp_val)[None, :] \
-            + wf * rows(q.tx_indptr, q.tx_val)[:, None] * rows(d.tx_indptr, txw)[None, :]
-        assert (up - sc[:, :, 3] <= (4 * 2.0 ** -9 + 1e-3) * parts + 1e-12).all()
+        assert (up - sc[:, :, 3] <= _slack(ix, w.queries, w.docs, pw, docs.dtype == B.AP_BF16)).all()
+    ix.close()
+
+
+def _rounded_most(rng, n):
+    """Values that lose nearly 2^-8 when they are rounded to bf16 (just below the middle between two neighbours, and above
+    it), and ordinary ones."""
+    v = 1.0 + 2.0 ** -8 + rng.choice([-1.0, 1.0], n) * rng.integers(1, 64, n) * 2.0 ** -18
+    return np.where(rng.random(n) < 0.5, v, 1.0 + rng.random(n)).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,dim,bf16", [(4500, 64, False), (4200, 100, False), (4300, 1024, True), (4100, 72, True)])
+def test_bounds_hold_where_rounding_takes_most(debug_knobs, n, dim, bf16):
+    """One-term lists and rows of one magnitude, signs aligned: every rounding error of a product points the same way, and the
+    inequality the slack comes from is all but an equation."""
+    rng, nq = np.random.default_rng(17), 96
+    sign = rng.choice([-1.0, 1.0], dim).astype(np.float32)
+    def vecs(m):
+        dense = sign * _rounded_most(rng, m)[:, None] / np.float32(np.sqrt(dim))
+        term = np.arange(m, dtype=np.int32) % 2   # two terms, half of the documents each (a term of all has a BM25 weight of nearly nothing)
+        ip = np.arange(m + 1, dtype=np.int64)
+        return VecSet(m, dim, dense.astype(np.float32), ip, term + 5, _rounded_most(rng, m), ip, term + 3, _rounded_most(rng, m), 50, 50)
+    d, q = vecs(n), vecs(nq)
+    if bf16:
+        bits = torch.from_numpy(d.dense).bfloat16()
+        d.dense, d.dense_bf16 = bits.float().numpy(), bits.view(torch.int16).numpy().view(np.uint16)
+    docs, qs = B.DeviceVecs(d, bf16=bf16), B.DeviceVecs(q)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
+    cand = np.tile(np.arange(n, dtype=np.int32), (nq, 1))
+    scale = _rounded_most(rng, nq * 3).reshape(nq, 3)
+    for which in ([1, 0, 0], [0, 1, 0], [0, 0, 1], [-1, 0, 0], [0, -1, 1], [1, 1, 1]):
+        pw = (scale * np.float32(which)).astype(np.float32)
+        print(which, flush=True)
+        sc = ix.hybrid_scores(qs, cand, pw)[:, :, 3]
+        up = ix.stage_score_bounds(qs, pw).double()
+        assert (up >= sc.double()).all(), (which, ((sc.double() - up) / sc.double().abs().clamp(min=1e-9)).max())
+        assert (up - sc.double() <= _slack(ix, q, d, pw, bf16)).all(), which
+        for k in (1, 200):
+            ids, got = ix.bruteforce_topk(qs, k, pw)
+            want, at = torch.sort(sc, dim=1, descending=True, stable=True)
+            assert torch.equal(got, want[:, :k]) and torch.equal(ids, at[:, :k].to(torch.int32)), (which, k)
+        for k, beam, width in ((10, 64, 1), (50, 2000, 4)):
+            got = []
+            for mode in (1, 2):
+                debug_knobs("search_bounds", mode)
+                got.append([t.clone() for t in ix.search_batch(qs, k, beam, pw, search_width=width)])
+            debug_knobs("search_bounds", 0)
+            assert all(torch.equal(a, b) for a, b in zip(*got)), (which, beam)
     ix.close()
 
 
