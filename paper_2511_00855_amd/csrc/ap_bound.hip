@@ -512,6 +512,7 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st,
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
     if (cs != hipStreamCaptureStatusNone) return AP_OK;
+    if (g_ap_debug.search_bounds_bytes > 0) cap = std::min(cap, (size_t)g_ap_debug.search_bounds_bytes);
     int64_t slabs = 1;
     while (slabs < nq && ap_bound_bytes(ix, (nq + slabs - 1) / slabs) > cap) slabs++;
     const int64_t slab = (nq + slabs - 1) / slabs;

@@ -139,6 +139,7 @@ struct ApDebug {
     int64_t search_query_lists = 0;      // 1: the searches look the query's terms up in its lists (the path of queries too long for the LDS tables)
     int64_t search_bounds = 0;           // 1: searches without the table of upper bounds, 2: with it whatever it costs
     int64_t search_floor = 0;            // 1: no neighbour waits below a floor, 2: the floor is far too high (forces the scan of what waits)
+    int64_t search_bounds_bytes = 0;     // cap of a stream's table of bounds (forces slabs of queries that each get a table)
     int64_t search_workspace_bytes = 0;  // cap of the search's visited-set workspace (forces searches in several slabs of queries)
 };
 extern ApDebug g_ap_debug;

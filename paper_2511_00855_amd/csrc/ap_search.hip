@@ -896,10 +896,6 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     const size_t words = ((size_t)ix->docs.n + 31) / 32;
     const size_t cap_bytes = g_ap_debug.search_workspace_bytes > 0 ? (size_t)g_ap_debug.search_workspace_bytes : AP_SEARCH_WS_BYTES;
     ws->slab = ap_slab_size(nq, words, cap_bytes / 4);
-    if (bounds) {
-        AP_TRY(ap_bound_reserve(ix, ws->slab, AP_BOUND_WS_BYTES, st, &ws->bound));
-        if (ws->bound.table) ws->slab = ws->bound.slab;
-    }
     const size_t need = words * (size_t)ws->slab;
     if (need > ix->visited_words) {
         if (ix->visited) { AP_CHECK_HIP(hipStreamSynchronize(st)); (void)hipFree(ix->visited); ix->visited = nullptr; ix->visited_words = 0; }
@@ -919,6 +915,12 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     ws->counts = ix->search_counts;
     ws->ev0 = ix->ev_search[0]; ws->ev1 = ix->ev_search[1];
     ix->last_nq = nq;
+    // The bounds come last, and what the search cannot do without is sized as if there were none: they never take the memory
+    // of a search that used to fit, and the same batch can run without them afterwards (captured, say) and allocate nothing.
+    if (bounds) {
+        AP_TRY(ap_bound_reserve(ix, ws->slab, AP_BOUND_WS_BYTES, st, &ws->bound));
+        if (ws->bound.table) ws->slab = ws->bound.slab;
+    }
     return AP_OK;
 }
 

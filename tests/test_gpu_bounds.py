@@ -162,6 +162,36 @@ def test_large_pools_with_a_floor_are_the_same(debug_knobs, base, n, dim):
     ix.close()
 
 
+def test_slabs_of_the_table_and_a_captured_search(debug_knobs):
+    """A table that holds some twenty of 70 queries: the search runs in slabs, each with a table of its own.  A captured search
+    goes without bounds, and after such a search of the same batch it needs no memory that is not there."""
+    n = 1500
+    w, docs, qs = _workload("tiny", n=n, nq=70)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=2, n_entry=16))
+    rng = np.random.default_rng(4)
+    pws = [torch.from_numpy(rng.uniform(-0.2, 1.0, (qs.n, 3)).astype(np.float32)).to(docs.device) for _ in range(3)]
+    debug_knobs("search_visited_global", 1)   # a corpus this small would keep its visited sets in LDS
+    debug_knobs("search_bounds", 2)
+    debug_knobs("search_bounds_bytes", 256 * (2 * (128 + 512) + 36) + 20 * 4 * 1536)
+    got = [[t.clone() for t in ix.search_batch(qs, 10, 96, p, search_width=2)] for p in pws]
+    torch.cuda.synchronize()
+    pw, out = pws[0].clone(), [t.clone() for t in got[0]]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ix.search_batch(qs, 10, 96, pw, search_width=2, out=out)
+    debug_knobs("search_bounds", 1)
+    want = [[t.clone() for t in ix.search_batch(qs, 10, 96, p, search_width=2)] for p in pws]
+    for i in (0, 2, 1, 1, 0):
+        pw.copy_(pws[i])
+        for t in out:
+            t.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want[i])), i
+        assert all(torch.equal(a, b) for a, b in zip(got[i], want[i])), i
+    ix.close()
+
+
 def test_two_streams_search_one_index_with_tables_of_their_own(debug_knobs):
     w, docs, qs = _workload("tiny", n=3000, nq=60)
     ix = B.Index.build(docs, B.build_params(16, nd_rounds=2, n_entry=16))
