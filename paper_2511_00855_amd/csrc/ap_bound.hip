@@ -20,12 +20,14 @@ int ap_validate_queries(const ap_queries *q);
 #define AP_BOUND_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of columns is kept for
 
 // The workspaces of an index: one per stream that searches it (grow only, at most AP_BOUND_STREAMS), so that searches
-// of one index on several streams do not share a table.
+// of one index on several streams do not share a table.  A further stream gets the one that has been idle longest; while all
+// of them are at work it goes without.  `done` is recorded behind a workspace's last use.
 #define AP_BOUND_STREAMS 4
 struct ApBoundPool {
     std::mutex lock;
-    struct { hipStream_t stream; void *mem; size_t bytes; } ws[AP_BOUND_STREAMS];
+    struct { hipStream_t stream; void *mem; size_t bytes; hipEvent_t done; uint64_t last; } ws[AP_BOUND_STREAMS];
     int used = 0;
+    uint64_t uses = 0;
 };
 
 // ------------------------------------------------------------------ ingest
@@ -497,7 +499,10 @@ void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b) {
 
 void ap_bound_release(ap_index *ix) {
     if (!ix->bd_pool) return;
-    for (int i = 0; i < ix->bd_pool->used; i++) if (ix->bd_pool->ws[i].mem) (void)hipFree(ix->bd_pool->ws[i].mem);
+    for (int i = 0; i < ix->bd_pool->used; i++) {
+        if (ix->bd_pool->ws[i].mem) (void)hipFree(ix->bd_pool->ws[i].mem);
+        (void)hipEventDestroy(ix->bd_pool->ws[i].done);
+    }
     delete ix->bd_pool;
     ix->bd_pool = nullptr;
 }
@@ -507,7 +512,6 @@ void ap_bound_release(ap_index *ix) {
 // bounds.  That is also what a captured search does: a graph's replays must not depend on a workspace that a later
 // call may replace.
 int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b) {
-    *b = ApBound();
     if (!ix->bd_mem || nq < 1 || st == hipStreamPerThread) return AP_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
@@ -522,9 +526,23 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st,
     std::unique_lock<std::mutex> hold(pool->lock);
     int i = 0;
     while (i < pool->used && pool->ws[i].stream != st) i++;
-    if (i == AP_BOUND_STREAMS) return AP_OK;
-    if (i == pool->used) { pool->ws[i] = {st, nullptr, 0}; pool->used++; }
+    if (i == pool->used && i < AP_BOUND_STREAMS) {
+        hipEvent_t done = nullptr;
+        if (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
+        pool->ws[i] = {st, nullptr, 0, done, 0};
+        pool->used++;
+    } else if (i == pool->used) {   // a stream beyond the workspaces
+        for (int j = 0; j < pool->used; j++)
+            if ((i == pool->used || pool->ws[j].last < pool->ws[i].last) && hipEventQuery(pool->ws[j].done) == hipSuccess) i = j;
+        (void)hipGetLastError();   // "not ready" is no error
+        if (i == pool->used) return AP_OK;
+        pool->ws[i].stream = st;
+    } else {
+        // work of the same stream comes behind its last use anyway, but the handle of a stream that is gone may name another now
+        AP_CHECK_HIP(hipStreamWaitEvent(st, pool->ws[i].done, 0));
+    }
     auto &w = pool->ws[i];
+    w.last = ++pool->uses;
     if (need > w.bytes) {
         if (w.mem) { AP_CHECK_HIP(hipStreamSynchronize(st)); (void)hipFree(w.mem); w.mem = nullptr; w.bytes = 0; }
         if (hipMalloc(&w.mem, need) != hipSuccess) { (void)hipGetLastError(); w.mem = nullptr; return AP_OK; }
@@ -532,6 +550,8 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st,
     }
     ap_bound_place(ix, w.mem, slab, b);
     b->hold = std::move(hold);
+    b->stream = st;
+    b->done = w.done;
     return AP_OK;
 }
 

@@ -193,7 +193,21 @@ struct ApBound {
     float *qc = nullptr;       // per query 8 floats: what the slack of its row is made of
     float *floor = nullptr;    // per query: an estimate of the last score of a pool (ap_bound_floors)
     int32_t slab = 0;          // queries the workspace holds
-    std::unique_lock<std::mutex> hold;   // of the index's workspaces, until everything that uses this one is enqueued
+    // The index's workspaces are held until everything that uses this one is enqueued: finish() (or the end of the object)
+    // marks that place on the stream and lets go.
+    std::unique_lock<std::mutex> hold;
+    hipStream_t stream = nullptr;
+    hipEvent_t done = nullptr;
+    void finish() {
+        if (!hold.owns_lock()) return;
+        if (hipEventRecord(done, stream) != hipSuccess) { (void)hipGetLastError(); (void)hipStreamSynchronize(stream); }
+        table = nullptr;
+        hold.unlock();
+    }
+    ApBound() = default;
+    ApBound(const ApBound &) = delete;
+    ApBound &operator=(const ApBound &) = delete;
+    ~ApBound() { finish(); }
 };
 // The visited-set workspace of a search call: `slab` queries are in flight at a time, each with a bitset of one bit
 // per document.  `counts` (nq x 3) and the two events belong to the index's measurement surface and may be absent.

@@ -214,6 +214,33 @@ def test_two_streams_search_one_index_with_tables_of_their_own(debug_knobs):
     ix.close()
 
 
+def test_any_number_of_streams_in_turn_search_with_bounds(debug_knobs):
+    """A search with bounds decides more documents without their dense rows: every stream's does, and none beyond the first few
+    takes more memory."""
+    w, docs, qs = _workload("tiny", n=3000, nq=2000)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=2, n_entry=16))
+    pw = torch.from_numpy(np.random.default_rng(8).uniform(0.1, 1.0, (qs.n, 3)).astype(np.float32)).to(docs.device)
+    seen = {}
+    for mode in (1, 2):
+        debug_knobs("search_bounds", mode)
+        out = ix.search_batch(qs, 10, 96, pw)
+        seen[mode] = [t.clone() for t in out] + [ix.search_stats(qs.n)[0].clone()]
+    assert seen[2][2][:, 2].sum() > seen[1][2][:, 2].sum()
+    streams = [torch.cuda.Stream() for _ in range(9)]
+    free = []
+    for i in list(range(9)) + [0, 5]:
+        torch.cuda.synchronize()
+        with torch.cuda.stream(streams[i]):
+            ix.search_batch(qs, 10, 96, pw, out=out)
+        torch.cuda.synchronize()
+        got = list(out) + [ix.search_stats(qs.n)[0]]
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, seen[2])), i
+        free.append(torch.cuda.mem_get_info()[0])
+    assert free[4] - min(free[4:]) < 16 << 20   # less than a table (25 MB); a stream has resources of its own
+    ix.close()
+
+
 @pytest.mark.parametrize("base,n,dim,k", [("tiny", 4096, 128, 1), ("tiny", 4097, 100, 10), ("cfg2", 4500, 768, 100), ("cfg3", 5000, 1024, 256),
                                           ("cfg3", 4200, 520, 10), ("tiny", 9001, 64, 37)])
 def test_exact_topk_out_of_the_bounds(base, n, dim, k):
