@@ -345,6 +345,7 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
                                                                       ws, b.table, b.ld, k, out_ids, out_scores, over));
         if (hipGetLastError() != hipSuccess) { ap_set_error("ap_bruteforce_topk failed to launch"); rc = AP_EHIP; }
     }
+    b.finish();   // the host waits below: searches of this index on other streams need not
     int32_t n_over = 0;
     std::vector<int32_t> list;
     hipError_t e = hipSuccess;

@@ -1,12 +1,15 @@
 """The table of upper bounds: never below a score that the scoring kernels give, no further above it than its rounding
 allows, and searches that use it return the same ids, scores and counts of scored documents, bit for bit, as searches
 that score every neighbour."""
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2511_00855_amd import binding as B
-from paper_2511_00855_amd.synth import VecSet, make_keywords, make_workload
+from paper_2511_00855_amd.synth import VecSet, make_keywords, make_workload, subset_vecset
 
 pytestmark = pytest.mark.gpu
 
@@ -211,6 +214,46 @@ def test_two_streams_search_one_index_with_tables_of_their_own(debug_knobs):
     for i in range(2):
         for o in outs[i]:
             assert all(torch.equal(a, b) for a, b in zip(o, ref[i]))
+    ix.close()
+
+
+def test_a_search_does_not_wait_on_the_host_for_an_exact_topk(debug_knobs):
+    """Weights of zero: every document ties, which the bounds leave undecided, and every document is scored.  Meanwhile another
+    thread enqueues a search of the same index on another stream."""
+    n, nq = 20_000, 6_000
+    w, docs, qs = _workload("tiny", n=n, nq=nq, dim=32, sp=("fixed", 2), tx=("fixed", 2))
+    few = B.DeviceVecs(subset_vecset(w.queries, np.arange(20)))
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
+    debug_knobs("search_bounds", 2)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    zero = torch.zeros((nq, 3), device=docs.device)
+    out = None
+    for _ in range(2):   # workspaces are there afterwards
+        with torch.cuda.stream(streams[1]):
+            out = ix.search_batch(few, 10, 64, out=out)
+        torch.cuda.synchronize()
+    t = {}
+
+    def exact():
+        with torch.cuda.stream(streams[0]):
+            t["begin"] = time.perf_counter()
+            t["ids"] = ix.bruteforce_topk(qs, 100, zero)[0]
+            t["end"] = time.perf_counter()
+    exact()
+    torch.cuda.synchronize()
+    took = t["end"] - t["begin"]
+    assert torch.equal(t["ids"], torch.arange(100, dtype=torch.int32, device=docs.device).repeat(nq, 1))
+    th = threading.Thread(target=exact)
+    th.start()
+    time.sleep(0.2 * took)
+    with torch.cuda.stream(streams[1]):
+        t0 = time.perf_counter()
+        ix.search_batch(few, 10, 64, out=out)
+        t1 = time.perf_counter()
+    th.join()
+    torch.cuda.synchronize()
+    print(f"exact top-k {took * 1e3:.1f} ms, the search's call {(t1 - t0) * 1e3:.2f} ms, begun {(t['end'] - t0) * 1e3:.1f} ms before its end")
+    assert t0 < t["end"] and t1 - t0 < 0.5 * (t["end"] - t0)
     ix.close()
 
 
