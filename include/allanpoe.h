@@ -129,9 +129,10 @@ int ap_set_weights(ap_index *index, const float w[3]);
  * nq x 3 (device) or NULL for the index default.  out_ids / out_scores are
  * nq x k.  The call sizes a per-index workspace (one visited bit per document
  * for every query in flight, at most 2 GiB, and where that pays upper bounds of
- * all scores, 4 bytes per query and document, at most 16 GiB per stream that
- * searches: larger batches run in slabs of queries, one launch each) and may
- * allocate on first use or when nq grows. */
+ * all scores, 4 bytes per query and document, at most 16 GiB and a quarter of the
+ * memory that is free for each of up to four streams that search: larger batches
+ * run in slabs of queries, one launch each) and may allocate on first use or when
+ * nq grows. */
 int ap_search_batch(ap_index *index, const ap_queries *queries, const float *per_query_w,
                     const ap_search_params *params, int32_t *out_ids, float *out_scores, void *stream);
 

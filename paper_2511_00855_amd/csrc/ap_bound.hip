@@ -19,7 +19,8 @@ int ap_validate_queries(const ap_queries *q);
 #define AP_BOUND_QT 256              // queries and documents of a tile
 #define AP_BOUND_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of columns is kept for
 
-// The workspaces of an index: one per stream that searches it (grow only, at most AP_BOUND_STREAMS), so that searches
+// The workspaces of an index: one per stream that searches it (at most AP_BOUND_STREAMS; insertion and large exact top-k
+// give theirs back, the others only grow), so that searches
 // of one index on several streams do not share a table.  A further stream gets the one that has been idle longest; while all
 // of them are at work it goes without.  `done` is recorded behind a workspace's last use.
 #define AP_BOUND_STREAMS 4
@@ -507,21 +508,28 @@ void ap_bound_release(ap_index *ix) {
     ix->bd_pool = nullptr;
 }
 
+// Queries per slab when a slab may take `cap` bytes (0: not even one).
+static int64_t bound_slab(const ap_index *ix, int64_t nq, size_t cap) {
+    int64_t slabs = 1;
+    while (slabs < nq && ap_bound_bytes(ix, (nq + slabs - 1) / slabs) > cap) slabs++;
+    const int64_t slab = (nq + slabs - 1) / slabs;
+    return ap_bound_bytes(ix, slab) <= cap ? slab : 0;
+}
+
 // Sizes the workspace of stream st for slabs of as many of nq queries as `cap` bytes hold, and holds it for the caller
-// (two threads may search on one stream).  b->table stays NULL where no workspace is to be had: the caller goes without
-// bounds.  That is also what a captured search does: a graph's replays must not depend on a workspace that a later
-// call may replace.
-int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b) {
+// (two threads may search on one stream).  A workspace that has to grow takes a quarter of the free memory at most, and
+// smaller slabs then, but of `least` queries at least (fewer than a launch keeps in flight cost more than the bounds save).
+// b->table stays NULL where no such workspace is to be had: the caller goes without bounds.  That is also what a captured
+// search does: a graph's replays must not depend on a workspace that a later call may replace.
+int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, hipStream_t st, ApBound *b) {
     if (!ix->bd_mem || nq < 1 || st == hipStreamPerThread) return AP_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
     if (cs != hipStreamCaptureStatusNone) return AP_OK;
     if (g_ap_debug.search_bounds_bytes > 0) cap = std::min(cap, (size_t)g_ap_debug.search_bounds_bytes);
-    int64_t slabs = 1;
-    while (slabs < nq && ap_bound_bytes(ix, (nq + slabs - 1) / slabs) > cap) slabs++;
-    const int64_t slab = (nq + slabs - 1) / slabs;
-    const size_t need = ap_bound_bytes(ix, slab);
-    if (need > cap) return AP_OK;
+    int64_t slab = bound_slab(ix, nq, cap);
+    if (slab == 0) return AP_OK;
+    least = std::min(least, slab);
     ApBoundPool *pool = ix->bd_pool;
     std::unique_lock<std::mutex> hold(pool->lock);
     int i = 0;
@@ -543,16 +551,52 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st,
     }
     auto &w = pool->ws[i];
     w.last = ++pool->uses;
-    if (need > w.bytes) {
-        if (w.mem) { AP_CHECK_HIP(hipStreamSynchronize(st)); (void)hipFree(w.mem); w.mem = nullptr; w.bytes = 0; }
-        if (hipMalloc(&w.mem, need) != hipSuccess) { (void)hipGetLastError(); w.mem = nullptr; return AP_OK; }
-        w.bytes = need;
+    if (ap_bound_bytes(ix, slab) > w.bytes) {
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) { (void)hipGetLastError(); free_b = 0; }
+        slab = bound_slab(ix, nq, std::min(cap, std::max(w.bytes, (free_b + w.bytes) / 4)));
+    }
+    if (slab < least) return AP_OK;
+    if (const size_t need = ap_bound_bytes(ix, slab); need > w.bytes) {
+        void *mem = nullptr;
+        if (hipMalloc(&mem, need) == hipSuccess) {
+            const hipError_t e = w.mem ? hipStreamSynchronize(st) : hipSuccess;
+            if (w.mem) (void)hipFree(w.mem);
+            w.mem = mem;
+            w.bytes = need;
+            AP_CHECK_HIP(e);
+        } else {   // what is there goes on serving
+            (void)hipGetLastError();
+            slab = bound_slab(ix, nq, std::min(cap, w.bytes));
+            if (slab < least) return AP_OK;
+        }
     }
     ap_bound_place(ix, w.mem, slab, b);
     b->hold = std::move(hold);
     b->stream = st;
     b->done = w.done;
     return AP_OK;
+}
+
+// Bytes of the workspace that stream st has, and its return to the device once a call that is not made again and again is
+// over (the stream has been waited for).
+size_t ap_bound_held(const ap_index *ix, hipStream_t st) {
+    if (!ix->bd_pool) return 0;
+    std::lock_guard<std::mutex> hold(ix->bd_pool->lock);
+    for (int i = 0; i < ix->bd_pool->used; i++)
+        if (ix->bd_pool->ws[i].stream == st) return ix->bd_pool->ws[i].bytes;
+    return 0;
+}
+void ap_bound_give_back(const ap_index *ix, hipStream_t st) {
+    if (!ix->bd_pool) return;
+    std::lock_guard<std::mutex> hold(ix->bd_pool->lock);
+    for (int i = 0; i < ix->bd_pool->used; i++) {
+        auto &w = ix->bd_pool->ws[i];
+        if (w.stream != st || !w.mem) continue;
+        (void)hipFree(w.mem);
+        w.mem = nullptr;
+        w.bytes = 0;
+    }
 }
 
 // Fills rows 0 .. nq of the table for queries q0 .. q0 + nq of Q (nq <= b.slab).
@@ -585,7 +629,7 @@ extern "C" int ap_stage_score_bounds(ap_index *ix, const ap_queries *q, const fl
     hipStream_t st = (hipStream_t)stream;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApBound b;
-    AP_TRY(ap_bound_reserve(ix, q->nq, AP_BOUND_WS_BYTES, st, &b));
+    AP_TRY(ap_bound_reserve(ix, q->nq, q->nq, AP_BOUND_WS_BYTES, st, &b));
     if (!b.table || b.slab != q->nq) { ap_set_error("no bounds for this index and batch"); return AP_ESTATE; }
     AP_TRY(ap_bound_fill(ix, b, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, 0, q->nq, kw_terms, kw_stride, st));
     AP_CHECK_HIP(hipMemcpy2DAsync(out, (size_t)ix->docs.n * 4, b.table, (size_t)b.ld * 4, (size_t)ix->docs.n * 4, (size_t)q->nq, hipMemcpyDeviceToDevice, st));

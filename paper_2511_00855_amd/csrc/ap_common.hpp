@@ -220,12 +220,15 @@ struct ApSearchWs {
 };
 // the workspace of one stream never grows beyond this (40,000 queries of 100,000 documents, 480 of 8.8 million)
 #define AP_BOUND_WS_BYTES ((size_t)16 << 30)
+#define AP_BOUND_KEEP_BYTES ((size_t)2 << 30)   // an exact top-k that had to take more gives it back
 #define AP_BOUND_COUNT 31u     // low bits of a table entry: keyword searches count the required tail terms a document holds there
 int ap_bound_ingest(ap_index *ix, hipStream_t st);
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq);
 void ap_bound_release(ap_index *ix);
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b);
-int ap_bound_reserve(const ap_index *ix, int64_t nq, size_t cap, hipStream_t st, ApBound *b);
+size_t ap_bound_held(const ap_index *ix, hipStream_t st);
+void ap_bound_give_back(const ap_index *ix, hipStream_t st);
+int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, hipStream_t st, ApBound *b);
 int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
                   const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);
 int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st);

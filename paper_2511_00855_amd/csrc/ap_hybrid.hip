@@ -332,7 +332,8 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     // Out of the table of bounds where that leaves most documents unscored: k well below the 1,024 documents the
     // threshold comes from, and a corpus well above them (below, the exhaustive scorer has little to do).
     ApBound b;
-    if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, AP_BOUND_WS_BYTES, st, &b));
+    const size_t held = ap_bound_held(ix, st);
+    if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, 256, AP_BOUND_WS_BYTES, st, &b));
     if (!b.table) return bf_exhaustive(ix, Q, w, ws, 0, q->nq, k, out_ids, out_scores, st);
     int32_t *over = nullptr;
     AP_TRY(ap_dev_alloc(&over, (size_t)q->nq + 1));
@@ -358,6 +359,8 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
         }
     }
     (void)hipFree(over);
+    // a workspace that this call made larger than its own scratch ever was does not stay
+    if (const size_t now = ap_bound_held(ix, st); now > held && now > AP_BOUND_KEEP_BYTES) ap_bound_give_back(ix, st);
     if (rc != AP_OK) return rc;
     if (e != hipSuccess) { ap_set_error("ap_bruteforce_topk failed: %s", hipGetErrorString(e)); return AP_EHIP; }
     std::sort(list.begin(), list.end());

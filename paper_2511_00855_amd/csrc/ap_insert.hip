@@ -228,6 +228,7 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, const ap
         AP_COPY(nx->deleted, old->deleted, w0, uint32_t);
     }
     AP_CHECK_HIP(hipStreamSynchronize(st));
+    ap_bound_give_back(nx, st);   // the search of step 1 had a batch of its own size
     float total = 0.f;
     for (int i = 0; i < 5; i++) {
         float ms = 0.f;

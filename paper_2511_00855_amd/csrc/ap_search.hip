@@ -918,7 +918,7 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     // The bounds come last, and what the search cannot do without is sized as if there were none: they never take the memory
     // of a search that used to fit, and the same batch can run without them afterwards (captured, say) and allocate nothing.
     if (bounds) {
-        AP_TRY(ap_bound_reserve(ix, ws->slab, AP_BOUND_WS_BYTES, st, &ws->bound));
+        AP_TRY(ap_bound_reserve(ix, ws->slab, 2048, AP_BOUND_WS_BYTES, st, &ws->bound));
         if (ws->bound.table) ws->slab = ws->bound.slab;
     }
     return AP_OK;

@@ -257,6 +257,59 @@ def test_a_search_does_not_wait_on_the_host_for_an_exact_topk(debug_knobs):
     ix.close()
 
 
+def _one_term(rng, n, dim):
+    """n rows of a few columns with lists of one term: what a test needs that is about amounts of memory."""
+    ip = np.arange(n + 1, dtype=np.int64)
+    dense = rng.standard_normal((n, dim)).astype(np.float32)
+    return VecSet(n, dim, dense, ip, rng.integers(0, 50, n).astype(np.int32), np.ones(n, np.float32), ip, rng.integers(0, 50, n).astype(np.int32),
+                  np.ones(n, np.float32), 50, 50)
+
+
+def test_the_table_takes_a_share_of_the_free_memory(debug_knobs):
+    rng, nq = np.random.default_rng(2), 10_000
+    d = _one_term(rng, 20_000, 16)
+    docs, qs = B.DeviceVecs(d), B.DeviceVecs(_one_term(rng, nq, 16))
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
+    debug_knobs("search_bounds", 1)
+    want = [t.clone() for t in ix.search_batch(qs, 5, 32)]
+    out = [t.clone() for t in want]
+    torch.cuda.synchronize()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - (2 << 30), dtype=torch.uint8, device=docs.device)
+    free0 = torch.cuda.mem_get_info()[0]
+    assert 1 << 30 < free0 < 3 << 30
+    debug_knobs("search_bounds", 2)
+    for _ in range(2):   # a table of all queries would be 0.8 GB
+        ix.search_batch(qs, 5, 32, out=out)
+        torch.cuda.synchronize()
+        taken = free0 - torch.cuda.mem_get_info()[0]
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+        assert 0 < taken <= free0 // 4 + (8 << 20), taken
+    del hold
+    torch.cuda.empty_cache()
+    ix.close()
+
+
+def test_workspaces_of_single_calls_are_given_back(debug_knobs):
+    rng, n, nq = np.random.default_rng(2), 20_000, 30_000
+    d = _one_term(rng, n, 16)
+    q = _one_term(rng, nq, 16)
+    docs, qs, few = B.DeviceVecs(d), B.DeviceVecs(q), B.DeviceVecs(subset_vecset(q, np.arange(1000)))
+    ix = B.Index.build(B.DeviceVecs(subset_vecset(d, np.arange(12_000))), B.build_params(16, nd_rounds=1, n_entry=16))
+    debug_knobs("search_bounds", 2)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    new = ix.insert(docs)         # searches for 8,000 documents among 20,000: a table of 640 MB
+    torch.cuda.synchronize()
+    free1 = torch.cuda.mem_get_info()[0]
+    assert free0 - free1 < 200 << 20, free0 - free1
+    small = new.bruteforce_topk(few, 3)     # 80 MB, which stay
+    out = new.bruteforce_topk(qs, 3)        # 2.4 GB
+    torch.cuda.synchronize()
+    assert free1 - torch.cuda.mem_get_info()[0] < 200 << 20, free1 - torch.cuda.mem_get_info()[0]
+    assert all(torch.equal(a, b[:1000]) for a, b in zip(small, out))
+    ix.close(); new.close()
+
+
 def test_any_number_of_streams_in_turn_search_with_bounds(debug_knobs):
     """A search with bounds decides more documents without their dense rows: every stream's does, and none beyond the first few
     takes more memory."""
