@@ -171,7 +171,7 @@ int ap_bound_ingest(ap_index *ix, hipStream_t st) {
     auto take = [&](size_t bytes) { const size_t a = at; at += ap_up(bytes, 256); return a; };
     const size_t o_clear = take(n_clear * 4), o_col = take((size_t)all * 4), o_run = take((size_t)all * 8), o_post = take((nnz + 1) * 8),
                  o_norms = take((size_t)c.n * 24), o_rows = take((size_t)c.n * (size_t)(kd + kh) * 2);
-    if (at > ((size_t)1 << 30)) {
+    if (at > ((size_t)64 << 20)) {
         size_t free_b = 0, total_b = 0;
         if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || at > free_b / 4) { (void)hipGetLastError(); return AP_OK; }
     }

@@ -1821,6 +1821,7 @@ struct BuildBufs {
     void release() {
         void *p[] = {knn[0], knn[1], knn_sc[0], knn_sc[1], spi[0], spi[1], sps[0], sps[1], se, sorted};
         for (void *x : p) if (x) (void)hipFree(x);
+        *this = BuildBufs();
     }
 };
 
@@ -1833,7 +1834,7 @@ static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
     hipEvent_t *ev = marks.ev;
     auto mark = [&](int i) { return hipEventRecord(ev[i], st); };
     AP_CHECK_HIP(mark(0));
-    AP_TRY(ap_ingest_impl(ix, st));
+    AP_TRY(ap_ingest_impl(ix, false, st));
     AP_CHECK_HIP(mark(1));
     for (int i = 0; i < 2; i++) {
         AP_TRY(ap_dev_alloc(&b.knn[i], (size_t)n * K));
@@ -1868,11 +1869,21 @@ static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
         ix->timings[i] = ms * 1e-3f;
         total += ms * 1e-3f;
     }
-    ix->timings[5] = total;
     ix->has_graph = true;
     // kept for later insertions
     ix->st_se = b.se; ix->st_sorted = b.sorted; ix->st_spi = b.spi[cur]; ix->st_sps = b.sps[cur];
     b.se = nullptr; b.sorted = nullptr; b.spi[cur] = nullptr; b.sps[cur] = nullptr;
+    // The columns of the bounds come when the construction's own memory is free again: its stages size theirs by what is free
+    // (the seed sweep by 62 % of it), and nothing of theirs reads the columns.  The time counts as ingest.
+    b.release();
+    AP_CHECK_HIP(mark(0));
+    AP_TRY(ap_bound_ingest(ix, st));
+    AP_CHECK_HIP(mark(1));
+    AP_CHECK_HIP(hipStreamSynchronize(st));
+    float ms = 0.f;
+    AP_CHECK_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
+    ix->timings[0] += ms * 1e-3f;
+    ix->timings[5] = total + ms * 1e-3f;
     return AP_OK;
 }
 

@@ -170,7 +170,7 @@ struct ApStageEvents {
 
 int ap_validate_corpus(const ap_corpus *c);
 int ap_validate_params(const ap_build_params *p);
-int ap_ingest_impl(ap_index *ix, hipStream_t st);
+int ap_ingest_impl(ap_index *ix, bool bounds, hipStream_t st);
 int ap_count_terms(const int32_t *idx, const float *tf, int64_t nnz, int32_t *df, unsigned long long *total, hipStream_t st);
 int ap_alloc_graph(ap_index *ix);
 int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);

@@ -265,6 +265,17 @@ def _one_term(rng, n, dim):
                   np.ones(n, np.float32), 50, 50)
 
 
+def _leave_free(want):
+    """Tensors that leave about `want` bytes of the device's memory free."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold = []
+    while torch.cuda.mem_get_info()[0] > want + (4 << 20):
+        hold.append(torch.empty(max(torch.cuda.mem_get_info()[0] - want, 2 << 20), dtype=torch.uint8, device="cuda:0"))
+    print("free", torch.cuda.mem_get_info()[0] >> 20, "MB", flush=True)
+    return hold
+
+
 def test_the_table_takes_a_share_of_the_free_memory(debug_knobs):
     rng, nq = np.random.default_rng(2), 10_000
     d = _one_term(rng, 20_000, 16)
@@ -274,7 +285,7 @@ def test_the_table_takes_a_share_of_the_free_memory(debug_knobs):
     want = [t.clone() for t in ix.search_batch(qs, 5, 32)]
     out = [t.clone() for t in want]
     torch.cuda.synchronize()
-    hold = torch.empty(torch.cuda.mem_get_info()[0] - (2 << 30), dtype=torch.uint8, device=docs.device)
+    hold = _leave_free(2 << 30)
     free0 = torch.cuda.mem_get_info()[0]
     assert 1 << 30 < free0 < 3 << 30
     debug_knobs("search_bounds", 2)
@@ -286,6 +297,36 @@ def test_the_table_takes_a_share_of_the_free_memory(debug_knobs):
         assert 0 < taken <= free0 // 4 + (8 << 20), taken
     del hold
     torch.cuda.empty_cache()
+    ix.close()
+
+
+def test_a_construction_has_the_memory_that_its_bounds_take_afterwards(debug_knobs):
+    """The seed sweep multiplies half of D D^T where its buffers (80 MB here) fit 62 % of the free memory, and all of it where
+    they do not.  With some 190 MB free at that
+    point they fit, unless the columns of the bounds (80 MB) are there before."""
+    n, dim, terms = 20_000, 1024, 60
+    rng = np.random.default_rng(2)
+    d = _one_term(rng, n, dim)
+    d.sp_indptr = d.tx_indptr = np.arange(0, n * terms + 1, terms, dtype=np.int64)
+    d.sp_idx = d.tx_idx = np.tile(np.arange(terms, dtype=np.int32), n) + np.repeat(rng.integers(0, 340, n).astype(np.int32), terms)
+    d.sp_val = d.tx_val = np.ones(n * terms, np.float32)
+    d.sp_vocab = d.tx_vocab = 400
+    docs, bp = B.DeviceVecs(d), B.build_params(16, knn_k=32, nd_rounds=0, n_entry=16)
+    debug_knobs("seed_sample_cols", 2048)
+    flops = {}
+    for one_sided in (1, 0):
+        debug_knobs("seed_one_sided", one_sided)
+        ix = B.Index.build(docs, bp)
+        flops[one_sided] = ix.build_counters()["seed_flops"]
+        graph = [t.clone() for t in ix.export_graph()]
+        ix.close()
+    assert flops[0] < 0.8 * flops[1]
+    hold = _leave_free(235 << 20)
+    ix = B.Index.build(docs, bp)
+    assert ix.build_counters()["seed_flops"] < 0.8 * flops[1]
+    del hold
+    torch.cuda.empty_cache()
+    assert all(torch.equal(a, b) for a, b in zip(graph, ix.export_graph()))
     ix.close()
 
 
