@@ -1,8 +1,6 @@
 // S1 as stand-alone calls: hybrid similarities of explicit (a, candidate)
 // pairs, and the exhaustive scorer + exact top-k used as ground truth.
 #include <algorithm>
-#include <new>
-#include <vector>
 #include "ap_tiles.hpp"
 
 #define AP_LIST_CAP 512  // a-side list entries staged in LDS; longer lists are read from global memory
@@ -113,11 +111,12 @@ extern "C" int ap_hybrid_scores_docs(const ap_index *ix, const int32_t *a_ids, i
 // document, then exact top-k by repeated arg-max under the total order.
 // The document row sits in registers and is reused for QB queries staged in
 // LDS, so the corpus is streamed nq/QB times instead of nq times.
+// list: the queries to do (place s of the batch is query list[s]); NULL: query s.
 #define AP_BF_QB 8
 #define AP_BF_QCAP 64
 
 template <int DT, int NV>
-__global__ __launch_bounds__(256) void k_bf_scores(ApVecs Q, ApVecs D, int32_t q0, int32_t nqb,
+__global__ __launch_bounds__(256) void k_bf_scores(ApVecs Q, ApVecs D, const int32_t *__restrict__ list, int32_t q0, int32_t nqb,
                                                    const float *__restrict__ w, int32_t w_stride,
                                                    float *__restrict__ scores /* nqb x n */) {
     constexpr int EPC = ApDense<DT>::EPC;
@@ -131,16 +130,16 @@ __global__ __launch_bounds__(256) void k_bf_scores(ApVecs Q, ApVecs D, int32_t q
     __shared__ float wq[AP_BF_QB][3];
     const int32_t qb = q0 + blockIdx.y * AP_BF_QB;
     const int32_t nq_here = (q0 + nqb - qb) < AP_BF_QB ? (q0 + nqb - qb) : AP_BF_QB;
-    for (int i = threadIdx.x; i < nq_here * Q.dim; i += blockDim.x)
-        qd[i] = static_cast<const float *>(Q.dense)[(int64_t)qb * Q.dim + i];
     for (int x = 0; x < nq_here; x++) {
-        const ApLists a = ap_stage_lists(Q, qb + x, qsi + x * AP_BF_QCAP, qsv + x * AP_BF_QCAP, qti + x * AP_BF_QCAP,
+        const int64_t q = list ? list[qb + x] : qb + x;   // uniform
+        for (int i = threadIdx.x; i < Q.dim; i += blockDim.x) qd[x * Q.dim + i] = static_cast<const float *>(Q.dense)[q * Q.dim + i];
+        const ApLists a = ap_stage_lists(Q, q, qsi + x * AP_BF_QCAP, qsv + x * AP_BF_QCAP, qti + x * AP_BF_QCAP,
                                          qtv + x * AP_BF_QCAP, AP_BF_QCAP);
         if (threadIdx.x == 0) {
             lists[x] = a;
-            wq[x][0] = w[(int64_t)(qb + x) * w_stride + 0];
-            wq[x][1] = w[(int64_t)(qb + x) * w_stride + 1];
-            wq[x][2] = w[(int64_t)(qb + x) * w_stride + 2];
+            wq[x][0] = w[q * w_stride + 0];
+            wq[x][1] = w[q * w_stride + 1];
+            wq[x][2] = w[q * w_stride + 2];
         }
     }
     __syncthreads();
@@ -172,11 +171,12 @@ __global__ __launch_bounds__(256) void k_bf_scores(ApVecs Q, ApVecs D, int32_t q
 
 // k rounds of block-wide arg-max: round r finds the best key that ranks after
 // the winner of round r-1.
-__global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ scores, int64_t n, int32_t k,
+__global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ scores, int64_t n, int32_t k, const int32_t *__restrict__ list, int32_t q0,
                                                  int32_t *__restrict__ out_ids, float *__restrict__ out_scores) {
     __shared__ uint64_t red[4];
     __shared__ uint64_t prev_s;
     const float *row = scores + (int64_t)blockIdx.x * n;
+    const int64_t q = list ? list[q0 + blockIdx.x] : (int64_t)q0 + blockIdx.x;
     uint64_t prev = ~0ull;
     for (int32_t r = 0; r < k; r++) {
         uint64_t best = 0;
@@ -194,8 +194,8 @@ __global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ score
             uint64_t b = red[0];
             for (int i = 1; i < 4; i++) b = red[i] > b ? red[i] : b;
             prev_s = b;
-            out_ids[(int64_t)blockIdx.x * k + r] = b ? ap_key_id(b) : -1;
-            out_scores[(int64_t)blockIdx.x * k + r] = b ? ap_key_score(b) : -INFINITY;
+            out_ids[q * k + r] = b ? ap_key_id(b) : -1;
+            out_scores[q * k + r] = b ? ap_key_score(b) : -INFINITY;
         }
         __syncthreads();
         prev = prev_s;  // 0 when nothing is left: later rounds find nothing either
@@ -282,8 +282,8 @@ __global__ __launch_bounds__(1024) void k_bound_topk(ApVecs Q, ApVecs D, int64_t
     }
 }
 
-// Every document scored, for queries [first, first + count).
-static int bf_exhaustive(const ap_index *ix, const ApVecs &Q, const float *w, int32_t ws, int32_t first, int32_t count, int32_t k, int32_t *out_ids,
+// Every document scored, for the `count` queries of the list (device), or the first `count` ones.
+static int bf_exhaustive(const ap_index *ix, const ApVecs &Q, const float *w, int32_t ws, const int32_t *list, int32_t count, int32_t k, int32_t *out_ids,
                          float *out_scores, hipStream_t st) {
     const int64_t n = ix->docs.n;
     // queries are processed in slabs so that the score scratch stays <= 2 GiB
@@ -296,8 +296,8 @@ static int bf_exhaustive(const ap_index *ix, const ApVecs &Q, const float *w, in
     const size_t smem = (size_t)AP_BF_QB * ((size_t)ix->docs.dim + 4 * AP_BF_QCAP) * 4;
     int rc = AP_OK;
     hipError_t e = hipSuccess;
-    for (int32_t q0 = first; q0 < first + count && e == hipSuccess; q0 += (int32_t)slab) {
-        const int32_t nqb = (first + count - q0) < slab ? (first + count - q0) : (int32_t)slab;
+    for (int32_t q0 = 0; q0 < count && e == hipSuccess; q0 += (int32_t)slab) {
+        const int32_t nqb = (count - q0) < slab ? (count - q0) : (int32_t)slab;
         int64_t xb = (n + 3) / 4;
         if (xb > 256) xb = 256;
         dim3 grid((unsigned)xb, (unsigned)((nqb + AP_BF_QB - 1) / AP_BF_QB));
@@ -305,12 +305,11 @@ static int bf_exhaustive(const ap_index *ix, const ApVecs &Q, const float *w, in
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bf_scores<DT, NV>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
             if (e == hipSuccess)
-                hipLaunchKernelGGL((k_bf_scores<DT, NV>), grid, dim3(256), smem, st, Q, ix->docs, q0, nqb, w, ws, scratch);
+                hipLaunchKernelGGL((k_bf_scores<DT, NV>), grid, dim3(256), smem, st, Q, ix->docs, list, q0, nqb, w, ws, scratch);
         });
         if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) break;
-        hipLaunchKernelGGL(k_bf_topk, dim3((unsigned)nqb), dim3(256), 0, st, scratch, n, k, out_ids + (int64_t)q0 * k,
-                           out_scores + (int64_t)q0 * k);
+        hipLaunchKernelGGL(k_bf_topk, dim3((unsigned)nqb), dim3(256), 0, st, scratch, n, k, list, q0, out_ids, out_scores);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -334,7 +333,7 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     ApBound b;
     const size_t held = ap_bound_held(ix, st);
     if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, 256, AP_BOUND_WS_BYTES, st, &b));
-    if (!b.table) return bf_exhaustive(ix, Q, w, ws, 0, q->nq, k, out_ids, out_scores, st);
+    if (!b.table) return bf_exhaustive(ix, Q, w, ws, nullptr, q->nq, k, out_ids, out_scores, st);
     int32_t *over = nullptr;
     AP_TRY(ap_dev_alloc(&over, (size_t)q->nq + 1));
     int rc = ap_fill_u32(over, 1, 0u, st);
@@ -348,27 +347,16 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     }
     b.finish();   // the host waits below: searches of this index on other streams need not
     int32_t n_over = 0;
-    std::vector<int32_t> list;
     hipError_t e = hipSuccess;
     if (rc == AP_OK) {
         e = hipMemcpyAsync(&n_over, over, sizeof(n_over), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e == hipSuccess && n_over > 0) {
-            try { list.resize((size_t)n_over); } catch (const std::bad_alloc &) { ap_set_error("out of host memory"); rc = AP_ENOMEM; }
-            if (rc == AP_OK) e = hipMemcpy(list.data(), over + 1, (size_t)n_over * sizeof(int32_t), hipMemcpyDeviceToHost);
-        }
     }
-    (void)hipFree(over);
     // a workspace that this call made larger than its own scratch ever was does not stay
     if (const size_t now = ap_bound_held(ix, st); now > held && now > AP_BOUND_KEEP_BYTES) ap_bound_give_back(ix, st);
-    if (rc != AP_OK) return rc;
-    if (e != hipSuccess) { ap_set_error("ap_bruteforce_topk failed: %s", hipGetErrorString(e)); return AP_EHIP; }
-    std::sort(list.begin(), list.end());
-    for (size_t i = 0; i < list.size();) {   // runs of queries the bounds left undecided
-        size_t j = i + 1;
-        while (j < list.size() && list[j] == list[j - 1] + 1) j++;
-        AP_TRY(bf_exhaustive(ix, Q, w, ws, list[i], (int32_t)(j - i), k, out_ids, out_scores, st));
-        i = j;
-    }
-    return AP_OK;
+    if (rc == AP_OK && e != hipSuccess) { ap_set_error("ap_bruteforce_topk failed: %s", hipGetErrorString(e)); rc = AP_EHIP; }
+    // the queries the bounds left undecided, in whatever order they were noted, as one batch (it waits for the stream)
+    if (rc == AP_OK && n_over > 0) rc = bf_exhaustive(ix, Q, w, ws, over + 1, n_over, k, out_ids, out_scores, st);
+    (void)hipFree(over);
+    return rc;
 }

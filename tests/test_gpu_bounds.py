@@ -397,6 +397,30 @@ def test_exact_topk_out_of_the_bounds(base, n, dim, k):
     ix.close()
 
 
+def test_scattered_undecided_queries_of_an_exact_topk():
+    """Weights of zero tie all documents, which the bounds leave undecided.  Every third query decided, the others not: the same
+    results, and no slower than none decided."""
+    n, nq, k = 20_000, 600, 20
+    w, docs, qs = _workload("tiny", n=n, nq=nq, dim=32, sp=("fixed", 2), tx=("fixed", 2))
+    ix = B.Index.ingest(docs, B.build_params(8))
+    pw = np.random.default_rng(1).uniform(0.1, 1.0, (nq, 3)).astype(np.float32)
+    pw[np.arange(nq) % 3 != 0] = 0
+    took = {}
+    for name, weights in (("none", np.zeros_like(pw)), ("some", pw)) * 2:
+        weights = torch.from_numpy(weights).to(docs.device)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        ids, sc = ix.bruteforce_topk(qs, k, weights)
+        torch.cuda.synchronize()
+        took[name] = time.perf_counter() - t0
+    print({a: f"{1e3 * b:.1f} ms" for a, b in took.items()})
+    all_sc = ix.hybrid_scores(qs, np.tile(np.arange(n, dtype=np.int32), (nq, 1)), pw)[:, :, 3]
+    want, at = torch.sort(all_sc, dim=1, descending=True, stable=True)
+    assert torch.equal(sc, want[:, :k]) and torch.equal(ids, at[:, :k].to(torch.int32))
+    assert took["some"] < 1.25 * took["none"]
+    ix.close()
+
+
 @pytest.mark.parametrize("w_k", [0.5, -0.4, 0.0])
 def test_entity_searches_with_and_without_bounds_are_the_same(debug_knobs, w_k):
     from paper_2511_00855_amd.synth import make_entity_graph
