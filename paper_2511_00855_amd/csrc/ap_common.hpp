@@ -228,6 +228,15 @@ void ap_bound_release(ap_index *ix);
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b);
 size_t ap_bound_held(const ap_index *ix, hipStream_t st);
 void ap_bound_give_back(const ap_index *ix, hipStream_t st);
+// An allocation that a call on stream st cannot do without: where it fails, the stream's workspace of bounds makes room.
+template <typename T>
+static inline int ap_bound_make_room(const ap_index *ix, hipStream_t st, T **p, size_t count) {
+    if (ap_dev_alloc(p, count) == AP_OK) return AP_OK;
+    (void)hipGetLastError();
+    AP_CHECK_HIP(hipStreamSynchronize(st));
+    ap_bound_give_back(ix, st);
+    return ap_dev_alloc(p, count);
+}
 int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, hipStream_t st, ApBound *b);
 int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
                   const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);

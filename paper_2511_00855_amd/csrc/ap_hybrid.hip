@@ -292,7 +292,7 @@ static int bf_exhaustive(const ap_index *ix, const ApVecs &Q, const float *w, in
     if (slab < AP_BF_QB) slab = AP_BF_QB;
     if (slab > count) slab = (count + AP_BF_QB - 1) / AP_BF_QB * AP_BF_QB;
     float *scratch = nullptr;
-    AP_TRY(ap_dev_alloc(&scratch, (size_t)slab * (size_t)n));
+    AP_TRY(ap_bound_make_room(ix, st, &scratch, (size_t)slab * (size_t)n));
     const size_t smem = (size_t)AP_BF_QB * ((size_t)ix->docs.dim + 4 * AP_BF_QCAP) * 4;
     int rc = AP_OK;
     hipError_t e = hipSuccess;

@@ -899,7 +899,7 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     const size_t need = words * (size_t)ws->slab;
     if (need > ix->visited_words) {
         if (ix->visited) { AP_CHECK_HIP(hipStreamSynchronize(st)); (void)hipFree(ix->visited); ix->visited = nullptr; ix->visited_words = 0; }
-        AP_TRY(ap_dev_alloc(&ix->visited, need));
+        AP_TRY(ap_bound_make_room(ix, st, &ix->visited, need));
         ix->visited_words = need;
     }
     if ((size_t)nq * 3 > ix->search_counts_cap) {

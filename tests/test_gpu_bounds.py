@@ -220,7 +220,7 @@ def test_two_streams_search_one_index_with_tables_of_their_own(debug_knobs):
 def test_a_search_does_not_wait_on_the_host_for_an_exact_topk(debug_knobs):
     """Weights of zero: every document ties, which the bounds leave undecided, and every document is scored.  Meanwhile another
     thread enqueues a search of the same index on another stream."""
-    n, nq = 20_000, 6_000
+    n, nq = 20_000, 20_000
     w, docs, qs = _workload("tiny", n=n, nq=nq, dim=32, sp=("fixed", 2), tx=("fixed", 2))
     few = B.DeviceVecs(subset_vecset(w.queries, np.arange(20)))
     ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
@@ -239,8 +239,9 @@ def test_a_search_does_not_wait_on_the_host_for_an_exact_topk(debug_knobs):
             t["begin"] = time.perf_counter()
             t["ids"] = ix.bruteforce_topk(qs, 100, zero)[0]
             t["end"] = time.perf_counter()
-    exact()
-    torch.cuda.synchronize()
+    for _ in range(2):   # the first call also loads its kernels
+        exact()
+        torch.cuda.synchronize()
     took = t["end"] - t["begin"]
     assert torch.equal(t["ids"], torch.arange(100, dtype=torch.int32, device=docs.device).repeat(nq, 1))
     th = threading.Thread(target=exact)
@@ -297,6 +298,39 @@ def test_the_table_takes_a_share_of_the_free_memory(debug_knobs):
         assert 0 < taken <= free0 // 4 + (8 << 20), taken
     del hold
     torch.cuda.empty_cache()
+    ix.close()
+
+
+def test_an_exact_topk_gets_the_memory_of_its_table_for_its_scores():
+    """All documents tie: the scores of all queries, 2 GiB at a time, fit what is free, but not beside the table of bounds that
+    left them undecided."""
+    rng, n, nq = np.random.default_rng(2), 20_000, 30_000
+    docs, qs = B.DeviceVecs(_one_term(rng, n, 16)), B.DeviceVecs(_one_term(rng, nq, 16))
+    ix = B.Index.ingest(docs, B.build_params(8))
+    zero = torch.zeros((nq, 3), device=docs.device)
+    hold = _leave_free(2300 << 20)
+    ids, sc = ix.bruteforce_topk(qs, 2, zero)
+    del hold
+    torch.cuda.empty_cache()
+    assert torch.equal(ids, torch.arange(2, dtype=torch.int32, device=docs.device).repeat(nq, 1)) and (sc == 0).all()
+    ix.close()
+
+
+def test_a_search_gets_the_memory_of_its_table_for_its_visited_sets(debug_knobs):
+    rng, n = np.random.default_rng(2), 20_000
+    q = _one_term(rng, 30_000, 16)
+    docs, qs, few = B.DeviceVecs(_one_term(rng, n, 16)), B.DeviceVecs(q), B.DeviceVecs(subset_vecset(q, np.arange(5000)))
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
+    out = (torch.empty((qs.n, 5), dtype=torch.int32, device=docs.device), torch.empty((qs.n, 5), device=docs.device))
+    debug_knobs("search_visited_global", 1)
+    debug_knobs("search_bounds", 2)
+    small = [t.clone() for t in ix.search_batch(few, 5, 32)]   # visited sets 12.5 MB, a table of 400 MB
+    hold = _leave_free(40 << 20)
+    ix.search_batch(qs, 5, 32, out=out)                        # visited sets 75 MB
+    torch.cuda.synchronize()
+    del hold
+    torch.cuda.empty_cache()
+    assert all(torch.equal(a, b[:few.n]) for a, b in zip(small, out))
     ix.close()
 
 
