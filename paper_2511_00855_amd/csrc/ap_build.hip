@@ -705,7 +705,7 @@ struct ApRefineHints {
 //    the candidate to the threshold T of the fused list or to the last entry of the per-path list by the dense part.
 //    T is the list's last score in later rounds.  In the first round, whose list carries no fused scores, the K candidates
 //    with the best sparse and lexical parts are scored first, and T is the least of their scores.
-// Phases: records of all candidates (a wave each, two on their way at a time), a thread per candidate decides about the
+// Phases: records of all candidates (a wave each, AP_RF_G on their way at a time), a thread per candidate decides about the
 // dense rows, dense rows of those that need one (a wave each), sort, lists.  Measured on 200,000 documents of 1,024 bf16
 // columns, three rounds: 308 ms with every candidate
 // scored in full, 150 ms now (7 TB/s of traffic in the first round: what a read-mostly kernel reaches here); 768 f32 columns,
@@ -722,7 +722,7 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
     __shared__ int32_t cand[AP_MAXC];
     __shared__ uint64_t keys[2048];   // fused keys of the candidates that can enter the list, sorted in place afterwards (AP_MAXC padded to a power of two)
     // per candidate: before it is scored, where its record lies, the two lengths and the dense norm; then the norm and the
-    // two list parts; then the three component scores (dense part -inf: not needed, not computed)
+    // two list parts; then the three component scores (candidates with the sign bit keep the norm: their dense part is not needed)
     __shared__ float comp[3][AP_MAXC];
     __shared__ int32_t l_sp_idx[AP_A_CAP], l_tx_idx[AP_A_CAP];
     __shared__ float l_sp_val[AP_A_CAP], l_tx_val[AP_A_CAP];
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
             float bd, bf;
             bound(t, bd, bf);
             if (!(bf < T) || !(bd < dP)) need[atomicAdd(&s_need, 1)] = (uint16_t)t;
-            else comp[0][t] = -INFINITY;
+            else cand[t] |= (int32_t)0x80000000;   // its dense part is not computed
         }
         __syncthreads();
         dense_rows(n_first, ap_uniform_i32(s_need), 0);
@@ -980,7 +980,7 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
     if (wave < 3) {
         const int p = wave;
         const int32_t nold = (int32_t)__popcll(__ballot(lane < 32 && oldk[p][lane & 31] != 0ull));
-        auto cand_key = [&](int32_t t) { return comp[p][t] == -INFINITY ? 0ull : ap_make_key(comp[p][t], cand[t] & ~AP_RF_TOP, 1u); };
+        auto cand_key = [&](int32_t t) { return p == 0 && cand[t] < 0 ? 0ull : ap_make_key(comp[p][t], cand[t] & 0x3fffffff, 1u); };
         uint64_t prev = ~0ull;
         auto put = [&](int32_t r, uint64_t best) {
             for (int o = 32; o > 0; o >>= 1) {

@@ -51,3 +51,29 @@ def test_rounds_of_a_construction_equal_rounds_called_one_by_one(name):
         # a round of a construction evaluates no more similarities than the same round on its own
         assert full.build_counters()["refine_similarities"] <= ix.build_counters()["refine_similarities"]
         full.close(); ix.close()
+
+
+def test_dense_scores_beyond_the_range_keep_their_place():
+    """Rows of +-3e19 in one column: products of two are +-inf in f32.  A list with room takes a -inf like any other score, in a
+    round of a construction and in one on its own, as the oracle does."""
+    import oracle as O
+    from paper_2511_00855_amd.synth import VecSet
+    n, K, S, P, rng = 8, 8, 8, 6, np.random.default_rng(5)
+    dense = np.zeros((n, 4), np.float32)
+    dense[:, 0] = np.float32(3e19) * np.array([1, -1, 1, 1, -1, -1, 1, -1], np.float32)
+    ip = np.arange(0, 3 * n + 1, 3, dtype=np.int64)
+    terms = lambda: np.concatenate([np.sort(rng.permutation(10)[:3]) for _ in range(n)]).astype(np.int32)
+    d = VecSet(n, 4, dense, ip, terms(), rng.uniform(0.5, 2.0, 3 * n).astype(np.float32), ip, terms(), np.ones(3 * n, np.float32), 10, 10)
+    docs, bp = B.DeviceVecs(d), B.build_params(8, knn_k=K, nd_rounds=1, nd_sample=S, sp_len=P, n_entry=4)
+    full = B.Index.build(docs, bp)
+    _, _, spi, sps = [t.cpu().numpy() for t in full.export_build_state()]
+    ix = B.Index.ingest(docs, bp)
+    ids, _ = ix.stage_seed_knn(K)
+    i2, s2 = O.empty_sp(n, P)
+    _, _, gi, gs = [t.cpu().numpy() for t in ix.stage_refine(K, S, P, ids, i2, s2)]
+    D = O.encode_docs(d)
+    _, _, oi, os_ = O.refine_round(D, [1.0, 1.0, 1.0], K, S, P, ids.cpu().numpy(), i2, s2)
+    assert np.isneginf(os_[0]).any() and (oi[0] >= 0).all()
+    assert np.array_equal(oi[0], gi[0]) and np.array_equal(os_[0], gs[0])
+    assert np.array_equal(spi, gi) and np.array_equal(sps, gs)
+    full.close(); ix.close()
