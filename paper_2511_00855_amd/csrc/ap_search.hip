@@ -661,7 +661,7 @@ void k_search(ApSearchArgs g) {
                 }
             }
             const uint64_t pkey = mine >= 0 ? cur[mine] : 0ull;
-            if (FLOOR && waiting && release(found, __any(mine >= 0 && ap_key_score(pkey) < floor_score))) scan = 0;
+            if (FLOOR && waiting && release(found, __any(mine >= 0 && !(ap_key_score(pkey) >= floor_score)))) scan = 0;   // a NaN counts as below
             else {
                 if (mine >= 0) {
                     s_par[lane] = ap_pool_id<KW>(pkey);     // every wave stores the same ids

@@ -165,6 +165,76 @@ def test_large_pools_with_a_floor_are_the_same(debug_knobs, base, n, dim):
     ix.close()
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+def test_rows_that_are_not_finite_are_scored(debug_knobs, bf16):
+    """Infinities and NaN of either sign in a third of the dense rows: bounds that compare with nothing keep nothing out.  The
+    order of such scores is that of their keys (a NaN with the sign bit ranks last), with and without bounds."""
+    n, nq, dim = 6007, 25, 64
+    w, _, qs = _workload("tiny", n=n, nq=nq, dim=dim, vocab=5_000)
+    rng, d = np.random.default_rng(6), w.docs
+    bits = d.dense.view(np.uint32)
+    bits &= np.uint32(0xffff0000)    # bf16 values in either case
+    rows = rng.permutation(n)[:n // 3]
+    bits[rows, rng.integers(0, dim, len(rows))] = rng.choice(np.array([0x7f800000, 0xff800000, 0x7fc00000, 0xffc00000, 0xffc00000, 0xffc00000, 0xffc00000], np.uint32), len(rows))
+    if bf16:
+        d.dense_bf16 = (bits >> 16).astype(np.uint16)
+    docs = B.DeviceVecs(d, bf16=bf16)
+    ix = B.Index.import_graph(docs, B.build_params(64, n_entry=16), rng.integers(0, n, (n, 64)).astype(np.int32), rng.permutation(n)[:16].astype(np.int32))
+    pw = rng.uniform(0.1, 1.0, (nq, 3)).astype(np.float32)
+    bytes_of = lambda t: t.view(torch.int32) if t.dtype == torch.float32 else t
+    for k, beam, width in ((10, 64, 2), (10, 800, 16), (100, 4300, 2), (1, 9000, 16)):
+        got = {}
+        for mode, floor in ((1, 0), (2, 0), (2, 1), (2, 2)):
+            debug_knobs("search_bounds", mode)
+            debug_knobs("search_floor", floor)
+            out = ix.search_batch(qs, k, beam, pw, search_width=width)
+            got[mode, floor] = [bytes_of(t).clone() for t in out] + [ix.search_stats(nq)[0][:, :2].clone()]
+        for key in got:
+            assert all(torch.equal(a, b) for a, b in zip(got[1, 0], got[key])), (key, k, beam, width)
+    debug_knobs("search_bounds", 0)
+    debug_knobs("search_floor", 0)
+    full = [bytes_of(t) for t in ix.bruteforce_topk(qs, 257, pw)]   # more than the bounds are used for: every document scored
+    for k in (1, 10, 200):
+        assert all(torch.equal(a[:, :k], bytes_of(b)) for a, b in zip(full, ix.bruteforce_topk(qs, k, pw))), k
+    ix.close()
+
+
+def test_what_waits_comes_before_scores_that_are_no_numbers(debug_knobs):
+    """A hundred documents above the floor lead to 300 that wait below it and to 100 whose score is a NaN that ranks last; the
+    first lead to 700 more, the second to 500 that score higher.  Those that wait are expanded before the NaN are, and push
+    them out of the pool: the 500 are never met."""
+    n, R, nq, L = 20_000, 64, 3, 800
+    rng = np.random.default_rng(1)
+    d, q = _one_term(rng, n, 64), _one_term(rng, nq, 64)
+    d.dense[:] = 0.0
+    q.dense[:] = 0.0
+    q.dense[:, 0] = 1.0
+    top, W, X, N, Y = np.arange(100), 2000 + np.arange(300), 3000 + np.arange(700), 4000 + np.arange(100), 5000 + np.arange(500)
+    d.dense[:1200, 0] = 1.2     # what the estimate of the floor is made of: a twentieth of the documents
+    for group, score in ((top, 2.0), (W, 0.5), (X, 0.4), (Y, 0.6)):
+        d.dense[group, 0] = score - 1e-4 * np.arange(len(group))
+    d.dense.view(np.uint32)[N, 1] = 0xffc00000
+    graph = np.full((n, R), -1, np.int32)
+    for j in range(100):   # the first 80, which are expanded first, know only their like: waiting has begun when the others are met
+        graph[top[j]] = top[(j + 1 + np.arange(R)) % 100] if j < 80 else np.concatenate([W[(15 * (j - 80) + np.arange(44)) % 300], N[(5 * (j - 80) + np.arange(20)) % 100]])
+        graph[N[j]] = Y[(5 * j + np.arange(R)) % 500]
+    for j in range(300):
+        graph[W[j]] = X[(3 * j + np.arange(R)) % 700]
+    docs, qs = B.DeviceVecs(d), B.DeviceVecs(q)
+    ix = B.Index.import_graph(docs, B.build_params(R, n_entry=16), graph, top[:16].astype(np.int32))
+    pw = np.tile(np.float32([1.0, 0.0, 0.0]), (nq, 1))
+    got = {}
+    for mode, floor in ((1, 0), (2, 0), (2, 1)):
+        debug_knobs("search_bounds", mode)
+        debug_knobs("search_floor", floor)
+        got[mode, floor] = [t.clone() for t in ix.search_batch(qs, L, L, pw, search_width=16)] + [ix.search_stats(nq)[0][:, :2].clone()]
+    ids = got[1, 0][0].cpu().numpy()
+    assert set(ids[0]) == set(top) | set(W) | set(ids[0][400:]) and set(ids[0][400:]) <= set(X)
+    for key in got:
+        assert all(torch.equal(a, b) for a, b in zip(got[1, 0], got[key])), key
+    ix.close()
+
+
 def test_slabs_of_the_table_and_a_captured_search(debug_knobs):
     """A table that holds some twenty of 70 queries: the search runs in slabs, each with a table of its own.  A captured search
     goes without bounds, and after such a search of the same batch it needs no memory that is not there."""
