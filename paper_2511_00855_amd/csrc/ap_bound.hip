@@ -16,6 +16,8 @@
 int ap_validate_queries(const ap_queries *q);
 
 #define AP_BOUND_HEAD 512
+#define AP_BOUND_QMAX 1e14f
+#define AP_BOUND_DMAX 1e15f
 #define AP_BOUND_QT 256              // queries and documents of a tile
 #define AP_BOUND_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of columns is kept for
 
@@ -221,7 +223,9 @@ static inline int32_t bound_kdense(const ap_index *ix) { return ix->bd_kd ? ix->
 // like values it does, but over many values it takes about 0.0017 of the norm.  qc[8 r ..]: per part |q^| and the factor of
 // |d|, then (6) the relative slack of an addition of the tail.  The factor of |d| is |q - q^| and, times |q|, what everything
 // else takes: the product's accumulation (k 2^-23), the rounding of the scoring kernels' own sums and of the tail's additions
-// (1e-5 and 2^-22 a term); 1e-18 of the norms for squares and products of values so small that they underflow.
+// (1e-5 and 2^-22 a term); 1e-18 of the norms for squares and products of values so small that they underflow.  Values so
+// large that a partial sum of the scoring kernels may overflow where the product's does not (a query's beyond AP_BOUND_QMAX, a
+// part of a document beyond AP_BOUND_DMAX) give a bound of infinity.
 __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int64_t nq, int32_t kdense,
                                                        int32_t kh, int32_t nsp, int32_t ntx, const int32_t *__restrict__ col,
                                                        uint16_t *__restrict__ qm, float *__restrict__ qc) {
@@ -243,11 +247,13 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
         sum[3 * part] = fmaf(x, x, sum[3 * part]); sum[3 * part + 1] = fmaf(y, y, sum[3 * part + 1]); sum[3 * part + 2] = fmaf(off, off, sum[3 * part + 2]);
         return y16;
     };
+    bool large = false;
     for (int32_t c = threadIdx.x * 4; c < kdense; c += 1024) {
         float x[4] = {0.f, 0.f, 0.f, 0.f};
         if (c < Q.dim) {
             const float4 y = *reinterpret_cast<const float4 *>(static_cast<const float *>(Q.dense) + q * Q.dim + c);
             x[0] = wd * y.x; x[1] = wd * y.y; x[2] = wd * y.z; x[3] = wd * y.w;
+            large = large || !(fmaxf(fmaxf(fabsf(y.x), fabsf(y.y)), fmaxf(fabsf(y.z), fabsf(y.w))) <= AP_BOUND_QMAX);
         }
         uint32_t y16[4];
 #pragma unroll
@@ -262,9 +268,11 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
         for (int64_t p = b + threadIdx.x; p < e; p += 256) {
             const int32_t t = part ? Q.tx_idx[p] : Q.sp_idx[p];
             if (t < 0 || t >= (part ? ntx : nsp)) continue;
+            const float v = part ? Q.tx_val[p] : Q.sp_val[p];
+            large = large || !(fabsf(v) <= AP_BOUND_QMAX);
             const int32_t c = col[part ? nsp + t : t];
             if (c < 0) continue;
-            const float x = part ? wf * Q.tx_val[p] : ws * Q.sp_val[p];
+            const float x = (part ? wf : ws) * v;
             head[c] = (uint16_t)(part ? add(2, x) : add(1, x));
         }
     }
@@ -273,14 +281,14 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
         sum[i] = ap_wave_sum(sum[i]);
         if ((threadIdx.x & 63) == 0) red[i][threadIdx.x >> 6] = sum[i];
     }
-    __syncthreads();
+    large = __syncthreads_or(large) != 0;
     for (int32_t c = threadIdx.x * 8; c < kh; c += 2048) *reinterpret_cast<uint4 *>(row + kdense + c) = *reinterpret_cast<const uint4 *>(head + c);
     if (threadIdx.x == 0) {
         float norm[9];
         for (int i = 0; i < 9; i++) norm[i] = sqrtf(red[i][0] + red[i][1] + red[i][2] + red[i][3]) * 1.0001f;
         const float rel = 1e-5f + 2.4e-7f * (float)terms, other = rel + 1.2e-7f * (float)(kdense + kh);
         for (int p = 0; p < 3; p++) {
-            qc[r * 8 + 2 * p] = norm[3 * p + 1] + 1e-18f;
+            qc[r * 8 + 2 * p] = large ? INFINITY : norm[3 * p + 1] + 1e-18f;
             qc[r * 8 + 2 * p + 1] = norm[3 * p + 2] + norm[3 * p] * other + 1e-18f;
         }
         qc[r * 8 + 6] = rel;
@@ -314,7 +322,7 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
         const int p = t / AP_BOUND_QT, j = t % AP_BOUND_QT;
         const float2 dn = norms[p * n + (d0 + j < n ? d0 + j : n - 1)];
         s_qc[p][j] = *reinterpret_cast<const float2 *>(qc + (r0 + j) * 8 + 2 * p);
-        s_dn[p][j] = make_float2(fmaf(dn.x, 1.0001f, 1e-15f), fmaf(dn.y, 1.0001f, 1e-15f));
+        s_dn[p][j] = make_float2(fmaf(dn.x, 1.0001f, 1e-15f), dn.y <= AP_BOUND_DMAX ? fmaf(dn.y, 1.0001f, 1e-15f) : INFINITY);
     }
     const int32_t kq = n_chunks * AP_BK16;
     const char *qa = reinterpret_cast<const char *>(qm + r0 * kq);
@@ -432,7 +440,7 @@ __global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__res
             for (uint32_t i = threadIdx.x; i < r.y; i += 256) {
                 const uint2 dv = post[r.x + i];
                 const float c = x * __uint_as_float(dv.y);
-                row[dv.x] = ap_bound_round(row[dv.x] + fmaf(fabsf(c), rel, c));
+                row[dv.x] = ap_bound_round(row[dv.x] + (fabsf(__uint_as_float(dv.y)) <= AP_BOUND_DMAX ? fmaf(fabsf(c), rel, c) : INFINITY));
             }
             if (r.y) __syncthreads();
         }

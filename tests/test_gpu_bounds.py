@@ -199,6 +199,42 @@ def test_rows_that_are_not_finite_are_scored(debug_knobs, bf16):
     ix.close()
 
 
+@pytest.mark.parametrize("where", ["dense", "lists"])
+def test_partial_sums_that_overflow(debug_knobs, where):
+    """Sums of the scoring kernels that are infinite although the bounds' are not: weights that make up for values beyond the
+    range only after the sum, and products of 3e38 of either sign in an order in which they cancel."""
+    n, nq, dim, rng = 2000, 20, 64, np.random.default_rng(9)
+    d, q = _one_term(rng, n, dim), _one_term(rng, nq, dim)
+    far = rng.permutation(n)[:40]
+    if where == "dense":
+        q.dense[:, 4] = np.float32(1e30)
+        d.dense[:, 4] = 0.0
+        d.dense[far, 4] = np.float32(1e9)
+    else:   # entries 0 and 64 of a list are summed by one lane, 1 and 66 by others; the bounds add the terms in ascending order
+        terms = 600   # as frequent as each other, more than there are columns: none has one
+        d.sp_indptr = np.arange(0, n * terms + 1, terms, dtype=np.int64)
+        d.sp_idx = np.tile(np.arange(terms, dtype=np.int32) * 3, n)
+        val = np.ones((n, terms), np.float32)
+        val[far[:, None], [0, 1, 64, 66]] = np.float32(1.7e19) * np.array([1, -1, 1, -1], np.float32)
+        d.sp_val, d.sp_vocab, q.sp_vocab = val.reshape(-1), 1800, 1800
+        q.sp_indptr = np.arange(0, nq * 4 + 1, 4, dtype=np.int64)
+        q.sp_idx, q.sp_val = np.tile(np.array([0, 3, 192, 198], np.int32), nq), np.full(nq * 4, np.float32(1.7e19))
+    docs, qs = B.DeviceVecs(d), B.DeviceVecs(q)
+    ix = B.Index.import_graph(docs, B.build_params(64, n_entry=16), rng.integers(0, n, (n, 64)).astype(np.int32), rng.permutation(n)[:16].astype(np.int32))
+    for pw in (np.ones((nq, 3)), np.tile([1e-20, 1e-20, 1.0], (nq, 1))):
+        pw = pw.astype(np.float32)
+        sc = ix.hybrid_scores(qs, np.tile(np.arange(n, dtype=np.int32), (nq, 1)), pw)[:, :, 3]
+        up = ix.stage_score_bounds(qs, pw)
+        assert bool(torch.isinf(sc).any()) and not bool((up < sc).any())
+        got = []
+        for mode in (1, 2):
+            debug_knobs("search_bounds", mode)
+            got.append([t.view(torch.int32).clone() for t in ix.search_batch(qs, 10, 64, pw)])
+        debug_knobs("search_bounds", 0)
+        assert all(torch.equal(a, b) for a, b in zip(*got))
+    ix.close()
+
+
 def test_what_waits_comes_before_scores_that_are_no_numbers(debug_knobs):
     """A hundred documents above the floor lead to 300 that wait below it and to 100 whose score is a NaN that ranks last; the
     first lead to 700 more, the second to 500 that score higher.  Those that wait are expanded before the NaN are, and push
