@@ -317,7 +317,7 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
                     similarities_per_s=round(refine_sims / max(bt["refine"], 1e-9), 1)),
         prune=dict(bound="alu", pair_similarities=N * K * (K - 1) // 2,
                    pair_similarities_per_s=round(N * K * (K - 1) / 2 / max(bt["prune"], 1e-9), 1),
-                   note="dense Gram (MFMA) + list merges + detour sort + prune walk; one pair = both sparse parts merged"))
+                   note="dense Gram (MFMA) + products of the lists by columns (MFMA) + detour sort + prune walk; one pair = all three parts"))
 
     # ---- ground truth: exact hybrid top-k under the same weights
     t0 = time.time()
@@ -370,7 +370,7 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
     t1 = time.time()
     for _ in range(steps):
         ix.search_batch(qs, k, beam, wq, out=out, search_width=width)
-        kernel_ms.append(ix.search_kernel_ms())   # events recorded around the kernel on its own stream
+        kernel_ms.append(ix.search_kernel_ms())   # events recorded around the kernels on their own stream
     torch.cuda.synchronize()
     elapsed = time.time() - t1
     ms_per_step = elapsed * 1e3 / steps
@@ -380,12 +380,14 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
     counts = counts.cpu().numpy().astype(np.int64)
     n_dist, n_iter, n_skip = int(counts[:, 0].sum()), int(counts[:, 1].sum()), int(counts[:, 2].sum())
 
-    # ---- roofline of the search kernel: algorithmic bytes / measured kernel time.  Units per launch: full similarities
-    # (descriptor + lists + dense row), partial ones (the document provably cannot enter the pool: its 4-byte bound), one
-    # adjacency row per iteration (at least one parent is expanded in every iteration), and the table of bounds itself, which
-    # the kernel time includes: every document once, every bound written.
+    # ---- roofline of a search: algorithmic bytes / measured time of its kernels (the events enclose the table of bounds and
+    # k_search).  A lower bound of what they read and write: full similarities (descriptor + lists + dense row); 4 bytes for every
+    # document that was decided without its dense row (its bound; the counters do not tell those whose record was read as well);
+    # one adjacency row per iteration (at least one parent is expanded in every iteration); the documents' columns of bf16 once
+    # (a slab of queries reads them again) and every bound written.
     partial_bytes = 4.0
-    bytes_per_launch = (n_dist - n_skip) * bytes_per_dist + n_skip * partial_bytes + n_iter * w.degree * 4.0 + N * bytes_per_dist + 4.0 * N * nq
+    column_bytes = 2.0 * ((w.docs.dim + 63) // 64 * 64 + min(512, (w.docs.sp_vocab + w.docs.tx_vocab + 63) // 64 * 64))
+    bytes_per_launch = (n_dist - n_skip) * bytes_per_dist + n_skip * partial_bytes + n_iter * w.degree * 4.0 + N * column_bytes + 4.0 * N * nq
     bytes_if_all_full = n_dist * bytes_per_dist + n_iter * w.degree * 4.0
     k_ms = float(np.mean(kernel_ms))
     achieved = bytes_per_launch / (k_ms * 1e-3) / 1e9
@@ -399,7 +401,7 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
         t = None
     if t is not None:   # HBM-side bytes per launch from the committed rocprofv3 --pmc summary of this same configuration
         traffic = round(t["fetch_bytes_per_launch"] + t["write_bytes_per_launch"])
-    roofline = dict(bound="hbm", kernel="k_search", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
+    roofline = dict(bound="hbm", kernel="k_search + table of bounds", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic, kernel_ms=round(k_ms, 3),
                     bytes_per_full_similarity=round(bytes_per_dist, 1), bytes_per_partial_similarity=round(partial_bytes, 1),
                     similarities_per_launch=n_dist, partial_similarities_per_launch=n_skip,
