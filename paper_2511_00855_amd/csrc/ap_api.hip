@@ -219,8 +219,8 @@ int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st) {
     return AP_OK;
 }
 
-// bounds: lay out the columns of the bounds as well (a construction does it at its end, ap_bound_ingest)
-int ap_ingest_impl(ap_index *ix, bool bounds, hipStream_t st) {
+// bounds_share: the columns of the bounds may take this part of the free memory (ap_bound_ingest)
+int ap_ingest_impl(ap_index *ix, int bounds_share, hipStream_t st) {
     const ap_corpus &c = ix->corpus;
     int64_t last = 0;
     AP_CHECK_HIP(hipMemcpyAsync(&last, c.tx_indptr + c.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
@@ -289,7 +289,7 @@ int ap_ingest_impl(ap_index *ix, bool bounds, hipStream_t st) {
         hipLaunchKernelGGL(k_pack_records, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, ix->docs, ix->dense_norm, ix->rec, ix->meta);
         AP_CHECK_HIP(hipGetLastError());
     }
-    if (bounds) AP_TRY(ap_bound_ingest(ix, st));
+    AP_TRY(ap_bound_ingest(ix, bounds_share, st));
     AP_CHECK_HIP(hipMemcpyAsync(ix->w_dev, ix->w_default, 3 * sizeof(float), hipMemcpyHostToDevice, st));
     AP_CHECK_HIP(hipStreamSynchronize(st));
     // set-up of this device for searches that must not allocate: the address of their static workspace
@@ -315,7 +315,7 @@ static int new_index(const ap_corpus *corpus, const ap_build_params *params, ap_
 
 extern "C" int ap_ingest(const ap_corpus *corpus, const ap_build_params *params, void *stream, ap_index **out) {
     AP_TRY(new_index(corpus, params, out));
-    int rc = ap_ingest_impl(*out, true, (hipStream_t)stream);
+    int rc = ap_ingest_impl(*out, 4, (hipStream_t)stream);
     if (rc != AP_OK) { ap_free_index(*out); *out = nullptr; }
     return rc;
 }
@@ -399,7 +399,7 @@ extern "C" int ap_import_graph(const ap_corpus *corpus, const ap_build_params *p
     AP_TRY(new_index(corpus, params, out));
     ap_index *ix = *out;
     hipStream_t st = (hipStream_t)stream;
-    int rc = ap_ingest_impl(ix, true, st);
+    int rc = ap_ingest_impl(ix, 4, st);
     if (rc == AP_OK) rc = ap_alloc_graph(ix);
     if (rc != AP_OK) { ap_free_index(ix); *out = nullptr; return rc; }
     const size_t n = (size_t)corpus->n, R = (size_t)params->degree;

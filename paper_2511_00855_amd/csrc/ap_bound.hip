@@ -156,9 +156,9 @@ __global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const in
 
 static inline size_t ap_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Lays out what the bounds of a corpus need.  Without it (vocabularies too large for a table of columns, not enough
-// memory) the searches run without bounds: never an error.
-int ap_bound_ingest(ap_index *ix, hipStream_t st) {
+// Lays out what the bounds of a corpus need, if that is at most 1/share of the free memory.  Without it (vocabularies too
+// large for a table of columns, not enough memory) the searches run without bounds: never an error.
+int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     const ap_corpus &c = ix->corpus;
     const int64_t all = (int64_t)c.sp_vocab + c.tx_vocab;
     if (all > AP_BOUND_VOCAB) return AP_OK;
@@ -173,10 +173,8 @@ int ap_bound_ingest(ap_index *ix, hipStream_t st) {
     auto take = [&](size_t bytes) { const size_t a = at; at += ap_up(bytes, 256); return a; };
     const size_t o_clear = take(n_clear * 4), o_col = take((size_t)all * 4), o_run = take((size_t)all * 8), o_post = take((nnz + 1) * 8),
                  o_norms = take((size_t)c.n * 24), o_rows = take((size_t)c.n * (size_t)(kd + kh) * 2);
-    if (at > ((size_t)64 << 20)) {
-        size_t free_b = 0, total_b = 0;
-        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || at > free_b / 4) { (void)hipGetLastError(); return AP_OK; }
-    }
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || at > free_b / (size_t)share) { (void)hipGetLastError(); return AP_OK; }
     if (!ix->bd_pool && !(ix->bd_pool = new (std::nothrow) ApBoundPool())) { ap_set_error("out of host memory"); return AP_ENOMEM; }
     if (hipMalloc(&ix->bd_mem, at) != hipSuccess) { (void)hipGetLastError(); ix->bd_mem = nullptr; return AP_OK; }
     char *m = static_cast<char *>(ix->bd_mem);

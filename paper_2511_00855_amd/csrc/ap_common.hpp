@@ -170,7 +170,7 @@ struct ApStageEvents {
 
 int ap_validate_corpus(const ap_corpus *c);
 int ap_validate_params(const ap_build_params *p);
-int ap_ingest_impl(ap_index *ix, bool bounds, hipStream_t st);
+int ap_ingest_impl(ap_index *ix, int bounds_share, hipStream_t st);
 int ap_count_terms(const int32_t *idx, const float *tf, int64_t nnz, int32_t *df, unsigned long long *total, hipStream_t st);
 int ap_alloc_graph(ap_index *ix);
 int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
@@ -222,7 +222,7 @@ struct ApSearchWs {
 #define AP_BOUND_WS_BYTES ((size_t)16 << 30)
 #define AP_BOUND_KEEP_BYTES ((size_t)2 << 30)   // an exact top-k that had to take more gives it back
 #define AP_BOUND_COUNT 31u     // low bits of a table entry: keyword searches count the required tail terms a document holds there
-int ap_bound_ingest(ap_index *ix, hipStream_t st);
+int ap_bound_ingest(ap_index *ix, int share, hipStream_t st);
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq);
 void ap_bound_release(ap_index *ix);
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b);

@@ -88,7 +88,7 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, const ap
     InsertBufs B;
     AP_CHECK_HIP(mark(0));
     // step 0: S0 over the enlarged corpus
-    AP_TRY(ap_ingest_impl(nx, true, st));
+    AP_TRY(ap_ingest_impl(nx, 4, st));
     AP_TRY(ap_alloc_graph(nx));
     AP_CHECK_HIP(mark(1));
 
