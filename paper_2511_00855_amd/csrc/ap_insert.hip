@@ -76,7 +76,7 @@ unsigned grid_for(size_t n) { return (unsigned)std::min<size_t>((n + 255) / 256,
 #define AP_COPY(dst, src, count, T) AP_CHECK_HIP(hipMemcpyAsync((dst), (src), (size_t)(count) * sizeof(T), hipMemcpyDeviceToDevice, st))
 }  // namespace
 
-static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, const ap_insert_trace *tr, hipStream_t st) {
+static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int bounds_share, const ap_insert_trace *tr, hipStream_t st) {
     const ap_build_params &p = nx->params;
     const int64_t n0 = old->corpus.n, n1 = nx->corpus.n, m = n1 - n0;
     const int32_t K = p.knn_k, R = p.degree, P = p.sp_len, KR = R / 2;
@@ -88,7 +88,7 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, const ap
     InsertBufs B;
     AP_CHECK_HIP(mark(0));
     // step 0: S0 over the enlarged corpus
-    AP_TRY(ap_ingest_impl(nx, 4, st));
+    AP_TRY(ap_ingest_impl(nx, bounds_share, st));
     AP_TRY(ap_alloc_graph(nx));
     AP_CHECK_HIP(mark(1));
 
@@ -117,6 +117,8 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, const ap
         const ApVecs Q{m, nx->docs.dim, qd, nx->docs.sp_indptr + n0, nx->docs.sp_idx, nx->docs.sp_val,
                        nx->docs.tx_indptr + n0, nx->docs.tx_idx, nx->docs.tx_val};
         AP_TRY(ap_search_core(nx, Q, w_dev, 0, K, L, 0, 1, true, c1_ids, c1_sc, st));   // runs in slabs of queries by itself
+        AP_CHECK_HIP(hipStreamSynchronize(st));
+        ap_bound_give_back(nx, st);   // a batch of this size does not come again, and the steps below want the memory
     }
     nx->has_graph = false;
 
@@ -228,7 +230,6 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, const ap
         AP_COPY(nx->deleted, old->deleted, w0, uint32_t);
     }
     AP_CHECK_HIP(hipStreamSynchronize(st));
-    ap_bound_give_back(nx, st);   // the search of step 1 had a batch of its own size
     float total = 0.f;
     for (int i = 0; i < 5; i++) {
         float ms = 0.f;
@@ -259,14 +260,28 @@ extern "C" int ap_insert_documents(const ap_index *old, const ap_corpus *enlarge
                enlarged->sp_vocab == old->corpus.sp_vocab && enlarged->tx_vocab == old->corpus.tx_vocab,
                "the enlarged corpus must keep dimension, dense type and vocabularies");
     AP_REQUIRE(beam >= 0 && beam <= AP_MAX_BEAM, "beam = %d must be in [0, %d] (0 = twice the list length)", beam, AP_MAX_BEAM);
-    ap_index *nx = new (std::nothrow) ap_index();
-    if (!nx) { ap_set_error("out of host memory"); return AP_ENOMEM; }
-    nx->corpus = *enlarged;
-    nx->params = old->params;
-    nx->dtype = enlarged->dense_dtype;
-    memcpy(nx->w_default, old->w_default, sizeof(nx->w_default));
-    const int rc = insert_impl(old, nx, beam, trace, (hipStream_t)stream);
-    (void)hipStreamSynchronize((hipStream_t)stream);
+    hipStream_t st = (hipStream_t)stream;
+    ap_index *nx = nullptr;
+    int rc = AP_OK;
+    // The columns of the bounds are there for the search of step 1.  Should the memory then not do for the rest, once more
+    // without them (they come at the end then, if there is room).
+    for (const int share : {4, INT32_MAX}) {
+        nx = new (std::nothrow) ap_index();
+        if (!nx) { ap_set_error("out of host memory"); return AP_ENOMEM; }
+        nx->corpus = *enlarged;
+        nx->params = old->params;
+        nx->dtype = enlarged->dense_dtype;
+        memcpy(nx->w_default, old->w_default, sizeof(nx->w_default));
+        rc = insert_impl(old, nx, beam, share, trace, st);
+        (void)hipStreamSynchronize(st);
+        if (rc != AP_ENOMEM || !nx->bd_mem) break;
+        ap_free_index(nx);
+        (void)hipGetLastError();
+    }
+    if (rc == AP_OK && !nx->bd_mem) {
+        rc = ap_bound_ingest(nx, 4, st);
+        (void)hipStreamSynchronize(st);
+    }
     if (rc != AP_OK) { nx->has_graph = false; ap_free_index(nx); return rc; }
     *out = nx;
     return AP_OK;

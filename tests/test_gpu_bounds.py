@@ -372,6 +372,17 @@ def _one_term(rng, n, dim):
                   np.ones(n, np.float32), 50, 50)
 
 
+def _many_terms(n, dim, terms=60):
+    """As _one_term, with lists of 60 of 400 terms."""
+    rng = np.random.default_rng(2)
+    d = _one_term(rng, n, dim)
+    d.sp_indptr = d.tx_indptr = np.arange(0, n * terms + 1, terms, dtype=np.int64)
+    d.sp_idx = d.tx_idx = np.tile(np.arange(terms, dtype=np.int32), n) + np.repeat(rng.integers(0, 340, n).astype(np.int32), terms)
+    d.sp_val = d.tx_val = np.ones(n * terms, np.float32)
+    d.sp_vocab = d.tx_vocab = 400
+    return d
+
+
 def _leave_free(want):
     """Tensors that leave about `want` bytes of the device's memory free."""
     torch.cuda.synchronize()
@@ -444,13 +455,7 @@ def test_a_construction_has_the_memory_that_its_bounds_take_afterwards(debug_kno
     """The seed sweep multiplies half of D D^T where its buffers (80 MB here) fit 62 % of the free memory, and all of it where
     they do not.  With some 190 MB free at that
     point they fit, unless the columns of the bounds (80 MB) are there before."""
-    n, dim, terms = 20_000, 1024, 60
-    rng = np.random.default_rng(2)
-    d = _one_term(rng, n, dim)
-    d.sp_indptr = d.tx_indptr = np.arange(0, n * terms + 1, terms, dtype=np.int64)
-    d.sp_idx = d.tx_idx = np.tile(np.arange(terms, dtype=np.int32), n) + np.repeat(rng.integers(0, 340, n).astype(np.int32), terms)
-    d.sp_val = d.tx_val = np.ones(n * terms, np.float32)
-    d.sp_vocab = d.tx_vocab = 400
+    d = _many_terms(20_000, 1024)
     docs, bp = B.DeviceVecs(d), B.build_params(16, knn_k=32, nd_rounds=0, n_entry=16)
     debug_knobs("seed_sample_cols", 2048)
     flops = {}
@@ -468,6 +473,25 @@ def test_a_construction_has_the_memory_that_its_bounds_take_afterwards(debug_kno
     torch.cuda.empty_cache()
     assert all(torch.equal(a, b) for a, b in zip(graph, ix.export_graph()))
     ix.close()
+
+
+def test_an_insertion_has_the_memory_that_its_bounds_take():
+    """With 380 MB free the columns of the bounds (80 MB) are less than a quarter of it, and what is left does not hold the pair
+    similarities (260 MB) beside the lists."""
+    d = _many_terms(20_000, 1024)
+    docs = B.DeviceVecs(d)
+    old = B.Index.build(B.DeviceVecs(subset_vecset(d, np.arange(19_000))), B.build_params(16, knn_k=256, nd_rounds=0, n_entry=16))
+    new = old.insert(docs)
+    graph = [t.clone() for t in new.export_graph()]
+    new.close()
+    hold = _leave_free(380 << 20)
+    new = old.insert(docs)
+    got = [t.clone() for t in new.export_graph()]
+    new.close()
+    del hold
+    torch.cuda.empty_cache()
+    assert all(torch.equal(a, b) for a, b in zip(graph, got))
+    old.close()
 
 
 def test_workspaces_of_single_calls_are_given_back(debug_knobs):
