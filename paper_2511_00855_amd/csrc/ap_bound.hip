@@ -295,7 +295,7 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
 }
 
 // The product and the slack: a tile of 256 queries x 256 documents, 16 waves of 64 x 64, chunks of 64 columns through two
-// LDS stages as in the seed sweep.  4,000 queries x 100,000 documents x 1,280 columns take 1.24 ms = 0.83 PFLOP/s; the
+// LDS stages as in the seed sweep.  10,000 queries x 100,000 documents x 1,280 columns take 3.22 ms = 0.82 PFLOP/s; the
 // matrix cores and the LDS reads that feed them bound it, as they bound the sweep.  The documents' columns come from two places: the dense part (dense, dense_ld) and
 // the head (rows + head_at, rows_ld).
 // Tile order: an XCD takes the document tiles in groups of four and walks each group's query tiles, so that a group's
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
 // One block per query: the tail terms' postings, one term after the other (a document occurs once in a term's postings,
 // so the additions need no atomics and always come in the same order); then, for keyword searches, the count of required
 // tail terms every document holds, in the entries' low bits (the head's are asked of the bitmaps).  Bound by the
-// scattered read-modify-writes: 1.4 ms for 4,000 queries of 100,000 documents (about one entry in twenty is touched).
+// scattered read-modify-writes: 3.35 ms for 10,000 queries of 100,000 documents (about one entry in twenty is touched).
 __global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int32_t nsp, int32_t ntx,
                                                     const int32_t *__restrict__ col, const uint2 *__restrict__ run, const uint2 *__restrict__ post,
                                                     const float *__restrict__ qc, const int32_t *__restrict__ kw_terms, int32_t kw_stride,

@@ -1262,8 +1262,8 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
 //  - a wave writes its 8 rows of a chunk (cleared, then the entries whose column falls into it), into one of two stages,
 //    while the other stage is multiplied: one barrier a chunk.
 // The lower triangle of the result is 36 blocks of 16 x 16 (K = 128): two a wave and four more on the first four waves, nine
-// on every SIMD.  200,003 bf16 documents: 298 ms with the walks, 105 ms here; 100,000 f32: 160 and 57 ms.  The MFMAs alone need
-// a third of that (their busy counter); the rest is the rows' writing, which shares the issue slots, and the waves' barriers.
+// on every SIMD.  200,000 bf16 documents: 299 ms with the walks, 109 ms here; 100,000 f32: 160 and 66 ms.  The MFMAs alone need
+// two fifths of that (their busy counter); the rest is the rows' writing, which shares the issue slots, and the waves' barriers.
 #define AP_GL_WORDS 8192          // words of a bitmap: vocabularies up to 2^18 terms
 #define AP_GL_C 64                // columns of a chunk
 #define AP_GL_STRIDE (AP_GL_C + 4)   // rows 16-byte aligned; 16 rows x 4 groups of 4 columns fall into distinct banks
