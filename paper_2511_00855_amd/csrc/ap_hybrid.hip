@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void k_bf_scores(ApVecs Q, ApVecs D, const int
                                                    const float *__restrict__ w, int32_t w_stride,
                                                    float *__restrict__ scores /* nqb x n */) {
     constexpr int EPC = ApDense<DT>::EPC;
-    extern __shared__ float smem[];
+    extern __shared__ __attribute__((aligned(16))) float smem[];
     float *qd = smem;                                                // QB x dim
     int32_t *qsi = reinterpret_cast<int32_t *>(qd + AP_BF_QB * Q.dim);  // QB x QCAP
     float *qsv = reinterpret_cast<float *>(qsi + AP_BF_QB * AP_BF_QCAP);
@@ -130,9 +130,13 @@ __global__ __launch_bounds__(256) void k_bf_scores(ApVecs Q, ApVecs D, const int
     __shared__ float wq[AP_BF_QB][3];
     const int32_t qb = q0 + blockIdx.y * AP_BF_QB;
     const int32_t nq_here = (q0 + nqb - qb) < AP_BF_QB ? (q0 + nqb - qb) : AP_BF_QB;
+    for (int x = ap_wave_id(); x < nq_here; x += 4) {   // a wave a row; dim is a multiple of 4
+        const int64_t q = list ? list[qb + x] : qb + x;
+        for (int i = (threadIdx.x & 63) * 4; i < Q.dim; i += 256)
+            *reinterpret_cast<float4 *>(qd + x * Q.dim + i) = *reinterpret_cast<const float4 *>(static_cast<const float *>(Q.dense) + q * Q.dim + i);
+    }
     for (int x = 0; x < nq_here; x++) {
         const int64_t q = list ? list[qb + x] : qb + x;   // uniform
-        for (int i = threadIdx.x; i < Q.dim; i += blockDim.x) qd[x * Q.dim + i] = static_cast<const float *>(Q.dense)[q * Q.dim + i];
         const ApLists a = ap_stage_lists(Q, q, qsi + x * AP_BF_QCAP, qsv + x * AP_BF_QCAP, qti + x * AP_BF_QCAP,
                                          qtv + x * AP_BF_QCAP, AP_BF_QCAP);
         if (threadIdx.x == 0) {
