@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ score
 // result reaches at least, so only documents whose bound is not below T have to be scored (some fifty for k = 10 on
 // 100,000 documents).  Two passes over the row, bound by reading it.  A query with more than AP_BT_CAND of them is left to
 // the exhaustive scorer.  1,000 queries of 100,000 documents (768 f32 columns), k = 10: 74.9 ms with the exhaustive scorer,
-// 0.93 ms with the table, which takes 0.71 ms of it.
+// 0.97 ms with the table, which takes 0.71 ms of it.
 #define AP_BT_CAND 4096
 template <int DT, int NV>
 __global__ __launch_bounds__(1024) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
