@@ -363,6 +363,8 @@ int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
  *   "max_launch_threads"      a multiple of 1024: launches that grow with the corpus run in slices of this many threads
  *   "search_workspace_bytes"  cap of the searches' visited-set workspace (forces searches in several slabs of queries)
  *   "search_bounds"           1: searches score every neighbour they meet, 2: they always sort neighbours out by the bounds
+ *   "search_walk"             1: small batches are searched as any other, 2: by the walk out of the bounds, 3: by the walk with
+ *                             every document scored ahead (both where the call can: no keywords, no capture)
  *   "search_bounds_bytes"     cap of the workspace that holds them (forces slabs of queries, each with a table of its own)
  *   "search_floor"            1: no neighbour waits below the estimated end of the pool, 2: the estimate is far too high
  *   "search_visited_global"   1: visited sets stay in the global workspace even where the search would keep them in LDS

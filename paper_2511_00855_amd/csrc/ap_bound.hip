@@ -487,20 +487,21 @@ int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t be
     return AP_OK;
 }
 
-// Bytes of the workspace a slab of nq queries takes.
-size_t ap_bound_bytes(const ap_index *ix, int64_t nq) {
+// Bytes of the workspace a slab of nq queries takes, with one table of n entries a query or two.
+size_t ap_bound_bytes(const ap_index *ix, int64_t nq, int tables) {
     const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
-    return rows * k * 2 + rows * 32 + rows * 4 + (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
+    return rows * k * 2 + rows * 32 + rows * 20 + (size_t)tables * (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
 }
 
-void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b) {
+void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBound *b) {
     const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
     char *m = static_cast<char *>(base);
     b->qm = reinterpret_cast<uint16_t *>(m); m += rows * k * 2;
     b->qc = reinterpret_cast<float *>(m); m += rows * 32;
-    b->floor = reinterpret_cast<float *>(m); m += rows * 4;
+    b->floor = reinterpret_cast<float *>(m); m += rows * 20;
     b->table = reinterpret_cast<float *>(m);
     b->ld = (int64_t)ap_up((size_t)ix->docs.n, 64);
+    b->second = tables > 1 ? b->table + (size_t)nq * (size_t)b->ld : nullptr;
     b->slab = (int32_t)nq;
 }
 
@@ -515,11 +516,11 @@ void ap_bound_release(ap_index *ix) {
 }
 
 // Queries per slab when a slab may take `cap` bytes (0: not even one).
-static int64_t bound_slab(const ap_index *ix, int64_t nq, size_t cap) {
+static int64_t bound_slab(const ap_index *ix, int64_t nq, size_t cap, int tables) {
     int64_t slabs = 1;
-    while (slabs < nq && ap_bound_bytes(ix, (nq + slabs - 1) / slabs) > cap) slabs++;
+    while (slabs < nq && ap_bound_bytes(ix, (nq + slabs - 1) / slabs, tables) > cap) slabs++;
     const int64_t slab = (nq + slabs - 1) / slabs;
-    return ap_bound_bytes(ix, slab) <= cap ? slab : 0;
+    return ap_bound_bytes(ix, slab, tables) <= cap ? slab : 0;
 }
 
 // Sizes the workspace of stream st for slabs of as many of nq queries as `cap` bytes hold, and holds it for the caller
@@ -527,13 +528,13 @@ static int64_t bound_slab(const ap_index *ix, int64_t nq, size_t cap) {
 // smaller slabs then, but of `least` queries at least (fewer than a launch keeps in flight cost more than the bounds save).
 // b->table stays NULL where no such workspace is to be had: the caller goes without bounds.  That is also what a captured
 // search does: a graph's replays must not depend on a workspace that a later call may replace.
-int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, hipStream_t st, ApBound *b) {
+int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, int tables, hipStream_t st, ApBound *b) {
     if (!ix->bd_mem || nq < 1 || st == hipStreamPerThread) return AP_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
     if (cs != hipStreamCaptureStatusNone) return AP_OK;
     if (g_ap_debug.search_bounds_bytes > 0) cap = std::min(cap, (size_t)g_ap_debug.search_bounds_bytes);
-    int64_t slab = bound_slab(ix, nq, cap);
+    int64_t slab = bound_slab(ix, nq, cap, tables);
     if (slab == 0) return AP_OK;
     least = std::min(least, slab);
     ApBoundPool *pool = ix->bd_pool;
@@ -557,13 +558,13 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, 
     }
     auto &w = pool->ws[i];
     w.last = ++pool->uses;
-    if (ap_bound_bytes(ix, slab) > w.bytes) {
+    if (ap_bound_bytes(ix, slab, tables) > w.bytes) {
         size_t free_b = 0, total_b = 0;
         if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) { (void)hipGetLastError(); free_b = 0; }
-        slab = bound_slab(ix, nq, std::min(cap, std::max(w.bytes, (free_b + w.bytes) / 4)));
+        slab = bound_slab(ix, nq, std::min(cap, std::max(w.bytes, (free_b + w.bytes) / 4)), tables);
     }
     if (slab < least) return AP_OK;
-    if (const size_t need = ap_bound_bytes(ix, slab); need > w.bytes) {
+    if (const size_t need = ap_bound_bytes(ix, slab, tables); need > w.bytes) {
         void *mem = nullptr;
         if (hipMalloc(&mem, need) == hipSuccess) {
             const hipError_t e = w.mem ? hipStreamSynchronize(st) : hipSuccess;
@@ -573,11 +574,11 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, 
             AP_CHECK_HIP(e);
         } else {   // what is there goes on serving
             (void)hipGetLastError();
-            slab = bound_slab(ix, nq, std::min(cap, w.bytes));
+            slab = bound_slab(ix, nq, std::min(cap, w.bytes), tables);
             if (slab < least) return AP_OK;
         }
     }
-    ap_bound_place(ix, w.mem, slab, b);
+    ap_bound_place(ix, w.mem, slab, tables, b);
     b->hold = std::move(hold);
     b->stream = st;
     b->done = w.done;
@@ -635,7 +636,7 @@ extern "C" int ap_stage_score_bounds(ap_index *ix, const ap_queries *q, const fl
     hipStream_t st = (hipStream_t)stream;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApBound b;
-    AP_TRY(ap_bound_reserve(ix, q->nq, q->nq, AP_BOUND_WS_BYTES, st, &b));
+    AP_TRY(ap_bound_reserve(ix, q->nq, q->nq, AP_BOUND_WS_BYTES, 1, st, &b));
     if (!b.table || b.slab != q->nq) { ap_set_error("no bounds for this index and batch"); return AP_ESTATE; }
     AP_TRY(ap_bound_fill(ix, b, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, 0, q->nq, kw_terms, kw_stride, st));
     AP_CHECK_HIP(hipMemcpy2DAsync(out, (size_t)ix->docs.n * 4, b.table, (size_t)b.ld * 4, (size_t)ix->docs.n * 4, (size_t)q->nq, hipMemcpyDeviceToDevice, st));

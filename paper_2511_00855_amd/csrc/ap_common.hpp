@@ -139,6 +139,7 @@ struct ApDebug {
     int64_t search_query_lists = 0;      // 1: the searches look the query's terms up in its lists (the path of queries too long for the LDS tables)
     int64_t search_bounds = 0;           // 1: searches without the table of upper bounds, 2: with it whatever it costs
     int64_t search_floor = 0;            // 1: no neighbour waits below a floor, 2: the floor is far too high (forces the scan of what waits)
+    int64_t search_walk = 0;             // 1: small batches are searched as any other, 2: by the walk out of the bounds, 3: by the walk with every document scored ahead
     int64_t search_bounds_bytes = 0;     // cap of a stream's table of bounds (forces slabs of queries that each get a table)
     int64_t search_workspace_bytes = 0;  // cap of the search's visited-set workspace (forces searches in several slabs of queries)
 };
@@ -192,6 +193,7 @@ struct ApBound {
     uint16_t *qm = nullptr;    // the slab's queries as bf16 rows
     float *qc = nullptr;       // per query 8 floats: what the slack of its row is made of
     float *floor = nullptr;    // per query: an estimate of the last score of a pool (ap_bound_floors)
+    float *second = nullptr;   // a second table of the same shape, where the call asked for one
     int32_t slab = 0;          // queries the workspace holds
     // The index's workspaces are held until everything that uses this one is enqueued: finish() (or the end of the object)
     // marks that place on the stream and lets go.
@@ -211,21 +213,32 @@ struct ApBound {
 };
 // The visited-set workspace of a search call: `slab` queries are in flight at a time, each with a bitset of one bit
 // per document.  `counts` (nq x 3) and the two events belong to the index's measurement surface and may be absent.
+// How a small batch is searched (ap_walk.hip): 0 = as any other, 1 = documents whose bounds reach the quantile `share` are scored
+// ahead, 2 = all documents are.
+struct ApWalkPlan { int mode = 0; float share[4] = {1.f, 1.f, 1.f, 1.f}; };
+struct ApWalk {
+    float *bound = nullptr;    // per query a row of ld bounds; NULL: all documents are scored ahead
+    float *exact = nullptr;    // per query a row of ld scores
+    float *line = nullptr;     // per query four floats, then a word per query
+    int64_t ld = 0;
+    float share[4] = {1.f, 1.f, 1.f, 1.f};
+};
 struct ApSearchWs {
     uint32_t *visited = nullptr;
     int32_t slab = 0;
     int32_t *counts = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     ApBound bound;
+    ApWalk walk;               // exact != NULL: the batch is searched by ap_walk_launch
 };
 // the workspace of one stream never grows beyond this (40,000 queries of 100,000 documents, 480 of 8.8 million)
 #define AP_BOUND_WS_BYTES ((size_t)16 << 30)
 #define AP_BOUND_KEEP_BYTES ((size_t)2 << 30)   // an exact top-k that had to take more gives it back
 #define AP_BOUND_COUNT 31u     // low bits of a table entry: keyword searches count the required tail terms a document holds there
 int ap_bound_ingest(ap_index *ix, int share, hipStream_t st);
-size_t ap_bound_bytes(const ap_index *ix, int64_t nq);
+size_t ap_bound_bytes(const ap_index *ix, int64_t nq, int tables);
 void ap_bound_release(ap_index *ix);
-void ap_bound_place(const ap_index *ix, void *base, int64_t nq, ApBound *b);
+void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBound *b);
 size_t ap_bound_held(const ap_index *ix, hipStream_t st);
 void ap_bound_give_back(const ap_index *ix, hipStream_t st);
 // An allocation that a call on stream st cannot do without: where it fails, the stream's workspace of bounds makes room.
@@ -237,12 +250,18 @@ static inline int ap_bound_make_room(const ap_index *ix, hipStream_t st, T **p, 
     ap_bound_give_back(ix, st);
     return ap_dev_alloc(p, count);
 }
-int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, hipStream_t st, ApBound *b);
+int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, int tables, hipStream_t st, ApBound *b);
 int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
                   const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);
 int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st);
 // sizes the workspace an index owns (grow only, capped) for a call of nq queries (ap_search.hip)
-int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds);
+int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan = ApWalkPlan());
+// the search of a small batch (ap_walk.hip): whether and how
+// (can_bound: the call can take a workspace for bounds), and the launch
+ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters, bool bounds, bool can_bound);
+int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, const ApVecs &Q, const float *w, int32_t w_stride, int32_t k, int32_t beam,
+                   int32_t width, int32_t *counts, int32_t *out_ids, float *out_scores, hipStream_t st);
+double ap_bound_cost(const ap_index *ix, int64_t nq);
 bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters);
 // address, on the current device, of the static workspace of ap_search_batch_noalloc (looked up once per device)
 int ap_static_scratch(void **out);

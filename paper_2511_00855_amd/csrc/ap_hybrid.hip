@@ -336,7 +336,7 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     // threshold comes from, and a corpus well above them (below, the exhaustive scorer has little to do).
     ApBound b;
     const size_t held = ap_bound_held(ix, st);
-    if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, 256, AP_BOUND_WS_BYTES, st, &b));
+    if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, 256, AP_BOUND_WS_BYTES, 1, st, &b));
     if (!b.table) return bf_exhaustive(ix, Q, w, ws, nullptr, q->nq, k, out_ids, out_scores, st);
     int32_t *over = nullptr;
     AP_TRY(ap_dev_alloc(&over, (size_t)q->nq + 1));

@@ -15,33 +15,9 @@
 #include <stdlib.h>
 #include <algorithm>
 #include <mutex>
-#include "ap_common.hpp"
-
+#include "ap_score.hpp"
 
 int ap_validate_queries(const ap_queries *q);
-
-// The visited set of a query: one bit per document, in LDS when the corpus is small enough for that not to cost a
-// workgroup its place on the CU (ap_search_launch decides), else in a per-call global workspace.  Marks document v and
-// tells whether it had been marked before.  Only the workgroup that searches the query ever touches its set, so the
-// global atomic needs workgroup scope only.
-#ifndef AP_VIS_SCOPE
-#define AP_VIS_SCOPE __HIP_MEMORY_SCOPE_WORKGROUP
-#endif
-struct ApVisited {
-    uint32_t *g;             // global bitset of this query
-    AP_LDS uint32_t *l;      // LDS bitset, or null
-    __device__ __forceinline__ bool test_and_set(int32_t v) const {
-        const uint32_t bit = 1u << (v & 31);
-        uint32_t old;
-        if (l) old = __hip_atomic_fetch_or(l + (v >> 5), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // uniform branch
-        else old = __hip_atomic_fetch_or(g + (v >> 5), bit, __ATOMIC_RELAXED, AP_VIS_SCOPE);
-        return (old & bit) != 0u;
-    }
-    __device__ __forceinline__ bool test(int32_t v) const {
-        const uint32_t w = l ? l[v >> 5] : __hip_atomic_load(g + (v >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return ((w >> (v & 31)) & 1u) != 0u;
-    }
-};
 
 struct ApSearchArgs {
     ApVecs D, Q;
@@ -75,19 +51,6 @@ struct ApSearchArgs {
     int32_t KR, kw_stride, kw_all, kw_use_edges;
 };
 
-// Pool keys.  Plain search: ap_make_key (30-bit id, bit 0 = "not yet expanded").
-// Keyword search: 29-bit id, bit 0 as before, bit 1 = "satisfies the keyword
-// constraint".  Ids are unique within a pool, so the flag bits never decide an order.
-#define AP_KW_MAX_TERMS 16
-template <bool KW> __device__ __forceinline__ uint64_t ap_pool_key(float s, int32_t id, uint32_t flags) {
-    if (KW) return ((uint64_t)ap_f2ord(s) << 32) | (uint64_t)(((0x1fffffffu - (uint32_t)id) << 2) | flags);
-    return ap_make_key(s, id, flags);
-}
-template <bool KW> __device__ __forceinline__ int32_t ap_pool_id(uint64_t k) {
-    if (KW) return (int32_t)(0x1fffffffu - (((uint32_t)k) >> 2));
-    return ap_key_id(k);
-}
-
 // Number of entries of the descending array keys[0..n) that rank before `key`.
 __device__ __forceinline__ int32_t ap_rank_in(const uint64_t *keys, int32_t n, uint64_t key) {
     int32_t lo = 0, hi = n;
@@ -96,115 +59,6 @@ __device__ __forceinline__ int32_t ap_rank_in(const uint64_t *keys, int32_t n, u
         if (keys[mid] > key) lo = mid + 1; else hi = mid;
     }
     return lo;
-}
-
-// Scores the c candidates of this iteration; wave w of the workgroup's NW takes candidates w, w+NW, ...
-// The sparse and lexical parts (the short segments) are evaluated first.  When
-// the pool is full and even the largest dense part the norms allow,
-// |w_d| |q_d| |d_d|, could not lift the candidate past the pool's last entry,
-// the dense row is not read at all: the candidate could not have entered the
-// pool, so the result of the search is unchanged (it still counts as visited).
-// TAB: the query's lists are look-up tables in LDS (the usual case); otherwise
-// they are searched where they lie in global memory.
-// Returns the number of candidates whose dense row was skipped (wave-uniform).
-// Sizes of the query's two look-up tables (at most a quarter full).  Ordinary queries: 256 + 128 slots (lists up to
-// 64 / 32 entries).  Queries that are documents (insertion): 1024 + 512 slots (lists up to 256 / 128 entries).  Both are
-// bucketed: two slots a bucket, a hash multiplier per table under which no bucket needs a third.
-template <bool BIG> struct ApQTab {
-    static constexpr int SPB = BIG ? 10 : 8;
-    static constexpr int TXB = BIG ? 9 : 7;
-    static constexpr int SLOTS = (1 << SPB) + (1 << TXB);
-};
-
-// KW: each candidate's lexical terms are also compared with the query's required
-// terms (s_kw[0..n_kw)); the key of a candidate that satisfies the constraint
-// carries the "satisfies" flag, and its dense row may only be skipped when the
-// bound also rules out the secondary pool (full, and its last score above the bound).
-// G: candidates a wave keeps on their way at once.  Their records are loaded together, then reduced one by one;
-// then the dense rows of those that still need one are loaded together and multiplied one by one.  G = 1 is the
-// plain order (record, sums, dense row); larger G trades registers for memory requests in flight, which pays where
-// a large pool leaves a CU with few waves.  pre: the candidates' dense rows are requested along with their records (they
-// got past their bounds, so nearly all of them need theirs).  The order of the additions inside a candidate does not depend on G.
-template <int DT, int NV, bool TAB, bool KW, bool BIG, int NW, int G>
-__device__ __forceinline__ int32_t ap_score_candidates(const ApVecs &D, const uint2 *rec, const float *qa, const uint64_t *qtab,
-                                                       const ApLists &a, float wd, float ws, float wf, float qnorm, bool pool_full,
-                                                       float worst_score, const uint4 *s_meta, int32_t c,
-                                                       uint64_t *newk, const int32_t *s_kw, int32_t n_kw, bool kw_all,
-                                                       bool second_full, float second_worst, uint32_t msp, uint32_t mtx, bool pre) {
-    const int lane = threadIdx.x & 63, wave = ap_wave_id();
-    int32_t skipped = 0;
-    for (int32_t i0 = wave; i0 < c; i0 += NW * G) {
-        uint2 xs[G][2], xt[G][1];
-        uint4 raw[G][NV];
-        const uint2 *r[G];
-        int32_t spn[G], txn[G], v[G];
-        float dn[G];
-#pragma unroll
-        for (int gi = 0; gi < G; gi++) {
-            const int32_t i = i0 + NW * gi;
-            if (i < c) {
-                const uint4 m = s_meta[i];
-                // the descriptor is the same in every lane: keep the record's address in scalar registers
-                r[gi] = rec + ap_uniform_u32(m.x);
-                spn[gi] = __builtin_amdgcn_readfirstlane((int32_t)(m.y & 0xffffu));
-                txn[gi] = __builtin_amdgcn_readfirstlane((int32_t)(m.y >> 16));
-                dn[gi] = __uint_as_float(ap_uniform_u32(m.z));
-                v[gi] = (int32_t)ap_uniform_u32(m.w);
-                ap_rec_load_raw<2, 1>(r[gi], spn[gi], txn[gi], xs[gi], xt[gi]);
-                if (pre) ap_dense_load_raw<DT, NV>(D, v[gi], raw[gi]);
-            }
-        }
-        float ss[G], sf[G];
-        uint32_t flags[G];
-        bool need[G];      // uniform: the candidate's dense row has to be read
-#pragma unroll
-        for (int gi = 0; gi < G; gi++) {
-            const int32_t i = i0 + NW * gi;
-            need[gi] = false;
-            if (i >= c) continue;
-            int32_t si[2], ti[1];
-            float sv[2], tv[1];
-            ap_rec_decode<2, 1>(xs[gi], xt[gi], spn[gi], txn[gi], si, sv, ti, tv);
-            if (TAB)   // bucketed tables, one read per look-up
-                ap_rec_reduce_bucket<2, 1, ApQTab<BIG>::SPB, ApQTab<BIG>::TXB>(r[gi], (const AP_LDS uint64_t *)qtab,
-                                                                               (const AP_LDS uint64_t *)(qtab + (1 << ApQTab<BIG>::SPB)),
-                                                                               msp, mtx, spn[gi], txn[gi], si, sv, ti, tv, ss[gi], sf[gi]);
-            else
-                ap_rec_reduce_lists<2, 1>(r[gi], a, spn[gi], txn[gi], si, sv, ti, tv, ss[gi], sf[gi]);
-            // upper bound of the fused score, with slack far above fp32 rounding
-            const float dmax = fabsf(wd) * qnorm * dn[gi] * 1.0001f;
-            const float part = fmaf(wf, sf[gi], ws * ss[gi]);
-            const float ub = part + dmax + 1e-5f * (fabsf(ws * ss[gi]) + fabsf(wf * sf[gi]) + dmax);
-            flags[gi] = 1u;
-            if (KW && n_kw > 0) {
-                uint32_t hit = 0;   // bit j: required term j occurs in the candidate's text
-                for (int32_t e0 = 0; e0 < txn[gi]; e0 += 64) {
-                    int32_t term = ti[0];
-                    if (e0 > 0) term = e0 + lane < txn[gi] ? (int32_t)r[gi][spn[gi] + e0 + lane].x : -1;
-                    for (int32_t j = 0; j < n_kw; j++) hit |= __ballot(term == s_kw[j]) != 0ull ? 1u << j : 0u;
-                }
-                const bool sat = kw_all ? hit == (1u << n_kw) - 1u : hit != 0u;
-                flags[gi] |= sat ? 2u : 0u;
-            }
-            if (pool_full && ub < worst_score && (!(flags[gi] & 2u) || (second_full && ub < second_worst))) {
-                if (lane == 0) newk[i] = (uint64_t)(uint32_t)(i + 1);   // ranks after every real key (score bits 0), distinct per candidate
-                skipped++;
-            } else {
-                need[gi] = true;
-            }
-        }
-#pragma unroll
-        for (int gi = 0; gi < G; gi++)
-            if (need[gi] && !pre) ap_dense_load_raw<DT, NV>(D, v[gi], raw[gi]);
-#pragma unroll
-        for (int gi = 0; gi < G; gi++) {
-            if (need[gi]) {
-                const float sd = ap_dense_dot_raw<DT, NV>(D, qa, raw[gi]);
-                if (lane == 0) newk[i0 + NW * gi] = ap_pool_key<KW>(ap_fuse(wd, ws, wf, sd, ss[gi], sf[gi]), v[gi], flags[gi]);
-            }
-        }
-    }
-    return skipped;
 }
 
 // Candidates a wave keeps in flight (ap_score_candidates' G), by workgroup size, as measured on a million-document
@@ -862,9 +716,14 @@ void k_search(ApSearchArgs g) {
 // Default cap of the index-owned workspace: 2 GiB of visited bits (16,384 queries of a million documents at a time).
 #define AP_SEARCH_WS_BYTES ((size_t)2 << 30)
 
-// Whether the bounds of all documents cost less than they save, by what was measured (microseconds):
-//  - the table: a document's columns are read once (0.4 ns), a tile of 256 queries takes 3.1 ps a pair at 1,280 columns, the
-//    tail's postings 3.5 ps a pair;
+// What the bounds of all documents cost, by what was measured (microseconds): a document's columns are read once (0.4 ns), a
+// tile of 256 queries takes 3.1 ps a pair at 1,280 columns, the tail's postings 3.5 ps a pair.
+double ap_bound_cost(const ap_index *ix, int64_t nq) {
+    const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256);
+    return 15.0 + (double)ix->docs.n * (0.4e-3 * cols + tiles * 256.0 * 3.1e-6 * cols + (double)nq * 3.5e-6);
+}
+
+// Whether that is less than they save:
 //  - a search that does without: at least 0.15 ns more for every document it reaches while the chip is full (100,000
 //    documents, beam 128: 22.1 ms for 10,000 queries without bounds, 13.3 ms with them, 2.9 of which are the table), and
 //    8 us more an iteration when it is not (one query, 128 iterations: 2.35 ms and 0.89 ms).
@@ -877,9 +736,7 @@ bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, 
     double iters = (double)beam / width;
     if (max_iters > 0) iters = std::min(iters, (double)max_iters);
     const double reached = n * (1.0 - exp(-iters * width * (double)ix->params.degree / n));
-    const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256);
-    const double cost = 15.0 + n * (0.4e-3 * cols + tiles * 256.0 * 3.1e-6 * cols + (double)nq * 3.5e-6);
-    return std::max((double)nq * reached * 0.15e-3, iters * 8.0) > cost;
+    return std::max((double)nq * reached * 0.15e-3, iters * 8.0) > ap_bound_cost(ix, nq);
 }
 
 // Queries per slab when `cap_words` words are available: as many as fit, then evened out over the slabs.
@@ -892,7 +749,7 @@ static int32_t ap_slab_size(int32_t nq, size_t words, size_t cap_words) {
 }
 
 // Sizes the workspace an index owns (grow only) for a call of nq queries.
-int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds) {
+int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan) {
     const size_t words = ((size_t)ix->docs.n + 31) / 32;
     const size_t cap_bytes = g_ap_debug.search_workspace_bytes > 0 ? (size_t)g_ap_debug.search_workspace_bytes : AP_SEARCH_WS_BYTES;
     ws->slab = ap_slab_size(nq, words, cap_bytes / 4);
@@ -917,8 +774,19 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     ix->last_nq = nq;
     // The bounds come last, and what the search cannot do without is sized as if there were none: they never take the memory
     // of a search that used to fit, and the same batch can run without them afterwards (captured, say) and allocate nothing.
+    if (plan.mode != 0 && ws->slab == nq) {   // a small batch, as a whole or not at all
+        AP_TRY(ap_bound_reserve(ix, nq, nq, AP_BOUND_WS_BYTES, plan.mode == 1 ? 2 : 1, st, &ws->bound));
+        if (ws->bound.table) {
+            ws->walk.bound = plan.mode == 1 ? ws->bound.table : nullptr;
+            ws->walk.exact = plan.mode == 1 ? ws->bound.second : ws->bound.table;
+            ws->walk.line = ws->bound.floor;
+            ws->walk.ld = ws->bound.ld;
+            for (int i = 0; i < 4; i++) ws->walk.share[i] = plan.share[i];
+            return AP_OK;
+        }
+    }
     if (bounds) {
-        AP_TRY(ap_bound_reserve(ix, ws->slab, 2048, AP_BOUND_WS_BYTES, st, &ws->bound));
+        AP_TRY(ap_bound_reserve(ix, ws->slab, 2048, AP_BOUND_WS_BYTES, 1, st, &ws->bound));
         if (ws->bound.table) ws->slab = ws->bound.slab;
     }
     return AP_OK;
@@ -936,6 +804,13 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // instantiation stays free of both.
     const bool kw = kw_terms != nullptr || ix->deleted != nullptr;
     const int32_t nq = (int32_t)Q.n;
+    if (ws.walk.exact) {
+        if (ws.ev0) AP_CHECK_HIP(hipEventRecord(ws.ev0, st));
+        if (ws.walk.bound) AP_TRY(ap_bound_fill(ix, ws.bound, Q, w_dev, w_stride, 0, nq, nullptr, 0, st));
+        AP_TRY(ap_walk_launch(ix, ws.walk, ws.visited, Q, w_dev, w_stride, k, beam, width, ws.counts, out_ids, out_scores, st));
+        if (ws.ev1) AP_CHECK_HIP(hipEventRecord(ws.ev1, st));
+        return AP_OK;
+    }
     if (!kw_terms) kw_stride = 0;
     ApSearchArgs g;
     g.D = ix->docs;
@@ -1062,7 +937,9 @@ static int ap_search_impl(ap_index *ix, const ap_queries *q, const float *per_qu
     if (q->nq == 0) return AP_OK;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApSearchWs ws;
-    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters)));
+    const bool bounds = ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters);
+    const ApWalkPlan plan = kw_terms ? ApWalkPlan() : ap_walk_plan(ix, q->nq, p->beam, p->search_width, p->max_iters, bounds, true);
+    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, bounds, plan));
     return ap_search_launch(ix, ws, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, p->k, p->beam, p->max_iters,
                             p->search_width, kw_terms, kw_stride, kw_flags, false, out_ids, out_scores, (hipStream_t)stream);
 }
@@ -1117,6 +994,15 @@ extern "C" int ap_search_batch_noalloc(const ap_index *ix, const ap_queries *q, 
     ApSearchWs ws;                       // no counters, no events: nothing of the index is written
     ws.visited = static_cast<uint32_t *>(base);
     ws.slab = ap_slab_size(q->nq, words, cap / 4);
+    // a small batch by the walk, with every document scored ahead, where the scores fit the array beside the visited sets
+    const ApWalkPlan plan = ap_walk_plan(ix, q->nq, p->beam, p->search_width, p->max_iters, false, false);
+    const size_t ld = ((size_t)ix->docs.n + 63) / 64 * 64, at = (words * (size_t)q->nq + 63) / 64 * 64;
+    if (plan.mode == 2 && (at + (ld + 5) * (size_t)q->nq) * 4 <= cap) {
+        ws.walk.exact = static_cast<float *>(base) + at;
+        ws.walk.line = ws.walk.exact + ld * (size_t)q->nq;
+        ws.walk.ld = (int64_t)ld;
+        for (int i = 0; i < 4; i++) ws.walk.share[i] = plan.share[i];
+    }
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     return ap_search_launch(ix, ws, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, p->k, p->beam, p->max_iters,
                             p->search_width, nullptr, 0, 0u, false, out_ids, out_scores, (hipStream_t)stream);

@@ -1,0 +1,98 @@
+"""Searches of small batches by the walk (scores first, then one wave a query) return the ids, scores, counts of scored
+documents and of iterations of the searches that score as they go, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00855_amd import binding as B
+from paper_2511_00855_amd.synth import make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _searches(ix, qs, pw, calls):
+    bits = lambda t: t.view(torch.int32) if t.dtype == torch.float32 else t   # a NaN compares by its bits
+    out = []
+    for k, beam, width in calls:
+        out += [bits(t).clone() for t in ix.search_batch(qs, k, beam, pw, search_width=width)]
+        out.append(ix.search_stats(qs.n)[0][:, :2].clone())
+    return out
+
+
+# degrees below, at and above a wave; a corpus smaller than the pool; more parents than the pool; visited sets in LDS and not
+@pytest.mark.parametrize("base,n,dim,vocab,degree,n_entry", [("tiny", 1500, 128, 10_000, 16, 16), ("cfg2", 2100, 260, 30_522, 64, 64),
+                                                             ("cfg3", 1100, 520, 5_000, 32, 100), ("cfg3", 900, 128, 250_002, 96, 7)])
+@pytest.mark.parametrize("visited_global", [0, 1])
+def test_walks_and_searches_are_the_same(debug_knobs, base, n, dim, vocab, degree, n_entry, visited_global):
+    w = make_workload(base, seed=11, n=n, nq=41, dim=dim, vocab=vocab)
+    docs, qs = B.DeviceVecs(w.docs, bf16=getattr(w.docs, "dense_bf16", None) is not None), B.DeviceVecs(w.queries)
+    ix = B.Index.build(docs, B.build_params(degree, nd_rounds=1, n_entry=n_entry))
+    pw = np.random.default_rng(5).uniform(-0.3, 1.0, (qs.n, 3)).astype(np.float32)
+    calls = [(1, 1, 1), (10, 16, 1), (5, 64, 3), (10, 130, 16), (10, 257, 1), (50, 700, 4), (10, n + 50, 1), (10, n + 50, 16)]
+    debug_knobs("search_visited_global", visited_global)
+    for weights in (pw, np.abs(pw)):
+        for deleted in (False, True):
+            ix.mark_deleted(np.random.default_rng(7).permutation(n)[:n // 3].astype(np.int32), restore=not deleted)
+            got = {}
+            for mode in (1, 2, 3):
+                debug_knobs("search_walk", mode)
+                got[mode] = _searches(ix, qs, weights, calls)
+            for mode in (2, 3):
+                for i, (a, b) in enumerate(zip(got[1], got[mode])):
+                    assert torch.equal(a, b), (mode, deleted, calls[i // 3], i % 3)
+    ix.close()
+
+
+def test_walks_that_start_again(debug_knobs):
+    """Graphs of random edges with repeated neighbours and holes, scores that are infinities and NaN: searches that the first
+    pass leaves undecided, and queries whose lists are longer than the tables in LDS."""
+    n, nq, dim = 6007, 25, 64
+    w = make_workload("tiny", seed=11, n=n, nq=nq, dim=dim, vocab=5_000)
+    rng, d = np.random.default_rng(6), w.docs
+    graph = rng.integers(-1, n, (n, 64)).astype(np.int32)
+    graph[:, 1] = graph[:, 0]
+    entry = rng.permutation(n)[:16].astype(np.int32)
+    pw = rng.uniform(0.1, 1.0, (nq, 3)).astype(np.float32)
+    calls = [(10, 64, 2), (10, 700, 16), (100, 1300, 1), (1, 33, 1)]
+    for special in (False, True):
+        if special:
+            rows = rng.permutation(n)[:n // 3]
+            d.dense.view(np.uint32)[rows, rng.integers(0, dim, len(rows))] = rng.choice(np.array([0x7f800000, 0xff800000, 0x7fc00000, 0xffc00000], np.uint32), len(rows))
+        docs, qs = B.DeviceVecs(d), B.DeviceVecs(w.queries)
+        ix = B.Index.import_graph(docs, B.build_params(64, n_entry=16), graph, entry)
+        for lists in (0, 1):
+            debug_knobs("search_query_lists", lists)
+            got = {}
+            for mode in (1, 2, 3):
+                debug_knobs("search_walk", mode)
+                got[mode] = _searches(ix, qs, pw, calls)
+            assert all(torch.equal(a, b) for mode in (2, 3) for a, b in zip(got[1], got[mode])), (special, lists)
+        ix.close()
+
+
+def test_noalloc_walk(debug_knobs):
+    """The entry point that allocates nothing: its scores ahead lie in the static array; captured into a graph, every replay gives
+    the eager result."""
+    w = make_workload("tiny", seed=33, n=3000, nq=40)
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    ix = B.Index.build(docs, B.build_params(w.degree))
+    pw = torch.from_numpy(np.random.default_rng(4).uniform(0.1, 1.0, (qs.n, 3)).astype(np.float32)).to(docs.device)
+    for k, beam, width in ((10, 96, 1), (10, 300, 4)):
+        debug_knobs("search_walk", 1)
+        ref = [t.clone() for t in ix.search_batch(qs, k, beam, pw, search_width=width)]
+        debug_knobs("search_walk", 3)
+        out = (torch.full((qs.n, k), -7, dtype=torch.int32, device=docs.device), torch.full((qs.n, k), float("nan"), device=docs.device))
+        ix.search_batch_noalloc(qs, k, beam, pw, out, search_width=width)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(ref, out))
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ix.search_batch_noalloc(qs, k, beam, pw, out, search_width=width)
+        for _ in range(3):
+            out[0].fill_(-7)
+            ix.search_batch(qs, k, beam, pw, search_width=width)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(ref, out))
+    ix.close()
