@@ -317,6 +317,153 @@ __global__ __launch_bounds__(256) void k_select_buf(const unsigned long long *__
     }
 }
 
+// Rows of f32 values rounded to bf16 (columns dim .. kd are zeros) for a sweep on the bf16 matrix cores whose candidates
+// k_rescore_buf scores again.  lost[r] = {|a - a^|, |a|} of row r (a^: a rounded; the differences are exact), each with room for its own
+// rounding and for squares that underflow.  stats: {largest |a|, largest |a - a^|, sum of |a|}, as float bits, zero at the start (a NaN or an
+// infinity among the values ends up in the first).  A wave a row.
+__global__ __launch_bounds__(256) void k_seed_round(const float *__restrict__ dense, int32_t dim, int64_t n, int32_t kd, uint16_t *__restrict__ rows,
+                                                    float2 *__restrict__ lost, uint32_t *__restrict__ stats) {
+    __shared__ uint32_t part[2][4];
+    __shared__ float total[4];
+    const int lane = threadIdx.x & 63, wave = ap_wave_id();
+    uint32_t most = 0, most_off = 0;
+    float sum = 0.f;
+    for (int64_t r = blockIdx.x * (int64_t)4 + wave; r < n; r += (int64_t)gridDim.x * 4) {
+        float s = 0.f, o = 0.f;
+        for (int32_t c = lane * 4; c < kd; c += 256) {
+            const float4 y = c < dim ? *reinterpret_cast<const float4 *>(dense + r * dim + c) : make_float4(0.f, 0.f, 0.f, 0.f);   // dim is a multiple of 4
+            const float x[4] = {y.x, y.y, y.z, y.w};
+            uint32_t h[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                h[e] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)x[e]);
+                const float off = x[e] - __uint_as_float(h[e] << 16);
+                s = fmaf(x[e], x[e], s);
+                o = fmaf(off, off, o);
+            }
+            *reinterpret_cast<uint2 *>(rows + r * kd + c) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+        }
+        const float norm = fmaf(sqrtf(ap_wave_sum(s)), 1.0001f, 1e-17f), off = fmaf(sqrtf(ap_wave_sum(o)), 1.0001f, 1e-17f);
+        if (lane == 0) lost[r] = make_float2(off, norm);
+        most = max(most, __float_as_uint(norm));
+        most_off = max(most_off, __float_as_uint(off));
+        sum += norm;
+    }
+    if (lane == 0) { part[0][wave] = most; part[1][wave] = most_off; total[wave] = sum; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const uint32_t *p = part[threadIdx.x];
+        atomicMax(&stats[threadIdx.x], max(max(p[0], p[1]), max(p[2], p[3])));
+    }
+    if (threadIdx.x == 2) atomicAdd(reinterpret_cast<float *>(&stats[2]), total[0] + total[1] + total[2] + total[3]);
+}
+
+// The exact top-K out of candidates whose scores are those of rounded rows.  With a^ for a rounded,  a b - a^ b^ = (a - a^) b + a^ (b - b^),
+// so a row's scores are off by at most  slack = |a - a^| max|b| + |a^| max|b - b^|  and what the sums of both products round (dim 2^-22 |a| max|b|
+// for the two).  With t the K-th best score of the rounded rows, a document of the exact top-K has one of at least t - 2 slack: those
+// candidates (the band; some 1.7 K of them) are scored again in f32, one a lane, as a chain of fused multiply-adds in ascending order of the
+// columns: what v_mfma_f32_32x32x2_f32 computes, so these are the bits of k_seed_scores and k_seed_thresh.  A row goes to the
+// exact path if the band reaches below tau (where candidates are missing), or holds more than AP_BAND.
+// What bounds it: the band's rows, gathered from all over the corpus.  A wave's candidates come in chunks of 32 columns, eight lanes a row (128 consecutive
+// bytes), through its own part of the LDS, the next chunk's loads in flight while one is summed: 15.2 ms for 100,000 rows of 768 columns
+// and K = 128 (some 71 GB at 4.7 TB/s).
+#define AP_BAND 1024
+__global__ __launch_bounds__(256) void k_rescore_buf(const float *__restrict__ dense, int32_t dim, const unsigned long long *__restrict__ buf, int32_t cap,
+                                                     const int32_t *__restrict__ cnt, const float *__restrict__ tau, const float2 *__restrict__ lost,
+                                                     const uint32_t *__restrict__ stats, int32_t K, int32_t *__restrict__ out_ids,
+                                                     float *__restrict__ out_sc, int32_t *__restrict__ n_overflow, int32_t *__restrict__ overflow_rows) {
+    __shared__ uint64_t keys[AP_BAND];
+    __shared__ __attribute__((aligned(16))) float s_a[1024];        // f32 rows have at most 1,024 columns
+    __shared__ __attribute__((aligned(16))) float stage[4][64 * AP_LDS_STRIDE];
+    __shared__ int32_t misc[4];
+    __shared__ uint64_t pre;
+    __shared__ uint32_t s_least;
+    __shared__ int32_t s_band;
+    // while the band is looked for: the candidates (as many as fit, which is all of them but for a forced capacity), the K best, a histogram
+    uint64_t *all = reinterpret_cast<uint64_t *>(stage[0]);
+    constexpr int32_t ALL = 4 * 64 * AP_LDS_STRIDE / 2;
+    uint64_t *sel = keys;                                           // [256]
+    uint32_t *hist = reinterpret_cast<uint32_t *>(keys + 256);      // [256]
+    const int64_t r = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = ap_wave_id();
+    const int32_t c = cnt[r];
+    if (c > cap || c < K) {   // uniform for the block
+        if (threadIdx.x == 0) overflow_rows[atomicAdd(n_overflow, 1)] = (int32_t)r;
+        return;
+    }
+    if (threadIdx.x == 0) { s_least = 0xffffffffu; s_band = 0; }
+    const unsigned long long *row = buf + r * (int64_t)cap;
+    for (int32_t j = threadIdx.x; j < c && j < ALL; j += 256) all[j] = row[j];
+    auto key_of = [&](int64_t j) -> uint64_t { return j < ALL ? all[j] : row[j]; };
+    __syncthreads();
+    const int32_t got = ap_radix_select_keys(key_of, c, c, K, hist, sel, misc, &pre);
+    if ((int32_t)threadIdx.x < got) atomicMin(&s_least, (uint32_t)(sel[threadIdx.x] >> 32));
+    for (int32_t x = threadIdx.x * 4; x < 1024; x += 1024)
+        *reinterpret_cast<float4 *>(&s_a[x]) = x < dim ? *reinterpret_cast<const float4 *>(dense + r * dim + x) : make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+    const float2 a = lost[r];
+    const float nmax = __uint_as_float(stats[0]), emax = __uint_as_float(stats[1]);
+    const float slack = 1.001f * (a.x * nmax + (a.y + a.x) * emax + (2.4e-7f * (float)(dim + 64)) * a.y * nmax);
+    const float least = ap_ord2f(s_least) - 2.f * slack;
+    if (least >= tau[r])
+        for (int32_t j = threadIdx.x; j < c; j += 256) {
+            const uint64_t key = key_of(j);
+            if (ap_key_score(key) >= least) {
+                const int32_t at = atomicAdd(&s_band, 1);
+                if (at < AP_BAND) keys[at] = key;
+            }
+        }
+    __syncthreads();
+    const int32_t nb = s_band;   // at least K, or 0
+    if (nb == 0 || nb > AP_BAND) {   // uniform
+        if (threadIdx.x == 0) overflow_rows[atomicAdd(n_overflow, 1)] = (int32_t)r;
+        return;
+    }
+    int32_t full = 256;
+    while (full < nb) full <<= 1;
+    for (int32_t x = nb + (int32_t)threadIdx.x; x < full; x += 256) keys[x] = 0;
+    const int32_t share = (nb + 3) >> 2, w1 = min(nb, (wave + 1) * share);
+    float *st = stage[wave];
+    for (int32_t p0 = wave * share; p0 < w1; p0 += 64) {
+        const int32_t m = min(64, w1 - p0);
+        const int col = (lane & 7) * 4;
+        const float *src[8];
+        float4 v[8];
+#pragma unroll
+        for (int p = 0; p < 8; p++) src[p] = dense + (int64_t)ap_key_id(keys[p0 + min((lane >> 3) + 8 * p, m - 1)]) * dim;
+        const int32_t id = ap_key_id(keys[p0 + min(lane, m - 1)]);
+#pragma unroll
+        for (int p = 0; p < 8; p++)
+            if (8 * p < m) v[p] = *reinterpret_cast<const float4 *>(src[p] + min(col, dim - 4));
+        float acc = 0.f;
+        for (int32_t k0 = 0; k0 < dim; k0 += 32) {
+            const bool inside = k0 + col < dim;   // s_a is zero where the columns end: any finite value does
+            ap_wave_sync();
+#pragma unroll
+            for (int p = 0; p < 8; p++)
+                if (8 * p < m) {
+                    float *d = st + ((lane >> 3) + 8 * p) * AP_LDS_STRIDE + col;
+                    d[0] = inside ? v[p].x : 0.f; d[1] = inside ? v[p].y : 0.f; d[2] = inside ? v[p].z : 0.f; d[3] = inside ? v[p].w : 0.f;
+                }
+            if (k0 + 32 < dim) {
+#pragma unroll
+                for (int p = 0; p < 8; p++)
+                    if (8 * p < m) v[p] = *reinterpret_cast<const float4 *>(src[p] + min(k0 + 32 + col, dim - 4));
+            }
+            ap_wave_sync();
+            const float *mine = st + min(lane, m - 1) * AP_LDS_STRIDE;
+#pragma unroll
+            for (int e = 0; e < 32; e++) acc = fmaf(s_a[k0 + e], mine[e], acc);
+        }
+        if (lane < m) keys[p0 + lane] = ap_make_key(acc, id, 1u);
+    }
+    ap_bitonic_desc(keys, full);
+    for (int32_t i = threadIdx.x; i < K; i += 256) {
+        out_ids[r * K + i] = ap_key_id(keys[i]);
+        out_sc[r * K + i] = ap_key_score(keys[i]);
+    }
+}
+
 // Exact path: full score rows of a slab, then selection.  Rows [row0, row0+nrows) of the node list.
 static hipError_t seed_exact_rows(const ap_index *ix, const int32_t *node_ids, int64_t row0, int64_t nrows, int32_t K,
                                   float *scratch, int64_t scratch_rows, int32_t *out_ids, float *out_sc, hipStream_t st) {
@@ -349,41 +496,82 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
     }
 }
 
-// S2 for a whole corpus of bf16 rows: the sweep with half the products.  D D^T is symmetric, so only the tiles on and
+// S2 for a whole corpus: the sweep with half the products.  D D^T is symmetric, so only the tiles on and
 // above the diagonal are multiplied and every score is offered to both of its documents (k_seed_thresh_big<.., SYM>).
 // For that every document's candidate buffer has to exist at once, so the buffers are short (cap entries, by the
 // memory that is free) and the thresholds tight: tau = the m-th best of cs sampled columns with m < K, chosen so that
 // a row expects about 0.45 cap candidates.  Such a tau is not a guaranteed lower bound of the row's K-th best: a row
 // that ends up with fewer than K candidates (a few in ten thousand) or more than cap is redone by the exact path,
 // like an overflowing row of the one-sided sweep.  The lists are the exact ones either way.
-// *done = false (and AP_OK): not applicable here (shape, memory); the caller takes the one-sided sweep.
-static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, int32_t *out_ids, float *out_sc, hipStream_t st, bool *done) {
+// rounded (f32 rows): thresholds and sweep take the rows rounded to bf16, at eight times the matrix rate, and the few candidates that the
+// rounding leaves open are scored in f32 (k_rescore_buf).  The lists are the same bits.  100,000 rows of 768 columns, K = 128: 82.7 ms with
+// f32 products (71 of them the sweep), 29.5 ms rounded (10.4 the sweep); 96 columns: 23.4 and 11.5 ms.
+// *done = false (and AP_OK): not applicable here (shape, memory; rounded: norms that differ too much, or rows too much alike for the
+// rounding to tell them apart); the caller takes the next sweep.
+static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, int32_t *out_ids, float *out_sc, hipStream_t st, bool *done) {
     *done = false;
-    const bool big = ix->dtype == AP_BF16;             // bf16 rows: 256x256 tiles; f32 rows: 128x128 tiles
+    const bool big = rounded || ix->dtype == AP_BF16;  // bf16 rows: 256x256 tiles; f32 rows: 128x128 tiles
     const int64_t E = big ? AP_BIG : AP_TILE;
     const int64_t n = ix->docs.n, T = n / E;
-    if ((big && ix->docs.dim % AP_BK16 != 0) || T < 2 || n > ((int64_t)1 << 30)) return AP_OK;
+    const int32_t dim = rounded ? (ix->docs.dim + AP_BK16 - 1) / AP_BK16 * AP_BK16 : ix->docs.dim;
+    if ((big && dim % AP_BK16 != 0) || T < 2 || n > ((int64_t)1 << 30)) return AP_OK;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return AP_OK;
     int64_t cap = 4096;
     while (cap > 512 && (double)n * (double)cap * 8.0 > 0.62 * (double)free_b) cap >>= 1;
     if ((double)n * (double)cap * 8.0 > 0.62 * (double)free_b) return AP_OK;
-    const double mean = 0.45 * (double)cap;
-    int64_t m = std::min<int64_t>(K, 24);
+    // Fewer candidates do where they are scored again: three times what the band takes, of a sample that need not be large.
+    const double mean = rounded ? std::min(0.45 * (double)cap, std::max(6.0 * K, 24.0 * (double)n / 4096.0)) : 0.45 * (double)cap;
+    // the rounded sweep needs more candidates than K: on a small corpus a rank beyond K
+    const int64_t m_max = rounded ? 256 : K;
+    int64_t m = std::min<int64_t>(m_max, 24);
     int64_t cs = (int64_t)((double)m * (double)n / mean) + 1;
     const int64_t cs_min = g_ap_debug.seed_sample_cols > 0 ? std::max<int64_t>(K + 1, g_ap_debug.seed_sample_cols) : 4096;
     if (cs < cs_min || g_ap_debug.seed_sample_cols > 0) {   // a fixed sample: the rank that gives the same expectation
         cs = cs_min;
-        m = std::min<int64_t>(K, std::max<int64_t>(m, (int64_t)(mean * (double)cs / (double)n) + 1));
+        m = std::min<int64_t>(m_max, std::max<int64_t>(m, (int64_t)(mean * (double)cs / (double)n) + 1));
     }
     cs = (cs + AP_TILE - 1) / AP_TILE * AP_TILE;
     if (n < 2 * cs) return AP_OK;
+    // The band takes some 1.7 K candidates, and a row's number of candidates is off by one part in sqrt(m).
+    if (rounded && ((double)m * (double)n / (double)cs < 4.0 * K || (double)n * ((double)cap * 8.0 + (double)dim * 2.0) > 0.75 * (double)free_b)) return AP_OK;
     if (g_ap_debug.seed_buffer_cap > 0) cap = g_ap_debug.seed_buffer_cap;   // forces overflows
     const int64_t RS = 8192;
     float *scratch = nullptr, *tau = nullptr, *tmp_sc = nullptr;
     unsigned long long *buf = nullptr;
     int32_t *cnt = nullptr, *ovf = nullptr;
+    const void *dense = ix->docs.dense;
+    uint16_t *r16 = nullptr;
+    float2 *lost = nullptr;
+    uint32_t *stats = nullptr;
+    if (rounded) {
+        float got[3] = {0.f, 0.f, 0.f};
+        int rr = ap_dev_alloc(&r16, (size_t)n * (size_t)dim);
+        if (rr == AP_OK) rr = ap_dev_alloc(&lost, (size_t)n);
+        if (rr == AP_OK) rr = ap_dev_alloc(&stats, 3);
+        if (rr == AP_OK) rr = ap_fill_u32(stats, 3, 0u, st);
+        if (rr == AP_OK) {
+            hipLaunchKernelGGL(k_seed_round, dim3((unsigned)std::min<int64_t>((n + 3) / 4, 2048)), dim3(256), 0, st, static_cast<const float *>(dense),
+                               ix->docs.dim, n, dim, r16, lost, stats);
+            if (hipGetLastError() != hipSuccess || hipMemcpyAsync(got, stats, sizeof(got), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                rr = AP_EHIP;
+        }
+        // one row's slack is made with the corpus's largest norms: of use while the others come near them
+        if (rr != AP_OK || !(got[0] >= 1e-10f && got[0] <= 1e15f && got[0] <= 4.f * got[2] / (float)n)) {
+            void *ptrs[] = {r16, lost, stats};
+            for (void *q : ptrs) if (q) (void)hipFree(q);
+            (void)hipGetLastError();
+            ap_set_error("%s", "");
+            return AP_OK;
+        }
+        dense = r16;
+    }
     int rc = ap_dev_alloc(&buf, (size_t)n * (size_t)cap);
+    if (rc != AP_OK) {
+        void *ptrs[] = {r16, lost, stats};
+        for (void *q : ptrs) if (q) (void)hipFree(q);
+    }
     if (rc != AP_OK) { (void)hipGetLastError(); ap_set_error("%s", ""); return AP_OK; }   // no room for the buffers after all: the one-sided sweep
     rc = ap_dev_alloc(&scratch, (size_t)RS * (size_t)cs);
     if (rc == AP_OK) rc = ap_dev_alloc(&tau, (size_t)n);
@@ -391,18 +579,19 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, int32_t *out_ids
     if (rc == AP_OK) rc = ap_dev_alloc(&cnt, (size_t)n);
     if (rc == AP_OK) rc = ap_dev_alloc(&ovf, (size_t)n + 1);
     hipError_t e = hipSuccess;
+    bool alike = false;   // the rounding left too many rows open
     int32_t *re_ids = nullptr; float *re_sc = nullptr, *ex_scratch = nullptr;
     if (rc == AP_OK) {
         // thresholds of all rows
         for (int64_t row0 = 0; row0 < n && e == hipSuccess; row0 += RS) {
             const int64_t nrows = std::min(RS, n - row0);
             dim3 gs(ap_seed_grid((nrows + AP_TILE - 1) / AP_TILE, cs / AP_TILE));
-            ix->seed_flops += (unsigned long long)(((nrows + AP_TILE - 1) / AP_TILE) * (cs / AP_TILE)) * 2ull * AP_TILE * AP_TILE * (unsigned long long)ix->docs.dim;
+            ix->seed_flops += (unsigned long long)(((nrows + AP_TILE - 1) / AP_TILE) * (cs / AP_TILE)) * 2ull * AP_TILE * AP_TILE * (unsigned long long)dim;
             if (big)
-                hipLaunchKernelGGL(k_seed_scores<AP_BF16>, gs, dim3(256), 0, st, ix->docs.dense, ix->docs.dim, n, (const int32_t *)nullptr, row0, nrows,
+                hipLaunchKernelGGL(k_seed_scores<AP_BF16>, gs, dim3(256), 0, st, dense, dim, n, (const int32_t *)nullptr, row0, nrows,
                                    (int64_t)0, cs, scratch);
             else
-                hipLaunchKernelGGL(k_seed_scores<AP_F32>, gs, dim3(256), 0, st, ix->docs.dense, ix->docs.dim, n, (const int32_t *)nullptr, row0, nrows,
+                hipLaunchKernelGGL(k_seed_scores<AP_F32>, gs, dim3(256), 0, st, dense, dim, n, (const int32_t *)nullptr, row0, nrows,
                                    (int64_t)0, cs, scratch);
             hipLaunchKernelGGL(k_select_rows, dim3((unsigned)nrows), dim3(256), 0, st, scratch, cs, (int32_t)m, (const int32_t *)nullptr, row0, 1,
                                (int64_t)0, (int32_t *)nullptr, tmp_sc);
@@ -417,7 +606,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, int32_t *out_ids
         ap_progress("seed lists: thresholds of %lld rows (rank %lld of %lld sampled columns), buffers of %lld", (long long)n, (long long)m,
                     (long long)cs, (long long)cap);
         // tiles multiplied: those on and above the diagonal, and the ragged last row and column of tiles
-        ix->seed_flops += (unsigned long long)(T * (T + 1) / 2 + (n % E != 0 ? 2 * T + 1 : 0)) * 2ull * (unsigned long long)(E * E) * (unsigned long long)ix->docs.dim;
+        ix->seed_flops += (unsigned long long)(T * (T + 1) / 2 + (n % E != 0 ? 2 * T + 1 : 0)) * 2ull * (unsigned long long)(E * E) * (unsigned long long)dim;
         if (big) {
             const dim3 tb(AP_BIG_WM * AP_BIG_WN * 64);
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, true, true>),
@@ -430,7 +619,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, int32_t *out_ids
             for (int64_t s0 = 0; s0 < T && e == hipSuccess; s0 += 32) {
                 const int64_t nrt = std::min<int64_t>(32, T - s0), nct = T - s0;
                 hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, true, true>), dim3(ap_seed_grid(nrt, nct)), tb, AP_BIG_LDS_BYTES, st,
-                                   ix->docs.dense, ix->docs.dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, s0, nrt, s0);
+                                   dense, dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, s0, nrt, s0);
                 e = hipGetLastError();
                 if ((s0 / 32) % 64 == 63) {
                     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -440,37 +629,42 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, int32_t *out_ids
             if (e == hipSuccess && n % AP_BIG != 0) {
                 // the ragged last column tile for the full row tiles, and the ragged last rows against every column: one-sided
                 hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>), dim3(ap_seed_grid(T, 1)), tb, AP_BIG_LDS_BYTES, st,
-                                   ix->docs.dense, ix->docs.dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, (int64_t)0, T, T);
+                                   dense, dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, (int64_t)0, T, T);
                 hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>), dim3(ap_seed_grid(1, T + 1)), tb, AP_BIG_LDS_BYTES, st,
-                                   ix->docs.dense, ix->docs.dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, T, (int64_t)1, (int64_t)0);
+                                   dense, dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, T, (int64_t)1, (int64_t)0);
                 e = hipGetLastError();
             }
         } else {
             // f32 rows: the same on 128x128 tiles, a slab of 64 row tiles (eight per XCD) a launch
             for (int64_t s0 = 0; s0 < T && e == hipSuccess; s0 += 64) {
                 const int64_t nrt = std::min<int64_t>(64, T - s0), nct = T - s0, r0 = s0 * AP_TILE;
-                hipLaunchKernelGGL((k_seed_thresh<AP_F32, true>), dim3(ap_seed_grid(nrt, nct)), dim3(256), 0, st, ix->docs.dense, ix->docs.dim, n,
+                hipLaunchKernelGGL((k_seed_thresh<AP_F32, true>), dim3(ap_seed_grid(nrt, nct)), dim3(256), 0, st, dense, dim, n,
                                    (const int32_t *)nullptr, r0, nrt * AP_TILE, tau + r0, buf + r0 * cap, (int32_t)cap, cnt + r0, s0);
                 e = hipGetLastError();
             }
             if (e == hipSuccess && n % AP_TILE != 0) {
                 const int64_t r0 = T * AP_TILE;
-                hipLaunchKernelGGL((k_seed_thresh<AP_F32, false>), dim3(ap_seed_grid(T, 1)), dim3(256), 0, st, ix->docs.dense, ix->docs.dim, n,
+                hipLaunchKernelGGL((k_seed_thresh<AP_F32, false>), dim3(ap_seed_grid(T, 1)), dim3(256), 0, st, dense, dim, n,
                                    (const int32_t *)nullptr, (int64_t)0, r0, tau, buf, (int32_t)cap, cnt, T);
-                hipLaunchKernelGGL((k_seed_thresh<AP_F32, false>), dim3(ap_seed_grid(1, T + 1)), dim3(256), 0, st, ix->docs.dense, ix->docs.dim, n,
+                hipLaunchKernelGGL((k_seed_thresh<AP_F32, false>), dim3(ap_seed_grid(1, T + 1)), dim3(256), 0, st, dense, dim, n,
                                    (const int32_t *)nullptr, r0, n - r0, tau + r0, buf + r0 * cap, (int32_t)cap, cnt + r0, (int64_t)0);
                 e = hipGetLastError();
             }
         }
         int32_t n_ovf = 0;
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_select_buf, dim3((unsigned)n), dim3(256), 0, st, buf, (int32_t)cap, cnt, K, (int32_t)std::min<int64_t>(K, n - 1),
-                               (int64_t)0, out_ids, out_sc, ovf, ovf + 1);
+            if (rounded)
+                hipLaunchKernelGGL(k_rescore_buf, dim3((unsigned)n), dim3(256), 0, st, static_cast<const float *>(ix->docs.dense), ix->docs.dim, buf, (int32_t)cap,
+                                   cnt, tau, lost, stats, K, out_ids, out_sc, ovf, ovf + 1);
+            else
+                hipLaunchKernelGGL(k_select_buf, dim3((unsigned)n), dim3(256), 0, st, buf, (int32_t)cap, cnt, K, (int32_t)std::min<int64_t>(K, n - 1),
+                                   (int64_t)0, out_ids, out_sc, ovf, ovf + 1);
             e = hipGetLastError();
         }
         if (e == hipSuccess) e = hipMemcpyAsync(&n_ovf, ovf, sizeof(int32_t), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e == hipSuccess && n_ovf > 0) {   // rows left short or overflowing: the exact path
+        if (e == hipSuccess && rounded && n_ovf > n / 16 && g_ap_debug.seed_buffer_cap == 0 && g_ap_debug.seed_tau_ulps == 0) alike = true;
+        else if (e == hipSuccess && n_ovf > 0) {   // rows left short or overflowing: the exact path
             ap_progress("seed lists: %d rows redone by the exact path", (int)n_ovf);
             (void)hipFree(buf); buf = nullptr;
             int64_t ex_rows = std::max<int64_t>(AP_TILE, (((int64_t)1 << 28) / n) / AP_TILE * AP_TILE);
@@ -490,21 +684,25 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, int32_t *out_ids
             }
         }
     }
-    void *ptrs[] = {scratch, tau, tmp_sc, buf, cnt, ovf, ex_scratch, re_ids, re_sc};
+    void *ptrs[] = {scratch, tau, tmp_sc, buf, cnt, ovf, ex_scratch, re_ids, re_sc, r16, lost, stats};
     for (void *q : ptrs) if (q) (void)hipFree(q);
     if (rc != AP_OK) return rc;
     if (e != hipSuccess) { ap_set_error("seed k-NN failed: %s", hipGetErrorString(e)); return AP_EHIP; }
-    *done = true;
+    *done = !alike;
     return AP_OK;
 }
 
+// Whole corpora of f32 rows from which the rounded sweep is the faster one, K = 128: 7.5 ms of score rows and 4.6 ms rounded at 20,000 documents of
+// 768 columns, 1.6 and 2.2 ms at 8,192 (K = 64 at 12,000: 3.0 and 2.5 ms).
+#define AP_ROUNDED_MIN 16384
 // S2.  Small corpora: every score row is materialised and the K best are
 // selected from it.  Large corpora: the N x N scores are never stored: a
 // sample of the columns gives each row a lower bound tau of its K-th best
 // score, then one sweep over all columns appends only the scores >= tau to a
 // per-row candidate buffer, from which the exact top-K is selected.  A row
 // whose buffer overflows (not observed; the buffer holds twice the expected
-// number of candidates) is redone by the exact path.
+// number of candidates) is redone by the exact path.  Whole corpora take the
+// symmetric sweeps where they apply.
 int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, int32_t K, int32_t *out_ids,
                          float *out_sc, hipStream_t st) {
     const int64_t n = ix->docs.n;
@@ -516,6 +714,12 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
     ex_rows = std::min<int64_t>(ex_rows, (nn + AP_TILE - 1) / AP_TILE * AP_TILE);
     hipError_t e = hipSuccess;
     int rc = AP_OK;
+    const bool whole = !node_ids && !g_ap_debug.seed_one_sided;   // the symmetric sweeps' case
+    if (whole && ix->dtype == AP_F32 && n < 2 * cs && n >= AP_ROUNDED_MIN) {
+        bool done = false;
+        rc = ap_seed_knn_symmetric(ix, K, true, out_ids, out_sc, st, &done);
+        if (rc != AP_OK || done) return rc;
+    }
     if (n < 2 * cs) {
         float *scratch = nullptr;
         AP_TRY(ap_dev_alloc(&scratch, (size_t)ex_rows * (size_t)n));
@@ -525,10 +729,12 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
         if (e != hipSuccess) { ap_set_error("seed k-NN failed: %s", hipGetErrorString(e)); return AP_EHIP; }
         return AP_OK;
     }
-    if (!node_ids && !g_ap_debug.seed_one_sided) {   // the whole corpus: the symmetric sweep where it applies
+    if (whole) {   // the symmetric sweep where it applies
         bool done = false;
-        rc = ap_seed_knn_symmetric(ix, K, out_ids, out_sc, st, &done);
-        if (rc != AP_OK || done) return rc;
+        for (int rounded = ix->dtype == AP_F32 ? 1 : 0; rounded >= 0; rounded--) {
+            rc = ap_seed_knn_symmetric(ix, K, rounded != 0, out_ids, out_sc, st, &done);
+            if (rc != AP_OK || done) return rc;
+        }
     }
     const int64_t RS = std::min<int64_t>(8192, (nn + AP_TILE - 1) / AP_TILE * AP_TILE);
     // expected candidates per row = K * n / cs (tau is the K-th best of cs sampled columns)

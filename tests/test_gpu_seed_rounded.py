@@ -1,0 +1,55 @@
+"""Seed lists of f32 rows out of a sweep over the rows rounded to bf16, whose candidates are scored again in f32: the same
+ids and scores, bit for bit, as the one-sided f32 products give."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00855_amd import binding as B
+from paper_2511_00855_amd.synth import make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(docs, K, one_sided):
+    B.debug_set("seed_one_sided", one_sided)
+    try:
+        ix = B.Index.ingest(docs, B.build_params(8, knn_k=max(K, 8), nd_rounds=1, nd_sample=4, n_entry=4))
+        out = [t.clone() for t in ix.stage_seed_knn(K)]
+        flops = ix.build_counters()["seed_flops"]
+        ix.close()
+    finally:
+        B.debug_reset()
+    return out, flops
+
+
+# the smallest corpus it takes; widths that are no multiple of a chunk, the narrowest and the widest; ragged last tiles; few and
+# most neighbours; beyond the smallest corpus of the f32 sweep
+@pytest.mark.parametrize("n,dim,K,kind", [
+    (16384, 4, 1, "plain"), (16641, 100, 200, "plain"), (20001, 260, 64, "norms"), (18000, 1024, 128, "plain"), (16500, 68, 256, "plain"),
+    (33001, 36, 32, "norms"), (17000, 64, 100, "ties"),
+    # one row dwarfs the others, a value is no number, all rows nearly the same: the f32 products decide
+    (17000, 64, 32, "giant"), (17000, 64, 32, "nan"), (17000, 64, 32, "alike")])
+def test_rounded_sweep_gives_the_lists_of_the_f32_products(n, dim, K, kind):
+    print(f"rounded seed sweep n={n} dim={dim} K={K} {kind}", flush=True)
+    w = make_workload("tiny", seed=n + dim, n=n, nq=1, dim=dim, sp=("fixed", 2), tx=("fixed", 2))
+    rng = np.random.default_rng(dim)
+    d = np.ascontiguousarray(w.docs.dense, dtype=np.float32)
+    if kind == "norms":
+        d = d * rng.uniform(0.3, 2.0, (n, 1)).astype(np.float32)
+    elif kind == "ties":         # every row eight times: equal scores, ranked by id
+        d = d[rng.integers(0, n // 8, n)]
+    elif kind == "giant":
+        d = d.copy()
+        d[n // 3] *= 1e6
+    elif kind == "nan":
+        d = d.copy()
+        d[5, 3] = np.nan
+    elif kind == "alike":
+        d = (d[:1] + 1e-4 * d).astype(np.float32)
+    w.docs.dense = np.ascontiguousarray(d)
+    docs = B.DeviceVecs(w.docs)
+    want, f_want = _lists(docs, K, 1)
+    got, f_got = _lists(docs, K, 0)
+    assert torch.equal(got[0], want[0])
+    assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+    assert (f_got == f_want) == (kind in ("giant", "nan")), (f_got, f_want)   # which sweep it was
