@@ -1456,25 +1456,39 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
 // The same products as matrix products.  What bounds the walks above is instruction issue: some 330 steps of 13
 // instructions per pair, nearly all of them over terms the other list does not hold.  Here the K lists of a neighbourhood
 // are turned into columns instead: a term that only one of the K documents holds contributes to no pair and is dropped; the
-// others (some 2,000 of a neighbourhood of 128) are numbered in ascending order, and the K x T matrix of their weights is
-// multiplied with its transpose by f32 MFMAs, 64 columns at a time.  Same f32 products and sums (an absent term adds exactly
-// 0); only the order of a sum's terms differs.
+// others (some 2,000 of a neighbourhood of 128) are numbered in ascending order.  Nine of ten of them have AP_GL_FEW holders
+// or fewer: their pairs are added one by one (a tenth of a percent of the products that their columns would take in a matrix).
+// The K x T matrix of the others' weights is multiplied with its transpose by f32 MFMAs, 64 columns at a time.  Same f32
+// products and sums (an absent term adds exactly 0); only the order of a sum's terms differs.
 //
 // One workgroup of 16 waves per node; per vocabulary:
 //  - a wave loads the lists of its 8 documents into registers (3 entries a lane: 192 a list; what a longer list holds beyond
 //    that is read again for every chunk);
 //  - two bitmaps over the vocabulary in LDS mark terms met and terms met twice; the number of set bits before a term's in
 //    the second is its column;
+//  - the columns' holders are counted, and those of the columns with few laid out one after the other (in any order: a document holds
+//    a term once).  Eight lanes take a row and add, for its entries in ascending order of the terms, the products with the holders
+//    of lower rows to the row's part of a triangle in LDS: every pair has one owner and one order.  The triangle is what the
+//    product's accumulators start with;
 //  - a wave writes its 8 rows of a chunk (cleared, then the entries whose column falls into it), into one of two stages,
 //    while the other stage is multiplied: one barrier a chunk.
 // The lower triangle of the result is 36 blocks of 16 x 16 (K = 128): two a wave and four more on the first four waves, nine
-// on every SIMD.  200,000 bf16 documents: 299 ms with the walks, 109 ms here; 100,000 f32: 160 and 66 ms.  The MFMAs alone need
-// two fifths of that (their busy counter); the rest is the rows' writing, which shares the issue slots, and the waves' barriers.
+// on every SIMD.  A neighbourhood with a list beyond the registers, or more columns or entries than the LDS holds, takes all of its
+// columns to the matrix, and so does one with AP_GL_SPLIT columns or fewer: the steps before the first product take some
+// 50,000 cycles a vocabulary, a chunk of the matrix 8,000 (2,000 documents of 64 neighbours and some 250 columns: 2.85 ms a construction
+// with its columns set apart, 2.67 ms without).  The prune stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all
+// columns in the matrix, 41 ms here; 200,000 bf16: 299, 109 and 76 ms.  Of a workgroup's 260,000 cycles the pairs take 55,000, the
+// matrix 60,000, marking, numbering and counting the columns 110,000: chains of LDS round trips that 16 waves do not hide.
 #define AP_GL_WORDS 8192          // words of a bitmap: vocabularies up to 2^18 terms
 #define AP_GL_C 64                // columns of a chunk
 #define AP_GL_STRIDE (AP_GL_C + 4)   // rows 16-byte aligned; 16 rows x 4 groups of 4 columns fall into distinct banks
 #define AP_GL_SLOTS 3             // list entries a lane holds in registers
-#define AP_GL_LDS (2 * AP_GL_WORDS * 4 + 2 * 128 * AP_GL_STRIDE * 4)
+#define AP_GL_FEW 8               // holders of a column whose pairs are added one by one
+#define AP_GL_SPLIT 512            // columns beyond which setting those with few holders apart pays
+#define AP_GL_COLS 4096           // columns whose holders are counted (16 KB where the bitmaps were)
+#define AP_GL_HOLD 6144           // entries of the columns with few holders (48 KB behind them, 48 KB behind the triangle)
+#define AP_GL_U 4                 // entries of a row on their way at a time
+#define AP_GL_LDS (2 * AP_GL_WORDS * 4 + 128 * 127 / 2 * 4 + AP_GL_HOLD * 8)
 typedef float ap_f32x4 __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ rec, const uint4 *__restrict__ meta, float wd, float ws, float wf,
                                                      int32_t sp_words, int32_t tx_words, int32_t K, const int32_t *__restrict__ knn,
@@ -1485,6 +1499,12 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
     __shared__ int32_t s_id[128], s_sn[128], s_tn[128];
     __shared__ uint32_t s_first[128], s_part[16], s_total;
     __shared__ float s_diag[2][128];
+    __shared__ int32_t s_rare[128], s_rare_at[128], s_rare_end[2];   // a row's entries of columns with few holders, the first one's place among its wave's
+    uint32_t *col_map = gl_lds;                                     // [AP_GL_COLS], once the columns are known
+    uint2 *hold = reinterpret_cast<uint2 *>(gl_lds + AP_GL_COLS);   // [AP_GL_HOLD] (row, weight)
+    float *tri = X;                                                 // [128 * 127 / 2] row i's sums with the rows below i, before the stages are written
+    uint2 *rare = reinterpret_cast<uint2 *>(X + 128 * 127 / 2);     // [AP_GL_HOLD] (first holder's place | their number << 13, weight)
+    static_assert(AP_GL_COLS + 2 * AP_GL_HOLD <= 2 * AP_GL_WORDS && 2 * 128 * AP_GL_STRIDE <= 128 * 127 / 2 + 2 * AP_GL_HOLD && AP_GL_FEW <= 8, "LDS");
     const int64_t x = blockIdx.x;
     const int64_t u = node_ids ? (int64_t)node_ids[x0 + x] : x0 + x;
     const int tid = threadIdx.x, lane = tid & 63, wave = ap_wave_id();
@@ -1494,6 +1514,7 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
         if (id >= 0) m = meta[id];
         s_id[tid] = id; s_first[tid] = m.x; s_sn[tid] = (int32_t)(m.y & 0xffffu); s_tn[tid] = (int32_t)(m.y >> 16);
     }
+    if (tid < 2) s_rare_end[tid] = 0;
     const int32_t blocks = (K + 15) / 16, n_tasks = blocks * (blocks + 1) / 2;
     // this wave's blocks of the lower triangle: tasks wave, wave + 16, wave + 32
     int32_t bi[3], bj[3];
@@ -1552,7 +1573,11 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
         {
             uint32_t cnt[8], sum = 0;
 #pragma unroll
-            for (int k = 0; k < 8; k++) { cnt[k] = tid * 8 + k < words ? (uint32_t)__popc(twice[tid * 8 + k]) : 0u; sum += cnt[k]; }
+            for (int k = 0; k < 8; k += 4) {   // words is a multiple of 4
+                const uint4 t4 = tid * 8 + k < words ? *reinterpret_cast<const uint4 *>(twice + tid * 8 + k) : make_uint4(0, 0, 0, 0);
+                cnt[k] = (uint32_t)__popc(t4.x); cnt[k + 1] = (uint32_t)__popc(t4.y); cnt[k + 2] = (uint32_t)__popc(t4.z); cnt[k + 3] = (uint32_t)__popc(t4.w);
+                sum += cnt[k] + cnt[k + 1] + cnt[k + 2] + cnt[k + 3];
+            }
             uint32_t upto = sum;
             for (int o = 1; o < 64; o <<= 1) { const uint32_t up = __shfl_up(upto, o, 64); if (lane >= o) upto += up; }
             if (lane == 63) s_part[wave] = upto;
@@ -1561,7 +1586,11 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
             for (int w = 0; w < wave; w++) base += s_part[w];
             base += upto - sum;
 #pragma unroll
-            for (int k = 0; k < 8; k++) { if (tid * 8 + k < words) seen[tid * 8 + k] = base; base += cnt[k]; }
+            for (int k = 0; k < 8; k += 4) {
+                const uint32_t b1 = base + cnt[k], b2 = b1 + cnt[k + 1], b3 = b2 + cnt[k + 2];
+                if (tid * 8 + k < words) *reinterpret_cast<uint4 *>(seen + tid * 8 + k) = make_uint4(base, b1, b2, b3);
+                base = b3 + cnt[k + 3];
+            }
             if (tid == 1023) s_total = base;
         }
         __syncthreads();
@@ -1569,17 +1598,126 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
             const uint32_t m = twice[t >> 5], bit = 1u << (t & 31);
             return m & bit ? seen[t >> 5] + (uint32_t)__popc(m & (bit - 1u)) : 0xffffffffu;
         };
-        uint32_t used = 0;   // uniform: slots that hold a column at all (a list of 60 entries leaves two of its three empty)
 #pragma unroll
         for (int d = 0; d < 8; d++)
 #pragma unroll
-            for (int k = 0; k < AP_GL_SLOTS; k++) {
+            for (int k = 0; k < AP_GL_SLOTS; k++)
                 if (ent[d][k].x != 0xffffffffu) ent[d][k].x = column(ent[d][k].x);
-                used |= __ballot(ent[d][k].x != 0xffffffffu) ? 1u << (d * AP_GL_SLOTS + k) : 0u;
-            }
         uint32_t longs = 0;   // uniform: documents of this wave whose list goes on behind the registers
         for (int d = 0; d < 8; d++) longs |= ap_uniform_i32(part ? s_tn[wave * 8 + d] : s_sn[wave * 8 + d]) > 64 * AP_GL_SLOTS ? 1u << d : 0u;
-        const int32_t n_chunks = ((int32_t)ap_uniform_u32(s_total) + AP_GL_C - 1) / AP_GL_C;
+        int32_t n_cols = (int32_t)ap_uniform_u32(s_total);   // columns of the matrix
+        if (!__syncthreads_or(longs != 0) && n_cols > AP_GL_SPLIT && n_cols <= AP_GL_COLS) {   // uniform; nobody asks the bitmaps any more
+            *reinterpret_cast<uint4 *>(col_map + tid * 4) = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            // an entry: column | place among its column's holders << 16
+#pragma unroll
+            for (int d = 0; d < 8; d++)
+#pragma unroll
+                for (int k = 0; k < AP_GL_SLOTS; k++)
+                    if (ent[d][k].x != 0xffffffffu) ent[d][k].x |= atomicAdd(&col_map[ent[d][k].x], 1u) << 16;
+            __syncthreads();
+            // four columns a thread: 1 << 31 | its column of the matrix, or the first holder's place | their number << 13.  Sums of
+            // both kinds in one scan: columns of the matrix << 18 | holders of the others (at most 8 * 4,096)
+            const uint4 c4 = *reinterpret_cast<const uint4 *>(col_map + tid * 4);
+            const uint32_t hc[4] = {c4.x, c4.y, c4.z, c4.w};
+            uint32_t own[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; k++) { own[k] = hc[k] > AP_GL_FEW ? 1u << 18 : hc[k]; sum += own[k]; }
+            uint32_t upto = sum;
+            for (int o = 1; o < 64; o <<= 1) { const uint32_t up = __shfl_up(upto, o, 64); if (lane >= o) upto += up; }
+            if (lane == 63) s_part[wave] = upto;
+            __syncthreads();
+            uint32_t base = upto - sum;
+            for (int w = 0; w < wave; w++) base += s_part[w];
+            uint32_t to[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                to[k] = hc[k] > AP_GL_FEW ? 0x80000000u | (base >> 18) : (base & 0x1fffu) | (hc[k] << 13);
+                base += own[k];
+            }
+            *reinterpret_cast<uint4 *>(col_map + tid * 4) = make_uint4(to[0], to[1], to[2], to[3]);
+            if (tid == 1023) s_total = base;
+            __syncthreads();
+            const uint32_t total = ap_uniform_u32(s_total);
+            if ((int32_t)(total & 0x3ffffu) <= AP_GL_HOLD) {   // uniform
+                n_cols = (int32_t)(total >> 18);
+                uint32_t most = 0, n_all = 0;   // uniform
+#pragma unroll
+                for (int d = 0; d < 8; d++) {
+                    uint32_t n_rare = 0;
+#pragma unroll
+                    for (int k = 0; k < AP_GL_SLOTS; k++) {
+                        const uint32_t e = ent[d][k].x;
+                        bool few = false;
+                        if (e != 0xffffffffu) {
+                            const uint32_t m = col_map[e & 0xffffu];
+                            few = m < 0x80000000u;
+                            if (few) hold[(m & 0x1fffu) + (e >> 16)] = make_uint2((uint32_t)(wave * 8 + d), ent[d][k].y);
+                            ent[d][k].x = few ? 0x80000000u | m : m & 0x7fffffffu;
+                        }
+                        n_rare += (uint32_t)__popcll(__ballot(few));
+                    }
+                    if (lane == 0) { s_rare[wave * 8 + d] = (int32_t)n_rare; s_rare_at[wave * 8 + d] = (int32_t)n_all; }
+                    n_all += n_rare;
+                    most = max(most, n_rare);
+                }
+                int32_t at = 0;   // the wave's place among the rows' entries; any will do
+                if (lane == 0) at = atomicAdd(&s_rare_end[part], (int32_t)n_all);
+                at = ap_uniform_i32(at);
+                const int32_t wave_at = at;
+#pragma unroll
+                for (int d = 0; d < 8; d++)
+#pragma unroll
+                    for (int k = 0; k < AP_GL_SLOTS; k++) {
+                        const uint32_t e = ent[d][k].x;
+                        const bool few = e != 0xffffffffu && e >= 0x80000000u;
+                        const uint64_t m = __ballot(few);
+                        if (few) rare[at + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = make_uint2(e & 0x7fffffffu, ent[d][k].y);
+                        at += __popcll(m);
+                    }
+                for (int32_t i = tid * 4; i < 128 * 127 / 2; i += 4096) *reinterpret_cast<float4 *>(tri + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+                __syncthreads();
+                {
+                    const int32_t i = wave * 8 + (lane >> 3), n_own = s_rare[i];
+                    const uint2 *mine = rare + wave_at + s_rare_at[i];
+                    float *ti = tri + i * (i - 1) / 2;
+                    for (int32_t e0 = 0; e0 < (int32_t)most; e0 += AP_GL_U) {
+                        uint2 e[AP_GL_U], y[AP_GL_U];
+#pragma unroll
+                        for (int o = 0; o < AP_GL_U; o++) e[o] = e0 + o < n_own ? mine[e0 + o] : make_uint2(0u, 0u);
+#pragma unroll
+                        for (int o = 0; o < AP_GL_U; o++) y[o] = (uint32_t)(lane & 7) < e[o].x >> 13 ? hold[(e[o].x & 0x1fffu) + (lane & 7)] : make_uint2(128u, 0u);
+#pragma unroll
+                        for (int o = 0; o < AP_GL_U; o++) {
+                            if ((int32_t)y[o].x < i) ti[y[o].x] = fmaf(__uint_as_float(e[o].y), __uint_as_float(y[o].y), ti[y[o].x]);
+                            ap_wave_sync();   // the next entry may add to the same sums by other lanes
+                        }
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int a = 0; a < 3; a++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        const int32_t i = bi[a] * 16 + 4 * (lane >> 4) + r, j = bj[a] * 16 + (lane & 15);
+                        const float v = wave + 16 * a < n_tasks && j < i ? tri[i * (i - 1) / 2 + j] : 0.f;
+                        if (part) acc[1][a][r] = v; else acc[0][a][r] = v;
+                    }
+                __syncthreads();   // the stages are written next
+            } else {
+#pragma unroll
+                for (int d = 0; d < 8; d++)
+#pragma unroll
+                    for (int k = 0; k < AP_GL_SLOTS; k++)
+                        if (ent[d][k].x != 0xffffffffu) ent[d][k].x &= 0xffffu;
+            }
+        }
+        uint32_t used = 0;   // uniform: slots that hold a column of the matrix at all
+#pragma unroll
+        for (int d = 0; d < 8; d++)
+#pragma unroll
+            for (int k = 0; k < AP_GL_SLOTS; k++) used |= __ballot(ent[d][k].x < 0x80000000u) ? 1u << (d * AP_GL_SLOTS + k) : 0u;
+        const int32_t n_chunks = (n_cols + AP_GL_C - 1) / AP_GL_C;
         auto scatter = [&](int32_t c) {
             float *rows = X + (c & 1) * 128 * AP_GL_STRIDE + wave * 8 * AP_GL_STRIDE;
             for (int32_t i = lane * 4; i < 8 * AP_GL_STRIDE; i += 256) *reinterpret_cast<float4 *>(rows + i) = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1628,21 +1766,36 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
     }
     // element r of a lane's four: row 4 (l / 16) + r, column l % 16 of its block
     float *out = pm + x * (int64_t)K * K;
+    float dense[3][4];
 #pragma unroll
     for (int a = 0; a < 3; a++) {
         if (wave + 16 * a >= n_tasks) continue;
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
+        for (int r = 0; r < 4; r++) {   // all of a lane's dense parts are on their way before the first is used
             const int32_t i = bi[a] * 16 + 4 * (lane >> 4) + r, j = bj[a] * 16 + (lane & 15);
+            dense[a][r] = out[(int64_t)min(i, K - 1) * K + min(j, K - 1)];
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        if (wave + 16 * a >= n_tasks) continue;
+        float four[4];
+        const int32_t i0 = bi[a] * 16 + 4 * (lane >> 4), j = bj[a] * 16 + (lane & 15);
+        const bool whole = bi[a] != bj[a] && K % 4 == 0 && ((uintptr_t)pm & 15) == 0;   // uniform: the mirrored four in one store
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int32_t i = i0 + r;
             if (i >= K || j > i) continue;
             float val = -INFINITY;
             if (s_id[i] >= 0 && s_id[j] >= 0) {
                 const float qs = i == j ? s_diag[0][i] : acc[0][a][r], qt = i == j ? s_diag[1][i] : acc[1][a][r];
-                val = fmaf(wd, out[(int64_t)i * K + j], fmaf(wf, qt, ws * qs));
+                val = fmaf(wd, dense[a][r], fmaf(wf, qt, ws * qs));
             }
             out[(int64_t)i * K + j] = val;
-            out[(int64_t)j * K + i] = val;
+            if (!whole) out[(int64_t)j * K + i] = val;
+            four[r] = val;
         }
+        if (whole && i0 < K) *reinterpret_cast<float4 *>(out + (int64_t)j * K + i0) = make_float4(four[0], four[1], four[2], four[3]);
     }
 }
 
