@@ -1290,7 +1290,12 @@ extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t
 }
 
 // =================================================================== S4: neighbourhood similarities
-// Dense part: G = X X^T for the K gathered rows of one neighbourhood (MFMA).
+// Dense part: G = X X^T for the K gathered rows of one neighbourhood (MFMA); what follows reads the lower triangle only.
+// A tile on the diagonal has the same rows on both sides, which are loaded and staged once, and takes the ten of its sixteen
+// 32 x 32 blocks that reach the triangle: three, two, two and three a wave, the roles going round with the node so that
+// the SIMDs of a CU get the same work.  Same products in the same order as the full tile, so the same bits.  Bound by the matrix units for
+// f32 rows and by the gather of the rows for bf16: 22.3 -> 17.3 ms for 100,000 documents of 768 f32 columns, 10.7 -> 9.5 ms for 200,000
+// of 1,024 bf16 columns.
 template <int DT>
 __global__ __launch_bounds__(256) void k_gram_dense(const void *dense, int32_t dim, int32_t K, const int32_t *__restrict__ knn,
                                                     const int32_t *__restrict__ node_ids, int64_t x0,
@@ -1301,16 +1306,107 @@ __global__ __launch_bounds__(256) void k_gram_dense(const void *dense, int32_t d
     const int64_t u = node_ids ? (int64_t)node_ids[x0 + x] : x0 + x;
     const int32_t tiles = (K + AP_TILE - 1) / AP_TILE;
     const int32_t i0 = (blockIdx.x / tiles) * AP_TILE, j0 = (blockIdx.x % tiles) * AP_TILE;
+    if (j0 > i0) return;   // uniform: above the triangle
     if (threadIdx.x < AP_TILE) {
         a_rows[threadIdx.x] = i0 + threadIdx.x < K ? knn[u * K + i0 + threadIdx.x] : -1;
         b_rows[threadIdx.x] = j0 + threadIdx.x < K ? knn[u * K + j0 + threadIdx.x] : -1;
     }
     ap_f32x16 acc[2][2];
-    ap_tile_product<DT>(dense, dim, a_rows, b_rows, lds, acc);
     float *out = pm + x * (int64_t)K * K;
-    ap_tile_foreach(acc, [&](int i, int j, float v) {
-        if (i0 + i < K && j0 + j < K) out[(int64_t)(i0 + i) * K + (j0 + j)] = v;
-    });
+    if (i0 != j0) {
+        ap_tile_product<DT>(dense, dim, a_rows, b_rows, lds, acc);
+        ap_tile_foreach(acc, [&](int i, int j, float v) {
+            if (i0 + i < K && j0 + j < K) out[(int64_t)(i0 + i) * K + (j0 + j)] = v;
+        });
+        return;
+    }
+    const int lane = threadIdx.x & 63, li = lane & 31, half = lane >> 5;
+    const int role = (ap_wave_id() + (int)(x & 3)) & 3;   // uniform
+    // roles 0 and 3: blocks (r, r), (r + 1, r), (r + 1, r + 1) of r = 0, 2; roles 1 and 2: (2, 0), (2, 1) and (3, 0), (3, 1)
+    const bool corner = role == 0 || role == 3;
+    const int r0 = corner ? (role ? 2 : 0) : role + 1, c0 = role == 3 ? 2 : 0;
+    const bool any = i0 + r0 * 32 < K;
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[a][b][r] = 0.f;
+    __syncthreads();   // the row list
+    if constexpr (DT == AP_F32) {
+        float *lA = reinterpret_cast<float *>(lds);
+        float4 va[4];
+        int32_t ra[4];
+#pragma unroll
+        for (int pass = 0; pass < 4; pass++) ra[pass] = a_rows[(threadIdx.x >> 3) + 32 * pass];
+        ap_tile_load<DT>(dense, dim, ra, 0, va);
+        for (int32_t k0 = 0; k0 < dim; k0 += AP_BK) {
+            __syncthreads();
+            ap_tile_store(va, ra, dim, k0, lA);
+            __syncthreads();
+            if (k0 + AP_BK < dim) ap_tile_load<DT>(dense, dim, ra, k0 + AP_BK, va);
+            const float *pa = lA + (r0 * 32 + li) * AP_LDS_STRIDE + half, *pb = lA + (c0 * 32 + li) * AP_LDS_STRIDE + half;
+            const float *pc = lA + ((corner ? r0 + 1 : c0 + 1) * 32 + li) * AP_LDS_STRIDE + half;
+            if (!any) continue;
+            if (corner) {
+#pragma unroll
+                for (int kk = 0; kk < AP_BK; kk += 2) {
+                    const float a0 = pa[kk], a1 = pc[kk];
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, a0, acc[0][0], 0, 0, 0);
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, a0, acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, a1, acc[1][1], 0, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int kk = 0; kk < AP_BK; kk += 2) {
+                    const float a0 = pa[kk], b0 = pb[kk], b1 = pc[kk];
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
+                    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
+                }
+            }
+        }
+    } else {
+        uint16_t *lA = reinterpret_cast<uint16_t *>(lds);
+        uint4 va[AP_NP16];
+        int32_t ra[AP_NP16];
+#pragma unroll
+        for (int pass = 0; pass < AP_NP16; pass++) ra[pass] = a_rows[threadIdx.x / AP_TPR16 + AP_RPP16 * pass];
+        ap_tile_load_bf16(dense, dim, ra, 0, va);
+        for (int32_t k0 = 0; k0 < dim; k0 += AP_BK16) {
+            __syncthreads();
+            ap_tile_store_bf16(va, ra, dim, k0, lA);
+            __syncthreads();
+            if (k0 + AP_BK16 < dim) ap_tile_load_bf16(dense, dim, ra, k0 + AP_BK16, va);
+            const uint16_t *pa = lA + (r0 * 32 + li) * AP_LDS_STRIDE16 + half * 8, *pb = lA + (c0 * 32 + li) * AP_LDS_STRIDE16 + half * 8;
+            const uint16_t *pc = lA + ((corner ? r0 + 1 : c0 + 1) * 32 + li) * AP_LDS_STRIDE16 + half * 8;
+            if (!any) continue;
+#pragma unroll
+            for (int kk = 0; kk < AP_BK16; kk += 16) {
+                const ap_bf16x8 a0 = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(pa + kk));
+                const ap_bf16x8 c1 = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(pc + kk));
+                if (corner) {
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, a0, acc[0][0], 0, 0, 0);
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1, a0, acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1, c1, acc[1][1], 0, 0, 0);
+                } else {
+                    const ap_bf16x8 b0 = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(pb + kk));
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
+                    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, c1, acc[0][1], 0, 0, 0);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+            if (corner ? (a == 0 && b == 1) : a == 1) continue;   // uniform: not this role's
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int i = i0 + (r0 + a) * 32 + 8 * (r >> 2) + 4 * half + (r & 3), j = j0 + (c0 + b) * 32 + li;
+                if (i < K && j <= i) out[(int64_t)i * K + j] = acc[a][b][r];
+            }
+        }
 }
 
 // Sparse and lexical parts of the neighbourhood similarities, and the fusion with the dense part: sorted lists are
