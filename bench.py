@@ -301,13 +301,14 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
     # rounds (every candidate's record, and the dense rows its bound calls for: HBM), the neighbourhood phase (pair similarities per second)
     K = bp.knn_k
     seed_flops = float(ix.build_counters()["seed_flops"]) or 2.0 * N * N * w.docs.dim   # what the stage's MFMA products executed
+    seed_bf16 = bf16 or N >= 16384   # f32 rows of a larger corpus are swept rounded to bf16
     seed_tflops = seed_flops / max(bt["seed"], 1e-9) / 1e12
     # a lower bound of what the rounds read: every candidate's record, and the dense rows of the K documents a node's first
     # round sets its threshold with
     refine_gbs = (refine_sims * partial_bytes + (N * K * dense_bytes if args.rounds else 0)) / max(bt["refine"], 1e-9) / 1e9
     build_roofline = dict(
-        seed=dict(bound="mfma", achieved=round(seed_tflops, 1), peak=MFMA_PEAK_TFLOPS[bf16], unit="TFLOP/s",
-                  frac=round(seed_tflops / MFMA_PEAK_TFLOPS[bf16], 4), flops=seed_flops,
+        seed=dict(bound="mfma", achieved=round(seed_tflops, 1), peak=MFMA_PEAK_TFLOPS[seed_bf16], unit="TFLOP/s",
+                  frac=round(seed_tflops / MFMA_PEAK_TFLOPS[seed_bf16], 4), flops=seed_flops,
                   full_product_flops=2.0 * N * N * w.docs.dim,
                   full_product_equivalent_TFLOPs=round(2.0 * N * N * w.docs.dim / max(bt["seed"], 1e-9) / 1e12, 1),
                   note="FLOPs the stage's dense products executed (sampled columns + sweep, padded tiles included; bf16 rows: only the "
