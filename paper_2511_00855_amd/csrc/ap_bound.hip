@@ -526,6 +526,7 @@ static int64_t bound_slab(const ap_index *ix, int64_t nq, size_t cap, int tables
 // Sizes the workspace of stream st for slabs of as many of nq queries as `cap` bytes hold, and holds it for the caller
 // (two threads may search on one stream).  A workspace that has to grow takes a quarter of the free memory at most, and
 // smaller slabs then, but of `least` queries at least (fewer than a launch keeps in flight cost more than the bounds save).
+// `cap` may ask for slabs smaller than that, unless `least` is AP_BOUND_WHOLE: then it is all nq queries in one slab or no bounds.
 // b->table stays NULL where no such workspace is to be had: the caller goes without bounds.  That is also what a captured
 // search does: a graph's replays must not depend on a workspace that a later call may replace.
 int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, int tables, hipStream_t st, ApBound *b) {
@@ -535,7 +536,7 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, 
     if (cs != hipStreamCaptureStatusNone) return AP_OK;
     if (g_ap_debug.search_bounds_bytes > 0) cap = std::min(cap, (size_t)g_ap_debug.search_bounds_bytes);
     int64_t slab = bound_slab(ix, nq, cap, tables);
-    if (slab == 0) return AP_OK;
+    if (slab == 0 || (least == AP_BOUND_WHOLE && slab < nq)) return AP_OK;
     least = std::min(least, slab);
     ApBoundPool *pool = ix->bd_pool;
     std::unique_lock<std::mutex> hold(pool->lock);
@@ -636,8 +637,8 @@ extern "C" int ap_stage_score_bounds(ap_index *ix, const ap_queries *q, const fl
     hipStream_t st = (hipStream_t)stream;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApBound b;
-    AP_TRY(ap_bound_reserve(ix, q->nq, q->nq, AP_BOUND_WS_BYTES, 1, st, &b));
-    if (!b.table || b.slab != q->nq) { ap_set_error("no bounds for this index and batch"); return AP_ESTATE; }
+    AP_TRY(ap_bound_reserve(ix, q->nq, AP_BOUND_WHOLE, AP_BOUND_WS_BYTES, 1, st, &b));
+    if (!b.table) { ap_set_error("no bounds for this index and batch"); return AP_ESTATE; }
     AP_TRY(ap_bound_fill(ix, b, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, 0, q->nq, kw_terms, kw_stride, st));
     AP_CHECK_HIP(hipMemcpy2DAsync(out, (size_t)ix->docs.n * 4, b.table, (size_t)b.ld * 4, (size_t)ix->docs.n * 4, (size_t)q->nq, hipMemcpyDeviceToDevice, st));
     return AP_OK;

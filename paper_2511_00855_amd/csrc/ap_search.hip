@@ -775,7 +775,7 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     // The bounds come last, and what the search cannot do without is sized as if there were none: they never take the memory
     // of a search that used to fit, and the same batch can run without them afterwards (captured, say) and allocate nothing.
     if (plan.mode != 0 && ws->slab == nq) {   // a small batch, as a whole or not at all
-        AP_TRY(ap_bound_reserve(ix, nq, nq, AP_BOUND_WS_BYTES, plan.mode == 1 ? 2 : 1, st, &ws->bound));
+        AP_TRY(ap_bound_reserve(ix, nq, AP_BOUND_WHOLE, AP_BOUND_WS_BYTES, plan.mode == 1 ? 2 : 1, st, &ws->bound));
         if (ws->bound.table) {
             ws->walk.bound = plan.mode == 1 ? ws->bound.table : nullptr;
             ws->walk.exact = plan.mode == 1 ? ws->bound.second : ws->bound.table;

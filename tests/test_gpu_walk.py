@@ -96,3 +96,21 @@ def test_noalloc_walk(debug_knobs):
             torch.cuda.synchronize()
             assert all(torch.equal(a, b) for a, b in zip(ref, out))
     ix.close()
+
+
+@pytest.mark.parametrize("queries_that_fit", [1, 20, 40])
+def test_a_workspace_smaller_than_the_batch(debug_knobs, queries_that_fit):
+    """The walk takes a batch as a whole: where its rows of bounds and scores may not be had for all queries, the batch is searched
+    as any other, in slabs of as many queries as the workspace holds."""
+    w = make_workload("tiny", seed=3, n=1500, nq=41)
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
+    calls = [(10, 96, 1), (10, 300, 4)]
+    debug_knobs("search_walk", 1)
+    want = _searches(ix, qs, None, calls)
+    # 256 queries' rows of at most 128 + 512 columns and what goes with them, one row of bounds a query
+    debug_knobs("search_bounds_bytes", 256 * (2 * (128 + 512) + 52) + queries_that_fit * 4 * 1536)
+    for mode in (2, 3, 0):
+        debug_knobs("search_walk", mode)
+        assert all(torch.equal(a, b) for a, b in zip(want, _searches(ix, qs, None, calls))), mode
+    ix.close()
