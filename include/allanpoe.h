@@ -333,7 +333,9 @@ int ap_import_graph(const ap_corpus *corpus, const ap_build_params *params, cons
  * search).  out_counts (device, may be NULL): nq x 3 int32 = per query the
  * number of candidates scored, the number of iterations, and the number of
  * scored candidates whose dense row was not read (their sparse + lexical parts
- * plus the largest possible dense part could not reach the pool).
+ * plus the largest possible dense part could not reach the pool).  A small batch
+ * scores documents before it walks the graph: the rows of those have been read,
+ * whether or not they reach the pool.
  * kernel_ms (host, may be NULL): duration of the search kernel alone, measured
  * with events on the stream it ran on. */
 int ap_search_stats(const ap_index *index, int32_t *out_counts, int32_t nq, float *kernel_ms, void *stream);

@@ -230,7 +230,7 @@ struct ApWalkLds {
     uint4 *meta;          // candidates to score
     uint64_t *newk, *cur; // their keys; the pool
     uint64_t *list, *done; // the lanes' lists; the expanded documents
-    int32_t *c, *full, *skip, *par;
+    int32_t *c, *full, *par;
     float *worst;
 };
 // All waves of the workgroup meet; what any wrote before is seen by all afterwards.
@@ -262,7 +262,7 @@ __device__ __forceinline__ bool ap_walk_lists(const ApWalkArgs &g, int64_t q, co
     const float t0 = line[0], t1 = line[1], t2 = line[2], t3 = line[3];
     float cut = -INFINITY;
     int32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;     // documents met at or above the lines
-    int32_t it = 0, nscored = 0, nwait = 0, nout = 0, n = 0;
+    int32_t it = 0, nscored = 0, nwait = 0, n = 0;
     bool bad = false;
     // per lane
     uint64_t head = 0ull;   // the best unexpanded document of the list, 0: none
@@ -284,7 +284,6 @@ __device__ __forceinline__ bool ap_walk_lists(const ApWalkArgs &g, int64_t q, co
         const int32_t m = (int32_t)__popcll(__ballot(on));
         nscored += m;
         if constexpr (!ALL) nwait += m - (int32_t)__popcll(__ballot(known));
-        nout += m - (int32_t)__popcll(__ballot(has));
         if (c3 < g.L) {   // uniform
             c0 += (int32_t)__popcll(__ballot(known && x >= t0));
             c1 += (int32_t)__popcll(__ballot(known && x >= t1));
@@ -432,7 +431,7 @@ __device__ __forceinline__ bool ap_walk_lists(const ApWalkArgs &g, int64_t q, co
     }
     n_done = n;
     if (bad || n >= g.done_cap || !sure()) return false;
-    if (lane == 0 && g.counts) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = nout; }
+    if (lane == 0 && g.counts) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = nwait; }   // the rows of what waits were not read
     return true;
 }
 
@@ -445,7 +444,7 @@ __device__ __forceinline__ void ap_walk_sorted(const ApWalkArgs &g, int64_t q, c
     const uint32_t *bound = ALL ? nullptr : g.bound + q * g.ld;
     const float *exact = g.exact + q * g.ld;
     // uniform
-    int32_t len = 0, fu = 0, it = 0, nscored = 0, ndropped = 0, cnt = 0;   // fu: every entry of the pool before it has been expanded
+    int32_t len = 0, fu = 0, it = 0, nscored = 0, nunread = 0, cnt = 0;   // fu: every entry of the pool before it has been expanded
     uint64_t worst = 0ull;      // the pool's last key while it is full, else 0: a key has to rank before it
     // Puts the keys of the lanes that hold one (each ranks before `worst`) into the pool.  The pool's entries are read in
     // chunks from the back; every entering key is compared with all of them at once, which gives the key its rank (a
@@ -512,11 +511,10 @@ __device__ __forceinline__ void ap_walk_sorted(const ApWalkArgs &g, int64_t q, c
         key = ap_make_key(x, v < 0 ? 0 : v, 1u);
         const bool has = known && key > worst;
         const bool ask = on && !known && !(full && __uint_as_float(e & ~AP_BOUND_COUNT) < ap_key_score(worst));
-        const uint64_t in = __ballot(on), in2 = __ballot(has || ask);
-        nscored += (int32_t)__popcll(in);
-        if (full) ndropped += (int32_t)__popcll(in) - (int32_t)__popcll(in2);
+        nscored += (int32_t)__popcll(__ballot(on));
         if constexpr (!ALL) {
             const uint64_t am = __ballot(ask);
+            nunread += (int32_t)__popcll(__ballot(on && !known && !ask));
             if (am) {
                 if (ask) {
                     const uint4 m = g.meta[v];
@@ -599,7 +597,7 @@ __device__ __forceinline__ void ap_walk_sorted(const ApWalkArgs &g, int64_t q, c
         it++;
         help();
     }
-    if (lane == 0 && g.counts) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = *l.skip + ndropped; }
+    if (lane == 0 && g.counts) { g.counts[q * 3] = nscored; g.counts[q * 3 + 1] = it; g.counts[q * 3 + 2] = nunread; }
     // S9: the best k entries that are not mark-deleted
     int32_t o = 0;
     for (int32_t base = 0; base < len && o < g.k; base += 64) {
@@ -691,7 +689,7 @@ template <int DT, int NV, bool ALL>
 __global__ __launch_bounds__(AP_WALK_NT) void k_walk_rest(ApWalkArgs g) {
     extern __shared__ __attribute__((aligned(16))) uint64_t walk_lds[];
     __shared__ __attribute__((aligned(16))) uint64_t qtab[ApQTab<false>::SLOTS];
-    __shared__ int32_t s_seed[2], s_c, s_full, s_skip, s_par[16];
+    __shared__ int32_t s_seed[2], s_c, s_full, s_par[16];
     __shared__ float s_worst;
     const int64_t q = blockIdx.x;
     if (g.undecided[q] == 0) return;   // uniform
@@ -699,10 +697,10 @@ __global__ __launch_bounds__(AP_WALK_NT) void k_walk_rest(ApWalkArgs g) {
     l.meta = reinterpret_cast<uint4 *>(walk_lds);
     l.newk = reinterpret_cast<uint64_t *>(l.meta + g.cmax);
     l.cur = l.newk + g.cmax;
-    l.c = &s_c; l.full = &s_full; l.skip = &s_skip; l.par = s_par; l.worst = &s_worst;
+    l.c = &s_c; l.full = &s_full; l.par = s_par; l.worst = &s_worst;
     const ApVisited vis = ap_walk_visited(g, q, walk_lds, g.vis_lds);
     if (!g.vis_lds) for (size_t i = threadIdx.x; i < g.words; i += AP_WALK_NT) vis.g[i] = 0u;
-    if (threadIdx.x == 0) { s_c = 0; s_skip = 0; }
+    if (threadIdx.x == 0) s_c = 0;
     ApWalkQuery<DT, NV> Q;
     Q.load(g, q, qtab, s_seed);
     __threadfence_block();
@@ -717,8 +715,7 @@ __global__ __launch_bounds__(AP_WALK_NT) void k_walk_rest(ApWalkArgs g) {
         ap_walk_meet();
         const int32_t c = ap_uniform_i32(s_c);
         if (c < 0) break;
-        const int32_t skipped = Q.template score<AP_WALK_NT / 64 - 1, 2, 1>(g, qtab, l.meta, c, l.newk, s_full != 0, s_worst, s_full != 0);
-        if ((threadIdx.x & 63) == 0 && skipped) atomicAdd(&s_skip, skipped);
+        (void)Q.template score<AP_WALK_NT / 64 - 1, 2, 1>(g, qtab, l.meta, c, l.newk, s_full != 0, s_worst, s_full != 0);   // rows requested along with the records
         ap_walk_meet();
     }
 }

@@ -114,3 +114,23 @@ def test_a_workspace_smaller_than_the_batch(debug_knobs, queries_that_fit):
         debug_knobs("search_walk", mode)
         assert all(torch.equal(a, b) for a, b in zip(want, _searches(ix, qs, None, calls))), mode
     ix.close()
+
+
+def test_counts_of_rows_not_read(debug_knobs):
+    """The third counter of a search: scored documents whose dense row was not read.  None where all rows are read ahead; what is
+    in the pool has been scored out of its row, whichever documents were scored ahead."""
+    n, nq = 6007, 25
+    w = make_workload("tiny", seed=11, n=n, nq=nq, dim=64, vocab=5_000)
+    rng = np.random.default_rng(6)
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    ix = B.Index.import_graph(docs, B.build_params(64, n_entry=16), rng.integers(-1, n, (n, 64)).astype(np.int32),
+                              rng.permutation(n)[:16].astype(np.int32))
+    pw = rng.uniform(0.1, 1.0, (nq, 3)).astype(np.float32)
+    for k, beam, width in ((10, 64, 1), (10, 64, 2), (10, 700, 16), (100, 1300, 1)):
+        for mode in (1, 2, 3):
+            debug_knobs("search_walk", mode)
+            ix.search_batch(qs, k, beam, pw, search_width=width)
+            c = ix.search_stats(nq)[0]
+            assert ((c[:, 2] >= 0) & (c[:, 0] - c[:, 2] >= c[:, 0].clamp(max=beam))).all(), (mode, beam)
+            assert (c[:, 2] == 0).all() if mode == 3 else (c[:, 2] > 0).any(), (mode, beam)
+    ix.close()
