@@ -1571,8 +1571,10 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
 // The lower triangle of the result is 36 blocks of 16 x 16 (K = 128): two a wave and four more on the first four waves, nine
 // on every SIMD.  A neighbourhood with a list beyond the registers, or more columns or entries than the LDS holds, takes all of its
 // columns to the matrix, and so does one with AP_GL_SPLIT columns or fewer: the steps before the first product take some
-// 50,000 cycles a vocabulary, a chunk of the matrix 8,000 (2,000 documents of 64 neighbours and some 250 columns: 2.85 ms a construction
-// with its columns set apart, 2.67 ms without).  The prune stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all
+// 50,000 cycles a vocabulary, a chunk of the matrix 8,000.
+// Both vocabularies are written out: with one body for the two the accumulators are chosen by the vocabulary at run time, and 64 registers
+// spill (prune stage of 6,000 documents of 128 columns, K = 32, lists of 20 and 13 terms: 1.21 and 0.95 ms; K = 128, lists of 50 and 30:
+// 3.67 and 2.98).  The prune stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all
 // columns in the matrix, 41 ms here; 200,000 bf16: 299, 109 and 76 ms.  Of a workgroup's 260,000 cycles the pairs take 55,000, the
 // matrix 60,000, marking, numbering and counting the columns 110,000: chains of LDS round trips that 16 waves do not hide.
 #define AP_GL_WORDS 8192          // words of a bitmap: vocabularies up to 2^18 terms
@@ -1626,6 +1628,7 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
 #pragma unroll
         for (int a = 0; a < 3; a++) acc[part][a] = ap_f32x4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
+#pragma unroll
     for (int part = 0; part < 2; part++) {
         const int32_t words = part ? tx_words : sp_words;
         for (int32_t i = tid * 4; i < words; i += 4096) {   // words is a multiple of 4
