@@ -1570,11 +1570,12 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
 //    while the other stage is multiplied: one barrier a chunk.
 // The lower triangle of the result is 36 blocks of 16 x 16 (K = 128): two a wave and four more on the first four waves, nine
 // on every SIMD.  A neighbourhood with a list beyond the registers, or more columns or entries than the LDS holds, takes all of its
-// columns to the matrix, and so does one with AP_GL_SPLIT columns or fewer: the steps before the first product take some
-// 50,000 cycles a vocabulary, a chunk of the matrix 8,000.
+// columns to the matrix, and so does one with AP_GL_SPLIT(K) columns or fewer: setting them apart takes the same steps for any K, a chunk
+// of the matrix the less the fewer blocks there are.  Prune stage of 6,000 documents of 128 columns with all columns in the matrix and
+// with those apart, ms: K = 128, 650 columns 3.37 and 2.98, 1,800: 5.67 and 3.90; K = 64, 490: 1.89 and 1.92, 640: 2.06 and 2.01,
+// 960: 2.48 and 2.28; K = 48, 500: 1.47 and 1.51, 730: 1.75 and 1.74; K = 32, 500: 1.34 and 1.44.
 // Both vocabularies are written out: with one body for the two the accumulators are chosen by the vocabulary at run time, and 64 registers
-// spill (prune stage of 6,000 documents of 128 columns, K = 32, lists of 20 and 13 terms: 1.21 and 0.95 ms; K = 128, lists of 50 and 30:
-// 3.67 and 2.98).  The prune stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all
+// spill (K = 32, lists of 20 and 13 terms, nothing set apart: 1.21 and 0.95 ms; K = 128 above: 3.67 and 2.98, 4.72 and 3.90).  The prune stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all
 // columns in the matrix, 41 ms here; 200,000 bf16: 299, 109 and 76 ms.  Of a workgroup's 260,000 cycles the pairs take 55,000, the
 // matrix 60,000, marking, numbering and counting the columns 110,000: chains of LDS round trips that 16 waves do not hide.
 #define AP_GL_WORDS 8192          // words of a bitmap: vocabularies up to 2^18 terms
@@ -1582,7 +1583,7 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
 #define AP_GL_STRIDE (AP_GL_C + 4)   // rows 16-byte aligned; 16 rows x 4 groups of 4 columns fall into distinct banks
 #define AP_GL_SLOTS 3             // list entries a lane holds in registers
 #define AP_GL_FEW 8               // holders of a column whose pairs are added one by one
-#define AP_GL_SPLIT 512            // columns beyond which setting those with few holders apart pays
+#define AP_GL_SPLIT(K) ((K) < 64 ? 32768 / (K) : 512)   // columns beyond which setting those with few holders apart pays
 #define AP_GL_COLS 4096           // columns whose holders are counted (16 KB where the bitmaps were)
 #define AP_GL_HOLD 6144           // entries of the columns with few holders (48 KB behind them, 48 KB behind the triangle)
 #define AP_GL_U 4                 // entries of a row on their way at a time
@@ -1705,7 +1706,7 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
         uint32_t longs = 0;   // uniform: documents of this wave whose list goes on behind the registers
         for (int d = 0; d < 8; d++) longs |= ap_uniform_i32(part ? s_tn[wave * 8 + d] : s_sn[wave * 8 + d]) > 64 * AP_GL_SLOTS ? 1u << d : 0u;
         int32_t n_cols = (int32_t)ap_uniform_u32(s_total);   // columns of the matrix
-        if (!__syncthreads_or(longs != 0) && n_cols > AP_GL_SPLIT && n_cols <= AP_GL_COLS) {   // uniform; nobody asks the bitmaps any more
+        if (!__syncthreads_or(longs != 0) && n_cols > AP_GL_SPLIT(K) && n_cols <= AP_GL_COLS) {   // uniform; nobody asks the bitmaps any more
             *reinterpret_cast<uint4 *>(col_map + tid * 4) = make_uint4(0, 0, 0, 0);
             __syncthreads();
             // an entry: column | place among its column's holders << 16

@@ -42,3 +42,36 @@ def test_pairs_and_matrix_against_64_bits(K, width, terms):
         want, got = Y @ Y.T, pm[r].double().cpu()
         # sums of at most `width` products that are not negative: each addition and product rounds by 2^-24 of the sum at most
         assert ((got - want).abs() <= (width + 4) * 2.0 ** -24 * want).all()
+
+
+# both sides of the number of columns from which those with few holders are set apart, which depends on K; the second vocabulary alone,
+# and both in one workgroup
+@pytest.mark.parametrize("K,sp,tx,terms,weights", [
+    (32, 100, 4, 1900, (0, 1, 0)), (32, 190, 4, 3000, (0, 1, 0)), (48, 50, 4, 900, (0, 1, 0)), (48, 100, 4, 1900, (0, 1, 0)),
+    (128, 4, 50, 1500, (0, 0, 1)), (128, 4, 190, 4000, (0, 0, 1)), (128, 50, 50, 1500, (0, 0.5, 0.5)), (128, 60, 50, 1500, (0, 0.5, 0.5)),
+    (128, 50, 2, 1500, (0, 0.5, 0.5)), (64, 100, 100, 2500, (0, 0.25, 1))])
+def test_both_vocabularies_against_64_bits(K, sp, tx, terms, weights):
+    n = 300
+    w = make_workload("tiny", seed=K + sp, n=n, nq=2, dim=64, vocab=16384, sp=("fixed", 4), tx=("fixed", 4))
+    rng = np.random.default_rng(sp + tx)
+    d = w.docs
+    d.sp_indptr, d.sp_idx = _uniform_lists(rng, n, sp, terms)
+    d.sp_val = np.abs(rng.standard_normal(len(d.sp_idx))).astype(np.float32)
+    d.tx_indptr, d.tx_idx = _uniform_lists(rng, n, tx, terms)
+    d.tx_val = rng.integers(1, 5, len(d.tx_idx)).astype(np.float32)
+    ix = B.Index.ingest(B.DeviceVecs(d), B.build_params(4, knn_k=K, n_entry=4, build_w=weights))
+    ids = np.stack([rng.permutation(np.setdiff1d(np.arange(n), [u]))[:K] for u in range(n)]).astype(np.int32)
+    sc = -np.sort(-rng.random((n, K)).astype(np.float32), axis=1)
+    sub = np.arange(0, n, 23).astype(np.int32)
+    pm = ix.stage_prune(K, 4, ids, sc, sub)["pm"]
+    assert torch.equal(pm, ix.stage_prune(K, 4, ids, sc, sub)["pm"])
+    bm25 = ix.export_ingest()[0].double().cpu()
+    ix.close()
+    X = torch.zeros(n, 2 * terms, dtype=torch.float64)
+    X[np.repeat(np.arange(n), sp), d.sp_idx] = torch.from_numpy(d.sp_val.astype(np.float64)) * np.sqrt(weights[1])
+    X[np.repeat(np.arange(n), tx), terms + d.tx_idx] = bm25 * np.sqrt(weights[2])
+    for r, u in enumerate(sub):
+        Y = X[ids[u]]
+        want, got = Y @ Y.T, pm[r].double().cpu()
+        # as above, and two roundings of the fusion
+        assert ((got - want).abs() <= (max(sp, tx) + 6) * 2.0 ** -24 * want).all()
