@@ -368,6 +368,10 @@ __global__ __launch_bounds__(256) void k_seed_round(const float *__restrict__ de
 // bytes), through its own part of the LDS, the next chunk's loads in flight while one is summed: 15.2 ms for 100,000 rows of 768 columns
 // and K = 128 (some 71 GB at 4.7 TB/s).
 #define AP_BAND 1024
+__device__ __forceinline__ float ap_seed_slack(float2 a, const uint32_t *stats, int32_t dim) {
+    const float nmax = __uint_as_float(stats[0]), emax = __uint_as_float(stats[1]);
+    return 1.001f * (a.x * nmax + (a.y + a.x) * emax + (2.4e-7f * (float)(dim + 64)) * a.y * nmax);
+}
 __global__ __launch_bounds__(256) void k_rescore_buf(const float *__restrict__ dense, int32_t dim, const unsigned long long *__restrict__ buf, int32_t cap,
                                                      const int32_t *__restrict__ cnt, const float *__restrict__ tau, const float2 *__restrict__ lost,
                                                      const uint32_t *__restrict__ stats, int32_t K, int32_t *__restrict__ out_ids,
@@ -401,10 +405,7 @@ __global__ __launch_bounds__(256) void k_rescore_buf(const float *__restrict__ d
     for (int32_t x = threadIdx.x * 4; x < 1024; x += 1024)
         *reinterpret_cast<float4 *>(&s_a[x]) = x < dim ? *reinterpret_cast<const float4 *>(dense + r * dim + x) : make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    const float2 a = lost[r];
-    const float nmax = __uint_as_float(stats[0]), emax = __uint_as_float(stats[1]);
-    const float slack = 1.001f * (a.x * nmax + (a.y + a.x) * emax + (2.4e-7f * (float)(dim + 64)) * a.y * nmax);
-    const float least = ap_ord2f(s_least) - 2.f * slack;
+    const float least = ap_ord2f(s_least) - 2.f * ap_seed_slack(lost[r], stats, dim);
     if (least >= tau[r])
         for (int32_t j = threadIdx.x; j < c; j += 256) {
             const uint64_t key = key_of(j);
@@ -464,6 +465,19 @@ __global__ __launch_bounds__(256) void k_rescore_buf(const float *__restrict__ d
     }
 }
 
+// Before the sweep: how many of a sample of rows it would leave open.  sc holds the m best scores of each with the sampled columns, `place`
+// is where the K-th best of all columns is to be expected among them, `last` where the band ends at the latest: at tau, or at AP_BAND candidates.
+__global__ __launch_bounds__(256) void k_seed_open(const float *__restrict__ sc, int32_t nrows, int32_t m, int32_t place, int32_t last,
+                                                   const int32_t *__restrict__ rows, const float2 *__restrict__ lost, const uint32_t *__restrict__ stats,
+                                                   int32_t dim, int32_t *__restrict__ n_open) {
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < nrows && sc[(int64_t)i * m + last] > sc[(int64_t)i * m + place] - 2.f * ap_seed_slack(lost[rows[i]], stats, dim)) atomicAdd(n_open, 1);
+}
+__global__ __launch_bounds__(256) void k_seed_spread(int32_t *__restrict__ rows, int32_t nrows, int64_t n) {
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < nrows) rows[i] = (int32_t)(i * n / nrows);
+}
+
 // Exact path: full score rows of a slab, then selection.  Rows [row0, row0+nrows) of the node list.
 static hipError_t seed_exact_rows(const ap_index *ix, const int32_t *node_ids, int64_t row0, int64_t nrows, int32_t K,
                                   float *scratch, int64_t scratch_rows, int32_t *out_ids, float *out_sc, hipStream_t st) {
@@ -507,7 +521,11 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
 // rounding leaves open are scored in f32 (k_rescore_buf).  The lists are the same bits.  100,000 rows of 768 columns, K = 128: 82.7 ms with
 // f32 products (71 of them the sweep), 29.5 ms rounded (10.4 the sweep); 96 columns: 23.4 and 11.5 ms.
 // *done = false (and AP_OK): not applicable here (shape, memory; rounded: norms that differ too much, or rows too much alike for the
-// rounding to tell them apart); the caller takes the next sweep.
+// rounding to tell them apart, which a sample of rows says before the sweep); the caller takes the next sweep.  Rows with a mean cosine of 0.8,
+// 100,000 x 768, K = 128: 84.5 ms, the f32 sweep alone 83.8, and 100 with the rounded sweep in front of it.
+// Where the line lies: a row left open takes the exact path, 5 us of 100,000 columns and 768 (1 us of 60,000 and 384), so that a tenth of them is
+// what the rounding saves; corpora whose next path is the exact one for all rows (below 32,768 documents) can leave a quarter open.  Once the sweep is over its
+// own time no longer counts, and an eighth (a half) may be open.
 static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, int32_t *out_ids, float *out_sc, hipStream_t st, bool *done) {
     *done = false;
     const bool big = rounded || ix->dtype == AP_BF16;  // bf16 rows: 256x256 tiles; f32 rows: 128x128 tiles
@@ -567,21 +585,44 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
         }
         dense = r16;
     }
-    int rc = ap_dev_alloc(&buf, (size_t)n * (size_t)cap);
-    if (rc != AP_OK) {
-        void *ptrs[] = {r16, lost, stats};
-        for (void *q : ptrs) if (q) (void)hipFree(q);
-    }
-    if (rc != AP_OK) { (void)hipGetLastError(); ap_set_error("%s", ""); return AP_OK; }   // no room for the buffers after all: the one-sided sweep
-    rc = ap_dev_alloc(&scratch, (size_t)RS * (size_t)cs);
-    if (rc == AP_OK) rc = ap_dev_alloc(&tau, (size_t)n);
+    int rc = ap_dev_alloc(&scratch, (size_t)RS * (size_t)cs);
     if (rc == AP_OK) rc = ap_dev_alloc(&tmp_sc, (size_t)RS * (size_t)m);
-    if (rc == AP_OK) rc = ap_dev_alloc(&cnt, (size_t)n);
     if (rc == AP_OK) rc = ap_dev_alloc(&ovf, (size_t)n + 1);
     hipError_t e = hipSuccess;
-    bool alike = false;   // the rounding left too many rows open
+    bool alike = false;   // the rounding leaves too many rows open
     int32_t *re_ids = nullptr; float *re_sc = nullptr, *ex_scratch = nullptr;
-    if (rc == AP_OK) {
+    const int64_t open_part = n < 32768 ? 4 : 10;
+    const bool forced = g_ap_debug.seed_buffer_cap != 0 || g_ap_debug.seed_tau_ulps != 0;
+    if (rc == AP_OK && rounded && !forced) {
+        const int32_t rows = 1024, place = std::max(0, (int32_t)((double)K * (double)cs / (double)n + 0.5) - 1);
+        const int32_t last = std::max(place, (int32_t)std::min<int64_t>(m, (int64_t)AP_BAND * cs / n) - 1);
+        int32_t n_open = 0;
+        rc = ap_fill_u32(ovf, 1, 0u, st);
+        if (rc == AP_OK) {
+            hipLaunchKernelGGL(k_seed_spread, dim3(rows / 256), dim3(256), 0, st, ovf + 1, rows, n);
+            ix->seed_flops += (unsigned long long)((rows / AP_TILE) * (cs / AP_TILE)) * 2ull * AP_TILE * AP_TILE * (unsigned long long)dim;
+            hipLaunchKernelGGL(k_seed_scores<AP_BF16>, dim3(ap_seed_grid(rows / AP_TILE, cs / AP_TILE)), dim3(256), 0, st, dense, dim, n, ovf + 1, (int64_t)0,
+                               (int64_t)rows, (int64_t)0, cs, scratch);
+            hipLaunchKernelGGL(k_select_rows, dim3(rows), dim3(256), 0, st, scratch, cs, (int32_t)m, ovf + 1, (int64_t)0, 1, (int64_t)0, (int32_t *)nullptr, tmp_sc);
+            hipLaunchKernelGGL(k_seed_open, dim3(rows / 256), dim3(256), 0, st, tmp_sc, rows, (int32_t)m, place, last, ovf + 1, lost, stats, ix->docs.dim, ovf);
+            e = hipGetLastError();
+            if (e == hipSuccess) e = hipMemcpyAsync(&n_open, ovf, sizeof(int32_t), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            alike = e == hipSuccess && n_open > rows / open_part;
+            ap_progress("seed lists: rounding leaves %d of %d sampled rows open", (int)n_open, (int)rows);
+        }
+    }
+    if (rc == AP_OK && !alike) rc = ap_dev_alloc(&tau, (size_t)n);
+    if (rc == AP_OK && !alike) rc = ap_dev_alloc(&cnt, (size_t)n);
+    const bool sweep = rc == AP_OK && e == hipSuccess && !alike;
+    if (sweep && ap_dev_alloc(&buf, (size_t)n * (size_t)cap) != AP_OK) {   // no room for the buffers after all: the next sweep
+        void *ptrs[] = {scratch, tau, tmp_sc, cnt, ovf, r16, lost, stats};
+        for (void *q : ptrs) if (q) (void)hipFree(q);
+        (void)hipGetLastError();
+        ap_set_error("%s", "");
+        return AP_OK;
+    }
+    if (sweep) {
         // thresholds of all rows
         for (int64_t row0 = 0; row0 < n && e == hipSuccess; row0 += RS) {
             const int64_t nrows = std::min(RS, n - row0);
@@ -602,7 +643,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
         if (e == hipSuccess) rc = ap_fill_u32(cnt, (size_t)n, 0u, st);
         if (rc == AP_OK) rc = ap_fill_u32(ovf, 1, 0u, st);
     }
-    if (rc == AP_OK && e == hipSuccess) {
+    if (sweep && rc == AP_OK && e == hipSuccess) {
         ap_progress("seed lists: thresholds of %lld rows (rank %lld of %lld sampled columns), buffers of %lld", (long long)n, (long long)m,
                     (long long)cs, (long long)cap);
         // tiles multiplied: those on and above the diagonal, and the ragged last row and column of tiles
@@ -663,7 +704,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
         }
         if (e == hipSuccess) e = hipMemcpyAsync(&n_ovf, ovf, sizeof(int32_t), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e == hipSuccess && rounded && n_ovf > n / 16 && g_ap_debug.seed_buffer_cap == 0 && g_ap_debug.seed_tau_ulps == 0) alike = true;
+        if (e == hipSuccess && rounded && n_ovf > n / (open_part - 2) && !forced) alike = true;
         else if (e == hipSuccess && n_ovf > 0) {   // rows left short or overflowing: the exact path
             ap_progress("seed lists: %d rows redone by the exact path", (int)n_ovf);
             (void)hipFree(buf); buf = nullptr;

@@ -53,3 +53,29 @@ def test_rounded_sweep_gives_the_lists_of_the_f32_products(n, dim, K, kind):
     assert torch.equal(got[0], want[0])
     assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
     assert (f_got == f_want) == (kind in ("giant", "nan")), (f_got, f_want)   # which sweep it was
+
+
+@pytest.mark.parametrize("n,dim,K", [(20001, 100, 64), (33001, 64, 32)])
+def test_rows_much_alike_are_not_swept_twice(n, dim, K):
+    """Rows around one direction, and rows of which one in seven has near duplicates: the same lists, and what the products of the
+    rounded rows may cost beside those of the f32 rows."""
+    rng = np.random.default_rng(n)
+    w = make_workload("tiny", seed=n, n=n, nq=1, dim=dim, sp=("fixed", 2), tx=("fixed", 2))
+    plain = np.ascontiguousarray(w.docs.dense, dtype=np.float32)
+    kd = (dim + 63) // 64 * 64
+    for kind in ("direction", "duplicates"):
+        d = plain.copy()
+        if kind == "direction":
+            d = plain[:1] + 1e-2 * d
+        else:
+            m = n // 7
+            d[rng.permutation(n)[:m]] = plain[rng.integers(0, max(1, m // 300), m)] + 1e-4 * plain[:m]
+        w.docs.dense = np.ascontiguousarray(d)
+        docs = B.DeviceVecs(w.docs)
+        want, f_want = _lists(docs, K, 1)
+        got, f_got = _lists(docs, K, 0)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1].view(torch.int32), want[1].view(torch.int32)), kind
+        if kind == "direction":   # 1,024 rows and at most 8,192 columns
+            assert f_got - f_want <= 2.0 * 1024 * 8192 * kd, (f_got, f_want)
+        else:   # the rounded sweep over the tiles of the upper triangle and what it takes its thresholds from; score rows of half the documents at most
+            assert f_got <= 1.1 * n * n * kd + 2.0 * n * 8192 * kd + 1.1 * n * n * dim, (f_got, f_want)
