@@ -79,3 +79,29 @@ def test_rows_much_alike_are_not_swept_twice(n, dim, K):
             assert f_got - f_want <= 2.0 * 1024 * 8192 * kd, (f_got, f_want)
         else:   # the rounded sweep over the tiles of the upper triangle and what it takes its thresholds from; score rows of half the documents at most
             assert f_got <= 1.1 * n * n * kd + 2.0 * n * 8192 * kd + 1.1 * n * n * dim, (f_got, f_want)
+
+
+def test_little_memory():
+    """The rounded sweep fits what is free, the score rows of the near duplicates that it leaves open do not: the f32 sweep gives
+    the lists, as it would have from the start."""
+    n, dim, K = 40_000, 1024, 32
+    w = make_workload("tiny", seed=5, n=n, nq=1, dim=dim, sp=("fixed", 2), tx=("fixed", 2))
+    rng = np.random.default_rng(5)
+    d = np.array(w.docs.dense, dtype=np.float32)
+    m = n // 20
+    d[rng.permutation(n)[:m]] = d[rng.integers(0, m // 400, m)] + 1e-4 * d[:m]
+    w.docs.dense = d
+    docs = B.DeviceVecs(w.docs)
+    want, _ = _lists(docs, K, 1)
+    ix = B.Index.ingest(docs, B.build_params(8, knn_k=K, nd_rounds=1, nd_sample=4, n_entry=4))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold, left = [], 430_000_000   # 164 MB of candidates, 82 of rounded rows, 138 of sampled scores; 320 of score rows
+    while torch.cuda.mem_get_info()[0] > left + (4 << 20):
+        hold.append(torch.empty(max(torch.cuda.mem_get_info()[0] - left, 2 << 20), dtype=torch.uint8, device="cuda:0"))
+    print("free", torch.cuda.mem_get_info()[0] >> 20, "MB", flush=True)
+    got = ix.stage_seed_knn(K)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+    del hold
+    torch.cuda.empty_cache()
+    ix.close()
