@@ -594,7 +594,8 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     const int64_t open_part = n < 32768 ? 4 : 10;
     const bool forced = g_ap_debug.seed_buffer_cap != 0 || g_ap_debug.seed_tau_ulps != 0;
     if (rc == AP_OK && rounded && !forced) {
-        const int32_t rows = 1024, place = std::max(0, (int32_t)((double)K * (double)cs / (double)n + 0.5) - 1);
+        const int32_t rows = (int32_t)std::min<int64_t>(1024, n / 256 * 256);   // two tiles of 256 at least; the list of rows has n + 1 entries
+        const int32_t place = std::max(0, (int32_t)((double)K * (double)cs / (double)n + 0.5) - 1);
         const int32_t last = std::max(place, (int32_t)std::min<int64_t>(m, (int64_t)AP_BAND * cs / n) - 1);
         int32_t n_open = 0;
         rc = ap_fill_u32(ovf, 1, 0u, st);

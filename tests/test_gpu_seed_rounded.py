@@ -81,6 +81,30 @@ def test_rows_much_alike_are_not_swept_twice(n, dim, K):
             assert f_got <= 1.1 * n * n * kd + 2.0 * n * 8192 * kd + 1.1 * n * n * dim, (f_got, f_want)
 
 
+@pytest.mark.parametrize("n", [512, 600, 1023, 1024, 1300])
+def test_the_sample_is_no_larger_than_the_corpus(debug_knobs, n):
+    """A small sample of columns takes a corpus of a few hundred rows to the rounded sweep: the rows that are looked at before it
+    are whole tiles of the corpus, at most 1,024."""
+    dim, K = 64, 16
+    print(f"rounded seed sweep of a small corpus n={n}", flush=True)
+    w = make_workload("tiny", seed=n, n=n, nq=1, dim=dim, sp=("fixed", 2), tx=("fixed", 2))
+    docs = B.DeviceVecs(w.docs)
+    debug_knobs("seed_one_sided", 1)
+    ix = B.Index.ingest(docs, B.build_params(8, knn_k=K, nd_rounds=1, nd_sample=4, n_entry=4))
+    want = [t.clone() for t in ix.stage_seed_knn(K)]
+    debug_knobs("seed_one_sided", 0)
+    debug_knobs("seed_sample_cols", 128)
+    flops = []
+    for cap in (4096, 0):   # with the buffers' size set nothing is looked at first
+        debug_knobs("seed_buffer_cap", cap)
+        f0 = ix.build_counters()["seed_flops"]
+        got = ix.stage_seed_knn(K)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+        flops.append(ix.build_counters()["seed_flops"] - f0)
+    assert flops[1] - flops[0] == 2.0 * min(1024, n // 256 * 256) * 128 * dim
+    ix.close()
+
+
 def test_little_memory():
     """The rounded sweep fits what is free, the score rows of the near duplicates that it leaves open do not: the f32 sweep gives
     the lists, as it would have from the start."""
