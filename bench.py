@@ -301,7 +301,7 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
     # rounds (every candidate's record, and the dense rows its bound calls for: HBM), the neighbourhood phase (pair similarities per second)
     K = bp.knn_k
     seed_flops = float(ix.build_counters()["seed_flops"]) or 2.0 * N * N * w.docs.dim   # what the stage's MFMA products executed
-    seed_bf16 = bf16 or N >= 16384   # f32 rows of a larger corpus are swept rounded to bf16
+    seed_bf16 = ix.seed_products_bf16()   # f32 rows of a larger corpus are swept rounded to bf16 where that tells them apart
     seed_tflops = seed_flops / max(bt["seed"], 1e-9) / 1e12
     # a lower bound of what the rounds read: every candidate's record, and the dense rows of the K documents a node's first
     # round sets its threshold with

@@ -355,6 +355,10 @@ int ap_build_timings(const ap_index *index, float out6[6]);
  *     the sweeps, the exact rows). */
 int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
 
+/* Which rows the products of the last seed stage on this index took (host int32): 1 = bf16, stored or rounded from
+ * f32 (the candidates are then scored again in f32), 0 = f32. */
+int ap_build_seed_bf16(const ap_index *index, int32_t *out);
+
 /* Debug settings, for tests: they drive small inputs through the code paths of large ones and never change a
  * result.  One process-wide value per name (host string), 0 = the library's own choice:
  *   "seed_sample_cols"        columns sampled for the seed threshold (forces the thresholded sweep on small corpora)

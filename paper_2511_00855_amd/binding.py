@@ -489,6 +489,12 @@ class Index:
             _check(lib().ap_build_counters(self._h, out, _stream()), "ap_build_counters")
         return dict(refine_similarities=int(out[0]), seed_flops=int(out[1]))
 
+    def seed_products_bf16(self) -> bool:
+        """Whether the last seed stage multiplied bf16 rows (stored, or rounded from f32 with the candidates scored again)."""
+        out = C.c_int32(0)
+        _check(lib().ap_build_seed_bf16(self._h, C.byref(out)), "ap_build_seed_bf16")
+        return bool(out.value)
+
     def build_timings(self):
         out = (C.c_float * 6)()
         _check(lib().ap_build_timings(self._h, out), "ap_build_timings")

@@ -491,6 +491,12 @@ extern "C" int ap_build_counters(const ap_index *ix, uint64_t out2[2], void *str
     return AP_OK;
 }
 
+extern "C" int ap_build_seed_bf16(const ap_index *ix, int32_t *out) {
+    AP_REQUIRE(ix && out, "NULL argument");
+    *out = ix->seed_bf16;
+    return AP_OK;
+}
+
 extern "C" int ap_build_timings(const ap_index *ix, float out6[6]) {
     AP_REQUIRE(ix && out6, "NULL argument");
     memcpy(out6, ix->timings, sizeof(ix->timings));

@@ -736,6 +736,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     if (rc != AP_OK) return rc;
     if (e != hipSuccess) { ap_set_error("seed k-NN failed: %s", hipGetErrorString(e)); return AP_EHIP; }
     *done = !alike;
+    if (*done && rounded) ix->seed_bf16 = 1;
     return AP_OK;
 }
 
@@ -762,6 +763,7 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
     hipError_t e = hipSuccess;
     int rc = AP_OK;
     const bool whole = !node_ids && !g_ap_debug.seed_one_sided;   // the symmetric sweeps' case
+    ix->seed_bf16 = ix->dtype == AP_BF16 ? 1 : 0;
     if (whole && ix->dtype == AP_F32 && n < 2 * cs && n >= AP_ROUNDED_MIN) {
         bool done = false;
         rc = ap_seed_knn_symmetric(ix, K, true, out_ids, out_sc, st, &done);

@@ -64,6 +64,7 @@ struct ap_index {
     float *tx_w = nullptr;     // owned: BM25 weight per lexical entry
     int32_t *df = nullptr;     // owned: document frequency per term
     unsigned long long *counters = nullptr;   // owned: [0] hybrid similarities evaluated by refinement rounds on this index
+    mutable int seed_bf16 = 0;                     // 1: the last seed stage's products over the whole corpus took bf16 rows (stored or rounded)
     mutable unsigned long long seed_flops = 0;   // FLOPs (2 per multiply-add, padded tiles included) of the seed stage's dense products so far
     float *stats = nullptr;    // owned: [0] avgdl
     float *self_sim = nullptr; // owned: fused self-similarity under build_w

@@ -105,6 +105,20 @@ def test_the_sample_is_no_larger_than_the_corpus(debug_knobs, n):
     ix.close()
 
 
+def test_which_rows_were_multiplied():
+    """What the index says about its seed stage: rounded rows, f32 rows where one dwarfs the others, f32 rows of a small corpus,
+    stored bf16 rows."""
+    for n, base, giant, want in ((16384, "tiny", False, True), (16384, "tiny", True, False), (2000, "tiny", False, False), (2000, "cfg3", False, True)):
+        w = make_workload(base, seed=n, n=n, nq=1, dim=64, vocab=5_000, sp=("fixed", 2), tx=("fixed", 2))
+        if giant:
+            w.docs.dense = np.array(w.docs.dense, dtype=np.float32)
+            w.docs.dense[n // 3] *= 1e6
+        ix = B.Index.ingest(B.DeviceVecs(w.docs, bf16=base == "cfg3"), B.build_params(8, knn_k=16, nd_rounds=1, nd_sample=4, n_entry=4))
+        ix.stage_seed_knn(16)
+        assert ix.seed_products_bf16() == want, (n, base, giant)
+        ix.close()
+
+
 def test_little_memory():
     """The rounded sweep fits what is free, the score rows of the near duplicates that it leaves open do not: the f32 sweep gives
     the lists, as it would have from the start."""
