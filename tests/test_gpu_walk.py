@@ -134,3 +134,48 @@ def test_counts_of_rows_not_read(debug_knobs):
             assert ((c[:, 2] >= 0) & (c[:, 0] - c[:, 2] >= c[:, 0].clamp(max=beam))).all(), (mode, beam)
             assert (c[:, 2] == 0).all() if mode == 3 else (c[:, 2] > 0).any(), (mode, beam)
     ix.close()
+
+
+def test_one_query_many_queries_and_the_plans_own_choice(debug_knobs):
+    """One query alone; a batch whose rows of scores do not fit the L2, which no wave brings near; and a batch that the cost model
+    itself gives to the walk out of the bounds: its third counter is that of the walk set by hand, not that of the other searches."""
+    n = 20_000
+    w = make_workload("tiny", seed=21, n=n, nq=320, dim=768, vocab=30_522, sp=("fixed", 120), tx=("fixed", 60))
+    docs = B.DeviceVecs(w.docs)
+    rng = np.random.default_rng(8)
+    ix = B.Index.import_graph(docs, B.build_params(64, n_entry=64), rng.integers(0, n, (n, 64)).astype(np.int32), rng.permutation(n)[:64].astype(np.int32))
+    qs = B.DeviceVecs(w.queries)
+    assert qs.n * n * 4 > 24e6
+    for first, calls in ((1, [(1, 16, 1), (10, 128, 1), (10, 512, 4)]), (40, [(10, 512, 1)]), (320, [(10, 128, 1)])):
+        part = make_workload("tiny", seed=21 + first, n=64, nq=first, dim=768, vocab=30_522, sp=("fixed", 120), tx=("fixed", 60))
+        part = B.DeviceVecs(part.queries) if first < 320 else qs
+        got, third = {}, {}
+        for mode in (1, 2, 3, 0):
+            debug_knobs("search_walk", mode)
+            got[mode] = _searches(ix, part, None, calls)
+            third[mode] = ix.search_stats(first)[0][:, 2].clone()
+        for mode in (2, 3, 0):
+            assert all(torch.equal(a, b) for a, b in zip(got[1], got[mode])), (first, mode)
+        if first == 40:
+            assert torch.equal(third[0], third[2]) and not torch.equal(third[0], third[1])
+    ix.close()
+
+
+def test_queries_that_only_the_second_pass_answers(debug_knobs):
+    """Every score of a query that holds a NaN is one: the walk with lists gives up at its first document, so the ids, scores and
+    counts of such a query are those of the second pass, beside queries that the first one decides."""
+    n, nq = 3000, 12
+    w = make_workload("tiny", seed=12, n=n, nq=nq, dim=128)
+    w.queries.dense = np.array(w.queries.dense, dtype=np.float32)
+    w.queries.dense[::3, 5] = np.nan
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    ix = B.Index.build(docs, B.build_params(16, nd_rounds=1, n_entry=16))
+    calls = [(10, 96, 1), (10, 300, 4)]
+    got = {}
+    for mode in (1, 2, 3):
+        debug_knobs("search_walk", mode)
+        got[mode] = _searches(ix, qs, None, calls)
+        assert (got[mode][0][::3] >= 0).all() and got[mode][1].view(torch.float32)[::3].isnan().all()
+    for mode in (2, 3):
+        assert all(torch.equal(a, b) for a, b in zip(got[1], got[mode])), mode
+    ix.close()
