@@ -1624,9 +1624,10 @@ __global__ __launch_bounds__(256) void k_gram_merge(const uint2 *__restrict__ re
 // with those apart, ms: K = 128, 650 columns 3.37 and 2.98, 1,800: 5.67 and 3.90; K = 64, 490: 1.89 and 1.92, 640: 2.06 and 2.01,
 // 960: 2.48 and 2.28; K = 48, 500: 1.47 and 1.51, 730: 1.75 and 1.74; K = 32, 500: 1.34 and 1.44.
 // Both vocabularies are written out: with one body for the two the accumulators are chosen by the vocabulary at run time, and 64 registers
-// spill (K = 32, lists of 20 and 13 terms, nothing set apart: 1.21 and 0.95 ms; K = 128 above: 3.67 and 2.98, 4.72 and 3.90).  The prune stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all
-// columns in the matrix, 41 ms here; 200,000 bf16: 299, 109 and 76 ms.  Of a workgroup's 260,000 cycles the pairs take 55,000, the
-// matrix 60,000, marking, numbering and counting the columns 110,000: chains of LDS round trips that 16 waves do not hide.
+// spill (K = 32, lists of 20 and 13 terms, nothing set apart: 1.21 and 0.95 ms; K = 128 above: 3.67 and 2.98, 4.72 and 3.90).  The prune
+// stage's lists over 100,000 f32 documents: 160 ms with the walks, 66 ms with all columns in the matrix, 41 ms with those of few holders
+// apart and spills, 28.9 ms here; 200,000 bf16: 299, 109, 76 and 53.8 ms.  What is left is mostly marking, numbering and counting the columns
+// and the pairs: chains of LDS round trips that 16 waves do not hide.
 #define AP_GL_WORDS 8192          // words of a bitmap: vocabularies up to 2^18 terms
 #define AP_GL_C 64                // columns of a chunk
 #define AP_GL_STRIDE (AP_GL_C + 4)   // rows 16-byte aligned; 16 rows x 4 groups of 4 columns fall into distinct banks

@@ -6,7 +6,7 @@
 //  - the scores come first: k_walk_score lets the whole chip score the documents that the search may want, those whose
 //    upper bound reaches a quantile of the query's bounds (or, of a small corpus, all of them), and leaves the scores in
 //    a row of floats per query;
-//  - one wave walks the graph (k_walk), 1.05 us an iteration: a round trip for the parent's edges, unless it was foreseen
+//  - one wave walks the graph (k_walk), 1.05 to 1.25 us an iteration: a round trip for the parent's edges, unless it was foreseen
 //    (every other one is), one for its neighbours' scores, and LDS for the rest; nothing in the loop waits for another wave.
 // A score is computed by the code that k_search runs, so the results have the same bits.
 #include <math.h>
@@ -793,8 +793,8 @@ int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, co
 //  - k_search: per iteration 5.5 with one parent, 13.6 with four, 18 with sixteen (0.45 of that on 3,000 documents, whose
 //    descriptors and rows are all close by; 18 and more where it runs without bounds), 0.09 ns for every document it reaches
 //    while the chip is full (0.24 without bounds).
-// One query of 100,000 documents, pool 128: 834 -> 254 us (all scored ahead); 37 of 120,011, pool 512: 3.14 -> 0.99 ms (out of
-// the bounds).  Where the walk would not be a fifth faster, k_search stays: 300 queries with a pool of 128, 1.2 and 1.6 ms.
+// One query of 100,000 documents, pool 128: 867 -> 254 us (all scored ahead: the scores 92, the lines 11, the walk 137);
+// 37 of 120,011, pool 512: 3.17 -> 1.01 ms (out of the bounds: these 0.19 ms, the lines 0.01, the scores 0.14, the walk 0.63).  Where the walk would not be a fifth faster, k_search stays: 300 queries with a pool of 128, 1.2 and 1.6 ms.
 // The first line: three times the share of the documents that the pool holds of those a search reaches, if it met them at
 // random, and so many that six of the entry points and first neighbours are above it; a search that finds less runs twice.
 ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters, bool bounds, bool can_bound) {
