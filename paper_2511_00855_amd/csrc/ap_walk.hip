@@ -795,6 +795,10 @@ int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, co
 //    while the chip is full (0.24 without bounds).
 // One query of 100,000 documents, pool 128: 867 -> 254 us (all scored ahead: the scores 92, the lines 11, the walk 137);
 // 37 of 120,011, pool 512: 3.17 -> 1.01 ms (out of the bounds: these 0.19 ms, the lines 0.01, the scores 0.14, the walk 0.63).  Where the walk would not be a fifth faster, k_search stays: 300 queries with a pool of 128, 1.2 and 1.6 ms.
+// A way whose lists would not hold what enters them is not taken: a query whose list is full is searched twice (43,000 documents, degree 32,
+// 3 queries, pool 2,048: 10.9 ms by k_search, 13.3 scored ahead, 4.3 out of the bounds; degree 64, pool 3,600: 14.8, 29.0 and 7.9).  Documents that are
+// met enter while they score at least the last line that the pool has filled, taking those met for any of the corpus; what leaves as a parent
+// makes up for lanes that get more than others.  Lists stayed whole up to 1.0 of their room by this count and were full from 1.1 on.
 // The first line: three times the share of the documents that the pool holds of those a search reaches, if it met them at
 // random, and so many that six of the entry points and first neighbours are above it; a search that finds less runs twice.
 ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters, bool bounds, bool can_bound) {
@@ -816,10 +820,27 @@ ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t wi
     const double near = std::min(1.2, std::max(0.4, 0.45 + 0.36 * log10(n / 3000.0)));
     const double other = bounds ? table + std::max(iters * near * (5.5 + std::min(2.7 * (width - 1), 12.5)), q * met * 0.09e-3)
                                 : std::max(iters * near * 18.0, q * met * 0.24e-3);
+    double lines[2][4] = {{first, first / 2, 1.5 * share, share}, {std::max(0.5, 8 * share), 8 * share, 3 * share, 1.2 * share}};
+    for (auto &l : lines) for (double &s : l) s = std::min(1.0, s);
+    // a lane's list takes the neighbours at its own places of the parents' edges
+    const double edges = (double)width * ix->params.degree, room = cap * edges / ceil(edges / 64.0);
+    auto fits = [&](int mode) {
+        const double *s = lines[mode - 1];
+        double enter = 0.0, seen = 0.0, part = mode == 1 ? first : 1.0;   // out of the bounds nothing enters that was not scored ahead
+        for (int i = 0; i < 5; i++) {
+            const double until = i < 4 ? std::min(met, beam / s[i]) : met;
+            if (until > seen) { enter += (until - seen) * part; seen = until; }
+            if (i < 4) part = s[i];
+        }
+        return enter <= room;
+    };
     const bool some = can_bound && ix->bd_mem != nullptr;
-    p.mode = some && (out_of_bounds < all || forced == 2) && forced != 3 ? 1 : 2;
-    if (forced == 0 && (p.mode == 1 ? out_of_bounds : all) > 0.8 * other) { p.mode = 0; return p; }
-    const double lines[2][4] = {{first, first / 2, 1.5 * share, share}, {std::max(0.5, 8 * share), 8 * share, 3 * share, 1.2 * share}};
-    for (int i = 0; i < 4; i++) p.share[i] = (float)std::min(1.0, lines[p.mode - 1][i]);
+    if (forced != 0) p.mode = some && forced == 2 ? 1 : 2;
+    else {
+        const double cost[2] = {some && fits(1) ? out_of_bounds : INFINITY, fits(2) ? all : INFINITY};
+        p.mode = cost[0] < cost[1] ? 1 : 2;
+        if (cost[p.mode - 1] > 0.8 * other) { p.mode = 0; return p; }
+    }
+    for (int i = 0; i < 4; i++) p.share[i] = (float)lines[p.mode - 1][i];
     return p;
 }

@@ -179,3 +179,24 @@ def test_queries_that_only_the_second_pass_answers(debug_knobs):
     for mode in (2, 3):
         assert all(torch.equal(a, b) for a, b in zip(got[1], got[mode])), mode
     ix.close()
+
+
+# the way a batch takes: nothing to read is left out where all documents are scored ahead; the walk out of the bounds and the searches
+# that score as they go leave out different numbers.  64 edges fill all of a wave's lists, 16 a quarter of them
+@pytest.mark.parametrize("degree,beam,way", [(64, 512, 3), (16, 512, 2), (16, 2500, 1)])
+def test_walks_whose_lists_would_not_hold_what_enters_them(debug_knobs, degree, beam, way):
+    """A query whose lists overflow is searched twice: the cost model takes a way whose lists hold what is to be expected, or none."""
+    n = 12_000
+    w = make_workload("tiny", seed=degree + beam, n=n, nq=3, dim=128)
+    rng = np.random.default_rng(9)
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    ix = B.Index.import_graph(docs, B.build_params(degree, n_entry=64), rng.integers(0, n, (n, degree)).astype(np.int32), rng.permutation(n)[:64].astype(np.int32))
+    got, third = {}, {}
+    for mode in (1, 2, 3, 0):
+        debug_knobs("search_walk", mode)
+        got[mode] = _searches(ix, qs, None, [(10, beam, 1)])
+        third[mode] = ix.search_stats(3)[0][:, 2].tolist()
+    assert all(torch.equal(a, b) for mode in (2, 3, 0) for a, b in zip(got[1], got[mode]))
+    assert third[1] != third[2] and max(third[3]) == 0 < min(third[1] + third[2])
+    assert third[0] == third[way], third
+    ix.close()
