@@ -34,12 +34,6 @@ struct ApBoundPool {
 };
 
 // ------------------------------------------------------------------ ingest
-// eight bins an octave of the document frequency
-__device__ __forceinline__ int ap_df_bin(int32_t df) {
-    if (df <= 0) return -1;
-    const int b = (int)(8.f * log2f((float)df));
-    return b > 255 ? 255 : b;
-}
 __global__ __launch_bounds__(256) void k_bd_hist(const int32_t *__restrict__ df_sp, int32_t nsp, const int32_t *__restrict__ df_tx, int32_t ntx,
                                                  int32_t *__restrict__ hist) {
     __shared__ int32_t h[256];
@@ -51,6 +45,12 @@ __global__ __launch_bounds__(256) void k_bd_hist(const int32_t *__restrict__ df_
     }
     __syncthreads();
     if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+}
+int ap_df_histogram(const int32_t *df_sp, int32_t nsp, const int32_t *df_tx, int32_t ntx, int32_t *hist, hipStream_t st) {
+    const int64_t all = (int64_t)nsp + ntx;
+    hipLaunchKernelGGL(k_bd_hist, dim3((unsigned)std::min<int64_t>((all + 255) / 256, 256)), dim3(256), 0, st, df_sp, nsp, df_tx, ntx, hist);
+    AP_CHECK_HIP(hipGetLastError());
+    return AP_OK;
 }
 // The head is every term of the top bins that fit kh columns together; every other term gets a run of postings.  misc[0]
 // counts columns, misc[1] postings handed out.
@@ -182,6 +182,7 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     uint32_t *cursor = reinterpret_cast<uint32_t *>(df_sp + c.sp_vocab);
     int32_t *hist = reinterpret_cast<int32_t *>(cursor + all);
     uint32_t *misc = reinterpret_cast<uint32_t *>(hist + 256);
+    ix->bd_df = df_sp;
     ix->bd_col = reinterpret_cast<int32_t *>(m + o_col);
     ix->bd_run = reinterpret_cast<uint2 *>(m + o_run);
     ix->bd_post = reinterpret_cast<uint2 *>(m + o_post);
@@ -192,7 +193,7 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     AP_TRY(ap_fill_u32(df_sp, n_clear, 0u, st));
     if (ix->sp_nnz > 0)
         AP_TRY(ap_count_terms(c.sp_idx, nullptr, ix->sp_nnz, df_sp, nullptr, st));
-    hipLaunchKernelGGL(k_bd_hist, dim3((unsigned)std::min<int64_t>((all + 255) / 256, 256)), dim3(256), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist);
+    AP_TRY(ap_df_histogram(df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, st));
     hipLaunchKernelGGL(k_bd_pick, dim3((unsigned)((all + 1023) / 1024)), dim3(1024), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, kh, ix->bd_col,
                        ix->bd_run, misc);
     const dim3 g((unsigned)std::min<int64_t>((c.n + 3) / 4, 4096));

@@ -6,7 +6,9 @@
 // decides an id depends on the order in which atomics arrive.
 #include <stdlib.h>
 #include <algorithm>
+#include <type_traits>
 #include "ap_tiles.hpp"
+#include "ap_packed.hpp"
 
 int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
 int ap_alloc_graph(ap_index *ix);
@@ -936,6 +938,9 @@ struct ApRefineHints {
     const float *knn_sc;
     const uint32_t *known;
     uint32_t *known_out;   // the same bits for the lists this round returns
+    // the lists of all documents, packed (NULL: not there)
+    const uint32_t *pk;
+    const uint2 *pk_at;
 };
 
 #define AP_RT_SPB 10   // look-up tables of the node's own lists: 1024 + 512 slots, at most a quarter full
@@ -944,55 +949,62 @@ struct ApRefineHints {
 // 153 ms, 4 and 2: 150 ms, 4 and 4: 150 ms, 8 and 2: 151 ms).
 #define AP_RF_G 4
 #define AP_RF_GD 2
-#define AP_RF_TOP 0x40000000   // bit of a candidate that is among the first S entries of the node's own list (ids have 30 bits)
+#define AP_RF_GP 2               // packed records a group of 16 lanes has on their way
+#define AP_RF_BINS 1024          // bins of the histogram that says what is scored first
+#define AP_RF_TOP 0x40000000     // bit of a candidate that is among the first S entries of the node's own list (ids have 30 bits)
+#define AP_RF_MORE(K) ((K) / 6)   // scored first beyond K (three rounds, 100,000 f32 and 200,000 bf16 documents: K / 4: 55.1 and 105.6 ms, K / 6: 53.8 and 105.1; less, and a bound far above its score makes T so low that the first bf16 round takes a tenth longer)
+#define AP_RF_FIRST ((int32_t)0x80000000)   // bit of a candidate that is scored first
 
 // One refinement round for one node.  What bounds it: the candidates' bytes (record and dense row) and the instructions
-// of their look-ups, so the work is to touch fewer of them.  With the hints of a construction three things need no
+// of their look-ups, so the work is to touch fewer of them.  With the hints of a construction four things need no
 // reading, and the lists stay what scoring everything gives, bit for bit:
 //  - a candidate scored for this node before.  Lists only improve: whatever a round scored and did not keep ranks after K
 //    documents that the list still holds or has exchanged for better ones, so it cannot enter again, and the per-path
 //    lists were offered it.  That is the node's own list (its scores are at hand), and every neighbour's neighbour
 //    w = N(v)[j] whose v was already among the first S of N(u) one round ago and w among the first S of N(v): both are
 //    bits of `known`.
+//  - the record of a candidate whose packed lists leave it out of reach: they are two fifths of its bytes, and give upper bounds of
+//    its learned-sparse and lexical parts that lie some 2 % above them.
 //  - the dense row of a candidate whose sparse and lexical parts leave it out of reach.  The seed lists are the exact
 //    dense neighbours, so a document outside the node's list has a dense part of at most tau (plus the rounding of two
-//    differently ordered sums, eps |u||w|) -- 0.1 where the norms alone would allow 1.  It is read only if that bound lifts
-//    the candidate to the threshold T of the fused list or to the last entry of the per-path list by the dense part.
-//    T is the list's last score in later rounds.  In the first round, whose list carries no fused scores, the K candidates
-//    with the best sparse and lexical parts are scored first, and T is the least of their scores.
-// Phases: records of all candidates (a wave each, AP_RF_G on their way at a time), a thread per candidate decides about the
-// dense rows, dense rows of those that need one (a wave each), sort, lists.  Measured on 200,000 documents of 1,024 bf16
-// columns, three rounds: 308 ms with every candidate
-// scored in full, 150 ms now (7 TB/s of traffic in the first round: what a read-mostly kernel reaches here); 768 f32 columns,
-// 100,000 documents: 202 -> 81 ms.
+//    differently ordered sums, eps |u||w|) -- 0.1 where the norms alone would allow 1.
+//  - what cannot beat the K best of this round.  A histogram of the candidates' bounds and the list's scores gives a line that
+//    5/4 K of them reach; those are scored first, and a histogram of the scores gives T, which K of them reach and so the new
+//    list's last entry does.  After that only candidates are scored whose bounds reach T, or the last entry of a per-path list (in the first
+//    round, where those are empty: the P-th best of what was scored first).
+// Phases: packed records of all candidates (16 lanes each; without packed lists the records themselves, a wave each), the
+// histogram, records and dense rows of what is scored first, a thread per candidate decides about the others, their
+// records and dense rows, sort, lists.
 template <int DT, int NV>
-__global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restrict__ rec, const uint4 *__restrict__ meta, float wd,
+__global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__restrict__ rec, const uint4 *__restrict__ meta, float wd,
                                                 float ws, float wf, int32_t K, int32_t S, int32_t P,
                                                 const int32_t *__restrict__ knn, const int32_t *__restrict__ sp_ids,
                                                 const float *__restrict__ sp_sc, const int32_t *__restrict__ node_ids,
                                                 int64_t nn, int64_t x0, int32_t *__restrict__ out_ids, float *__restrict__ out_sc,
                                                 int32_t *__restrict__ out_sp_ids, float *__restrict__ out_sp_sc,
                                                 unsigned long long *__restrict__ n_sims, ApRefineHints hint) {
-    __shared__ __attribute__((aligned(16))) int32_t ht[AP_HT];
+    // 32 KB that serve three times: the hash set of the candidates; the node's weights by slot, a byte each; the histogram
+    // and what else the decisions need, with the fused keys (AP_MAXC padded to a power of two) behind them
+    __shared__ __attribute__((aligned(16))) uint32_t pool[AP_PK_SLOTS / 4];
+    static_assert(AP_HT * 4 == 16384 && AP_PK_SLOTS == 32768, "the layout below");
+    int32_t *ht = reinterpret_cast<int32_t *>(pool);
+    uint32_t *hist = pool;                                                              // [AP_RF_BINS]
+    uint2 *where = reinterpret_cast<uint2 *>(pool + AP_RF_BINS);                        // [AP_MAXC] records of need[]
+    uint64_t (*better)[64] = reinterpret_cast<uint64_t (*)[64]>(pool + AP_RF_BINS + 2 * AP_MAXC);   // [3][64] candidates that beat a full per-path list's last entry
+    static_assert(AP_RF_BINS * 4 + AP_MAXC * 8 + 3 * 64 * 8 <= AP_HT * 4, "what takes the hash set's place");
+    uint64_t *keys = reinterpret_cast<uint64_t *>(pool + AP_HT);                        // [2048]
     __shared__ int32_t cand[AP_MAXC];
-    __shared__ uint64_t keys[2048];   // fused keys of the candidates that can enter the list, sorted in place afterwards (AP_MAXC padded to a power of two)
     // per candidate: before it is scored, where its record lies, the two lengths and the dense norm; then the norm and the
-    // two list parts; then the three component scores (candidates with the sign bit keep the norm: their dense part is not needed)
+    // two list parts (or their bounds); then the three component scores of those that need[] names
     __shared__ float comp[3][AP_MAXC];
     __shared__ int32_t l_sp_idx[AP_A_CAP], l_tx_idx[AP_A_CAP];
     __shared__ float l_sp_val[AP_A_CAP], l_tx_val[AP_A_CAP];
     __shared__ uint64_t oldk[3][32];
     __shared__ __attribute__((aligned(16))) uint64_t qtab[(1 << AP_RT_SPB) + (1 << AP_RT_TXB)];
-    __shared__ uint16_t need[AP_MAXC];        // candidates whose dense row is to be read
-    __shared__ int32_t misc[4];
-    __shared__ uint64_t pre;
-    __shared__ int32_t s_cnt, s_seed[2], s_nk, s_need;
-    __shared__ uint32_t s_T;
-    __shared__ float s_dP;
-    // with hints the hash set is done with once the candidates are known, and its space serves again
-    uint64_t *sel = reinterpret_cast<uint64_t *>(ht);               // [256] first round: the K best by sparse and lexical parts
-    uint32_t *hist = reinterpret_cast<uint32_t *>(ht) + 512;        // [256]
-    uint64_t (*better)[64] = reinterpret_cast<uint64_t (*)[64]>(ht + 768);   // [3][64] candidates that beat a full per-path list's last entry
+    __shared__ uint16_t need[AP_MAXC];        // from the front: candidates that are scored in full; from the back: those whose list parts alone are
+    __shared__ int32_t s_cnt, s_seed[2], s_nk, s_need, s_lists;
+    __shared__ uint32_t s_lo, s_hi, s_line;
+    __shared__ float s_last[3];
     const int64_t x = x0 + blockIdx.x;   // the launch covers nodes x0 .. x0 + gridDim.x of the nn
     const int64_t u = node_ids ? (int64_t)node_ids[x] : x;
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
@@ -1006,23 +1018,20 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
     // look-up, as in the search); lists that are longer, or that no multiplier fits, are searched where they lie
     bool use_tab = a.sp_n <= (1 << AP_RT_SPB) / 4 && a.tx_n <= (1 << AP_RT_TXB) / 4;   // uniform
     uint32_t msp = 0, mtx = 0;
-    if (threadIdx.x == 0) { s_cnt = 0; s_nk = 0; s_need = 0; s_T = 0xffffffffu; }
+    if (threadIdx.x == 0) { s_cnt = 0; s_nk = 0; s_need = 0; s_lists = 0; s_lo = 0xffffffffu; s_hi = 0u; }
     __syncthreads();
     if (use_tab && wave == 0) {
         const int32_t s0 = ap_bucket_build<4>(a.sp_idx, a.sp_val, a.sp_n, qtab, AP_RT_SPB);
         const int32_t s1 = ap_bucket_build<2>(a.tx_idx, a.tx_val, a.tx_n, qtab + (1 << AP_RT_SPB), AP_RT_TXB);
         if (lane == 0) { s_seed[0] = s0; s_seed[1] = s1; }
     }
-    // candidates: the node's own list ...
+    // candidates: the node's own list (in later rounds its scores are at hand: it only stays out of the candidates) ...
     const int32_t sl = S < K ? S : K;
     for (int32_t s = threadIdx.x; s < K; s += blockDim.x) {
         const int32_t v = knn[u * K + s];
-        if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v)) {
-            if (later) keys[atomicAdd(&s_nk, 1)] = ap_make_key(hint.knn_sc[u * K + s], v, s < sl ? 1u : 0u);   // scored in an earlier round
-            else {
-                const int32_t at = atomicAdd(&s_cnt, 1);
-                cand[fast ? s : at] = v | (s < sl ? AP_RF_TOP : 0);   // a seed list's members are distinct and lead the list: candidate s is member s
-            }
+        if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v) && !later) {
+            const int32_t at = atomicAdd(&s_cnt, 1);
+            cand[fast ? s : at] = v | (s < sl ? AP_RF_TOP : 0);   // a seed list's members are distinct and lead the list: candidate s is member s
         }
     }
     __syncthreads();
@@ -1048,11 +1057,27 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
     __syncthreads();
     const int32_t cnt = ap_uniform_i32(s_cnt);
     if (threadIdx.x == 0 && n_sims) atomicAdd(n_sims, (unsigned long long)cnt);   // measurement: similarities of this node and round
+    // the node's own scales; a list that has none (a negative value) has no bounds either
+    float own_sp = 0.f, own_tx = 0.f;
+    uint2 own_at = make_uint2(0, 0);
+    bool packed = hint.pk != nullptr;   // uniform
+    if (packed) {
+        own_at = hint.pk_at[u];
+        const uint32_t *r = hint.pk + (size_t)own_at.x * (AP_PK_LINE / 4);
+        own_sp = __uint_as_float(r[0]); own_tx = __uint_as_float(r[1]);
+        packed = own_sp < INFINITY && own_tx < INFINITY;
+    }
     // where each candidate's record lies and how long it is, fetched for all candidates at once, so that the scoring loop
     // starts its loads without a round trip of its own
     for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
-        const uint4 m = meta[cand[t] & ~AP_RF_TOP];
-        comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y); comp[2][t] = __uint_as_float(m.z);
+        const int32_t v = cand[t] & ~AP_RF_TOP;
+        if (packed) {
+            const uint2 m = hint.pk_at[v];
+            comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y);
+        } else {
+            const uint4 m = meta[v];
+            comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y); comp[2][t] = __uint_as_float(m.z);
+        }
     }
     // the per-path lists so far, in keys (entries scored again in a round that scores everything are left out: there the
     // caller's scores need not be this kernel's)
@@ -1068,9 +1093,64 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
         ap_wave_sync();
         if (have) oldk[wave][__popcll(hm & ((1ull << lane) - 1ull))] = ok;
     }
-    __syncthreads();
-    // the sparse and lexical parts of all candidates
-    if (use_tab) {
+    __syncthreads();   // the hash set is done with
+    // the sparse and lexical parts of all candidates, or bounds of them
+    if (packed) {
+        for (int32_t i = threadIdx.x; i < AP_PK_SLOTS / 16; i += blockDim.x) reinterpret_cast<uint4 *>(pool)[i] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        {
+            const ApPkUnit *r = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)own_at.x * (AP_PK_LINE / 4));
+            const int32_t entries = 4 * (int32_t)((own_at.y & 0xffffu) + (own_at.y >> 16));
+            for (int32_t i = threadIdx.x; i < entries; i += blockDim.x) {
+                const ApPkUnit d = r[1 + (i >> 2)];
+                const uint32_t at = ((i & 2 ? d.s23 : d.s01) >> (16 * (i & 1))) & 0xffffu, w = (d.w >> (8 * (i & 3))) & 255u;
+                if (w) atomicOr(&pool[at >> 2], w << (8 * (at & 3u)));   // two terms of one slot: at least the larger of them
+            }
+        }
+        __syncthreads();
+        constexpr int G = AP_RF_GP, U = 3;
+        const AP_LDS uint8_t *tab = (const AP_LDS uint8_t *)pool;
+        const int sub = lane >> 4, l16 = lane & 15;
+        own_sp *= 1.00004f; own_tx *= 1.00004f;   // what the sums of the scoring kernels may round up
+        for (int32_t i0 = wave * 4 * G; i0 < cnt; i0 += NW * 4 * G) {
+            ApPkUnit d[G][U];
+            const ApPkUnit *r[G];
+            int32_t nsp[G], units[G];
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const int32_t i = i0 + 4 * g + sub;
+                const uint32_t line = i < cnt ? __float_as_uint(comp[0][i]) : own_at.x, len = i < cnt ? __float_as_uint(comp[1][i]) : 0u;
+                r[g] = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)line * (AP_PK_LINE / 4));
+                nsp[g] = (int32_t)(len & 0xffffu); units[g] = 1 + nsp[g] + (int32_t)(len >> 16);
+#pragma unroll
+                for (int j = 0; j < U; j++) d[g][j] = r[g][l16 + 16 * j < units[g] ? l16 + 16 * j : 0];
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const int32_t i = i0 + 4 * g + sub;
+                uint32_t ps = 0, pf = 0;
+                auto add = [&](const ApPkUnit &e, int32_t at) {
+                    const uint32_t p = ap_pk_dot(tab, e);
+                    ps += at >= 1 && at <= nsp[g] ? p : 0u;
+                    pf += at > nsp[g] && at < units[g] ? p : 0u;
+                };
+#pragma unroll
+                for (int j = 0; j < U; j++) add(d[g][j], l16 + 16 * j);
+                for (int32_t at = l16 + 16 * U; __any(at < units[g]); at += 16) add(r[g][at < units[g] ? at : 0], at);
+                float fs = (float)ps, ff = (float)pf;
+                fs += ap_dpp<0xB1>(fs); ff += ap_dpp<0xB1>(ff);
+                fs += ap_dpp<0x4E>(fs); ff += ap_dpp<0x4E>(ff);
+                fs += ap_dpp<0x141>(fs); ff += ap_dpp<0x141>(ff);
+                fs += ap_dpp<0x140>(fs); ff += ap_dpp<0x140>(ff);
+                if (l16 == 0 && i < cnt) {   // unit 0 is the first thing lane 0 of a group loaded
+                    comp[0][i] = __uint_as_float(d[g][0].s23);
+                    comp[1][i] = fs * (own_sp * __uint_as_float(d[g][0].w));
+                    comp[2][i] = ff * (own_tx * __uint_as_float(d[g][0].s01));
+                }
+            }
+        }
+        __syncthreads();
+    } else if (use_tab) {
         constexpr int G = AP_RF_G;
         for (int32_t i0 = wave; i0 < cnt; i0 += G * NW) {
             uint2 xs[G][2], xt[G][1];
@@ -1111,64 +1191,103 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
             if (lane == 0) { comp[0][i] = norm; comp[1][i] = ss; comp[2][i] = sf; }
         }
     }
-    __syncthreads();
 
-    // dense rows of the candidates need[d0 .. d1): a wave each; the first n_t of them (from 0) set the threshold T
-    auto dense_rows = [&](int32_t d0, int32_t d1, int32_t n_t) {
+    auto list_parts = [&](const uint2 *r, int32_t spn, int32_t txn, const uint2 *xs, const uint2 *xt, float &ss, float &sf) {
+        int32_t si[2], ti[1];
+        float sv[2], tv[1];
+        ap_rec_decode<2, 1>(xs, xt, spn, txn, si, sv, ti, tv);
+        if (use_tab)
+            ap_rec_reduce_bucket<2, 1, AP_RT_SPB, AP_RT_TXB>(r, (const AP_LDS uint64_t *)qtab, (const AP_LDS uint64_t *)(qtab + (1 << AP_RT_SPB)), msp, mtx, spn,
+                                                             txn, si, sv, ti, tv, ss, sf);
+        else
+            ap_rec_reduce_lists<2, 1>(r, a, spn, txn, si, sv, ti, tv, ss, sf);
+    };
+    // the candidates need[d0 .. d1) in full, a wave each: dense rows, and the records where only bounds of the list parts are known
+    // (where[] says where they lie)
+    auto score = [&](int32_t d0, int32_t d1) {
         constexpr int G = AP_RF_GD;
         for (int32_t e0 = d0 + wave; e0 < d1; e0 += G * NW) {
             uint4 raw[G][NV];
-            int32_t cand_i[G], cv[G];
+            uint2 xs[G][2], xt[G][1];
+            const uint2 *r[G];
+            int32_t cand_i[G], cv[G], spn[G], txn[G];
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 const int32_t d = e0 + NW * g < d1 ? e0 + NW * g : e0;
                 cand_i[g] = ap_uniform_i32(need[d]);
-                cv[g] = ap_uniform_i32(cand[cand_i[g]]);
+                cv[g] = ap_uniform_i32(cand[cand_i[g]]) & ~AP_RF_FIRST;
+                if (packed) {
+                    const uint2 m = where[d];
+                    const uint32_t my = ap_uniform_u32(m.y);
+                    r[g] = rec + ap_uniform_u32(m.x);
+                    spn[g] = (int32_t)(my & 0xffffu); txn[g] = (int32_t)(my >> 16);
+                    ap_rec_load_raw<2, 1>(r[g], spn[g], txn[g], xs[g], xt[g]);
+                }
                 ap_dense_load_raw<DT, NV>(D, cv[g] & ~AP_RF_TOP, raw[g]);
             }
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 if (e0 + NW * g >= d1) break;   // uniform
                 const int32_t i = cand_i[g];
-                const float ss = comp[1][i], sf = comp[2][i];
+                float ss, sf;
+                if (packed) {
+                    list_parts(r[g], spn[g], txn[g], xs[g], xt[g], ss, sf);
+                } else { ss = comp[1][i]; sf = comp[2][i]; }
                 const float sd = ap_dense_dot_raw<DT, NV>(D, qa, raw[g]);
                 if (lane == 0) {
                     const float f = ap_fuse(wd, ws, wf, sd, ss, sf);
                     comp[0][i] = sd;
+                    if (packed) { comp[1][i] = ss; comp[2][i] = sf; }
                     keys[atomicAdd(&s_nk, 1)] = ap_make_key(f, cv[g] & ~AP_RF_TOP, cv[g] & AP_RF_TOP ? 1u : 0u);
-                    if (e0 + NW * g < n_t) atomicMin(&s_T, ap_f2ord(f));
                 }
             }
         }
     };
+    // the list parts alone of the n candidates at the end of need[]
+    auto score_lists = [&](int32_t n) {
+        for (int32_t e0 = wave; e0 < n; e0 += 2 * NW) {
+            uint2 xs[2][2], xt[2][1];
+            const uint2 *r[2];
+            int32_t spn[2], txn[2];
+#pragma unroll
+            for (int g = 0; g < 2; g++) {
+                const uint2 m = where[AP_MAXC - 1 - (e0 + NW * g < n ? e0 + NW * g : e0)];
+                const uint32_t my = ap_uniform_u32(m.y);
+                r[g] = rec + ap_uniform_u32(m.x);
+                spn[g] = (int32_t)(my & 0xffffu); txn[g] = (int32_t)(my >> 16);
+                ap_rec_load_raw<2, 1>(r[g], spn[g], txn[g], xs[g], xt[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < 2; g++) {
+                if (e0 + NW * g >= n) break;   // uniform
+                float ss, sf;
+                list_parts(r[g], spn[g], txn[g], xs[g], xt[g], ss, sf);
+                const int32_t i = need[AP_MAXC - 1 - (e0 + NW * g)];
+                if (lane == 0) { comp[1][i] = ss; comp[2][i] = sf; }
+            }
+        }
+    };
+    // the list so far takes its place among the keys (the records' bounds were the last use of its space)
+    if (later) {
+        for (int32_t s = threadIdx.x; s < K; s += blockDim.x) {
+            const int32_t v = knn[u * K + s];
+            if (v >= 0 && v != (int32_t)u) keys[atomicAdd(&s_nk, 1)] = ap_make_key(hint.knn_sc[u * K + s], v, s < sl ? 1u : 0u);
+        }
+    }
     if (!fast) {
         for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) need[t] = (uint16_t)t;
+        if (threadIdx.x == 0) s_need = cnt;
         __syncthreads();
-        dense_rows(0, cnt, 0);
+        score(0, cnt);
     } else {
+        for (int32_t i = threadIdx.x; i < AP_RF_BINS; i += blockDim.x) hist[i] = 0;
+        __syncthreads();
+        const int32_t n_old = ap_uniform_i32(s_nk);
         // Bounds of the dense part of candidate t with norm |w|: the seed stage's score (members of the seed list, whose
         // scores the first round has) or its K-th score (documents outside it), plus eps |u||w|: each of the two differently
         // ordered fp32 sums is off by at most dim 2^-24 |u||w| from the exact product; twice that for each is allowed.
         const float un = __uint_as_float(meta[u].z), eps = 4.f * (float)D.dim * 5.9604645e-8f;
         const float tau = hint.tau[u];
-        // the last entry of the per-path list by the dense part, or a lower bound of it
-        float dP = -INFINITY;
-        if (later) {
-            const uint64_t last = oldk[0][P - 1];
-            if (last) dP = ap_key_score(last);
-        } else if (P <= K && n_own >= P) {   // the P best of the seed list by their seed scores are at least this good
-            if (wave == 0) {
-                float lo = INFINITY;
-                if (lane < P) {
-                    const int32_t v = knn[u * K + lane];
-                    lo = v >= 0 ? hint.seed_sc[u * K + lane] - eps * un * __uint_as_float(meta[v].z) * 1.0001f : -INFINITY;
-                }
-                for (int o = 32; o > 0; o >>= 1) lo = fminf(lo, __shfl_xor(lo, o, 64));
-                if (lane == 0) s_dP = lo;
-            }
-            __syncthreads();
-            dP = s_dP;
-        }
         auto bound = [&](int32_t t, float &bd, float &bf) {   // upper bounds of the dense part and of the fused score
             const float nb = un * comp[0][t] * 1.0001f, ss = comp[1][t], sf = comp[2][t];
             const float most = t < n_own ? hint.seed_sc[u * K + t] : tau;   // n_own is 0 in later rounds
@@ -1176,46 +1295,146 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
             const float lift = wd >= 0.f ? wd * bd : -wd * nb;
             bf = fmaf(wf, sf, ws * ss) + lift + 1e-5f * (fabsf(ws * ss) + fabsf(wf * sf) + fabsf(wd) * nb);
         };
-        float T = -INFINITY;
-        int32_t n_first = 0;
+        float T = later && n_old == K ? hint.knn_sc[u * K + K - 1] : -INFINITY;
+        // the last entries of the per-path lists, or lower bounds of what they will be
+        float last[3] = {-INFINITY, -INFINITY, -INFINITY};
         if (later) {
-            if (s_nk == K) T = hint.knn_sc[u * K + K - 1];   // nothing was added to the keys since
-        } else {
-            // the K best by sparse and lexical parts, and whatever the dense list may want of the node's own list
-            for (int32_t i = threadIdx.x; i < 256; i += blockDim.x) sel[i] = 0ull;
-            __syncthreads();
-            const int32_t got = ap_radix_select_keys([&](int64_t t) -> uint64_t { return ap_make_key(fmaf(wf, comp[2][t], ws * comp[1][t]), (int32_t)t, 1u); },
-                                                     cnt, cnt, K, hist, sel, misc, &pre);
-            for (int32_t i = threadIdx.x; i < got; i += blockDim.x) {
-                const int32_t t = ap_key_id(sel[i]);
-                need[i] = (uint16_t)t;
+#pragma unroll
+            for (int p = 0; p < 3; p++)
+                if (oldk[p][P - 1]) last[p] = ap_key_score(oldk[p][P - 1]);
+        } else if (P <= K && n_own >= P && wave == 0) {   // the P best of the seed list by their seed scores are at least this good
+            float lo = INFINITY;
+            if (lane < P) {
+                const int32_t v = knn[u * K + lane];
+                lo = v >= 0 ? hint.seed_sc[u * K + lane] - eps * un * __uint_as_float(meta[v].z) * 1.0001f : -INFINITY;
             }
-            n_first = got;
-            __syncthreads();
-            dense_rows(0, got, got);
-            __syncthreads();
-            if (got == K) T = ap_ord2f(s_T);
+            for (int o = 32; o > 0; o >>= 1) lo = fminf(lo, __shfl_xor(lo, o, 64));
+            if (lane == 0) s_last[0] = lo;
         }
-        if (threadIdx.x == 0) s_need = n_first;
-        __syncthreads();
-        if (!later) {   // the K scored already are marked by a bit of their candidate word
-            for (int32_t i = threadIdx.x; i < n_first; i += blockDim.x) cand[need[i]] |= (int32_t)0x80000000;
-            __syncthreads();
-        }
-        for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
-            if (cand[t] < 0) { cand[t] &= 0x7fffffff; continue; }
+        // What is scored first: everything from a line on that at least K scores and bounds reach, and a quarter more, since a bound
+        // may lie far above its score (from T on, where the list is full).
+        uint32_t mine[3] = {0u, 0u, 0u}, lo = 0xffffffffu, hi = 0u;
+        static_assert(AP_MAXC <= 3 * 512, "candidates of a thread");
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int32_t t = threadIdx.x + 512 * k;
+            if (t >= cnt) continue;
             float bd, bf;
             bound(t, bd, bf);
-            if (!(bf < T) || !(bd < dP)) need[atomicAdd(&s_need, 1)] = (uint16_t)t;
-            else cand[t] |= (int32_t)0x80000000;   // its dense part is not computed
+            if (bf < T) continue;
+            const uint32_t o = ap_f2ord(bf);
+            mine[k] = o ? o : 1u;   // 0: not to be scored first (no bound of a score has the lowest code)
+            lo = min(lo, mine[k]); hi = max(hi, mine[k]);
+        }
+        for (int32_t t = threadIdx.x; t < n_old; t += 512) {
+            const uint32_t o = (uint32_t)(keys[t] >> 32);
+            lo = min(lo, o); hi = max(hi, o);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+            hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+        }
+        if (lane == 0) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
+        __syncthreads();
+        lo = ap_uniform_u32(s_lo); hi = ap_uniform_u32(s_hi);
+        int sh = 0;
+        while (lo < hi && ((hi - lo) >> sh) >= AP_RF_BINS) sh++;
+        auto count = [&](uint32_t o) { atomicAdd(&hist[(min(max(o, lo), hi) - lo) >> sh], 1u); };
+        // wave 0: the lower edge of the bin from which on at least `least` are counted, and where all are fewer, but `enough`, of the last bin; 0xffffffff:
+        // fewer than that
+        auto edge = [&](uint32_t least, uint32_t enough) {
+            constexpr int PER = AP_RF_BINS / 64;   // lane l: bins 16 (63 - l) .. + 15, so that the prefix sum runs from the top
+            uint32_t n = 0;
+            for (int b = 0; b < PER; b++) n += hist[PER * (63 - lane) + b];
+            uint32_t upto = n;
+            for (int o = 1; o < 64; o <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)upto, o, 64); if (lane >= o) upto += up; }
+            const uint64_t m = __ballot(upto >= least);
+            if (m == 0ull) { if (lane == 63) s_line = upto >= enough ? lo : 0xffffffffu; }
+            else if (lane == (int)__ffsll((unsigned long long)m) - 1) {
+                uint32_t above = upto - n;
+                int b = PER * (63 - lane) + PER - 1;
+                for (; above + hist[b] < least; b--) above += hist[b];
+                s_line = lo + ((uint32_t)b << sh);
+            }
+        };
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+            if (mine[k]) count(mine[k]);
+        for (int32_t t = threadIdx.x; t < n_old; t += 512) count((uint32_t)(keys[t] >> 32));
+        __syncthreads();
+        if (wave == 0) edge((uint32_t)(K + AP_RF_MORE(K)), (uint32_t)K);
+        __syncthreads();
+        const uint32_t line = ap_uniform_u32(s_line);
+        for (int i = threadIdx.x; i < AP_RF_BINS; i += 512) hist[i] = 0;
+        if (line != 0xffffffffu) {
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const int32_t t = threadIdx.x + 512 * k;
+                if (mine[k] && mine[k] >= line) {
+                    const int32_t at = atomicAdd(&s_need, 1);
+                    need[at] = (uint16_t)t;
+                    cand[t] |= AP_RF_FIRST;
+                    if (packed) { const uint4 m = meta[cand[t] & (AP_RF_TOP - 1)]; where[at] = make_uint2(m.x, m.y); }
+                }
+            }
         }
         __syncthreads();
-        dense_rows(n_first, ap_uniform_i32(s_need), 0);
+        const int32_t n_first = ap_uniform_i32(s_need);
+        score(0, n_first);
+        __syncthreads();
+        if (line != 0xffffffffu) {   // T: the lower edge of the bin that the K-th best score so far lies in
+            const int32_t nk = ap_uniform_i32(s_nk);
+            for (int32_t t = threadIdx.x; t < nk; t += 512) {
+                const uint32_t o = (uint32_t)(keys[t] >> 32);
+                if (o >= lo) count(o);
+            }
+            __syncthreads();
+            if (wave == 0) edge((uint32_t)K, 0xffffffffu);
+            __syncthreads();
+            const uint32_t at = ap_uniform_u32(s_line);
+            if (at != 0xffffffffu) T = fmaxf(T, ap_ord2f(at));
+        }
+        if (!later) {
+            // first round: the P-th best list parts of what was scored first (equal ones drawn once: no more than that)
+            if (wave == 1 || wave == 2) {
+                constexpr int PER = 4;
+                uint32_t o[PER];
+#pragma unroll
+                for (int j = 0; j < PER; j++) o[j] = j * 64 + lane < n_first ? ap_f2ord(comp[wave][need[j * 64 + lane]]) : 0u;
+                uint32_t prev = 0xffffffffu;
+                for (int32_t r = 0; r < P && prev; r++) {
+                    uint32_t best = 0;
+#pragma unroll
+                    for (int j = 0; j < PER; j++)
+                        if (o[j] < prev) best = max(best, o[j]);
+                    for (int s = 32; s > 0; s >>= 1) best = max(best, (uint32_t)__shfl_xor((int)best, s, 64));
+                    prev = best;
+                }
+                if (lane == 0) s_last[wave] = prev ? ap_ord2f(prev) : -INFINITY;
+            }
+            __syncthreads();
+            last[0] = P <= K && n_own >= P ? s_last[0] : -INFINITY;
+            last[1] = s_last[1]; last[2] = s_last[2];
+        }
+        for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
+            if (cand[t] < 0) { cand[t] &= ~AP_RF_FIRST; continue; }
+            float bd, bf;
+            bound(t, bd, bf);
+            const bool whole = !(bf < T) || !(bd < last[0]);
+            if (whole || !(comp[1][t] < last[1]) || !(comp[2][t] < last[2])) {
+                const int32_t at = whole ? atomicAdd(&s_need, 1) : AP_MAXC - 1 - atomicAdd(&s_lists, 1);
+                need[at] = (uint16_t)t;
+                if (packed) { const uint4 m = meta[cand[t] & ~AP_RF_TOP]; where[at] = make_uint2(m.x, m.y); }
+            }
+        }
+        __syncthreads();
+        score(n_first, ap_uniform_i32(s_need));
+        if (packed) score_lists(ap_uniform_i32(s_lists));
     }
     __syncthreads();
     // top-K under the fused score: the keys (all different: a key carries its id) sorted in LDS.  What was left out above
     // ranks after K of them.
-    const int32_t nk = ap_uniform_i32(s_nk);
+    const int32_t nk = ap_uniform_i32(s_nk), n_whole = ap_uniform_i32(s_need);
     int32_t n2 = 64;
     while (n2 < nk) n2 <<= 1;   // uniform; nk <= K + S*S <= AP_MAXC <= 2048
     for (int32_t t = nk + threadIdx.x; t < n2; t += blockDim.x) keys[t] = 0ull;
@@ -1229,13 +1448,18 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
         const uint64_t m = __ballot(lane < sl && lane < nk && (keys[lane < n2 ? lane : 0] & 1ull));
         if (lane == 0) hint.known_out[x] = (uint32_t)m;
     }
-    // per-path lists: the best P by each single similarity among this round's candidates and the previous list.  One wave
+    // per-path lists: the best P by each single similarity among what was scored and the previous list (with hints, what was not
+    // ranks after a full list's last entry, or after P of what was scored first).  One wave
     // per path, on its own: every lane keeps its share of the keys in registers and the P best are drawn one after the
     // other by wave-wide maxima (no block-wide pass, no barrier).
     if (wave < 3) {
         const int p = wave;
         const int32_t nold = (int32_t)__popcll(__ballot(lane < 32 && oldk[p][lane & 31] != 0ull));
-        auto cand_key = [&](int32_t t) { return p == 0 && cand[t] < 0 ? 0ull : ap_make_key(comp[p][t], cand[t] & 0x3fffffff, 1u); };
+        auto cand_key = [&](int32_t e) {
+            const int32_t t = need[e < n_whole ? e : AP_MAXC - 1 - (e - n_whole)];
+            return ap_make_key(comp[p][t], cand[t] & (AP_RF_TOP - 1), 1u);
+        };
+        const int32_t n_scored = n_whole + (p ? ap_uniform_i32(s_lists) : 0);
         uint64_t prev = ~0ull;
         auto put = [&](int32_t r, uint64_t best) {
             for (int o = 32; o > 0; o >>= 1) {
@@ -1252,8 +1476,8 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
             // a full list: what can enter is what beats its last entry, usually few enough for one key a lane
             const uint64_t last = oldk[p][P - 1];
             int32_t nb = 0;
-            for (int32_t t0 = 0; t0 < cnt; t0 += 64) {
-                const uint64_t key = t0 + lane < cnt ? cand_key(t0 + lane) : 0ull;
+            for (int32_t t0 = 0; t0 < n_scored; t0 += 64) {
+                const uint64_t key = t0 + lane < n_scored ? cand_key(t0 + lane) : 0ull;
                 const uint64_t m = __ballot(key > last);
                 const int32_t at = nb + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
                 if (key > last && at < 64) better[p][at] = key;
@@ -1266,20 +1490,24 @@ __global__ __launch_bounds__(512) void k_refine(ApVecs D, const uint2 *__restric
                 return;
             }
         }
-        constexpr int PER = (AP_MAXC + 32 + 63) / 64;
-        uint64_t mine[PER];
+        auto draw = [&](auto per) {
+            constexpr int PER = decltype(per)::value;
+            uint64_t key[PER];
 #pragma unroll
-        for (int j = 0; j < PER; j++) {
-            const int32_t t = j * 64 + lane;
-            mine[j] = t < cnt ? cand_key(t) : (t < cnt + nold ? oldk[p][t - cnt] : 0ull);
-        }
-        for (int32_t r = 0; r < P; r++) {
-            uint64_t best = 0;
+            for (int j = 0; j < PER; j++) {
+                const int32_t t = j * 64 + lane;
+                key[j] = t < n_scored ? cand_key(t) : (t < n_scored + nold ? oldk[p][t - n_scored] : 0ull);
+            }
+            for (int32_t r = 0; r < P; r++) {
+                uint64_t best = 0;
 #pragma unroll
-            for (int j = 0; j < PER; j++)
-                if (mine[j] < prev && mine[j] > best) best = mine[j];
-            put(r, best);
-        }
+                for (int j = 0; j < PER; j++)
+                    if (key[j] < prev && key[j] > best) best = key[j];
+                put(r, best);
+            }
+        };
+        if (n_scored + nold <= 6 * 64) draw(std::integral_constant<int, 6>());
+        else draw(std::integral_constant<int, (AP_MAXC + 32 + 63) / 64>());
     }
 }
 
@@ -1315,14 +1543,16 @@ int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, i
         hipLaunchKernelGGL(k_take_tau, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc[0], n, K, 0u, tau);
         if (hipGetLastError() != hipSuccess) { ap_set_error("refinement failed to start"); rc = AP_EHIP; }
     }
+    ApPacked pk;
+    if (rc == AP_OK) rc = ap_pack_lists(ix, st, &pk);
     for (int32_t t = 0; t < rounds && rc == AP_OK; t++) {
         const int c = *cur;
-        const ApRefineHints hint = t == 0 ? ApRefineHints{tau, sc[c], nullptr, nullptr, known[0]}
-                                          : ApRefineHints{tau, nullptr, sc[c], known[(t - 1) & 1], known[t & 1]};
+        const ApRefineHints hint = t == 0 ? ApRefineHints{tau, sc[c], nullptr, nullptr, known[0], pk.rec, pk.at}
+                                          : ApRefineHints{tau, nullptr, sc[c], known[(t - 1) & 1], known[t & 1], pk.rec, pk.at};
         rc = ap_refine_round(ix, K, S, P, ids[c], spi[c], sps[c], nullptr, n, ids[1 - c], sc[1 - c], spi[1 - c], sps[1 - c], hint, st);
         *cur = 1 - c;
     }
-    void *ptrs[] = {tau, known[0], known[1]};
+    void *ptrs[] = {tau, known[0], known[1], pk.mem};
     for (void *p : ptrs) if (p) (void)hipFree(p);   // waits for the rounds
     return rc;
 }
@@ -1335,7 +1565,7 @@ extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t
     if (!node_ids) nn = ix->docs.n;
     if (nn <= 0) return AP_OK;
     return ap_refine_round(ix, K, S, P, knn_ids, sp_ids, sp_sc, node_ids, nn, out_ids, out_sc, out_sp_ids, out_sp_sc,
-                           ApRefineHints{nullptr, nullptr, nullptr, nullptr, nullptr}, (hipStream_t)stream);
+                           ApRefineHints{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr}, (hipStream_t)stream);
 }
 
 // =================================================================== S4: neighbourhood similarities

@@ -88,6 +88,7 @@ struct ap_index {
     float *w_dev = nullptr;    // 3 floats: device copy of w_default
     // what the upper bounds of the scores are computed from (ap_bound.hip): one allocation, the parts below point into it
     void *bd_mem = nullptr;
+    int32_t *bd_df = nullptr;          // document frequencies of the learned-sparse terms
     uint16_t *bd_rows = nullptr;       // n x (bd_kd + bd_kh) bf16: dense part where bd_kd > 0, then the head columns
     int32_t bd_kd = 0, bd_kh = 0;      // columns of a copied dense part (0: the corpus's own rows serve), head columns
     int32_t *bd_col = nullptr;         // per term (learned-sparse vocabulary, then lexical): its head column or -1
@@ -171,6 +172,7 @@ struct ApStageEvents {
 };
 
 int ap_validate_corpus(const ap_corpus *c);
+int ap_df_histogram(const int32_t *df_sp, int32_t nsp, const int32_t *df_tx, int32_t ntx, int32_t *hist, hipStream_t st);
 int ap_validate_params(const ap_build_params *p);
 int ap_ingest_impl(ap_index *ix, int bounds_share, hipStream_t st);
 int ap_count_terms(const int32_t *idx, const float *tf, int64_t nnz, int32_t *df, unsigned long long *total, hipStream_t st);
@@ -380,6 +382,13 @@ __device__ __forceinline__ void ap_wave_sum2(float a, float b, float &sa, float 
 }
 
 #define AP_LDS __attribute__((address_space(3)))
+
+// eight bins an octave of the document frequency
+__device__ __forceinline__ int ap_df_bin(int32_t df) {
+    if (df <= 0) return -1;
+    const int b = (int)(8.f * log2f((float)df));
+    return b > 255 ? 255 : b;
+}
 
 // Orders one wave's LDS traffic: what any lane wrote before this point is what every lane of the wave reads after it.
 // The barrier alone only pins the instruction schedule; the fence is what keeps the compiler from moving or caching

@@ -1,0 +1,69 @@
+"""The rounds of a construction tell by packed lists (three bytes an entry, weights rounded up to 8 bits, rare terms sharing slots)
+which candidates can enter a list.  The lists must stay those of rounds that score every candidate, bit for bit: nothing is rounded
+but the bounds."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00855_amd import binding as B
+from paper_2511_00855_amd.synth import make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _negative(d, rng):   # such a list has no bound; nodes that hold one read every record
+    rows = rng.random(d.n) < 0.3
+    d.sp_val[np.repeat(rows, np.diff(d.sp_indptr)) & (rng.random(len(d.sp_val)) < 0.5)] *= -1
+
+
+def _far_apart(d, rng):   # one weight decides a list's scale
+    d.sp_val[:] = 10.0 ** rng.uniform(-30, 3, len(d.sp_val))
+    d.sp_val[rng.random(len(d.sp_val)) < 0.2] = 0.0
+
+
+def _beyond(d, rng):   # products of two such weights overflow
+    d.sp_val[rng.random(len(d.sp_val)) < 0.01] = 3e38
+
+
+def _alike(d, rng):   # nothing to tell candidates apart by
+    d.sp_val[:], d.tx_val[:] = 1.0, 1.0
+    d.dense[:] = d.dense[0]
+
+
+SP, TX = ("poisson", 100), ("lognormal", 60)
+CASES = {   # name: (workload, K, S, P, build weights, what is done to the documents)
+    "ordinary": (dict(n=1300, sp=SP, tx=TX), 128, 32, 11, (1.0, 1.0, 1.0), None),
+    "rare terms share slots": (dict(n=1500, vocab=200_000, sp=SP, tx=TX), 64, 32, 11, (1.0, 1.0, 1.0), None),
+    "units beyond three a lane": (dict(n=500, sp=("fixed", 131), tx=("fixed", 120)), 32, 24, 6, (1.0, 1.0, 1.0), None),
+    "empty and short lists": (dict(n=700, sp=("poisson", 1), tx=("fixed", 5)), 32, 32, 32, (1.0, 1.0, 1.0), None),
+    "negative weights": (dict(n=900, sp=SP, tx=TX), 64, 32, 11, (1.0, 1.0, 1.0), _negative),
+    "weights far apart": (dict(n=900), 64, 32, 11, (1.0, 1.0, 1.0), _far_apart),
+    "sums beyond the range": (dict(n=600), 32, 32, 8, (1.0, 1.0, 1.0), _beyond),
+    "documents alike": (dict(n=600, sp=("fixed", 20), tx=("fixed", 20)), 48, 32, 11, (1.0, 1.0, 1.0), _alike),
+    "negative weight of a path": (dict(n=700), 32, 32, 8, (0.5, -1.0, 1.0), None),
+    "lexical part alone": (dict(n=1100, sp=SP, tx=TX), 96, 32, 16, (0.0, 0.0, 1.0), None),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_packed_lists_change_no_list(name):
+    kw, K, S, P, wv, change = CASES[name]
+    w = make_workload("tiny", seed=11, nq=2, **kw)
+    d = w.docs
+    if change:
+        change(d, np.random.default_rng(4))
+    docs = B.DeviceVecs(d)
+    print(name, flush=True)
+    bp = B.build_params(16, knn_k=K, nd_rounds=3, nd_sample=S, sp_len=P, n_entry=4, build_w=wv)
+    full = B.Index.build(docs, bp)
+    _, srt, spi, sps = full.export_build_state()
+    ix = B.Index.ingest(docs, bp)
+    ids, sc = ix.stage_seed_knn(K)
+    i2 = torch.full((3, d.n, P), -1, dtype=torch.int32, device=docs.device)
+    s2 = torch.full((3, d.n, P), -np.inf, dtype=torch.float32, device=docs.device)
+    for _ in range(3):
+        ids, sc, i2, s2 = ix.stage_refine(K, S, P, ids, i2, s2)
+    g = ix.stage_prune(K, 16, ids, sc, want_pm=False)
+    assert torch.equal(spi, i2) and torch.equal(sps.view(torch.int32), s2.view(torch.int32))
+    assert torch.equal(srt, g["sorted_ids"])
+    full.close(); ix.close()
