@@ -949,10 +949,10 @@ struct ApRefineHints {
 // 153 ms, 4 and 2: 150 ms, 4 and 4: 150 ms, 8 and 2: 151 ms).
 #define AP_RF_G 4
 #define AP_RF_GD 2
-#define AP_RF_GP 2               // packed records a group of 16 lanes has on their way
-#define AP_RF_BINS 1024          // bins of the histogram that says what is scored first
+#define AP_RF_GP 2               // packed records a group of 16 lanes has on their way, twice
+#define AP_RF_BINS 512           // bins of the histogram that says what is scored first
 #define AP_RF_TOP 0x40000000     // bit of a candidate that is among the first S entries of the node's own list (ids have 30 bits)
-#define AP_RF_MORE(K) ((K) / 6)   // scored first beyond K (three rounds, 100,000 f32 and 200,000 bf16 documents: K / 4: 55.1 and 105.6 ms, K / 6: 53.8 and 105.1; less, and a bound far above its score makes T so low that the first bf16 round takes a tenth longer)
+#define AP_RF_MORE(K) ((K) / 6)   // scored first beyond K (three rounds, 100,000 f32 and 200,000 bf16 documents: K / 4: 55.1 and 105.6 ms, K / 6: 53.8 and 105.1)
 #define AP_RF_FIRST ((int32_t)0x80000000)   // bit of a candidate that is scored first
 
 // One refinement round for one node.  What bounds it: the candidates' bytes (record and dense row) and the instructions
@@ -972,9 +972,13 @@ struct ApRefineHints {
 //    5/4 K of them reach; those are scored first, and a histogram of the scores gives T, which K of them reach and so the new
 //    list's last entry does.  After that only candidates are scored whose bounds reach T, or the last entry of a per-path list (in the first
 //    round, where those are empty: the P-th best of what was scored first).
-// Phases: packed records of all candidates (16 lanes each; without packed lists the records themselves, a wave each), the
-// histogram, records and dense rows of what is scored first, a thread per candidate decides about the others, their
-// records and dense rows, sort, lists.
+// Phases: packed records of all candidates (16 lanes each, the next ones on their way; without packed lists the records themselves,
+// a wave each), the histograms, records and dense rows of what is scored first, a thread per candidate decides about the others, their
+// records and dense rows, the lists by counting what ranks before each entry.  With two workgroups a CU the short phases between the reads are
+// what is left to hide: what a node needs of itself is requested at the start, one wave builds its tables while the others read, no
+// list is sorted.  Three rounds on 200,000 documents of 1,024 bf16 columns: 308 ms with every candidate scored in full, 150 with the
+// first and third of the above, 105 with all four, 89 with the short phases cut; 100,000 of 768 f32 columns: 202, 81, 54 and 49 ms
+// (the first round reads 1.6 MB a node, 8 TB/s).
 template <int DT, int NV>
 __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__restrict__ rec, const uint4 *__restrict__ meta, float wd,
                                                 float ws, float wf, int32_t K, int32_t S, int32_t P,
@@ -1002,75 +1006,55 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
     __shared__ uint64_t oldk[3][32];
     __shared__ __attribute__((aligned(16))) uint64_t qtab[(1 << AP_RT_SPB) + (1 << AP_RT_TXB)];
     __shared__ uint16_t need[AP_MAXC];        // from the front: candidates that are scored in full; from the back: those whose list parts alone are
-    __shared__ int32_t s_cnt, s_seed[2], s_nk, s_need, s_lists;
-    __shared__ uint32_t s_lo, s_hi, s_line;
+    __shared__ int32_t first_ids[32];
+    __shared__ int32_t s_cnt, s_seed[2], s_nk, s_need, s_lists, s_next;
+    __shared__ uint32_t s_lo, s_hi, s_line, s_known;
     __shared__ float s_last[3];
     const int64_t x = x0 + blockIdx.x;   // the launch covers nodes x0 .. x0 + gridDim.x of the nn
     const int64_t u = node_ids ? (int64_t)node_ids[x] : x;
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
     constexpr int NW = 8;
     const bool fast = hint.tau != nullptr, later = hint.knn_sc != nullptr;   // uniform
-    const ApLists a = ap_stage_lists(D, u, l_sp_idx, l_sp_val, l_tx_idx, l_tx_val, AP_A_CAP);
-    float qa[NV * ApDense<DT>::EPC];
-    ap_load_aside<DT, NV, DT>(D.dense, u, D.dim, qa);
-    for (int i = threadIdx.x; i < AP_HT; i += blockDim.x) ht[i] = -1;
-    // the node's own lists as bucket tables with a hash multiplier of their own (the usual case: one 16-byte read per
-    // look-up, as in the search); lists that are longer, or that no multiplier fits, are searched where they lie
-    bool use_tab = a.sp_n <= (1 << AP_RT_SPB) / 4 && a.tx_n <= (1 << AP_RT_TXB) / 4;   // uniform
-    uint32_t msp = 0, mtx = 0;
-    if (threadIdx.x == 0) { s_cnt = 0; s_nk = 0; s_need = 0; s_lists = 0; s_lo = 0xffffffffu; s_hi = 0u; }
-    __syncthreads();
-    if (use_tab && wave == 0) {
-        const int32_t s0 = ap_bucket_build<4>(a.sp_idx, a.sp_val, a.sp_n, qtab, AP_RT_SPB);
-        const int32_t s1 = ap_bucket_build<2>(a.tx_idx, a.tx_val, a.tx_n, qtab + (1 << AP_RT_SPB), AP_RT_TXB);
-        if (lane == 0) { s_seed[0] = s0; s_seed[1] = s1; }
-    }
-    // candidates: the node's own list (in later rounds its scores are at hand: it only stays out of the candidates) ...
-    const int32_t sl = S < K ? S : K;
-    for (int32_t s = threadIdx.x; s < K; s += blockDim.x) {
-        const int32_t v = knn[u * K + s];
-        if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v) && !later) {
-            const int32_t at = atomicAdd(&s_cnt, 1);
-            cand[fast ? s : at] = v | (s < sl ? AP_RF_TOP : 0);   // a seed list's members are distinct and lead the list: candidate s is member s
-        }
-    }
-    __syncthreads();
-    if (use_tab) {
-        const int32_t seed0 = ap_uniform_i32(s_seed[0]), seed1 = ap_uniform_i32(s_seed[1]);
-        use_tab = seed0 >= 0 && seed1 >= 0;
-        if (use_tab) { msp = ap_seed_mult(seed0); mtx = ap_seed_mult(seed1); }
-    }
-    const int32_t n_own = ap_uniform_i32(s_cnt);   // candidates of the node's own list (0 in later rounds)
-    __syncthreads();
-    // ... and the first S neighbours of the first S neighbours
-    {
-        const uint32_t mine = later ? hint.known[u] : 0u;
-        for (int32_t s = threadIdx.x; s < sl * sl; s += blockDim.x) {
-            const int32_t i = s / sl, j = s % sl;
-            const int32_t p = knn[u * K + i];
-            if (p < 0) continue;
-            if ((mine >> i) & 1u && (hint.known[p] >> j) & 1u) continue;   // scored for this node in an earlier round
-            const int32_t v = knn[(int64_t)p * K + j];
-            if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v)) cand[atomicAdd(&s_cnt, 1)] = v;
-        }
-    }
-    __syncthreads();
-    const int32_t cnt = ap_uniform_i32(s_cnt);
-    if (threadIdx.x == 0 && n_sims) atomicAdd(n_sims, (unsigned long long)cnt);   // measurement: similarities of this node and round
-    // the node's own scales; a list that has none (a negative value) has no bounds either
-    float own_sp = 0.f, own_tx = 0.f;
+    // what later phases need of the node itself is requested now: its packed lists (a unit a thread, four threads a unit), the first
+    // neighbours of its list, its per-path lists
     uint2 own_at = make_uint2(0, 0);
+    ApPkUnit own_unit = {0, 0, 0};
+    float own_sp = 0.f, own_tx = 0.f;
+    int32_t own_entries = 0;
     bool packed = hint.pk != nullptr;   // uniform
     if (packed) {
         own_at = hint.pk_at[u];
-        const uint32_t *r = hint.pk + (size_t)own_at.x * (AP_PK_LINE / 4);
-        own_sp = __uint_as_float(r[0]); own_tx = __uint_as_float(r[1]);
-        packed = own_sp < INFINITY && own_tx < INFINITY;
+        const ApPkUnit *r = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)own_at.x * (AP_PK_LINE / 4));
+        own_entries = 4 * (int32_t)((own_at.y & 0xffffu) + (own_at.y >> 16));
+        own_unit = r[(int)threadIdx.x < own_entries ? 1 + ((int)threadIdx.x >> 2) : 0];
+        own_sp = __uint_as_float(r[0].w); own_tx = __uint_as_float(r[0].s01);
+        packed = own_sp < INFINITY && own_tx < INFINITY;   // a list without a scale (a negative value) has no bounds
     }
-    // where each candidate's record lies and how long it is, fetched for all candidates at once, so that the scoring loop
-    // starts its loads without a round trip of its own
-    for (int32_t t = threadIdx.x; t < cnt; t += blockDim.x) {
-        const int32_t v = cand[t] & ~AP_RF_TOP;
+    int32_t old_id = -1;
+    float old_sc = 0.f;
+    if (wave < 3 && lane < P) {
+        old_id = sp_ids[((int64_t)wave * D.n + u) * P + lane];
+        old_sc = sp_sc[((int64_t)wave * D.n + u) * P + lane];
+    }
+    const ApLists a = ap_stage_lists(D, u, l_sp_idx, l_sp_val, l_tx_idx, l_tx_val, AP_A_CAP);
+    float qa[NV * ApDense<DT>::EPC];
+    ap_load_aside<DT, NV, DT>(D.dense, u, D.dim, qa);
+    for (int i = threadIdx.x; i < AP_HT / 4; i += blockDim.x) reinterpret_cast<int4 *>(ht)[i] = make_int4(-1, -1, -1, -1);
+    if (threadIdx.x == 0) { s_cnt = 0; s_nk = 0; s_need = 0; s_lists = 0; s_next = 0; s_known = 0u; s_lo = 0xffffffffu; s_hi = 0u; s_last[0] = s_last[1] = s_last[2] = -INFINITY; }
+    __syncthreads();
+    // the node's own lists as bucket tables with a hash multiplier of their own (the usual case: one 16-byte read per
+    // look-up, as in the search); lists that are longer, or that no multiplier fits, are searched where they lie.  One wave
+    // builds them; they are there after the next barrier.
+    auto build_tables = [&]() {
+        const bool fits = a.sp_n <= (1 << AP_RT_SPB) / 4 && a.tx_n <= (1 << AP_RT_TXB) / 4;
+        const int32_t s0 = fits ? ap_bucket_build<4>(a.sp_idx, a.sp_val, a.sp_n, qtab, AP_RT_SPB) : -1;
+        const int32_t s1 = fits ? ap_bucket_build<2>(a.tx_idx, a.tx_val, a.tx_n, qtab + (1 << AP_RT_SPB), AP_RT_TXB) : -1;
+        if (lane == 0) { s_seed[0] = s0; s_seed[1] = s1; }
+    };
+    if (!packed && wave == NW - 1) build_tables();
+    // a candidate, and where its record lies and how long it is, so that the scoring loop starts its loads without a round trip of its own
+    auto put_candidate = [&](int32_t t, int32_t v, int32_t mark) {
+        cand[t] = v | mark;
         if (packed) {
             const uint2 m = hint.pk_at[v];
             comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y);
@@ -1078,65 +1062,105 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
             const uint4 m = meta[v];
             comp[0][t] = __uint_as_float(m.x); comp[1][t] = __uint_as_float(m.y); comp[2][t] = __uint_as_float(m.z);
         }
+    };
+    // candidates: the node's own list (in later rounds its scores are at hand: it only stays out of the candidates) ...
+    const int32_t sl = S < K ? S : K;
+    for (int32_t s = threadIdx.x; s < K; s += blockDim.x) {
+        const int32_t v = knn[u * K + s];
+        if (s < sl) first_ids[s] = v;
+        if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v) && !later) {
+            const int32_t at = atomicAdd(&s_cnt, 1);
+            put_candidate(fast ? s : at, v, s < sl ? AP_RF_TOP : 0);   // a seed list's members are distinct and lead the list: candidate s is member s
+        }
     }
+    __syncthreads();
+    const int32_t n_own = ap_uniform_i32(s_cnt);   // candidates of the node's own list (0 in later rounds)
+    __syncthreads();
+    // ... and the first S neighbours of the first S neighbours
+    {
+        const uint32_t mine = later ? hint.known[u] : 0u;
+        for (int32_t s = threadIdx.x; s < sl * sl; s += blockDim.x) {
+            const int32_t i = s / sl, j = s % sl;
+            const int32_t p = first_ids[i];
+            if (p < 0) continue;
+            const int32_t v = knn[(int64_t)p * K + j];
+            if ((mine >> i) & 1u && (hint.known[p] >> j) & 1u) continue;   // scored for this node in an earlier round
+            if (v >= 0 && v != (int32_t)u && ap_ht_insert(ht, v)) put_candidate(atomicAdd(&s_cnt, 1), v, 0);
+        }
+    }
+    __syncthreads();
+    const int32_t cnt = ap_uniform_i32(s_cnt);
+    if (threadIdx.x == 0 && n_sims) atomicAdd(n_sims, (unsigned long long)cnt);   // measurement: similarities of this node and round
     // the per-path lists so far, in keys (entries scored again in a round that scores everything are left out: there the
     // caller's scores need not be this kernel's)
     if (wave < 3) {
-        uint64_t ok = 0;
-        bool have = false;
-        if (lane < P) {
-            const int32_t id = sp_ids[((int64_t)wave * D.n + u) * P + lane];
-            if (id >= 0 && (fast || !ap_ht_has(ht, id))) { have = true; ok = ap_make_key(sp_sc[((int64_t)wave * D.n + u) * P + lane], id, 1u); }
-        }
+        const bool have = old_id >= 0 && (fast || !ap_ht_has(ht, old_id));
         const uint64_t hm = __ballot(have);
         if (lane < 32) oldk[wave][lane] = 0ull;
         ap_wave_sync();
-        if (have) oldk[wave][__popcll(hm & ((1ull << lane) - 1ull))] = ok;
+        if (have) oldk[wave][__popcll(hm & ((1ull << lane) - 1ull))] = ap_make_key(old_sc, old_id, 1u);
     }
     __syncthreads();   // the hash set is done with
+    bool use_tab = false;   // uniform
+    uint32_t msp = 0, mtx = 0;
+    auto take_tables = [&]() {
+        const int32_t seed0 = ap_uniform_i32(s_seed[0]), seed1 = ap_uniform_i32(s_seed[1]);
+        use_tab = seed0 >= 0 && seed1 >= 0;
+        if (use_tab) { msp = ap_seed_mult(seed0); mtx = ap_seed_mult(seed1); }
+    };
+    if (!packed) take_tables();
     // the sparse and lexical parts of all candidates, or bounds of them
     if (packed) {
         for (int32_t i = threadIdx.x; i < AP_PK_SLOTS / 16; i += blockDim.x) reinterpret_cast<uint4 *>(pool)[i] = make_uint4(0, 0, 0, 0);
         __syncthreads();
-        {
-            const ApPkUnit *r = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)own_at.x * (AP_PK_LINE / 4));
-            const int32_t entries = 4 * (int32_t)((own_at.y & 0xffffu) + (own_at.y >> 16));
-            for (int32_t i = threadIdx.x; i < entries; i += blockDim.x) {
-                const ApPkUnit d = r[1 + (i >> 2)];
-                const uint32_t at = ((i & 2 ? d.s23 : d.s01) >> (16 * (i & 1))) & 0xffffu, w = (d.w >> (8 * (i & 3))) & 255u;
-                if (w) atomicOr(&pool[at >> 2], w << (8 * (at & 3u)));   // two terms of one slot: at least the larger of them
-            }
-        }
+        auto put_own = [&](const ApPkUnit &d, int32_t i) {
+            const uint32_t at = ((i & 2 ? d.s23 : d.s01) >> (16 * (i & 1))) & 0xffffu, w = (d.w >> (8 * (i & 3))) & 255u;
+            if (w) atomicOr(&pool[at >> 2], w << (8 * (at & 3u)));   // two terms of one slot: at least the larger of them
+        };
+        const ApPkUnit *own = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)own_at.x * (AP_PK_LINE / 4));
+        if ((int)threadIdx.x < own_entries) put_own(own_unit, threadIdx.x);
+        for (int32_t i = threadIdx.x + 512; i < own_entries; i += 512) put_own(own[1 + (i >> 2)], i);
         __syncthreads();
         constexpr int G = AP_RF_GP, U = 3;
         const AP_LDS uint8_t *tab = (const AP_LDS uint8_t *)pool;
         const int sub = lane >> 4, l16 = lane & 15;
         own_sp *= 1.00004f; own_tx *= 1.00004f;   // what the sums of the scoring kernels may round up
-        for (int32_t i0 = wave * 4 * G; i0 < cnt; i0 += NW * 4 * G) {
-            ApPkUnit d[G][U];
-            const ApPkUnit *r[G];
-            int32_t nsp[G], units[G];
+        if (wave == NW - 1) build_tables();   // the others begin without it: 4 G candidates at a time go to the wave that asks
+        auto ask = [&]() {
+            int32_t i = 0;
+            if (lane == 0) i = atomicAdd(&s_next, 4 * G);
+            return ap_uniform_i32(i);
+        };
+        ApPkUnit d[2][G][U];
+        uint32_t len[2][G];
+        auto load = [&](int32_t i0, ApPkUnit (&d)[G][U], uint32_t (&len)[G]) {
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 const int32_t i = i0 + 4 * g + sub;
-                const uint32_t line = i < cnt ? __float_as_uint(comp[0][i]) : own_at.x, len = i < cnt ? __float_as_uint(comp[1][i]) : 0u;
-                r[g] = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)line * (AP_PK_LINE / 4));
-                nsp[g] = (int32_t)(len & 0xffffu); units[g] = 1 + nsp[g] + (int32_t)(len >> 16);
+                const uint32_t line = i < cnt ? __float_as_uint(comp[0][i]) : own_at.x;   // past the end: unit 0 of the node's own record, for nothing
+                len[g] = i < cnt ? __float_as_uint(comp[1][i]) : 0u;
+                const ApPkUnit *r = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)line * (AP_PK_LINE / 4));
+                const int32_t units = 1 + (int32_t)((len[g] & 0xffffu) + (len[g] >> 16));
 #pragma unroll
-                for (int j = 0; j < U; j++) d[g][j] = r[g][l16 + 16 * j < units[g] ? l16 + 16 * j : 0];
+                for (int j = 0; j < U; j++) d[g][j] = r[l16 + 16 * j < units ? l16 + 16 * j : 0];
             }
+        };
+        auto sum = [&](int32_t i0, const ApPkUnit (&d)[G][U], const uint32_t (&len)[G]) {
 #pragma unroll
             for (int g = 0; g < G; g++) {
-                const int32_t i = i0 + 4 * g + sub;
+                const int32_t i = i0 + 4 * g + sub, nsp = (int32_t)(len[g] & 0xffffu), units = 1 + nsp + (int32_t)(len[g] >> 16);
                 uint32_t ps = 0, pf = 0;
                 auto add = [&](const ApPkUnit &e, int32_t at) {
                     const uint32_t p = ap_pk_dot(tab, e);
-                    ps += at >= 1 && at <= nsp[g] ? p : 0u;
-                    pf += at > nsp[g] && at < units[g] ? p : 0u;
+                    ps += at >= 1 && at <= nsp ? p : 0u;
+                    pf += at > nsp && at < units ? p : 0u;
                 };
 #pragma unroll
                 for (int j = 0; j < U; j++) add(d[g][j], l16 + 16 * j);
-                for (int32_t at = l16 + 16 * U; __any(at < units[g]); at += 16) add(r[g][at < units[g] ? at : 0], at);
+                if (__any(units > 16 * U)) {
+                    const ApPkUnit *r = reinterpret_cast<const ApPkUnit *>(hint.pk + (size_t)(i < cnt ? __float_as_uint(comp[0][i]) : own_at.x) * (AP_PK_LINE / 4));
+                    for (int32_t at = l16 + 16 * U; __any(at < units); at += 16) add(r[at < units ? at : 0], at);
+                }
                 float fs = (float)ps, ff = (float)pf;
                 fs += ap_dpp<0xB1>(fs); ff += ap_dpp<0xB1>(ff);
                 fs += ap_dpp<0x4E>(fs); ff += ap_dpp<0x4E>(ff);
@@ -1148,8 +1172,20 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
                     comp[2][i] = ff * (own_tx * __uint_as_float(d[g][0].s01));
                 }
             }
+        };
+        int32_t i0 = ask();
+        load(i0, d[0], len[0]);
+        while (i0 < cnt) {   // the next candidates' units travel while these are summed
+            const int32_t i1 = ask();
+            load(i1, d[1], len[1]);
+            sum(i0, d[0], len[0]);
+            if (i1 >= cnt) break;
+            i0 = ask();
+            load(i0, d[0], len[0]);
+            sum(i1, d[1], len[1]);
         }
         __syncthreads();
+        take_tables();
     } else if (use_tab) {
         constexpr int G = AP_RF_G;
         for (int32_t i0 = wave; i0 < cnt; i0 += G * NW) {
@@ -1280,7 +1316,7 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         __syncthreads();
         score(0, cnt);
     } else {
-        for (int32_t i = threadIdx.x; i < AP_RF_BINS; i += blockDim.x) hist[i] = 0;
+        if (threadIdx.x < AP_RF_BINS) hist[threadIdx.x] = 0;
         __syncthreads();
         const int32_t n_old = ap_uniform_i32(s_nk);
         // Bounds of the dense part of candidate t with norm |w|: the seed stage's score (members of the seed list, whose
@@ -1337,24 +1373,31 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         if (lane == 0) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
         __syncthreads();
         lo = ap_uniform_u32(s_lo); hi = ap_uniform_u32(s_hi);
+        if (hi > lo && hi - lo > (4u << 23)) lo = hi - (4u << 23);   // four octaves (one bound may lie far above all scores): what lies below is counted in the first bin
         int sh = 0;
         while (lo < hi && ((hi - lo) >> sh) >= AP_RF_BINS) sh++;
         auto count = [&](uint32_t o) { atomicAdd(&hist[(min(max(o, lo), hi) - lo) >> sh], 1u); };
-        // wave 0: the lower edge of the bin from which on at least `least` are counted, and where all are fewer, but `enough`, of the last bin; 0xffffffff:
-        // fewer than that
+        // wave 0: the lower edge of the bin from which on at least `least` are counted (of the first bin: 0), 0 too where all are fewer, but
+        // `enough`; 0xffffffff: fewer than that
         auto edge = [&](uint32_t least, uint32_t enough) {
-            constexpr int PER = AP_RF_BINS / 64;   // lane l: bins 16 (63 - l) .. + 15, so that the prefix sum runs from the top
+            static_assert(AP_RF_BINS == 512, "eight bins a lane");
+            const uint4 h = reinterpret_cast<const uint4 *>(hist)[2 * (63 - lane) + 1], l = reinterpret_cast<const uint4 *>(hist)[2 * (63 - lane)];   // from the top: lane 0 has the last eight
+            const uint32_t bin[8] = {h.w, h.z, h.y, h.x, l.w, l.z, l.y, l.x};
             uint32_t n = 0;
-            for (int b = 0; b < PER; b++) n += hist[PER * (63 - lane) + b];
+#pragma unroll
+            for (int i = 0; i < 8; i++) n += bin[i];
             uint32_t upto = n;
             for (int o = 1; o < 64; o <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)upto, o, 64); if (lane >= o) upto += up; }
             const uint64_t m = __ballot(upto >= least);
-            if (m == 0ull) { if (lane == 63) s_line = upto >= enough ? lo : 0xffffffffu; }
+            if (m == 0ull) { if (lane == 63) s_line = upto >= enough ? 0u : 0xffffffffu; }
             else if (lane == (int)__ffsll((unsigned long long)m) - 1) {
-                uint32_t above = upto - n;
-                int b = PER * (63 - lane) + PER - 1;
-                for (; above + hist[b] < least; b--) above += hist[b];
-                s_line = lo + ((uint32_t)b << sh);
+                uint32_t above = upto - n, b = 8u * (64 - lane);
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    b -= above < least ? 1u : 0u;
+                    above += bin[i];
+                }
+                s_line = b ? lo + (b << sh) : 0u;
             }
         };
 #pragma unroll
@@ -1365,7 +1408,7 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         if (wave == 0) edge((uint32_t)(K + AP_RF_MORE(K)), (uint32_t)K);
         __syncthreads();
         const uint32_t line = ap_uniform_u32(s_line);
-        for (int i = threadIdx.x; i < AP_RF_BINS; i += 512) hist[i] = 0;
+        if (threadIdx.x < AP_RF_BINS) hist[threadIdx.x] = 0;
         if (line != 0xffffffffu) {
 #pragma unroll
             for (int k = 0; k < 3; k++) {
@@ -1395,22 +1438,16 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
             if (at != 0xffffffffu) T = fmaxf(T, ap_ord2f(at));
         }
         if (!later) {
-            // first round: the P-th best list parts of what was scored first (equal ones drawn once: no more than that)
+            // first round: the P-th best of the lanes' best list parts of what was scored first, so at most the P-th best of all
             if (wave == 1 || wave == 2) {
-                constexpr int PER = 4;
-                uint32_t o[PER];
-#pragma unroll
-                for (int j = 0; j < PER; j++) o[j] = j * 64 + lane < n_first ? ap_f2ord(comp[wave][need[j * 64 + lane]]) : 0u;
-                uint32_t prev = 0xffffffffu;
-                for (int32_t r = 0; r < P && prev; r++) {
-                    uint32_t best = 0;
-#pragma unroll
-                    for (int j = 0; j < PER; j++)
-                        if (o[j] < prev) best = max(best, o[j]);
-                    for (int s = 32; s > 0; s >>= 1) best = max(best, (uint32_t)__shfl_xor((int)best, s, 64));
-                    prev = best;
+                uint32_t best = 0;
+                for (int32_t e = lane; e < n_first; e += 64) best = max(best, ap_f2ord(comp[wave][need[e]]));
+                int32_t rank = 0;
+                for (int j = 0; j < 64; j++) {
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)best, j);
+                    rank += o > best || (o == best && j < lane) ? 1 : 0;
                 }
-                if (lane == 0) s_last[wave] = prev ? ap_ord2f(prev) : -INFINITY;
+                if (rank == P - 1) s_last[wave] = best ? ap_ord2f(best) : -INFINITY;
             }
             __syncthreads();
             last[0] = P <= K && n_own >= P ? s_last[0] : -INFINITY;
@@ -1432,26 +1469,9 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         if (packed) score_lists(ap_uniform_i32(s_lists));
     }
     __syncthreads();
-    // top-K under the fused score: the keys (all different: a key carries its id) sorted in LDS.  What was left out above
-    // ranks after K of them.
+    // Three waves make the per-path lists: the best P by each single similarity among what was scored and the previous list
+    // (with hints, what was not ranks after a full list's last entry, or after P of what was scored first).
     const int32_t nk = ap_uniform_i32(s_nk), n_whole = ap_uniform_i32(s_need);
-    int32_t n2 = 64;
-    while (n2 < nk) n2 <<= 1;   // uniform; nk <= K + S*S <= AP_MAXC <= 2048
-    for (int32_t t = nk + threadIdx.x; t < n2; t += blockDim.x) keys[t] = 0ull;
-    ap_bitonic_desc(keys, n2);   // begins and ends with a barrier
-    for (int32_t t = threadIdx.x; t < K; t += blockDim.x) {
-        const uint64_t key = t < nk ? keys[t] : 0ull;
-        out_ids[x * K + t] = t < nk ? ap_key_id(key) : -1;
-        out_sc[x * K + t] = t < nk ? ap_key_score(key) : -INFINITY;
-    }
-    if (hint.known_out && wave == NW - 1) {
-        const uint64_t m = __ballot(lane < sl && lane < nk && (keys[lane < n2 ? lane : 0] & 1ull));
-        if (lane == 0) hint.known_out[x] = (uint32_t)m;
-    }
-    // per-path lists: the best P by each single similarity among what was scored and the previous list (with hints, what was not
-    // ranks after a full list's last entry, or after P of what was scored first).  One wave
-    // per path, on its own: every lane keeps its share of the keys in registers and the P best are drawn one after the
-    // other by wave-wide maxima (no block-wide pass, no barrier).
     if (wave < 3) {
         const int p = wave;
         const int32_t nold = (int32_t)__popcll(__ballot(lane < 32 && oldk[p][lane & 31] != 0ull));
@@ -1460,39 +1480,39 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
             return ap_make_key(comp[p][t], cand[t] & (AP_RF_TOP - 1), 1u);
         };
         const int32_t n_scored = n_whole + (p ? ap_uniform_i32(s_lists) : 0);
-        uint64_t prev = ~0ull;
-        auto put = [&](int32_t r, uint64_t best) {
-            for (int o = 32; o > 0; o >>= 1) {
-                const uint64_t other = __shfl_xor(best, o, 64);
-                best = other > best ? other : best;
-            }
-            if (lane == 0) {
-                out_sp_ids[((int64_t)p * nn + x) * P + r] = best ? ap_key_id(best) : -1;
-                out_sp_sc[((int64_t)p * nn + x) * P + r] = best ? ap_key_score(best) : -INFINITY;
-            }
-            prev = best;   // 0 once exhausted: nothing ranks after it
+        auto put = [&](int32_t r, uint64_t key) {
+            out_sp_ids[((int64_t)p * nn + x) * P + r] = key ? ap_key_id(key) : -1;
+            out_sp_sc[((int64_t)p * nn + x) * P + r] = key ? ap_key_score(key) : -INFINITY;
         };
-        if (fast && nold == P) {
-            // a full list: what can enter is what beats its last entry, usually few enough for one key a lane
-            const uint64_t last = oldk[p][P - 1];
-            int32_t nb = 0;
-            for (int32_t t0 = 0; t0 < n_scored; t0 += 64) {
-                const uint64_t key = t0 + lane < n_scored ? cand_key(t0 + lane) : 0ull;
-                const uint64_t m = __ballot(key > last);
-                const int32_t at = nb + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
-                if (key > last && at < 64) better[p][at] = key;
-                nb += (int32_t)__popcll(m);
-            }
-            ap_wave_sync();
-            if (nb + nold <= 64) {
-                const uint64_t key = lane < nb ? better[p][lane] : lane < nb + nold ? oldk[p][lane - nb] : 0ull;
-                for (int32_t r = 0; r < P; r++) put(r, key < prev ? key : 0ull);
-                return;
-            }
+        // what can enter: what beats a full list's last entry, or reaches the line that P of the candidates do; usually few enough for one key a lane
+        const uint64_t full = fast && nold == P ? oldk[p][P - 1] : 0ull;
+        const float line = fast && !later ? s_last[p] : -INFINITY;
+        int32_t nb = 0;
+        for (int32_t t0 = 0; t0 < n_scored && nb + nold <= 64; t0 += 64) {
+            const uint64_t key = t0 + lane < n_scored ? cand_key(t0 + lane) : 0ull;
+            const bool in = key > full && !(ap_key_score(key) < line);
+            const uint64_t m = __ballot(in);
+            const int32_t at = nb + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+            if (in && at < 64) better[p][at] = key;
+            nb += (int32_t)__popcll(m);
         }
-        auto draw = [&](auto per) {
-            constexpr int PER = decltype(per)::value;
-            uint64_t key[PER];
+        ap_wave_sync();
+        const int32_t n = nb + nold;
+        if (n <= 64) {
+            uint64_t key = lane < nb ? better[p][lane] : lane < n ? oldk[p][lane - nb] : 0ull;
+            for (int32_t j = 0; j < nold; j++)   // a candidate met once more may be on the list already
+                if (lane < nb && key == oldk[p][j]) key = 0ull;
+            const int kh = (int)(key >> 32), kl = (int)(uint32_t)key;
+            int32_t rank = 0;
+            for (int32_t j = 0; j < n; j++) {
+                const uint64_t other = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(kh, j) << 32) | (uint32_t)__builtin_amdgcn_readlane(kl, j);
+                rank += other > key ? 1 : 0;
+            }
+            if (key && rank < P) put(rank, key);
+            if (lane >= (int)__popcll(__ballot(key != 0ull)) && lane < P) put(lane, 0ull);
+        } else {   // every lane keeps its share of the keys and the P best are drawn one after the other by wave-wide maxima
+            constexpr int PER = (AP_MAXC + 32 + 63) / 64;
+            uint64_t key[PER], prev = ~0ull;
 #pragma unroll
             for (int j = 0; j < PER; j++) {
                 const int32_t t = j * 64 + lane;
@@ -1503,11 +1523,36 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
 #pragma unroll
                 for (int j = 0; j < PER; j++)
                     if (key[j] < prev && key[j] > best) best = key[j];
-                put(r, best);
+                for (int o = 32; o > 0; o >>= 1) {
+                    const uint64_t other = __shfl_xor(best, o, 64);
+                    best = other > best ? other : best;
+                }
+                if (lane == 0) put(r, best);
+                prev = best;   // 0 once exhausted: nothing ranks after it
             }
-        };
-        if (n_scored + nold <= 6 * 64) draw(std::integral_constant<int, 6>());
-        else draw(std::integral_constant<int, (AP_MAXC + 32 + 63) / 64>());
+        }
+    } else {
+        // The others the top-K under the fused score.  The keys are all different (a key carries its id), so a key's place is the number
+        // of larger ones; what was left out above ranks after K of them.  (By a bitonic sort this phase took 7.5 of a node's 90 us.)
+        for (int32_t t = threadIdx.x - 192; t < nk; t += 320) {
+            const uint64_t key = keys[t];
+            int32_t rank = 0;
+            for (int32_t j = 0; j + 1 < nk; j += 2) {
+                const ulonglong2 o = *reinterpret_cast<const ulonglong2 *>(keys + j);
+                rank += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0);
+            }
+            if (nk & 1) rank += keys[nk - 1] > key ? 1 : 0;
+            if (rank < K) {
+                out_ids[x * K + rank] = ap_key_id(key);
+                out_sc[x * K + rank] = ap_key_score(key);
+                if (rank < sl && (key & 1ull)) atomicOr(&s_known, 1u << rank);
+            }
+        }
+        for (int32_t t = nk + threadIdx.x - 192; t < K; t += 320) { out_ids[x * K + t] = -1; out_sc[x * K + t] = -INFINITY; }
+    }
+    if (hint.known_out) {
+        __syncthreads();
+        if (threadIdx.x == 0) hint.known_out[x] = s_known;
     }
 }
 
@@ -1535,10 +1580,9 @@ int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, i
     const int64_t n = ix->docs.n;
     *cur = 0;
     if (rounds <= 0) return AP_OK;
-    float *tau = nullptr;
-    uint32_t *known[2] = {nullptr, nullptr};
-    int rc = ap_dev_alloc(&tau, (size_t)n);
-    for (int i = 0; i < 2 && rc == AP_OK; i++) rc = ap_dev_alloc(&known[i], (size_t)n);
+    float *tau = nullptr;   // n, then the two sets of n words of known bits
+    int rc = ap_dev_alloc(&tau, (size_t)3 * n);
+    uint32_t *known[2] = {reinterpret_cast<uint32_t *>(tau + n), reinterpret_cast<uint32_t *>(tau + 2 * n)};
     if (rc == AP_OK) {
         hipLaunchKernelGGL(k_take_tau, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc[0], n, K, 0u, tau);
         if (hipGetLastError() != hipSuccess) { ap_set_error("refinement failed to start"); rc = AP_EHIP; }
@@ -1552,7 +1596,7 @@ int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, i
         rc = ap_refine_round(ix, K, S, P, ids[c], spi[c], sps[c], nullptr, n, ids[1 - c], sc[1 - c], spi[1 - c], sps[1 - c], hint, st);
         *cur = 1 - c;
     }
-    void *ptrs[] = {tau, known[0], known[1], pk.mem};
+    void *ptrs[] = {tau, pk.mem};
     for (void *p : ptrs) if (p) (void)hipFree(p);   // waits for the rounds
     return rc;
 }

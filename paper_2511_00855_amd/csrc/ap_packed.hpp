@@ -10,6 +10,7 @@
 #define AP_PK_SP 4096        // slots that the other learned-sparse terms share
 #define AP_PK_TX 12288       // ... and the other lexical terms
 #define AP_PK_SLOTS (AP_PK_DIRECT + AP_PK_SP + AP_PK_TX)
+#define AP_PK_LEAST 512      // documents below which nothing is packed
 #define AP_PK_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of slots is made for
 
 // The line a record begins on, from the entries before it and its number: a record of e entries takes at most 12 + 3 e + 18

@@ -34,7 +34,10 @@ SP, TX = ("poisson", 100), ("lognormal", 60)
 CASES = {   # name: (workload, K, S, P, build weights, what is done to the documents)
     "ordinary": (dict(n=1300, sp=SP, tx=TX), 128, 32, 11, (1.0, 1.0, 1.0), None),
     "rare terms share slots": (dict(n=1500, vocab=200_000, sp=SP, tx=TX), 64, 32, 11, (1.0, 1.0, 1.0), None),
-    "units beyond three a lane": (dict(n=500, sp=("fixed", 131), tx=("fixed", 120)), 32, 24, 6, (1.0, 1.0, 1.0), None),
+    "units beyond three a lane": (dict(n=600, sp=("fixed", 131), tx=("fixed", 120)), 32, 24, 6, (1.0, 1.0, 1.0), None),
+    "lists too long for the tables": (dict(n=520, sp=("fixed", 300), tx=("fixed", 200)), 24, 16, 6, (1.0, 1.0, 1.0), None),
+    "fewest that are packed": (dict(n=512), 32, 32, 11, (1.0, 1.0, 1.0), None),
+    "one fewer": (dict(n=511), 32, 32, 11, (1.0, 1.0, 1.0), None),
     "empty and short lists": (dict(n=700, sp=("poisson", 1), tx=("fixed", 5)), 32, 32, 32, (1.0, 1.0, 1.0), None),
     "negative weights": (dict(n=900, sp=SP, tx=TX), 64, 32, 11, (1.0, 1.0, 1.0), _negative),
     "weights far apart": (dict(n=900), 64, 32, 11, (1.0, 1.0, 1.0), _far_apart),
