@@ -2231,6 +2231,7 @@ __global__ __launch_bounds__(1024) void k_gram_lists(const uint2 *__restrict__ r
 // recycled as a keyword edge if its keyword flag is set, i.e. if it shares a
 // keyword with A and no current member of SE covers all the shared keywords.
 #define AP_T_CAP 512
+#define AP_DP_BITS 9      // slots of the table of the node's keywords: at most a quarter full
 
 __device__ __forceinline__ bool ap_list_has(const int32_t *idx, int64_t beg, int64_t end, int32_t t) {
     int64_t lo = beg, hi = end;
@@ -2241,17 +2242,19 @@ __device__ __forceinline__ bool ap_list_has(const int32_t *idx, int64_t beg, int
     return lo < end && idx[lo] == t;
 }
 
-// Where t stands in a list of n ascending ids in LDS, -1 if it is not there.
-__device__ __forceinline__ int32_t ap_list_find_lds(const int32_t *idx, int32_t n, int32_t t) {
-    int32_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (idx[mid] < t) lo = mid + 1; else hi = mid;
-    }
-    return lo < n && idx[lo] == t ? lo : -1;
-}
-
-__global__ __launch_bounds__(256) void k_detour_prune(ApVecs D, const float *__restrict__ self_sim, int32_t K, int32_t R,
+// Detour counts and order by 256 threads, then the walk, which is sequential in v, by one wave.  What made the walk slow was what
+// it asked memory and LDS one after the other at each of its steps: the offsets of v's keywords, the keywords, a search of each, the
+// similarities to the members of SE (20 ms for 100,000 nodes of 128 neighbours, 320 us a node).  Nothing of that depends on the
+// walk, so all of it is asked ahead, by all threads:
+//  - a bit per neighbour w, sim(w,v) >= sim(v,v), noted while the detours of v are counted, which read the same column;
+//  - a bit per keyword of the node that v holds too, by a wave for four neighbours at a time and one read a keyword of a table that one
+//    wave builds while the others count;
+//  - a bit per neighbour w that holds every keyword that v shares with the node.
+// A step then is one read of LDS, requested a step before, and a ballot.  100,000 nodes of 128 neighbours: 19.8 -> 5.3 ms; 200,000:
+// 40.4 -> 10.8 ms (the same with a search instead of the table, a loop over the members' keywords in the walk and dependent reads in the count of
+// the ranks: 8.4 and 17.2).
+// Nodes with more than AP_T_CAP keywords search the lists as the walk goes on.
+__global__ __launch_bounds__(256, 6) void k_detour_prune(ApVecs D, const float *__restrict__ self_sim, int32_t K, int32_t R,
                                                       int32_t ke_cap, const int32_t *__restrict__ knn,
                                                       const float *__restrict__ knn_sc, const int32_t *__restrict__ node_ids,
                                                       int64_t x0, int64_t xout0, const float *__restrict__ pm,
@@ -2259,49 +2262,128 @@ __global__ __launch_bounds__(256) void k_detour_prune(ApVecs D, const float *__r
                                                       int32_t *__restrict__ o_se, int32_t *__restrict__ o_ke,
                                                       int32_t *__restrict__ o_ke_count, int32_t *__restrict__ o_flag,
                                                       int32_t mode) {
-    __shared__ int32_t ids[256], cnt[256], order[256], se_pos[128], flag[256];
+    __shared__ int32_t ids[256], cnt[256], order[256], se_pos[128], flag[256], tx_n[256];
+    __shared__ uint32_t tx_b[256];       // the two parts of a corpus hold fewer than 2^32 entries together
     __shared__ float simA[256];
-    __shared__ int32_t T[AP_T_CAP];
-    __shared__ int32_t a_tx[AP_T_CAP];   // the node's own keywords: every step of the walk searches them
-    // Per keyword of the node, the members of SE that hold it (bit i = the i-th member; |SE| <= R <= 128).  "Some member
-    // holds every shared keyword" is then an AND over the shared keywords' words instead of a search of every
-    // member's list for every shared keyword.
-    __shared__ unsigned long long kwm[AP_T_CAP][2];
+    __shared__ int32_t a_tx[AP_T_CAP];   // the node's own keywords; of a node with more, those that it shares with v
+    __shared__ __attribute__((aligned(16))) int32_t rank_key[256];
+    __shared__ __attribute__((aligned(16))) uint64_t a_tab[1 << AP_DP_BITS];   // keyword -> its place in the node's list + 1, as a number's bits
+    __shared__ int32_t s_valid, s_seed;
+    extern __shared__ uint32_t dp_lds[];
+    const int32_t KW = (K + 31) / 32;
+    uint32_t *rows = dp_lds;                   // [K][2 KW]: the neighbours with sim(w,v) >= sim(v,v), then those that hold what v shares with the node
+    uint32_t *shared = dp_lds + 2 * K * KW;    // [AP_T_CAP / 32][K]
     const int64_t x = blockIdx.x;               // index inside the chunk (pm)
     const int64_t xo = xout0 + x;               // index in the output arrays
     const int64_t u = node_ids ? (int64_t)node_ids[x0 + x] : x0 + x;
     const float *P = pm + x * (int64_t)K * K;
-    const int t = threadIdx.x;
-    if (t < K) { ids[t] = knn[u * K + t]; simA[t] = knn_sc[u * K + t]; flag[t] = 0; }
+    const int t = threadIdx.x, lane = t & 63, wave = ap_wave_id();
+    if (t == 0) s_valid = 0;
     const int64_t a_beg = D.tx_indptr[u], a_end = D.tx_indptr[u + 1];
     const bool a_in_lds = a_end - a_beg <= AP_T_CAP;   // uniform
-    if (a_in_lds) for (int32_t e = t; e < (int32_t)(a_end - a_beg); e += 256) { a_tx[e] = D.tx_idx[a_beg + e]; kwm[e][0] = 0ull; kwm[e][1] = 0ull; }
-    __syncthreads();
+    const int32_t an = a_in_lds ? (int32_t)(a_end - a_beg) : 0, W = (an + 31) / 32;
     if (t < K) {
-        int32_t c = 0;
-        if (ids[t] >= 0) {
-            const float sy = simA[t];
-            for (int32_t xx = 0; xx < K; xx++) {
-                if (xx == t || ids[xx] < 0) continue;
-                const float a = simA[xx], b = P[(int64_t)xx * K + t];
-                c += (a < b ? a : b) > sy;
+        const int32_t v = knn[u * K + t];
+        ids[t] = v; simA[t] = v >= 0 ? knn_sc[u * K + t] : -INFINITY; flag[t] = 0; cnt[t] = 0;
+        int64_t b = 0, e = 0;
+        if (v >= 0) { b = D.tx_indptr[v]; e = D.tx_indptr[v + 1]; }
+        tx_b[t] = (uint32_t)b; tx_n[t] = (int32_t)(e - b);
+    }
+    for (int32_t e = t; e < an; e += 256) a_tx[e] = D.tx_idx[a_beg + e];
+    if (t < 128) order[t] = t + 1;   // the places, for the table; the order itself comes later
+    for (int32_t i = t; i < W * K; i += 256) shared[i] = 0u;
+    __syncthreads();
+    if (wave == 3) {
+        const int32_t seed = an > 0 && an <= 128 ? ap_bucket_build<2>(a_tx, reinterpret_cast<const float *>(order), an, a_tab, AP_DP_BITS) : -1;
+        if (lane == 0) s_seed = seed;
+    }
+    {   // a column a thread, or two or four threads a column with some of the rows each
+        const int32_t parts = K <= 64 ? 4 : K <= 128 ? 2 : 1, stride = 256 / parts, col = t % stride, part = t / stride, per = (KW + parts - 1) / parts;
+        if (col < K && ids[col] >= 0) {
+            const float sy = simA[col], sv = self_sim[ids[col]];
+            int32_t c = 0;
+            for (int32_t w = part * per; w < min((part + 1) * per, KW); w++) {
+                uint32_t bits = 0;
+                for (int32_t i0 = 0; i0 < 32; i0 += 8) {
+                    float b[8];
+#pragma unroll
+                    for (int i = 0; i < 8; i++) b[i] = P[(int64_t)min(32 * w + i0 + i, K - 1) * K + col];
+#pragma unroll
+                    for (int i = 0; i < 8; i++) {
+                        const int32_t xx = 32 * w + i0 + i;
+                        if (xx >= K) continue;
+                        const float a = simA[xx];   // -inf for a hole: no route goes through it
+                        c += xx != col && (a < b[i] ? a : b[i]) > sy ? 1 : 0;
+                        bits |= b[i] < sv ? 0u : 1u << (i0 + i);
+                    }
+                }
+                rows[col * 2 * KW + w] = bits;
             }
+            if (c) atomicAdd(&cnt[col], c);
+            if (part == 0) atomicAdd(&s_valid, 1);
         }
-        cnt[t] = c;
     }
     __syncthreads();
-    if (t < K) {
-        int32_t r = 0;
-        if (ids[t] >= 0) {
-            if (mode == AP_PRUNE_IP_ONLY) {   // ablation: no detour sort, the list as ranked by similarity
-                for (int32_t z = 0; z < t; z++) r += ids[z] >= 0;
-            } else {
-                for (int32_t z = 0; z < K; z++) r += ids[z] >= 0 && (cnt[z] < cnt[t] || (cnt[z] == cnt[t] && z < t));
+    // the keywords that a neighbour shares with the node: a wave for four neighbours at a time, every lane a keyword of each
+    if (an > 0) {
+        const int32_t step0 = ap_pow2_floor(an);
+        const int32_t seed = ap_uniform_i32(s_seed);
+        const uint32_t mult = ap_seed_mult(max(seed, 0));
+        auto find = [&](int32_t term) {   // its place in the node's list, -1 if it is not there (term -1 never is)
+            if (seed >= 0) return __float_as_int(ap_bucket_get((const AP_LDS uint64_t *)a_tab, mult, AP_DP_BITS, term)) - 1;   // uniform
+            int32_t pos = 0;
+            for (int32_t st = step0; st > 0; st >>= 1) {
+                const int32_t p2 = pos + st, at = (p2 < an ? p2 : an) - 1;
+                pos = ((p2 <= an) & (a_tx[at] < term)) ? p2 : pos;
             }
-        } else {
-            for (int32_t z = 0; z < K; z++) r += ids[z] >= 0 || z < t;
+            return pos < an && a_tx[pos] == term ? pos : -1;
+        };
+        constexpr int G = 4;
+        for (int32_t v0 = G * wave; v0 < K; v0 += 4 * G) {
+            int32_t n[G], most = 0;
+            const int32_t *l[G];
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const int32_t v = min(v0 + g, K - 1);   // past the end the last one again
+                n[g] = ap_uniform_i32(tx_n[v]); l[g] = D.tx_idx + tx_b[v];
+                most = max(most, n[g]);
+            }
+            for (int32_t e = lane; e < most; e += 64) {
+                int32_t term[G], at[G];
+#pragma unroll
+                for (int g = 0; g < G; g++) term[g] = e < n[g] ? l[g][e] : -1;
+#pragma unroll
+                for (int g = 0; g < G; g++) at[g] = find(term[g]);
+#pragma unroll
+                for (int g = 0; g < G; g++)
+                    if (at[g] >= 0) atomicOr(&shared[(at[g] >> 5) * K + min(v0 + g, K - 1)], 1u << (at[g] & 31));
+            }
+        }
+    }
+    // order: by detours, then by place (ablation: by place alone), holes last
+    if (t < 256) rank_key[t] = t < K ? (ids[t] >= 0 ? (mode == AP_PRUNE_IP_ONLY ? 0 : cnt[t] * 256) : 1 << 20) + t : INT32_MAX;
+    __syncthreads();
+    if (t < K) {
+        const int32_t mine = rank_key[t];
+        int32_t r = 0;
+        for (int32_t z = 0; z < K; z += 4) {
+            const int4 o = *reinterpret_cast<const int4 *>(rank_key + z);
+            r += (o.x < mine) + (o.y < mine) + (o.z < mine) + (o.w < mine);
         }
         order[r] = t;
+    }
+    if (a_in_lds) {   // who holds what v shares with the node
+        for (int32_t i = t; i < K * KW; i += 256) {
+            const int32_t v = i % K, j0 = i / K * 32, last = K - 1 - j0;
+            uint32_t miss = 0;
+            for (int32_t w = 0; w < W; w++) {
+                const uint32_t s = shared[w * K + v];
+                const uint32_t *of = shared + w * K + j0;
+#pragma unroll
+                for (int32_t j = 0; j < 32; j++) miss |= s & ~of[min(j, last)] ? 1u << j : 0u;
+            }
+            rows[v * 2 * KW + KW + i / K] = ~miss;
+        }
     }
     __syncthreads();
     if (t < K) {
@@ -2309,75 +2391,72 @@ __global__ __launch_bounds__(256) void k_detour_prune(ApVecs D, const float *__r
         if (o_sorted) o_sorted[xo * K + t] = ids[order[t]];
     }
     if (t >= 64) return;   // the walk is sequential in v; one wave does it
-    const int lane = t;
-    const int64_t ab = D.tx_indptr[u], ae = D.tx_indptr[u + 1];
+    const int32_t n_valid = ap_uniform_i32(s_valid);   // holes are sorted last
     int32_t nse = 0, nke = 0;
-    for (int32_t r = 0; r < K; r++) {
-        const int32_t pv = order[r], v = ids[pv];
-        if (v < 0) break;   // holes are sorted last
-        if (nse == 0 && !a_in_lds) { if (lane == 0) se_pos[0] = pv; nse = 1; ap_wave_sync(); continue; }
-        // T = K(A) n K(v): the shared keywords themselves, or (node's list in LDS) their places in the node's list
-        const int64_t vb = D.tx_indptr[v], ve = D.tx_indptr[v + 1];
-        int32_t nt_all = 0;
-        for (int64_t e0 = vb; e0 < ve; e0 += 64) {
-            const int64_t e = e0 + lane;
-            const int32_t term = e < ve ? D.tx_idx[e] : -1;
-            int32_t at = -1;
-            if (term >= 0) at = a_in_lds ? ap_list_find_lds(a_tx, (int32_t)(ae - ab), term) : (ap_list_has(D.tx_idx, ab, ae, term) ? 0 : -1);
-            const bool in = at >= 0;
-            const uint64_t m = __ballot(in);
-            if (in) { const int32_t pos = nt_all + __popcll(m & ((1ull << lane) - 1ull)); if (pos < AP_T_CAP) T[pos] = a_in_lds ? at : term; }
-            nt_all += __popcll(m);
-        }
-        ap_wave_sync();
-        const int32_t nt = nt_all < AP_T_CAP ? nt_all : AP_T_CAP;
-        if (nse == 0) {   // the first member of SE: its keywords are noted, nothing is tested
-            if (lane == 0) se_pos[0] = pv;
-            for (int32_t k = lane; k < nt; k += 64) kwm[T[k]][0] |= 1ull;
-            nse = 1;
-            ap_wave_sync();
-            continue;
-        }
+    uint32_t se_bits = 0;   // lanes l and KW + l: bits 32 l .. of the neighbours that are members
+    int32_t place[4];       // order[64 q + lane]
+#pragma unroll
+    for (int q = 0; q < 4; q++) place[q] = 64 * q + lane < K ? order[64 * q + lane] : 0;
+    auto at = [&](int32_t r) {   // order[r]
+        const int32_t v = r < 64 ? place[0] : r < 128 ? place[1] : r < 192 ? place[2] : place[3];   // r is uniform
+        return __builtin_amdgcn_readlane(v, r & 63);
+    };
+    int32_t pv = n_valid ? at(0) : 0;
+    uint32_t row = lane < 2 * KW ? rows[pv * 2 * KW + lane] : 0u;
+    for (int32_t r = 0; r < n_valid; r++) {
+        if (!o_flag && nse >= R && nke >= ke_cap) break;   // nothing but flags is left to tell
+        const int32_t next = at(min(r + 1, n_valid - 1));
+        const uint32_t row_next = lane < 2 * KW ? rows[next * 2 * KW + lane] : 0u;
         int32_t fl = 0;
-        if (nt_all > 0 && a_in_lds) {
-            // a member holds every shared keyword iff its bit survives the AND of those keywords' words
-            unsigned long long w0 = ~0ull, w1 = ~0ull;
-            for (int32_t k = lane; k < nt; k += 64) { w0 &= kwm[T[k]][0]; w1 &= kwm[T[k]][1]; }
-            for (int32_t o = 32; o > 0; o >>= 1) { w0 &= __shfl_xor(w0, o); w1 &= __shfl_xor(w1, o); }
-            fl = (w0 | w1) ? 0 : 1;
-        } else if (nt_all > 0) {
-            // does some member of SE hold every shared keyword?
-            bool covered = false;
-            for (int32_t i = lane; i < nse; i += 64) {
-                const int32_t y = ids[se_pos[i]];
-                const int64_t yb = D.tx_indptr[y], ye = D.tx_indptr[y + 1];
-                bool all_in = true;
-                for (int32_t k = 0; k < nt && all_in; k++) all_in = ap_list_has(D.tx_idx, yb, ye, T[k]);
-                if (all_in && nt_all > AP_T_CAP) {   // rare: the shared set overflowed T; test the rest directly
-                    for (int64_t e = vb; e < ve && all_in; e++) {
-                        const int32_t term = D.tx_idx[e];
-                        if (ap_list_has(D.tx_idx, ab, ae, term)) all_in = ap_list_has(D.tx_idx, yb, ye, term);
+        bool ok = true;
+        if (nse > 0) {   // the first one is a member whatever it is
+            const uint64_t met = __ballot((row & se_bits) != 0u), low = (1ull << KW) - 1ull;
+            if (a_in_lds) fl = met & ~low ? 0 : 1;   // no member holds every shared keyword (where none is shared, all do)
+            else {
+                // the shared keywords themselves, AP_T_CAP of them at a time: which members hold all of them?
+                const int64_t vb = tx_b[pv], ve = vb + tx_n[pv];
+                uint32_t holds = 3u;   // bit i: member 64 i + lane
+                int32_t nt = 0;
+                bool any = false;
+                auto ask = [&]() {
+                    ap_wave_sync();
+                    for (int32_t i = 0; i < 2; i++) {
+                        if (64 * i + lane >= nse || !(holds >> i & 1u)) continue;
+                        const int32_t y = ids[se_pos[64 * i + lane]];
+                        const int64_t yb = D.tx_indptr[y], ye = D.tx_indptr[y + 1];
+                        for (int32_t k = 0; k < nt; k++)
+                            if (!ap_list_has(D.tx_idx, yb, ye, a_tx[k])) { holds &= ~(1u << i); break; }
                     }
+                    ap_wave_sync();
+                    nt = 0;
+                };
+                for (int64_t e0 = vb; e0 < ve; e0 += 64) {
+                    const int32_t term = e0 + lane < ve ? D.tx_idx[e0 + lane] : -1;
+                    const bool in = term >= 0 && ap_list_has(D.tx_idx, a_beg, a_end, term);
+                    const uint64_t m = __ballot(in);
+                    any = any || m;
+                    if (in) a_tx[nt + __popcll(m & ((1ull << lane) - 1ull))] = term;
+                    nt += __popcll(m);
+                    if (nt > AP_T_CAP - 64) ask();
                 }
-                covered = covered || all_in;
+                ask();
+                const bool covered = (lane < nse && (holds & 1u)) || (64 + lane < nse && (holds & 2u));
+                fl = any && !__ballot(covered) ? 1 : 0;
             }
-            fl = __ballot(covered) ? 0 : 1;
+            // IP test against every member of SE (ablation: without it SE is the first R of the detour order)
+            ok = nse < R && (mode == AP_PRUNE_RNG_ONLY || !(met & low));
         }
-        // IP test against every member of SE
-        bool bad = false;
-        const float sv = self_sim[v];
-        if (mode != AP_PRUNE_RNG_ONLY)   // ablation: without the test SE is the first R of the detour order
-            for (int32_t i = lane; i < nse; i += 64) bad = bad || !(P[(int64_t)se_pos[i] * K + pv] < sv);
-        const bool ok = nse < R && !__ballot(bad);
         if (lane == 0) {
             flag[pv] = fl;
             if (ok) se_pos[nse] = pv;
-            else if (fl && nke < ke_cap && o_ke) o_ke[xo * ke_cap + nke] = v;
+            else if (fl && nke < ke_cap && o_ke) o_ke[xo * ke_cap + nke] = ids[pv];
         }
-        if (ok && a_in_lds) for (int32_t k = lane; k < nt; k += 64) kwm[T[k]][nse >> 6] |= 1ull << (nse & 63);
-        if (ok) nse++;
-        else if (fl && nke < ke_cap) nke++;
-        ap_wave_sync();
+        if (ok) {
+            if (lane < 2 * KW && (lane < KW ? lane : lane - KW) == pv >> 5) se_bits |= 1u << (pv & 31);
+            nse++;
+        } else if (fl && nke < ke_cap) nke++;
+        if (!a_in_lds) ap_wave_sync();   // se_pos is read
+        pv = next; row = row_next;
     }
     ap_wave_sync();
     for (int32_t i = lane; i < R; i += 64) if (o_se) o_se[xo * R + i] = i < nse ? ids[se_pos[i]] : -1;
@@ -2424,7 +2503,7 @@ int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_i
             e = hipGetLastError();
         }
         if (e != hipSuccess) break;
-        hipLaunchKernelGGL(k_detour_prune, dim3((unsigned)cn), dim3(256), 0, st, ix->docs, ix->self_sim, K, R, R / 2, knn_ids,
+        hipLaunchKernelGGL(k_detour_prune, dim3((unsigned)cn), dim3(256), ((size_t)2 * ((K + 31) / 32) + AP_T_CAP / 32) * K * 4, st, ix->docs, ix->self_sim, K, R, R / 2, knn_ids,
                            knn_sc, node_ids, x0, x0, pm, count, sorted_ids, se, ke, ke_count, flag, ix->params.prune_mode);
         e = hipGetLastError();
     }
