@@ -102,6 +102,7 @@ extern "C" int ap_debug_search_profile(unsigned long long out8[8]) {
 #define AP_PROF_FLUSH
 #endif
 
+#define AP_CUS 256              // compute units of the chip
 // NT threads per workgroup.  256 (four waves) is the usual size: seven workgroups share a CU while the pool is small
 // enough, and the register budget is the 72 VGPRs of seven waves per SIMD.  When the pool is so large that the LDS
 // holds four workgroups or fewer, 512 or 1024 threads keep the CU's SIMDs occupied with one query's candidates.
@@ -117,7 +118,7 @@ extern "C" int ap_debug_search_profile(unsigned long long out8[8]) {
 // Wide bf16 rows (more than 1024 columns: 24 or 32 query values per lane) do not fit seven waves' registers without
 // spilling; they run at five waves per SIMD.
 template <int DT, int NV, int NT> struct ApSearchWaves {
-    static constexpr int MIN = (DT == AP_BF16 && NV >= 3) ? (NT == 1024 ? 4 : 5) : NT == 256 ? AP_SEARCH_WAVES_PER_SIMD : NT == 512 ? AP_SEARCH_WAVES_512 : 4;
+    static constexpr int MIN = (DT == AP_BF16 && NV >= 3) ? (NT == 1024 ? 4 : 5) : NT <= 256 ? AP_SEARCH_WAVES_PER_SIMD : NT == 512 ? AP_SEARCH_WAVES_512 : 4;
 };
 // FLOOR: neighbours with a bound below the estimated end of the pool wait (large pools searched with bounds).
 template <int DT, int NV, bool KW, bool BIG, int NT, bool FLOOR>
@@ -854,16 +855,32 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
         const size_t per_cu = (size_t)160 * 1024 / lds_bytes(256);
         nt = per_cu > AP_SEARCH_NT512_AT ? 256 : per_cu > AP_SEARCH_NT1024_AT ? 512 : 1024;
     }
+    // Two waves a query, twice as many queries on the chip at a time: a query then takes some 1.2 times as long (its few candidates
+    // an iteration keep four waves no busier than two, the steps between them wait for memory either way), so this pays where it saves
+    // a second, half empty round.  2,500 queries (1,792 of four waves run at a time, 3,584 of two), pool 512: 100,000 f32 documents
+    // with keywords 13.7 -> 10.8 ms, plain 9.05 -> 8.24; 60,000 bf16 10.1 -> 8.7 and 7.1 -> 6.2; 10,000 narrow ones 6.2 -> 4.8 and 4.0 -> 3.0.
+    // Not where the batch fits one round of four waves (400 to 1,792 queries: 0.80 to 0.93 of the speed) nor without bounds or with
+    // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).
+    const int32_t slots_of = ix->dtype == AP_BF16 && ix->docs.dim > 1024 ? 5 : AP_SEARCH_WAVES_PER_SIMD;   // waves a SIMD holds (ApSearchWaves)
+    auto slots = [&](int32_t threads, size_t bytes) -> int64_t { return AP_CUS * (int64_t)std::min<size_t>((size_t)slots_of * 256 / threads, (size_t)160 * 1024 / bytes); };
+    const int64_t at_once = std::min(ws.slab, nq);
+    if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96 && at_once * 10 > slots(256, lds_bytes(256)) * 11 &&
+        at_once <= slots(128, lds_bytes(128)))
+        nt = 128;
     // A floor below which neighbours wait: where a search ends by itself, in large pools.  In small ones (256 threads) what
     // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
     g.bound_floor = ws.bound.table && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? ws.bound.floor : nullptr;
-    g.nxtw = nt == 256 && g.cmax > nt ? g.cmax : 0;
+    g.nxtw = nt <= 256 && g.cmax > nt ? g.cmax : 0;
     size_t smem = lds_bytes(nt);
-    // Visited sets in LDS (four-wave workgroups only): when the bitset fits beside the kernel's other arrays without
+    // Visited sets in LDS (small workgroups only): when the bitset fits beside the kernel's other arrays without
     // taking a workgroup's place on the CU (seven of them run on one while the pool is small).  Measured on 100,000
     // documents (12.5 KB a set): 4 to 5 % faster up to beam 512, 29 % slower at beam 2144 where it costs two of the
     // seven workgroups, which is why the rule is about occupancy.  Same results either way.
     g.vis_lds = 0;
+    if (nt == 128 && g_ap_debug.search_visited_global == 0) {   // two waves: as long as the whole batch runs at once
+        const size_t with = smem + g.words * 4 + 8;
+        if (with <= (size_t)160 * 1024 && slots(128, with) >= at_once) { g.vis_lds = 1; smem = with; }
+    }
     if (nt == 256 && g_ap_debug.search_visited_global == 0) {
         const size_t with = smem + g.words * 4 + 8, lds = (size_t)160 * 1024;
         const size_t now = std::min<size_t>(7, lds / smem), then = with <= lds ? std::min<size_t>(7, lds / with) : 0;
@@ -891,8 +908,10 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
             AP_TRY(ap_bound_fill(ix, ws.bound, Q, w_dev, w_stride, q0, qn, kw_terms, kw_stride, st));
             if (g.bound_floor) AP_TRY(ap_bound_floors(ix, ws.bound, qn, beam, st));
         }
-        if (kw) AP_LAUNCH_SEARCH(true, false, 256, false);
+        if (kw && nt == 128) AP_LAUNCH_SEARCH(true, false, 128, false);
+        else if (kw) AP_LAUNCH_SEARCH(true, false, 256, false);
         else if (big_tables) AP_LAUNCH_SEARCH(false, true, 256, false);
+        else if (nt == 128) AP_LAUNCH_SEARCH(false, false, 128, false);
         else if (nt == 256) AP_LAUNCH_SEARCH(false, false, 256, false);
         else if (nt == 512 && g.bound_floor) AP_LAUNCH_SEARCH(false, false, 512, true);
         else if (nt == 512) AP_LAUNCH_SEARCH(false, false, 512, false);

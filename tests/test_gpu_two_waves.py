@@ -1,0 +1,38 @@
+"""A batch a little too large to run at once is searched by workgroups of two waves, its halves by workgroups of four: the same ids,
+scores and counts, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00855_amd import binding as B
+from paper_2511_00855_amd.synth import make_keywords, make_workload, subset_vecset
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bf16,dim,degree,nq", [(False, 128, 64, 2300), (False, 768, 16, 1972), (True, 1024, 32, 3584), (True, 1536, 64, 2000)])
+def test_two_waves_and_four(debug_knobs, bf16, dim, degree, nq):
+    w = make_workload("tiny", seed=3, n=1700, nq=nq, dim=dim, bf16=bf16, sp=("poisson", 60))
+    docs = B.DeviceVecs(w.docs, bf16=bf16)
+    ix = B.Index.build(docs, B.build_params(degree, nd_rounds=1, n_entry=16))
+    kw = make_keywords(w.queries, seed=2, max_terms=2, stride=2, p_none=0.1)
+    pw = np.random.default_rng(1).uniform(0.0, 1.0, (nq, 3)).astype(np.float32)
+    half = nq // 2
+    parts = [(0, nq), (0, half), (half, nq)]
+    qs = [B.DeviceVecs(w.queries if b - a == nq else subset_vecset(w.queries, np.arange(a, b))) for a, b in parts]
+    debug_knobs("search_bounds", 2)
+    for deleted in (False, True):
+        if deleted:
+            ix.mark_deleted(np.arange(0, 1700, 9, dtype=np.int32))
+        for beam, glob in ((1, 0), (40, 0), (300, 0), (300, 1)):
+            debug_knobs("search_visited_global", glob)
+            for words in (False, True):
+                print(bf16, dim, nq, beam, glob, words, deleted, flush=True)
+                got = []
+                for q, (a, b) in zip(qs, parts):
+                    k = min(beam, 10)
+                    r = ix.search_batch_keywords(q, k, beam, kw[a:b], pw[a:b]) if words else ix.search_batch(q, k, beam, pw[a:b])
+                    got.append([t.clone() for t in r] + [ix.search_stats(b - a)[0][:, :2].clone()])
+                for whole, first, second in zip(*got):
+                    assert torch.equal(whole, torch.cat([first, second])), (beam, glob, words, deleted)
+    ix.close()
