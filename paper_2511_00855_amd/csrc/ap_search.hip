@@ -26,6 +26,7 @@ struct ApSearchArgs {
     const float *w;     // per query (stride 3) or the index default (stride 0)
     int32_t w_stride;
     int32_t R, E, k, L, max_iters, width, cmax;
+    int32_t icap;       // large pools: > 0: an iteration's neighbours are listed by their ids (this many at most) and scored cmax at a time; 0: all at once
     int32_t vis_lds;    // the visited sets live in LDS (words words after the kernel's other arrays), not in `visited`
     int32_t nxtw;       // words of the scratch that parks positions when more keys enter at once than the workgroup has threads (else 0)
     int32_t q0;         // the launch covers queries q0 .. q0 + gridDim.x (a slab of the batch)
@@ -78,10 +79,12 @@ __device__ __forceinline__ int32_t ap_rank_in(const uint64_t *keys, int32_t n, u
 #define AP_RANK_LANES 16        // lanes that rank one entering key of a large pool (16, 32 or 64)
 #endif
 #define AP_RANK_SORT 128        // entering keys of a large pool beyond which they are sorted instead of ranked one against the other
+#define AP_SEARCH_LISTED 256    // listed neighbours that are scored at a time
 #ifndef AP_SEARCH_WAVES_512
 #define AP_SEARCH_WAVES_512 6
 #endif
-template <int NT> struct ApSearchG { static constexpr int G = NT == 1024 ? AP_SEARCH_G_1024 : NT == 512 ? AP_SEARCH_G_512 : AP_SEARCH_G_256; };
+#define AP_SEARCH_G_LIST 2
+template <int NT, bool LIST> struct ApSearchG { static constexpr int G = LIST ? AP_SEARCH_G_LIST : NT == 1024 ? AP_SEARCH_G_1024 : NT == 512 ? AP_SEARCH_G_512 : AP_SEARCH_G_256; };
 
 // Profiling aid of debug builds (-DAP_SEARCH_PROFILE): thread 0 of every workgroup adds the time it spent in each
 // phase of the loop (100 MHz ticks) to a device array that ap_debug_search_profile reads and clears.
@@ -117,13 +120,15 @@ extern "C" int ap_debug_search_profile(unsigned long long out8[8]) {
 #endif
 // Wide bf16 rows (more than 1024 columns: 24 or 32 query values per lane) do not fit seven waves' registers without
 // spilling; they run at five waves per SIMD.
-template <int DT, int NV, int NT> struct ApSearchWaves {
-    static constexpr int MIN = (DT == AP_BF16 && NV >= 3) ? (NT == 1024 ? 4 : 5) : NT <= 256 ? AP_SEARCH_WAVES_PER_SIMD : NT == 512 ? AP_SEARCH_WAVES_512 : 4;
+template <int DT, int NV, int NT, bool LIST> struct ApSearchWaves {
+    static constexpr int MIN = LIST ? 4 : (DT == AP_BF16 && NV >= 3) ? (NT == 1024 ? 4 : 5) : NT <= 256 ? AP_SEARCH_WAVES_PER_SIMD : NT == 512 ? AP_SEARCH_WAVES_512 : 4;
 };
 // FLOOR: neighbours with a bound below the estimated end of the pool wait (large pools searched with bounds).
-template <int DT, int NV, bool KW, bool BIG, int NT, bool FLOOR>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ApSearchWaves<DT, NV, NT>::MIN, 8)))
+// LIST: an iteration's neighbours are listed by their ids and scored g.cmax at a time (large pools of which two then fit a CU).
+template <int DT, int NV, bool KW, bool BIG, int NT, bool FLOOR, bool LIST = false>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ApSearchWaves<DT, NV, NT, LIST>::MIN, 8)))
 void k_search(ApSearchArgs g) {
+    static_assert(!LIST || (!KW && !BIG && NT == 512), "lists are for the plain search's large pools");
     static_assert(!FLOOR || (!KW && !BIG && NT >= 512), "the floor is for the plain search's large pools");
     extern __shared__ __attribute__((aligned(16))) uint64_t smem64[];   // 16-byte aligned: the descriptors are read as uint4
     // Large pools (workgroups of 512 or 1024 threads): the keys that cannot enter are dropped before sorting, and
@@ -144,7 +149,8 @@ void k_search(ApSearchArgs g) {
     uint64_t *xk = PIPE ? reinterpret_cast<uint64_t *>(s_meta) : nxt + g.nxtw;   // cmax words.  KW: satisfying keys the pool did not keep in this iteration; PIPE: entering keys, unordered
     uint64_t *kwc = nxt + g.nxtw + (KW ? g.cmax : 0);   // KW: the secondary pool, k keys, best first
     uint64_t *umask = kwc + (KW ? g.k : 0);   // PIPE: one bit per pool entry; after it the visited set when it lives in LDS
-    __shared__ int32_t s_cnt, s_np, s_skip, s_drop, s_wait, s_stop, s_xn, s_kc, s_nin, s_rmin;
+    int32_t *s_ids = reinterpret_cast<int32_t *>(umask + (g.L + 63) / 64 + 1);   // LIST: the ids (umask also holds a word a block and one more)
+    __shared__ int32_t s_cnt, s_nid, s_np, s_skip, s_drop, s_wait, s_stop, s_xn, s_kc, s_nin, s_rmin;
     __shared__ int32_t s_par[16], s_psat[16];
     __shared__ int32_t s_kw[AP_KW_MAX_TERMS], s_kwcol[AP_KW_MAX_TERMS];
     __shared__ int32_t s_seed[2];
@@ -188,7 +194,7 @@ void k_search(ApSearchArgs g) {
         vis.l = (AP_LDS uint32_t *)reinterpret_cast<uint32_t *>(umask + (PIPE ? (g.L + 63) / 64 : 0));
         for (size_t i = threadIdx.x; i < g.words; i += blockDim.x) vis.l[i] = 0u;
     }
-    if (threadIdx.x == 0) { s_cnt = 0; s_skip = 0; s_drop = 0; s_wait = 0; s_xn = 0; s_kc = 0; s_nin = 0; }
+    if (threadIdx.x == 0) { s_cnt = 0; s_nid = 0; s_skip = 0; s_drop = 0; s_wait = 0; s_xn = 0; s_kc = 0; s_nin = 0; }
     // the query's required terms, unused slots squeezed out (uniform)
     int32_t n_kw = 0;
     if (KW) {
@@ -233,17 +239,28 @@ void k_search(ApSearchArgs g) {
     const uint32_t AP_NO_BOUND = 0xff800000u;   // -inf
     bool waiting = false, may_wait = FLOOR;       // uniform
     int64_t scan = -1;                            // where the scan of what waits is, -1: none under way
+    int32_t n_id = 0, next_id = 0;                // uniform: listed neighbours of this iteration, those taken from the list
     AP_PROF_DECL;
     for (;;) {
         AP_PROF(0);
-        const int32_t c = ap_uniform_i32(s_cnt);   // counts and keys that every thread reads alike are kept in scalar registers
+        int32_t c = ap_uniform_i32(s_cnt);   // counts and keys that every thread reads alike are kept in scalar registers
+        if (LIST && next_id < n_id) {   // uniform: the next of the listed neighbours
+            c = n_id - next_id < g.cmax ? n_id - next_id : g.cmax;
+            for (int32_t t = threadIdx.x; t < c; t += NT) {
+                const int32_t v = s_ids[next_id + t];
+                const uint4 m = g.meta[v];
+                s_meta[t] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
+            }
+            next_id += c;
+            __syncthreads();
+        }
         nscored += c;
         const bool pool_full = len == g.L;
         const uint64_t worst = pool_full ? ap_uniform_u64(cur[g.L - 1]) : 0ull;
         const float worst_score = ap_key_score(worst);
         const bool second_full = kw_on && s_kc == g.k;   // s_kc and kwc were last written before the previous barriers
         const float second_worst = second_full ? ap_key_score(kwc[g.k - 1]) : 0.f;
-        constexpr int G = ApSearchG<NT>::G;
+        constexpr int G = ApSearchG<NT, LIST>::G;
         if (use_tab)
             nskipped += ap_score_candidates<DT, NV, true, KW, BIG, NT / 64, G>(g.D, g.rec, qa, qtab, a, wd, ws, wf, qnorm, pool_full, worst_score,
                                                                  s_meta, c, newk, s_kw, n_kw, g.kw_all != 0, second_full, second_worst, msp, mtx, bound_on);
@@ -473,6 +490,10 @@ void k_search(ApSearchArgs g) {
             }
         }
         AP_PROF(4);
+        if (LIST && next_id < n_id) {
+            if (cin == 0) __syncthreads();   // else the merge has ended with one
+            continue;
+        }
         if (g.max_iters > 0 && it >= g.max_iters) break;
         // S8: pick the best `width` unexpanded entries (wave 0), mark them expanded
         int32_t pipe_np = 0;
@@ -634,6 +655,7 @@ void k_search(ApSearchArgs g) {
                     if (out) { ndropped++; continue; }
                     if (wait) { s_wait = 1; ndropped++; continue; }
                     if (below) bound[v[j]] = AP_NO_BOUND;
+                    if (LIST) { s_ids[atomicAdd(&s_nid, 1)] = v[j]; continue; }
                     const uint4 m = g.meta[v[j]];
                     s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v[j]);
                 }
@@ -645,13 +667,22 @@ void k_search(ApSearchArgs g) {
                     // the descriptor (where the record is, how long, the dense norm) is fetched along with the visited
                     // test, not after it: one memory round trip less per iteration for 16 bytes per neighbour already seen
                     const bool seen = vis.test_and_set(v);
-                    const uint4 m = g.meta[v];
-                    if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
+                    if (LIST) { if (!seen) s_ids[atomicAdd(&s_nid, 1)] = v; }
+                    else {
+                        const uint4 m = g.meta[v];
+                        if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
+                    }
                     if (FLOOR && !seen && may_wait) bound[v] = AP_NO_BOUND;
                 }
             }
         }
         __syncthreads();
+        if (LIST) {
+            n_id = ap_uniform_i32(s_nid);
+            next_id = 0;
+            __syncthreads();   // everyone has read the count
+            if (threadIdx.x == 0) s_nid = 0;   // next touched after further barriers
+        }
         AP_PROF(6);
         it++;
     }
@@ -841,19 +872,31 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     g.bound_col = ix->bd_mem ? ix->bd_col + ix->corpus.sp_vocab : nullptr;
     g.bound_bits = ix->bd_bits;
     g.tx_vocab = ix->corpus.tx_vocab;
-    auto lds_bytes = [&](int32_t nt) {
+    auto lds_bytes = [&](int32_t nt, int32_t cmax, int32_t icap) {
         const bool pipe = !kw && !big_tables && nt >= 512;   // the large-pool path: entering keys in the candidates' space, a bitmap of the pool
-        const int32_t nxtw = !pipe && g.cmax > nt ? g.cmax : 0;
-        return (size_t)(g.L + (pipe ? 1 : 2) * g.cmax + nxtw + (kw ? g.cmax + g.k : 0)) * 8 + (size_t)g.cmax * 16 +
-               (size_t)(big_tables ? ApQTab<true>::SLOTS : ApQTab<false>::SLOTS) * 8 + (pipe ? (size_t)((g.L + 63) / 64) * 8 : 0);
+        const int32_t nxtw = !pipe && cmax > nt ? cmax : 0;
+        return (size_t)(g.L + (pipe ? 1 : 2) * cmax + nxtw + (kw ? cmax + g.k : 0)) * 8 + (size_t)cmax * 16 +
+               (size_t)(big_tables ? ApQTab<true>::SLOTS : ApQTab<false>::SLOTS) * 8 + (pipe ? (size_t)((g.L + 63) / 64) * 8 : 0) + (pipe && icap ? 8 + (size_t)icap * 4 : 0);
     };
     // Workgroup size (plain search): four waves as long as the LDS holds at least five workgroups per CU; a pool
     // that leaves room for two to four gets eight waves, one that fills the CU alone sixteen (measured: each is the
     // fastest in its range).
+    const int64_t at_once = std::min(ws.slab, nq);
     int32_t nt = 256;
+    g.icap = 0;
     if (!kw && !big_tables) {
-        const size_t per_cu = (size_t)160 * 1024 / lds_bytes(256);
+        const size_t per_cu = (size_t)160 * 1024 / lds_bytes(256, g.cmax, 0);
         nt = per_cu > AP_SEARCH_NT512_AT ? 256 : per_cu > AP_SEARCH_NT1024_AT ? 512 : 1024;
+        // A pool that fills the CU alone because of the candidates beside it: their descriptors and keys take 28 bytes each, their ids 4,
+        // and what gets past the bounds is a few dozen an iteration.  Listed and scored AP_SEARCH_LISTED at a time, two queries
+        // of eight waves share the CU, and one reads while the other ranks and merges.  2,000 queries of 500,000 bf16 documents,
+        // pool 8,192, sixteen parents: 79.6 -> 64.3 ms; 300 of 100,000 f32 13.8 -> 10.5, 1,500 43.6 -> 36.9.  (Pools of which three would fit then instead of two keep their candidates:
+        // three take the registers of the second candidate in flight.)
+        if (nt == 1024 && at_once > AP_CUS && ws.bound.table && g.cmax > AP_SEARCH_LISTED && 2 * (lds_bytes(512, AP_SEARCH_LISTED, g.cmax) + 640) <= (size_t)160 * 1024) {
+            nt = 512;
+            g.icap = g.cmax;
+            g.cmax = AP_SEARCH_LISTED;   // at least the 256 entry points an index may have
+        }
     }
     // Two waves a query, twice as many queries on the chip at a time: a query then takes some 1.2 times as long (its few candidates
     // an iteration keep four waves no busier than two, the steps between them wait for memory either way), so this pays where it saves
@@ -863,15 +906,14 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).
     const int32_t slots_of = ix->dtype == AP_BF16 && ix->docs.dim > 1024 ? 5 : AP_SEARCH_WAVES_PER_SIMD;   // waves a SIMD holds (ApSearchWaves)
     auto slots = [&](int32_t threads, size_t bytes) -> int64_t { return AP_CUS * (int64_t)std::min<size_t>((size_t)slots_of * 256 / threads, (size_t)160 * 1024 / bytes); };
-    const int64_t at_once = std::min(ws.slab, nq);
-    if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96 && at_once * 10 > slots(256, lds_bytes(256)) * 11 &&
-        at_once <= slots(128, lds_bytes(128)))
+    if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96 && at_once * 10 > slots(256, lds_bytes(256, g.cmax, 0)) * 11 &&
+        at_once <= slots(128, lds_bytes(128, g.cmax, 0)))
         nt = 128;
     // A floor below which neighbours wait: where a search ends by itself, in large pools.  In small ones (256 threads) what
     // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
     g.bound_floor = ws.bound.table && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? ws.bound.floor : nullptr;
     g.nxtw = nt <= 256 && g.cmax > nt ? g.cmax : 0;
-    size_t smem = lds_bytes(nt);
+    size_t smem = lds_bytes(nt, g.cmax, g.icap);
     // Visited sets in LDS (small workgroups only): when the bitset fits beside the kernel's other arrays without
     // taking a workgroup's place on the CU (seven of them run on one while the pool is small).  Measured on 100,000
     // documents (12.5 KB a set): 4 to 5 % faster up to beam 512, 29 % slower at beam 2144 where it costs two of the
@@ -890,12 +932,12 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     AP_REQUIRE(smem + 512 <= 160 * 1024, "beam and search_width need %zu bytes of LDS (limit 160 KiB)", smem + 512);
     const size_t dyn = smem - (size_t)(big_tables ? ApQTab<true>::SLOTS : ApQTab<false>::SLOTS) * 8;   // the tables are a static array
     hipError_t le = hipSuccess;
-#define AP_LAUNCH_SEARCH(KWF, BIGF, NTF, FLOORF)                                                                                         \
+#define AP_LAUNCH_SEARCH(KWF, BIGF, NTF, ...)                                                                                         \
     AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, {                                                                                  \
         if (smem > 48 * 1024)                                                                                                     \
-            le = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_search<DT, NV, KWF, BIGF, NTF, FLOORF>),                           \
+            le = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_search<DT, NV, KWF, BIGF, NTF, __VA_ARGS__>),                           \
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);                                       \
-        if (le == hipSuccess) hipLaunchKernelGGL((k_search<DT, NV, KWF, BIGF, NTF, FLOORF>), dim3((unsigned)qn), dim3(NTF), dyn, st, g);  \
+        if (le == hipSuccess) hipLaunchKernelGGL((k_search<DT, NV, KWF, BIGF, NTF, __VA_ARGS__>), dim3((unsigned)qn), dim3(NTF), dyn, st, g);  \
     })
     for (int32_t q0 = 0; q0 < nq; q0 += ws.slab) {
         const int32_t qn = std::min(ws.slab, nq - q0);
@@ -913,6 +955,8 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
         else if (big_tables) AP_LAUNCH_SEARCH(false, true, 256, false);
         else if (nt == 128) AP_LAUNCH_SEARCH(false, false, 128, false);
         else if (nt == 256) AP_LAUNCH_SEARCH(false, false, 256, false);
+        else if (g.icap && g.bound_floor) AP_LAUNCH_SEARCH(false, false, 512, true, true);
+        else if (g.icap) AP_LAUNCH_SEARCH(false, false, 512, false, true);
         else if (nt == 512 && g.bound_floor) AP_LAUNCH_SEARCH(false, false, 512, true);
         else if (nt == 512) AP_LAUNCH_SEARCH(false, false, 512, false);
         else if (g.bound_floor) AP_LAUNCH_SEARCH(false, false, 1024, true);
