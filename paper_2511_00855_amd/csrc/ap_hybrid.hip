@@ -206,23 +206,28 @@ __global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ score
     }
 }
 
-// The exact top-k out of the table of upper bounds: one workgroup per query.  Every thread's best bound of its share of
-// the row gives 1,024 documents; the k best of them are scored, and the least of their scores, T, is one that the k-th
+// The exact top-k out of the table of upper bounds: one workgroup per query.  Every thread keeps the AP_BT_KEPT best bounds of its
+// share of the row; k of the best of all of them are scored, and the least of their scores, T, is one that the k-th
 // result reaches at least, so only documents whose bound is not below T have to be scored (some fifty for k = 10 on
-// 100,000 documents).  Two passes over the row, bound by reading it.  A query with more than AP_BT_CAND of them is left to
+// 100,000 documents).  Those are among the kept ones, unless all that a thread kept reach T: then the row is read once more.  Bound by
+// reading the row and by the waits of the few scores that follow; eight waves a workgroup, so that four share a CU and
+// 1,000 queries run at once.  A query with more than AP_BT_CAND candidates is left to
 // the exhaustive scorer.  1,000 queries of 100,000 documents (768 f32 columns), k = 10: 74.9 ms with the exhaustive scorer,
-// 0.97 ms with the table, which takes 0.71 ms of it.
+// 0.96 ms with the table read twice by 1,024 threads that sort their best bounds (this kernel 0.249), 0.84 now (scalar registers of seven waves a SIMD: 0.88).
 #define AP_BT_CAND 4096
+#define AP_BT_NT 512
+#define AP_BT_KEPT 4
+#define AP_BT_BINS 512
 template <int DT, int NV>
-__global__ __launch_bounds__(1024) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
+__global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF16 && NV >= 3 ? 5 : 8, 8))) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
                                                      const float *__restrict__ table, int64_t ld, int32_t k, int32_t *__restrict__ out_ids,
                                                      float *__restrict__ out_scores, int32_t *__restrict__ over /* [0] count, then queries */) {
-    __shared__ uint64_t keys[AP_BT_CAND];
-    __shared__ int32_t cand[AP_BT_CAND];
+    __shared__ uint64_t keys[AP_BT_CAND];   // candidates: their ids, then their keys
     __shared__ int32_t l_sp_idx[AP_BF_QCAP], l_tx_idx[AP_BF_QCAP];
     __shared__ float l_sp_val[AP_BF_QCAP], l_tx_val[AP_BF_QCAP];
+    __shared__ uint32_t hist[AP_BT_BINS];
     __shared__ int32_t s_n;
-    __shared__ uint32_t s_T;
+    __shared__ uint32_t s_T, s_lo, s_hi, s_line;
     const int64_t q = q0 + blockIdx.x;
     const float *row = table + (int64_t)blockIdx.x * ld;
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
@@ -236,34 +241,98 @@ __global__ __launch_bounds__(1024) void k_bound_topk(ApVecs Q, ApVecs D, int64_t
         return ap_fuse(wd, ws, wf, sd, ss, sf);
     };
     const int64_t n4 = (D.n + 3) / 4;
-    float best = -INFINITY;
-    int32_t best_id = -1;
-    for (int64_t j = threadIdx.x; j < n4; j += 1024) {
+    // bounds as codes that ascend with them, one that is no number above all; 0: none
+    uint32_t best[AP_BT_KEPT];
+    int32_t id[AP_BT_KEPT];
+#pragma unroll
+    for (int i = 0; i < AP_BT_KEPT; i++) { best[i] = 0u; id[i] = -1; }
+    for (int64_t j = threadIdx.x; j < n4; j += AP_BT_NT) {
         const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
         const float x[4] = {x4.x, x4.y, x4.z, x4.w};
 #pragma unroll
-        for (int e = 0; e < 4; e++)
-            if (j * 4 + e < D.n && (best_id < 0 || !(x[e] <= best))) { best = x[e]; best_id = (int32_t)(j * 4 + e); }
+        for (int e = 0; e < 4; e++) {
+            uint32_t o = x[e] == x[e] ? ap_f2ord(x[e]) : 0xffffffffu;
+            if (j * 4 + e >= D.n) o = 0u;
+            if (o > best[AP_BT_KEPT - 1]) {
+                int32_t v = (int32_t)(j * 4 + e);
+#pragma unroll
+                for (int i = 0; i < AP_BT_KEPT; i++) {   // into its place, what it pushes out one further
+                    const bool up = o > best[i];
+                    const uint32_t ob = best[i];
+                    const int32_t oi = id[i];
+                    best[i] = up ? o : ob; id[i] = up ? v : oi;
+                    o = up ? ob : o; v = up ? oi : v;
+                }
+            }
+        }
     }
-    keys[threadIdx.x] = best_id >= 0 ? ap_make_key(best == best ? best : INFINITY, best_id, 1u) : 0ull;
-    if (threadIdx.x == 0) { s_n = 0; s_T = 0xffffffffu; }
-    ap_bitonic_desc(keys, 1024);
-    for (int32_t i = wave; i < k; i += 16) {
-        const uint64_t key = ap_uniform_u64(keys[i]);
-        const float s = key ? score(ap_key_id(key)) : -INFINITY;
+    // k of the best: everything above the bin that the k-th lies in, and as many of the bin as are missing
+    for (int32_t i = threadIdx.x; i < AP_BT_BINS; i += AP_BT_NT) hist[i] = 0u;
+    if (threadIdx.x == 0) { s_n = 0; s_T = 0xffffffffu; s_lo = 0xffffffffu; s_hi = 0u; s_line = 0u; }
+    __syncthreads();
+    {
+        uint32_t lo = best[0] ? best[0] : 0xffffffffu, hi = best[0];   // the k best of all are best of their shares or above the worst of those
+        for (int o = 32; o > 0; o >>= 1) { lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64)); hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64)); }
+        if (lane == 0) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
+    }
+    __syncthreads();
+    const uint32_t lo = ap_uniform_u32(s_lo), hi = ap_uniform_u32(s_hi);
+    int sh = 0;
+    while (lo < hi && ((hi - lo) >> sh) >= AP_BT_BINS) sh++;
+#pragma unroll
+    for (int i = 0; i < AP_BT_KEPT; i++)
+        if (best[i] && best[i] >= lo) atomicAdd(&hist[(best[i] - lo) >> sh], 1u);
+    __syncthreads();
+    if (wave == 0) {   // lane l: bins 8 (63 - l) .. + 7, so that the prefix sum runs from the top
+        uint32_t bin[8], n = 0;
+#pragma unroll
+        for (int i = 0; i < 8; i++) { bin[i] = hist[8 * (63 - lane) + 7 - i]; n += bin[i]; }
+        uint32_t upto = n;
+        for (int o = 1; o < 64; o <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)upto, o, 64); if (lane >= o) upto += up; }
+        const uint64_t m = __ballot(upto >= (uint32_t)k);
+        if (m && lane == (int)__ffsll((unsigned long long)m) - 1) {
+            uint32_t above = upto - n, b = 8u * (64 - lane);
+#pragma unroll
+            for (int i = 0; i < 8; i++) { b -= above < (uint32_t)k ? 1u : 0u; above += bin[i]; }
+            s_line = b;
+        }
+    }
+    __syncthreads();
+    const uint32_t line = ap_uniform_u32(s_line);
+    auto bin_of = [&](uint32_t o) { return o && o >= lo ? (int32_t)((o - lo) >> sh) : -1; };
+#pragma unroll
+    for (int i = 0; i < AP_BT_KEPT; i++)
+        if (bin_of(best[i]) > (int32_t)line) keys[atomicAdd(&s_n, 1)] = (uint64_t)(uint32_t)id[i];   // fewer than k of them
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < AP_BT_KEPT; i++)
+        if (bin_of(best[i]) == (int32_t)line) { const int32_t at = atomicAdd(&s_n, 1); if (at < k) keys[at] = (uint64_t)(uint32_t)id[i]; }
+    __syncthreads();
+    const int32_t first = min(ap_uniform_i32(s_n), k);
+    for (int32_t i = wave; i < first; i += AP_BT_NT / 64) {
+        const float s = score((int32_t)ap_uniform_u32((uint32_t)keys[i]));
         if (lane == 0) atomicMin(&s_T, ap_f2ord(s));
     }
     __syncthreads();
-    const float T = ap_ord2f(s_T);
-    for (int64_t j = threadIdx.x; j < n4; j += 1024) {
-        const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
-        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+    const float T = first == k ? ap_ord2f(s_T) : -INFINITY;
+    const bool more = !(ap_ord2f(best[AP_BT_KEPT - 1]) < T) && best[AP_BT_KEPT - 1] != 0u;
+    if (threadIdx.x == 0) s_n = 0;
+    const bool again = __syncthreads_or(more) != 0;   // uniform
+    if (!again) {
 #pragma unroll
-        for (int e = 0; e < 4; e++)
-            if (j * 4 + e < D.n && !(x[e] < T)) {
-                const int32_t pos = atomicAdd(&s_n, 1);
-                if (pos < AP_BT_CAND) cand[pos] = (int32_t)(j * 4 + e);
-            }
+        for (int i = 0; i < AP_BT_KEPT; i++)
+            if (best[i] && !(ap_ord2f(best[i]) < T)) keys[atomicAdd(&s_n, 1)] = (uint64_t)(uint32_t)id[i];   // 4 * 512 at most
+    } else {
+        for (int64_t j = threadIdx.x; j < n4; j += AP_BT_NT) {
+            const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
+            const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (j * 4 + e < D.n && !(x[e] < T)) {
+                    const int32_t pos = atomicAdd(&s_n, 1);
+                    if (pos < AP_BT_CAND) keys[pos] = (uint64_t)(uint32_t)(j * 4 + e);
+                }
+        }
     }
     __syncthreads();
     const int32_t c = ap_uniform_i32(s_n);
@@ -271,16 +340,16 @@ __global__ __launch_bounds__(1024) void k_bound_topk(ApVecs Q, ApVecs D, int64_t
         if (threadIdx.x == 0) over[1 + atomicAdd(over, 1)] = (int32_t)q;
         return;
     }
-    for (int32_t i = wave; i < c; i += 16) {
-        const int32_t v = ap_uniform_i32(cand[i]);
+    for (int32_t i = wave; i < c; i += AP_BT_NT / 64) {
+        const int32_t v = (int32_t)ap_uniform_u32((uint32_t)keys[i]);
         const float s = score(v);
         if (lane == 0) keys[i] = ap_make_key(s, v, 1u);
     }
     int32_t n2 = 64;
     while (n2 < c) n2 <<= 1;
-    for (int32_t i = c + (int32_t)threadIdx.x; i < n2; i += 1024) keys[i] = 0ull;
+    for (int32_t i = c + (int32_t)threadIdx.x; i < n2; i += AP_BT_NT) keys[i] = 0ull;
     ap_bitonic_desc(keys, n2);
-    for (int32_t i = threadIdx.x; i < k; i += 1024) {
+    for (int32_t i = threadIdx.x; i < k; i += AP_BT_NT) {
         out_ids[q * k + i] = ap_key_id(keys[i]);
         out_scores[q * k + i] = ap_key_score(keys[i]);
     }
@@ -332,7 +401,7 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     const ApVecs Q = query_view(q, ix->docs.dim);
     const float *w = per_query_w ? per_query_w : ix->w_dev;
     const int32_t ws = per_query_w ? 3 : 0;
-    // Out of the table of bounds where that leaves most documents unscored: k well below the 1,024 documents the
+    // Out of the table of bounds where that leaves most documents unscored: k well below the 2,048 documents the
     // threshold comes from, and a corpus well above them (below, the exhaustive scorer has little to do).
     ApBound b;
     const size_t held = ap_bound_held(ix, st);
@@ -345,7 +414,7 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
         const int32_t nqb = std::min(b.slab, q->nq - q0);
         rc = ap_bound_fill(ix, b, Q, w, ws, q0, nqb, nullptr, 0, st);
         if (rc != AP_OK) break;
-        AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV>), dim3((unsigned)nqb), dim3(1024), 0, st, Q, ix->docs, (int64_t)q0, w,
+        AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV>), dim3((unsigned)nqb), dim3(AP_BT_NT), 0, st, Q, ix->docs, (int64_t)q0, w,
                                                                       ws, b.table, b.ld, k, out_ids, out_scores, over));
         if (hipGetLastError() != hipSuccess) { ap_set_error("ap_bruteforce_topk failed to launch"); rc = AP_EHIP; }
     }
