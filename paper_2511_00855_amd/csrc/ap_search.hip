@@ -79,6 +79,7 @@ __device__ __forceinline__ int32_t ap_rank_in(const uint64_t *keys, int32_t n, u
 #define AP_RANK_LANES 16        // lanes that rank one entering key of a large pool (16, 32 or 64)
 #endif
 #define AP_RANK_SORT 128        // entering keys of a large pool beyond which they are sorted instead of ranked one against the other
+#define AP_SEARCH_WAVES_KW2 6   // two waves a query with keywords: without spills at six waves a SIMD (2,500 queries 11.05 -> 10.62 ms)
 #define AP_SEARCH_LISTED 256    // listed neighbours that are scored at a time
 #ifndef AP_SEARCH_WAVES_512
 #define AP_SEARCH_WAVES_512 6
@@ -120,13 +121,13 @@ extern "C" int ap_debug_search_profile(unsigned long long out8[8]) {
 #endif
 // Wide bf16 rows (more than 1024 columns: 24 or 32 query values per lane) do not fit seven waves' registers without
 // spilling; they run at five waves per SIMD.
-template <int DT, int NV, int NT, bool LIST> struct ApSearchWaves {
-    static constexpr int MIN = LIST ? 4 : (DT == AP_BF16 && NV >= 3) ? (NT == 1024 ? 4 : 5) : NT <= 256 ? AP_SEARCH_WAVES_PER_SIMD : NT == 512 ? AP_SEARCH_WAVES_512 : 4;
+template <int DT, int NV, int NT, bool LIST, bool KW> struct ApSearchWaves {
+    static constexpr int MIN = LIST ? 4 : (DT == AP_BF16 && NV >= 3) ? (NT == 1024 ? 4 : 5) : NT == 128 && KW ? AP_SEARCH_WAVES_KW2 : NT <= 256 ? AP_SEARCH_WAVES_PER_SIMD : NT == 512 ? AP_SEARCH_WAVES_512 : 4;
 };
 // FLOOR: neighbours with a bound below the estimated end of the pool wait (large pools searched with bounds).
 // LIST: an iteration's neighbours are listed by their ids and scored g.cmax at a time (large pools of which two then fit a CU).
 template <int DT, int NV, bool KW, bool BIG, int NT, bool FLOOR, bool LIST = false>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ApSearchWaves<DT, NV, NT, LIST>::MIN, 8)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ApSearchWaves<DT, NV, NT, LIST, KW>::MIN, 8)))
 void k_search(ApSearchArgs g) {
     static_assert(!LIST || (!KW && !BIG && NT == 512), "lists are for the plain search's large pools");
     static_assert(!FLOOR || (!KW && !BIG && NT >= 512), "the floor is for the plain search's large pools");
@@ -901,11 +902,14 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // Two waves a query, twice as many queries on the chip at a time: a query then takes some 1.2 times as long (its few candidates
     // an iteration keep four waves no busier than two, the steps between them wait for memory either way), so this pays where it saves
     // a second, half empty round.  2,500 queries (1,792 of four waves run at a time, 3,584 of two), pool 512: 100,000 f32 documents
-    // with keywords 13.7 -> 10.8 ms, plain 9.05 -> 8.24; 60,000 bf16 10.1 -> 8.7 and 7.1 -> 6.2; 10,000 narrow ones 6.2 -> 4.8 and 4.0 -> 3.0.
+    // with keywords 13.7 -> 10.4 ms, plain 9.05 -> 8.24; 60,000 bf16 10.1 -> 8.7 and 7.1 -> 6.2; 10,000 narrow ones 6.2 -> 4.8 and 4.0 -> 3.0.
     // Not where the batch fits one round of four waves (400 to 1,792 queries: 0.80 to 0.93 of the speed) nor without bounds or with
     // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).
     const int32_t slots_of = ix->dtype == AP_BF16 && ix->docs.dim > 1024 ? 5 : AP_SEARCH_WAVES_PER_SIMD;   // waves a SIMD holds (ApSearchWaves)
-    auto slots = [&](int32_t threads, size_t bytes) -> int64_t { return AP_CUS * (int64_t)std::min<size_t>((size_t)slots_of * 256 / threads, (size_t)160 * 1024 / bytes); };
+    auto slots = [&](int32_t threads, size_t bytes) -> int64_t {
+        const int32_t waves = threads == 128 && kw ? std::min(slots_of, AP_SEARCH_WAVES_KW2) : slots_of;
+        return AP_CUS * (int64_t)std::min<size_t>((size_t)waves * 256 / threads, (size_t)160 * 1024 / bytes);
+    };
     if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96 && at_once * 10 > slots(256, lds_bytes(256, g.cmax, 0)) * 11 &&
         at_once <= slots(128, lds_bytes(128, g.cmax, 0)))
         nt = 128;
