@@ -298,14 +298,15 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
     partial_bytes = bytes_per_dist - dense_bytes
 
     # what bounds each construction stage, against its own peak: the exact dense seed product (MFMA), the refinement
-    # rounds (every candidate's record, and the dense rows its bound calls for: HBM), the neighbourhood phase (pair similarities per second)
+    # rounds (every candidate's packed lists, and the records and rows its bound calls for: HBM), the neighbourhood phase (pair similarities per second)
     K = bp.knn_k
     seed_flops = float(ix.build_counters()["seed_flops"]) or 2.0 * N * N * w.docs.dim   # what the stage's MFMA products executed
     seed_bf16 = ix.seed_products_bf16()   # f32 rows of a larger corpus are swept rounded to bf16 where that tells them apart
     seed_tflops = seed_flops / max(bt["seed"], 1e-9) / 1e12
-    # a lower bound of what the rounds read: every candidate's record, and the dense rows of the K documents a node's first
-    # round sets its threshold with
-    refine_gbs = (refine_sims * partial_bytes + (N * K * dense_bytes if args.rounds else 0)) / max(bt["refine"], 1e-9) / 1e9
+    # a lower bound of what the rounds read: every candidate's packed lists (12 bytes and 3 an entry), and the records and dense
+    # rows of the K documents a node's first round sets its threshold with
+    packed_bytes = 12.0 + 3.0 * (sp_nnz + tx_nnz)
+    refine_gbs = (refine_sims * packed_bytes + (N * K * bytes_per_dist if args.rounds else 0)) / max(bt["refine"], 1e-9) / 1e9
     build_roofline = dict(
         seed=dict(bound="mfma", achieved=round(seed_tflops, 1), peak=MFMA_PEAK_TFLOPS[seed_bf16], unit="TFLOP/s",
                   frac=round(seed_tflops / MFMA_PEAK_TFLOPS[seed_bf16], 4), flops=seed_flops,
@@ -314,7 +315,7 @@ def run_workload(args, name, *, n, nq, steps, warmup, sweep_text, cpu_seconds, g
                   note="FLOPs the stage's dense products executed (sampled columns + sweep, padded tiles included; bf16 rows: only the "
                        "tiles on and above the diagonal of D D^T) over the whole stage's time (products, selections)"),
         refine=dict(bound="hbm", achieved=round(refine_gbs, 1), peak=HBM_PEAK_GBS, unit="GB/s", frac=round(refine_gbs / HBM_PEAK_GBS, 4),
-                    similarities=refine_sims, record_bytes=round(partial_bytes, 1),
+                    similarities=refine_sims, packed_bytes=round(packed_bytes, 1),
                     similarities_per_s=round(refine_sims / max(bt["refine"], 1e-9), 1)),
         prune=dict(bound="alu", pair_similarities=N * K * (K - 1) // 2,
                    pair_similarities_per_s=round(N * K * (K - 1) / 2 / max(bt["prune"], 1e-9), 1),
