@@ -210,16 +210,18 @@ __global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ score
 // share of the row; k of the best of all of them are scored, and the least of their scores, T, is one that the k-th
 // result reaches at least, so only documents whose bound is not below T have to be scored (some fifty for k = 10 on
 // 100,000 documents).  Those are among the kept ones, unless all that a thread kept reach T: then the row is read once more.  Bound by
-// reading the row and by the waits of the few scores that follow; eight waves a workgroup, so that four share a CU and
-// 1,000 queries run at once.  A query with more than AP_BT_CAND candidates is left to
+// reading the row and by the waits of the few scores that follow; eight waves a workgroup where there are many queries, so that four share
+// a CU and 1,000 queries run at once.  A query with more than AP_BT_CAND candidates is left to
 // the exhaustive scorer.  1,000 queries of 100,000 documents (768 f32 columns), k = 10: 74.9 ms with the exhaustive scorer,
 // 0.96 ms with the table read twice by 1,024 threads that sort their best bounds (this kernel 0.249), 0.84 now (scalar registers of seven waves a SIMD: 0.88).
 #define AP_BT_CAND 4096
-#define AP_BT_NT 512
+// Queries up to which a workgroup has 1,024 threads, two of which fit a CU: with fewer queries a CU would have waves to spare.  With 512 threads
+// instead, k = 100: 1 query of 150,000 documents 301 -> 347 us, 16 of 12,000 158 -> 190, 400 of 12,000 201 -> 229 (k = 10: 150 -> 151).
+#define AP_BT_FEW 512
 #define AP_BT_KEPT 4
 #define AP_BT_BINS 512
-template <int DT, int NV>
-__global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF16 && NV >= 3 ? 5 : 8, 8))) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
+template <int DT, int NV, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF16 && NV >= 3 ? 5 : 8, 8))) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
                                                      const float *__restrict__ table, int64_t ld, int32_t k, int32_t *__restrict__ out_ids,
                                                      float *__restrict__ out_scores, int32_t *__restrict__ over /* [0] count, then queries */) {
     __shared__ uint64_t keys[AP_BT_CAND];   // candidates: their ids, then their keys
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == 
     int32_t id[AP_BT_KEPT];
 #pragma unroll
     for (int i = 0; i < AP_BT_KEPT; i++) { best[i] = 0u; id[i] = -1; }
-    for (int64_t j = threadIdx.x; j < n4; j += AP_BT_NT) {
+    for (int64_t j = threadIdx.x; j < n4; j += NT) {
         const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
         const float x[4] = {x4.x, x4.y, x4.z, x4.w};
 #pragma unroll
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == 
         }
     }
     // k of the best: everything above the bin that the k-th lies in, and as many of the bin as are missing
-    for (int32_t i = threadIdx.x; i < AP_BT_BINS; i += AP_BT_NT) hist[i] = 0u;
+    for (int32_t i = threadIdx.x; i < AP_BT_BINS; i += NT) hist[i] = 0u;
     if (threadIdx.x == 0) { s_n = 0; s_T = 0xffffffffu; s_lo = 0xffffffffu; s_hi = 0u; s_line = 0u; }
     __syncthreads();
     {
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == 
         if (bin_of(best[i]) == (int32_t)line) { const int32_t at = atomicAdd(&s_n, 1); if (at < k) keys[at] = (uint64_t)(uint32_t)id[i]; }
     __syncthreads();
     const int32_t first = min(ap_uniform_i32(s_n), k);
-    for (int32_t i = wave; i < first; i += AP_BT_NT / 64) {
+    for (int32_t i = wave; i < first; i += NT / 64) {
         const float s = score((int32_t)ap_uniform_u32((uint32_t)keys[i]));
         if (lane == 0) atomicMin(&s_T, ap_f2ord(s));
     }
@@ -321,9 +323,9 @@ __global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == 
     if (!again) {
 #pragma unroll
         for (int i = 0; i < AP_BT_KEPT; i++)
-            if (best[i] && !(ap_ord2f(best[i]) < T)) keys[atomicAdd(&s_n, 1)] = (uint64_t)(uint32_t)id[i];   // 4 * 512 at most
+            if (best[i] && !(ap_ord2f(best[i]) < T)) keys[atomicAdd(&s_n, 1)] = (uint64_t)(uint32_t)id[i];   // 4 * NT at most, which keys[] holds
     } else {
-        for (int64_t j = threadIdx.x; j < n4; j += AP_BT_NT) {
+        for (int64_t j = threadIdx.x; j < n4; j += NT) {
             const float4 x4 = reinterpret_cast<const float4 *>(row)[j];
             const float x[4] = {x4.x, x4.y, x4.z, x4.w};
 #pragma unroll
@@ -340,16 +342,16 @@ __global__ __launch_bounds__(AP_BT_NT) __attribute__((amdgpu_waves_per_eu(DT == 
         if (threadIdx.x == 0) over[1 + atomicAdd(over, 1)] = (int32_t)q;
         return;
     }
-    for (int32_t i = wave; i < c; i += AP_BT_NT / 64) {
+    for (int32_t i = wave; i < c; i += NT / 64) {
         const int32_t v = (int32_t)ap_uniform_u32((uint32_t)keys[i]);
         const float s = score(v);
         if (lane == 0) keys[i] = ap_make_key(s, v, 1u);
     }
     int32_t n2 = 64;
     while (n2 < c) n2 <<= 1;
-    for (int32_t i = c + (int32_t)threadIdx.x; i < n2; i += AP_BT_NT) keys[i] = 0ull;
+    for (int32_t i = c + (int32_t)threadIdx.x; i < n2; i += NT) keys[i] = 0ull;
     ap_bitonic_desc(keys, n2);
-    for (int32_t i = threadIdx.x; i < k; i += AP_BT_NT) {
+    for (int32_t i = threadIdx.x; i < k; i += NT) {
         out_ids[q * k + i] = ap_key_id(keys[i]);
         out_scores[q * k + i] = ap_key_score(keys[i]);
     }
@@ -414,8 +416,12 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
         const int32_t nqb = std::min(b.slab, q->nq - q0);
         rc = ap_bound_fill(ix, b, Q, w, ws, q0, nqb, nullptr, 0, st);
         if (rc != AP_OK) break;
-        AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV>), dim3((unsigned)nqb), dim3(AP_BT_NT), 0, st, Q, ix->docs, (int64_t)q0, w,
-                                                                      ws, b.table, b.ld, k, out_ids, out_scores, over));
+        if (nqb <= AP_BT_FEW)
+            AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV, 1024>), dim3((unsigned)nqb), dim3(1024), 0, st, Q, ix->docs,
+                                                                          (int64_t)q0, w, ws, b.table, b.ld, k, out_ids, out_scores, over));
+        else
+            AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV, 512>), dim3((unsigned)nqb), dim3(512), 0, st, Q, ix->docs,
+                                                                          (int64_t)q0, w, ws, b.table, b.ld, k, out_ids, out_scores, over));
         if (hipGetLastError() != hipSuccess) { ap_set_error("ap_bruteforce_topk failed to launch"); rc = AP_EHIP; }
     }
     b.finish();   // the host waits below: searches of this index on other streams need not

@@ -1,4 +1,5 @@
-"""Exact top-k out of the table of bounds: a thread keeps the four best of its share of the row (four documents in every 2,048).  The
+"""Exact top-k out of the table of bounds: a thread keeps the four best of its share of the row (four documents in every 2,048 or 4,096:
+few queries get 1,024 threads each, more of them 512).  The
 results are those of scoring everything, also where the best documents all lie in one share, where all scores tie, and at the
 smallest corpus that takes this way."""
 import numpy as np
@@ -11,10 +12,10 @@ from paper_2511_00855_amd.synth import make_workload
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("nq", [37, 513])
 @pytest.mark.parametrize("n,dim,bf16,where", [(4096, 64, False, "spread"), (4099, 100, False, "one share"), (20_001, 64, True, "one share"), (9000, 1544, True, "spread"),
                                               (12_345, 768, False, "one share"), (5000, 32, False, "alike")])
-def test_against_all_scores(n, dim, bf16, where):
-    nq = 37
+def test_against_all_scores(n, dim, bf16, where, nq):
     w = make_workload("tiny", seed=6, n=n, nq=nq, dim=dim, bf16=bf16)
     d = w.docs
     rng = np.random.default_rng(2)
