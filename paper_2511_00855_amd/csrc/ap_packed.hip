@@ -98,6 +98,7 @@ int ap_pack_lists(const ap_index *ix, hipStream_t st, ApPacked *out) {
         AP_CHECK_HIP(hipStreamSynchronize(st));
         nnz -= first[0] + first[1];
     }
+    if (nnz * ix->params.knn_k < AP_PK_WORK) return AP_OK;
     const size_t rec_bytes = (size_t)ap_pk_line(nnz, n) * AP_PK_LINE;
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     const bool count = ix->bd_df == nullptr;   // the columns of the bounds are not there: their document frequencies are not either

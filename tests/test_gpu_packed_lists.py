@@ -36,13 +36,14 @@ CASES = {   # name: (workload, K, S, P, build weights, what is done to the docum
     "rare terms share slots": (dict(n=1500, vocab=200_000, sp=SP, tx=TX), 64, 32, 11, (1.0, 1.0, 1.0), None),
     "units beyond three a lane": (dict(n=600, sp=("fixed", 131), tx=("fixed", 120)), 32, 24, 6, (1.0, 1.0, 1.0), None),
     "lists too long for the tables": (dict(n=520, sp=("fixed", 300), tx=("fixed", 200)), 24, 16, 6, (1.0, 1.0, 1.0), None),
-    "fewest that are packed": (dict(n=512), 32, 32, 11, (1.0, 1.0, 1.0), None),
-    "one fewer": (dict(n=511), 32, 32, 11, (1.0, 1.0, 1.0), None),
-    "empty and short lists": (dict(n=700, sp=("poisson", 1), tx=("fixed", 5)), 32, 32, 32, (1.0, 1.0, 1.0), None),
+    "fewest that are packed": (dict(n=512, sp=SP, tx=TX), 32, 32, 11, (1.0, 1.0, 1.0), None),
+    "one fewer": (dict(n=511, sp=SP, tx=TX), 32, 32, 11, (1.0, 1.0, 1.0), None),
+    "too short for it": (dict(n=700, sp=("poisson", 10), tx=("fixed", 10)), 32, 32, 11, (1.0, 1.0, 1.0), None),
+    "empty and short lists": (dict(n=14000, sp=("poisson", 1), tx=("fixed", 5)), 32, 32, 32, (1.0, 1.0, 1.0), None),
     "negative weights": (dict(n=900, sp=SP, tx=TX), 64, 32, 11, (1.0, 1.0, 1.0), _negative),
     "weights far apart": (dict(n=900), 64, 32, 11, (1.0, 1.0, 1.0), _far_apart),
-    "sums beyond the range": (dict(n=600), 32, 32, 8, (1.0, 1.0, 1.0), _beyond),
-    "documents alike": (dict(n=600, sp=("fixed", 20), tx=("fixed", 20)), 48, 32, 11, (1.0, 1.0, 1.0), _alike),
+    "sums beyond the range": (dict(n=1300), 32, 32, 8, (1.0, 1.0, 1.0), _beyond),
+    "documents alike": (dict(n=1400, sp=("fixed", 20), tx=("fixed", 20)), 48, 32, 11, (1.0, 1.0, 1.0), _alike),
     "negative weight of a path": (dict(n=700), 32, 32, 8, (0.5, -1.0, 1.0), None),
     "lexical part alone": (dict(n=1100, sp=SP, tx=TX), 96, 32, 16, (0.0, 0.0, 1.0), None),
 }
