@@ -1124,7 +1124,11 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         constexpr int G = AP_RF_GP, U = 3;
         const AP_LDS uint8_t *tab = (const AP_LDS uint8_t *)pool;
         const int sub = lane >> 4, l16 = lane & 15;
-        own_sp *= 1.00004f; own_tx *= 1.00004f;   // what the sums of the scoring kernels may round up
+        // What a sum of the scoring kernels may come out above the exact one: a lane adds what the lists share one after the other, each addition
+        // rounds up by at most 2^-24 of the sum so far, and the node's list is the longest that two can share; 1e-5 for the six additions over the
+        // lanes and what the products here round off.  (A fixed 4e-5 for all of it held up to some 46,000 entries, 738 a lane, of the 65,535 that are taken.)
+        own_sp *= fmaf(6e-8f, 4.f * (float)(own_at.y & 0xffffu), 1.00001f);
+        own_tx *= fmaf(6e-8f, 4.f * (float)(own_at.y >> 16), 1.00001f);
         if (wave == NW - 1) build_tables();   // the others begin without it: 4 G candidates at a time go to the wave that asks
         auto ask = [&]() {
             int32_t i = 0;

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2511_00855_amd import binding as B
-from paper_2511_00855_amd.synth import make_workload
+from paper_2511_00855_amd.synth import VecSet, make_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -70,4 +70,64 @@ def test_packed_lists_change_no_list(name):
     g = ix.stage_prune(K, 16, ids, sc, want_pm=False)
     assert torch.equal(spi, i2) and torch.equal(sps.view(torch.int32), s2.view(torch.int32))
     assert torch.equal(srt, g["sorted_ids"])
+    full.close(); ix.close()
+
+
+def _longest_lists():
+    """Two documents, U and U + 10, with learned-sparse lists of 65,473 terms, of whose sum of products every addition rounds up:
+    64 large weights, one at the head of each lane's share, then 1,022 terms a lane whose product is a little more than half a unit
+    in the last place above a whole number of them.  All weights lie just below a step of the 8-bit weights, so the packed lists add next
+    to nothing.  One other document, U + 1, has a learned-sparse part with U that lies 7e-6 below that sum as it comes out and 5e-5 above
+    the exact one."""
+    f, n, U, nb, per = np.float32, 600, 300, 64, 1022
+    most = f(np.sqrt(1.0034) * 254 / 253)
+    scale = f(most * f(f(1.00001) / f(254))); inv = f(f(1.000002) / scale)
+
+    def below(level):   # the largest weight that is rounded up to this step
+        x = f(level * scale)
+        while int(f(x * inv)) + 1 > level:
+            x = np.nextafter(x, f(0))
+        return x
+    a, s = below(253), below(1)
+    lane = f(float(a) ** 2)
+    for _ in range(per):   # fused multiply-adds of one lane; the 64 lanes are alike, so their sum is exact
+        lane = f(float(lane) + float(s) ** 2)
+    exact = nb * (float(a) ** 2 + per * float(s) ** 2)
+    total = 64 * float(lane)
+    assert total > exact * (1 + 5.5e-5)
+    m = nb + 64 * per
+    long_idx, long_val = np.arange(m), np.concatenate([np.full(nb, a), np.full(m - nb, s)])
+    rng = np.random.default_rng(8)
+    sp, tx = [], []
+    for u in range(n):
+        if u in (U, U + 10):   # the largest weight of each is on a term that the other does not hold
+            sp.append((np.append(long_idx, m + (u != U)), np.append(long_val, most)))
+        elif u == U + 1:
+            sp.append((np.array([m]), np.array([(0.125 * exact + 0.875 * total) / float(most)])))
+        else:   # the large terms are frequent, the others share slots
+            sp.append((np.append(np.arange(nb), [m, m + 1]), rng.uniform(1e-4, 1e-3, nb + 2)))
+        # U and the documents around it, U + 10 not among them, share a keyword: what U + 10 lacks for U's list
+        tx.append([1 if U - 12 <= u <= U + 9 else 0])
+    ip = lambda rows: np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    turn = 2 * np.pi * np.arange(n) / n
+    dense = np.stack([np.cos(turn), np.sin(turn), 0 * turn, 0 * turn], axis=1).astype(np.float32)
+    return VecSet(n, 4, dense, ip([r[0] for r in sp]), np.concatenate([r[0] for r in sp]).astype(np.int32),
+                  np.concatenate([r[1] for r in sp]).astype(np.float32), ip(tx), np.concatenate(tx).astype(np.int32), np.ones(n, np.float32), m + 2, 2), U
+
+
+def test_sums_of_the_longest_lists():
+    """A lane's sum may round up at each of its additions, 6e-8 of it at a time: the bound allows for as many as there are."""
+    d, U = _longest_lists()
+    K, S = 16, 16
+    docs = B.DeviceVecs(d)
+    bp = B.build_params(16, knn_k=K, nd_rounds=1, nd_sample=S, sp_len=1, n_entry=4, build_w=(1.0, 0.0, 1.0))
+    full = B.Index.build(docs, bp)
+    _, _, spi, sps = full.export_build_state()
+    ix = B.Index.ingest(docs, bp)
+    ids, _ = ix.stage_seed_knn(K)
+    i2 = torch.full((3, d.n, 1), -1, dtype=torch.int32, device=docs.device)
+    s2 = torch.full((3, d.n, 1), -np.inf, dtype=torch.float32, device=docs.device)
+    ids, _, i2, s2 = ix.stage_refine(K, S, 1, ids, i2, s2)
+    assert int(i2[1, U, 0]) == U + 10 and not bool((ids[U] == U + 10).any())   # it enters the per-path list alone
+    assert torch.equal(spi, i2) and torch.equal(sps.view(torch.int32), s2.view(torch.int32))
     full.close(); ix.close()
