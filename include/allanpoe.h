@@ -359,6 +359,14 @@ int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
  * f32 (the candidates are then scored again in f32), 0 = f32. */
 int ap_build_seed_bf16(const ap_index *index, int32_t *out);
 
+/* Whether the rounds of the last construction or insertion that gave this index told candidates apart by packed lists
+ * (host int32): 1 = yes, 0 = every candidate's record was read. */
+int ap_build_packed(const ap_index *index, int32_t *out);
+
+/* How the last search that wrote this index's counters ran (host array): [0] threads a query, 0 = by the walk of small
+ * batches, [1] 1 = an iteration's neighbours are listed by their ids, [2] 1 = the visited sets lie in LDS. */
+int ap_search_form(const ap_index *index, int32_t out3[3]);
+
 /* Debug settings, for tests: they drive small inputs through the code paths of large ones and never change a
  * result.  One process-wide value per name (host string), 0 = the library's own choice:
  *   "seed_sample_cols"        columns sampled for the seed threshold (forces the thresholded sweep on small corpora)

@@ -495,6 +495,18 @@ class Index:
         _check(lib().ap_build_seed_bf16(self._h, C.byref(out)), "ap_build_seed_bf16")
         return bool(out.value)
 
+    def packed_lists(self) -> bool:
+        """Whether the refinement rounds that made this index told candidates apart by packed lists."""
+        out = C.c_int32(0)
+        _check(lib().ap_build_packed(self._h, C.byref(out)), "ap_build_packed")
+        return bool(out.value)
+
+    def search_form(self):
+        """How the last search ran: threads a query (0: the walk of small batches), neighbours listed, visited sets in LDS."""
+        out = (C.c_int32 * 3)()
+        _check(lib().ap_search_form(self._h, out), "ap_search_form")
+        return dict(threads=int(out[0]), listed=bool(out[1]), visited_lds=bool(out[2]))
+
     def build_timings(self):
         out = (C.c_float * 6)()
         _check(lib().ap_build_timings(self._h, out), "ap_build_timings")

@@ -497,6 +497,12 @@ extern "C" int ap_build_seed_bf16(const ap_index *ix, int32_t *out) {
     return AP_OK;
 }
 
+extern "C" int ap_build_packed(const ap_index *ix, int32_t *out) {
+    AP_REQUIRE(ix && out, "NULL argument");
+    *out = ix->packed_lists;
+    return AP_OK;
+}
+
 extern "C" int ap_build_timings(const ap_index *ix, float out6[6]) {
     AP_REQUIRE(ix && out6, "NULL argument");
     memcpy(out6, ix->timings, sizeof(ix->timings));

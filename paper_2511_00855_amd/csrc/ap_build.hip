@@ -1593,6 +1593,7 @@ int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, i
     }
     ApPacked pk;
     if (rc == AP_OK) rc = ap_pack_lists(ix, st, &pk);
+    ix->packed_lists = pk.rec != nullptr;
     for (int32_t t = 0; t < rounds && rc == AP_OK; t++) {
         const int c = *cur;
         const ApRefineHints hint = t == 0 ? ApRefineHints{tau, sc[c], nullptr, nullptr, known[0], pk.rec, pk.at}

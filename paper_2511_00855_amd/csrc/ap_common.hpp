@@ -65,6 +65,7 @@ struct ap_index {
     int32_t *df = nullptr;     // owned: document frequency per term
     unsigned long long *counters = nullptr;   // owned: [0] hybrid similarities evaluated by refinement rounds on this index
     mutable int seed_bf16 = 0;                     // 1: the last seed stage's products over the whole corpus took bf16 rows (stored or rounded)
+    mutable int packed_lists = 0;                  // 1: the last refinement rounds had packed lists
     mutable unsigned long long seed_flops = 0;   // FLOPs (2 per multiply-add, padded tiles included) of the seed stage's dense products so far
     float *stats = nullptr;    // owned: [0] avgdl
     float *self_sim = nullptr; // owned: fused self-similarity under build_w
@@ -100,6 +101,7 @@ struct ap_index {
     int32_t *search_counts = nullptr;  // nq x 2 of the last search: similarities evaluated, iterations
     size_t search_counts_cap = 0;
     int32_t last_nq = 0;
+    mutable int32_t search_form[3] = {0, 0, 0};   // of the last search: threads a query (0: the walk), neighbours listed by their ids, visited sets in LDS
     hipEvent_t ev_search[2] = {nullptr, nullptr};
     float timings[6] = {0, 0, 0, 0, 0, 0};
     // owned: what the construction leaves behind for later insertions (NULL for imported graphs):

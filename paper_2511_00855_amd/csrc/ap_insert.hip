@@ -152,6 +152,7 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
         AP_TRY(B.get(&r_sc[1], (size_t)m * K));
         AP_TRY(ap_seed_knn_impl(&vx, nullptr, m, K, r_ids[0], r_sc[0], st));
         AP_TRY(ap_refine_rounds(&vx, p.nd_rounds, K, p.nd_sample, P, r_ids, r_sc, spi2, sps2, &cur, st));
+        nx->packed_lists = vx.packed_lists;
         if (p.nd_rounds == 0) AP_TRY(ap_rescore_lists(&vx, m, K, r_ids[cur], r_sc[cur], st));
         hipLaunchKernelGGL(k_shift_ids, dim3(grid_for((size_t)m * K)), dim3(256), 0, st, r_ids[cur], (size_t)m * K, (int32_t)n0);
         hipLaunchKernelGGL(k_shift_ids, dim3(grid_for((size_t)3 * m * P)), dim3(256), 0, st, spi2[cur], (size_t)3 * m * P, (int32_t)n0);

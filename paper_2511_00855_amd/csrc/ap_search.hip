@@ -13,6 +13,7 @@
 // workspace of bounded size (large batches run in slabs of queries).
 #include <math.h>
 #include <stdlib.h>
+#include <string.h>
 #include <algorithm>
 #include <mutex>
 #include "ap_score.hpp"
@@ -837,7 +838,12 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // instantiation stays free of both.
     const bool kw = kw_terms != nullptr || ix->deleted != nullptr;
     const int32_t nq = (int32_t)Q.n;
+    auto note_form = [&](int32_t threads, int32_t listed, int32_t vis_lds) {   // where the call may write to the index
+        if (!ws.counts) return;
+        ix->search_form[0] = threads; ix->search_form[1] = listed; ix->search_form[2] = vis_lds;
+    };
     if (ws.walk.exact) {
+        note_form(0, 0, 0);
         if (ws.ev0) AP_CHECK_HIP(hipEventRecord(ws.ev0, st));
         if (ws.walk.bound) AP_TRY(ap_bound_fill(ix, ws.bound, Q, w_dev, w_stride, 0, nq, nullptr, 0, st));
         AP_TRY(ap_walk_launch(ix, ws.walk, ws.visited, Q, w_dev, w_stride, k, beam, width, ws.counts, out_ids, out_scores, st));
@@ -934,6 +940,7 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     }
     // the kernel's static arrays (counters, parents, required terms) take a few hundred bytes more
     AP_REQUIRE(smem + 512 <= 160 * 1024, "beam and search_width need %zu bytes of LDS (limit 160 KiB)", smem + 512);
+    note_form(nt, g.icap > 0, g.vis_lds);
     const size_t dyn = smem - (size_t)(big_tables ? ApQTab<true>::SLOTS : ApQTab<false>::SLOTS) * 8;   // the tables are a static array
     hipError_t le = hipSuccess;
 #define AP_LAUNCH_SEARCH(KWF, BIGF, NTF, ...)                                                                                         \
@@ -1087,6 +1094,13 @@ extern "C" int ap_search_batch_keywords(ap_index *ix, const ap_queries *q, const
     AP_REQUIRE(ix->docs.n < (1ll << 29), "keyword search needs n < 2^29");
     if (q->nq == 0) return ap_search_impl(ix, q, per_query_w, p, nullptr, 0, 0u, out_ids, out_scores, stream);
     return ap_search_impl(ix, q, per_query_w, p, kw_terms, kw_stride, kw_flags, out_ids, out_scores, stream);
+}
+
+extern "C" int ap_search_form(const ap_index *ix, int32_t out3[3]) {
+    AP_REQUIRE(ix && out3, "NULL argument");
+    if (ix->last_nq == 0) { ap_set_error("no search has run on this index"); return AP_ESTATE; }
+    memcpy(out3, ix->search_form, sizeof(ix->search_form));
+    return AP_OK;
 }
 
 extern "C" int ap_search_stats(const ap_index *ix, int32_t *out_counts, int32_t nq, float *kernel_ms, void *stream) {

@@ -60,6 +60,7 @@ def test_packed_lists_change_no_list(name):
     print(name, flush=True)
     bp = B.build_params(16, knn_k=K, nd_rounds=3, nd_sample=S, sp_len=P, n_entry=4, build_w=wv)
     full = B.Index.build(docs, bp)
+    assert full.packed_lists() == (name not in ("one fewer", "too short for it", "negative weight of a path"))
     _, srt, spi, sps = full.export_build_state()
     ix = B.Index.ingest(docs, bp)
     ids, sc = ix.stage_seed_knn(K)
@@ -122,6 +123,7 @@ def test_sums_of_the_longest_lists():
     docs = B.DeviceVecs(d)
     bp = B.build_params(16, knn_k=K, nd_rounds=1, nd_sample=S, sp_len=1, n_entry=4, build_w=(1.0, 0.0, 1.0))
     full = B.Index.build(docs, bp)
+    assert full.packed_lists()
     _, _, spi, sps = full.export_build_state()
     ix = B.Index.ingest(docs, bp)
     ids, _ = ix.stage_seed_knn(K)

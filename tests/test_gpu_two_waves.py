@@ -33,6 +33,9 @@ def test_two_waves_and_four(debug_knobs, bf16, dim, degree, nq):
                     k = min(beam, 10)
                     r = ix.search_batch_keywords(q, k, beam, kw[a:b], pw[a:b]) if words else ix.search_batch(q, k, beam, pw[a:b])
                     got.append([t.clone() for t in r] + [ix.search_stats(b - a)[0][:, :2].clone()])
+                    # with keywords or deletions a compute unit holds twelve workgroups of two waves: 3,072 queries at once
+                    two = b - a == nq and (nq <= 3072 or not (words or deleted))
+                    assert ix.search_form()["threads"] == (128 if two else 256), (b - a, beam, words, deleted)
                 for whole, first, second in zip(*got):
                     assert torch.equal(whole, torch.cat([first, second])), (beam, glob, words, deleted)
     ix.close()
