@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2511_00855_amd import binding as B
-from paper_2511_00855_amd.synth import VecSet, make_workload
+from paper_2511_00855_amd.synth import VecSet, make_workload, subset_vecset
 
 pytestmark = pytest.mark.gpu
 
@@ -133,3 +133,36 @@ def test_sums_of_the_longest_lists():
     assert int(i2[1, U, 0]) == U + 10 and not bool((ids[U] == U + 10).any())   # it enters the per-path list alone
     assert torch.equal(spi, i2) and torch.equal(sps.view(torch.int32), s2.view(torch.int32))
     full.close(); ix.close()
+
+
+@pytest.mark.parametrize("bf16,dim,n0", [(False, 96, 1000), (True, 1032, 1003), (False, 128, 3)])
+def test_lists_of_the_documents_of_an_insertion(bf16, dim, n0):
+    """An insertion packs the lists of its new documents alone: records from the first new one on, slots by the term frequencies of all.
+    Its rounds are those that score every candidate, called one by one on the enlarged index."""
+    n, K, S, P = n0 + 700, 48, 24, 11
+    w = make_workload("tiny", seed=31, n=n, nq=2, dim=dim, bf16=bf16, sp=("poisson", 90), tx=("lognormal", 70))
+    d = w.docs
+    before = int(d.sp_indptr[n0] + d.tx_indptr[n0])
+    if before % 2 == 0:   # an entry less: the new documents' entries begin at an odd place
+        d.sp_idx, d.sp_val = d.sp_idx[1:], d.sp_val[1:]
+        d.sp_indptr[1:] -= 1
+    assert int(d.sp_indptr[n0] + d.tx_indptr[n0]) % 2 == 1
+    d.sp_val[d.sp_indptr[n0 + 5]] *= -1   # a list without a scale
+    bp = B.build_params(16, knn_k=K, nd_rounds=3, nd_sample=S, sp_len=P, n_entry=4)
+    old = B.Index.build(B.DeviceVecs(subset_vecset(d, np.arange(n0)), bf16=bf16), bp)
+    docs = B.DeviceVecs(d, bf16=bf16)
+    print(bf16, dim, n0, flush=True)
+    new, tr = old.insert(docs, trace=True)
+    assert new.packed_lists()
+    alone = B.Index.ingest(B.DeviceVecs(subset_vecset(d, np.arange(n0, n)), bf16=bf16), bp)
+    seeds, _ = alone.stage_seed_knn(K)
+    nodes = np.arange(n0, n, dtype=np.int32)
+    ids = torch.full((n, K), -1, dtype=torch.int32, device=docs.device)
+    i2 = torch.full((3, n, P), -1, dtype=torch.int32, device=docs.device)
+    s2 = torch.full((3, n, P), -np.inf, dtype=torch.float32, device=docs.device)
+    ids[n0:] = torch.where(seeds >= 0, seeds + n0, seeds)
+    for _ in range(3):
+        ids[n0:], sc, i2[:, n0:], s2[:, n0:] = new.stage_refine(K, S, P, ids, i2, s2, nodes)
+    for mine, theirs in ((tr["cand2_ids"], ids[n0:]), (tr["cand2_sc"], sc), (tr["cand2_sp_ids"], i2[:, n0:]), (tr["cand2_sp_sc"], s2[:, n0:])):
+        assert torch.equal(mine.view(torch.int32), theirs.contiguous().view(torch.int32))
+    old.close(); new.close(); alone.close()
