@@ -108,6 +108,9 @@ extern "C" int ap_debug_search_profile(unsigned long long out8[8]) {
 #endif
 
 #define AP_CUS 256              // compute units of the chip
+#define AP_LDS_BLOCKS 128       // what the LDS of one is handed out in ...
+#define AP_LDS_BLOCK 1280       // ... bytes each
+#define AP_SEARCH_STATIC 320    // bytes of k_search's static arrays beside its look-up tables, at most
 // NT threads per workgroup.  256 (four waves) is the usual size: seven workgroups share a CU while the pool is small
 // enough, and the register budget is the 72 VGPRs of seven waves per SIMD.  When the pool is so large that the LDS
 // holds four workgroups or fewer, 512 or 1024 threads keep the CU's SIMDs occupied with one query's candidates.
@@ -908,13 +911,29 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // Two waves a query, twice as many queries on the chip at a time: a query then takes some 1.2 times as long (its few candidates
     // an iteration keep four waves no busier than two, the steps between them wait for memory either way), so this pays where it saves
     // a second, half empty round.  2,500 queries (1,792 of four waves run at a time, 3,584 of two), pool 512: 100,000 f32 documents
-    // with keywords 13.7 -> 10.4 ms, plain 9.05 -> 8.24; 60,000 bf16 10.1 -> 8.7 and 7.1 -> 6.2; 10,000 narrow ones 6.2 -> 4.8 and 4.0 -> 3.0.
-    // Not where the batch fits one round of four waves (400 to 1,792 queries: 0.80 to 0.93 of the speed) nor without bounds or with
+    // with keywords 14.6 -> 10.9 ms, plain 9.32 -> 8.36; 60,000 bf16 10.6 -> 8.6 and 7.25 -> 6.32; 10,000 narrow ones 6.6 -> 4.5 and 4.3 -> 3.1.
+    // Not where the batch fits one round of four waves (400 to 1,500 queries: 0.67 to 0.98 of the speed) nor without bounds or with
     // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).
+    // Beyond one round of two waves four are taken, though they are not always the faster: from 3,900 to 7,000 queries two would run plain searches at
+    // 0.80 to 1.38 times the speed (f32 0.80 to 0.97, bf16 0.82 to 1.0, narrow rows 1.05 to 1.38) and those with keywords at 0.86 to 1.16 with a
+    // pool of 32 and 1.01 to 1.34 with pools of 128 and 512.
     const int32_t slots_of = ix->dtype == AP_BF16 && ix->docs.dim > 1024 ? 5 : AP_SEARCH_WAVES_PER_SIMD;   // waves a SIMD holds (ApSearchWaves)
     auto slots = [&](int32_t threads, size_t bytes) -> int64_t {
         const int32_t waves = threads == 128 && kw ? std::min(slots_of, AP_SEARCH_WAVES_KW2) : slots_of;
-        return AP_CUS * (int64_t)std::min<size_t>((size_t)waves * 256 / threads, (size_t)160 * 1024 / bytes);
+        // LDS is handed out in 128 blocks of 1,280 bytes a CU.  (By bytes alone 2,500 queries of 50,000 documents, pool 512, were taken to run
+        // at once with their visited sets in LDS: 10 workgroups of 15,592 bytes a CU, where 9 do.  8.90 ms before, 9.71 with them, 7.54 now.)
+        return AP_CUS * (int64_t)std::min<size_t>((size_t)waves * 256 / threads, AP_LDS_BLOCKS / ((bytes + AP_SEARCH_STATIC + AP_LDS_BLOCK - 1) / AP_LDS_BLOCK));
+    };
+    // Visited sets in LDS (small workgroups only).  Four waves: when the bitset fits beside the kernel's other arrays without
+    // taking a workgroup's place on the CU (seven of them run on one while the pool is small).  Measured on 100,000
+    // documents (12.5 KB a set): 4 to 5 % faster up to beam 512, 29 % slower at beam 2144 where it costs two of the
+    // seven workgroups, which is why the rule is about occupancy.  Two waves: as long as the whole batch runs at once.  Same results either way.
+    auto visited_fit = [&](int32_t threads) {
+        if (threads > 256 || g_ap_debug.search_visited_global != 0) return false;
+        const size_t without = lds_bytes(threads, g.cmax, 0), with = without + g.words * 4 + 8, lds = (size_t)160 * 1024;
+        if (with > lds) return false;
+        if (threads == 128) return slots(128, with) >= at_once;
+        return lds / with >= std::min<size_t>(7, lds / without);
     };
     if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96 && at_once * 10 > slots(256, lds_bytes(256, g.cmax, 0)) * 11 &&
         at_once <= slots(128, lds_bytes(128, g.cmax, 0)))
@@ -923,21 +942,8 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
     g.bound_floor = ws.bound.table && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? ws.bound.floor : nullptr;
     g.nxtw = nt <= 256 && g.cmax > nt ? g.cmax : 0;
-    size_t smem = lds_bytes(nt, g.cmax, g.icap);
-    // Visited sets in LDS (small workgroups only): when the bitset fits beside the kernel's other arrays without
-    // taking a workgroup's place on the CU (seven of them run on one while the pool is small).  Measured on 100,000
-    // documents (12.5 KB a set): 4 to 5 % faster up to beam 512, 29 % slower at beam 2144 where it costs two of the
-    // seven workgroups, which is why the rule is about occupancy.  Same results either way.
-    g.vis_lds = 0;
-    if (nt == 128 && g_ap_debug.search_visited_global == 0) {   // two waves: as long as the whole batch runs at once
-        const size_t with = smem + g.words * 4 + 8;
-        if (with <= (size_t)160 * 1024 && slots(128, with) >= at_once) { g.vis_lds = 1; smem = with; }
-    }
-    if (nt == 256 && g_ap_debug.search_visited_global == 0) {
-        const size_t with = smem + g.words * 4 + 8, lds = (size_t)160 * 1024;
-        const size_t now = std::min<size_t>(7, lds / smem), then = with <= lds ? std::min<size_t>(7, lds / with) : 0;
-        if (then >= now && then > 0) { g.vis_lds = 1; smem = with; }
-    }
+    g.vis_lds = visited_fit(nt) ? 1 : 0;
+    const size_t smem = lds_bytes(nt, g.cmax, g.icap) + (g.vis_lds ? g.words * 4 + 8 : 0);
     // the kernel's static arrays (counters, parents, required terms) take a few hundred bytes more
     AP_REQUIRE(smem + 512 <= 160 * 1024, "beam and search_width need %zu bytes of LDS (limit 160 KiB)", smem + 512);
     note_form(nt, g.icap > 0, g.vis_lds);

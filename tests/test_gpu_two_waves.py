@@ -39,3 +39,23 @@ def test_two_waves_and_four(debug_knobs, bf16, dim, degree, nq):
                 for whole, first, second in zip(*got):
                     assert torch.equal(whole, torch.cat([first, second])), (beam, glob, words, deleted)
     ix.close()
+
+
+def test_where_two_waves_keep_their_visited_sets(debug_knobs):
+    """LDS is handed out in blocks of 1,280 bytes.  2,400 queries do not run at once with 15,432 bytes each and the kernel's static arrays
+    (nine workgroups a compute unit, not ten): their visited sets stay in memory.  Ids, scores and counts are those of the batch's halves either way."""
+    w = make_workload("tiny", seed=5, n=12_000, nq=3500, dim=32, sp=("poisson", 20))
+    docs = B.DeviceVecs(w.docs)
+    ix = B.Index.build(docs, B.build_params(32, nd_rounds=1, n_entry=64))
+    debug_knobs("search_bounds", 2)
+    for nq, beam, threads, lds in ((2400, 1100, 128, False), (2300, 1100, 128, True), (3300, 700, 128, False), (3072, 700, 128, True)):
+        print(nq, beam, flush=True)
+        got = []
+        for a, b in ((0, nq), (0, nq // 2), (nq // 2, nq)):
+            r = ix.search_batch(B.DeviceVecs(subset_vecset(w.queries, np.arange(a, b))), 10, beam)
+            if b - a == nq:
+                assert ix.search_form() == dict(threads=threads, listed=False, visited_lds=lds), (nq, beam)
+            got.append([t.clone() for t in r] + [ix.search_stats(b - a)[0][:, :2].clone()])
+        for whole, first, second in zip(*got):
+            assert torch.equal(whole, torch.cat([first, second])), (nq, beam)
+    ix.close()

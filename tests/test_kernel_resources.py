@@ -39,3 +39,13 @@ def test_kernels_that_must_not_spill(kernel):
     assert found
     for k in found:   # a few registers that are written once outside the loops do not count
         assert k[".vgpr_spill_count"] <= 4 and k[".private_segment_fixed_size"] <= 16, (k[".name"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"])
+
+
+def test_static_arrays_of_the_search_are_what_its_launch_reckons_with():
+    """How many workgroups a compute unit holds is reckoned from the dynamic LDS, the look-up tables (384 or 1,536 slots of 8 bytes) and
+    at most 320 bytes of other static arrays."""
+    found = [k for k in _kernels() if "k_searchI" in k[".name"]]
+    assert found
+    for k in found:
+        tables = 1536 * 8 if k[".group_segment_fixed_size"] > 8192 else 384 * 8
+        assert 0 <= k[".group_segment_fixed_size"] - tables <= 320, k[".name"]
