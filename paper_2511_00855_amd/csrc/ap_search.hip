@@ -913,7 +913,9 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // a second, half empty round.  2,500 queries (1,792 of four waves run at a time, 3,584 of two), pool 512: 100,000 f32 documents
     // with keywords 14.6 -> 10.9 ms, plain 9.32 -> 8.36; 60,000 bf16 10.6 -> 8.6 and 7.25 -> 6.32; 10,000 narrow ones 6.6 -> 4.5 and 4.3 -> 3.1.
     // Not where the batch fits one round of four waves (400 to 1,500 queries: 0.67 to 0.98 of the speed) nor without bounds or with
-    // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).
+    // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).  Nor where the batch
+    // nearly fills two rounds of four waves and only those have their visited sets in LDS: plain, pools 128 to 512 of 100,000 f32 and 60,000 bf16
+    // documents, 1.0 at 3,300 queries (1.84 rounds), 0.97 to 1.01 at 3,500; with keywords 1.10 to 1.30 up to the 3,072 that run at once.
     // Beyond one round of two waves four are taken, though they are not always the faster: from 3,900 to 7,000 queries two would run plain searches at
     // 0.80 to 1.38 times the speed (f32 0.80 to 0.97, bf16 0.82 to 1.0, narrow rows 1.05 to 1.38) and those with keywords at 0.86 to 1.16 with a
     // pool of 32 and 1.01 to 1.34 with pools of 128 and 512.
@@ -935,9 +937,12 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
         if (threads == 128) return slots(128, with) >= at_once;
         return lds / with >= std::min<size_t>(7, lds / without);
     };
-    if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96 && at_once * 10 > slots(256, lds_bytes(256, g.cmax, 0)) * 11 &&
-        at_once <= slots(128, lds_bytes(128, g.cmax, 0)))
-        nt = 128;
+    if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96) {
+        const int64_t four = slots(256, lds_bytes(256, g.cmax, 0));
+        if (at_once * 10 > four * 11 && at_once <= slots(128, lds_bytes(128, g.cmax, 0)) &&
+            (kw || at_once * 10 <= four * 19 || visited_fit(128) || !visited_fit(256)))
+            nt = 128;
+    }
     // A floor below which neighbours wait: where a search ends by itself, in large pools.  In small ones (256 threads) what
     // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
     g.bound_floor = ws.bound.table && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? ws.bound.floor : nullptr;

@@ -43,12 +43,13 @@ def test_two_waves_and_four(debug_knobs, bf16, dim, degree, nq):
 
 def test_where_two_waves_keep_their_visited_sets(debug_knobs):
     """LDS is handed out in blocks of 1,280 bytes.  2,400 queries do not run at once with 15,432 bytes each and the kernel's static arrays
-    (nine workgroups a compute unit, not ten): their visited sets stay in memory.  Ids, scores and counts are those of the batch's halves either way."""
+    (nine workgroups a compute unit, not ten): their visited sets stay in memory.  And batches of nearly two rounds of four waves take four
+    where only those have the sets in LDS.  Ids, scores and counts are those of the batch's halves either way."""
     w = make_workload("tiny", seed=5, n=12_000, nq=3500, dim=32, sp=("poisson", 20))
     docs = B.DeviceVecs(w.docs)
     ix = B.Index.build(docs, B.build_params(32, nd_rounds=1, n_entry=64))
     debug_knobs("search_bounds", 2)
-    for nq, beam, threads, lds in ((2400, 1100, 128, False), (2300, 1100, 128, True), (3300, 700, 128, False), (3072, 700, 128, True)):
+    for nq, beam, threads, lds in ((2400, 1100, 128, False), (2300, 1100, 128, True), (3300, 700, 128, False), (3500, 700, 256, True), (3072, 700, 128, True)):
         print(nq, beam, flush=True)
         got = []
         for a, b in ((0, nq), (0, nq // 2), (nq // 2, nq)):
