@@ -355,6 +355,10 @@ int ap_build_timings(const ap_index *index, float out6[6]);
  *     the sweeps, the exact rows). */
 int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
 
+/* How many of the similarities of ap_build_counters' [0] were computed in full, all three parts of them (host uint64; synchronises `stream`).
+ * The others were left out because an upper bound keeps them from every list. */
+int ap_build_scored(const ap_index *index, uint64_t *out, void *stream);
+
 /* Which rows the products of the last seed stage on this index took (host int32): 1 = bf16, stored or rounded from
  * f32 (the candidates are then scored again in f32), 0 = f32. */
 int ap_build_seed_bf16(const ap_index *index, int32_t *out);

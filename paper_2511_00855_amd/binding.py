@@ -489,6 +489,13 @@ class Index:
             _check(lib().ap_build_counters(self._h, out, _stream()), "ap_build_counters")
         return dict(refine_similarities=int(out[0]), seed_flops=int(out[1]))
 
+    def refine_scored(self) -> int:
+        """How many similarities the refinement rounds on this index computed in full; bounds kept the others from every list."""
+        out = C.c_uint64(0)
+        with torch.cuda.device(self.device):
+            _check(lib().ap_build_scored(self._h, C.byref(out), _stream()), "ap_build_scored")
+        return int(out.value)
+
     def seed_products_bf16(self) -> bool:
         """Whether the last seed stage multiplied bf16 rows (stored, or rounded from f32 with the candidates scored again)."""
         out = C.c_int32(0)

@@ -491,6 +491,15 @@ extern "C" int ap_build_counters(const ap_index *ix, uint64_t out2[2], void *str
     return AP_OK;
 }
 
+extern "C" int ap_build_scored(const ap_index *ix, uint64_t *out, void *stream) {
+    AP_REQUIRE(ix && out, "NULL argument");
+    unsigned long long h = 0;
+    AP_CHECK_HIP(hipMemcpyAsync(&h, ix->counters + 1, sizeof(h), hipMemcpyDeviceToHost, (hipStream_t)stream));
+    AP_CHECK_HIP(hipStreamSynchronize((hipStream_t)stream));
+    *out = h;
+    return AP_OK;
+}
+
 extern "C" int ap_build_seed_bf16(const ap_index *ix, int32_t *out) {
     AP_REQUIRE(ix && out, "NULL argument");
     *out = ix->seed_bf16;

@@ -63,7 +63,7 @@ struct ap_index {
     int64_t tx_nnz, sp_nnz;
     float *tx_w = nullptr;     // owned: BM25 weight per lexical entry
     int32_t *df = nullptr;     // owned: document frequency per term
-    unsigned long long *counters = nullptr;   // owned: [0] hybrid similarities evaluated by refinement rounds on this index
+    unsigned long long *counters = nullptr;   // owned: [0] candidates met by refinement rounds on this index, [1] those scored in full
     mutable int seed_bf16 = 0;                     // 1: the last seed stage's products over the whole corpus took bf16 rows (stored or rounded)
     mutable int packed_lists = 0;                  // 1: the last refinement rounds had packed lists
     mutable unsigned long long seed_flops = 0;   // FLOPs (2 per multiply-add, padded tiles included) of the seed stage's dense products so far

@@ -53,6 +53,50 @@ def test_rounds_of_a_construction_equal_rounds_called_one_by_one(name):
         full.close(); ix.close()
 
 
+
+def _twice(d):   # every document, and once more with a slightly other dense row
+    half = d.n // 2
+    d.dense[half:] = d.dense[:half] + np.float32(0.01) * d.dense[half:]
+    for p in ("sp", "tx"):
+        ip, idx, val = getattr(d, p + "_indptr"), getattr(d, p + "_idx"), getattr(d, p + "_val")
+        end = ip[half]
+        setattr(d, p + "_indptr", np.concatenate([ip[:half + 1], ip[1:half + 1] + end]))
+        setattr(d, p + "_idx", np.concatenate([idx[:end]] * 2))
+        setattr(d, p + "_val", np.concatenate([val[:end]] * 2))
+
+
+# Scored in full of what the first round meets: 0.08 to 0.15.  Bins over the first four octaves alone: 0.99, 0.23, 0.33, 0.15 (these scores lie within
+# four octaves) and 1.0.
+@pytest.mark.parametrize("name,wv,twice,packed", [("near duplicates", (1.0, 1.0, 1.0), True, True), ("near duplicates, sparse parts", (0.2, 1.0, 0.2), True, True),
+                                                  ("negative sparse weight", (0.5, -0.3, 0.2), False, False), ("all weights negative", (-0.5, -0.3, -0.2), False, False),
+                                                  ("near duplicates, negative sparse weight", (0.5, -0.3, 0.2), True, False)])
+def test_first_scored_far_below_the_best_bound(name, wv, twice, packed):
+    """Where the K best lie more than four octaves below the best bound, or below zero, only about K candidates are scored first all the
+    same; the lists are those of rounds that score everything."""
+    w = make_workload("tiny", seed=5, n=3000, nq=2, dim=96, vocab=60_000, sp=("poisson", 100), tx=("lognormal", 60))
+    if twice:
+        _twice(w.docs)
+    docs = B.DeviceVecs(w.docs)
+    K, S, P = 48, 32, 11
+    bp = B.build_params(16, knn_k=K, nd_rounds=1, nd_sample=S, sp_len=P, n_entry=4, build_w=wv)
+    full = B.Index.build(docs, bp)
+    assert full.packed_lists() == packed
+    _, srt, spi, sps = full.export_build_state()
+    ix = B.Index.ingest(docs, bp)
+    ids, sc = ix.stage_seed_knn(K)
+    i2 = torch.full((3, docs.n, P), -1, dtype=torch.int32, device=docs.device)
+    s2 = torch.full((3, docs.n, P), -np.inf, dtype=torch.float32, device=docs.device)
+    ids, sc, i2, s2 = ix.stage_refine(K, S, P, ids, i2, s2)
+    g = ix.stage_prune(K, 16, ids, sc, want_pm=False)
+    assert torch.equal(spi, i2) and torch.equal(sps.view(torch.int32), s2.view(torch.int32))
+    assert torch.equal(srt, g["sorted_ids"])
+    met, scored = full.build_counters()["refine_similarities"], full.refine_scored()
+    print(name, met, scored, scored / met, flush=True)
+    assert ix.refine_scored() == ix.build_counters()["refine_similarities"]   # a round on its own scores all
+    assert scored < 0.2 * met
+    full.close(); ix.close()
+
+
 def test_dense_scores_beyond_the_range_keep_their_place():
     """Rows of +-3e19 in one column: products of two are +-inf in f32.  A list with room takes a -inf like any other score, in a
     round of a construction and in one on its own, as the oracle does."""
