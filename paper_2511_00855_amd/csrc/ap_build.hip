@@ -1245,7 +1245,9 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
     // the candidates need[d0 .. d1) in full, a wave each: dense rows, and the records where only bounds of the list parts are known
     // (where[] says where they lie)
     auto score = [&](int32_t d0, int32_t d1) {
-        constexpr int G = AP_RF_GD;
+        // One candidate at a time where a lane holds 32 columns of the node: two do not fit the registers beside them (60,000 documents of 2,048 bf16
+        // columns, spilling 6 registers 74.4 ms, one at a time 74.0).
+        constexpr int G = DT == AP_BF16 && NV >= 4 ? 1 : AP_RF_GD;
         for (int32_t e0 = d0 + wave; e0 < d1; e0 += G * NW) {
             uint4 raw[G][NV];
             uint2 xs[G][2], xt[G][1];

@@ -33,7 +33,7 @@ def _kernels():
         at = b.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 24)
 
 
-@pytest.mark.parametrize("kernel", ["k_gram_lists"])
+@pytest.mark.parametrize("kernel", ["k_gram_lists", "k_refineI"])
 def test_kernels_that_must_not_spill(kernel):
     found = [k for k in _kernels() if kernel in k[".name"]]
     assert found
