@@ -214,14 +214,21 @@ __global__ __launch_bounds__(256) void k_bf_topk(const float *__restrict__ score
 // a CU and 1,000 queries run at once.  A query with more than AP_BT_CAND candidates is left to
 // the exhaustive scorer.  1,000 queries of 100,000 documents (768 f32 columns), k = 10: 74.9 ms with the exhaustive scorer,
 // 0.96 ms with the table read twice by 1,024 threads that sort their best bounds (this kernel 0.249), 0.84 now (scalar registers of seven waves a SIMD: 0.88).
+// A call lasts as long as its query with the most candidates, some thousands where the bounds tell little (lexical part alone, negative
+// weights), and fewer waves a query take longer for those.  So a candidate costs one wait, for its record and its row, and not three (offsets,
+// lists, row).  4,200 documents, 1,000 queries, lexical part alone, k = 10, 100, 256: 0.82, 1.43, 2.11 ms with 1,024 threads and three waits, 1.19, 1.85,
+// 2.32 with 512 and three, 0.99, 1.58, 2.04 with 512 and one, 0.68, 1.15, 1.64 with 1,024 and one; 150,000 documents, weights 0.5, -0.3, -0.2, k = 100: 2.12, 2.50, 2.19, 1.84.
 #define AP_BT_CAND 4096
 // Queries up to which a workgroup has 1,024 threads, two of which fit a CU: with fewer queries a CU would have waves to spare.  With 512 threads
 // instead, k = 100: 1 query of 150,000 documents 301 -> 347 us, 16 of 12,000 158 -> 190, 400 of 12,000 201 -> 229 (k = 10: 150 -> 151).
-#define AP_BT_FEW 512
+// More queries where k is larger than 64, for the sake of those with many candidates (k = 100, 1,000 queries of 4,200, 20,000 and 100,000 documents:
+// 249, 346 and 979 us with 512 threads, 257, 348 and 962 with 1,024; 4,000 queries: 610, 1,123 and 3,510 us, 670, 1,163 and 3,530).
+#define AP_BT_FEW(k) ((k) > 64 ? 1024 : 512)
 #define AP_BT_KEPT 4
 #define AP_BT_BINS 512
 template <int DT, int NV, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF16 && NV >= 3 ? 5 : 8, 8))) void k_bound_topk(ApVecs Q, ApVecs D, int64_t q0, const float *__restrict__ w, int32_t w_stride,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF16 && NV >= 3 ? 5 : 8, 8))) void k_bound_topk(ApVecs Q, ApVecs D, const uint2 *__restrict__ rec,
+                                                     const uint4 *__restrict__ meta, int64_t q0, const float *__restrict__ w, int32_t w_stride,
                                                      const float *__restrict__ table, int64_t ld, int32_t k, int32_t *__restrict__ out_ids,
                                                      float *__restrict__ out_scores, int32_t *__restrict__ over /* [0] count, then queries */) {
     __shared__ uint64_t keys[AP_BT_CAND];   // candidates: their ids, then their keys
@@ -237,10 +244,29 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF1
     float qa[NV * ApDense<DT>::EPC];
     ap_load_aside<DT, NV, AP_F32>(Q.dense, q, D.dim, qa);
     const float wd = w[q * w_stride], ws = w[q * w_stride + 1], wf = w[q * w_stride + 2];
-    auto score = [&](int32_t v) -> float {   // a wave
-        float sd, ss, sf;
-        ap_hybrid_wave<DT, NV>(D, qa, a, v, sd, ss, sf);
-        return ap_fuse(wd, ws, wf, sd, ss, sf);
+    // the documents keys[0 .. n), a wave each: a wave's lanes fetch the descriptors of its next 64 at once
+    auto score = [&](int32_t n, auto &&put) {
+        constexpr int NW = NT / 64;
+        for (int32_t i0 = wave; i0 < n; i0 += NT) {
+            const int32_t own = (int32_t)(uint32_t)keys[i0 + NW * lane < n ? i0 + NW * lane : i0];
+            const uint4 m = meta[own];
+            for (int32_t i = i0, j = 0; i < n && j < 64; i += NW, j++) {
+                const int32_t v = __builtin_amdgcn_readlane(own, j);
+                const uint2 *r = rec + (uint32_t)__builtin_amdgcn_readlane((int)m.x, j);
+                const uint32_t len = (uint32_t)__builtin_amdgcn_readlane((int)m.y, j);
+                const int32_t spn = (int32_t)(len & 0xffffu), txn = (int32_t)(len >> 16);
+                uint2 xs[2], xt[1];
+                uint4 raw[NV];
+                int32_t si[2], ti[1];
+                float sv[2], tv[1], ss, sf;
+                ap_rec_load_raw<2, 1>(r, spn, txn, xs, xt);
+                ap_dense_load_raw<DT, NV>(D, v, raw);
+                ap_rec_decode<2, 1>(xs, xt, spn, txn, si, sv, ti, tv);
+                ap_rec_reduce_lists<2, 1>(r, a, spn, txn, si, sv, ti, tv, ss, sf);
+                const float sd = ap_dense_dot_raw<DT, NV>(D, qa, raw);
+                if (lane == 0) put(i, v, ap_fuse(wd, ws, wf, sd, ss, sf));
+            }
+        }
     };
     const int64_t n4 = (D.n + 3) / 4;
     // bounds as codes that ascend with them, one that is no number above all; 0: none
@@ -311,10 +337,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF1
         if (bin_of(best[i]) == (int32_t)line) { const int32_t at = atomicAdd(&s_n, 1); if (at < k) keys[at] = (uint64_t)(uint32_t)id[i]; }
     __syncthreads();
     const int32_t first = min(ap_uniform_i32(s_n), k);
-    for (int32_t i = wave; i < first; i += NT / 64) {
-        const float s = score((int32_t)ap_uniform_u32((uint32_t)keys[i]));
-        if (lane == 0) atomicMin(&s_T, ap_f2ord(s));
-    }
+    score(first, [&](int32_t, int32_t, float s) { atomicMin(&s_T, ap_f2ord(s)); });
     __syncthreads();
     const float T = first == k ? ap_ord2f(s_T) : -INFINITY;
     const bool more = !(ap_ord2f(best[AP_BT_KEPT - 1]) < T) && best[AP_BT_KEPT - 1] != 0u;
@@ -342,11 +365,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DT == AP_BF1
         if (threadIdx.x == 0) over[1 + atomicAdd(over, 1)] = (int32_t)q;
         return;
     }
-    for (int32_t i = wave; i < c; i += NT / 64) {
-        const int32_t v = (int32_t)ap_uniform_u32((uint32_t)keys[i]);
-        const float s = score(v);
-        if (lane == 0) keys[i] = ap_make_key(s, v, 1u);
-    }
+    score(c, [&](int32_t i, int32_t v, float s) { keys[i] = ap_make_key(s, v, 1u); });
     int32_t n2 = 64;
     while (n2 < c) n2 <<= 1;
     for (int32_t i = c + (int32_t)threadIdx.x; i < n2; i += NT) keys[i] = 0ull;
@@ -416,11 +435,11 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
         const int32_t nqb = std::min(b.slab, q->nq - q0);
         rc = ap_bound_fill(ix, b, Q, w, ws, q0, nqb, nullptr, 0, st);
         if (rc != AP_OK) break;
-        if (nqb <= AP_BT_FEW)
-            AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV, 1024>), dim3((unsigned)nqb), dim3(1024), 0, st, Q, ix->docs,
+        if (nqb <= AP_BT_FEW(k))
+            AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV, 1024>), dim3((unsigned)nqb), dim3(1024), 0, st, Q, ix->docs, ix->rec, ix->meta,
                                                                           (int64_t)q0, w, ws, b.table, b.ld, k, out_ids, out_scores, over));
         else
-            AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV, 512>), dim3((unsigned)nqb), dim3(512), 0, st, Q, ix->docs,
+            AP_DISPATCH_DENSE(ix->dtype, ix->docs.dim, hipLaunchKernelGGL((k_bound_topk<DT, NV, 512>), dim3((unsigned)nqb), dim3(512), 0, st, Q, ix->docs, ix->rec, ix->meta,
                                                                           (int64_t)q0, w, ws, b.table, b.ld, k, out_ids, out_scores, over));
         if (hipGetLastError() != hipSuccess) { ap_set_error("ap_bruteforce_topk failed to launch"); rc = AP_EHIP; }
     }
