@@ -969,7 +969,7 @@ struct ApRefineHints {
 //    dense neighbours, so a document outside the node's list has a dense part of at most tau (plus the rounding of two
 //    differently ordered sums, eps |u||w|) -- 0.1 where the norms alone would allow 1.
 //  - what cannot beat the K best of this round.  A histogram of the candidates' bounds and the list's scores gives a line that
-//    5/4 K of them reach; those are scored first, and a histogram of the scores gives T, which K of them reach and so the new
+//    K + AP_RF_MORE(K) of them (7/6 K) reach; those are scored first, and a histogram of the scores gives T, which K of them reach and so the new
 //    list's last entry does.  After that only candidates are scored whose bounds reach T, or the last entry of a per-path list (in the first
 //    round, where those are empty: the P-th best of what was scored first).
 // Phases: packed records of all candidates (16 lanes each, the next ones on their way; without packed lists the records themselves,
@@ -1353,7 +1353,7 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
             for (int o = 32; o > 0; o >>= 1) lo = fminf(lo, __shfl_xor(lo, o, 64));
             if (lane == 0) s_last[0] = lo;
         }
-        // What is scored first: everything from a line on that at least K scores and bounds reach, and a quarter more, since a bound
+        // What is scored first: everything from a line on that at least K scores and bounds reach, and AP_RF_MORE(K) more, since a bound
         // may lie far above its score (from T on, where the list is full).
         uint32_t mine[3] = {0u, 0u, 0u}, lo = 0xffffffffu, hi = 0u;
         static_assert(AP_MAXC <= 3 * 512, "candidates of a thread");

@@ -422,11 +422,15 @@ extern "C" int ap_bruteforce_topk(const ap_index *ix, const ap_queries *q, const
     const ApVecs Q = query_view(q, ix->docs.dim);
     const float *w = per_query_w ? per_query_w : ix->w_dev;
     const int32_t ws = per_query_w ? 3 : 0;
-    // Out of the table of bounds where that leaves most documents unscored: k well below the 2,048 documents the
-    // threshold comes from, and a corpus well above them (below, the exhaustive scorer has little to do).
+    // Out of the table of bounds where that leaves most documents unscored: k well below the AP_BT_KEPT * NT documents (2,048 or 4,096) that
+    // the threshold comes from, and a corpus as large at least (below, the exhaustive scorer has little to do).  The histogram of the kept
+    // bounds begins at the worst of the threads' best ones, so it holds as many as there are threads at least: with 4,096 documents every
+    // one of 1,024 threads has four.
+    constexpr int32_t most_k = 256, least_n = 4096;
+    static_assert(most_k <= 512 && least_n / 4 >= 1024, "k of the kept bounds are in the histogram");
     ApBound b;
     const size_t held = ap_bound_held(ix, st);
-    if (k <= 256 && ix->docs.n >= 4096) AP_TRY(ap_bound_reserve(ix, q->nq, 256, AP_BOUND_WS_BYTES, 1, st, &b));
+    if (k <= most_k && ix->docs.n >= least_n) AP_TRY(ap_bound_reserve(ix, q->nq, 256, AP_BOUND_WS_BYTES, 1, st, &b));
     if (!b.table) return bf_exhaustive(ix, Q, w, ws, nullptr, q->nq, k, out_ids, out_scores, st);
     int32_t *over = nullptr;
     AP_TRY(ap_dev_alloc(&over, (size_t)q->nq + 1));

@@ -80,7 +80,9 @@ __device__ __forceinline__ int32_t ap_rank_in(const uint64_t *keys, int32_t n, u
 #define AP_RANK_LANES 16        // lanes that rank one entering key of a large pool (16, 32 or 64)
 #endif
 #define AP_RANK_SORT 128        // entering keys of a large pool beyond which they are sorted instead of ranked one against the other
-#define AP_SEARCH_WAVES_KW2 6   // two waves a query with keywords: without spills at six waves a SIMD (2,500 queries 11.05 -> 10.62 ms)
+// Two waves a query with keywords: at six waves a SIMD they spill less than at seven (768 f32 columns 6 registers instead of 13, 1,024 f32 17 and 29,
+// 1,024 bf16 5 and 11); 2,500 queries of 768 f32 columns 11.05 -> 10.62 ms.
+#define AP_SEARCH_WAVES_KW2 6
 #define AP_SEARCH_LISTED 256    // listed neighbours that are scored at a time
 #ifndef AP_SEARCH_WAVES_512
 #define AP_SEARCH_WAVES_512 6
