@@ -915,9 +915,14 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     // a second, half empty round.  2,500 queries (1,792 of four waves run at a time, 3,584 of two), pool 512: 100,000 f32 documents
     // with keywords 14.6 -> 10.9 ms, plain 9.32 -> 8.36; 60,000 bf16 10.6 -> 8.6 and 7.25 -> 6.32; 10,000 narrow ones 6.6 -> 4.5 and 4.3 -> 3.1.
     // Not where the batch fits one round of four waves (400 to 1,500 queries: 0.67 to 0.98 of the speed) nor without bounds or with
-    // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).  Nor where the batch
-    // nearly fills two rounds of four waves and only those have their visited sets in LDS: plain, pools 128 to 512 of 100,000 f32 and 60,000 bf16
-    // documents, 1.0 at 3,300 queries (1.84 rounds), 0.97 to 1.01 at 3,500; with keywords 1.10 to 1.30 up to the 3,072 that run at once.
+    // more candidates an iteration, where two waves have more to score than they hide (0.6 to 0.9; 128 candidates: 0.7).  With keywords 1.05 to 1.5
+    // up to the 3,072 that run at once.  A plain search has less to hide behind, and that shows in three places (speeds by two waves, pools 48 to 1,400):
+    //  - wide bf16 rows, of which five waves a SIMD run: 0.77 to 1.05 for 1,300 to 2,560 queries of 1,536 and 2,048 columns (1,280 and 2,560 run at a time);
+    //    with keywords 0.85 to 1.15 up to 1,800, 1.03 to 1.22 from 2,100 on;
+    //  - bf16 rows of 513 to 1,024 columns where only four waves have their visited sets in LDS: 0.90 to 1.03 (where both do or neither does 0.98 to 1.17);
+    //  - other rows where only four waves do, towards two full rounds: rows of 768 f32 columns 1.02 to 1.14 up to 2,500 queries, 0.99 to 1.02 at 2,750 (1.53
+    //    rounds), 0.96 to 1.0 at 3,000; 1,024 columns 1.03 to 1.05 at 2,750 and 1.0 to 1.02 at 3,000; shorter rows (128 and 384 f32, 512 bf16) 0.97 to 1.13 from
+    //    2,250 to 3,300 queries (1.84 rounds), 0.96 to 1.04 at 3,550.
     // Beyond one round of two waves four are taken, though they are not always the faster: from 3,900 to 7,000 queries two would run plain searches at
     // 0.80 to 1.38 times the speed (f32 0.80 to 0.97, bf16 0.82 to 1.0, narrow rows 1.05 to 1.38) and those with keywords at 0.86 to 1.16 with a
     // pool of 32 and 1.01 to 1.34 with pools of 128 and 512.
@@ -941,9 +946,11 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     };
     if (nt == 256 && !big_tables && ws.bound.table && g.cmax <= 96) {
         const int64_t four = slots(256, lds_bytes(256, g.cmax, 0));
-        if (at_once * 10 > four * 11 && at_once <= slots(128, lds_bytes(128, g.cmax, 0)) &&
-            (kw || at_once * 10 <= four * 19 || visited_fit(128) || !visited_fit(256)))
-            nt = 128;
+        const bool bf16 = ix->dtype == AP_BF16;
+        int32_t least = 11, most = 20;   // tenths of a round of four waves
+        if (bf16 && ix->docs.dim > 1024) { least = 15; most = kw ? 20 : 0; }
+        else if (!kw && !visited_fit(128) && visited_fit(256)) most = bf16 && ix->docs.dim > 512 ? 0 : !bf16 && ix->docs.dim > 512 ? 16 : 19;
+        if (at_once * 10 > four * least && at_once * 10 <= four * most && at_once <= slots(128, lds_bytes(128, g.cmax, 0))) nt = 128;
     }
     // A floor below which neighbours wait: where a search ends by itself, in large pools.  In small ones (256 threads) what
     // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.

@@ -35,22 +35,30 @@ def test_two_waves_and_four(debug_knobs, bf16, dim, degree, nq):
                     got.append([t.clone() for t in r] + [ix.search_stats(b - a)[0][:, :2].clone()])
                     # with keywords or deletions a compute unit holds twelve workgroups of two waves: 3,072 queries at once
                     two = b - a == nq and (nq <= 3072 or not (words or deleted))
+                    if bf16 and dim > 1024:   # five waves a SIMD: 1,280 queries at once by four waves, and two pay only with keywords or deletions
+                        two = two and (words or deleted)
                     assert ix.search_form()["threads"] == (128 if two else 256), (b - a, beam, words, deleted)
                 for whole, first, second in zip(*got):
                     assert torch.equal(whole, torch.cat([first, second])), (beam, glob, words, deleted)
     ix.close()
 
 
-def test_where_two_waves_keep_their_visited_sets(debug_knobs):
+@pytest.mark.parametrize("bf16,dim,cases", [
+    (False, 32, ((2400, 1100, 128, False), (2300, 1100, 128, True), (3300, 700, 128, False), (3500, 700, 256, True), (3072, 700, 128, True))),
+    (False, 516, ((2400, 1100, 128, False), (2900, 1000, 256, True), (3000, 700, 128, True))),
+    (True, 520, ((2400, 1100, 256, True), (2300, 1100, 128, True))),
+    (True, 1032, ((1400, 300, 256, True), (2300, 300, 256, True)))])
+def test_where_two_waves_keep_their_visited_sets(debug_knobs, bf16, dim, cases):
     """LDS is handed out in blocks of 1,280 bytes.  2,400 queries do not run at once with 15,432 bytes each and the kernel's static arrays
-    (nine workgroups a compute unit, not ten): their visited sets stay in memory.  And batches of nearly two rounds of four waves take four
-    where only those have the sets in LDS.  Ids, scores and counts are those of the batch's halves either way."""
-    w = make_workload("tiny", seed=5, n=12_000, nq=3500, dim=32, sp=("poisson", 20))
-    docs = B.DeviceVecs(w.docs)
+    (nine workgroups a compute unit, not ten): their visited sets stay in memory.  Batches of nearly two rounds of four waves take four
+    where only those have the sets in LDS, from 1.6 rounds on where rows are long, and bf16 rows of more than 512 columns always then; wide
+    bf16 rows take four whatever fits.  Ids, scores and counts are those of the batch's halves either way."""
+    w = make_workload("tiny", seed=5, n=12_000, nq=max(c[0] for c in cases), dim=dim, bf16=bf16, sp=("poisson", 20))
+    docs = B.DeviceVecs(w.docs, bf16=bf16)
     ix = B.Index.build(docs, B.build_params(32, nd_rounds=1, n_entry=64))
     debug_knobs("search_bounds", 2)
-    for nq, beam, threads, lds in ((2400, 1100, 128, False), (2300, 1100, 128, True), (3300, 700, 128, False), (3500, 700, 256, True), (3072, 700, 128, True)):
-        print(nq, beam, flush=True)
+    for nq, beam, threads, lds in cases:
+        print(bf16, dim, nq, beam, flush=True)
         got = []
         for a, b in ((0, nq), (0, nq // 2), (nq // 2, nq)):
             r = ix.search_batch(B.DeviceVecs(subset_vecset(w.queries, np.arange(a, b))), 10, beam)
