@@ -1090,7 +1090,6 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
     }
     __syncthreads();
     const int32_t cnt = ap_uniform_i32(s_cnt);
-    if (threadIdx.x == 0 && n_sims) atomicAdd(n_sims, (unsigned long long)cnt);   // measurement: similarities of this node and round
     // the per-path lists so far, in keys (entries scored again in a round that scores everything are left out: there the
     // caller's scores need not be this kernel's)
     if (wave < 3) {
@@ -1381,13 +1380,12 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         lo = ap_uniform_u32(s_lo); hi = ap_uniform_u32(s_hi);
         const uint32_t least = lo;
         if (hi > lo && hi - lo > (4u << 23)) lo = hi - (4u << 23);   // four octaves (one bound may lie far above all scores): what lies below is counted in the first bin
-        int sh = 0;
-        auto bins = [&]() { sh = 0; while (lo < hi && ((hi - lo) >> sh) >= AP_RF_BINS) sh++; };
-        bins();
-        auto count = [&](uint32_t o) { atomicAdd(&hist[(min(max(o, lo), hi) - lo) >> sh], 1u); };
+        auto width = [](uint32_t lo, uint32_t hi) { int sh = 0; while (lo < hi && ((hi - lo) >> sh) >= AP_RF_BINS) sh++; return sh; };
+        const int sh = width(lo, hi);
+        auto count = [&](uint32_t o, uint32_t lo, uint32_t hi, int sh) { atomicAdd(&hist[(min(max(o, lo), hi) - lo) >> sh], 1u); };
         // wave 0: the lower edge of the bin from which on at least `many` are counted (of the first bin: 0), 1 where all are fewer, but
         // `enough`; 0xffffffff: fewer than that
-        auto edge = [&](uint32_t many, uint32_t enough) {
+        auto edge = [&](uint32_t many, uint32_t enough, uint32_t lo, int sh) {
             static_assert(AP_RF_BINS == 512, "eight bins a lane");
             const uint4 h = reinterpret_cast<const uint4 *>(hist)[2 * (63 - lane) + 1], l = reinterpret_cast<const uint4 *>(hist)[2 * (63 - lane)];   // from the top: lane 0 has the last eight
             const uint32_t bin[8] = {h.w, h.z, h.y, h.x, l.w, l.z, l.y, l.x};
@@ -1408,31 +1406,31 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
                 s_line = b ? lo + (b << sh) : 0u;
             }
         };
-        uint32_t line;
-        bool below = false;   // uniform
-        for (;;) {
+        auto find_line = [&](uint32_t lo, uint32_t hi, int sh) {
 #pragma unroll
             for (int k = 0; k < 3; k++)
-                if (mine[k]) count(mine[k]);
-            for (int32_t t = threadIdx.x; t < n_old; t += 512) count((uint32_t)(keys[t] >> 32));
+                if (mine[k]) count(mine[k], lo, hi, sh);
+            for (int32_t t = threadIdx.x; t < n_old; t += 512) count((uint32_t)(keys[t] >> 32), lo, hi, sh);
             __syncthreads();
-            if (wave == 0) edge((uint32_t)(K + AP_RF_MORE(K)), (uint32_t)K);
+            if (wave == 0) edge((uint32_t)(K + AP_RF_MORE(K)), (uint32_t)K, lo, sh);
             __syncthreads();
-            line = ap_uniform_u32(s_line);
             if (threadIdx.x < AP_RF_BINS) hist[threadIdx.x] = 0;
-            // Where the line lies below the four octaves (a near duplicate far above all others, or scores that a negative weight takes
-            // below zero) the bins are laid over what is left, then over the one of them that it lies in.  Else all would be scored first:
-            // 30,000 documents of 768 f32 columns, every one there twice, are built in 66.0 ms then, in 55.5 so; a sparse weight of -0.3: 58.5 and 48.2.
-            if (!below) {
-                if (line != 0u || lo == least) break;
-                below = true; hi = lo; lo = least;
-            } else {
-                line = max(line, lo);
-                if (sh <= 14) break;
-                lo = line; hi = min(hi, lo + ((1u << sh) - 1u));
+            return ap_uniform_u32(s_line);
+        };
+        uint32_t line = find_line(lo, hi, sh);
+        // Where the line lies below the four octaves (a near duplicate far above all others, or scores that a negative weight takes
+        // below zero) the bins are laid over what is left, then over the one of them that it lies in.  Else all would be scored first:
+        // 30,000 documents of 768 f32 columns, every one there twice, are built in 66.0 ms then, in 55.5 so; a sparse weight of -0.3: 58.5 and 48.2.
+        const bool below = line == 0u && lo > least;   // uniform
+        if (below) {
+            uint32_t from = least, to = lo;
+            for (;;) {
+                const int w = width(from, to);
+                __syncthreads();
+                line = max(find_line(from, to, w), from);
+                if (w <= 14) break;
+                from = line; to = min(to, from + ((1u << w) - 1u));
             }
-            bins();
-            __syncthreads();
         }
         if (line != 0xffffffffu) {
 #pragma unroll
@@ -1464,10 +1462,10 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
             const int32_t nk = ap_uniform_i32(s_nk);
             for (int32_t t = threadIdx.x; t < nk; t += 512) {
                 const uint32_t o = (uint32_t)(keys[t] >> 32);
-                if (o >= lo) count(o);
+                if (o >= lo) count(o, lo, hi, sh);
             }
             __syncthreads();
-            if (wave == 0) edge((uint32_t)K, 0xffffffffu);
+            if (wave == 0) edge((uint32_t)K, 0xffffffffu, lo, sh);
             __syncthreads();
             const uint32_t at = ap_uniform_u32(s_line);
             if (at != 0xffffffffu) T = fmaxf(T, ap_ord2f(at ? at : lo));
@@ -1507,7 +1505,7 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
     // Three waves make the per-path lists: the best P by each single similarity among what was scored and the previous list
     // (with hints, what was not ranks after a full list's last entry, or after P of what was scored first).
     const int32_t nk = ap_uniform_i32(s_nk), n_whole = ap_uniform_i32(s_need);
-    if (threadIdx.x == 0 && n_sims) atomicAdd(n_sims + 1, (unsigned long long)n_whole);   // measurement: of those, scored in full
+    if (threadIdx.x >= 510 && n_sims) atomicAdd(n_sims + (threadIdx.x - 510), (unsigned long long)(threadIdx.x == 510 ? cnt : n_whole));   // measurement: similarities of this node and round, those computed in full
     if (wave < 3) {
         const int p = wave;
         const int32_t nold = (int32_t)__popcll(__ballot(lane < 32 && oldk[p][lane & 31] != 0ull));
