@@ -206,6 +206,7 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------ the table
+__device__ __forceinline__ float ap_bound_value(float entry) { return __uint_as_float(__float_as_uint(entry) & ~AP_BOUND_COUNT); }
 // Entries carry a count in their low bits (keyword searches: how many of the query's required terms the document holds);
 // what clearing them takes off a value is added first.
 __device__ __forceinline__ float ap_bound_round(float v) {
@@ -456,42 +457,101 @@ __global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__res
     }
 }
 
-// One block per query: the bound that `share` of the documents reach, from a sample of at most 4,096 (64 runs spread over the
-// corpus, 256 bytes each).
+// One block per query: the bounds that shares of the documents reach, from a sample of at most 4,096 (64 runs spread over the
+// corpus, 256 bytes each), and a word of two bitmaps per 32 documents: which of them a search has met (none yet), and, in the upper half, which have a
+// bound that reaches the first of those floors.  The floors are the lower edges of the bins that the sample's values at the given ranks lie in
+// (22 bits of their codes).  Bound by the reading of the table: 4,000 queries of 100,000 documents take 0.56 ms, of which a sort of the
+// sample for one floor alone took 0.47; the search reads a bit where it read an entry, a line of memory each.
 #define AP_FLOOR_SAMPLE 4096
-__global__ __launch_bounds__(256) void k_bound_floor(const float *__restrict__ table, int64_t ld, int64_t n, float share, float *__restrict__ out) {
-    __shared__ uint64_t keys[AP_FLOOR_SAMPLE];
+__global__ __launch_bounds__(1024) void k_bound_floor(const float *__restrict__ table, int64_t ld, int64_t n, float4 share, float4 *__restrict__ out,
+                                                      uint64_t *__restrict__ marks, int64_t words) {
+    __shared__ uint32_t hist[3][2048];
+    __shared__ uint32_t s_bin[3], s_left[3];
+    const int lane = threadIdx.x & 63, wave = ap_wave_id();
     const float *row = table + (int64_t)blockIdx.x * ld;
     const int32_t m = n < AP_FLOOR_SAMPLE ? (int32_t)n : AP_FLOOR_SAMPLE;
-    for (int32_t i = threadIdx.x; i < AP_FLOOR_SAMPLE; i += 256) {
+    const float shares[3] = {share.x, share.y, share.z};
+    uint32_t code[AP_FLOOR_SAMPLE / 1024];
+#pragma unroll
+    for (int j = 0; j < AP_FLOOR_SAMPLE / 1024; j++) {
+        const int32_t i = (int32_t)threadIdx.x + 1024 * j;
         const int64_t d = n <= AP_FLOOR_SAMPLE ? i : (i >> 6) * ((n - 64) / 63) + (i & 63);
         float x = i < m ? row[d] : -INFINITY;
         if (!(x < INFINITY)) x = -INFINITY;   // says nothing about the scores
-        keys[i] = i < m ? ((uint64_t)ap_f2ord(x) << 32) | (uint32_t)(i + 1) : 0ull;
+        code[j] = i < m ? ap_f2ord(x) : 0xffffffffu;
     }
-    int32_t n2 = 64;
-    while (n2 < m) n2 <<= 1;
-    ap_bitonic_desc(keys, n2);
-    if (threadIdx.x == 0) {
-        const int32_t at = (int32_t)(share * (float)m);
-        out[blockIdx.x] = at < m ? ap_key_score(keys[at]) : -INFINITY;
+    // wave w < 3: the bin of the entry that `rank` others of hist[w] lie above, and how many of the bin's own do
+    auto find = [&](const uint32_t *h, uint32_t rank) {
+        uint32_t sum = 0;
+        for (int j = 0; j < 32; j++) sum += h[2016 - 32 * lane + ((j + lane) & 31)];   // from the top: lane 0 has the last 32 bins
+        uint32_t upto = sum;
+        for (int o = 1; o < 64; o <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)upto, o, 64); if (lane >= o) upto += up; }
+        if (upto > rank && upto - sum <= rank) {   // at most one lane
+            uint32_t above = upto - sum;
+            int b = 2047 - 32 * lane;
+            while (above + h[b] <= rank) above += h[b--];
+            s_bin[wave] = (uint32_t)b; s_left[wave] = rank - above;
+        }
+    };
+    for (int i = threadIdx.x; i < 3 * 2048; i += 1024) (&hist[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < AP_FLOOR_SAMPLE / 1024; j++)
+        if (code[j] != 0xffffffffu) atomicAdd(&hist[0][code[j] >> 21], 1u);
+    __syncthreads();
+    const int32_t rank = (int32_t)(shares[wave < 3 ? wave : 0] * (float)m);
+    const bool asked = wave < 3 && rank < m;   // uniform
+    if (asked) find(hist[0], (uint32_t)rank);
+    __syncthreads();
+    uint32_t top[3];
+#pragma unroll
+    for (int p = 0; p < 3; p++) top[p] = s_bin[p];
+    for (int i = threadIdx.x; i < 3 * 2048; i += 1024) (&hist[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < AP_FLOOR_SAMPLE / 1024; j++)
+#pragma unroll
+        for (int p = 0; p < 3; p++)
+            if (code[j] != 0xffffffffu && (code[j] >> 21) == top[p]) atomicAdd(&hist[p][(code[j] >> 10) & 2047u], 1u);
+    __syncthreads();
+    if (asked) find(hist[wave], s_left[wave]);
+    __syncthreads();
+    float floors[3];
+#pragma unroll
+    for (int p = 0; p < 3; p++) floors[p] = (int32_t)(shares[p] * (float)m) < m ? fmaxf(ap_ord2f((top[p] << 21) | (s_bin[p] << 10)), -INFINITY) : -INFINITY;   // below the code of -inf lie those of NaNs
+    if (threadIdx.x == 0) out[blockIdx.x] = make_float4(floors[0], floors[1], floors[2], 0.f);
+    uint64_t *mark = marks + (int64_t)blockIdx.x * words;
+    for (int64_t d0 = (int64_t)wave * 512; d0 < n; d0 += 16 * 512) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) x[j] = d0 + 64 * j + lane < n ? row[d0 + 64 * j + lane] : -INFINITY;
+        uint32_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const uint64_t b = __ballot(!(ap_bound_value(x[j]) < floors[0]));   // a NaN reaches any floor
+            if ((lane >> 1) == j) mine = (uint32_t)(b >> (32 * (lane & 1)));
+        }
+        if (lane < 16 && (d0 >> 5) + lane < words) mark[(d0 >> 5) + lane] = (uint64_t)mine << 32;
     }
 }
 
 // The floors of the slab's queries for a pool of `beam` entries: as if the documents a search meets were drawn at random,
-// with a quarter of the pool on top; they are better than that, so the pool's last score usually ends above it.
+// with a quarter of the pool on top; they are better than that, so the pool's last score usually ends above it.  The lower ones, which four and sixteen
+// times as many documents reach, serve the first iterations.
 int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st) {
     const double n = (double)ix->docs.n, met = n * (1.0 - exp(-(double)beam * ix->params.degree / n));
-    const double share = g_ap_debug.search_floor == 2 ? 0.002 : std::min(1.0, 1.25 * beam / met);
-    hipLaunchKernelGGL(k_bound_floor, dim3((unsigned)nq), dim3(256), 0, st, b.table, b.ld, ix->docs.n, (float)share, b.floor);
+    const float share = (float)(g_ap_debug.search_floor == 2 ? 0.002 : std::min(1.0, 1.25 * beam / met));
+    hipLaunchKernelGGL(k_bound_floor, dim3((unsigned)nq), dim3(1024), 0, st, b.table, b.ld, ix->docs.n, make_float4(share, 4.f * share, 16.f * share, 0.f),
+                       reinterpret_cast<float4 *>(b.floor), b.marks, (ix->docs.n + 31) / 32);
     AP_CHECK_HIP(hipGetLastError());
     return AP_OK;
 }
 
-// Bytes of the workspace a slab of nq queries takes, with one table of n entries a query or two.
+// Bytes of the workspace a slab of nq queries takes, with one table of n entries a query or two (AP_BOUND_MARKS: one, and the words of
+// the two bitmaps beside it).
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq, int tables) {
-    const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh);
-    return rows * k * 2 + rows * 32 + rows * 20 + (size_t)tables * (size_t)nq * ap_up((size_t)ix->docs.n, 64) * 4;
+    const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh), n = (size_t)ix->docs.n;
+    return rows * k * 2 + rows * 32 + rows * 20 + (size_t)nq * (tables == AP_BOUND_MARKS ? ap_up(n, 64) * 4 + (n + 31) / 32 * 8 : (size_t)tables * ap_up(n, 64) * 4);
 }
 
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBound *b) {
@@ -502,7 +562,9 @@ void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBo
     b->floor = reinterpret_cast<float *>(m); m += rows * 20;
     b->table = reinterpret_cast<float *>(m);
     b->ld = (int64_t)ap_up((size_t)ix->docs.n, 64);
-    b->second = tables > 1 ? b->table + (size_t)nq * (size_t)b->ld : nullptr;
+    float *behind = b->table + (size_t)nq * (size_t)b->ld;
+    b->second = tables == 2 ? behind : nullptr;
+    b->marks = tables == AP_BOUND_MARKS ? reinterpret_cast<uint64_t *>(behind) : nullptr;
     b->slab = (int32_t)nq;
 }
 

@@ -197,7 +197,8 @@ struct ApBound {
     int64_t ld = 0;            // documents, padded
     uint16_t *qm = nullptr;    // the slab's queries as bf16 rows
     float *qc = nullptr;       // per query 8 floats: what the slack of its row is made of
-    float *floor = nullptr;    // per query: an estimate of the last score of a pool (ap_bound_floors)
+    float *floor = nullptr;    // per query four floats: an estimate of the last score of a pool, two lower ones (ap_bound_floors)
+    uint64_t *marks = nullptr; // per query a word for 32 documents: which of them the search has met, and (upper half) which have a bound that reaches the floor
     float *second = nullptr;   // a second table of the same shape, where the call asked for one
     int32_t slab = 0;          // queries the workspace holds
     // The index's workspaces are held until everything that uses this one is enqueued: finish() (or the end of the object)
@@ -239,6 +240,7 @@ struct ApSearchWs {
 // the workspace of one stream never grows beyond this (40,000 queries of 100,000 documents, 480 of 8.8 million)
 #define AP_BOUND_WS_BYTES ((size_t)16 << 30)
 #define AP_BOUND_WHOLE INT64_MAX   // ap_bound_reserve: the whole batch in one slab, or none
+#define AP_BOUND_MARKS 3           // `tables` of a workspace with one table and the marks of its queries
 #define AP_BOUND_KEEP_BYTES ((size_t)2 << 30)   // an exact top-k that had to take more gives it back
 #define AP_BOUND_COUNT 31u     // low bits of a table entry: keyword searches count the required tail terms a document holds there
 int ap_bound_ingest(ap_index *ix, int share, hipStream_t st);
@@ -260,8 +262,8 @@ int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, 
 int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
                   const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);
 int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st);
-// sizes the workspace an index owns (grow only, capped) for a call of nq queries (ap_search.hip)
-int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan = ApWalkPlan());
+// sizes the workspace an index owns (grow only, capped) for a call of nq queries (ap_search.hip); marks: the search may take a floor (k_search)
+int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan = ApWalkPlan(), bool marks = false);
 // the search of a small batch (ap_walk.hip): whether and how
 // (can_bound: the call can take a workspace for bounds), and the launch
 ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters, bool bounds, bool can_bound);

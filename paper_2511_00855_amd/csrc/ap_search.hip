@@ -41,7 +41,8 @@ struct ApSearchArgs {
     const uint4 *meta;  // per document: first entry, counts, |d_dense|
     const uint32_t *deleted;   // one bit per document, NULL = nothing is mark-deleted: left out of the answers only
     float *bound;              // upper bounds of the scores, a row of bound_ld documents per query of the slab; NULL: none
-    const float *bound_floor;  // per query of the slab: neighbours with a bound below it wait (see k_search); NULL: none wait
+    const float4 *bound_floor; // per query of the slab: neighbours with a bound below it wait (see k_search); two lower ones; NULL: none wait
+    uint64_t *marks;           // with bound_floor: per query of the slab a word for 32 documents, visited | bound reaches the floor << 32
     int64_t bound_ld;
     const int32_t *bound_col;  // keyword searches with bounds: head column of every lexical term (-1: the entry's count tells), bitmaps of the columns
     const uint32_t *bound_bits;
@@ -197,6 +198,13 @@ void k_search(ApSearchArgs g) {
     }
     const float wd = g.w[q * g.w_stride + 0], ws = g.w[q * g.w_stride + 1], wf = g.w[q * g.w_stride + 2];
     ApVisited vis{g.visited + (size_t)blockIdx.x * g.words, nullptr};
+    uint64_t *marks = FLOOR ? g.marks + (size_t)blockIdx.x * g.words : nullptr;
+    // marks document v as visited.  1: it was before; 2 (FLOOR): its bound reaches the floor
+    auto meet = [&](int32_t v) -> uint32_t {
+        if (!FLOOR) return vis.test_and_set(v) ? 1u : 0u;
+        const uint64_t old = __hip_atomic_fetch_or(marks + (v >> 5), 1ull << (v & 31), __ATOMIC_RELAXED, AP_VIS_SCOPE);
+        return ((uint32_t)old >> (v & 31) & 1u) | ((uint32_t)(old >> 32) >> (v & 31) & 1u) << 1;
+    };
     if (g.vis_lds) {   // uniform
         vis.l = (AP_LDS uint32_t *)reinterpret_cast<uint32_t *>(umask + (PIPE ? (g.L + 63) / 64 : 0));
         for (size_t i = threadIdx.x; i < g.words; i += blockDim.x) vis.l[i] = 0u;
@@ -221,7 +229,7 @@ void k_search(ApSearchArgs g) {
     for (int32_t i = threadIdx.x; i < g.E; i += blockDim.x) {
         const int32_t v = g.entry[i];
         if (v >= 0) {
-            const bool seen = vis.test_and_set(v);
+            const bool seen = (meet(v) & 1u) != 0u;
             const uint4 m = g.meta[v];
             if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
             if (FLOOR) reinterpret_cast<uint32_t *>(g.bound)[(int64_t)blockIdx.x * g.bound_ld + v] = 0xff800000u;   // -inf: scored
@@ -242,9 +250,16 @@ void k_search(ApSearchArgs g) {
     // were scored although their bound is below the floor (before waiting began) lose their bound, so that the scan passes
     // over them.  4,000 queries of 100,000 documents at beam 2112 : 16: 9,340 -> 4,740 documents scored, 39.0 -> 29.9 ms;
     // 2,000 of 500,000 at beam 8192 : 16: 34,900 -> 13,700, 102.6 -> 79.7 ms.
-    const float floor_score = FLOOR ? g.bound_floor[blockIdx.x] : 0.f;
+    // Whether a bound reaches the floor is a bit beside the visited bit, so that the one atomic tells both: of the neighbours met for the first time
+    // only one in thirty has its bound read then, a line of memory each (all of them: as many bytes as the scoring reads).  The first
+    // iterations, whose parents lie below the floor, take the highest of two lower floors that enough of the pool reaches.  Beam 2112 : 16
+    // as above: 4,740 -> 3,820 documents scored, the search 26.7 -> 23.9 ms; beam 8192 : 16, where steps that wait for one another bound it: 13,700 ->
+    // 13,070, 57.6 -> 56.5.
+    const float4 floors = FLOOR ? g.bound_floor[blockIdx.x] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float floor_score = floors.x;
+    float level = -INFINITY;                      // uniform: the floor in force; what waits has a bound below it
     const uint32_t AP_NO_BOUND = 0xff800000u;   // -inf
-    bool waiting = false, may_wait = FLOOR;       // uniform
+    bool waiting = false, may_wait = FLOOR;       // uniform: something may wait; it may come to that
     int64_t scan = -1;                            // where the scan of what waits is, -1: none under way
     int32_t n_id = 0, next_id = 0;                // uniform: listed neighbours of this iteration, those taken from the list
     AP_PROF_DECL;
@@ -507,7 +522,7 @@ void k_search(ApSearchArgs g) {
         // Parents below the floor, or too few of them, while documents wait that the pool might hold: those come first.
         auto release = [&](int32_t found, bool below) -> bool {
             if (found == g.width && !below) return false;
-            return !(len == g.L && ap_key_score(ap_uniform_u64(cur[g.L - 1])) >= floor_score);
+            return !(len == g.L && ap_key_score(ap_uniform_u64(cur[g.L - 1])) >= level);
         };
         if (!FLOOR || scan < 0) {
         if (FLOOR && may_wait && !waiting) waiting = ap_uniform_i32(s_wait) != 0;   // not again once what waited has been scanned
@@ -544,7 +559,7 @@ void k_search(ApSearchArgs g) {
                 }
             }
             const uint64_t pkey = mine >= 0 ? cur[mine] : 0ull;
-            if (FLOOR && waiting && release(found, __any(mine >= 0 && !(ap_key_score(pkey) >= floor_score)))) scan = 0;   // a NaN counts as below
+            if (FLOOR && waiting && release(found, __any(mine >= 0 && !(ap_key_score(pkey) >= level)))) scan = 0;   // a NaN counts as below
             else {
                 if (mine >= 0) {
                     s_par[lane] = ap_pool_id<KW>(pkey);     // every wave stores the same ids
@@ -588,7 +603,9 @@ void k_search(ApSearchArgs g) {
             while (scan < g.D.n && taken < g.cmax) {   // uniform
                 for (int j = 0; j < SU; j++) {
                     const int64_t v = scan + j * NT + threadIdx.x;
-                    if (v >= g.D.n || !vis.test((int32_t)v)) continue;
+                    if (v >= g.D.n) continue;
+                    const uint64_t mark = __hip_atomic_load(marks + (v >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (v & 31);
+                    if ((mark & (1ull | 1ull << 32)) != 1ull) continue;   // met, with a bound below the floor
                     const uint32_t e = bound[v];
                     const float ub = __uint_as_float(e & ~AP_BOUND_COUNT);
                     if (e == AP_NO_BOUND || !(ub < floor_score) || ub < lowest) continue;
@@ -620,11 +637,21 @@ void k_search(ApSearchArgs g) {
         // marked visited: its descriptor, record and dense row are not read.
         const int32_t per = g.R + (KW ? g.KR : 0);
         bound_on = g.bound && len == g.L;
-        const float b_worst = bound_on ? ap_key_score(ap_uniform_u64(cur[g.L - 1])) : 0.f;
+        const float b_worst = bound_on ? ap_key_score(ap_uniform_u64(cur[g.L - 1])) : -INFINITY;
         const bool b_second_full = kw_on && s_kc == g.k;
-        // waiting begins once the pool holds a few iterations' parents that score at least the floor
-        const int32_t m_on = 4 * g.width + 16 < g.L ? 4 * g.width + 16 : g.L;
-        const bool wait_on = FLOOR && may_wait && (waiting || (len >= m_on && ap_key_score(ap_uniform_u64(cur[m_on - 1])) >= floor_score));
+        // Waiting begins once the pool holds a few iterations' parents that score at least the floor; below a lower floor, which far more
+        // of the neighbours to come reach, once it holds the next iteration's.
+        if (FLOOR && may_wait && level < floor_score) {
+            const int32_t m_on = 4 * g.width + 16 < g.L ? 4 * g.width + 16 : g.L;
+            const int64_t next = (int64_t)(it + 1) * g.width + (g.width > 16 ? g.width : 16);
+            if (len >= m_on && ap_key_score(ap_uniform_u64(cur[m_on - 1])) >= floor_score) level = floor_score;
+            else if (len >= next) {
+                const float at = ap_key_score(ap_uniform_u64(cur[next - 1]));
+                level = fmaxf(level, at >= floors.y ? floors.y : at >= floors.z ? floors.z : -INFINITY);
+            }
+        }
+        const bool wait_on = FLOOR && may_wait && level > -INFINITY;
+        const bool by_bit = wait_on && level == floor_score;   // whether a neighbour waits is its bit
         const float b_second = b_second_full ? ap_key_score(kwc[g.k - 1]) : 0.f;
         auto neighbour = [&](int32_t i) -> int32_t {
             if (KW) {
@@ -640,19 +667,30 @@ void k_search(ApSearchArgs g) {
             for (int32_t i0 = threadIdx.x; i0 < np * per; i0 += GU * NT) {
                 int32_t v[GU];
                 uint32_t e[GU];
+                bool low[GU];
 #pragma unroll
                 for (int j = 0; j < GU; j++) v[j] = i0 + j * NT < np * per ? neighbour(i0 + j * NT) : -1;
 #pragma unroll
-                for (int j = 0; j < GU; j++)
-                    if (v[j] >= 0 && vis.test_and_set(v[j])) v[j] = -1;
+                for (int j = 0; j < GU; j++) {
+                    low[j] = false;
+                    if (v[j] < 0) continue;
+                    const uint32_t met = meet(v[j]);
+                    low[j] = FLOOR && may_wait && !(met & 2u);   // its bound lies below the floor
+                    if (met & 1u) v[j] = -1;
+                    else if (FLOOR && by_bit && low[j]) {   // waits, or cannot enter anyway
+                        if (!(b_worst >= floor_score)) s_wait = 1;
+                        ndropped++;
+                        v[j] = -1;
+                    }
+                }
 #pragma unroll
-                for (int j = 0; j < GU; j++) e[j] = v[j] >= 0 ? bound[v[j]] : 0u;
+                for (int j = 0; j < GU; j++) e[j] = v[j] >= 0 && (!FLOOR || bound_on || low[j]) ? bound[v[j]] : 0x7f800000u;
 #pragma unroll
                 for (int j = 0; j < GU; j++) {
                     if (v[j] < 0) continue;
                     const float ub = __uint_as_float(e[j] & ~AP_BOUND_COUNT);
                     bool out = bound_on && ub < b_worst;
-                    const bool below = FLOOR && may_wait && ub < floor_score, wait = wait_on && below && !out;
+                    const bool wait = FLOOR && wait_on && ub < level && !out;
                     if (kw_on && out) {
                         int32_t held = (int32_t)(e[j] & AP_BOUND_COUNT);
                         for (int32_t t = 0; t < n_kw; t++)
@@ -661,7 +699,7 @@ void k_search(ApSearchArgs g) {
                     }
                     if (out) { ndropped++; continue; }
                     if (wait) { s_wait = 1; ndropped++; continue; }
-                    if (below) bound[v[j]] = AP_NO_BOUND;
+                    if (FLOOR && low[j]) bound[v[j]] = AP_NO_BOUND;
                     if (LIST) { s_ids[atomicAdd(&s_nid, 1)] = v[j]; continue; }
                     const uint4 m = g.meta[v[j]];
                     s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v[j]);
@@ -673,13 +711,14 @@ void k_search(ApSearchArgs g) {
                 if (v >= 0) {
                     // the descriptor (where the record is, how long, the dense norm) is fetched along with the visited
                     // test, not after it: one memory round trip less per iteration for 16 bytes per neighbour already seen
-                    const bool seen = vis.test_and_set(v);
+                    const uint32_t met = meet(v);
+                    const bool seen = (met & 1u) != 0u;
                     if (LIST) { if (!seen) s_ids[atomicAdd(&s_nid, 1)] = v; }
                     else {
                         const uint4 m = g.meta[v];
                         if (!seen) s_meta[atomicAdd(&s_cnt, 1)] = make_uint4(m.x, m.y, m.z, (uint32_t)v);
                     }
-                    if (FLOOR && !seen && may_wait) bound[v] = AP_NO_BOUND;
+                    if (FLOOR && met == 0u && may_wait) bound[v] = AP_NO_BOUND;
                 }
             }
         }
@@ -788,7 +827,7 @@ static int32_t ap_slab_size(int32_t nq, size_t words, size_t cap_words) {
 }
 
 // Sizes the workspace an index owns (grow only) for a call of nq queries.
-int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan) {
+int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan, bool marks) {
     const size_t words = ((size_t)ix->docs.n + 31) / 32;
     const size_t cap_bytes = g_ap_debug.search_workspace_bytes > 0 ? (size_t)g_ap_debug.search_workspace_bytes : AP_SEARCH_WS_BYTES;
     ws->slab = ap_slab_size(nq, words, cap_bytes / 4);
@@ -825,7 +864,7 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
         }
     }
     if (bounds) {
-        AP_TRY(ap_bound_reserve(ix, ws->slab, 2048, AP_BOUND_WS_BYTES, 1, st, &ws->bound));
+        AP_TRY(ap_bound_reserve(ix, ws->slab, 2048, AP_BOUND_WS_BYTES, marks ? AP_BOUND_MARKS : 1, st, &ws->bound));
         if (ws->bound.table) ws->slab = ws->bound.slab;
     }
     return AP_OK;
@@ -954,7 +993,8 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     }
     // A floor below which neighbours wait: where a search ends by itself, in large pools.  In small ones (256 threads) what
     // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
-    g.bound_floor = ws.bound.table && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? ws.bound.floor : nullptr;
+    g.bound_floor = ws.bound.table && ws.bound.marks && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? reinterpret_cast<const float4 *>(ws.bound.floor) : nullptr;
+    g.marks = ws.bound.marks;
     g.nxtw = nt <= 256 && g.cmax > nt ? g.cmax : 0;
     g.vis_lds = visited_fit(nt) ? 1 : 0;
     const size_t smem = lds_bytes(nt, g.cmax, g.icap) + (g.vis_lds ? g.words * 4 + 8 : 0);
@@ -975,7 +1015,7 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
         g.q0 = q0;
         g.no_tables = g_ap_debug.search_query_lists != 0;
         // every slab starts from empty visited sets (a fill kernel, not a memset: callers may capture the stream)
-        if (!g.vis_lds) AP_TRY(ap_fill_u32(ws.visited, g.words * (size_t)qn, 0u, st));
+        if (!g.vis_lds && !g.bound_floor) AP_TRY(ap_fill_u32(ws.visited, g.words * (size_t)qn, 0u, st));
         if (q0 == 0 && ws.ev0) AP_CHECK_HIP(hipEventRecord(ws.ev0, st));
         if (ws.bound.table) {
             AP_TRY(ap_bound_fill(ix, ws.bound, Q, w_dev, w_stride, q0, qn, kw_terms, kw_stride, st));
@@ -1033,7 +1073,7 @@ static int ap_search_impl(ap_index *ix, const ap_queries *q, const float *per_qu
     ApSearchWs ws;
     const bool bounds = ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters);
     const ApWalkPlan plan = kw_terms ? ApWalkPlan() : ap_walk_plan(ix, q->nq, p->beam, p->search_width, p->max_iters, bounds, true);
-    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, bounds, plan));
+    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, bounds, plan, !kw_terms && !ix->deleted && p->max_iters == 0));
     return ap_search_launch(ix, ws, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, p->k, p->beam, p->max_iters,
                             p->search_width, kw_terms, kw_stride, kw_flags, false, out_ids, out_scores, (hipStream_t)stream);
 }
