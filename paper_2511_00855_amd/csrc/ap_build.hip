@@ -59,54 +59,66 @@ __global__ __launch_bounds__(256) void k_seed_scores(const void *dense, int32_t 
 // Appending a tile's candidates to their rows' buffers.  A candidate is not appended on the spot (an atomic on the
 // row's counter whose answer the store has to wait for, at some forty of a lane's sixty-four elements): the wave notes
 // it in its own part of the LDS the product has left (place = a running count + the lane's rank among the lanes that
-// passed: no atomic, no wait); afterwards the candidates are counted per row in LDS, every row that has some takes its
-// places in buf with ONE atomic for the whole tile, and the candidates are written out.
-// An entry: score bits | column in the tile << 32 | row in the tile << 40 | side << 48 | (later) place << 49.
-// side 0: the candidate goes to the buffer of its row's document (id = its column's document); side 1, used by the
-// symmetric sweep only: the score is also that of the mirrored pair, and the candidate goes to the buffer of its
-// column's document (id = its row's document).
-// direct(side, i, j, v): the append on the spot, for what the wave's part (wcap entries) cannot hold.
+// passed: no atomic, no wait); afterwards the candidates are counted per buffer in LDS, every buffer that has some takes its
+// places with ONE atomic for the whole tile, and the candidates are written out.
+// An entry: score bits | column in the tile << 32 | row in the tile << 40 | (later) place in the row's buffer << 48 | in the column's << 56.  One
+// entry serves both sides of the symmetric sweep: the buffer of its row's document, with the id of its column's, and that of its
+// column's document, with the id of its row's.  Which of them it is for is told when it is counted and when it is written, so that an
+// element costs one comparison, with the lower of its two thresholds.
+// direct(i, j, v): the append on the spot, for what the wave's part (wcap entries) cannot hold.
 template <typename DIRECT>
-__device__ __forceinline__ void ap_seed_stage(bool pass, int side, int i, int j, float v, uint64_t *stage, int32_t wcap, int32_t &nw, DIRECT direct) {
+__device__ __forceinline__ void ap_seed_stage(bool pass, int i, int j, float v, uint64_t *stage, int32_t wcap, int32_t &nw, DIRECT direct) {
     const uint64_t m = __ballot(pass);
     if (m) {
         if (pass) {
             const int32_t slot = nw + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (slot < wcap) stage[slot] = ((uint64_t)(uint32_t)((side << 16) | (i << 8) | j) << 32) | __float_as_uint(v);
-            else direct(side, i, j, v);
+            if (slot < wcap) stage[slot] = ((uint64_t)(uint32_t)((i << 8) | j) << 32) | __float_as_uint(v);
+            else direct(i, j, v);
         }
         nw += __popcll(m);
     }
 }
-// Called by every thread of the workgroup once its wave has staged nw candidates.  drop(side, i, j): a candidate that is
-// not one after all (the document itself, a row or column past the end).  s_cnt[2 * rows] must be zero on entry
-// ([rows] if no candidate has side 1).  Buffers and counters are indexed by row0 + (row in the tile) for side 0 and by
-// row1 + (column in the tile) for side 1; the ids stored are id0 + column and id1 + row.
-template <typename DROP>
-__device__ __forceinline__ void ap_seed_flush(uint64_t *stage, int32_t wcap, int32_t nw, int32_t rows, bool both_sides, int32_t *s_cnt,
-                                              int32_t *s_base, int32_t *__restrict__ cnt, unsigned long long *__restrict__ buf, int32_t cap,
-                                              int64_t row0, int32_t id0, int64_t row1, int32_t id1, DROP drop) {
+// Called by every thread of the workgroup once its wave has staged nw candidates.  to_row(i, j, v), to_col(i, j, v): whether a score is for the
+// buffer of its row's document, of its column's.  s_cnt must be zero on entry: counters of the E rows, then (both) of the E columns; a buffer gets at
+// most E <= 256 of a tile's candidates.  Buffers and counters are indexed by row0 + row and by col0 + column; the ids stored are id0 + column and id1 + row.
+template <int E, typename TO_ROW, typename TO_COL>
+__device__ __forceinline__ void ap_seed_flush(uint64_t *stage, int32_t wcap, int32_t nw, bool both, int32_t *s_cnt, int32_t *s_base, int32_t *__restrict__ cnt,
+                                              unsigned long long *__restrict__ buf, int32_t cap, int64_t row0, int32_t id0, int64_t col0, int32_t id1,
+                                              TO_ROW to_row, TO_COL to_col) {
+    static_assert(E <= 256, "places of eight bits");
     const int lane = threadIdx.x & 63;
     const int32_t ns = nw < wcap ? nw : wcap;
     for (int32_t p = lane; p < ns; p += 64) {
         const uint64_t e = stage[p];
-        const int32_t j = (int32_t)(e >> 32) & 255, i = (int32_t)(e >> 40) & 255, side = (int32_t)(e >> 48) & 1;
-        if (drop(side, i, j)) { stage[p] = e | (0x7fffull << 49); continue; }
-        stage[p] = e | ((uint64_t)atomicAdd(&s_cnt[side ? rows + j : i], 1) << 49);
+        const int32_t j = (int32_t)(e >> 32) & 255, i = (int32_t)(e >> 40) & 255;
+        const float v = __uint_as_float((uint32_t)e);
+        const uint32_t r = to_row(i, j, v) ? (uint32_t)atomicAdd(&s_cnt[i], 1) : 0u, c = both && to_col(i, j, v) ? (uint32_t)atomicAdd(&s_cnt[E + j], 1) : 0u;
+        stage[p] = e | ((uint64_t)(r | (c << 8)) << 48);
     }
     __syncthreads();
-    for (int32_t x = threadIdx.x; x < (both_sides ? 2 * rows : rows); x += blockDim.x) {
+    for (int32_t x = threadIdx.x; x < (both ? 2 * E : E); x += blockDim.x) {
         const int32_t c = s_cnt[x];
-        s_base[x] = c ? atomicAdd(&cnt[x < rows ? row0 + x : row1 + (x - rows)], c) : 0;
+        s_base[x] = c ? atomicAdd(&cnt[x < E ? row0 + x : col0 + (x - E)], c) : 0;
     }
     __syncthreads();
     for (int32_t p = lane; p < ns; p += 64) {
         const uint64_t e = stage[p];
-        const int32_t j = (int32_t)(e >> 32) & 255, i = (int32_t)(e >> 40) & 255, side = (int32_t)(e >> 48) & 1, place = (int32_t)(e >> 49);
-        if (place == 0x7fff) continue;
-        const int32_t pos = s_base[side ? rows + j : i] + place;
-        if (pos < cap) buf[(side ? row1 + j : row0 + i) * (int64_t)cap + pos] = ap_make_key(__uint_as_float((uint32_t)e), side ? id1 + i : id0 + j, 1u);
+        const int32_t j = (int32_t)(e >> 32) & 255, i = (int32_t)(e >> 40) & 255;
+        const float v = __uint_as_float((uint32_t)e);
+        if (to_row(i, j, v)) {
+            const int32_t pos = s_base[i] + ((int32_t)(e >> 48) & 255);
+            if (pos < cap) buf[(row0 + i) * (int64_t)cap + pos] = ap_make_key(v, id0 + j, 1u);
+        }
+        if (both && to_col(i, j, v)) {
+            const int32_t pos = s_base[E + j] + (int32_t)(e >> 56);
+            if (pos < cap) buf[(col0 + j) * (int64_t)cap + pos] = ap_make_key(v, id1 + i, 1u);
+        }
     }
+}
+// The append on the spot.
+__device__ __forceinline__ void ap_seed_append(int64_t row, int32_t id, float v, int32_t *__restrict__ cnt, unsigned long long *__restrict__ buf, int32_t cap) {
+    const int32_t pos = atomicAdd(&cnt[row], 1);
+    if (pos < cap) buf[row * (int64_t)cap + pos] = ap_make_key(v, id, 1u);
 }
 
 // The same product over all columns, but instead of storing the scores, every
@@ -134,7 +146,7 @@ __global__ __launch_bounds__(256) void k_seed_thresh(const void *dense, int32_t 
     if (threadIdx.x < AP_TILE) {
         const int64_t r = i0 + threadIdx.x;
         s_cnt[threadIdx.x] = 0;
-        if (SYM) { s_cnt[AP_TILE + threadIdx.x] = 0; s_tauc[threadIdx.x] = tau[j0 - row0 + threadIdx.x]; }
+        if (SYM) { s_cnt[AP_TILE + threadIdx.x] = 0; s_tauc[threadIdx.x] = mirror ? tau[j0 - row0 + threadIdx.x] : INFINITY; }
         a_rows[threadIdx.x] = r < nrows ? (node_ids ? node_ids[row0 + r] : (int32_t)(row0 + r)) : -1;
         s_tau[threadIdx.x] = r < nrows ? tau[r] : INFINITY;
         const int64_t j = j0 + threadIdx.x;
@@ -145,20 +157,16 @@ __global__ __launch_bounds__(256) void k_seed_thresh(const void *dense, int32_t 
     __syncthreads();   // the product's LDS is free
     constexpr int W_CAP = ApTileLds<DT>::BYTES / 4 / 8;
     uint64_t *stage = reinterpret_cast<uint64_t *>(lds) + ap_wave_id() * W_CAP;
-    auto drop = [&](int, int i, int j) { return !(i0 + i < nrows && j0 + j < n && a_rows[i] != (int32_t)(j0 + j)); };
-    auto direct = [&](int side, int i, int j, float v) {
-        if (!drop(side, i, j)) {
-            const int64_t row = side ? j0 - row0 + j : i0 + i;
-            const int32_t pos = atomicAdd(&cnt[row], 1);
-            if (pos < cap) buf[row * (int64_t)cap + pos] = ap_make_key(v, side ? (int32_t)(row0 + i0 + i) : (int32_t)(j0 + j), 1u);
-        }
+    auto in = [&](int i, int j) { return i0 + i < nrows && j0 + j < n && a_rows[i] != (int32_t)(j0 + j); };   // not the document itself, nor a row or column past the end
+    auto to_row = [&](int i, int j, float v) { return v >= s_tau[i] && in(i, j); };
+    auto to_col = [&](int i, int j, float v) { return mirror && v >= s_tauc[j] && in(i, j); };
+    auto direct = [&](int i, int j, float v) {
+        if (to_row(i, j, v)) ap_seed_append(i0 + i, (int32_t)(j0 + j), v, cnt, buf, cap);
+        if (SYM && to_col(i, j, v)) ap_seed_append(j0 - row0 + j, (int32_t)(row0 + i0 + i), v, cnt, buf, cap);
     };
     int32_t nw = 0;
-    ap_tile_foreach(acc, [&](int i, int j, float v) {
-        ap_seed_stage(v >= s_tau[i], 0, i, j, v, stage, W_CAP, nw, direct);
-        if (SYM) ap_seed_stage(mirror && v >= s_tauc[j], 1, i, j, v, stage, W_CAP, nw, direct);
-    });
-    ap_seed_flush(stage, W_CAP, nw, AP_TILE, SYM, s_cnt, s_base, cnt, buf, cap, i0, (int32_t)j0, j0 - row0, (int32_t)(row0 + i0), drop);
+    ap_tile_foreach(acc, [&](int i, int j, float v) { ap_seed_stage(v >= (SYM ? fminf(s_tau[i], s_tauc[j]) : s_tau[i]), i, j, v, stage, W_CAP, nw, direct); });
+    ap_seed_flush<AP_TILE>(stage, W_CAP, nw, SYM, s_cnt, s_base, cnt, buf, cap, i0, (int32_t)j0, j0 - row0, (int32_t)(row0 + i0), to_row, to_col);
 }
 
 // The thresholded sweep for bf16 rows on 256x256 tiles (the product above): the same appends as k_seed_thresh.
@@ -190,40 +198,38 @@ __global__ __launch_bounds__(WM * WN * 64) void k_seed_thresh_big(const void *de
     if (!ap_seed_tile(nrt, rt, ct)) return;
     const int64_t i0 = (rt0 + rt) * AP_BIG, j0 = (ct0 + ct) * AP_BIG;
     if (SYM && j0 < i0) return;   // below the diagonal: its mirror image does the work
-    for (int32_t x = threadIdx.x; x < AP_BIG; x += blockDim.x) {
-        s_cnt[x] = 0;
-        if (SYM) { s_cnt[AP_BIG + x] = 0; s_tauc[x] = tau[j0 + x]; }
-        const int64_t r = i0 + x;
-        a_rows[x] = r < nrows ? (node_ids ? node_ids[row0 + r] : (int32_t)(row0 + r)) : -1;
-        s_tau[x] = r < nrows ? tau[r] : INFINITY;
-        const int64_t j = j0 + x;
-        b_rows[x] = j < n ? (int32_t)j : -1;
-    }
     ap_f32x16 acc[ApBig<WM, WN>::FA][ApBig<WM, WN>::FB];
+    constexpr int W_CAP = AP_BIG_LDS_BYTES / (WM * WN) / 8;   // entries of a wave's part of the LDS
+    uint64_t *stage = reinterpret_cast<uint64_t *>(big_lds) + ap_wave_id() * W_CAP;
+    int32_t nw = 0;   // uniform: candidates of this wave so far
     if (RUN) {
         const int32_t a_first = (int32_t)(row0 + i0), b_first = (int32_t)j0;
-        ap_big_gemm_bf16<WM, WN, true>(dense, dim, a_rows, b_rows, a_first, b_first, reinterpret_cast<uint16_t *>(big_lds), acc);
-        // A lane holds 4 consecutive rows x (FB x 32 columns apart) per 8-row group: the rows' thresholds come as one
-        // 16-byte LDS read, and an element costs a compare and a (rarely taken) branch.  Only a tile whose row and
-        // column runs overlap can pair a document with itself.
+        // Only a tile whose row and column runs overlap can pair a document with itself.
         const bool diagonal = a_first < b_first + AP_BIG && b_first < a_first + AP_BIG;
         const bool mirror = SYM && !diagonal;   // uniform: the scores also go to the column documents
+        // the thresholds travel while the product runs: a thread's is one of the rows' or one of the columns'
+        static_assert(WM * WN * 64 >= 2 * AP_BIG, "a threshold a thread");
+        const int32_t x = threadIdx.x & (AP_BIG - 1);
+        float own = INFINITY;
+        if (threadIdx.x < AP_BIG) own = tau[i0 + x];
+        else if (mirror && threadIdx.x < 2 * AP_BIG) own = tau[j0 + x];
+        ap_big_gemm_bf16<WM, WN, true>(dense, dim, a_rows, b_rows, a_first, b_first, reinterpret_cast<uint16_t *>(big_lds), acc);
+        if (threadIdx.x < AP_BIG) { s_tau[x] = own; s_cnt[x] = 0; }
+        else if (SYM && threadIdx.x < 2 * AP_BIG) { s_tauc[x] = own; s_cnt[AP_BIG + x] = 0; }
+        __syncthreads();
         const int lane = threadIdx.x & 63, wave = ap_wave_id();
         const int wm = wave / WN, wn = wave % WN;
-        constexpr int W_CAP = AP_BIG_LDS_BYTES / (WM * WN) / 8;   // entries of a wave's part of the LDS
-        uint64_t *stage = reinterpret_cast<uint64_t *>(big_lds) + wave * W_CAP;
-        auto drop = [&](int, int i, int j) { return diagonal && a_first + i == b_first + j; };
-        auto direct = [&](int side, int i, int j, float v) {
-            if (!drop(side, i, j)) {
-                const int64_t row = side ? j0 + j : i0 + i;
-                const int32_t pos = atomicAdd(&cnt[row], 1);
-                if (pos < cap) buf[row * (int64_t)cap + pos] = ap_make_key(v, side ? a_first + i : b_first + j, 1u);
-            }
+        auto to_row = [&](int i, int j, float v) { return v >= s_tau[i] && !(diagonal && a_first + i == b_first + j); };
+        auto to_col = [&](int, int j, float v) { return mirror && v >= s_tauc[j]; };
+        auto direct = [&](int i, int j, float v) {
+            if (to_row(i, j, v)) ap_seed_append(i0 + i, b_first + j, v, cnt, buf, cap);
+            if (SYM && to_col(i, j, v)) ap_seed_append(j0 + j, a_first + i, v, cnt, buf, cap);
         };
+        // A lane holds 4 consecutive rows x (FB x 32 columns apart) per 8-row group: the rows' thresholds come as one
+        // 16-byte LDS read, and an element costs a minimum, a compare and a branch, taken at some three of ten.
         float tc[ApBig<WM, WN>::FB];   // the thresholds of this lane's columns
 #pragma unroll
         for (int b = 0; b < ApBig<WM, WN>::FB; b++) tc[b] = SYM ? s_tauc[wn * (AP_BIG / WN) + b * 32 + (lane & 31)] : INFINITY;
-        int32_t nw = 0;   // uniform: candidates of this wave so far
 #pragma unroll
         for (int a = 0; a < ApBig<WM, WN>::FA; a++)
 #pragma unroll
@@ -236,26 +242,23 @@ __global__ __launch_bounds__(WM * WN * 64) void k_seed_thresh_big(const void *de
 #pragma unroll
                     for (int rr = 0; rr < 4; rr++) {
                         const float v = acc[a][b][4 * q + rr];
-                        const int j = wn * (AP_BIG / WN) + b * 32 + (lane & 31);
-                        ap_seed_stage(v >= tt[rr], 0, ib + rr, j, v, stage, W_CAP, nw, direct);
-                        if (SYM) ap_seed_stage(mirror && v >= tc[b], 1, ib + rr, j, v, stage, W_CAP, nw, direct);
+                        ap_seed_stage(v >= (SYM ? fminf(tt[rr], tc[b]) : tt[rr]), ib + rr, wn * (AP_BIG / WN) + b * 32 + (lane & 31), v, stage, W_CAP, nw, direct);
                     }
             }
-        ap_seed_flush(stage, W_CAP, nw, AP_BIG, SYM, s_cnt, s_base, cnt, buf, cap, i0, b_first, j0, a_first, drop);
+        ap_seed_flush<AP_BIG>(stage, W_CAP, nw, SYM, s_cnt, s_base, cnt, buf, cap, i0, b_first, j0, a_first, to_row, to_col);
     } else {
+        for (int32_t x = threadIdx.x; x < AP_BIG; x += blockDim.x) {
+            const int64_t r = i0 + x, j = j0 + x;
+            a_rows[x] = r < nrows ? (node_ids ? node_ids[row0 + r] : (int32_t)(row0 + r)) : -1;
+            s_tau[x] = r < nrows ? tau[r] : INFINITY;
+            s_cnt[x] = 0;
+            b_rows[x] = j < n ? (int32_t)j : -1;
+        }
         ap_big_gemm_bf16<WM, WN, false>(dense, dim, a_rows, b_rows, 0, 0, reinterpret_cast<uint16_t *>(big_lds), acc);
-        constexpr int W_CAP = AP_BIG_LDS_BYTES / (WM * WN) / 8;
-        uint64_t *stage = reinterpret_cast<uint64_t *>(big_lds) + ap_wave_id() * W_CAP;
-        auto drop = [&](int, int i, int j) { return !(i0 + i < nrows && j0 + j < n && a_rows[i] != (int32_t)(j0 + j)); };
-        auto direct = [&](int, int i, int j, float v) {
-            if (!drop(0, i, j)) {
-                const int32_t pos = atomicAdd(&cnt[i0 + i], 1);
-                if (pos < cap) buf[(i0 + i) * (int64_t)cap + pos] = ap_make_key(v, (int32_t)(j0 + j), 1u);
-            }
-        };
-        int32_t nw = 0;
-        ap_big_foreach<WM, WN>(acc, [&](int i, int j, float v) { ap_seed_stage(v >= s_tau[i], 0, i, j, v, stage, W_CAP, nw, direct); });
-        ap_seed_flush(stage, W_CAP, nw, AP_BIG, false, s_cnt, s_base, cnt, buf, cap, i0, (int32_t)j0, (int64_t)0, 0, drop);
+        auto to_row = [&](int i, int j, float v) { return v >= s_tau[i] && i0 + i < nrows && j0 + j < n && a_rows[i] != (int32_t)(j0 + j); };
+        auto direct = [&](int i, int j, float v) { if (to_row(i, j, v)) ap_seed_append(i0 + i, (int32_t)(j0 + j), v, cnt, buf, cap); };
+        ap_big_foreach<WM, WN>(acc, [&](int i, int j, float v) { ap_seed_stage(v >= s_tau[i], i, j, v, stage, W_CAP, nw, direct); });
+        ap_seed_flush<AP_BIG>(stage, W_CAP, nw, false, s_cnt, s_base, cnt, buf, cap, i0, (int32_t)j0, (int64_t)0, 0, to_row, [](int, int, float) { return false; });
     }
 }
 
@@ -516,12 +519,12 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
 // above the diagonal are multiplied and every score is offered to both of its documents (k_seed_thresh_big<.., SYM>).
 // For that every document's candidate buffer has to exist at once, so the buffers are short (cap entries, by the
 // memory that is free) and the thresholds tight: tau = the m-th best of cs sampled columns with m < K, chosen so that
-// a row expects about 0.45 cap candidates.  Such a tau is not a guaranteed lower bound of the row's K-th best: a row
-// that ends up with fewer than K candidates (a few in ten thousand) or more than cap is redone by the exact path,
+// a row expects some 6 K candidates (less than half the buffer).  Such a tau is not a guaranteed lower bound of the row's K-th best: a row
+// that ends up with fewer than K candidates (hardly any) or more than cap is redone by the exact path,
 // like an overflowing row of the one-sided sweep.  The lists are the exact ones either way.
 // rounded (f32 rows): thresholds and sweep take the rows rounded to bf16, at eight times the matrix rate, and the few candidates that the
 // rounding leaves open are scored in f32 (k_rescore_buf).  The lists are the same bits.  100,000 rows of 768 columns, K = 128: 82.7 ms with
-// f32 products (71 of them the sweep), 29.5 ms rounded (10.4 the sweep); 96 columns: 23.4 and 11.5 ms.
+// f32 products (71 of them the sweep), 29.5 ms rounded (9.4 the sweep); 96 columns: 23.4 and 11.5 ms.
 // *done = false (and AP_OK): not applicable here (shape, memory; rounded: norms that differ too much, or rows too much alike for the
 // rounding to tell them apart, which a sample of rows says before the sweep); the caller takes the next sweep.  Rows with a mean cosine of 0.8,
 // 100,000 x 768, K = 128: 84.5 ms, the f32 sweep alone 83.8, and 100 with the rounded sweep in front of it.
@@ -540,11 +543,14 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     int64_t cap = 4096;
     while (cap > 512 && (double)n * (double)cap * 8.0 > 0.62 * (double)free_b) cap >>= 1;
     if ((double)n * (double)cap * 8.0 > 0.62 * (double)free_b) return AP_OK;
-    // Fewer candidates do where they are scored again: three times what the band takes, of a sample that need not be large.
-    const double mean = rounded ? std::min(0.45 * (double)cap, std::max(6.0 * K, 24.0 * (double)n / 4096.0)) : 0.45 * (double)cap;
+    // Every candidate costs the sweep and the selection (200,000 bf16 documents of 1,024 columns, K = 128: the sweep 45.1 ms with 1,843 a row and a
+    // comparison for each side of an element, 40.0 with 781 and one), and 6 K of them
+    // do, from a sample that need not be large: where they are scored again that is three times what the band takes, and a rank of 24 leaves a
+    // row in ten thousand short; where K are enough a rank of 12 leaves one in a million.
+    const double mean = std::min(0.45 * (double)cap, std::max(6.0 * K, (rounded ? 24.0 : 12.0) * (double)n / 4096.0));
     // the rounded sweep needs more candidates than K: on a small corpus a rank beyond K
     const int64_t m_max = rounded ? 256 : K;
-    int64_t m = std::min<int64_t>(m_max, 24);
+    int64_t m = std::min<int64_t>(m_max, rounded || mean < 6.0 * K ? 24 : 12);
     int64_t cs = (int64_t)((double)m * (double)n / mean) + 1;
     const int64_t cs_min = g_ap_debug.seed_sample_cols > 0 ? std::max<int64_t>(K + 1, g_ap_debug.seed_sample_cols) : 4096;
     if (cs < cs_min || g_ap_debug.seed_sample_cols > 0) {   // a fixed sample: the rank that gives the same expectation
