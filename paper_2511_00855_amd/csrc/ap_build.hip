@@ -1657,11 +1657,27 @@ extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t
 // Dense part: G = X X^T for the K gathered rows of one neighbourhood (MFMA); what follows reads the lower triangle only.
 // A tile on the diagonal has the same rows on both sides, which are loaded and staged once, and takes the ten of its sixteen
 // 32 x 32 blocks that reach the triangle: three, two, two and three a wave, the roles going round with the node so that
-// the SIMDs of a CU get the same work.  Same products in the same order as the full tile, so the same bits.  Bound by the matrix units for
-// f32 rows and by the gather of the rows for bf16: 22.3 -> 17.3 ms for 100,000 documents of 768 f32 columns, 10.7 -> 9.5 ms for 200,000
-// of 1,024 bf16 columns.
+// the SIMDs of a CU get the same work.  Same products in the same order as the full tile, so the same bits.  Bound by the gather of the rows (bf16
+// rows: 10.7 -> 9.5 ms for 200,000 documents of 1,024 columns); for f32 rows it was the f32 matrix instructions, at a sixteenth of the bf16
+// rate.  A f32 value is the sum of three bf16 values, each the rounding of what the ones before it leave, and of the nine products of two such sums six
+// matter: what the other three add lies 2^-26 below the product, a quarter of what rounding it to f32 takes off.  So a tile on the diagonal is
+// split while it goes to LDS and takes six bf16 instructions for sixteen columns where f32 ones take eight at twice the cycles each.
+// 100,000 documents of 768 columns: 17.1 -> 9.7 ms.  Largest and root mean square error against 64 bits, of |a||b|: 1.8e-7 and 1.8e-8 -> 1.4e-7 and
+// 1.5e-8 (768 Gaussian columns), 1.26e-6 and 2.7e-7 -> 9.3e-7 and 2.0e-7 (768 positive ones); smaller too at 96, 260 and 1,024 columns.
+// Not where a norm says that values may overflow as bf16 (beyond 1e15) or that a rounding's rest may get lost among the smallest numbers (below
+// 1e-12), nor with an infinity or a NaN: those neighbourhoods take the f32 instructions.
+#define AP_GD_STRIDE (AP_BK + 8)   // bf16 elements: 80-byte rows, of which eight lanes' 16-byte reads meet every bank once
+typedef __bf16 ap_bf16x2 __attribute__((ext_vector_type(2)));
+// The three parts of two values, packed as they lie in LDS.
+__device__ __forceinline__ void ap_split_bf16(float x, float y, uint32_t (&part)[3]) {
+#pragma unroll
+    for (int p = 0; p < 3; p++) {
+        part[p] = __builtin_bit_cast(uint32_t, ap_bf16x2{(__bf16)x, (__bf16)y});
+        x -= __uint_as_float(part[p] << 16); y -= __uint_as_float(part[p] & 0xffff0000u);   // exact
+    }
+}
 template <int DT>
-__global__ __launch_bounds__(256) void k_gram_dense(const void *dense, int32_t dim, int32_t K, const int32_t *__restrict__ knn,
+__global__ __launch_bounds__(256) void k_gram_dense(const void *dense, const float *__restrict__ norm, int32_t dim, int32_t K, const int32_t *__restrict__ knn,
                                                     const int32_t *__restrict__ node_ids, int64_t x0,
                                                     float *__restrict__ pm /* chunk x K x K */) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[ApTileLds<DT>::BYTES];
@@ -1696,8 +1712,70 @@ __global__ __launch_bounds__(256) void k_gram_dense(const void *dense, int32_t d
         for (int b = 0; b < 2; b++)
 #pragma unroll
             for (int r = 0; r < 16; r++) acc[a][b][r] = 0.f;
-    __syncthreads();   // the row list
-    if constexpr (DT == AP_F32) {
+    bool odd = false;   // uniform, f32 rows: a neighbourhood whose values three bf16 ones may not hold
+    if (DT == AP_F32) {
+        if (threadIdx.x < AP_TILE && a_rows[threadIdx.x] >= 0) {   // this thread's own entry
+            const float x = norm[a_rows[threadIdx.x]];
+            odd = !(x <= 1e15f && x >= 1e-12f);
+        }
+        odd = __syncthreads_or(odd) != 0;
+    } else __syncthreads();   // the row list
+    if constexpr (DT == AP_F32) if (!odd) {
+        uint16_t *lS = reinterpret_cast<uint16_t *>(lds);   // [3][128][AP_GD_STRIDE]
+        static_assert(3 * AP_TILE * AP_GD_STRIDE * 2 <= ApTileLds<AP_F32>::BYTES, "LDS");
+        constexpr int PLANE = AP_TILE * AP_GD_STRIDE;
+        float4 va[4];
+        int32_t ra[4];
+#pragma unroll
+        for (int pass = 0; pass < 4; pass++) ra[pass] = a_rows[(threadIdx.x >> 3) + 32 * pass];
+        ap_tile_load<DT>(dense, dim, ra, 0, va);
+        const uint16_t *pa = lS + (r0 * 32 + li) * AP_GD_STRIDE + half * 8, *pb = lS + (c0 * 32 + li) * AP_GD_STRIDE + half * 8;
+        const uint16_t *pc = lS + ((corner ? r0 + 1 : c0 + 1) * 32 + li) * AP_GD_STRIDE + half * 8;
+        auto read = [&](const uint16_t *at, ap_bf16x8 (&f)[3]) {
+#pragma unroll
+            for (int p = 0; p < 3; p++) f[p] = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(at + p * PLANE));
+        };
+        constexpr int TA[6] = {1, 2, 0, 1, 0, 0}, TB[6] = {1, 0, 2, 0, 1, 0};   // the smallest products first
+        for (int32_t k0 = 0; k0 < dim; k0 += AP_BK) {
+            __syncthreads();
+            const bool inside = k0 + (int)(threadIdx.x & 7) * 4 < dim;
+#pragma unroll
+            for (int pass = 0; pass < 4; pass++) {
+                const bool keep = ra[pass] >= 0 && inside;
+                uint32_t lo[3], hi[3];
+                ap_split_bf16(keep ? va[pass].x : 0.f, keep ? va[pass].y : 0.f, lo);
+                ap_split_bf16(keep ? va[pass].z : 0.f, keep ? va[pass].w : 0.f, hi);
+                uint16_t *to = lS + ((threadIdx.x >> 3) + 32 * pass) * AP_GD_STRIDE + (threadIdx.x & 7) * 4;
+#pragma unroll
+                for (int p = 0; p < 3; p++) *reinterpret_cast<uint2 *>(to + p * PLANE) = make_uint2(lo[p], hi[p]);
+            }
+            __syncthreads();
+            if (k0 + AP_BK < dim) ap_tile_load<DT>(dense, dim, ra, k0 + AP_BK, va);
+            if (!any) continue;
+#pragma unroll
+            for (int kk = 0; kk < AP_BK; kk += 16) {
+                ap_bf16x8 a0[3], c1[3], b0[3];
+                read(pa + kk, a0);
+                read(pc + kk, c1);
+                if (corner) {
+#pragma unroll
+                    for (int t = 0; t < 6; t++) {
+                        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[TA[t]], a0[TB[t]], acc[0][0], 0, 0, 0);
+                        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1[TA[t]], a0[TB[t]], acc[1][0], 0, 0, 0);
+                        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1[TA[t]], c1[TB[t]], acc[1][1], 0, 0, 0);
+                    }
+                } else {
+                    read(pb + kk, b0);
+#pragma unroll
+                    for (int t = 0; t < 6; t++) {
+                        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[TA[t]], b0[TB[t]], acc[0][0], 0, 0, 0);
+                        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[TA[t]], c1[TB[t]], acc[0][1], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+    if (DT == AP_F32 && odd) {
         float *lA = reinterpret_cast<float *>(lds);
         float4 va[4];
         int32_t ra[4];
@@ -1729,7 +1807,8 @@ __global__ __launch_bounds__(256) void k_gram_dense(const void *dense, int32_t d
                 }
             }
         }
-    } else {
+    }
+    if constexpr (DT == AP_BF16) {
         uint16_t *lA = reinterpret_cast<uint16_t *>(lds);
         uint4 va[AP_NP16];
         int32_t ra[AP_NP16];
@@ -2527,9 +2606,9 @@ int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_i
             const int64_t yn = std::min<int64_t>(32768, cn - y0);
             dim3 g1((unsigned)(tiles * tiles), (unsigned)yn);
             if (ix->dtype == AP_F32)
-                hipLaunchKernelGGL(k_gram_dense<AP_F32>, g1, dim3(256), 0, st, ix->docs.dense, ix->docs.dim, K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
+                hipLaunchKernelGGL(k_gram_dense<AP_F32>, g1, dim3(256), 0, st, ix->docs.dense, ix->dense_norm, ix->docs.dim, K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
             else
-                hipLaunchKernelGGL(k_gram_dense<AP_BF16>, g1, dim3(256), 0, st, ix->docs.dense, ix->docs.dim, K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
+                hipLaunchKernelGGL(k_gram_dense<AP_BF16>, g1, dim3(256), 0, st, ix->docs.dense, ix->dense_norm, ix->docs.dim, K, knn_ids, node_ids, x0 + y0, pm + y0 * per);
             e = hipGetLastError();
             if (e != hipSuccess) break;
             if (by_columns) {

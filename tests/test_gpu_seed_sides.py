@@ -17,6 +17,8 @@ def test_scores_that_reach_both_thresholds(debug_knobs, bf16, n, huge):
     w.docs.dense[:] = w.docs.dense[np.arange(n) % 5]   # a fifth of the corpus ties for every row's best
     if huge:
         w.docs.dense[-huge:] = 1e20 * np.abs(w.docs.dense[-huge:])   # their products overflow
+    if bf16:
+        w.docs.dense_bf16[:] = torch.from_numpy(w.docs.dense).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
     docs = B.DeviceVecs(w.docs, bf16=bf16)
     ix = B.Index.ingest(docs, B.build_params(8, knn_k=24, nd_rounds=1, nd_sample=4, n_entry=4))
     exact = [t.clone().view(torch.int32) for t in ix.stage_seed_knn(24)]
