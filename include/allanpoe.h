@@ -359,8 +359,8 @@ int ap_build_counters(const ap_index *index, uint64_t out2[2], void *stream);
  * The others were left out because an upper bound keeps them from every list. */
 int ap_build_scored(const ap_index *index, uint64_t *out, void *stream);
 
-/* Which rows the products of the last seed stage on this index took (host int32): 1 = bf16, stored or rounded from
- * f32 (the candidates are then scored again in f32), 0 = f32. */
+/* Which rows the products of the last seed stage on this index took (host int32): 1 = 16-bit ones: stored bf16, or f32 rounded to
+ * f16 (the candidates are then scored again in f32), 0 = f32. */
 int ap_build_seed_bf16(const ap_index *index, int32_t *out);
 
 /* Whether the rounds of the last construction or insertion that gave this index told candidates apart by packed lists

@@ -5,6 +5,7 @@
 // Every stage is a pure function of the previous stage's arrays; nothing that
 // decides an id depends on the order in which atomics arrive.
 #include <stdlib.h>
+#include <string.h>
 #include <algorithm>
 #include <type_traits>
 #include "ap_tiles.hpp"
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(256) void k_seed_thresh(const void *dense, int32_t 
 // diagonal are computed (a launch's tiles below it return at once), and a score of an off-diagonal tile is offered
 // twice: to its row's document against that document's threshold, and to its column's document against that one's.
 // The mirrored pair would have got the same bits: the same products summed over k in the same order.
-template <int WM, int WN, bool RUN, bool SYM>
+template <int DT, int WM, int WN, bool RUN, bool SYM>
 __global__ __launch_bounds__(WM * WN * 64) void k_seed_thresh_big(const void *dense, int32_t dim, int64_t n, const int32_t *node_ids,
                                                                   int64_t row0, int64_t nrows, const float *__restrict__ tau,
                                                                   unsigned long long *__restrict__ buf, int32_t cap,
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_seed_thresh_big(const void *de
         float own = INFINITY;
         if (threadIdx.x < AP_BIG) own = tau[i0 + x];
         else if (mirror && threadIdx.x < 2 * AP_BIG) own = tau[j0 + x];
-        ap_big_gemm_bf16<WM, WN, true>(dense, dim, a_rows, b_rows, a_first, b_first, reinterpret_cast<uint16_t *>(big_lds), acc);
+        ap_big_gemm_bf16<DT, WM, WN, true>(dense, dim, a_rows, b_rows, a_first, b_first, reinterpret_cast<uint16_t *>(big_lds), acc);
         if (threadIdx.x < AP_BIG) { s_tau[x] = own; s_cnt[x] = 0; }
         else if (SYM && threadIdx.x < 2 * AP_BIG) { s_tauc[x] = own; s_cnt[AP_BIG + x] = 0; }
         __syncthreads();
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_seed_thresh_big(const void *de
             s_cnt[x] = 0;
             b_rows[x] = j < n ? (int32_t)j : -1;
         }
-        ap_big_gemm_bf16<WM, WN, false>(dense, dim, a_rows, b_rows, 0, 0, reinterpret_cast<uint16_t *>(big_lds), acc);
+        ap_big_gemm_bf16<DT, WM, WN, false>(dense, dim, a_rows, b_rows, 0, 0, reinterpret_cast<uint16_t *>(big_lds), acc);
         auto to_row = [&](int i, int j, float v) { return v >= s_tau[i] && i0 + i < nrows && j0 + j < n && a_rows[i] != (int32_t)(j0 + j); };
         auto direct = [&](int i, int j, float v) { if (to_row(i, j, v)) ap_seed_append(i0 + i, (int32_t)(j0 + j), v, cnt, buf, cap); };
         ap_big_foreach<WM, WN>(acc, [&](int i, int j, float v) { ap_seed_stage(v >= s_tau[i], i, j, v, stage, W_CAP, nw, direct); });
@@ -322,27 +323,40 @@ __global__ __launch_bounds__(256) void k_select_buf(const unsigned long long *__
     }
 }
 
-// Rows of f32 values rounded to bf16 (columns dim .. kd are zeros) for a sweep on the bf16 matrix cores whose candidates
-// k_rescore_buf scores again.  lost[r] = {|a - a^|, |a|} of row r (a^: a rounded; the differences are exact), each with room for its own
-// rounding and for squares that underflow.  stats: {largest |a|, largest |a - a^|, sum of |a|}, as float bits, zero at the start (a NaN or an
-// infinity among the values ends up in the first).  A wave a row.
+// The largest |value| of a table, as bits (of a NaN: larger than those of any number), zero at the start.  count is a multiple of 4.
+__global__ __launch_bounds__(256) void k_seed_most(const float *__restrict__ v, int64_t count, uint32_t *__restrict__ most) {
+    uint32_t m = 0;
+    for (int64_t i = (blockIdx.x * (int64_t)256 + threadIdx.x) * 4; i < count; i += (int64_t)gridDim.x * 1024) {
+        const uint4 y = *reinterpret_cast<const uint4 *>(v + i);
+        m = max(m, max(max(y.x & 0x7fffffffu, y.y & 0x7fffffffu), max(y.z & 0x7fffffffu, y.w & 0x7fffffffu)));
+    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(most, m);
+}
+// The power of two that takes values of at most that size below 2^15 (f16 ends at 2^16), from its bits.
+__host__ __device__ static inline int ap_seed_shift(uint32_t most) { return 141 - (int)(most >> 23); }
+// Rows of f32 values times a power of two, rounded to f16 (columns dim .. kd are zeros; what f16 holds with fewer bits than 11 becomes zero) for a sweep on the 16-bit
+// matrix cores whose candidates k_rescore_buf scores again.  lost[r] = {|a - a^|, |a|} of row r, in these units (a^: a rounded; the differences are exact), each with
+// room for its own rounding.  stats: {largest |a|, largest |a - a^|, sum of |a|, largest |value| of the rows as they were}, as float bits, the first
+// three zero at the start (a NaN or an infinity among the values ends up in the first).  A wave a row.
 __global__ __launch_bounds__(256) void k_seed_round(const float *__restrict__ dense, int32_t dim, int64_t n, int32_t kd, uint16_t *__restrict__ rows,
                                                     float2 *__restrict__ lost, uint32_t *__restrict__ stats) {
     __shared__ uint32_t part[2][4];
     __shared__ float total[4];
-    const int lane = threadIdx.x & 63, wave = ap_wave_id();
+    const int lane = threadIdx.x & 63, wave = ap_wave_id(), shift = ap_seed_shift(stats[3]);
     uint32_t most = 0, most_off = 0;
     float sum = 0.f;
     for (int64_t r = blockIdx.x * (int64_t)4 + wave; r < n; r += (int64_t)gridDim.x * 4) {
         float s = 0.f, o = 0.f;
         for (int32_t c = lane * 4; c < kd; c += 256) {
             const float4 y = c < dim ? *reinterpret_cast<const float4 *>(dense + r * dim + c) : make_float4(0.f, 0.f, 0.f, 0.f);   // dim is a multiple of 4
-            const float x[4] = {y.x, y.y, y.z, y.w};
+            const float x[4] = {ldexpf(y.x, shift), ldexpf(y.y, shift), ldexpf(y.z, shift), ldexpf(y.w, shift)};
             uint32_t h[4];
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                h[e] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)x[e]);
-                const float off = x[e] - __uint_as_float(h[e] << 16);
+                const _Float16 f = fabsf(x[e]) < 0x1p-14f ? (_Float16)0.f : (_Float16)x[e];
+                h[e] = (uint32_t)__builtin_bit_cast(uint16_t, f);
+                const float off = x[e] - (float)f;
                 s = fmaf(x[e], x[e], s);
                 o = fmaf(off, off, o);
             }
@@ -366,12 +380,12 @@ __global__ __launch_bounds__(256) void k_seed_round(const float *__restrict__ de
 // The exact top-K out of candidates whose scores are those of rounded rows.  With a^ for a rounded,  a b - a^ b^ = (a - a^) b + a^ (b - b^),
 // so a row's scores are off by at most  slack = |a - a^| max|b| + |a^| max|b - b^|  and what the sums of both products round (dim 2^-22 |a| max|b|
 // for the two).  With t the K-th best score of the rounded rows, a document of the exact top-K has one of at least t - 2 slack: those
-// candidates (the band; some 1.7 K of them) are scored again in f32, one a lane, as a chain of fused multiply-adds in ascending order of the
+// candidates (the band; some 1.1 K of them) are scored again in f32, one a lane, as a chain of fused multiply-adds in ascending order of the
 // columns: what v_mfma_f32_32x32x2_f32 computes, so these are the bits of k_seed_scores and k_seed_thresh.  A row goes to the
 // exact path if the band reaches below tau (where candidates are missing), or holds more than AP_BAND.
 // What bounds it: the band's rows, gathered from all over the corpus.  A wave's candidates come in chunks of 32 columns, eight lanes a row (128 consecutive
-// bytes), through its own part of the LDS, the next chunk's loads in flight while one is summed: 15.2 ms for 100,000 rows of 768 columns
-// and K = 128 (some 71 GB at 4.7 TB/s).
+// bytes), through its own part of the LDS, the next chunk's loads in flight while one is summed: 9.8 ms for 100,000 rows of 768 columns
+// and K = 128 (some 45 GB at 4.6 TB/s); with rows rounded to bf16, whose slack is eight times as wide and whose band 1.7 K, 15.2.
 #define AP_BAND 1024
 __device__ __forceinline__ float ap_seed_slack(float2 a, const uint32_t *stats, int32_t dim) {
     const float nmax = __uint_as_float(stats[0]), emax = __uint_as_float(stats[1]);
@@ -522,9 +536,9 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
 // a row expects some 6 K candidates (less than half the buffer).  Such a tau is not a guaranteed lower bound of the row's K-th best: a row
 // that ends up with fewer than K candidates (hardly any) or more than cap is redone by the exact path,
 // like an overflowing row of the one-sided sweep.  The lists are the exact ones either way.
-// rounded (f32 rows): thresholds and sweep take the rows rounded to bf16, at eight times the matrix rate, and the few candidates that the
+// rounded (f32 rows): thresholds and sweep take the rows rounded to f16, at eight times the matrix rate, and the few candidates that the
 // rounding leaves open are scored in f32 (k_rescore_buf).  The lists are the same bits.  100,000 rows of 768 columns, K = 128: 82.7 ms with
-// f32 products (71 of them the sweep), 29.5 ms rounded (9.4 the sweep); 96 columns: 23.4 and 11.5 ms.
+// f32 products (71 of them the sweep), 23 ms rounded (9.4 the sweep); 96 columns: 23.4 and 11.5 ms.
 // *done = false (and AP_OK): not applicable here (shape, memory; rounded: norms that differ too much, or rows too much alike for the
 // rounding to tell them apart, which a sample of rows says before the sweep); the caller takes the next sweep.  Rows with a mean cosine of 0.8,
 // 100,000 x 768, K = 128: 84.5 ms, the f32 sweep alone 83.8, and 100 with the rounded sweep in front of it.
@@ -533,7 +547,7 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
 // own time no longer counts, and an eighth (a half) may be open.
 static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, int32_t *out_ids, float *out_sc, hipStream_t st, bool *done) {
     *done = false;
-    const bool big = rounded || ix->dtype == AP_BF16;  // bf16 rows: 256x256 tiles; f32 rows: 128x128 tiles
+    const bool big = rounded || ix->dtype == AP_BF16;  // 16-bit rows: 256x256 tiles; f32 rows: 128x128 tiles
     const int64_t E = big ? AP_BIG : AP_TILE;
     const int64_t n = ix->docs.n, T = n / E;
     const int32_t dim = rounded ? (ix->docs.dim + AP_BK16 - 1) / AP_BK16 * AP_BK16 : ix->docs.dim;
@@ -545,9 +559,9 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     if ((double)n * (double)cap * 8.0 > 0.62 * (double)free_b) return AP_OK;
     // Every candidate costs the sweep and the selection (200,000 bf16 documents of 1,024 columns, K = 128: the sweep 45.1 ms with 1,843 a row and a
     // comparison for each side of an element, 40.0 with 781 and one), and 6 K of them
-    // do, from a sample that need not be large: where they are scored again that is three times what the band takes, and a rank of 24 leaves a
-    // row in ten thousand short; where K are enough a rank of 12 leaves one in a million.
-    const double mean = std::min(0.45 * (double)cap, std::max(6.0 * K, (rounded ? 24.0 : 12.0) * (double)n / 4096.0));
+    // do, from a sample that need not be large: a rank of 12 leaves a row in a million short of K.  Where they are scored again 4.5 K are four times
+    // what the band takes, and a rank of 24 leaves a row in a hundred thousand short.
+    const double mean = std::min(0.45 * (double)cap, rounded ? std::max(4.5 * K, 24.0 * (double)n / 4096.0) : std::max(6.0 * K, 12.0 * (double)n / 4096.0));
     // the rounded sweep needs more candidates than K: on a small corpus a rank beyond K
     const int64_t m_max = rounded ? 256 : K;
     int64_t m = std::min<int64_t>(m_max, rounded || mean < 6.0 * K ? 24 : 12);
@@ -559,8 +573,8 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     }
     cs = (cs + AP_TILE - 1) / AP_TILE * AP_TILE;
     if (n < 2 * cs) return AP_OK;
-    // The band takes some 1.7 K candidates, and a row's number of candidates is off by one part in sqrt(m).
-    if (rounded && ((double)m * (double)n / (double)cs < 4.0 * K || (double)n * ((double)cap * 8.0 + (double)dim * 2.0) > 0.75 * (double)free_b)) return AP_OK;
+    // The band takes some 1.1 K candidates, and a row's number of candidates is off by one part in sqrt(m).
+    if (rounded && ((double)m * (double)n / (double)cs < 3.0 * K || (double)n * ((double)cap * 8.0 + (double)dim * 2.0) > 0.75 * (double)free_b)) return AP_OK;
     if (g_ap_debug.seed_buffer_cap > 0) cap = g_ap_debug.seed_buffer_cap;   // forces overflows
     const int64_t RS = 8192;
     float *scratch = nullptr, *tau = nullptr, *tmp_sc = nullptr;
@@ -572,17 +586,21 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     uint32_t *stats = nullptr;
     if (rounded) {
         float got[3] = {0.f, 0.f, 0.f};
+        uint32_t bits[4] = {0u, 0u, 0u, 0u};
         int rr = ap_dev_alloc(&r16, (size_t)n * (size_t)dim);
         if (rr == AP_OK) rr = ap_dev_alloc(&lost, (size_t)n);
-        if (rr == AP_OK) rr = ap_dev_alloc(&stats, 3);
-        if (rr == AP_OK) rr = ap_fill_u32(stats, 3, 0u, st);
+        if (rr == AP_OK) rr = ap_dev_alloc(&stats, 4);
+        if (rr == AP_OK) rr = ap_fill_u32(stats, 4, 0u, st);
         if (rr == AP_OK) {
+            hipLaunchKernelGGL(k_seed_most, dim3(1024), dim3(256), 0, st, static_cast<const float *>(dense), n * ix->docs.dim, stats + 3);
             hipLaunchKernelGGL(k_seed_round, dim3((unsigned)std::min<int64_t>((n + 3) / 4, 2048)), dim3(256), 0, st, static_cast<const float *>(dense),
                                ix->docs.dim, n, dim, r16, lost, stats);
-            if (hipGetLastError() != hipSuccess || hipMemcpyAsync(got, stats, sizeof(got), hipMemcpyDeviceToHost, st) != hipSuccess ||
+            if (hipGetLastError() != hipSuccess || hipMemcpyAsync(bits, stats, sizeof(bits), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 rr = AP_EHIP;
         }
+        memcpy(got, bits, sizeof(got));
+        for (int i = 0; i < 3; i += 2) got[i] = ldexpf(got[i], -ap_seed_shift(bits[3]));   // the norms as they were
         // one row's slack is made with the corpus's largest norms: of use while the others come near them
         if (rr != AP_OK || !(got[0] >= 1e-10f && got[0] <= 1e15f && got[0] <= 4.f * got[2] / (float)n)) {
             void *ptrs[] = {r16, lost, stats};
@@ -610,7 +628,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
         if (rc == AP_OK) {
             hipLaunchKernelGGL(k_seed_spread, dim3(rows / 256), dim3(256), 0, st, ovf + 1, rows, n);
             ix->seed_flops += (unsigned long long)((rows / AP_TILE) * (cs / AP_TILE)) * 2ull * AP_TILE * AP_TILE * (unsigned long long)dim;
-            hipLaunchKernelGGL(k_seed_scores<AP_BF16>, dim3(ap_seed_grid(rows / AP_TILE, cs / AP_TILE)), dim3(256), 0, st, dense, dim, n, ovf + 1, (int64_t)0,
+            hipLaunchKernelGGL(k_seed_scores<AP_F16>, dim3(ap_seed_grid(rows / AP_TILE, cs / AP_TILE)), dim3(256), 0, st, dense, dim, n, ovf + 1, (int64_t)0,
                                (int64_t)rows, (int64_t)0, cs, scratch);
             hipLaunchKernelGGL(k_select_rows, dim3(rows), dim3(256), 0, st, scratch, cs, (int32_t)m, ovf + 1, (int64_t)0, 1, (int64_t)0, (int32_t *)nullptr, tmp_sc);
             hipLaunchKernelGGL(k_seed_open, dim3(rows / 256), dim3(256), 0, st, tmp_sc, rows, (int32_t)m, place, last, ovf + 1, lost, stats, ix->docs.dim, ovf);
@@ -637,7 +655,10 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
             const int64_t nrows = std::min(RS, n - row0);
             dim3 gs(ap_seed_grid((nrows + AP_TILE - 1) / AP_TILE, cs / AP_TILE));
             ix->seed_flops += (unsigned long long)(((nrows + AP_TILE - 1) / AP_TILE) * (cs / AP_TILE)) * 2ull * AP_TILE * AP_TILE * (unsigned long long)dim;
-            if (big)
+            if (rounded)
+                hipLaunchKernelGGL(k_seed_scores<AP_F16>, gs, dim3(256), 0, st, dense, dim, n, (const int32_t *)nullptr, row0, nrows,
+                                   (int64_t)0, cs, scratch);
+            else if (big)
                 hipLaunchKernelGGL(k_seed_scores<AP_BF16>, gs, dim3(256), 0, st, dense, dim, n, (const int32_t *)nullptr, row0, nrows,
                                    (int64_t)0, cs, scratch);
             else
@@ -657,18 +678,19 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
                     (long long)cs, (long long)cap);
         // tiles multiplied: those on and above the diagonal, and the ragged last row and column of tiles
         ix->seed_flops += (unsigned long long)(T * (T + 1) / 2 + (n % E != 0 ? 2 * T + 1 : 0)) * 2ull * (unsigned long long)(E * E) * (unsigned long long)dim;
-        if (big) {
+        auto sweep = [&](auto type) {
+            constexpr int DT = decltype(type)::value;
             const dim3 tb(AP_BIG_WM * AP_BIG_WN * 64);
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, true, true>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<DT, AP_BIG_WM, AP_BIG_WN, true, true>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES);
             if (e == hipSuccess)
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>),
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<DT, AP_BIG_WM, AP_BIG_WN, false, false>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES);
             // the square of full tiles, a slab of 32 row tiles a launch: each XCD keeps four row tiles and walks the column
             // tiles from the slab's own first column on
             for (int64_t s0 = 0; s0 < T && e == hipSuccess; s0 += 32) {
                 const int64_t nrt = std::min<int64_t>(32, T - s0), nct = T - s0;
-                hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, true, true>), dim3(ap_seed_grid(nrt, nct)), tb, AP_BIG_LDS_BYTES, st,
+                hipLaunchKernelGGL((k_seed_thresh_big<DT, AP_BIG_WM, AP_BIG_WN, true, true>), dim3(ap_seed_grid(nrt, nct)), tb, AP_BIG_LDS_BYTES, st,
                                    dense, dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, s0, nrt, s0);
                 e = hipGetLastError();
                 if ((s0 / 32) % 64 == 63) {
@@ -678,13 +700,16 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
             }
             if (e == hipSuccess && n % AP_BIG != 0) {
                 // the ragged last column tile for the full row tiles, and the ragged last rows against every column: one-sided
-                hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>), dim3(ap_seed_grid(T, 1)), tb, AP_BIG_LDS_BYTES, st,
+                hipLaunchKernelGGL((k_seed_thresh_big<DT, AP_BIG_WM, AP_BIG_WN, false, false>), dim3(ap_seed_grid(T, 1)), tb, AP_BIG_LDS_BYTES, st,
                                    dense, dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, (int64_t)0, T, T);
-                hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>), dim3(ap_seed_grid(1, T + 1)), tb, AP_BIG_LDS_BYTES, st,
+                hipLaunchKernelGGL((k_seed_thresh_big<DT, AP_BIG_WM, AP_BIG_WN, false, false>), dim3(ap_seed_grid(1, T + 1)), tb, AP_BIG_LDS_BYTES, st,
                                    dense, dim, n, (const int32_t *)nullptr, (int64_t)0, n, tau, buf, (int32_t)cap, cnt, T, (int64_t)1, (int64_t)0);
                 e = hipGetLastError();
             }
-        } else {
+        };
+        if (rounded) sweep(std::integral_constant<int, AP_F16>());
+        else if (big) sweep(std::integral_constant<int, AP_BF16>());
+        else {
             // f32 rows: the same on 128x128 tiles, a slab of 64 row tiles (eight per XCD) a launch
             for (int64_t s0 = 0; s0 < T && e == hipSuccess; s0 += 64) {
                 const int64_t nrt = std::min<int64_t>(64, T - s0), nct = T - s0, r0 = s0 * AP_TILE;
@@ -841,16 +866,16 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
                 const dim3 gb(ap_seed_grid(nrt, nct));
                 const dim3 tb(AP_BIG_WM * AP_BIG_WN * 64);
                 if (lean) {
-                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, true, false>),
+                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BF16, AP_BIG_WM, AP_BIG_WN, true, false>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES);
                     if (e == hipSuccess)
-                        hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, true, false>), gb, tb, AP_BIG_LDS_BYTES, st, ix->docs.dense, ix->docs.dim, n,
+                        hipLaunchKernelGGL((k_seed_thresh_big<AP_BF16, AP_BIG_WM, AP_BIG_WN, true, false>), gb, tb, AP_BIG_LDS_BYTES, st, ix->docs.dense, ix->docs.dim, n,
                                            node_ids, row0, nrows, tau, buf, (int32_t)cap, cnt, rt0, nrt, ct0);
                 } else {
-                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>),
+                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seed_thresh_big<AP_BF16, AP_BIG_WM, AP_BIG_WN, false, false>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES);
                     if (e == hipSuccess)
-                        hipLaunchKernelGGL((k_seed_thresh_big<AP_BIG_WM, AP_BIG_WN, false, false>), gb, tb, AP_BIG_LDS_BYTES, st, ix->docs.dense, ix->docs.dim, n,
+                        hipLaunchKernelGGL((k_seed_thresh_big<AP_BF16, AP_BIG_WM, AP_BIG_WN, false, false>), gb, tb, AP_BIG_LDS_BYTES, st, ix->docs.dense, ix->docs.dim, n,
                                            node_ids, row0, nrows, tau, buf, (int32_t)cap, cnt, rt0, nrt, ct0);
                 }
                 if (e == hipSuccess) e = hipGetLastError();

@@ -104,6 +104,13 @@ __device__ __forceinline__ void ap_tile_gemm(const void *dense, int32_t dim, con
 // lane l feeds A[l%32][8*(l/32) .. +8] and B[8*(l/32) .. +8][l%32] per 16-wide
 // step; the result layout is that of the f32 instruction.
 typedef __bf16 ap_bf16x8 __attribute__((ext_vector_type(8)));
+// f16 rows (f32 rows rounded for a sweep of the construction) take the same path with v_mfma_f32_32x32x16_f16: DT = AP_F16.
+typedef _Float16 ap_f16x8 __attribute__((ext_vector_type(8)));
+#define AP_F16 2
+template <int DT> __device__ __forceinline__ ap_f32x16 ap_mfma16(ap_bf16x8 a, ap_bf16x8 b, ap_f32x16 c) {
+    if constexpr (DT == AP_F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(ap_f16x8, a), __builtin_bit_cast(ap_f16x8, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 #define AP_BK16 64
 #define AP_LDS_STRIDE16 (AP_BK16 + 8)   // in bf16 elements: 144-byte rows keep the 16-byte operand reads spread over the banks
 
@@ -130,6 +137,7 @@ __device__ __forceinline__ void ap_tile_store_bf16(const uint4 v[AP_NP16], const
             (row[pass] >= 0 && inside) ? v[pass] : make_uint4(0, 0, 0, 0);
 }
 
+template <int DT>
 __device__ __forceinline__ void ap_tile_gemm_bf16(const void *dense, int32_t dim, const int32_t *a_rows, const int32_t *b_rows,
                                                   uint16_t *lA, uint16_t *lB, ap_f32x16 acc[2][2]) {
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
@@ -170,10 +178,10 @@ __device__ __forceinline__ void ap_tile_gemm_bf16(const void *dense, int32_t dim
             const ap_bf16x8 a1 = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(pa1 + kk));
             const ap_bf16x8 b0 = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(pb0 + kk));
             const ap_bf16x8 b1 = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(pb1 + kk));
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1][1], 0, 0, 0);
+            acc[0][0] = ap_mfma16<DT>(a0, b0, acc[0][0]);
+            acc[0][1] = ap_mfma16<DT>(a0, b1, acc[0][1]);
+            acc[1][0] = ap_mfma16<DT>(a1, b0, acc[1][0]);
+            acc[1][1] = ap_mfma16<DT>(a1, b1, acc[1][1]);
         }
     }
 }
@@ -236,7 +244,7 @@ __device__ __forceinline__ void ap_big_store_run(const ap_u32x4 (&v)[NP], uint16
 // inside the corpus, and dim is a multiple of 64 -- the case of every tile of a sweep but those on its edges.  Then an
 // address is a uniform base plus a 32-bit offset that is fixed for the whole product, nothing needs zeroing, and a
 // chunk costs no vector instruction besides its loads, stores and MFMAs.
-template <int WM, int WN, bool RUN>
+template <int DT, int WM, int WN, bool RUN>
 __device__ __forceinline__ void ap_big_gemm_bf16(const void *dense, int32_t dim, const int32_t *a_rows, const int32_t *b_rows,
                                                  int32_t a_first, int32_t b_first, uint16_t *lds,
                                                  ap_f32x16 acc[ApBig<WM, WN>::FA][ApBig<WM, WN>::FB]) {
@@ -303,7 +311,7 @@ _Pragma("unroll")                                                               
 _Pragma("unroll")                                                                                                                                     \
             for (int a = 0; a < FA; a++)                                                                                                              \
 _Pragma("unroll")                                                                                                                                     \
-                for (int b = 0; b < FB; b++) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);                   \
+                for (int b = 0; b < FB; b++) acc[a][b] = ap_mfma16<DT>(fa[a], fb[b], acc[a][b]);                                                     \
         }                                                                                                                                             \
         __syncthreads();                                                                                                                              \
     } while (0)
@@ -336,16 +344,16 @@ __device__ __forceinline__ void ap_big_foreach(const ap_f32x16 acc[ApBig<WM, WN>
 
 // LDS bytes the tile product needs (both operands) for a storage type.
 template <int DT> struct ApTileLds {
-    static constexpr int BYTES = DT == AP_BF16 ? 2 * AP_TILE * AP_LDS_STRIDE16 * 2 : 2 * AP_TILE * AP_LDS_STRIDE * 4;
+    static constexpr int BYTES = DT != AP_F32 ? 2 * AP_TILE * AP_LDS_STRIDE16 * 2 : 2 * AP_TILE * AP_LDS_STRIDE * 4;
 };
 
 // Tile product for storage type DT out of one raw LDS area of ApTileLds<DT>::BYTES bytes.
 template <int DT>
 __device__ __forceinline__ void ap_tile_product(const void *dense, int32_t dim, const int32_t *a_rows, const int32_t *b_rows,
                                                 void *lds, ap_f32x16 acc[2][2]) {
-    if (DT == AP_BF16) {
+    if constexpr (DT != AP_F32) {
         uint16_t *l = static_cast<uint16_t *>(lds);
-        ap_tile_gemm_bf16(dense, dim, a_rows, b_rows, l, l + AP_TILE * AP_LDS_STRIDE16, acc);
+        ap_tile_gemm_bf16<DT>(dense, dim, a_rows, b_rows, l, l + AP_TILE * AP_LDS_STRIDE16, acc);
     } else {
         float *l = static_cast<float *>(lds);
         ap_tile_gemm<AP_F32>(dense, dim, a_rows, b_rows, l, l + AP_TILE * AP_LDS_STRIDE, acc);
