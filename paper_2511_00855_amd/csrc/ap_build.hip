@@ -384,8 +384,15 @@ __global__ __launch_bounds__(256) void k_seed_round(const float *__restrict__ de
 // columns: what v_mfma_f32_32x32x2_f32 computes, so these are the bits of k_seed_scores and k_seed_thresh.  A row goes to the
 // exact path if the band reaches below tau (where candidates are missing), or holds more than AP_BAND.
 // What bounds it: the band's rows, gathered from all over the corpus.  A wave's candidates come in chunks of 32 columns, eight lanes a row (128 consecutive
-// bytes), through its own part of the LDS, the next chunk's loads in flight while one is summed: 9.8 ms for 100,000 rows of 768 columns
+// bytes), through its own part of the LDS, the next chunk's loads in flight while one is summed; of few candidates (no more than 8 or 16 a wave) eight or four
+// chunks come at a time, as many bytes on their way as of many: 9.8 ms for 100,000 rows of 768 columns
 // and K = 128 (some 45 GB at 4.6 TB/s); with rows rounded to bf16, whose slack is eight times as wide and whose band 1.7 K, 15.2.
+// slack != NULL: what a construction needs of the lists, which is less: their members, which of them are the first `top`, the K-th score, and the
+// others' scores within slack[r] of what is given.  With t the K-th best score of the rounded rows a candidate beyond t + 2 slack is one of
+// the K best, whatever the rounding took, and with t' the top-th best one beyond t' + 2 slack is among the first `top`, one below t' - 2 slack is not: scored
+// again are only the candidates within 2 slack of t or of t' (some twenty of 128), the others keep the rounded score.  Sorted together the
+// two kinds fall on the right sides of both lines: an exact score above a line's true place lies at most slack above t, or at least slack below.
+// 9.8 -> 4.4 ms of the 100,000 x 768 below (5.8 with one chunk of a row at a time).
 #define AP_BAND 1024
 __device__ __forceinline__ float ap_seed_slack(float2 a, const uint32_t *stats, int32_t dim) {
     const float nmax = __uint_as_float(stats[0]), emax = __uint_as_float(stats[1]);
@@ -393,15 +400,15 @@ __device__ __forceinline__ float ap_seed_slack(float2 a, const uint32_t *stats, 
 }
 __global__ __launch_bounds__(256) void k_rescore_buf(const float *__restrict__ dense, int32_t dim, const unsigned long long *__restrict__ buf, int32_t cap,
                                                      const int32_t *__restrict__ cnt, const float *__restrict__ tau, const float2 *__restrict__ lost,
-                                                     const uint32_t *__restrict__ stats, int32_t K, int32_t *__restrict__ out_ids,
+                                                     const uint32_t *__restrict__ stats, int32_t K, int32_t top, float *__restrict__ slack, int32_t *__restrict__ out_ids,
                                                      float *__restrict__ out_sc, int32_t *__restrict__ n_overflow, int32_t *__restrict__ overflow_rows) {
     __shared__ uint64_t keys[AP_BAND];
     __shared__ __attribute__((aligned(16))) float s_a[1024];        // f32 rows have at most 1,024 columns
     __shared__ __attribute__((aligned(16))) float stage[4][64 * AP_LDS_STRIDE];
     __shared__ int32_t misc[4];
     __shared__ uint64_t pre;
-    __shared__ uint32_t s_least;
-    __shared__ int32_t s_band;
+    __shared__ uint32_t s_least, s_top;
+    __shared__ int32_t s_band, s_sure;
     // while the band is looked for: the candidates (as many as fit, which is all of them but for a forced capacity), the K best, a histogram
     uint64_t *all = reinterpret_cast<uint64_t *>(stage[0]);
     constexpr int32_t ALL = 4 * 64 * AP_LDS_STRIDE / 2;
@@ -410,72 +417,102 @@ __global__ __launch_bounds__(256) void k_rescore_buf(const float *__restrict__ d
     const int64_t r = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
     const int32_t c = cnt[r];
+    if (slack && threadIdx.x == 0) slack[r] = 0.f;   // rows left to the caller get exact scores
     if (c > cap || c < K) {   // uniform for the block
         if (threadIdx.x == 0) overflow_rows[atomicAdd(n_overflow, 1)] = (int32_t)r;
         return;
     }
-    if (threadIdx.x == 0) { s_least = 0xffffffffu; s_band = 0; }
+    if (threadIdx.x == 0) { s_least = 0xffffffffu; s_top = 0xffffffffu; s_band = 0; s_sure = 0; }
     const unsigned long long *row = buf + r * (int64_t)cap;
     for (int32_t j = threadIdx.x; j < c && j < ALL; j += 256) all[j] = row[j];
     auto key_of = [&](int64_t j) -> uint64_t { return j < ALL ? all[j] : row[j]; };
     __syncthreads();
     const int32_t got = ap_radix_select_keys(key_of, c, c, K, hist, sel, misc, &pre);
-    if ((int32_t)threadIdx.x < got) atomicMin(&s_least, (uint32_t)(sel[threadIdx.x] >> 32));
+    if ((int32_t)threadIdx.x < got) {
+        const uint64_t own = sel[threadIdx.x];
+        atomicMin(&s_least, (uint32_t)(own >> 32));
+        if (slack && top < K) {   // uniform
+            int32_t rank = 0;
+            for (int32_t j = 0; j < got; j++) rank += sel[j] > own ? 1 : 0;
+            if (rank == top - 1) s_top = (uint32_t)(own >> 32);
+        }
+    }
     for (int32_t x = threadIdx.x * 4; x < 1024; x += 1024)
         *reinterpret_cast<float4 *>(&s_a[x]) = x < dim ? *reinterpret_cast<const float4 *>(dense + r * dim + x) : make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    const float least = ap_ord2f(s_least) - 2.f * ap_seed_slack(lost[r], stats, dim);
+    const float off = ap_seed_slack(lost[r], stats, dim), least = ap_ord2f(s_least) - 2.f * off, most = slack ? ap_ord2f(s_least) + 2.f * off : INFINITY;
+    const float t_top = slack && s_top != 0xffffffffu ? ap_ord2f(s_top) : -INFINITY;
     if (least >= tau[r])
         for (int32_t j = threadIdx.x; j < c; j += 256) {
             const uint64_t key = key_of(j);
-            if (ap_key_score(key) >= least) {
-                const int32_t at = atomicAdd(&s_band, 1);
-                if (at < AP_BAND) keys[at] = key;
+            const float x = ap_key_score(key);
+            if (x >= least) {
+                const bool open = !(x > most) || (x >= t_top - 2.f * off && x <= t_top + 2.f * off);
+                const int32_t at = open ? atomicAdd(&s_band, 1) : AP_BAND - 1 - atomicAdd(&s_sure, 1);
+                if (at >= 0 && at < AP_BAND) keys[at] = key;
             }
         }
     __syncthreads();
-    const int32_t nb = s_band;   // at least K, or 0
-    if (nb == 0 || nb > AP_BAND) {   // uniform
+    const int32_t nb = s_band, sure = s_sure, all_n = nb + sure;   // all_n: at least K, or 0; sure: fewer than K
+    if (nb == 0 || all_n > AP_BAND) {   // uniform
         if (threadIdx.x == 0) overflow_rows[atomicAdd(n_overflow, 1)] = (int32_t)r;
         return;
     }
     int32_t full = 256;
-    while (full < nb) full <<= 1;
-    for (int32_t x = nb + (int32_t)threadIdx.x; x < full; x += 256) keys[x] = 0;
+    while (full < all_n) full <<= 1;
+    if (slack) {   // uniform: what keeps its score lies behind the others from here on
+        const uint64_t key = (int32_t)threadIdx.x < sure ? keys[AP_BAND - 1 - threadIdx.x] : 0ull;
+        const int scale = -2 * ap_seed_shift(stats[3]);
+        __syncthreads();
+        if ((int32_t)threadIdx.x < sure) keys[nb + threadIdx.x] = ap_make_key(ldexpf(ap_key_score(key), scale), ap_key_id(key), 1u);
+        if (threadIdx.x == 0) slack[r] = 1.0001f * ldexpf(off, scale);
+        __syncthreads();
+    }
+    for (int32_t x = all_n + (int32_t)threadIdx.x; x < full; x += 256) keys[x] = 0;
     const int32_t share = (nb + 3) >> 2, w1 = min(nb, (wave + 1) * share);
     float *st = stage[wave];
-    for (int32_t p0 = wave * share; p0 < w1; p0 += 64) {
-        const int32_t m = min(64, w1 - p0);
+    // m <= 64 / SUB candidates from p0 on, SUB chunks of their rows at a time
+    auto score = [&](int32_t p0, int32_t m, auto sub) {
+        constexpr int SUB = decltype(sub)::value, G = 8 / SUB;   // groups of eight rows
         const int col = (lane & 7) * 4;
-        const float *src[8];
+        const float *src[G];
         float4 v[8];
 #pragma unroll
-        for (int p = 0; p < 8; p++) src[p] = dense + (int64_t)ap_key_id(keys[p0 + min((lane >> 3) + 8 * p, m - 1)]) * dim;
+        for (int g = 0; g < G; g++) src[g] = dense + (int64_t)ap_key_id(keys[p0 + min((lane >> 3) + 8 * g, m - 1)]) * dim;
         const int32_t id = ap_key_id(keys[p0 + min(lane, m - 1)]);
+        auto load = [&](int32_t k0) {
 #pragma unroll
-        for (int p = 0; p < 8; p++)
-            if (8 * p < m) v[p] = *reinterpret_cast<const float4 *>(src[p] + min(col, dim - 4));
+            for (int p = 0; p < 8; p++)
+                if (8 * (p % G) < m) v[p] = *reinterpret_cast<const float4 *>(src[p % G] + min(k0 + 32 * (p / G) + col, dim - 4));
+        };
+        load(0);
         float acc = 0.f;
-        for (int32_t k0 = 0; k0 < dim; k0 += 32) {
-            const bool inside = k0 + col < dim;   // s_a is zero where the columns end: any finite value does
+        for (int32_t k0 = 0; k0 < dim; k0 += 32 * SUB) {
             ap_wave_sync();
 #pragma unroll
             for (int p = 0; p < 8; p++)
-                if (8 * p < m) {
+                if (8 * (p % G) < m) {
+                    const bool inside = k0 + 32 * (p / G) + col < dim;   // s_a is zero where the columns end: any finite value does
                     float *d = st + ((lane >> 3) + 8 * p) * AP_LDS_STRIDE + col;
                     d[0] = inside ? v[p].x : 0.f; d[1] = inside ? v[p].y : 0.f; d[2] = inside ? v[p].z : 0.f; d[3] = inside ? v[p].w : 0.f;
                 }
-            if (k0 + 32 < dim) {
-#pragma unroll
-                for (int p = 0; p < 8; p++)
-                    if (8 * p < m) v[p] = *reinterpret_cast<const float4 *>(src[p] + min(k0 + 32 + col, dim - 4));
-            }
+            if (k0 + 32 * SUB < dim) load(k0 + 32 * SUB);
             ap_wave_sync();
-            const float *mine = st + min(lane, m - 1) * AP_LDS_STRIDE;
 #pragma unroll
-            for (int e = 0; e < 32; e++) acc = fmaf(s_a[k0 + e], mine[e], acc);
+            for (int q = 0; q < SUB; q++) {
+                const float *mine = st + (8 * G * q + min(lane, m - 1)) * AP_LDS_STRIDE;
+#pragma unroll
+                for (int e = 0; e < 32; e++) acc = fmaf(s_a[k0 + 32 * q + e], mine[e], acc);
+            }
         }
         if (lane < m) keys[p0 + lane] = ap_make_key(acc, id, 1u);
+    };
+    if (share <= 8) {   // uniform for the block
+        if (wave * share < w1) score(wave * share, w1 - wave * share, std::integral_constant<int, 8>());
+    } else if (share <= 16) {
+        if (wave * share < w1) score(wave * share, w1 - wave * share, std::integral_constant<int, 4>());
+    } else {
+        for (int32_t p0 = wave * share; p0 < w1; p0 += 64) score(p0, min(64, w1 - p0), std::integral_constant<int, 1>());
     }
     ap_bitonic_desc(keys, full);
     for (int32_t i = threadIdx.x; i < K; i += 256) {
@@ -545,7 +582,7 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
 // Where the line lies: a row left open takes the exact path, 5 us of 100,000 columns and 768 (1 us of 60,000 and 384), so that a tenth of them is
 // what the rounding saves; corpora whose next path is the exact one for all rows (below 32,768 documents) can leave a quarter open.  Once the sweep is over its
 // own time no longer counts, and an eighth (a half) may be open.
-static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, int32_t *out_ids, float *out_sc, hipStream_t st, bool *done) {
+static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, int32_t *out_ids, float *out_sc, hipStream_t st, ApSeedRelax *relax, bool *done) {
     *done = false;
     const bool big = rounded || ix->dtype == AP_BF16;  // 16-bit rows: 256x256 tiles; f32 rows: 128x128 tiles
     const int64_t E = big ? AP_BIG : AP_TILE;
@@ -584,6 +621,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     uint16_t *r16 = nullptr;
     float2 *lost = nullptr;
     uint32_t *stats = nullptr;
+    float *slack = nullptr;
     if (rounded) {
         float got[3] = {0.f, 0.f, 0.f};
         uint32_t bits[4] = {0u, 0u, 0u, 0u};
@@ -641,9 +679,10 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     }
     if (rc == AP_OK && !alike) rc = ap_dev_alloc(&tau, (size_t)n);
     if (rc == AP_OK && !alike) rc = ap_dev_alloc(&cnt, (size_t)n);
+    if (rc == AP_OK && !alike && rounded && relax) rc = ap_dev_alloc(&slack, (size_t)n);
     const bool sweep = rc == AP_OK && e == hipSuccess && !alike;
     if (sweep && ap_dev_alloc(&buf, (size_t)n * (size_t)cap) != AP_OK) {   // no room for the buffers after all: the next sweep
-        void *ptrs[] = {scratch, tau, tmp_sc, cnt, ovf, r16, lost, stats};
+        void *ptrs[] = {scratch, tau, tmp_sc, cnt, ovf, r16, lost, stats, slack};
         for (void *q : ptrs) if (q) (void)hipFree(q);
         (void)hipGetLastError();
         ap_set_error("%s", "");
@@ -730,7 +769,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
         if (e == hipSuccess) {
             if (rounded)
                 hipLaunchKernelGGL(k_rescore_buf, dim3((unsigned)n), dim3(256), 0, st, static_cast<const float *>(ix->docs.dense), ix->docs.dim, buf, (int32_t)cap,
-                                   cnt, tau, lost, stats, K, out_ids, out_sc, ovf, ovf + 1);
+                                   cnt, tau, lost, stats, K, relax ? relax->top : 0, slack, out_ids, out_sc, ovf, ovf + 1);
             else
                 hipLaunchKernelGGL(k_select_buf, dim3((unsigned)n), dim3(256), 0, st, buf, (int32_t)cap, cnt, K, (int32_t)std::min<int64_t>(K, n - 1),
                                    (int64_t)0, out_ids, out_sc, ovf, ovf + 1);
@@ -761,6 +800,8 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
     }
     void *ptrs[] = {scratch, tau, tmp_sc, buf, cnt, ovf, ex_scratch, re_ids, re_sc, r16, lost, stats};
     for (void *q : ptrs) if (q) (void)hipFree(q);
+    if (slack && rc == AP_OK && e == hipSuccess && !alike) relax->slack = slack;
+    else if (slack) (void)hipFree(slack);
     if (rc == AP_ENOMEM && rounded) {   // the f32 sweep takes less: no rounded rows, and hardly any score rows
         (void)hipGetLastError();
         ap_set_error("%s", "");
@@ -785,7 +826,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
 // number of candidates) is redone by the exact path.  Whole corpora take the
 // symmetric sweeps where they apply.
 int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, int32_t K, int32_t *out_ids,
-                         float *out_sc, hipStream_t st) {
+                         float *out_sc, hipStream_t st, ApSeedRelax *relax) {
     const int64_t n = ix->docs.n;
     int64_t cs = std::max<int64_t>(16384, (n + 63) / 64);
     if (g_ap_debug.seed_sample_cols > 0) cs = std::max<int64_t>(K + 1, g_ap_debug.seed_sample_cols);
@@ -799,7 +840,7 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
     ix->seed_bf16 = ix->dtype == AP_BF16 ? 1 : 0;
     if (whole && ix->dtype == AP_F32 && n < 2 * cs && n >= AP_ROUNDED_MIN) {
         bool done = false;
-        rc = ap_seed_knn_symmetric(ix, K, true, out_ids, out_sc, st, &done);
+        rc = ap_seed_knn_symmetric(ix, K, true, out_ids, out_sc, st, relax, &done);
         if (rc != AP_OK || done) return rc;
     }
     if (n < 2 * cs) {
@@ -814,7 +855,7 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
     if (whole) {   // the symmetric sweep where it applies
         bool done = false;
         for (int rounded = ix->dtype == AP_F32 ? 1 : 0; rounded >= 0; rounded--) {
-            rc = ap_seed_knn_symmetric(ix, K, rounded != 0, out_ids, out_sc, st, &done);
+            rc = ap_seed_knn_symmetric(ix, K, rounded != 0, out_ids, out_sc, st, relax, &done);
             if (rc != AP_OK || done) return rc;
         }
     }
@@ -962,8 +1003,8 @@ struct ApRefineHints {
     // [nn]: no document outside the node's exact dense seed list has a dense part above this (the seed stage's K-th score, in
     // that stage's arithmetic); -inf where the seed list holds every other document
     const float *tau;
-    // first round only: the scores the seed stage gave the lists' members
-    const float *seed_sc;
+    // first round only: the scores the seed stage gave the lists' members, and how far they may be off (NULL: they are exact)
+    const float *seed_sc, *seed_slack;
     // later rounds: the fused scores of the lists, and per node one bit for each of the first S list entries, set if the entry
     // was among the first S of the node's list one round ago
     const float *knn_sc;
@@ -1359,10 +1400,10 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
         // scores the first round has) or its K-th score (documents outside it), plus eps |u||w|: each of the two differently
         // ordered fp32 sums is off by at most dim 2^-24 |u||w| from the exact product; twice that for each is allowed.
         const float un = __uint_as_float(meta[u].z), eps = 4.f * (float)D.dim * 5.9604645e-8f;
-        const float tau = hint.tau[u];
+        const float tau = hint.tau[u], seed_off = hint.seed_slack ? hint.seed_slack[u] : 0.f;
         auto bound = [&](int32_t t, float &bd, float &bf) {   // upper bounds of the dense part and of the fused score
             const float nb = un * comp[0][t] * 1.0001f, ss = comp[1][t], sf = comp[2][t];
-            const float most = t < n_own ? hint.seed_sc[u * K + t] : tau;   // n_own is 0 in later rounds
+            const float most = t < n_own ? hint.seed_sc[u * K + t] + seed_off : tau;   // n_own is 0 in later rounds
             bd = most - most == 0.f ? fminf(nb, most + eps * nb) : nb;
             const float lift = wd >= 0.f ? wd * bd : -wd * nb;
             bf = fmaf(wf, sf, ws * ss) + lift + 1e-5f * (fabsf(ws * ss) + fabsf(wf * sf) + fabsf(wd) * nb);
@@ -1378,7 +1419,7 @@ __global__ __launch_bounds__(512, 4) void k_refine(ApVecs D, const uint2 *__rest
             float lo = INFINITY;
             if (lane < P) {
                 const int32_t v = knn[u * K + lane];
-                lo = v >= 0 ? hint.seed_sc[u * K + lane] - eps * un * __uint_as_float(meta[v].z) * 1.0001f : -INFINITY;
+                lo = v >= 0 ? hint.seed_sc[u * K + lane] - seed_off - eps * un * __uint_as_float(meta[v].z) * 1.0001f : -INFINITY;
             }
             for (int o = 32; o > 0; o >>= 1) lo = fminf(lo, __shfl_xor(lo, o, 64));
             if (lane == 0) s_last[0] = lo;
@@ -1638,10 +1679,10 @@ int ap_refine_round(const ap_index *ix, int32_t K, int32_t S, int32_t P, const i
     return AP_OK;
 }
 
-// The refinement rounds of a construction: from the exact dense seed lists (ids[0], sc[0]) of all n = ix->docs.n documents
+// The refinement rounds of a construction: from the exact dense seed lists (ids[0], sc[0]; seed_slack != NULL: their scores but the K-th are within that) of all n = ix->docs.n documents
 // and empty per-path lists (spi[0], sps[0]).  Returns in *cur which of the two buffers holds the result.
 int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
-                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st) {
+                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st, const float *seed_slack) {
     const int64_t n = ix->docs.n;
     *cur = 0;
     if (rounds <= 0) return AP_OK;
@@ -1657,8 +1698,8 @@ int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, i
     ix->packed_lists = pk.rec != nullptr;
     for (int32_t t = 0; t < rounds && rc == AP_OK; t++) {
         const int c = *cur;
-        const ApRefineHints hint = t == 0 ? ApRefineHints{tau, sc[c], nullptr, nullptr, known[0], pk.rec, pk.at}
-                                          : ApRefineHints{tau, nullptr, sc[c], known[(t - 1) & 1], known[t & 1], pk.rec, pk.at};
+        const ApRefineHints hint = t == 0 ? ApRefineHints{tau, sc[c], seed_slack, nullptr, nullptr, known[0], pk.rec, pk.at}
+                                          : ApRefineHints{tau, nullptr, nullptr, sc[c], known[(t - 1) & 1], known[t & 1], pk.rec, pk.at};
         rc = ap_refine_round(ix, K, S, P, ids[c], spi[c], sps[c], nullptr, n, ids[1 - c], sc[1 - c], spi[1 - c], sps[1 - c], hint, st);
         *cur = 1 - c;
     }
@@ -1675,7 +1716,7 @@ extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t
     if (!node_ids) nn = ix->docs.n;
     if (nn <= 0) return AP_OK;
     return ap_refine_round(ix, K, S, P, knn_ids, sp_ids, sp_sc, node_ids, nn, out_ids, out_sc, out_sp_ids, out_sp_sc,
-                           ApRefineHints{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr}, (hipStream_t)stream);
+                           ApRefineHints{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr}, (hipStream_t)stream);
 }
 
 // =================================================================== S4: neighbourhood similarities
@@ -2825,8 +2866,9 @@ struct BuildBufs {
     int32_t *spi[2] = {nullptr, nullptr};
     float *sps[2] = {nullptr, nullptr};
     int32_t *se = nullptr, *sorted = nullptr;
+    float *slack = nullptr;   // of the seed lists' scores
     void release() {
-        void *p[] = {knn[0], knn[1], knn_sc[0], knn_sc[1], spi[0], spi[1], sps[0], sps[1], se, sorted};
+        void *p[] = {slack, knn[0], knn[1], knn_sc[0], knn_sc[1], spi[0], spi[1], sps[0], sps[1], se, sorted};
         for (void *x : p) if (x) (void)hipFree(x);
         *this = BuildBufs();
     }
@@ -2853,13 +2895,17 @@ static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
     AP_TRY(ap_dev_alloc(&b.sorted, (size_t)n * K));
     AP_TRY(ap_alloc_graph(ix));
     ap_progress("ingest done; seed lists of %lld documents", (long long)n);
-    AP_TRY(ap_seed_knn_impl(ix, nullptr, n, K, b.knn[0], b.knn_sc[0], st));
+    // the rounds read the lists' members, the first nd_sample of them as a set, and bounds of their scores
+    ApSeedRelax relax;
+    relax.top = std::min(K, p.nd_sample);
+    AP_TRY(ap_seed_knn_impl(ix, nullptr, n, K, b.knn[0], b.knn_sc[0], st, p.nd_rounds > 0 ? &relax : nullptr));
+    b.slack = relax.slack;
     ap_progress("seed lists done; %d refinement rounds, pruning, assembly", p.nd_rounds);
     AP_CHECK_HIP(mark(2));
     AP_TRY(ap_fill_u32(b.spi[0], (size_t)3 * n * P, 0xffffffffu, st));          // id -1
     AP_TRY(ap_fill_u32(b.sps[0], (size_t)3 * n * P, 0xff800000u, st));          // -inf
     int cur = 0;
-    AP_TRY(ap_refine_rounds(ix, p.nd_rounds, K, p.nd_sample, P, b.knn, b.knn_sc, b.spi, b.sps, &cur, st));
+    AP_TRY(ap_refine_rounds(ix, p.nd_rounds, K, p.nd_sample, P, b.knn, b.knn_sc, b.spi, b.sps, &cur, st, b.slack));
     if (p.nd_rounds == 0) AP_TRY(ap_rescore_lists(ix, n, K, b.knn[cur], b.knn_sc[cur], st));
     AP_CHECK_HIP(mark(3));
     AP_TRY(ap_prune_impl(ix, K, R, b.knn[cur], b.knn_sc[cur], nullptr, n, nullptr, nullptr, b.sorted, b.se, ix->kw, ix->kw_count,

@@ -181,15 +181,18 @@ int ap_count_terms(const int32_t *idx, const float *tf, int64_t nnz, int32_t *df
 int ap_alloc_graph(ap_index *ix);
 int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
 // stage bodies shared by the whole build and by insertion (ap_build.hip)
+// Seed lists whose scores may be off, but the K-th, and whose order may be, but for which of them come first: in: `top` of them; out: by
+// how much the scores may be off (an allocation of a float per document that the caller frees), NULL: not at all
+struct ApSeedRelax { int32_t top = 0; float *slack = nullptr; };
 int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, int32_t K, int32_t *out_ids, float *out_sc,
-                     hipStream_t st);
+                     hipStream_t st, ApSeedRelax *relax = nullptr);
 int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_ids, const float *knn_sc, const int32_t *node_ids,
                   int64_t nn, float *pm_out, int32_t *count, int32_t *sorted_ids, int32_t *se, int32_t *ke, int32_t *ke_count,
                   int32_t *flag, hipStream_t st);
 int ap_assemble_impl(const ap_index *ix, int32_t R, int32_t K, int32_t P, const int32_t *se, const int32_t *sorted_ids,
                      const int32_t *sp_ids, int32_t *out_graph, hipStream_t st);
 int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
-                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st);
+                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st, const float *seed_slack = nullptr);
 int ap_rescore_lists(const ap_index *ix, int64_t nn, int32_t K, const int32_t *knn, float *sc, hipStream_t st);
 // Upper bounds of the fused scores of a slab of queries against every document (ap_bound.hip).
 struct ApBound {
