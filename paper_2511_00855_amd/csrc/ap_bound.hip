@@ -5,7 +5,7 @@
 //   table[q][d] >= w_d <q_d,d_d> + w_s <q_s,d_s> + w_f <q_f,d_f>   as the scoring kernels round it.
 //
 // The dense part and the most frequent terms of both vocabularies (the "head": at most AP_BOUND_HEAD columns) are one
-// bf16 matrix product; the remaining terms (the "tail") are added from postings.  Rounding to bf16 is paid for by a
+// bf16 matrix product; the remaining terms (the "tail") are added to a tile of it from postings of the tile's documents.  Rounding to bf16 is paid for by a
 // slack per pair, made of what it took off the two sides, so nothing that decides a result depends on the product's precision: a candidate the bound lets
 // through is scored as ever, and one it stops could not have entered.
 #include <math.h>
@@ -20,6 +20,12 @@ int ap_validate_queries(const ap_queries *q);
 #define AP_BOUND_DMAX 1e15f
 #define AP_BOUND_QT 256              // queries and documents of a tile
 #define AP_BOUND_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of columns is kept for
+#define AP_BOUND_BITS_MIN 8          // buckets of a tile's postings: 2^8 to 2^13
+#define AP_BOUND_BITS 13
+#define AP_BOUND_TERMS 4             // terms of a query that a lane looks up at once
+#define AP_BOUND_LIST (1 + 128)      // a query's tail as the product's kernel reads it: (entries, AP_BOUND_NONE or the first term of the lists that found no place), then (term, weighted value)
+#define AP_BOUND_NONE 0xffffffffu
+#define AP_BOUND_AHEAD 4             // postings of a bucket that are read at once, and entries behind the last one for it
 
 // The workspaces of an index: one per stream that searches it (at most AP_BOUND_STREAMS; insertion and large exact top-k
 // give theirs back, the others only grow), so that searches
@@ -52,58 +58,121 @@ int ap_df_histogram(const int32_t *df_sp, int32_t nsp, const int32_t *df_tx, int
     AP_CHECK_HIP(hipGetLastError());
     return AP_OK;
 }
-// The head is every term of the top bins that fit kh columns together; every other term gets a run of postings.  misc[0]
-// counts columns, misc[1] postings handed out.
+// The head is every term of the top bins that fit kh columns together.  *taken counts columns.
 __global__ __launch_bounds__(1024) void k_bd_pick(const int32_t *__restrict__ df_sp, int32_t nsp, const int32_t *__restrict__ df_tx, int32_t ntx,
-                                                  const int32_t *__restrict__ hist, int32_t kh, int32_t *__restrict__ col,
-                                                  uint2 *__restrict__ run, uint32_t *__restrict__ misc) {
-    __shared__ int32_t s_low;
-    __shared__ uint32_t part[16], s_base;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                                  const int32_t *__restrict__ hist, int32_t kh, int32_t *__restrict__ col, uint32_t *__restrict__ taken) {
+    __shared__ int32_t s_low, s_hist[256];
+    if (threadIdx.x < 256) s_hist[threadIdx.x] = hist[threadIdx.x];
+    __syncthreads();
     if (threadIdx.x == 0) {
         int32_t low = 256, sum = 0;
-        while (low > 0 && sum + hist[low - 1] <= kh) sum += hist[--low];
+        while (low > 0 && sum + s_hist[low - 1] <= kh) sum += s_hist[--low];
         s_low = low;
     }
     __syncthreads();
-    const int64_t t = blockIdx.x * (int64_t)1024 + threadIdx.x, all = (int64_t)nsp + ntx;
-    const int32_t df = t < all ? (t < nsp ? df_sp[t] : df_tx[t - nsp]) : 0;
-    const bool head = df > 0 && ap_df_bin(df) >= s_low;
-    const uint32_t len = head ? 0u : (uint32_t)df;
-    uint32_t upto = len;
+    const int64_t t = blockIdx.x * (int64_t)1024 + threadIdx.x;
+    if (t >= (int64_t)nsp + ntx) return;
+    const int32_t df = t < nsp ? df_sp[t] : df_tx[t - nsp];
+    col[t] = df > 0 && ap_df_bin(df) >= s_low ? (int32_t)atomicAdd(taken, 1u) : -1;
+}
+
+// A tile's postings: the tail entries of AP_BOUND_QT consecutive documents, grouped by a hash of their terms.  An entry is
+// (term << 8 | document in the tile, value bits); terms of both vocabularies count through and stay below AP_BOUND_VOCAB.
+// The tile's entries begin where its documents' lists do (both vocabularies' offsets together), start[b] is where those of
+// bucket b do behind that.  One block per tile; the order within a bucket is left to chance: a term has one entry per
+// document, so no sum depends on it.
+static_assert(AP_BOUND_VOCAB <= (int64_t)1 << 24 && AP_BOUND_QT == 256, "a term and a document of a tile share a word");
+__device__ __forceinline__ uint32_t ap_bound_bucket(uint32_t t, int bits) { return (t * 0x9E3779B1u) >> (32 - bits); }
+__device__ __forceinline__ void ap_bd_post(const ApVecs &D, int64_t tile, int32_t nsp, const int32_t *__restrict__ col, int bits, uint32_t *__restrict__ start,
+                                           uint2 *__restrict__ post, uint32_t *post_cnt /* 1 << bits */) {
+    __shared__ uint32_t part[16], begin[2][AP_BOUND_QT];   // where the documents' lists begin (past the end: behind all entries)
+    const int lane = threadIdx.x & 63, wave = ap_wave_id(), buckets = 1 << bits;
+    const int64_t d0 = tile * AP_BOUND_QT, d1 = d0 + AP_BOUND_QT < D.n ? d0 + AP_BOUND_QT : D.n;
+    const int64_t from[2] = {D.sp_indptr[d0], D.tx_indptr[d0]};
+    uint2 *to = post + from[0] + from[1];
+    if (threadIdx.x < 2 * AP_BOUND_QT) {
+        const int64_t v = d0 + threadIdx.x % AP_BOUND_QT;
+        const int p = threadIdx.x / AP_BOUND_QT;
+        begin[p][threadIdx.x % AP_BOUND_QT] = v < d1 ? (uint32_t)((p ? D.tx_indptr[v] : D.sp_indptr[v]) - from[p]) : 0xffffffffu;
+    }
+    uint32_t *first = start + tile * (buckets + 1);
+    for (int b = threadIdx.x; b < buckets; b += 1024) post_cnt[b] = 0;
+    __syncthreads();
+    // four entries a thread at once, term by term and vocabulary by vocabulary
+    auto each = [&](auto &&f) {
+        for (int p = 0; p < 2; p++) {
+            const int32_t *idx = p ? D.tx_idx : D.sp_idx;
+            const int64_t e = p ? D.tx_indptr[d1] : D.sp_indptr[d1];
+            for (int64_t i0 = (p ? D.tx_indptr[d0] : D.sp_indptr[d0]) + threadIdx.x; i0 < e; i0 += 4096) {
+                int32_t t[4], c[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) t[j] = (p ? nsp : 0) + idx[i0 + 1024 * j < e ? i0 + 1024 * j : i0];
+#pragma unroll
+                for (int j = 0; j < 4; j++) c[j] = i0 + 1024 * j < e ? col[t[j]] : 0;
+                f(p, i0, t, c);
+            }
+        }
+    };
+    each([&](int, int64_t, const int32_t (&t)[4], const int32_t (&c)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (c[j] < 0) atomicAdd(&post_cnt[ap_bound_bucket((uint32_t)t[j], bits)], 1u);
+    });
+    __syncthreads();
+    const int per = (buckets + 1023) / 1024, b0 = (int)threadIdx.x * per;
+    uint32_t sum = 0;
+    for (int b = b0; b < b0 + per && b < buckets; b++) sum += post_cnt[b];
+    uint32_t upto = sum;
     for (int o = 1; o < 64; o <<= 1) { const uint32_t up = __shfl_up(upto, o, 64); if (lane >= o) upto += up; }
     if (lane == 63) part[wave] = upto;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t sum = 0;
-        for (int w = 0; w < 16; w++) { const uint32_t p = part[w]; part[w] = sum; sum += p; }
-        s_base = sum ? atomicAdd(&misc[1], sum) : 0u;
+    uint32_t at = upto - sum;
+    for (int w = 0; w < wave; w++) at += part[w];
+    for (int b = b0; b < b0 + per && b < buckets; b++) {
+        const uint32_t c = post_cnt[b];
+        post_cnt[b] = first[b] = at;
+        at += c;
     }
+    if (threadIdx.x == 1023) first[buckets] = at;
     __syncthreads();
-    if (t < all) {
-        col[t] = head ? (int32_t)atomicAdd(&misc[0], 1u) : -1;
-        run[t] = make_uint2(s_base + part[wave] + upto - len, len);
-    }
+    each([&](int p, int64_t i0, const int32_t (&t)[4], const int32_t (&c)[4]) {
+        const float *val = p ? D.tx_val : D.sp_val;
+        float x[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) x[j] = c[j] < 0 ? val[i0 + 1024 * j] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (c[j] < 0) {
+                int d = 0;   // the last document whose list begins at or before the entry
+                for (int o = AP_BOUND_QT / 2; o > 0; o >>= 1)
+                    if (begin[p][d + o] <= (uint32_t)(i0 + 1024 * j - from[p])) d += o;
+                to[atomicAdd(&post_cnt[ap_bound_bucket((uint32_t)t[j], bits)], 1u)] = make_uint2((uint32_t)t[j] << 8 | (uint32_t)d, __float_as_uint(x[j]));
+            }
+    });
 }
 
 __device__ __forceinline__ uint32_t ap_bf16_bits(float f) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f); }   // to nearest even
 
 __device__ __forceinline__ float ap_bf16_value(uint32_t bits) { return __uint_as_float(bits << 16); }
 
-// One wave per document: its bound row (dense part rounded to bf16 if kd > 0, then the head columns), what the slack of its
-// column is made of, its postings, and its bit in the bitmaps of the lexical head terms it holds.  norms: planes of n
+// The first blocks take a tile's postings each (one launch, since a few tiles leave the chip idle: 2,000 documents 42 -> 26 us), the others a wave
+// per document: its bound row (dense part rounded to bf16 if kd > 0, then the head columns), what the slack of its
+// column is made of, and its bit in the bitmaps of the lexical head terms it holds.  norms: planes of n
 // entries for the dense part and the head columns of either vocabulary, each the norm of what rounding to bf16 took off the
 // part (exact differences: a value and its rounding lie within a factor of two) and the part's own norm.
 template <int DT>
-__global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const int32_t *__restrict__ col, const uint2 *__restrict__ run,
-                                                 uint32_t *__restrict__ cursor, int32_t kd, int32_t kh, uint16_t *__restrict__ rows,
-                                                 uint2 *__restrict__ post, const float *__restrict__ dnorm, float2 *__restrict__ norms, uint32_t *__restrict__ bits,
-                                                 int64_t words) {
-    __shared__ __attribute__((aligned(16))) uint16_t s_head[4][AP_BOUND_HEAD];
+__global__ __launch_bounds__(1024) void k_bd_rows(ApVecs D, int32_t nsp, const int32_t *__restrict__ col, int32_t kd, int32_t kh, uint16_t *__restrict__ rows,
+                                                  const float *__restrict__ dnorm, float2 *__restrict__ norms, uint32_t *__restrict__ bits, int64_t words,
+                                                  uint32_t tiles, int bucket_bits, uint32_t *__restrict__ start, uint2 *__restrict__ post) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t bd_lds[];   // a tile's buckets, or a head row per wave
+    if (blockIdx.x < tiles) {   // uniform
+        ap_bd_post(D, blockIdx.x, nsp, col, bucket_bits, start, post, bd_lds);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = ap_wave_id();
-    uint16_t *head = s_head[wave];
+    uint16_t *head = reinterpret_cast<uint16_t *>(bd_lds) + wave * AP_BOUND_HEAD;
     const int32_t ld = kd + kh;
-    for (int64_t v = blockIdx.x * (int64_t)4 + wave; v < D.n; v += (int64_t)gridDim.x * 4) {
+    for (int64_t v = (int64_t)(blockIdx.x - tiles) * 16 + wave; v < D.n; v += (int64_t)(gridDim.x - tiles) * 16) {
         uint16_t *row = rows + v * ld;
         float sum[2] = {0.f, 0.f}, lost[3] = {0.f, 0.f, 0.f};
         for (int32_t c = lane * 4; c < kd; c += 256) {
@@ -138,7 +207,7 @@ __global__ __launch_bounds__(256) void k_bd_rows(ApVecs D, int32_t nsp, const in
                     const float off = x - ap_bf16_value(h);
                     head[c] = (uint16_t)h; sum[part] = fmaf(x, x, sum[part]); lost[1 + part] = fmaf(off, off, lost[1 + part]);
                     if (part) atomicOr(&bits[c * words + (v >> 5)], 1u << (v & 31));
-                } else post[run[t].x + atomicAdd(&cursor[t], 1u)] = make_uint2((uint32_t)v, __float_as_uint(x));
+                }
             }
         }
         ap_wave_sync();
@@ -167,11 +236,16 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     const int32_t kh = (int32_t)std::min<int64_t>(AP_BOUND_HEAD, (int64_t)ap_up((size_t)all, AP_BK16));
     const size_t nnz = (size_t)ix->tx_nnz + (size_t)ix->sp_nnz;
     const int64_t words = (c.n + 31) / 32;
-    // cleared: document frequencies of the learned-sparse terms, cursors, histogram, misc, bitmaps
-    const size_t n_clear = (size_t)c.sp_vocab + (size_t)all + 256 + 2 + (size_t)kh * (size_t)words;
+    // two buckets for three entries of a tile's lists, about half of which are in the tail (2^14 instead of 2^13 for 165 entries a document: 1 to 8 %
+    // off the product and the tail, for twice the memory and 20 us at ingest)
+    const int64_t doc_tiles = (c.n + AP_BOUND_QT - 1) / AP_BOUND_QT;
+    int bits = AP_BOUND_BITS_MIN;
+    while (bits < AP_BOUND_BITS && ((int64_t)1 << bits) * 3 * doc_tiles < 2 * (int64_t)nnz) bits++;
+    // cleared: document frequencies of the learned-sparse terms, histogram, columns taken, bitmaps
+    const size_t n_clear = (size_t)c.sp_vocab + 256 + 1 + (size_t)kh * (size_t)words;
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t a = at; at += ap_up(bytes, 256); return a; };
-    const size_t o_clear = take(n_clear * 4), o_col = take((size_t)all * 4), o_run = take((size_t)all * 8), o_post = take((nnz + 1) * 8),
+    const size_t o_clear = take(n_clear * 4), o_col = take((size_t)all * 4), o_start = take((size_t)doc_tiles * (((size_t)1 << bits) + 1) * 4), o_post = take((nnz + AP_BOUND_AHEAD) * 8),
                  o_norms = take((size_t)c.n * 24), o_rows = take((size_t)c.n * (size_t)(kd + kh) * 2);
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || at > free_b / (size_t)share) { (void)hipGetLastError(); return AP_OK; }
@@ -179,28 +253,28 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     if (hipMalloc(&ix->bd_mem, at) != hipSuccess) { (void)hipGetLastError(); ix->bd_mem = nullptr; return AP_OK; }
     char *m = static_cast<char *>(ix->bd_mem);
     int32_t *df_sp = reinterpret_cast<int32_t *>(m + o_clear);
-    uint32_t *cursor = reinterpret_cast<uint32_t *>(df_sp + c.sp_vocab);
-    int32_t *hist = reinterpret_cast<int32_t *>(cursor + all);
-    uint32_t *misc = reinterpret_cast<uint32_t *>(hist + 256);
+    int32_t *hist = df_sp + c.sp_vocab;
+    uint32_t *taken = reinterpret_cast<uint32_t *>(hist + 256);
     ix->bd_df = df_sp;
     ix->bd_col = reinterpret_cast<int32_t *>(m + o_col);
-    ix->bd_run = reinterpret_cast<uint2 *>(m + o_run);
+    ix->bd_start = reinterpret_cast<uint32_t *>(m + o_start);
+    ix->bd_start_bits = bits;
     ix->bd_post = reinterpret_cast<uint2 *>(m + o_post);
     ix->bd_norms = reinterpret_cast<float2 *>(m + o_norms);
     ix->bd_rows = reinterpret_cast<uint16_t *>(m + o_rows);
-    ix->bd_bits = misc + 2;
+    ix->bd_bits = taken + 1;
     ix->bd_kd = kd; ix->bd_kh = kh;
     AP_TRY(ap_fill_u32(df_sp, n_clear, 0u, st));
     if (ix->sp_nnz > 0)
         AP_TRY(ap_count_terms(c.sp_idx, nullptr, ix->sp_nnz, df_sp, nullptr, st));
     AP_TRY(ap_df_histogram(df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, st));
-    hipLaunchKernelGGL(k_bd_pick, dim3((unsigned)((all + 1023) / 1024)), dim3(1024), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, kh, ix->bd_col,
-                       ix->bd_run, misc);
-    const dim3 g((unsigned)std::min<int64_t>((c.n + 3) / 4, 4096));
+    hipLaunchKernelGGL(k_bd_pick, dim3((unsigned)((all + 1023) / 1024)), dim3(1024), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, kh, ix->bd_col, taken);
+    const dim3 g((unsigned)(doc_tiles + std::min<int64_t>((c.n + 15) / 16, 1024)));
+    const size_t lds = std::max((size_t)4 << bits, (size_t)16 * AP_BOUND_HEAD * 2);
     if (ix->dtype == AP_F32)
-        hipLaunchKernelGGL(k_bd_rows<AP_F32>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->dense_norm, ix->bd_norms, ix->bd_bits, words);
+        hipLaunchKernelGGL(k_bd_rows<AP_F32>, g, dim3(1024), lds, st, ix->docs, c.sp_vocab, ix->bd_col, kd, kh, ix->bd_rows, ix->dense_norm, ix->bd_norms, ix->bd_bits, words, (uint32_t)doc_tiles, bits, ix->bd_start, ix->bd_post);
     else
-        hipLaunchKernelGGL(k_bd_rows<AP_BF16>, g, dim3(256), 0, st, ix->docs, c.sp_vocab, ix->bd_col, ix->bd_run, cursor, kd, kh, ix->bd_rows, ix->bd_post, ix->dense_norm, ix->bd_norms, ix->bd_bits, words);
+        hipLaunchKernelGGL(k_bd_rows<AP_BF16>, g, dim3(1024), lds, st, ix->docs, c.sp_vocab, ix->bd_col, kd, kh, ix->bd_rows, ix->dense_norm, ix->bd_norms, ix->bd_bits, words, (uint32_t)doc_tiles, bits, ix->bd_start, ix->bd_post);
     AP_CHECK_HIP(hipGetLastError());
     return AP_OK;
 }
@@ -208,10 +282,29 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
 // ------------------------------------------------------------------ the table
 __device__ __forceinline__ float ap_bound_value(float entry) { return __uint_as_float(__float_as_uint(entry) & ~AP_BOUND_COUNT); }
 // Entries carry a count in their low bits (keyword searches: how many of the query's required terms the document holds);
-// what clearing them takes off a value is added first.
-__device__ __forceinline__ float ap_bound_round(float v) {
-    return __uint_as_float(__float_as_uint(fmaf(fabsf(v), 1e-5f, v)) & ~AP_BOUND_COUNT);
+// what clearing them takes off a value (2^-18 of it) is added first, and what the additions of the tail may have: rel is at
+// least 1e-5 and 2^-22 for each of them.
+__device__ __forceinline__ float ap_bound_round(float v, float rel) {
+    return __uint_as_float(__float_as_uint(fmaf(fabsf(v), rel, v)) & ~AP_BOUND_COUNT);
 }
+__device__ __forceinline__ void ap_lds_add(float *at, float v) { (void)unsafeAtomicAdd(at, v); }   // ds_add_f32
+
+// What the product's kernel adds the tail from: the queries' lists and weights, the tiles' postings, and for keyword
+// searches the required terms (the head's are asked of the bitmaps).
+struct ApBoundTail {
+    const float *w;
+    int32_t w_stride, nsp, ntx, bits, kw_stride;
+    int64_t q0;
+    const int64_t *q_sp_indptr, *q_tx_indptr;
+    const int32_t *q_sp_idx, *q_tx_idx;
+    const float *q_sp_val, *q_tx_val;
+    const int64_t *sp_indptr, *tx_indptr;   // of the documents
+    const uint2 *lists;                     // per row of the table AP_BOUND_LIST entries
+    const uint32_t *start;
+    const uint2 *post;
+    const int32_t *kw_terms;
+};
+static_assert(128 * AP_BOUND_QT * 4 <= AP_BIG_LDS_BYTES, "half a tile takes the place of the product's stages");
 
 static inline int32_t bound_kdense(const ap_index *ix) { return ix->bd_kd ? ix->bd_kd : ix->docs.dim; }
 
@@ -228,12 +321,14 @@ static inline int32_t bound_kdense(const ap_index *ix) { return ix->bd_kd ? ix->
 // part of a document beyond AP_BOUND_DMAX) give a bound of infinity.
 __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int64_t nq, int32_t kdense,
                                                        int32_t kh, int32_t nsp, int32_t ntx, const int32_t *__restrict__ col,
-                                                       uint16_t *__restrict__ qm, float *__restrict__ qc) {
+                                                       uint16_t *__restrict__ qm, float *__restrict__ qc, uint2 *__restrict__ tails) {
     __shared__ __attribute__((aligned(16))) uint16_t head[AP_BOUND_HEAD];
     __shared__ float red[9][4];
     const int64_t r = blockIdx.x, q = q0 + r;
     uint16_t *row = qm + r * (kdense + kh);
+    uint2 *list = tails + r * AP_BOUND_LIST;
     if (r >= nq) {
+        if (threadIdx.x <= 8 * AP_BOUND_TERMS) list[threadIdx.x] = threadIdx.x ? make_uint2(AP_BOUND_NONE, 0u) : make_uint2(0u, AP_BOUND_NONE);
         for (int32_t c = threadIdx.x * 8; c < kdense + kh; c += 2048) *reinterpret_cast<uint4 *>(row + c) = make_uint4(0, 0, 0, 0);
         if (threadIdx.x < 8) qc[r * 8 + threadIdx.x] = 0.f;
         return;
@@ -262,8 +357,21 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
     }
     __syncthreads();
     int64_t terms = 0;
+    uint32_t n_tail = 0, rest = AP_BOUND_NONE;
     for (int part = 0; part < 2; part++) {
         const int64_t b = part ? Q.tx_indptr[q] : Q.sp_indptr[q], e = part ? Q.tx_indptr[q + 1] : Q.sp_indptr[q + 1];
+        if (threadIdx.x >= 192) {   // the last wave lists the tail
+            const int lane = threadIdx.x & 63;
+            for (int64_t p0 = b; p0 < e && rest == AP_BOUND_NONE; p0 += 64) {
+                const int32_t t = p0 + lane < e ? (part ? Q.tx_idx : Q.sp_idx)[p0 + lane] : -1;
+                const bool in = t >= 0 && t < (part ? ntx : nsp) && col[part ? nsp + t : t] < 0;
+                const uint64_t m = __ballot(in);
+                const uint32_t at = n_tail + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)), upto = n_tail + (uint32_t)__popcll(m);
+                if (upto >= AP_BOUND_LIST) { rest = (uint32_t)(terms + (p0 - b)); break; }   // uniform
+                if (in) list[1 + at] = make_uint2((uint32_t)(part ? nsp + t : t), __float_as_uint((part ? wf * Q.tx_val[p0 + lane] : ws * Q.sp_val[p0 + lane])));
+                n_tail = upto;
+            }
+        }
         terms += e - b;
         for (int64_t p = b + threadIdx.x; p < e; p += 256) {
             const int32_t t = part ? Q.tx_idx[p] : Q.sp_idx[p];
@@ -281,6 +389,11 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
         sum[i] = ap_wave_sum(sum[i]);
         if ((threadIdx.x & 63) == 0) red[i][threadIdx.x >> 6] = sum[i];
     }
+    if (threadIdx.x >= 192) {   // whole batches
+        for (uint32_t i = n_tail + (threadIdx.x & 63); i < AP_BOUND_LIST - 1 && (i < 8 * AP_BOUND_TERMS || i < (n_tail + 8 * AP_BOUND_TERMS - 1) / (8 * AP_BOUND_TERMS) * (8 * AP_BOUND_TERMS)); i += 64)
+            list[1 + i] = make_uint2(AP_BOUND_NONE, 0u);
+        if (threadIdx.x == 192) list[0] = make_uint2(n_tail, rest);
+    }
     large = __syncthreads_or(large) != 0;
     for (int32_t c = threadIdx.x * 8; c < kh; c += 2048) *reinterpret_cast<uint4 *>(row + kdense + c) = *reinterpret_cast<const uint4 *>(head + c);
     if (threadIdx.x == 0) {
@@ -297,16 +410,21 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
 }
 
 // The product and the slack: a tile of 256 queries x 256 documents, 16 waves of 64 x 64, chunks of 64 columns through two
-// LDS stages as in the seed sweep.  10,000 queries x 100,000 documents x 1,280 columns take 3.22 ms = 0.82 PFLOP/s; the
-// matrix cores and the LDS reads that feed them bound it, as they bound the sweep.  The documents' columns come from two places: the dense part (dense, dense_ld) and
+// LDS stages as in the seed sweep.  10,000 queries x 100,000 documents x 1,280 columns take 3.1 ms = 0.84 PFLOP/s without the
+// tail; the matrix cores and the LDS reads that feed them bound it, as they bound the sweep.  The documents' columns come from two places: the dense part (dense, dense_ld) and
 // the head (rows + head_at, rows_ld).
+// The tail is added while the tile is in LDS (4.1 ms in all; about one entry in twenty is touched): a kernel of its own that went
+// through the queries' postings, one block a query, took 3.3 ms for the read-modify-writes of four fifths of the table's lines.
+// What is left of it is the wait for three reads that depend on each other (a query's terms, where their buckets lie, their
+// entries), 8 us for half a tile when each was asked for in its turn, 4 as it is.  A lane per document entry would look up five times as
+// many terms.  1,000 queries: 707 -> 480 us; 4,000 of some 150 terms, 80,000 documents of 1,024 bf16 columns: 5.5 -> 3.0 ms.
 // Tile order: an XCD takes the document tiles in groups of four and walks each group's query tiles, so that a group's
 // documents and the queries stay in its L2 while they are used.
 #define AP_BOUND_GROUP 4
 __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict__ qm, const float *__restrict__ qc, int32_t nq, int32_t q_tiles,
                                                       const uint16_t *__restrict__ dense, int32_t dense_ld, int32_t n_dense,
                                                       const uint16_t *__restrict__ head, int32_t head_ld, int32_t n_chunks,
-                                                      const float2 *__restrict__ norms, int64_t n, int64_t doc_tiles,
+                                                      const float2 *__restrict__ norms, int64_t n, int64_t doc_tiles, ApBoundTail tail,
                                                       float *__restrict__ table, int64_t ld) {
     extern __shared__ __attribute__((aligned(16))) uint16_t bound_lds[];
     __shared__ float2 s_qc[3][AP_BOUND_QT], s_dn[3][AP_BOUND_QT];   // per part: |q^| and the factor of |d|; |d - d^| and |d|
@@ -392,68 +510,145 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
         round(k, va0, vb0);
         if (k + 1 < n_chunks) round(k + 1, va1, vb1);
     }
-    float2 dn[2][3];
+    // The tile goes to LDS by halves, where the tail is added, and from there to memory.  Half a holds the queries of every
+    // wave's accumulators a: place p of its 128 is query (p >> 5) * 64 + a * 32 + (p & 31).  Eight lanes take a query, a wave
+    // the same eight queries from the first addition to the last store: only the way into LDS needs barriers.
+    // What a query's additions wait for is asked for early: its terms before the accumulators go to LDS, where their buckets
+    // lie before the barrier behind that, the first entries of all buckets at once.
+    float *tile = reinterpret_cast<float *>(bound_lds);
+    const uint32_t *start = tail.start + dt * ((1 << tail.bits) + 1);
+    const uint2 *post = tail.post + tail.sp_indptr[d0] + tail.tx_indptr[d0];
+    const int own = wave * 8 + (lane >> 3), sub = lane & 7;
+    const int64_t r_own = r0 + (own >> 5) * 64 + (own & 31);   // and 32 more in the second half
+    const uint2 *lists = tail.lists + r_own * AP_BOUND_LIST;
+    uint2 term[AP_BOUND_TERMS], first;
+    uint32_t at[AP_BOUND_TERMS], to[AP_BOUND_TERMS];
+    auto ask_terms = [&](const uint2 *list, uint32_t from) {
 #pragma unroll
-    for (int b = 0; b < 2; b++)
+        for (int u = 0; u < AP_BOUND_TERMS; u++) term[u] = list[1 + from + sub + 8 * u];
+    };
+    auto ask_buckets = [&]() {
 #pragma unroll
-        for (int p = 0; p < 3; p++) dn[b][p] = s_dn[p][wn * 64 + b * 32 + li];
+        for (int u = 0; u < AP_BOUND_TERMS; u++) {
+            const uint32_t b = ap_bound_bucket(term[u].x, tail.bits);
+            at[u] = start[b];
+            to[u] = start[b + 1];
+            if (term[u].x == AP_BOUND_NONE) to[u] = at[u];
+        }
+    };
+    first = lists[0];
+    ask_terms(lists, 0);
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+    for (int a = 0; a < 2; a++) {
+        if (a) {
+            __syncthreads();
+            lists += 32 * AP_BOUND_LIST;
+        }
+        float2 dn[2][3];
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int p = 0; p < 3; p++) dn[b][p] = s_dn[p][wn * 64 + b * 32 + li];
 #pragma unroll
         for (int r = 0; r < 16; r++) {
-            const int i = wm * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            const int in = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), i = wm * 64 + a * 32 + in;
             const float2 c0 = s_qc[0][i], c1 = s_qc[1][i], c2 = s_qc[2][i];
 #pragma unroll
             for (int b = 0; b < 2; b++) {
-                const int j = wn * 64 + b * 32 + li;
                 float slack = fmaf(c0.x, dn[b][0].x, 1e-36f);
                 slack = fmaf(c0.y, dn[b][0].y, slack);
                 slack = fmaf(c1.x, dn[b][1].x, slack);
                 slack = fmaf(c1.y, dn[b][1].y, slack);
                 slack = fmaf(c2.x, dn[b][2].x, slack);
                 slack = fmaf(c2.y, dn[b][2].y, slack);
-                if (r0 + i < nq && d0 + j < n) table[(r0 + i) * ld + d0 + j] = ap_bound_round(acc[a][b][r] + slack);
+                tile[(wm * 32 + in) * AP_BOUND_QT + wn * 64 + b * 32 + li] = acc[a][b][r] + slack;
             }
         }
-}
-
-// One block per query: the tail terms' postings, one term after the other (a document occurs once in a term's postings,
-// so the additions need no atomics and always come in the same order); then, for keyword searches, the count of required
-// tail terms every document holds, in the entries' low bits (the head's are asked of the bitmaps).  Bound by the
-// scattered read-modify-writes: 3.35 ms for 10,000 queries of 100,000 documents (about one entry in twenty is touched).
-__global__ __launch_bounds__(256) void k_bound_tail(ApVecs Q, const float *__restrict__ w, int32_t w_stride, int64_t q0, int32_t nsp, int32_t ntx,
-                                                    const int32_t *__restrict__ col, const uint2 *__restrict__ run, const uint2 *__restrict__ post,
-                                                    const float *__restrict__ qc, const int32_t *__restrict__ kw_terms, int32_t kw_stride,
-                                                    float *__restrict__ table, int64_t ld) {
-    const int64_t q = q0 + blockIdx.x;
-    float *row = table + (int64_t)blockIdx.x * ld;
-    const float ws = w[q * w_stride + 1], wf = w[q * w_stride + 2], rel = qc[blockIdx.x * (int64_t)8 + 6];
-    for (int part = 0; part < 2; part++) {
-        const int64_t b = part ? Q.tx_indptr[q] : Q.sp_indptr[q], e = part ? Q.tx_indptr[q + 1] : Q.sp_indptr[q + 1];
-        for (int64_t p = b; p < e; p++) {   // uniform
-            const int32_t t = part ? Q.tx_idx[p] : Q.sp_idx[p];
-            if (t < 0 || t >= (part ? ntx : nsp)) continue;
-            const int32_t at = part ? nsp + t : t;
-            if (col[at] >= 0) continue;
-            const uint2 r = run[at];
-            const float x = part ? wf * Q.tx_val[p] : ws * Q.sp_val[p];
-            for (uint32_t i = threadIdx.x; i < r.y; i += 256) {
-                const uint2 dv = post[r.x + i];
-                const float c = x * __uint_as_float(dv.y);
-                row[dv.x] = ap_bound_round(row[dv.x] + (fabsf(__uint_as_float(dv.y)) <= AP_BOUND_DMAX ? fmaf(fabsf(c), rel, c) : INFINITY));
+        ask_buckets();
+        __syncthreads();
+        const int64_t r = r_own + 32 * a, q = tail.q0 + r;
+        float *row = tile + own * AP_BOUND_QT;
+        const float rel = qc[r * 8 + 6];
+        auto add = [&](const uint2 &dv, bool in, uint32_t term, float x) {
+            if (in && (dv.x >> 8) == term) {
+                const float y = __uint_as_float(dv.y), c = x * y;
+                ap_lds_add(&row[dv.x & 255u], fabsf(y) <= AP_BOUND_DMAX ? fmaf(fabsf(c), rel, c) : INFINITY);
             }
-            if (r.y) __syncthreads();
+        };
+        // the buckets' first entries all at once, what is left of them one bucket after the other
+        auto add_batch = [&]() {
+            uint2 dv[AP_BOUND_TERMS][AP_BOUND_AHEAD];
+#pragma unroll
+            for (int u = 0; u < AP_BOUND_TERMS; u++)
+#pragma unroll
+                for (int j = 0; j < AP_BOUND_AHEAD; j++)
+                    if (at[u] + j < to[u]) dv[u][j] = post[at[u] + j];
+#pragma unroll
+            for (int u = 0; u < AP_BOUND_TERMS; u++)
+#pragma unroll
+                for (int j = 0; j < AP_BOUND_AHEAD; j++) add(dv[u][j], at[u] + j < to[u], term[u].x, __uint_as_float(term[u].y));
+#pragma unroll
+            for (int u = 0; u < AP_BOUND_TERMS; u++)
+                for (uint32_t i = at[u] + AP_BOUND_AHEAD; i < to[u]; i += AP_BOUND_AHEAD) {
+                    uint2 more[AP_BOUND_AHEAD];
+#pragma unroll
+                    for (int j = 0; j < AP_BOUND_AHEAD; j++) more[j] = post[i + j];
+#pragma unroll
+                    for (int j = 0; j < AP_BOUND_AHEAD; j++) add(more[j], i + j < to[u], term[u].x, __uint_as_float(term[u].y));
+                }
+        };
+        add_batch();
+        for (uint32_t from = 8 * AP_BOUND_TERMS; from < first.x; from += 8 * AP_BOUND_TERMS) {
+            ask_terms(lists, from);
+            ask_buckets();
+            add_batch();
         }
-    }
-    for (int32_t j = 0; j < kw_stride; j++) {
-        const int32_t t = kw_terms[q * kw_stride + j];
-        if (t < 0 || t >= ntx || col[nsp + t] >= 0) continue;
-        const uint2 r = run[nsp + t];
-        for (uint32_t i = threadIdx.x; i < r.y; i += 256) {
-            uint32_t *at = reinterpret_cast<uint32_t *>(row + post[r.x + i].x);
-            *at = *at + 1u;   // at most 16 required terms: the count stays inside its bits
+        const uint32_t rest = first.y;
+        if (a == 0) {   // the second half's, while this one's are added to the end and stored
+            first = lists[32 * AP_BOUND_LIST];
+            ask_terms(lists + 32 * AP_BOUND_LIST, 0);
         }
-        if (r.y) __syncthreads();
+        if (rest != AP_BOUND_NONE) {   // what the list had no place for
+            const float ws = tail.w[q * tail.w_stride + 1], wf = tail.w[q * tail.w_stride + 2];
+            const int64_t sp0 = tail.q_sp_indptr[q], tx0 = tail.q_tx_indptr[q], sp_n = tail.q_sp_indptr[q + 1] - sp0, all = sp_n + (tail.q_tx_indptr[q + 1] - tx0);
+            for (int64_t p = (int64_t)rest + sub; p < all; p += 8) {
+                const bool sp = p < sp_n;
+                const int32_t t = sp ? tail.q_sp_idx[sp0 + p] : tail.q_tx_idx[tx0 + p - sp_n];
+                const float x = sp ? ws * tail.q_sp_val[sp0 + p] : wf * tail.q_tx_val[tx0 + p - sp_n];
+                if (t < 0 || t >= (sp ? tail.nsp : tail.ntx)) continue;
+                const uint32_t other = (uint32_t)(sp ? t : tail.nsp + t), b = ap_bound_bucket(other, tail.bits);
+                for (uint32_t i = start[b], e = start[b + 1]; i < e; i++) add(post[i], true, other, x);
+            }
+        }
+        ap_wave_sync();
+        if (tail.kw_terms) {   // uniform
+            if (r < nq) for (int j = sub; j < AP_BOUND_QT; j += 8) row[j] = ap_bound_round(row[j], rel);
+            ap_wave_sync();
+            if (r < nq)
+                for (int j = sub; j < tail.kw_stride; j += 8) {
+                    const int32_t t = tail.kw_terms[q * tail.kw_stride + j];
+                    if (t < 0 || t >= tail.ntx) continue;
+                    const uint32_t term = (uint32_t)(tail.nsp + t), b = ap_bound_bucket(term, tail.bits);
+                    for (uint32_t i = start[b], to = start[b + 1]; i < to; i++) {
+                        const uint32_t d = post[i].x;
+                        if ((d >> 8) == term) atomicAdd(reinterpret_cast<uint32_t *>(row + (d & 255u)), 1u);   // at most 16 required terms: the count stays inside its bits
+                    }
+                }
+            ap_wave_sync();
+        }
+        const int64_t j = d0 + lane * 4;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int at = wave * 8 + i;
+            const int64_t to = r0 + (at >> 5) * 64 + a * 32 + (at & 31);
+            if (to >= nq || j >= ld) continue;
+            float4 v = *reinterpret_cast<const float4 *>(tile + at * AP_BOUND_QT + lane * 4);
+            if (!tail.kw_terms) {
+                const float f = __shfl(rel, i * 8, 64);
+                v = make_float4(ap_bound_round(v.x, f), ap_bound_round(v.y, f), ap_bound_round(v.z, f), ap_bound_round(v.w, f));
+            }
+            *reinterpret_cast<float4 *>(table + to * ld + j) = v;
+        }
     }
 }
 
@@ -551,7 +746,7 @@ int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t be
 // the two bitmaps beside it).
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq, int tables) {
     const size_t rows = ap_up((size_t)nq, AP_BOUND_QT), k = (size_t)(bound_kdense(ix) + ix->bd_kh), n = (size_t)ix->docs.n;
-    return rows * k * 2 + rows * 32 + rows * 20 + (size_t)nq * (tables == AP_BOUND_MARKS ? ap_up(n, 64) * 4 + (n + 31) / 32 * 8 : (size_t)tables * ap_up(n, 64) * 4);
+    return rows * k * 2 + rows * 32 + rows * 20 + ap_up(rows * AP_BOUND_LIST * 8, 256) + (size_t)nq * (tables == AP_BOUND_MARKS ? ap_up(n, 64) * 4 + (n + 31) / 32 * 8 : (size_t)tables * ap_up(n, 64) * 4);
 }
 
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBound *b) {
@@ -560,6 +755,7 @@ void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBo
     b->qm = reinterpret_cast<uint16_t *>(m); m += rows * k * 2;
     b->qc = reinterpret_cast<float *>(m); m += rows * 32;
     b->floor = reinterpret_cast<float *>(m); m += rows * 20;
+    b->tails = reinterpret_cast<uint2 *>(m); m += ap_up(rows * AP_BOUND_LIST * 8, 256);
     b->table = reinterpret_cast<float *>(m);
     b->ld = (int64_t)ap_up((size_t)ix->docs.n, 64);
     float *behind = b->table + (size_t)nq * (size_t)b->ld;
@@ -678,14 +874,14 @@ int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const f
     const int64_t groups = (doc_tiles + 8 * AP_BOUND_GROUP - 1) / (8 * AP_BOUND_GROUP);
     const bool own = ix->bd_kd != 0;
     hipLaunchKernelGGL(k_bound_queries, dim3((unsigned)(q_tiles * AP_BOUND_QT)), dim3(256), 0, st, Q, w, w_stride, q0, nq, kdense, kh, nsp, ntx, ix->bd_col, b.qm,
-                       b.qc);
+                       b.qc, b.tails);
     AP_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bound_table), hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES));
     const int32_t ld = ix->bd_kd + kh;
+    const ApBoundTail tail{w, w_stride, nsp, ntx, ix->bd_start_bits, kw_terms ? kw_stride : 0, q0, Q.sp_indptr, Q.tx_indptr, Q.sp_idx, Q.tx_idx, Q.sp_val, Q.tx_val,
+                           ix->docs.sp_indptr, ix->docs.tx_indptr, b.tails, ix->bd_start, ix->bd_post, kw_terms};
     hipLaunchKernelGGL(k_bound_table, dim3((unsigned)(groups * 8 * AP_BOUND_GROUP * q_tiles)), dim3(1024), AP_BIG_LDS_BYTES, st, b.qm, b.qc, (int32_t)nq,
                        (int32_t)q_tiles, own ? ix->bd_rows : static_cast<const uint16_t *>(ix->docs.dense), own ? ld : ix->docs.dim, kdense / AP_BK16,
-                       ix->bd_rows + ix->bd_kd, ld, (kdense + kh) / AP_BK16, ix->bd_norms, n, doc_tiles, b.table, b.ld);
-    hipLaunchKernelGGL(k_bound_tail, dim3((unsigned)nq), dim3(256), 0, st, Q, w, w_stride, q0, nsp, ntx, ix->bd_col, ix->bd_run, ix->bd_post, b.qc, kw_terms,
-                       kw_terms ? kw_stride : 0, b.table, b.ld);
+                       ix->bd_rows + ix->bd_kd, ld, (kdense + kh) / AP_BK16, ix->bd_norms, n, doc_tiles, tail, b.table, b.ld);
     AP_CHECK_HIP(hipGetLastError());
     return AP_OK;
 }

@@ -93,8 +93,9 @@ struct ap_index {
     uint16_t *bd_rows = nullptr;       // n x (bd_kd + bd_kh) bf16: dense part where bd_kd > 0, then the head columns
     int32_t bd_kd = 0, bd_kh = 0;      // columns of a copied dense part (0: the corpus's own rows serve), head columns
     int32_t *bd_col = nullptr;         // per term (learned-sparse vocabulary, then lexical): its head column or -1
-    uint2 *bd_run = nullptr;           // per term: first posting, number of postings (0 for head terms)
-    uint2 *bd_post = nullptr;          // (document, weight bits)
+    uint32_t *bd_start = nullptr;      // per 256 documents: where the buckets of their postings begin
+    int bd_start_bits = 0;             // 2^bits buckets each
+    uint2 *bd_post = nullptr;          // (term and document of the 256, value bits) of every entry that has no head column
     float2 *bd_norms = nullptr;        // 3 planes of n (dense part, learned-sparse and lexical head columns): norm of the rounding's loss, norm
     uint32_t *bd_bits = nullptr;       // per head column a bit per document: it holds that lexical term
     struct ApBoundPool *bd_pool = nullptr;   // search-time workspaces
@@ -200,6 +201,7 @@ struct ApBound {
     int64_t ld = 0;            // documents, padded
     uint16_t *qm = nullptr;    // the slab's queries as bf16 rows
     float *qc = nullptr;       // per query 8 floats: what the slack of its row is made of
+    uint2 *tails = nullptr;    // per query its terms without a head column
     float *floor = nullptr;    // per query four floats: an estimate of the last score of a pool, two lower ones (ap_bound_floors)
     uint64_t *marks = nullptr; // per query a word for 32 documents: which of them the search has met, and (upper half) which have a bound that reaches the floor
     float *second = nullptr;   // a second table of the same shape, where the call asked for one

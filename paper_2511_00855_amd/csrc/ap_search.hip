@@ -795,17 +795,19 @@ void k_search(ApSearchArgs g) {
 #define AP_SEARCH_WS_BYTES ((size_t)2 << 30)
 
 // What the bounds of all documents cost, by what was measured (microseconds): a document's columns are read once (0.4 ns), a
-// tile of 256 queries takes 3.1 ps a pair at 1,280 columns, the tail's postings 3.5 ps a pair.
+// tile of 256 queries takes 3.1 ps a pair at 1,280 columns and 1.1 ps for the tail.
 double ap_bound_cost(const ap_index *ix, int64_t nq) {
     const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256);
-    return 15.0 + (double)ix->docs.n * (0.4e-3 * cols + tiles * 256.0 * 3.1e-6 * cols + (double)nq * 3.5e-6);
+    return 15.0 + (double)ix->docs.n * (0.4e-3 * cols + tiles * 256.0 * (3.1e-6 * cols + 1.1e-6));
 }
 
 // Whether that is less than they save:
-//  - a search that does without: at least 0.15 ns more for every document it reaches while the chip is full (100,000
-//    documents, beam 128: 22.1 ms for 10,000 queries without bounds, 13.3 ms with them, 2.9 of which are the table), and
-//    8 us more an iteration when it is not (one query, 128 iterations: 2.35 ms and 0.89 ms).
-// On 100,000 documents the line lies near a pool of 40 entries at degree 64; searches below it run without.
+//  - a search that does without: 0.22 ns more for every document it reaches while the chip is full (10,000 queries of 100,000
+//    documents: 0.22 to 0.28 where both take the same time, which is at pools of 16, 25 and 36 entries for 128 f32, 768 f32 and
+//    1,024 bf16 columns; at 128 entries of 768 f32 columns 22.1 ms without bounds, 10.5 with them);
+//  - 40 us more an iteration while it is not, for 30 queries and more (30 to 1,500 queries, pools of 10 to 96: 40 to
+//    80; 200 queries of 1,024 bf16 columns, 16 iterations: 1.16 ms and 0.40), and 8 us for fewer (one query, 128 iterations:
+//    2.35 ms and 0.89).
 bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters) {
     if (!ix->bd_mem || g_ap_debug.search_bounds == 1 || nq < 1) return false;
     const double n = (double)ix->docs.n;
@@ -814,7 +816,7 @@ bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, 
     double iters = (double)beam / width;
     if (max_iters > 0) iters = std::min(iters, (double)max_iters);
     const double reached = n * (1.0 - exp(-iters * width * (double)ix->params.degree / n));
-    return std::max((double)nq * reached * 0.15e-3, iters * 8.0) > ap_bound_cost(ix, nq);
+    return std::max((double)nq * reached * 0.22e-3, iters * (nq >= 30 ? 40.0 : 8.0)) > ap_bound_cost(ix, nq);
 }
 
 // Queries per slab when `cap_words` words are available: as many as fit, then evened out over the slabs.

@@ -1,0 +1,56 @@
+"""The terms without a column of their own (the tail) in the bounds' table: where a query's list of them ends (32 entries at once, 128 in
+all, then straight from the query), where a bucket of a tile's postings holds more entries than are read at once, at the edges of the
+tiles, and the counts of required terms beside the values."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00855_amd import binding as B
+from paper_2511_00855_amd.synth import VecSet
+from test_gpu_bounds import _slack
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(rng, rows, lengths, lo, vocab):
+    """CSR of lengths[r] distinct terms of lo .. vocab a row, ascending, with values of both signs."""
+    idx = [np.sort(rng.choice(np.arange(lo, vocab, dtype=np.int32), k, replace=False)) for k in lengths]
+    ip = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    return ip, np.concatenate(idx).astype(np.int32), rng.standard_normal(int(ip[-1])).astype(np.float32)
+
+
+# few terms (every bucket holds many documents) and many; queries of no tail at all up to more than a list of 128 takes
+@pytest.mark.parametrize("n,vocab,doc_terms", [(1, 700, 3), (256, 700, 60), (257, 4000, 90), (511, 700, 200), (600, 20_000, 150)])
+def test_tail_of_every_length(n, vocab, doc_terms):
+    rng, dim = np.random.default_rng(n + vocab), 64
+    lengths = [0, 1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 127, 128, 129, 130, 200, 300, 500] * 15   # 270 queries: two tiles
+    nq = len(lengths)
+    def vecs(m, sp, tx):
+        tx = (tx[0], tx[1], rng.integers(1, 4, len(tx[1])).astype(np.float32))
+        return VecSet(m, dim, rng.standard_normal((m, dim)).astype(np.float32) / 8, *sp, *tx, vocab, vocab)
+    few = np.maximum(rng.integers(0, doc_terms, (2, n)), np.arange(n) % 2 == 0)
+    docs = vecs(n, _lists(rng, n, few[0], 0, vocab), _lists(rng, n, few[1], 0, vocab))
+    queries = vecs(nq, _lists(rng, nq, lengths, 0, vocab), _lists(rng, nq, lengths[::-1], 0, vocab))
+    d, q = B.DeviceVecs(docs), B.DeviceVecs(queries)
+    ix = B.Index.ingest(d, B.build_params(8))
+    for pw in (np.ones((nq, 3)), rng.uniform(-1.0, 1.0, (nq, 3))):
+        pw = pw.astype(np.float32)
+        sc = ix.hybrid_scores(q, np.tile(np.arange(n, dtype=np.int32), (nq, 1)), pw)[:, :, 3].double()
+        up = ix.stage_score_bounds(q, pw).double()
+        assert (up >= sc).all()
+        assert (up - sc <= _slack(ix, queries, docs, pw, False)).all()
+    # required terms: those that few documents hold have no column, and the entries count them
+    df = np.bincount(docs.tx_idx, minlength=vocab) + np.zeros(vocab)
+    both = np.sort(np.concatenate([df, np.bincount(docs.sp_idx, minlength=vocab)]))[::-1]
+    rare = np.flatnonzero((df > 0) & (df < (both[512] if len(both) > 512 else 0) / 2))
+    if len(rare):
+        kw = rng.choice(rare, (nq, 16)).astype(np.int32)
+        kw[:, 12:] = -1
+        kw[::3, 3] = vocab + 5
+        held = np.zeros((n, vocab), np.int32)
+        held[np.repeat(np.arange(n), np.diff(docs.tx_indptr)), docs.tx_idx] = 1
+        want = sum(np.where((kw[:, j] >= 0) & (kw[:, j] < vocab), held[:, np.clip(kw[:, j], 0, vocab - 1)], 0).T for j in range(16))
+        with_kw = ix.stage_score_bounds(q, pw, torch.from_numpy(kw).cuda())
+        assert np.array_equal((with_kw.view(torch.int32) & 31).cpu().numpy(), want)
+        assert ((with_kw.view(torch.int32) & ~31).view(torch.float32).double() >= sc).all()
+    ix.close()
