@@ -256,14 +256,10 @@ int ap_ingest_impl(ap_index *ix, int bounds_share, hipStream_t st) {
     AP_REQUIRE(found[0] == 0, "the corpus CSR is malformed in %d places (row offsets must ascend from 0 to the total; term ids strictly "
                "ascending within a row and inside the vocabulary; values finite, term counts not negative)", found[0]);
     AP_REQUIRE(found[1] < 65536, "a document list has %d entries; at most 65535 per part are supported", found[1]);
-    AP_TRY(ap_dev_alloc(&ix->tx_w, (size_t)last));
-    AP_TRY(ap_dev_alloc(&ix->df, (size_t)c.tx_vocab));
-    AP_TRY(ap_dev_alloc(&ix->self_sim, (size_t)c.n));
-    AP_TRY(ap_dev_alloc(&ix->dense_norm, (size_t)c.n));
-    AP_TRY(ap_dev_alloc(&ix->w_dev, 4));
-    AP_TRY(ap_dev_alloc(&ix->counters, 2));
-    AP_TRY(ap_fill_u32(ix->counters, 4, 0u, st));
-    AP_TRY(ap_fill_u32(ix->df, (size_t)c.tx_vocab, 0, st));
+    AP_TRY(ap_dev_alloc_parts(&ix->mem_ingest, {AP_PART(ix->counters, 32), AP_PART(ix->df, c.tx_vocab), AP_PART(ix->tx_w, last), AP_PART(ix->self_sim, c.n),
+                                                AP_PART(ix->dense_norm, c.n), AP_PART(ix->w_dev, 4), AP_PART(ix->meta, c.n),
+                                                AP_PART(ix->rec, last + sp_last + 1)}));   // one spare entry: the scorers read a record's first entry unconditionally
+    AP_TRY(ap_fill_u32(ix->counters, 64 + (size_t)c.tx_vocab, 0u, st));   // and the frequencies behind them
     AP_TRY(ap_fill_u32(ix->stats, 4, 0, st));
     unsigned long long *total = reinterpret_cast<unsigned long long *>(ix->stats + 2);
     AP_TRY(ap_count_terms(c.tx_idx, c.tx_tf, last, ix->df, total, st));
@@ -284,8 +280,6 @@ int ap_ingest_impl(ap_index *ix, int bounds_share, hipStream_t st) {
         AP_CHECK_HIP(hipGetLastError());
     }
     {
-        AP_TRY(ap_dev_alloc(&ix->rec, (size_t)(last + sp_last) + 1));   // one spare entry: the scorers read a record's first entry unconditionally
-        AP_TRY(ap_dev_alloc(&ix->meta, (size_t)c.n));
         int64_t waves = c.n < 16384 ? c.n : 16384;
         hipLaunchKernelGGL(k_pack_records, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, ix->docs, ix->dense_norm, ix->rec, ix->meta);
         AP_CHECK_HIP(hipGetLastError());
@@ -323,8 +317,8 @@ extern "C" int ap_ingest(const ap_corpus *corpus, const ap_build_params *params,
 
 extern "C" void ap_free_index(ap_index *ix) {
     if (!ix) return;
-    void *ptrs[] = {ix->kg_en_ip, ix->kg_en, ix->kg_le, ix->kg_le_count, ix->st_se, ix->st_sorted, ix->st_spi, ix->st_sps, ix->deleted, ix->deleted_bad, ix->counters, ix->tx_w, ix->df, ix->stats, ix->self_sim, ix->graph, ix->kw, ix->kw_count, ix->entry, ix->visited, ix->w_dev,
-                    ix->search_counts, ix->dense_norm, ix->rec, ix->meta, ix->bd_mem};
+    void *ptrs[] = {ix->kg_en_ip, ix->kg_en, ix->kg_le, ix->kg_le_count, ix->mem_state, ix->deleted, ix->deleted_bad, ix->stats, ix->mem_graph, ix->mem_ingest, ix->visited,
+                    ix->search_counts, ix->bd_mem};
     ap_bound_release(ix);
     for (void *p : ptrs) if (p) (void)hipFree(p);
     for (hipEvent_t e : ix->ev_search) if (e) (void)hipEventDestroy(e);
@@ -352,11 +346,8 @@ extern "C" int ap_export_ingest(const ap_index *ix, float *tx_w, int32_t *df, fl
 
 int ap_alloc_graph(ap_index *ix) {
     const size_t n = (size_t)ix->corpus.n, R = (size_t)ix->params.degree;
-    if (!ix->graph) AP_TRY(ap_dev_alloc(&ix->graph, n * R));
-    if (!ix->kw) AP_TRY(ap_dev_alloc(&ix->kw, n * (R / 2)));
-    if (!ix->kw_count) AP_TRY(ap_dev_alloc(&ix->kw_count, n));
-    if (!ix->entry) AP_TRY(ap_dev_alloc(&ix->entry, (size_t)ix->params.n_entry));
-    return AP_OK;
+    if (ix->mem_graph) return AP_OK;
+    return ap_dev_alloc_parts(&ix->mem_graph, {AP_PART(ix->graph, n * R), AP_PART(ix->kw, n * (R / 2)), AP_PART(ix->kw_count, n), AP_PART(ix->entry, ix->params.n_entry)});
 }
 
 // An imported graph comes from outside: every id must be -1 (padding) or a document, every keyword count within

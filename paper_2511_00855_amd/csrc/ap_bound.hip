@@ -854,6 +854,15 @@ size_t ap_bound_held(const ap_index *ix, hipStream_t st) {
         if (ix->bd_pool->ws[i].stream == st) return ix->bd_pool->ws[i].bytes;
     return 0;
 }
+// The same memory as scratch for what comes behind the search on its stream, where nothing else searches the index (an insertion's new one).
+ApWork ap_bound_borrow(const ap_index *ix, hipStream_t st) {
+    ApWork w;
+    if (!ix->bd_pool) return w;
+    std::lock_guard<std::mutex> hold(ix->bd_pool->lock);
+    for (int i = 0; i < ix->bd_pool->used; i++)
+        if (ix->bd_pool->ws[i].stream == st && ix->bd_pool->ws[i].mem) { w.mem = ix->bd_pool->ws[i].mem; w.bytes = ix->bd_pool->ws[i].bytes; }
+    return w;
+}
 void ap_bound_give_back(const ap_index *ix, hipStream_t st) {
     if (!ix->bd_pool) return;
     std::lock_guard<std::mutex> hold(ix->bd_pool->lock);

@@ -826,7 +826,7 @@ static int ap_seed_knn_symmetric(const ap_index *ix, int32_t K, bool rounded, in
 // number of candidates) is redone by the exact path.  Whole corpora take the
 // symmetric sweeps where they apply.
 int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, int32_t K, int32_t *out_ids,
-                         float *out_sc, hipStream_t st, ApSeedRelax *relax) {
+                         float *out_sc, hipStream_t st, ApSeedRelax *relax, const ApWork &work) {
     const int64_t n = ix->docs.n;
     int64_t cs = std::max<int64_t>(16384, (n + 63) / 64);
     if (g_ap_debug.seed_sample_cols > 0) cs = std::max<int64_t>(K + 1, g_ap_debug.seed_sample_cols);
@@ -844,11 +844,13 @@ int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, in
         if (rc != AP_OK || done) return rc;
     }
     if (n < 2 * cs) {
-        float *scratch = nullptr;
-        AP_TRY(ap_dev_alloc(&scratch, (size_t)ex_rows * (size_t)n));
+        float *own = nullptr, *scratch = work.take<float>((size_t)ex_rows * (size_t)n);
+        if (!scratch) { AP_TRY(ap_dev_alloc(&own, (size_t)ex_rows * (size_t)n)); scratch = own; }
         e = seed_exact_rows(ix, node_ids, 0, nn, K, scratch, ex_rows, out_ids, out_sc, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        (void)hipFree(scratch);
+        if (own) {
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            (void)hipFree(own);
+        }
         if (e != hipSuccess) { ap_set_error("seed k-NN failed: %s", hipGetErrorString(e)); return AP_EHIP; }
         return AP_OK;
     }
@@ -956,22 +958,27 @@ extern "C" int ap_stage_seed_knn(const ap_index *ix, const int32_t *node_ids, in
     if (!node_ids) nn = ix->docs.n;
     AP_REQUIRE(nn >= 0, "nn is negative");
     if (nn == 0) return AP_OK;
-    return ap_seed_knn_impl(ix, node_ids, nn, K, out_ids, out_scores, (hipStream_t)stream);
+    return ap_seed_knn_impl(ix, node_ids, nn, K, out_ids, out_scores, (hipStream_t)stream, nullptr, ApWork());
+}
+
+int ap_entry_points_impl(const ap_index *ix, int32_t E, int32_t *out_entry, hipStream_t st, const ApWork &work) {
+    float *own = nullptr, *sc = work.take<float>((size_t)E);
+    if (!sc) { AP_TRY(ap_dev_alloc(&own, (size_t)E)); sc = own; }
+    hipLaunchKernelGGL(k_select_rows, dim3(1), dim3(256), 0, st, ix->self_sim, ix->docs.n, E, (const int32_t *)nullptr,
+                       (int64_t)0, 0, (int64_t)0, out_entry, sc);
+    hipError_t e = hipGetLastError();
+    if (own) {
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        (void)hipFree(own);
+    }
+    if (e != hipSuccess) { ap_set_error("entry point selection failed: %s", hipGetErrorString(e)); return AP_EHIP; }
+    return AP_OK;
 }
 
 extern "C" int ap_stage_entry_points(const ap_index *ix, int32_t E, int32_t *out_entry, void *stream) {
     AP_REQUIRE(ix && out_entry, "NULL argument");
     AP_REQUIRE(E >= 1 && E <= 256, "E = %d must be in [1, 256]", E);
-    hipStream_t st = (hipStream_t)stream;
-    float *sc = nullptr;
-    AP_TRY(ap_dev_alloc(&sc, (size_t)E));
-    hipLaunchKernelGGL(k_select_rows, dim3(1), dim3(256), 0, st, ix->self_sim, ix->docs.n, E, (const int32_t *)nullptr,
-                       (int64_t)0, 0, (int64_t)0, out_entry, sc);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(sc);
-    if (e != hipSuccess) { ap_set_error("entry point selection failed: %s", hipGetErrorString(e)); return AP_EHIP; }
-    return AP_OK;
+    return ap_entry_points_impl(ix, E, out_entry, (hipStream_t)stream, ApWork());
 }
 
 // =================================================================== S3: refinement round
@@ -1680,14 +1687,16 @@ int ap_refine_round(const ap_index *ix, int32_t K, int32_t S, int32_t P, const i
 }
 
 // The refinement rounds of a construction: from the exact dense seed lists (ids[0], sc[0]; seed_slack != NULL: their scores but the K-th are within that) of all n = ix->docs.n documents
-// and empty per-path lists (spi[0], sps[0]).  Returns in *cur which of the two buffers holds the result.
+// and empty per-path lists (spi[0], sps[0]).  Returns in *cur which of the two buffers holds the result (rounds % 2), in *later what
+// is to be freed once the rounds are over.
 int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
-                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st, const float *seed_slack) {
+                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st, const float *seed_slack, const ApWork &work, void **later) {
     const int64_t n = ix->docs.n;
     *cur = 0;
     if (rounds <= 0) return AP_OK;
-    float *tau = nullptr;   // n, then the two sets of n words of known bits
-    int rc = ap_dev_alloc(&tau, (size_t)3 * n);
+    float *own = nullptr, *tau = work.take<float>((size_t)3 * n);   // n, then the two sets of n words of known bits
+    int rc = AP_OK;
+    if (!tau) { rc = ap_dev_alloc(&own, (size_t)3 * n); tau = own; }
     uint32_t *known[2] = {reinterpret_cast<uint32_t *>(tau + n), reinterpret_cast<uint32_t *>(tau + 2 * n)};
     if (rc == AP_OK) {
         hipLaunchKernelGGL(k_take_tau, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc[0], n, K, 0u, tau);
@@ -1703,7 +1712,8 @@ int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, i
         rc = ap_refine_round(ix, K, S, P, ids[c], spi[c], sps[c], nullptr, n, ids[1 - c], sc[1 - c], spi[1 - c], sps[1 - c], hint, st);
         *cur = 1 - c;
     }
-    void *ptrs[] = {tau, pk.mem};
+    if (later && pk.bytes <= AP_WORK_BYTES) { *later = pk.mem; pk.mem = nullptr; }
+    void *ptrs[] = {own, pk.mem};
     for (void *p : ptrs) if (p) (void)hipFree(p);   // waits for the rounds
     return rc;
 }
@@ -2653,11 +2663,11 @@ __global__ __launch_bounds__(256, 6) void k_detour_prune(ApVecs D, const float *
 
 int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_ids, const float *knn_sc,
                       const int32_t *node_ids, int64_t nn, float *pm_out, int32_t *count, int32_t *sorted_ids,
-                      int32_t *se, int32_t *ke, int32_t *ke_count, int32_t *flag, hipStream_t st) {
+                      int32_t *se, int32_t *ke, int32_t *ke_count, int32_t *flag, hipStream_t st, const ApWork &work) {
     const int64_t per = (int64_t)K * K;
     int64_t chunk = pm_out ? nn : std::min<int64_t>(nn, std::max<int64_t>(1, ((int64_t)1 << 28) / per));
-    float *scratch = nullptr;
-    if (!pm_out) AP_TRY(ap_dev_alloc(&scratch, (size_t)chunk * (size_t)per));
+    float *own = nullptr, *scratch = pm_out ? nullptr : work.take<float>((size_t)chunk * (size_t)per);
+    if (!pm_out && !scratch) { AP_TRY(ap_dev_alloc(&own, (size_t)chunk * (size_t)per)); scratch = own; }
     const float *w = ix->params.build_w;
     const int32_t tiles = (K + AP_TILE - 1) / AP_TILE;
     hipError_t e = hipSuccess;
@@ -2693,8 +2703,10 @@ int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_i
                            knn_sc, node_ids, x0, x0, pm, count, sorted_ids, se, ke, ke_count, flag, ix->params.prune_mode);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (scratch) (void)hipFree(scratch);
+    if (own || pm_out || !work.mem) {
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (own) (void)hipFree(own);
+    }
     if (e != hipSuccess) { ap_set_error("prune stage failed: %s", hipGetErrorString(e)); return AP_EHIP; }
     return AP_OK;
 }
@@ -2706,7 +2718,7 @@ extern "C" int ap_stage_prune(const ap_index *ix, int32_t K, int32_t R, const in
     AP_REQUIRE(K >= 1 && K <= 256 && R >= 2 && R <= 128, "need 1<=K<=256, 2<=R<=128");
     if (!node_ids) nn = ix->docs.n;
     if (nn <= 0) return AP_OK;
-    return ap_prune_impl(ix, K, R, knn_ids, knn_sc, node_ids, nn, pm, count, sorted_ids, se, ke, ke_count, flag, (hipStream_t)stream);
+    return ap_prune_impl(ix, K, R, knn_ids, knn_sc, node_ids, nn, pm, count, sorted_ids, se, ke, ke_count, flag, (hipStream_t)stream, ApWork());
 }
 
 // =================================================================== S6: assembly
@@ -2787,11 +2799,11 @@ __global__ __launch_bounds__(256) void k_assemble(int64_t n, int32_t R, int32_t 
 }
 
 int ap_assemble_impl(const ap_index *ix, int32_t R, int32_t K, int32_t P, const int32_t *se, const int32_t *sorted_ids,
-                         const int32_t *sp_ids, int32_t *out_graph, hipStream_t st) {
+                         const int32_t *sp_ids, int32_t *out_graph, hipStream_t st, const ApWork &work) {
     const int64_t n = ix->docs.n;
     const int32_t q = R / 4;
-    unsigned long long *rev = nullptr;
-    AP_TRY(ap_dev_alloc(&rev, (size_t)n * (size_t)q));
+    unsigned long long *own = nullptr, *rev = work.take<unsigned long long>((size_t)n * (size_t)q);
+    if (!rev) { AP_TRY(ap_dev_alloc(&own, (size_t)n * (size_t)q)); rev = own; }
     int rc = ap_fill_u32(rev, (size_t)n * q * 2, 0xffffffffu, st);
     hipError_t e = hipSuccess;
     if (rc == AP_OK) {
@@ -2809,9 +2821,9 @@ int ap_assemble_impl(const ap_index *ix, int32_t R, int32_t K, int32_t P, const 
                 e = hipGetLastError();
             }
         }
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (own && e == hipSuccess) e = hipStreamSynchronize(st);
     }
-    (void)hipFree(rev);
+    if (own) (void)hipFree(own);
     if (rc != AP_OK) return rc;
     if (e != hipSuccess) { ap_set_error("assemble stage failed: %s", hipGetErrorString(e)); return AP_EHIP; }
     return AP_OK;
@@ -2821,7 +2833,7 @@ extern "C" int ap_stage_assemble(const ap_index *ix, int32_t R, int32_t K, int32
                                  const int32_t *sorted_ids, const int32_t *sp_ids, int32_t *out_graph, void *stream) {
     AP_REQUIRE(ix && se && sorted_ids && sp_ids && out_graph, "NULL argument");
     AP_REQUIRE(R >= 4 && R % 4 == 0 && R <= 128 && K >= 1 && K <= 256 && P >= 1 && P <= 32, "need R%%4==0, 4<=R<=128, 1<=K<=256, 1<=P<=32");
-    return ap_assemble_impl(ix, R, K, P, se, sorted_ids, sp_ids, out_graph, (hipStream_t)stream);
+    return ap_assemble_impl(ix, R, K, P, se, sorted_ids, sp_ids, out_graph, (hipStream_t)stream, ApWork());
 }
 
 // =================================================================== the whole build
@@ -2866,13 +2878,25 @@ struct BuildBufs {
     int32_t *spi[2] = {nullptr, nullptr};
     float *sps[2] = {nullptr, nullptr};
     int32_t *se = nullptr, *sorted = nullptr;
+    ApWork work;
     float *slack = nullptr;   // of the seed lists' scores
+    void *mem = nullptr, *state = nullptr, *packed = nullptr;   // what is given back at the end; what the index keeps; the packed lists
     void release() {
-        void *p[] = {slack, knn[0], knn[1], knn_sc[0], knn_sc[1], spi[0], spi[1], sps[0], sps[1], se, sorted};
+        void *p[] = {slack, packed, mem, state};
         for (void *x : p) if (x) (void)hipFree(x);
         *this = BuildBufs();
     }
 };
+
+// Bytes of the scratch that a construction's stages after ingest take one after the other: those of the refinement, the assembly and the
+// entry points, and of the exact seed lists and the neighbourhood similarities where they are small.
+static size_t build_work_bytes(const ap_build_params &p, int64_t n) {
+    const size_t K = (size_t)p.knn_k, N = (size_t)n, seed = (N + AP_TILE - 1) / AP_TILE * AP_TILE * N * 4, pm = N * K * K * 4;
+    size_t most = std::max({N * 12, N * (size_t)(p.degree / 4) * 8, (size_t)p.n_entry * 4});
+    if (seed <= AP_WORK_BYTES) most = std::max(most, seed);
+    if (pm <= AP_WORK_BYTES) most = std::max(most, pm);
+    return most;
+}
 
 static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
     const ap_build_params &p = ix->params;
@@ -2885,34 +2909,31 @@ static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
     AP_CHECK_HIP(mark(0));
     AP_TRY(ap_ingest_impl(ix, 64, st));
     AP_CHECK_HIP(mark(1));
-    for (int i = 0; i < 2; i++) {
-        AP_TRY(ap_dev_alloc(&b.knn[i], (size_t)n * K));
-        AP_TRY(ap_dev_alloc(&b.knn_sc[i], (size_t)n * K));
-        AP_TRY(ap_dev_alloc(&b.spi[i], (size_t)3 * n * P));
-        AP_TRY(ap_dev_alloc(&b.sps[i], (size_t)3 * n * P));
-    }
-    AP_TRY(ap_dev_alloc(&b.se, (size_t)n * R));
-    AP_TRY(ap_dev_alloc(&b.sorted, (size_t)n * K));
+    const int kept = p.nd_rounds & 1;   // which of the per-path lists the rounds end with
+    b.work.bytes = build_work_bytes(p, n);
+    AP_TRY(ap_dev_alloc_parts(&b.state, {AP_PART(b.se, n * R), AP_PART(b.sorted, n * K), AP_PART(b.spi[kept], 3 * n * P), AP_PART(b.sps[kept], 3 * n * P)}));
+    AP_TRY(ap_dev_alloc_parts(&b.mem, {AP_PART(b.knn[0], n * K), AP_PART(b.knn[1], n * K), AP_PART(b.knn_sc[0], n * K), AP_PART(b.knn_sc[1], n * K),
+                                       AP_PART(b.spi[1 - kept], 3 * n * P), AP_PART(b.sps[1 - kept], 3 * n * P), ApPart{&b.work.mem, b.work.bytes}}));
     AP_TRY(ap_alloc_graph(ix));
     ap_progress("ingest done; seed lists of %lld documents", (long long)n);
     // the rounds read the lists' members, the first nd_sample of them as a set, and bounds of their scores
     ApSeedRelax relax;
     relax.top = std::min(K, p.nd_sample);
-    AP_TRY(ap_seed_knn_impl(ix, nullptr, n, K, b.knn[0], b.knn_sc[0], st, p.nd_rounds > 0 ? &relax : nullptr));
+    AP_TRY(ap_seed_knn_impl(ix, nullptr, n, K, b.knn[0], b.knn_sc[0], st, p.nd_rounds > 0 ? &relax : nullptr, b.work));
     b.slack = relax.slack;
     ap_progress("seed lists done; %d refinement rounds, pruning, assembly", p.nd_rounds);
     AP_CHECK_HIP(mark(2));
     AP_TRY(ap_fill_u32(b.spi[0], (size_t)3 * n * P, 0xffffffffu, st));          // id -1
     AP_TRY(ap_fill_u32(b.sps[0], (size_t)3 * n * P, 0xff800000u, st));          // -inf
     int cur = 0;
-    AP_TRY(ap_refine_rounds(ix, p.nd_rounds, K, p.nd_sample, P, b.knn, b.knn_sc, b.spi, b.sps, &cur, st, b.slack));
+    AP_TRY(ap_refine_rounds(ix, p.nd_rounds, K, p.nd_sample, P, b.knn, b.knn_sc, b.spi, b.sps, &cur, st, b.slack, b.work, &b.packed));
     if (p.nd_rounds == 0) AP_TRY(ap_rescore_lists(ix, n, K, b.knn[cur], b.knn_sc[cur], st));
     AP_CHECK_HIP(mark(3));
     AP_TRY(ap_prune_impl(ix, K, R, b.knn[cur], b.knn_sc[cur], nullptr, n, nullptr, nullptr, b.sorted, b.se, ix->kw, ix->kw_count,
-                      nullptr, st));
+                      nullptr, st, b.work));
     AP_CHECK_HIP(mark(4));
-    AP_TRY(ap_assemble_impl(ix, R, K, P, b.se, b.sorted, b.spi[cur], ix->graph, st));
-    AP_TRY(ap_stage_entry_points(ix, p.n_entry, ix->entry, st));
+    AP_TRY(ap_assemble_impl(ix, R, K, P, b.se, b.sorted, b.spi[cur], ix->graph, st, b.work));
+    AP_TRY(ap_entry_points_impl(ix, p.n_entry, ix->entry, st, b.work));
     AP_CHECK_HIP(mark(5));
     AP_CHECK_HIP(hipStreamSynchronize(st));
     float total = 0.f;
@@ -2925,7 +2946,8 @@ static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {
     ix->has_graph = true;
     // kept for later insertions
     ix->st_se = b.se; ix->st_sorted = b.sorted; ix->st_spi = b.spi[cur]; ix->st_sps = b.sps[cur];
-    b.se = nullptr; b.sorted = nullptr; b.spi[cur] = nullptr; b.sps[cur] = nullptr;
+    ix->mem_state = b.state;
+    b.state = nullptr;
     ix->timings[5] = total;
     if (ix->bd_mem) return AP_OK;
     // Columns of the bounds that are more than a small part (1/64) of the free memory come when the construction's own memory

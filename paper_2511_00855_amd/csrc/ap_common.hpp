@@ -67,6 +67,8 @@ struct ap_index {
     mutable int seed_bf16 = 0;                     // 1: the last seed stage's products over the whole corpus took bf16 rows (stored or rounded)
     mutable int packed_lists = 0;                  // 1: the last refinement rounds had packed lists
     mutable unsigned long long seed_flops = 0;   // FLOPs (2 per multiply-add, padded tiles included) of the seed stage's dense products so far
+    // owned: what ingest, the graph and the construction's state are parts of
+    void *mem_ingest = nullptr, *mem_graph = nullptr, *mem_state = nullptr;
     float *stats = nullptr;    // owned: [0] avgdl
     float *self_sim = nullptr; // owned: fused self-similarity under build_w
     float *dense_norm = nullptr; // owned: |d_dense| per document (upper bound of the dense part in the search)
@@ -131,6 +133,29 @@ static inline int ap_dev_alloc(T **p, size_t count) {
     return AP_OK;
 }
 
+// Several arrays in one allocation, each at a multiple of 256 bytes; the base is what is given back.  An allocation or a free costs 10 to 60 us whatever
+// its size (0.3 ms and more in a process that has made thousands): a construction of 2,000 documents made 38 of them, half of its time.
+struct ApPart { void **p; size_t bytes; };
+static inline int ap_dev_alloc_parts(void **base, std::initializer_list<ApPart> parts) {
+    size_t all = 0;
+    for (const ApPart &a : parts) all += (a.bytes + 255) / 256 * 256;
+    char *m = nullptr;
+    AP_TRY(ap_dev_alloc(&m, all));
+    *base = m;
+    for (const ApPart &a : parts) { *a.p = m; m += (a.bytes + 255) / 256 * 256; }
+    return AP_OK;
+}
+#define AP_PART(ptr, count) ApPart{reinterpret_cast<void **>(&(ptr)), (size_t)(count) * sizeof(*(ptr))}
+
+// Memory that the stages of a construction or an insertion use one after the other, on one stream.  A stage whose scratch does not fit
+// (or that is called by itself) makes its own and waits for its end to give it back.
+struct ApWork {
+    void *mem = nullptr;
+    size_t bytes = 0;
+    template <typename T> T *take(size_t count) const { return count * sizeof(T) <= bytes ? static_cast<T *>(mem) : nullptr; }
+};
+#define AP_WORK_BYTES ((size_t)64 << 20)   // scratch beyond that is not held through the stages that do not need it
+
 // Debug settings (ap_debug_set): 0 = the library's own choice.  They exist so that tests can drive small inputs
 // through the code paths of large ones; nothing here changes a result.
 struct ApDebug {
@@ -186,14 +211,15 @@ int ap_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
 // how much the scores may be off (an allocation of a float per document that the caller frees), NULL: not at all
 struct ApSeedRelax { int32_t top = 0; float *slack = nullptr; };
 int ap_seed_knn_impl(const ap_index *ix, const int32_t *node_ids, int64_t nn, int32_t K, int32_t *out_ids, float *out_sc,
-                     hipStream_t st, ApSeedRelax *relax = nullptr);
+                     hipStream_t st, ApSeedRelax *relax, const ApWork &work);
 int ap_prune_impl(const ap_index *ix, int32_t K, int32_t R, const int32_t *knn_ids, const float *knn_sc, const int32_t *node_ids,
                   int64_t nn, float *pm_out, int32_t *count, int32_t *sorted_ids, int32_t *se, int32_t *ke, int32_t *ke_count,
-                  int32_t *flag, hipStream_t st);
+                  int32_t *flag, hipStream_t st, const ApWork &work);
 int ap_assemble_impl(const ap_index *ix, int32_t R, int32_t K, int32_t P, const int32_t *se, const int32_t *sorted_ids,
-                     const int32_t *sp_ids, int32_t *out_graph, hipStream_t st);
+                     const int32_t *sp_ids, int32_t *out_graph, hipStream_t st, const ApWork &work);
+int ap_entry_points_impl(const ap_index *ix, int32_t E, int32_t *out_entry, hipStream_t st, const ApWork &work);
 int ap_refine_rounds(const ap_index *ix, int32_t rounds, int32_t K, int32_t S, int32_t P, int32_t *const ids[2], float *const sc[2],
-                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st, const float *seed_slack = nullptr);
+                     int32_t *const spi[2], float *const sps[2], int *cur, hipStream_t st, const float *seed_slack, const ApWork &work, void **later);
 int ap_rescore_lists(const ap_index *ix, int64_t nn, int32_t K, const int32_t *knn, float *sc, hipStream_t st);
 // Upper bounds of the fused scores of a slab of queries against every document (ap_bound.hip).
 struct ApBound {
@@ -252,6 +278,7 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st);
 size_t ap_bound_bytes(const ap_index *ix, int64_t nq, int tables);
 void ap_bound_release(ap_index *ix);
 void ap_bound_place(const ap_index *ix, void *base, int64_t nq, int tables, ApBound *b);
+ApWork ap_bound_borrow(const ap_index *ix, hipStream_t st);
 size_t ap_bound_held(const ap_index *ix, hipStream_t st);
 void ap_bound_give_back(const ap_index *ix, hipStream_t st);
 // An allocation that a call on stream st cannot do without: where it fails, the stream's workspace of bounds makes room.

@@ -17,7 +17,6 @@
 extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t P, const int32_t *knn_ids,
                                const int32_t *sp_ids, const float *sp_sc, const int32_t *node_ids, int64_t nn,
                                int32_t *out_ids, float *out_sc, int32_t *out_sp_ids, float *out_sp_sc, void *stream);
-extern "C" int ap_stage_entry_points(const ap_index *index, int32_t E, int32_t *out_entry, void *stream);
 extern "C" void ap_free_index(ap_index *ix);
 
 // ids >= 0 move up by `shift` (lists computed on the new documents alone use local ids)
@@ -60,15 +59,11 @@ __global__ __launch_bounds__(512) void k_merge_ranked(int32_t K, const int32_t *
 
 namespace {
 struct InsertBufs {
-    void *all[32];
-    int n = 0;
-    template <typename T> int get(T **p, size_t count) {
-        const int rc = ap_dev_alloc(p, count);
-        if (rc == AP_OK) all[n++] = *p;
-        return rc;
+    void *mem = nullptr, *state = nullptr, *packed = nullptr;   // scratch, what the index keeps, the packed lists
+    ~InsertBufs() {
+        void *all[] = {mem, state, packed};
+        for (void *p : all) if (p) (void)hipFree(p);
     }
-    void keep(void *p) { for (int i = 0; i < n; i++) if (all[i] == p) all[i] = nullptr; }
-    ~InsertBufs() { for (int i = 0; i < n; i++) if (all[i]) (void)hipFree(all[i]); }
 };
 
 unsigned grid_for(size_t n) { return (unsigned)std::min<size_t>((n + 255) / 256, 8192); }
@@ -98,15 +93,19 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
     AP_TRY(ap_fill_u32(nx->graph + (size_t)n0 * R, (size_t)m * R, 0xffffffffu, st));
     AP_COPY(nx->entry, old->entry, p.n_entry, int32_t);
     nx->has_graph = true;
-    int32_t *c1_ids = nullptr, *c2_ids = nullptr, *spi2[2] = {nullptr, nullptr}, *new_ids = nullptr;
-    float *c1_sc = nullptr, *c2_sc = nullptr, *sps2[2] = {nullptr, nullptr}, *w_dev = nullptr, *qdense = nullptr;
-    AP_TRY(B.get(&c1_ids, (size_t)m * K));
-    AP_TRY(B.get(&c1_sc, (size_t)m * K));
-    AP_TRY(B.get(&w_dev, 4));
+    int32_t *c1_ids = nullptr, *c2_ids = nullptr, *spi2[2] = {nullptr, nullptr}, *new_ids = nullptr, *knn = nullptr, *spi = nullptr, *se = nullptr, *sorted = nullptr,
+            *f_ids = nullptr, *f_spi = nullptr, *r_ids[2] = {nullptr, nullptr};
+    float *c1_sc = nullptr, *c2_sc = nullptr, *sps2[2] = {nullptr, nullptr}, *w_dev = nullptr, *qdense = nullptr, *knn_sc = nullptr, *sps = nullptr, *f_sc = nullptr,
+          *f_sps = nullptr, *r_sc[2] = {nullptr, nullptr};
+    AP_TRY(ap_dev_alloc_parts(&B.state, {AP_PART(se, n1 * R), AP_PART(sorted, n1 * K), AP_PART(spi, 3 * n1 * P), AP_PART(sps, 3 * n1 * P)}));
+    AP_TRY(ap_dev_alloc_parts(&B.mem, {AP_PART(c1_ids, m * K), AP_PART(c1_sc, m * K), AP_PART(c2_ids, m * K), AP_PART(c2_sc, m * K), AP_PART(r_ids[1], m * K),
+                                       AP_PART(r_sc[1], m * K), AP_PART(spi2[0], 3 * m * P), AP_PART(spi2[1], 3 * m * P), AP_PART(sps2[0], 3 * m * P),
+                                       AP_PART(sps2[1], 3 * m * P), AP_PART(f_ids, m * K), AP_PART(f_sc, m * K), AP_PART(f_spi, 3 * m * P), AP_PART(f_sps, 3 * m * P),
+                                       AP_PART(knn, n1 * K), AP_PART(knn_sc, n1 * K), AP_PART(new_ids, m), AP_PART(w_dev, 4),
+                                       AP_PART(qdense, nx->dtype != AP_F32 ? m * nx->docs.dim : 0)}));
     AP_CHECK_HIP(hipMemcpyAsync(w_dev, p.build_w, 3 * sizeof(float), hipMemcpyHostToDevice, st));
     const void *qd = static_cast<const char *>(nx->docs.dense) + (size_t)n0 * nx->docs.dim * esize;
     if (nx->dtype != AP_F32) {   // the search reads its queries' dense rows as f32
-        AP_TRY(B.get(&qdense, (size_t)m * nx->docs.dim));
         hipLaunchKernelGGL(k_bf16_to_f32, dim3(grid_for((size_t)m * nx->docs.dim)), dim3(256), 0, st, static_cast<const uint16_t *>(qd),
                            qdense, (size_t)m * nx->docs.dim);
         AP_CHECK_HIP(hipGetLastError());
@@ -126,21 +125,16 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
             ap_bound_give_back(nx, st);
         }
     }
+    const ApWork work = ap_bound_borrow(nx, st);   // the search is over when the steps below use it
     nx->has_graph = false;
 
     // step 2: candidate set two -- seed lists and refinement rounds among the new documents alone, on a view of the
     // index that starts at document n0 (list offsets are absolute, so only the row-indexed arrays shift)
-    AP_TRY(B.get(&c2_ids, (size_t)m * K));
-    AP_TRY(B.get(&c2_sc, (size_t)m * K));
-    for (int i = 0; i < 2; i++) {
-        AP_TRY(B.get(&spi2[i], (size_t)3 * m * P));
-        AP_TRY(B.get(&sps2[i], (size_t)3 * m * P));
-    }
     AP_TRY(ap_fill_u32(spi2[0], (size_t)3 * m * P, 0xffffffffu, st));
     AP_TRY(ap_fill_u32(sps2[0], (size_t)3 * m * P, 0xff800000u, st));
     int cur = 0;
-    int32_t *r_ids[2] = {c2_ids, nullptr};
-    float *r_sc[2] = {c2_sc, nullptr};
+    r_ids[0] = c2_ids;
+    r_sc[0] = c2_sc;
     if (m >= 2) {
         ap_index vx = *nx;
         vx.corpus.n = m;
@@ -148,10 +142,8 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
         vx.docs.dense = static_cast<const char *>(nx->docs.dense) + (size_t)n0 * nx->docs.dim * esize;
         vx.docs.sp_indptr += n0; vx.docs.tx_indptr += n0;
         vx.self_sim += n0; vx.dense_norm += n0; vx.meta += n0;
-        AP_TRY(B.get(&r_ids[1], (size_t)m * K));
-        AP_TRY(B.get(&r_sc[1], (size_t)m * K));
-        AP_TRY(ap_seed_knn_impl(&vx, nullptr, m, K, r_ids[0], r_sc[0], st));
-        AP_TRY(ap_refine_rounds(&vx, p.nd_rounds, K, p.nd_sample, P, r_ids, r_sc, spi2, sps2, &cur, st));
+        AP_TRY(ap_seed_knn_impl(&vx, nullptr, m, K, r_ids[0], r_sc[0], st, nullptr, work));
+        AP_TRY(ap_refine_rounds(&vx, p.nd_rounds, K, p.nd_sample, P, r_ids, r_sc, spi2, sps2, &cur, st, nullptr, work, &B.packed));
         nx->packed_lists = vx.packed_lists;
         if (p.nd_rounds == 0) AP_TRY(ap_rescore_lists(&vx, m, K, r_ids[cur], r_sc[cur], st));
         hipLaunchKernelGGL(k_shift_ids, dim3(grid_for((size_t)m * K)), dim3(256), 0, st, r_ids[cur], (size_t)m * K, (int32_t)n0);
@@ -165,19 +157,6 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
 
     // step 3: the K-list of a new document = the best K of both sets; scored once more without 2-hop exploration so
     // that its per-path lists take in the list's members
-    int32_t *knn = nullptr, *spi = nullptr, *se = nullptr, *sorted = nullptr, *f_ids = nullptr, *f_spi = nullptr;
-    float *knn_sc = nullptr, *sps = nullptr, *f_sc = nullptr, *f_sps = nullptr;
-    AP_TRY(B.get(&knn, (size_t)n1 * K));
-    AP_TRY(B.get(&knn_sc, (size_t)n1 * K));
-    AP_TRY(B.get(&spi, (size_t)3 * n1 * P));
-    AP_TRY(B.get(&sps, (size_t)3 * n1 * P));
-    AP_TRY(B.get(&se, (size_t)n1 * R));
-    AP_TRY(B.get(&sorted, (size_t)n1 * K));
-    AP_TRY(B.get(&f_ids, (size_t)m * K));
-    AP_TRY(B.get(&f_sc, (size_t)m * K));
-    AP_TRY(B.get(&f_spi, (size_t)3 * m * P));
-    AP_TRY(B.get(&f_sps, (size_t)3 * m * P));
-    AP_TRY(B.get(&new_ids, (size_t)m));
     AP_TRY(ap_fill_u32(knn, (size_t)n0 * K, 0xffffffffu, st));          // rows of old documents are never read
     AP_TRY(ap_fill_u32(knn_sc, (size_t)n0 * K, 0xff800000u, st));
     const int64_t slice = AP_MAX_LAUNCH_THREADS / 512;
@@ -223,11 +202,11 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
     AP_COPY(nx->kw, old->kw, (size_t)n0 * KR, int32_t);
     AP_COPY(nx->kw_count, old->kw_count, (size_t)n0, int32_t);
     AP_TRY(ap_prune_impl(nx, K, R, knn, knn_sc, new_ids, m, nullptr, nullptr, sorted + (size_t)n0 * K, se + (size_t)n0 * R,
-                         nx->kw + (size_t)n0 * KR, nx->kw_count + n0, nullptr, st));
+                         nx->kw + (size_t)n0 * KR, nx->kw_count + n0, nullptr, st, work));
     AP_CHECK_HIP(mark(4));
     // S6 over all documents: old documents gain reverse neighbours among the new ones
-    AP_TRY(ap_assemble_impl(nx, R, K, P, se, sorted, spi, nx->graph, st));
-    AP_TRY(ap_stage_entry_points(nx, p.n_entry, nx->entry, st));
+    AP_TRY(ap_assemble_impl(nx, R, K, P, se, sorted, spi, nx->graph, st, work));
+    AP_TRY(ap_entry_points_impl(nx, p.n_entry, nx->entry, st, work));
     AP_CHECK_HIP(mark(5));
     if (old->deleted) {   // marks of deletion carry over (bits past n0 in the old last word were never set)
         const size_t w0 = ((size_t)n0 + 31) / 32, w1 = ((size_t)n1 + 31) / 32;
@@ -248,7 +227,8 @@ static int insert_impl(const ap_index *old, ap_index *nx, int32_t beam, int boun
     nx->timings[5] = total;
     nx->has_graph = true;
     nx->st_se = se; nx->st_sorted = sorted; nx->st_spi = spi; nx->st_sps = sps;
-    B.keep(se); B.keep(sorted); B.keep(spi); B.keep(sps);
+    nx->mem_state = B.state;
+    B.state = nullptr;
     return AP_OK;
 }
 

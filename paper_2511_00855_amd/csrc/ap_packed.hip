@@ -109,6 +109,7 @@ int ap_pack_lists(const ap_index *ix, hipStream_t st, ApPacked *out) {
     void *mem = nullptr;
     if (hipMalloc(&mem, bytes) != hipSuccess) { (void)hipGetLastError(); return AP_OK; }
     out->mem = mem;
+    out->bytes = bytes;
     char *m = static_cast<char *>(mem);
     uint32_t *rec = reinterpret_cast<uint32_t *>(m);
     uint2 *at = reinterpret_cast<uint2 *>(m + o_at);

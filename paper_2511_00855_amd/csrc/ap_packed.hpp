@@ -21,6 +21,7 @@
 __host__ __device__ static inline int64_t ap_pk_line(int64_t entries_before, int64_t v) { return (3 * entries_before + 96 * v + AP_PK_LINE - 1) / AP_PK_LINE; }
 
 struct ApPacked {
+    size_t bytes = 0;
     void *mem = nullptr;             // one allocation; NULL: no packed lists
     const uint32_t *rec = nullptr;
     const uint2 *at = nullptr;       // per document: its line, units of either list (16 bits each)
