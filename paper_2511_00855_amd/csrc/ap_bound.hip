@@ -409,6 +409,116 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
     }
 }
 
+// The tail of one query and one tile's documents, by eight lanes (sub: which of them): what its additions wait for is asked for early, its terms and then
+// where their buckets lie, the first entries of all buckets at once.  row: its AP_BOUND_QT entries in LDS, which no other wave touches.
+struct ApTailJoin {
+    const uint32_t *start;
+    const uint2 *post;
+    int bits, sub;
+    uint2 term[AP_BOUND_TERMS], first;
+    uint32_t at[AP_BOUND_TERMS], to[AP_BOUND_TERMS];
+    __device__ __forceinline__ ApTailJoin(const ApBoundTail &tail, int64_t dt, int sub_)
+        : start(tail.start + dt * ((1 << tail.bits) + 1)), post(tail.post + tail.sp_indptr[dt * AP_BOUND_QT] + tail.tx_indptr[dt * AP_BOUND_QT]), bits(tail.bits), sub(sub_) {}
+    __device__ __forceinline__ void ask_terms(const uint2 *list, uint32_t from) {
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_TERMS; u++) term[u] = list[1 + from + sub + 8 * u];
+    }
+    __device__ __forceinline__ void ask(const uint2 *list) { first = list[0]; ask_terms(list, 0); }
+    __device__ __forceinline__ void ask_buckets() {
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_TERMS; u++) {
+            const uint32_t b = ap_bound_bucket(term[u].x, bits);
+            at[u] = start[b];
+            to[u] = start[b + 1];
+            if (term[u].x == AP_BOUND_NONE) to[u] = at[u];
+        }
+    }
+    static __device__ __forceinline__ void add(const uint2 &dv, bool in, uint32_t term, float x, float *row, float rel) {
+        if (in && (dv.x >> 8) == term) {
+            const float y = __uint_as_float(dv.y), c = x * y;
+            ap_lds_add(&row[dv.x & 255u], fabsf(y) <= AP_BOUND_DMAX ? fmaf(fabsf(c), rel, c) : INFINITY);
+        }
+    }
+    __device__ __forceinline__ void add_batch(float *row, float rel) {
+        uint2 dv[AP_BOUND_TERMS][AP_BOUND_AHEAD];
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_TERMS; u++)
+#pragma unroll
+            for (int j = 0; j < AP_BOUND_AHEAD; j++)
+                if (at[u] + j < to[u]) dv[u][j] = post[at[u] + j];
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_TERMS; u++)
+#pragma unroll
+            for (int j = 0; j < AP_BOUND_AHEAD; j++) add(dv[u][j], at[u] + j < to[u], term[u].x, __uint_as_float(term[u].y), row, rel);
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_TERMS; u++)   // what is left of them one bucket after the other
+            for (uint32_t i = at[u] + AP_BOUND_AHEAD; i < to[u]; i += AP_BOUND_AHEAD) {
+                uint2 more[AP_BOUND_AHEAD];
+#pragma unroll
+                for (int j = 0; j < AP_BOUND_AHEAD; j++) more[j] = post[i + j];
+#pragma unroll
+                for (int j = 0; j < AP_BOUND_AHEAD; j++) add(more[j], i + j < to[u], term[u].x, __uint_as_float(term[u].y), row, rel);
+            }
+    }
+    // everything behind ask_buckets(); then the next row's terms (NULL: there is none) travel with what is left to do
+    __device__ __forceinline__ void add_all(const ApBoundTail &tail, const uint2 *list, const uint2 *next, int64_t r, int64_t nq, float *row, float rel) {
+        const int64_t q = tail.q0 + r;
+        add_batch(row, rel);
+        for (uint32_t from = 8 * AP_BOUND_TERMS; from < first.x; from += 8 * AP_BOUND_TERMS) {
+            ask_terms(list, from);
+            ask_buckets();
+            add_batch(row, rel);
+        }
+        const uint32_t rest = first.y;
+        if (next) ask(next);
+        if (rest != AP_BOUND_NONE) {   // what the list had no place for
+            const float ws = tail.w[q * tail.w_stride + 1], wf = tail.w[q * tail.w_stride + 2];
+            const int64_t sp0 = tail.q_sp_indptr[q], tx0 = tail.q_tx_indptr[q], sp_n = tail.q_sp_indptr[q + 1] - sp0, all = sp_n + (tail.q_tx_indptr[q + 1] - tx0);
+            for (int64_t p = (int64_t)rest + sub; p < all; p += 8) {
+                const bool sp = p < sp_n;
+                const int32_t t = sp ? tail.q_sp_idx[sp0 + p] : tail.q_tx_idx[tx0 + p - sp_n];
+                const float x = sp ? ws * tail.q_sp_val[sp0 + p] : wf * tail.q_tx_val[tx0 + p - sp_n];
+                if (t < 0 || t >= (sp ? tail.nsp : tail.ntx)) continue;
+                const uint32_t other = (uint32_t)(sp ? t : tail.nsp + t), b = ap_bound_bucket(other, bits);
+                for (uint32_t i = start[b], e = start[b + 1]; i < e; i++) add(post[i], true, other, x, row, rel);
+            }
+        }
+        ap_wave_sync();
+        if (!tail.kw_terms) return;   // uniform
+        if (r < nq) for (int j = sub; j < AP_BOUND_QT; j += 8) row[j] = ap_bound_round(row[j], rel);
+        ap_wave_sync();
+        if (r < nq)
+            for (int j = sub; j < tail.kw_stride; j += 8) {
+                const int32_t t = tail.kw_terms[q * tail.kw_stride + j];
+                if (t < 0 || t >= tail.ntx) continue;
+                const uint32_t want = (uint32_t)(tail.nsp + t), b = ap_bound_bucket(want, bits);
+                for (uint32_t i = start[b], e = start[b + 1]; i < e; i++) {
+                    const uint32_t d = post[i].x;
+                    if ((d >> 8) == want) atomicAdd(reinterpret_cast<uint32_t *>(row + (d & 255u)), 1u);   // at most 16 required terms: the count stays inside its bits
+                }
+            }
+        ap_wave_sync();
+    }
+    // four entries of a row, as the table holds them
+    static __device__ __forceinline__ float4 entries(const float *in, float rel, const ApBoundTail &tail) {
+        const float4 v = *reinterpret_cast<const float4 *>(in);
+        if (tail.kw_terms) return v;   // rounded before they were counted in
+        return make_float4(ap_bound_round(v.x, rel), ap_bound_round(v.y, rel), ap_bound_round(v.z, rel), ap_bound_round(v.w, rel));
+    }
+};
+__device__ __forceinline__ float ap_bound_slack(float2 c0, float2 c1, float2 c2, const float2 (&dn)[3]) {
+    float slack = fmaf(c0.x, dn[0].x, 1e-36f);
+    slack = fmaf(c0.y, dn[0].y, slack);
+    slack = fmaf(c1.x, dn[1].x, slack);
+    slack = fmaf(c1.y, dn[1].y, slack);
+    slack = fmaf(c2.x, dn[2].x, slack);
+    return fmaf(c2.y, dn[2].y, slack);
+}
+// a document's norms as the slack takes them: |d - d^| and |d|, rounded up
+__device__ __forceinline__ float2 ap_bound_dnorm(float2 dn) {
+    return make_float2(fmaf(dn.x, 1.0001f, 1e-15f), dn.y <= AP_BOUND_DMAX ? fmaf(dn.y, 1.0001f, 1e-15f) : INFINITY);
+}
+
 // The product and the slack: a tile of 256 queries x 256 documents, 16 waves of 64 x 64, chunks of 64 columns through two
 // LDS stages as in the seed sweep.  10,000 queries x 100,000 documents x 1,280 columns take 3.1 ms = 0.84 PFLOP/s without the
 // tail; the matrix cores and the LDS reads that feed them bound it, as they bound the sweep.  The documents' columns come from two places: the dense part (dense, dense_ld) and
@@ -440,7 +550,7 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
         const int p = t / AP_BOUND_QT, j = t % AP_BOUND_QT;
         const float2 dn = norms[p * n + (d0 + j < n ? d0 + j : n - 1)];
         s_qc[p][j] = *reinterpret_cast<const float2 *>(qc + (r0 + j) * 8 + 2 * p);
-        s_dn[p][j] = make_float2(fmaf(dn.x, 1.0001f, 1e-15f), dn.y <= AP_BOUND_DMAX ? fmaf(dn.y, 1.0001f, 1e-15f) : INFINITY);
+        s_dn[p][j] = ap_bound_dnorm(dn);
     }
     const int32_t kq = n_chunks * AP_BK16;
     const char *qa = reinterpret_cast<const char *>(qm + r0 * kq);
@@ -513,37 +623,16 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
     // The tile goes to LDS by halves, where the tail is added, and from there to memory.  Half a holds the queries of every
     // wave's accumulators a: place p of its 128 is query (p >> 5) * 64 + a * 32 + (p & 31).  Eight lanes take a query, a wave
     // the same eight queries from the first addition to the last store: only the way into LDS needs barriers.
-    // What a query's additions wait for is asked for early: its terms before the accumulators go to LDS, where their buckets
-    // lie before the barrier behind that, the first entries of all buckets at once.
+    __builtin_amdgcn_sched_barrier(0);   // what follows, begun earlier, takes registers that the loop has not got: it would spill them in every round
     float *tile = reinterpret_cast<float *>(bound_lds);
-    const uint32_t *start = tail.start + dt * ((1 << tail.bits) + 1);
-    const uint2 *post = tail.post + tail.sp_indptr[d0] + tail.tx_indptr[d0];
-    const int own = wave * 8 + (lane >> 3), sub = lane & 7;
+    const int own = wave * 8 + (lane >> 3);
     const int64_t r_own = r0 + (own >> 5) * 64 + (own & 31);   // and 32 more in the second half
     const uint2 *lists = tail.lists + r_own * AP_BOUND_LIST;
-    uint2 term[AP_BOUND_TERMS], first;
-    uint32_t at[AP_BOUND_TERMS], to[AP_BOUND_TERMS];
-    auto ask_terms = [&](const uint2 *list, uint32_t from) {
-#pragma unroll
-        for (int u = 0; u < AP_BOUND_TERMS; u++) term[u] = list[1 + from + sub + 8 * u];
-    };
-    auto ask_buckets = [&]() {
-#pragma unroll
-        for (int u = 0; u < AP_BOUND_TERMS; u++) {
-            const uint32_t b = ap_bound_bucket(term[u].x, tail.bits);
-            at[u] = start[b];
-            to[u] = start[b + 1];
-            if (term[u].x == AP_BOUND_NONE) to[u] = at[u];
-        }
-    };
-    first = lists[0];
-    ask_terms(lists, 0);
+    ApTailJoin join(tail, dt, lane & 7);
+    join.ask(lists);
 #pragma unroll
     for (int a = 0; a < 2; a++) {
-        if (a) {
-            __syncthreads();
-            lists += 32 * AP_BOUND_LIST;
-        }
+        if (a) __syncthreads();
         float2 dn[2][3];
 #pragma unroll
         for (int b = 0; b < 2; b++)
@@ -554,101 +643,125 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
             const int in = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), i = wm * 64 + a * 32 + in;
             const float2 c0 = s_qc[0][i], c1 = s_qc[1][i], c2 = s_qc[2][i];
 #pragma unroll
-            for (int b = 0; b < 2; b++) {
-                float slack = fmaf(c0.x, dn[b][0].x, 1e-36f);
-                slack = fmaf(c0.y, dn[b][0].y, slack);
-                slack = fmaf(c1.x, dn[b][1].x, slack);
-                slack = fmaf(c1.y, dn[b][1].y, slack);
-                slack = fmaf(c2.x, dn[b][2].x, slack);
-                slack = fmaf(c2.y, dn[b][2].y, slack);
-                tile[(wm * 32 + in) * AP_BOUND_QT + wn * 64 + b * 32 + li] = acc[a][b][r] + slack;
-            }
+            for (int b = 0; b < 2; b++) tile[(wm * 32 + in) * AP_BOUND_QT + wn * 64 + b * 32 + li] = acc[a][b][r] + ap_bound_slack(c0, c1, c2, dn[b]);
         }
-        ask_buckets();
+        join.ask_buckets();
         __syncthreads();
-        const int64_t r = r_own + 32 * a, q = tail.q0 + r;
-        float *row = tile + own * AP_BOUND_QT;
+        const int64_t r = r_own + 32 * a;
         const float rel = qc[r * 8 + 6];
-        auto add = [&](const uint2 &dv, bool in, uint32_t term, float x) {
-            if (in && (dv.x >> 8) == term) {
-                const float y = __uint_as_float(dv.y), c = x * y;
-                ap_lds_add(&row[dv.x & 255u], fabsf(y) <= AP_BOUND_DMAX ? fmaf(fabsf(c), rel, c) : INFINITY);
-            }
-        };
-        // the buckets' first entries all at once, what is left of them one bucket after the other
-        auto add_batch = [&]() {
-            uint2 dv[AP_BOUND_TERMS][AP_BOUND_AHEAD];
-#pragma unroll
-            for (int u = 0; u < AP_BOUND_TERMS; u++)
-#pragma unroll
-                for (int j = 0; j < AP_BOUND_AHEAD; j++)
-                    if (at[u] + j < to[u]) dv[u][j] = post[at[u] + j];
-#pragma unroll
-            for (int u = 0; u < AP_BOUND_TERMS; u++)
-#pragma unroll
-                for (int j = 0; j < AP_BOUND_AHEAD; j++) add(dv[u][j], at[u] + j < to[u], term[u].x, __uint_as_float(term[u].y));
-#pragma unroll
-            for (int u = 0; u < AP_BOUND_TERMS; u++)
-                for (uint32_t i = at[u] + AP_BOUND_AHEAD; i < to[u]; i += AP_BOUND_AHEAD) {
-                    uint2 more[AP_BOUND_AHEAD];
-#pragma unroll
-                    for (int j = 0; j < AP_BOUND_AHEAD; j++) more[j] = post[i + j];
-#pragma unroll
-                    for (int j = 0; j < AP_BOUND_AHEAD; j++) add(more[j], i + j < to[u], term[u].x, __uint_as_float(term[u].y));
-                }
-        };
-        add_batch();
-        for (uint32_t from = 8 * AP_BOUND_TERMS; from < first.x; from += 8 * AP_BOUND_TERMS) {
-            ask_terms(lists, from);
-            ask_buckets();
-            add_batch();
-        }
-        const uint32_t rest = first.y;
-        if (a == 0) {   // the second half's, while this one's are added to the end and stored
-            first = lists[32 * AP_BOUND_LIST];
-            ask_terms(lists + 32 * AP_BOUND_LIST, 0);
-        }
-        if (rest != AP_BOUND_NONE) {   // what the list had no place for
-            const float ws = tail.w[q * tail.w_stride + 1], wf = tail.w[q * tail.w_stride + 2];
-            const int64_t sp0 = tail.q_sp_indptr[q], tx0 = tail.q_tx_indptr[q], sp_n = tail.q_sp_indptr[q + 1] - sp0, all = sp_n + (tail.q_tx_indptr[q + 1] - tx0);
-            for (int64_t p = (int64_t)rest + sub; p < all; p += 8) {
-                const bool sp = p < sp_n;
-                const int32_t t = sp ? tail.q_sp_idx[sp0 + p] : tail.q_tx_idx[tx0 + p - sp_n];
-                const float x = sp ? ws * tail.q_sp_val[sp0 + p] : wf * tail.q_tx_val[tx0 + p - sp_n];
-                if (t < 0 || t >= (sp ? tail.nsp : tail.ntx)) continue;
-                const uint32_t other = (uint32_t)(sp ? t : tail.nsp + t), b = ap_bound_bucket(other, tail.bits);
-                for (uint32_t i = start[b], e = start[b + 1]; i < e; i++) add(post[i], true, other, x);
-            }
-        }
-        ap_wave_sync();
-        if (tail.kw_terms) {   // uniform
-            if (r < nq) for (int j = sub; j < AP_BOUND_QT; j += 8) row[j] = ap_bound_round(row[j], rel);
-            ap_wave_sync();
-            if (r < nq)
-                for (int j = sub; j < tail.kw_stride; j += 8) {
-                    const int32_t t = tail.kw_terms[q * tail.kw_stride + j];
-                    if (t < 0 || t >= tail.ntx) continue;
-                    const uint32_t term = (uint32_t)(tail.nsp + t), b = ap_bound_bucket(term, tail.bits);
-                    for (uint32_t i = start[b], to = start[b + 1]; i < to; i++) {
-                        const uint32_t d = post[i].x;
-                        if ((d >> 8) == term) atomicAdd(reinterpret_cast<uint32_t *>(row + (d & 255u)), 1u);   // at most 16 required terms: the count stays inside its bits
-                    }
-                }
-            ap_wave_sync();
-        }
+        join.add_all(tail, lists + 32 * a * AP_BOUND_LIST, a == 0 ? lists + 32 * AP_BOUND_LIST : nullptr, r, nq, tile + own * AP_BOUND_QT, rel);
         const int64_t j = d0 + lane * 4;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
             const int at = wave * 8 + i;
             const int64_t to = r0 + (at >> 5) * 64 + a * 32 + (at & 31);
-            if (to >= nq || j >= ld) continue;
-            float4 v = *reinterpret_cast<const float4 *>(tile + at * AP_BOUND_QT + lane * 4);
-            if (!tail.kw_terms) {
-                const float f = __shfl(rel, i * 8, 64);
-                v = make_float4(ap_bound_round(v.x, f), ap_bound_round(v.y, f), ap_bound_round(v.z, f), ap_bound_round(v.w, f));
-            }
-            *reinterpret_cast<float4 *>(table + to * ld + j) = v;
+            const float f = __shfl(rel, i * 8, 64);
+            if (to < nq && j < ld) *reinterpret_cast<float4 *>(table + to * ld + j) = ApTailJoin::entries(tile + at * AP_BOUND_QT + lane * 4, f, tail);
         }
+    }
+}
+
+// The same for few queries, which the reading of the documents' columns bounds: A x 32 of them, every one's columns in turn out of LDS (two chunks of
+// 64 a stage), a wave 32 documents, whose columns go straight to the matrix unit: a lane reads 64 consecutive bytes of a chunk, half a line, so
+// that the instruction's eight columns are other ones than in the tile above, the same on both sides.  Two chunks are on their way while two are multiplied.
+// 8 waves share 256 documents and their postings.  One query of 100,000 documents of 1,280 columns: 156 us by the tile of 256 queries, 54 so
+// (4.7 TB/s); 37 of 120,011 of 1,536: 175 and 104; 64: 97 and 110; from 65 on the tile takes less than two passes.
+#define AP_BOUND_FEW_STRIDE (256 + 16)   // bytes of a query's two chunks in LDS
+template <int A>
+__global__ __launch_bounds__(512, 4) void k_bound_few(const uint16_t *__restrict__ qm, const float *__restrict__ qc, int32_t nq, const uint16_t *__restrict__ dense,
+                                                      int32_t dense_ld, int32_t n_dense, const uint16_t *__restrict__ head, int32_t head_ld, int32_t n_chunks,
+                                                      const float2 *__restrict__ norms, int64_t n, ApBoundTail tail, float *__restrict__ table, int64_t ld) {
+    constexpr int ROWS = 32 * A, STAGE = ROWS * AP_BOUND_FEW_STRIDE;
+    static_assert(2 * STAGE <= ROWS * AP_BOUND_QT * 4, "the tile takes the place of the stages");
+    __shared__ __attribute__((aligned(16))) unsigned char few_lds[ROWS * AP_BOUND_QT * 4];
+    __shared__ float2 s_qc[3][ROWS];
+    const int t = threadIdx.x, lane = t & 63, wave = ap_wave_id(), li = lane & 31, half = lane >> 5;
+    const int64_t dt = blockIdx.x, d0 = dt * AP_BOUND_QT, d = d0 + wave * 32 + li < n ? d0 + wave * 32 + li : n - 1;
+    if (t < 3 * ROWS) s_qc[t / ROWS][t % ROWS] = *reinterpret_cast<const float2 *>(qc + (t % ROWS) * 8 + 2 * (t / ROWS));
+    float2 dn[3];
+#pragma unroll
+    for (int p = 0; p < 3; p++) dn[p] = ap_bound_dnorm(norms[p * n + d]);
+    const char *drow = reinterpret_cast<const char *>(dense + d * dense_ld) + 64 * half, *hrow = reinterpret_cast<const char *>(head + d * head_ld) + 64 * half;
+    const int32_t kq = n_chunks * AP_BK16;
+    ap_u32x4 b0[2][4], b1[2][4], va[A];
+    auto load_docs = [&](int32_t k, ap_u32x4 (&to)[2][4]) {
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            const int32_t kc = k + c < n_chunks ? k + c : k;   // uniform
+            const char *from = kc < n_dense ? drow + (int64_t)kc * 128 : hrow + (int64_t)(kc - n_dense) * 128;
+#pragma unroll
+            for (int s = 0; s < 4; s++) to[c][s] = *reinterpret_cast<const ap_u32x4 *>(from + 16 * s);
+        }
+    };
+    // the queries' two chunks: 16 threads a row, 32 rows at a time
+    auto load_queries = [&](int32_t k) {
+        const int32_t at = (t & 15) * 8, col = k * AP_BK16 + at;
+#pragma unroll
+        for (int p = 0; p < A; p++) va[p] = *reinterpret_cast<const ap_u32x4 *>(qm + (int64_t)(32 * p + (t >> 4)) * kq + (col < kq ? col : at));
+    };
+    auto store_queries = [&](unsigned char *to) {
+#pragma unroll
+        for (int p = 0; p < A; p++) *reinterpret_cast<ap_u32x4 *>(to + (32 * p + (t >> 4)) * AP_BOUND_FEW_STRIDE + (t & 15) * 16) = va[p];
+    };
+    ap_f32x16 acc[A];
+#pragma unroll
+    for (int a = 0; a < A; a++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[a][r] = 0.f;
+    load_queries(0);
+    load_docs(0, b0);
+    store_queries(few_lds);
+    if (n_chunks > 2) load_queries(2);
+    __syncthreads();
+    // round k: chunks k and k + 1 are multiplied out of stage (k / 2) & 1 while k + 2 and k + 3 travel; the queries' are there already
+    auto round = [&](int32_t k, const ap_u32x4 (&b)[2][4], ap_u32x4 (&next)[2][4]) {
+        const unsigned char *cur = few_lds + ((k >> 1) & 1) * STAGE;
+        if (k + 2 < n_chunks) {
+            load_docs(k + 2, next);
+            store_queries(few_lds + (((k >> 1) + 1) & 1) * STAGE);
+            if (k + 4 < n_chunks) load_queries(k + 4);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            if (k + c >= n_chunks) break;   // uniform
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int a = 0; a < A; a++) {
+                    const ap_u32x4 q = *reinterpret_cast<const ap_u32x4 *>(cur + (32 * a + li) * AP_BOUND_FEW_STRIDE + c * 128 + 64 * half + 16 * s);
+                    acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(ap_bf16x8, q), __builtin_bit_cast(ap_bf16x8, b[c][s]), acc[a], 0, 0, 0);
+                }
+        }
+        __syncthreads();
+    };
+    for (int32_t k = 0; k < n_chunks; k += 4) {
+        round(k, b0, b1);
+        if (k + 2 < n_chunks) round(k + 2, b1, b0);
+    }
+    // the first 4 A waves take eight queries each, as above
+    float *tile = reinterpret_cast<float *>(few_lds);
+    const int own = wave * 8 + (lane >> 3);
+    ApTailJoin join(tail, dt, lane & 7);
+    const uint2 *list = tail.lists + (int64_t)own * AP_BOUND_LIST;
+    if (wave < 4 * A) join.ask(list);
+#pragma unroll
+    for (int a = 0; a < A; a++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const int i = 32 * a + 8 * (r >> 2) + 4 * half + (r & 3);
+            tile[i * AP_BOUND_QT + wave * 32 + li] = acc[a][r] + ap_bound_slack(s_qc[0][i], s_qc[1][i], s_qc[2][i], dn);
+        }
+    if (wave < 4 * A) join.ask_buckets();
+    __syncthreads();
+    if (wave >= 4 * A) return;
+    const float rel = qc[own * 8 + 6];
+    join.add_all(tail, list, nullptr, own, nq, tile + own * AP_BOUND_QT, rel);
+    const int64_t j = d0 + lane * 4;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int at = wave * 8 + i;
+        const float f = __shfl(rel, i * 8, 64);
+        if (at < nq && j < ld) *reinterpret_cast<float4 *>(table + at * ld + j) = ApTailJoin::entries(tile + at * AP_BOUND_QT + lane * 4, f, tail);
     }
 }
 
@@ -884,13 +997,24 @@ int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const f
     const bool own = ix->bd_kd != 0;
     hipLaunchKernelGGL(k_bound_queries, dim3((unsigned)(q_tiles * AP_BOUND_QT)), dim3(256), 0, st, Q, w, w_stride, q0, nq, kdense, kh, nsp, ntx, ix->bd_col, b.qm,
                        b.qc, b.tails);
-    AP_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bound_table), hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES));
     const int32_t ld = ix->bd_kd + kh;
     const ApBoundTail tail{w, w_stride, nsp, ntx, ix->bd_start_bits, kw_terms ? kw_stride : 0, q0, Q.sp_indptr, Q.tx_indptr, Q.sp_idx, Q.tx_idx, Q.sp_val, Q.tx_val,
                            ix->docs.sp_indptr, ix->docs.tx_indptr, b.tails, ix->bd_start, ix->bd_post, kw_terms};
+    const uint16_t *rows = own ? ix->bd_rows : static_cast<const uint16_t *>(ix->docs.dense), *heads = ix->bd_rows + ix->bd_kd;
+    const int32_t rows_ld = own ? ld : ix->docs.dim, n_dense = kdense / AP_BK16, n_chunks = (kdense + kh) / AP_BK16;
+    if (nq <= AP_BOUND_FEW) {   // one pass over the documents' columns either way
+        if (nq <= 32)
+            hipLaunchKernelGGL(k_bound_few<1>, dim3((unsigned)doc_tiles), dim3(512), 0, st, b.qm, b.qc, (int32_t)nq, rows, rows_ld, n_dense, heads, ld, n_chunks, ix->bd_norms, n, tail,
+                               b.table, b.ld);
+        else
+            hipLaunchKernelGGL(k_bound_few<2>, dim3((unsigned)doc_tiles), dim3(512), 0, st, b.qm, b.qc, (int32_t)nq, rows, rows_ld, n_dense, heads, ld, n_chunks, ix->bd_norms, n, tail,
+                               b.table, b.ld);
+        AP_CHECK_HIP(hipGetLastError());
+        return AP_OK;
+    }
+    AP_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bound_table), hipFuncAttributeMaxDynamicSharedMemorySize, AP_BIG_LDS_BYTES));
     hipLaunchKernelGGL(k_bound_table, dim3((unsigned)(groups * 8 * AP_BOUND_GROUP * q_tiles)), dim3(1024), AP_BIG_LDS_BYTES, st, b.qm, b.qc, (int32_t)nq,
-                       (int32_t)q_tiles, own ? ix->bd_rows : static_cast<const uint16_t *>(ix->docs.dense), own ? ld : ix->docs.dim, kdense / AP_BK16,
-                       ix->bd_rows + ix->bd_kd, ld, (kdense + kh) / AP_BK16, ix->bd_norms, n, doc_tiles, tail, b.table, b.ld);
+                       (int32_t)q_tiles, rows, rows_ld, n_dense, heads, ld, n_chunks, ix->bd_norms, n, doc_tiles, tail, b.table, b.ld);
     AP_CHECK_HIP(hipGetLastError());
     return AP_OK;
 }

@@ -270,6 +270,7 @@ struct ApSearchWs {
 };
 // the workspace of one stream never grows beyond this (40,000 queries of 100,000 documents, 480 of 8.8 million)
 #define AP_BOUND_WS_BYTES ((size_t)16 << 30)
+#define AP_BOUND_FEW 64            // queries whose bounds one pass over the documents' columns gives (k_bound_few)
 #define AP_BOUND_WHOLE INT64_MAX   // ap_bound_reserve: the whole batch in one slab, or none
 #define AP_BOUND_MARKS 3           // `tables` of a workspace with one table and the marks of its queries
 #define AP_BOUND_KEEP_BYTES ((size_t)2 << 30)   // an exact top-k that had to take more gives it back

@@ -795,9 +795,10 @@ void k_search(ApSearchArgs g) {
 #define AP_SEARCH_WS_BYTES ((size_t)2 << 30)
 
 // What the bounds of all documents cost, by what was measured (microseconds): a document's columns are read once (0.4 ns), a
-// tile of 256 queries takes 3.1 ps a pair at 1,280 columns and 1.1 ps for the tail.
+// tile of 256 queries takes 3.1 ps a pair at 1,280 columns and 1.1 ps for the tail; up to 64 queries take one pass over the columns (0.54 to 0.97 ns a document).
 double ap_bound_cost(const ap_index *ix, int64_t nq) {
     const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256);
+    if (nq <= AP_BOUND_FEW) return 15.0 + (double)ix->docs.n * (0.55e-3 + 7e-6 * (double)nq) * cols;
     return 15.0 + (double)ix->docs.n * (0.4e-3 * cols + tiles * 256.0 * (3.1e-6 * cols + 1.1e-6));
 }
 

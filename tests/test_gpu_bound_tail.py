@@ -54,3 +54,24 @@ def test_tail_of_every_length(n, vocab, doc_terms):
         assert np.array_equal((with_kw.view(torch.int32) & 31).cpu().numpy(), want)
         assert ((with_kw.view(torch.int32) & ~31).view(torch.float32).double() >= sc).all()
     ix.close()
+
+
+# one pass over the documents' columns for up to 64 queries: 32 and 64 of them, two to seven chunks of 64 columns, read two at a time
+@pytest.mark.parametrize("nq", [1, 31, 32, 33, 64, 65])
+@pytest.mark.parametrize("n,dim,vocab,bf16", [(255, 64, 30, False), (257, 72, 30, True), (300, 192, 30, True), (1, 128, 40, False), (256, 260, 30, False), (513, 320, 60, True)])
+def test_bounds_of_few_queries(n, dim, vocab, bf16, nq):
+    rng = np.random.default_rng(dim + nq)
+    def vecs(m):
+        ip, idx, val = _lists(rng, m, np.full(m, 9), 0, vocab)
+        ip2, idx2, _ = _lists(rng, m, np.full(m, 7), 0, vocab)
+        return VecSet(m, dim, rng.standard_normal((m, dim)).astype(np.float32), ip, idx, val, ip2, idx2, rng.integers(1, 4, len(idx2)).astype(np.float32), vocab, vocab)
+    docs, queries = vecs(n), vecs(nq)
+    if bf16:
+        bits = torch.from_numpy(docs.dense).bfloat16()
+        docs.dense, docs.dense_bf16 = bits.float().numpy(), bits.view(torch.int16).numpy().view(np.uint16)
+    ix, q = B.Index.ingest(B.DeviceVecs(docs, bf16=bf16), B.build_params(8)), B.DeviceVecs(queries)
+    pw = rng.uniform(-1.0, 1.0, (nq, 3)).astype(np.float32)
+    sc = ix.hybrid_scores(q, np.tile(np.arange(n, dtype=np.int32), (nq, 1)), pw)[:, :, 3].double()
+    up = ix.stage_score_bounds(q, pw).double()
+    assert (up >= sc).all() and (up - sc <= _slack(ix, queries, docs, pw, bf16)).all()
+    ix.close()
