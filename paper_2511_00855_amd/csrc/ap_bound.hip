@@ -528,9 +528,10 @@ __device__ __forceinline__ float2 ap_bound_dnorm(float2 dn) {
 // What is left of it is the wait for three reads that depend on each other (a query's terms, where their buckets lie, their
 // entries), 8 us for half a tile when each was asked for in its turn, 4 as it is.  A lane per document entry would look up five times as
 // many terms.  1,000 queries: 707 -> 480 us; 4,000 of some 150 terms, 80,000 documents of 1,024 bf16 columns: 5.5 -> 3.0 ms.
-// Tile order: an XCD takes the document tiles in groups of four and walks each group's query tiles, so that a group's
-// documents and the queries stay in its L2 while they are used.
-#define AP_BOUND_GROUP 4
+// Tile order: an XCD takes the document tiles in groups of two and walks each group's query tiles, so that a group's
+// documents and the queries stay in its L2 while they are used.  Groups of four leave some XCDs a group more than others: 4,000 queries of 20,000 documents
+// (79 tiles) 425 us, 367 by two, 359 by one; 10,000 of 100,000 4.1 ms, 3.9 and 4.2.
+#define AP_BOUND_GROUP 2
 __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict__ qm, const float *__restrict__ qc, int32_t nq, int32_t q_tiles,
                                                       const uint16_t *__restrict__ dense, int32_t dense_ld, int32_t n_dense,
                                                       const uint16_t *__restrict__ head, int32_t head_ld, int32_t n_chunks,
