@@ -794,7 +794,8 @@ int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, co
 //    documents, whose descriptors and rows are all close by; 18 and more where it runs without bounds), 0.09 ns for every document it reaches
 //    while the chip is full (0.24 without bounds).
 // One query of 100,000 documents, pool 128: 867 -> 254 us (all scored ahead: the scores 92, the lines 11, the walk 137);
-// 37 of 120,011, pool 512: 3.17 -> 0.93 ms (out of the bounds: these 0.10 ms, the lines 0.01, the scores 0.14, the walk 0.63).  Where the walk would not be an eighth faster by this count, k_search stays:
+// 37 of 120,011, pool 512: 3.17 -> 0.93 ms (out of the bounds: these 0.10 ms, the lines 0.01, the scores 0.14, the walk 0.63).  Where the walk would not be an eighth faster by this count (a fifth with more parents, for which
+// the 60, the 80 and the 6.6 were not measured), k_search stays:
 // 300 queries with a pool of 128, 1.2 and 1.6 ms.  16 queries of 60,000 documents of 128 columns, pool 32: 293 and 178 us, 64 of 100,000 of 768, pool 128: 1,067 and 647.
 // A way whose lists would not hold what enters them is not taken: a query whose list is full is searched twice (43,000 documents, degree 32,
 // 3 queries, pool 2,048: 10.9 ms by k_search, 13.3 scored ahead, 4.3 out of the bounds; degree 64, pool 3,600: 14.8, 29.0 and 7.9).  Documents that are
@@ -814,12 +815,13 @@ ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t wi
     const double first = std::min(1.0, std::max(3.0 * share, 6.0 / (ix->params.n_entry + ix->params.degree)));
     const double row = (double)ix->docs.dim * (ix->dtype == AP_BF16 ? 2 : 4) + 8.0 * (double)(ix->sp_nnz + ix->tx_nnz) / n;   // bytes of a document
     const double per_cu = std::min(8.0, floor(160.0 * 1024 / (double)(bytes + 1024 + (n <= 65536 ? n / 8 : 0))));
-    const double walk = 60.0 + beam * (1.1 + std::max(0, beam - 512) * 6e-4) * ceil(q / (256.0 * std::max(1.0, per_cu)));
+    const bool single = width == 1;
+    const double walk = (single ? 60.0 : 90.0) + beam * (1.1 + std::max(0, beam - 512) * 6e-4) * ceil(q / (256.0 * std::max(1.0, per_cu)));
     const double table = ap_bound_cost(ix, nq);
     const double out_of_bounds = walk + 45.0 + table + q * first * n * std::max(0.4e-3, row / 5e6);
     const double all = walk + n * row / 5e6 + (q - 1) * n * std::max(0.16e-3, row / (n * row <= 2e8 ? 16e6 : 7.5e6));
     const double near = std::min(1.2, std::max(0.4, 0.45 + 0.36 * log10(n / 3000.0)));
-    const double other = bounds ? table + 80.0 + std::max(iters * near * (5.5 + 0.012 * std::min(q, 90.0) + std::min(2.7 * (width - 1), 12.5)), q * met * 0.09e-3)
+    const double other = bounds ? table + (single ? 80.0 : 0.0) + std::max(iters * near * (5.5 + (single ? 0.012 * std::min(q, 90.0) : std::min(2.7 * (width - 1), 12.5))), q * met * 0.09e-3)
                                 : std::max(iters * near * 18.0, q * met * 0.24e-3);
     double lines[2][4] = {{first, first / 2, 1.5 * share, share}, {std::max(0.5, 8 * share), 8 * share, 3 * share, 1.2 * share}};
     for (auto &l : lines) for (double &s : l) s = std::min(1.0, s);
@@ -840,7 +842,7 @@ ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t wi
     else {
         const double cost[2] = {some && fits(1) ? out_of_bounds : INFINITY, fits(2) ? all : INFINITY};
         p.mode = cost[0] < cost[1] ? 1 : 2;
-        if (cost[p.mode - 1] > 0.88 * other) { p.mode = 0; return p; }
+        if (cost[p.mode - 1] > (single ? 0.88 : 0.8) * other) { p.mode = 0; return p; }
     }
     for (int i = 0; i < 4; i++) p.share[i] = (float)lines[p.mode - 1][i];
     return p;
