@@ -384,6 +384,7 @@ int ap_search_form(const ap_index *index, int32_t out3[3]);
  *   "search_walk"             1: small batches are searched as any other, 2: by the walk out of the bounds, 3: by the walk with
  *                             every document scored ahead (both where the call can: no keywords, no capture)
  *   "search_bounds_bytes"     cap of the workspace that holds them (forces slabs of queries, each with a table of its own)
+ *   "bound_buckets"           2^this many buckets for the postings of 256 documents (8 to 15), where bounds are laid out from then on
  *   "search_floor"            1: no neighbour waits below the estimated end of the pool, 2: the estimate is far too high
  *   "search_visited_global"   1: visited sets stay in the global workspace even where the search would keep them in LDS
  *   "search_query_lists"      1: the plain and keyword searches look query terms up in the query's lists, not in LDS tables

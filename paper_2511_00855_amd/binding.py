@@ -105,7 +105,8 @@ def debug_set(name: str, value: int):
 
 
 DEBUG_NAMES = ("seed_sample_cols", "seed_buffer_cap", "seed_tau_ulps", "max_launch_threads", "search_workspace_bytes",
-               "search_visited_global", "search_query_lists", "seed_one_sided", "search_bounds", "search_walk", "search_bounds_bytes", "search_floor", "prune_walks")
+               "search_visited_global", "search_query_lists", "seed_one_sided", "search_bounds", "search_walk", "search_bounds_bytes", "search_floor", "prune_walks",
+               "bound_buckets")
 
 
 def debug_reset():

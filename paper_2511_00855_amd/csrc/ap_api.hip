@@ -30,6 +30,7 @@ extern "C" int ap_debug_set(const char *name, int64_t value) {
         {"search_workspace_bytes", &g_ap_debug.search_workspace_bytes}, {"search_visited_global", &g_ap_debug.search_visited_global},
         {"search_query_lists", &g_ap_debug.search_query_lists},         {"seed_one_sided", &g_ap_debug.seed_one_sided},
         {"search_bounds", &g_ap_debug.search_bounds}, {"search_walk", &g_ap_debug.search_walk}, {"search_bounds_bytes", &g_ap_debug.search_bounds_bytes}, {"search_floor", &g_ap_debug.search_floor}, {"prune_walks", &g_ap_debug.prune_walks},
+        {"bound_buckets", &g_ap_debug.bound_buckets},
     };
     for (auto &t : table)
         if (strcmp(name, t.name) == 0) { *t.field = value; return AP_OK; }

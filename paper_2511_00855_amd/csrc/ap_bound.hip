@@ -20,11 +20,13 @@ int ap_validate_queries(const ap_queries *q);
 #define AP_BOUND_DMAX 1e15f
 #define AP_BOUND_QT 256              // queries and documents of a tile
 #define AP_BOUND_VOCAB ((int64_t)1 << 24)   // terms of both vocabularies together a table of columns is kept for
-#define AP_BOUND_BITS_MIN 8          // buckets of a tile's postings: 2^8 to 2^13
+#define AP_BOUND_BITS_MIN 8          // buckets of a tile's postings: 2^8 to 2^13, for long lists up to 2^15 (128 KB of LDS at ingest)
 #define AP_BOUND_BITS 13
+#define AP_BOUND_BITS_LONG 15
 #define AP_BOUND_TERMS 4             // terms of a query that a lane looks up at once
 #define AP_BOUND_LIST (1 + 128)      // a query's tail as the product's kernel reads it: (entries, AP_BOUND_NONE or the first term of the lists that found no place), then (term, weighted value)
 #define AP_BOUND_NONE 0xffffffffu
+#define AP_BOUND_MUCH 16             // entries of a bucket beyond those for which a query's eight lanes read it together
 #define AP_BOUND_AHEAD 4             // postings of a bucket that are read at once, and entries behind the last one for it
 
 // The workspaces of an index: one per stream that searches it (at most AP_BOUND_STREAMS; insertion and large exact top-k
@@ -236,11 +238,15 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     const int32_t kh = (int32_t)std::min<int64_t>(AP_BOUND_HEAD, (int64_t)ap_up((size_t)all, AP_BK16));
     const size_t nnz = (size_t)ix->tx_nnz + (size_t)ix->sp_nnz;
     const int64_t words = (c.n + 31) / 32;
-    // two buckets for three entries of a tile's lists, about half of which are in the tail (2^14 instead of 2^13 for 165 entries a document: 1 to 8 %
-    // off the product and the tail, for twice the memory and 20 us at ingest)
+    // two buckets for three entries of a tile's lists, about half of which are in the tail, as far as 2^13 buckets go (2^14 for 165 entries a document:
+    // 1 to 8 % off the product and the tail, for twice the memory and 20 us at ingest), and more once a bucket would have over eight
+    // entries, which every lookup reads past.  20,000 documents of 1,279 entries out of 500,000 terms, 1,000 queries of 28, 300 and 1,500 terms: 2^13 buckets
+    // 0.44, 2.79 and 15.0 ms, 2^15 0.37, 2.26 and 11.7, 2^16 0.36, 2.17 and 11.4, for which ingest would have to go through the lists twice (3.3 -> 4.0 ms).
     const int64_t doc_tiles = (c.n + AP_BOUND_QT - 1) / AP_BOUND_QT;
     int bits = AP_BOUND_BITS_MIN;
     while (bits < AP_BOUND_BITS && ((int64_t)1 << bits) * 3 * doc_tiles < 2 * (int64_t)nnz) bits++;
+    while (bits >= AP_BOUND_BITS && bits < AP_BOUND_BITS_LONG && ((int64_t)1 << bits) * 8 * doc_tiles < (int64_t)nnz) bits++;
+    if (g_ap_debug.bound_buckets > 0) bits = (int)std::min<int64_t>(std::max<int64_t>(g_ap_debug.bound_buckets, AP_BOUND_BITS_MIN), AP_BOUND_BITS_LONG);
     // cleared: document frequencies of the learned-sparse terms, histogram, columns taken, bitmaps
     const size_t n_clear = (size_t)c.sp_vocab + 256 + 1 + (size_t)kh * (size_t)words;
     size_t at = 0;
@@ -271,6 +277,10 @@ int ap_bound_ingest(ap_index *ix, int share, hipStream_t st) {
     hipLaunchKernelGGL(k_bd_pick, dim3((unsigned)((all + 1023) / 1024)), dim3(1024), 0, st, df_sp, c.sp_vocab, ix->df, c.tx_vocab, hist, kh, ix->bd_col, taken);
     const dim3 g((unsigned)(doc_tiles + std::min<int64_t>((c.n + 15) / 16, 1024)));
     const size_t lds = std::max((size_t)4 << bits, (size_t)16 * AP_BOUND_HEAD * 2);
+    if (lds > 48 * 1024) {
+        const void *f = ix->dtype == AP_F32 ? reinterpret_cast<const void *>(&k_bd_rows<AP_F32>) : reinterpret_cast<const void *>(&k_bd_rows<AP_BF16>);
+        AP_CHECK_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    }
     if (ix->dtype == AP_F32)
         hipLaunchKernelGGL(k_bd_rows<AP_F32>, g, dim3(1024), lds, st, ix->docs, c.sp_vocab, ix->bd_col, kd, kh, ix->bd_rows, ix->dense_norm, ix->bd_norms, ix->bd_bits, words, (uint32_t)doc_tiles, bits, ix->bd_start, ix->bd_post);
     else
@@ -411,6 +421,11 @@ __global__ __launch_bounds__(256) void k_bound_queries(ApVecs Q, const float *__
 
 // The tail of one query and one tile's documents, by eight lanes (sub: which of them): what its additions wait for is asked for early, its terms and then
 // where their buckets lie, the first entries of all buckets at once.  row: its AP_BOUND_QT entries in LDS, which no other wave touches.
+// Long lists make long buckets, of terms that most documents hold above all: the eight lanes read those together, and what the query's list has no place for
+// is taken by 32 terms as what it has.  20,000 documents of 1,279 entries, 1,000 queries of 28, 300 and 1,500 terms: 0.56, 4.47 and 33.6 ms by a lane a bucket and a term
+// at a time (2^13 buckets), 0.37, 2.25 and 11.7 so (2^15); one block a query through postings by terms, in a kernel of its own, 0.38, 2.54 and 12.0.  With lists of
+// several thousand entries, most of them of terms that hardly any document holds, such a kernel would be the faster one (6,000 documents of 6,284
+// entries, 1,000 queries of 28 terms 0.24 and 0.44 ms; 4,000 of them 0.96 and 0.93).
 struct ApTailJoin {
     const uint32_t *start;
     const uint2 *post;
@@ -439,6 +454,16 @@ struct ApTailJoin {
             ap_lds_add(&row[dv.x & 255u], fabsf(y) <= AP_BOUND_DMAX ? fmaf(fabsf(c), rel, c) : INFINITY);
         }
     }
+    // counts a required term's documents among AP_BOUND_AHEAD entries of its bucket
+    __device__ __forceinline__ void count(uint32_t k, uint32_t step, uint32_t end, uint32_t want, float *row) {
+        uint32_t d[AP_BOUND_AHEAD];
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_AHEAD; u++)
+            if (k + step * u < end) d[u] = post[k + step * u].x;
+#pragma unroll
+        for (int u = 0; u < AP_BOUND_AHEAD; u++)
+            if (k + step * u < end && (d[u] >> 8) == want) atomicAdd(reinterpret_cast<uint32_t *>(row + (d[u] & 255u)), 1u);   // at most 16 required terms: the count stays inside its bits
+    }
     __device__ __forceinline__ void add_batch(float *row, float rel) {
         uint2 dv[AP_BOUND_TERMS][AP_BOUND_AHEAD];
 #pragma unroll
@@ -451,50 +476,72 @@ struct ApTailJoin {
 #pragma unroll
             for (int j = 0; j < AP_BOUND_AHEAD; j++) add(dv[u][j], at[u] + j < to[u], term[u].x, __uint_as_float(term[u].y), row, rel);
 #pragma unroll
-        for (int u = 0; u < AP_BOUND_TERMS; u++)   // what is left of them one bucket after the other
-            for (uint32_t i = at[u] + AP_BOUND_AHEAD; i < to[u]; i += AP_BOUND_AHEAD) {
+        for (int u = 0; u < AP_BOUND_TERMS; u++) {   // what is left of them one bucket after the other, much by all eight lanes
+            uint32_t i = at[u] + AP_BOUND_AHEAD, e = to[u];
+            for (uint32_t much = (uint32_t)(__ballot(e > i + AP_BOUND_MUCH) >> (threadIdx.x & 56)) & 255u; much; much &= much - 1) {
+                const int l = __ffs(much) - 1;
+                const uint32_t b = __shfl(i, l, 8), end = __shfl(e, l, 8), t = __shfl(term[u].x, l, 8);
+                const float x = __uint_as_float(__shfl(term[u].y, l, 8));
+                for (uint32_t k = b + sub; k < end; k += 8 * AP_BOUND_AHEAD) {
+                    uint2 more[AP_BOUND_AHEAD];
+#pragma unroll
+                    for (int j = 0; j < AP_BOUND_AHEAD; j++) more[j] = post[k + 8 * j < end ? k + 8 * j : k];
+#pragma unroll
+                    for (int j = 0; j < AP_BOUND_AHEAD; j++) add(more[j], k + 8 * j < end, t, x, row, rel);
+                }
+                if (sub == l) e = 0;
+            }
+            for (; i < e; i += AP_BOUND_AHEAD) {
                 uint2 more[AP_BOUND_AHEAD];
 #pragma unroll
                 for (int j = 0; j < AP_BOUND_AHEAD; j++) more[j] = post[i + j];
 #pragma unroll
-                for (int j = 0; j < AP_BOUND_AHEAD; j++) add(more[j], i + j < to[u], term[u].x, __uint_as_float(term[u].y), row, rel);
+                for (int j = 0; j < AP_BOUND_AHEAD; j++) add(more[j], i + j < e, term[u].x, __uint_as_float(term[u].y), row, rel);
             }
+        }
     }
     // everything behind ask_buckets(); then the next row's terms (NULL: there is none) travel with what is left to do
     __device__ __forceinline__ void add_all(const ApBoundTail &tail, const uint2 *list, const uint2 *next, int64_t r, int64_t nq, float *row, float rel) {
         const int64_t q = tail.q0 + r;
-        add_batch(row, rel);
-        for (uint32_t from = 8 * AP_BOUND_TERMS; from < first.x; from += 8 * AP_BOUND_TERMS) {
-            ask_terms(list, from);
-            ask_buckets();
+        uint32_t from = 8 * AP_BOUND_TERMS;
+        int64_t p0 = first.y != AP_BOUND_NONE ? (int64_t)first.y : INT64_MAX;   // the first of the terms that the list had no place for
+        for (;;) {   // the eight lanes together
             add_batch(row, rel);
+            if (from < first.x) {
+                ask_terms(list, from);
+                from += 8 * AP_BOUND_TERMS;
+            } else if (p0 != INT64_MAX) {
+                const int64_t sp0 = tail.q_sp_indptr[q], tx0 = tail.q_tx_indptr[q], sp_n = tail.q_sp_indptr[q + 1] - sp0, all = sp_n + (tail.q_tx_indptr[q + 1] - tx0);
+                if (p0 >= all) break;
+                const float ws = tail.w[q * tail.w_stride + 1], wf = tail.w[q * tail.w_stride + 2];
+#pragma unroll
+                for (int u = 0; u < AP_BOUND_TERMS; u++) {
+                    const int64_t at = p0 + sub + 8 * u, p = at < all ? at : p0;
+                    const bool sp = p < sp_n;
+                    const int32_t t = sp ? tail.q_sp_idx[sp0 + p] : tail.q_tx_idx[tx0 + p - sp_n];
+                    const float x = sp ? ws * tail.q_sp_val[sp0 + p] : wf * tail.q_tx_val[tx0 + p - sp_n];
+                    term[u] = make_uint2(at < all && t >= 0 && t < (sp ? tail.nsp : tail.ntx) ? (uint32_t)(sp ? t : tail.nsp + t) : AP_BOUND_NONE, __float_as_uint(x));
+                }
+                p0 += 8 * AP_BOUND_TERMS;
+            } else break;
+            ask_buckets();
         }
-        const uint32_t rest = first.y;
         if (next) ask(next);
-        if (rest != AP_BOUND_NONE) {   // what the list had no place for
-            const float ws = tail.w[q * tail.w_stride + 1], wf = tail.w[q * tail.w_stride + 2];
-            const int64_t sp0 = tail.q_sp_indptr[q], tx0 = tail.q_tx_indptr[q], sp_n = tail.q_sp_indptr[q + 1] - sp0, all = sp_n + (tail.q_tx_indptr[q + 1] - tx0);
-            for (int64_t p = (int64_t)rest + sub; p < all; p += 8) {
-                const bool sp = p < sp_n;
-                const int32_t t = sp ? tail.q_sp_idx[sp0 + p] : tail.q_tx_idx[tx0 + p - sp_n];
-                const float x = sp ? ws * tail.q_sp_val[sp0 + p] : wf * tail.q_tx_val[tx0 + p - sp_n];
-                if (t < 0 || t >= (sp ? tail.nsp : tail.ntx)) continue;
-                const uint32_t other = (uint32_t)(sp ? t : tail.nsp + t), b = ap_bound_bucket(other, bits);
-                for (uint32_t i = start[b], e = start[b + 1]; i < e; i++) add(post[i], true, other, x, row, rel);
-            }
-        }
         ap_wave_sync();
         if (!tail.kw_terms) return;   // uniform
         if (r < nq) for (int j = sub; j < AP_BOUND_QT; j += 8) row[j] = ap_bound_round(row[j], rel);
         ap_wave_sync();
         if (r < nq)
-            for (int j = sub; j < tail.kw_stride; j += 8) {
-                const int32_t t = tail.kw_terms[q * tail.kw_stride + j];
-                if (t < 0 || t >= tail.ntx) continue;
-                const uint32_t want = (uint32_t)(tail.nsp + t), b = ap_bound_bucket(want, bits);
-                for (uint32_t i = start[b], e = start[b + 1]; i < e; i++) {
-                    const uint32_t d = post[i].x;
-                    if ((d >> 8) == want) atomicAdd(reinterpret_cast<uint32_t *>(row + (d & 255u)), 1u);   // at most 16 required terms: the count stays inside its bits
+            for (int j0 = 0; j0 < tail.kw_stride; j0 += 8) {   // a lane looks a term up, all eight read a long bucket
+                const int32_t t = j0 + sub < tail.kw_stride ? tail.kw_terms[q * tail.kw_stride + j0 + sub] : -1;
+                const uint32_t own = (uint32_t)(tail.nsp + t), bucket = ap_bound_bucket(own, bits);
+                const bool in = t >= 0 && t < tail.ntx;
+                const uint32_t b = in ? start[bucket] : 0u, e = in ? start[bucket + 1] : 0u;
+                count(b, 1, e, own, row);
+                for (uint32_t more = (uint32_t)(__ballot(e > b + AP_BOUND_AHEAD) >> (threadIdx.x & 56)) & 255u; more; more &= more - 1) {
+                    const int l = __ffs(more) - 1;
+                    const uint32_t want = __shfl(own, l, 8), end = __shfl(e, l, 8);
+                    for (uint32_t k = __shfl(b, l, 8) + AP_BOUND_AHEAD + sub; k < end; k += 8 * AP_BOUND_AHEAD) count(k, 8, end, want, row);
                 }
             }
         ap_wave_sync();

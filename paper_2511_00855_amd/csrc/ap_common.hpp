@@ -171,6 +171,7 @@ struct ApDebug {
     int64_t search_floor = 0;            // 1: no neighbour waits below a floor, 2: the floor is far too high (forces the scan of what waits)
     int64_t search_walk = 0;             // 1: small batches are searched as any other, 2: by the walk out of the bounds, 3: by the walk with every document scored ahead
     int64_t search_bounds_bytes = 0;     // cap of a stream's table of bounds (forces slabs of queries that each get a table)
+    int64_t bound_buckets = 0;           // log2 of the buckets that a tile's postings are grouped into (8 to 15)
     int64_t search_workspace_bytes = 0;  // cap of the search's visited-set workspace (forces searches in several slabs of queries)
 };
 extern ApDebug g_ap_debug;

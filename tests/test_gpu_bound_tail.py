@@ -75,3 +75,66 @@ def test_bounds_of_few_queries(n, dim, vocab, bf16, nq):
     up = ix.stage_score_bounds(q, pw).double()
     assert (up >= sc).all() and (up - sc <= _slack(ix, queries, docs, pw, bf16)).all()
     ix.close()
+
+
+# documents of lists so long that a tile's postings get more than 2^13 buckets, and any number of buckets on the same lists: buckets that one
+# lane reads, that a query's eight lanes read together (a term that most documents hold), lists of queries in the middle of a batch of 32
+@pytest.mark.parametrize("buckets", [0, 8, 13, 15])
+@pytest.mark.parametrize("n,vocab,doc_terms,nq", [(300, 3_000, 700, 65), (513, 20_000, 500, 300), (256, 1_500, 1_000, 20)])
+def test_long_lists(debug_knobs, n, vocab, doc_terms, nq, buckets):
+    rng, dim = np.random.default_rng(n + nq), 64
+    lengths = np.resize([0, 40, 127, 129, 160, 161, 400, 1000], nq)
+    def vecs(m, sp, tx):
+        tx = (tx[0], tx[1], rng.integers(1, 4, len(tx[1])).astype(np.float32))
+        return VecSet(m, dim, rng.standard_normal((m, dim)).astype(np.float32) / 8, *sp, *tx, vocab, vocab)
+    docs = vecs(n, _lists(rng, n, rng.integers(doc_terms // 2, doc_terms, n), 0, vocab), _lists(rng, n, rng.integers(doc_terms // 2, doc_terms, n), 0, vocab))
+    queries = vecs(nq, _lists(rng, nq, lengths, 0, vocab), _lists(rng, nq, lengths[::-1], 0, vocab))
+    debug_knobs("bound_buckets", buckets)
+    ix, q = B.Index.ingest(B.DeviceVecs(docs), B.build_params(8)), B.DeviceVecs(queries)
+    pw = rng.uniform(-1.0, 1.0, (nq, 3)).astype(np.float32)
+    sc = ix.hybrid_scores(q, np.tile(np.arange(n, dtype=np.int32), (nq, 1)), pw)[:, :, 3].double()
+    up = ix.stage_score_bounds(q, pw).double()
+    assert (up >= sc).all() and (up - sc <= _slack(ix, queries, docs, pw, False)).all()
+    # required terms without a column: rarer than the 512th of both vocabularies' frequencies by more than a bin of them is wide (an eighth)
+    df = [np.bincount(i, minlength=vocab) for i in (docs.sp_idx, docs.tx_idx)]
+    rare = np.flatnonzero((df[1] > 0) & (df[1] < np.sort(np.concatenate(df))[::-1][512] / 2))
+    if not len(rare):
+        rare = np.array([vocab + 5])   # all alike: none is sure to have no column
+    kw = rng.choice(rare, (nq, 13)).astype(np.int32)
+    kw[::3, 3], kw[1::3, 9:] = vocab + 5, -1
+    held = np.zeros((n, vocab), np.int32)
+    held[np.repeat(np.arange(n), np.diff(docs.tx_indptr)), docs.tx_idx] = 1
+    want = sum(np.where((kw[:, j] >= 0) & (kw[:, j] < vocab), held[:, np.clip(kw[:, j], 0, vocab - 1)], 0).T for j in range(13))
+    with_kw = ix.stage_score_bounds(q, pw, torch.from_numpy(kw).cuda())
+    assert np.array_equal((with_kw.view(torch.int32) & 31).cpu().numpy(), want)
+    assert ((with_kw.view(torch.int32) & ~31).view(torch.float32).double() >= sc).all()
+    ix.close()
+
+
+def test_long_lists_get_the_buckets_they_need(debug_knobs):
+    """1,250 entries a document: with 2^13 buckets a lookup reads past tens of entries, which costs a quarter of the time and more."""
+    rng, n, nq, vocab = np.random.default_rng(2), 10_240, 1024, 250_000
+    def vecs(m, terms):
+        lists = []
+        for _ in range(2):   # strictly ascending ids: a random start and steps below the vocabulary's share
+            steps = rng.integers(1, vocab // terms, (m, terms))
+            lists.append((np.arange(m + 1, dtype=np.int64) * terms, (np.cumsum(steps, 1) - 1).astype(np.int32).ravel()))
+        (ip, idx), (ip2, idx2) = lists
+        return VecSet(m, 64, rng.standard_normal((m, 64)).astype(np.float32), ip, idx, rng.random(len(idx)).astype(np.float32), ip2, idx2,
+                      np.ones(len(idx2), np.float32), vocab, vocab)
+    docs, q = B.DeviceVecs(vecs(n, 625)), B.DeviceVecs(vecs(nq, 400))
+    pw = np.ones((nq, 3), np.float32)
+    took = {}
+    for buckets in (0, 13, 15):
+        debug_knobs("bound_buckets", buckets)
+        ix = B.Index.ingest(docs, B.build_params(8))
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record(); ix.stage_score_bounds(q, pw); b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took[buckets] = min(times[1:])
+        ix.close()
+    print(took, flush=True)
+    assert took[0] <= 1.1 * min(took.values()), took
