@@ -806,9 +806,13 @@ double ap_bound_cost(const ap_index *ix, int64_t nq) {
 //  - a search that does without: 0.22 ns more for every document it reaches while the chip is full (10,000 queries of 100,000
 //    documents: 0.22 to 0.28 where both take the same time, which is at pools of 16, 25 and 36 entries for 128 f32, 768 f32 and
 //    1,024 bf16 columns; at 128 entries of 768 f32 columns 22.1 ms without bounds, 10.5 with them);
-//  - 40 us more an iteration while it is not, for 30 queries and more (30 to 1,500 queries, pools of 10 to 96: 40 to
-//    80; 200 queries of 1,024 bf16 columns, 16 iterations: 1.16 ms and 0.40), and 8 us for fewer (one query, 128 iterations:
-//    2.35 ms and 0.89).
+//  - while it is not, so much more an iteration (60,000 to 150,000 documents of 128 and 768 f32 and 1,024 bf16 columns, pools of 10 and 16, where the line lies):
+//      degree      1 query      8      29      64     200   1,000
+//        64         11..22  16..29  24..34  29..36  32..44  37..49 us
+//        32          5..11   9..12  10..17  13..21  14..22  17..25
+//        16          2.. 4   3.. 4   4.. 8   5.. 9   6..12   8..15
+//    and 10 to 20 at degree 64 with pools of 128, where it no longer matters (one query 2.53 and 0.79 ms).  1,000 queries of 100,000 f32 documents at degree 16, pool 16:
+//    0.32 ms without bounds, 0.67 with them; 24 at degree 64, pool 10: 0.47 and 0.23.
 bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters) {
     if (!ix->bd_mem || g_ap_debug.search_bounds == 1 || nq < 1) return false;
     const double n = (double)ix->docs.n;
@@ -817,7 +821,8 @@ bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, 
     double iters = (double)beam / width;
     if (max_iters > 0) iters = std::min(iters, (double)max_iters);
     const double reached = n * (1.0 - exp(-iters * width * (double)ix->params.degree / n));
-    return std::max((double)nq * reached * 0.22e-3, iters * (nq >= 30 ? 40.0 : 8.0)) > ap_bound_cost(ix, nq);
+    const double iteration = std::min(40.0, 12.0 + 4.0 * log2((double)nq)) * std::min(1.0, pow(ix->params.degree / 64.0, 1.25));
+    return std::max((double)nq * reached * 0.22e-3, iters * iteration) > ap_bound_cost(ix, nq);
 }
 
 // Queries per slab when `cap_words` words are available: as many as fit, then evened out over the slabs.

@@ -600,3 +600,37 @@ def test_entity_searches_with_and_without_bounds_are_the_same(debug_knobs, w_k):
             got.append([t.clone() for t in ix.search_batch_entities(qs, k, beam, kgs.q_ent, w_k, hops, pw)] + [ix.search_stats(qs.n)[0][:, :2].clone()])
         assert all(torch.equal(a, b) for a, b in zip(*got)), (k, beam, hops)
     ix.close()
+
+
+def _plain_corpus(rng, n, nq, dim, vocab, terms, q_terms, degree):
+    """Vector sets whose lists all have `terms` (`q_terms`) strictly ascending terms, and a random graph's index of the first."""
+    def vecs(m, k):
+        lists = [(np.cumsum(rng.integers(1, vocab // k, (m, k)), 1) - 1).astype(np.int32).ravel() for _ in range(2)]
+        ip = np.arange(m + 1, dtype=np.int64) * k
+        return VecSet(m, dim, rng.standard_normal((m, dim)).astype(np.float32), ip, lists[0], rng.random(m * k).astype(np.float32), ip, lists[1],
+                      np.ones(m * k, np.float32), vocab, vocab)
+    docs, qs = B.DeviceVecs(vecs(n, terms)), B.DeviceVecs(vecs(nq, q_terms))
+    ix = B.Index.import_graph(docs, B.build_params(degree, n_entry=16), rng.integers(0, n, (n, degree)).astype(np.int32), rng.permutation(n)[:16].astype(np.int32))
+    return ix, qs
+
+
+def _way(debug_knobs, ix, qs, beam):
+    """What a search's counters say without bounds, with them, and by the library's own choice; the answers are the same."""
+    debug_knobs("search_walk", 1)
+    pw, got, counts = np.ones((qs.n, 3), np.float32), {}, {}
+    for mode in (1, 2, 0):
+        debug_knobs("search_bounds", mode)
+        got[mode] = [t.clone().view(torch.int32) for t in ix.search_batch(qs, min(10, beam), beam, pw)]
+        counts[mode] = ix.search_stats(qs.n)[0][:, 2].clone()
+    assert all(torch.equal(a, b) for mode in (2, 0) for a, b in zip(got[1], got[mode]))
+    assert not torch.equal(counts[1], counts[2])
+    return counts
+
+
+# an iteration of few edges spares little by the bounds, and one of a few dozen queries as much as one of many
+@pytest.mark.parametrize("n,nq,degree,beam,mode", [(40_960, 1024, 16, 16, 1), (40_960, 1024, 64, 16, 2), (250_000, 24, 64, 10, 2), (250_000, 24, 16, 10, 1)])
+def test_small_pools_by_what_their_iterations_spare(debug_knobs, n, nq, degree, beam, mode):
+    ix, qs = _plain_corpus(np.random.default_rng(n), n, nq, 64, 10_000, 20, 12, degree)
+    counts = _way(debug_knobs, ix, qs, beam)
+    assert torch.equal(counts[0], counts[mode])
+    ix.close()
