@@ -795,11 +795,13 @@ void k_search(ApSearchArgs g) {
 #define AP_SEARCH_WS_BYTES ((size_t)2 << 30)
 
 // What the bounds of all documents cost, by what was measured (microseconds): a document's columns are read once (0.4 ns), a
-// tile of 256 queries takes 3.1 ps a pair at 1,280 columns and 1.1 ps for the tail; up to 64 queries take one pass over the columns (0.54 to 0.97 ns a document).
+// tile of 256 queries takes 3.1 ps a pair at 1,280 columns and 1.1 ps for the tail of 165 entries a document, which grows with the lists (519 entries 3.1,
+// 1,254 7.3, 2,259 12); up to 64 queries take one pass over the columns (0.54 to 0.97 ns a document; 37 queries of 1,254 entries 25 us more for 20,000).
+static double ap_list_share(const ap_index *ix) { return std::max(1.0, (double)(ix->sp_nnz + ix->tx_nnz) / (165.0 * (double)ix->docs.n)); }
 double ap_bound_cost(const ap_index *ix, int64_t nq) {
-    const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256);
-    if (nq <= AP_BOUND_FEW) return 15.0 + (double)ix->docs.n * (0.55e-3 + 7e-6 * (double)nq) * cols;
-    return 15.0 + (double)ix->docs.n * (0.4e-3 * cols + tiles * 256.0 * (3.1e-6 * cols + 1.1e-6));
+    const double cols = (double)((ix->bd_kd ? ix->bd_kd : ix->docs.dim) + ix->bd_kh) / 1280.0, tiles = (double)((nq + 255) / 256), lists = ap_list_share(ix);
+    if (nq <= AP_BOUND_FEW) return 15.0 + (double)ix->docs.n * ((0.55e-3 + 7e-6 * (double)nq) * cols + 5e-6 * (double)nq * (lists - 1.0));
+    return 15.0 + (double)ix->docs.n * (0.4e-3 * cols + tiles * 256.0 * (3.1e-6 * cols + 1.1e-6 * lists));
 }
 
 // Whether that is less than they save:
@@ -812,7 +814,10 @@ double ap_bound_cost(const ap_index *ix, int64_t nq) {
 //        32          5..11   9..12  10..17  13..21  14..22  17..25
 //        16          2.. 4   3.. 4   4.. 8   5.. 9   6..12   8..15
 //    and 10 to 20 at degree 64 with pools of 128, where it no longer matters (one query 2.53 and 0.79 ms).  1,000 queries of 100,000 f32 documents at degree 16, pool 16:
-//    0.32 ms without bounds, 0.67 with them; 24 at degree 64, pool 10: 0.47 and 0.23.
+//    0.32 ms without bounds, 0.67 with them; 24 at degree 64, pool 10: 0.47 and 0.23;
+//  - more where documents have long lists, which a search without bounds reads (1,254 entries, 768 f32 columns, degree 64: 2.4 to 3.5 ns a document, and an
+//    iteration of one query 80 us, of 24 to 1,000 190 to 240).  4,000 queries of 100,000 such documents, pools of 10, 16 and 24: 9.2, 13.1 and 19.2 ms
+//    without bounds, 5.0, 5.4 and 6.0 with them.
 bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters) {
     if (!ix->bd_mem || g_ap_debug.search_bounds == 1 || nq < 1) return false;
     const double n = (double)ix->docs.n;
@@ -822,7 +827,8 @@ bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, 
     if (max_iters > 0) iters = std::min(iters, (double)max_iters);
     const double reached = n * (1.0 - exp(-iters * width * (double)ix->params.degree / n));
     const double iteration = std::min(40.0, 12.0 + 4.0 * log2((double)nq)) * std::min(1.0, pow(ix->params.degree / 64.0, 1.25));
-    return std::max((double)nq * reached * 0.22e-3, iters * iteration) > ap_bound_cost(ix, nq);
+    const double lists = ap_list_share(ix);
+    return std::max((double)nq * reached * 0.22e-3 * (1.5 * lists - 0.5), iters * iteration * lists) > ap_bound_cost(ix, nq);
 }
 
 // Queries per slab when `cap_words` words are available: as many as fit, then evened out over the slabs.

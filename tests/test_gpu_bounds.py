@@ -634,3 +634,12 @@ def test_small_pools_by_what_their_iterations_spare(debug_knobs, n, nq, degree, 
     counts = _way(debug_knobs, ix, qs, beam)
     assert torch.equal(counts[0], counts[mode])
     ix.close()
+
+
+# a search without bounds reads the lists: the longer they are, the smaller the pool from which on bounds pay
+@pytest.mark.parametrize("terms,mode", [(20, 1), (625, 2)])
+def test_small_pools_by_the_length_of_the_lists(debug_knobs, terms, mode):
+    ix, qs = _plain_corpus(np.random.default_rng(terms), 40_960, 1024, 64, 100_000, terms, 12, 32)
+    counts = _way(debug_knobs, ix, qs, 6)
+    assert torch.equal(counts[0], counts[mode])
+    ix.close()
