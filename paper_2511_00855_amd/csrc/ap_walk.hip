@@ -787,7 +787,7 @@ int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, co
 // Whether a batch is searched by the walk, and whether out of the bounds (1) or with every document scored ahead (2), by what was
 // measured (microseconds; f32 rows of 768 columns and bf16 rows of 1,024, 3,000 to 100,000 documents, 1 to 1,000 queries):
 //  - the walk: 60 and 1.1 an entry of the pool (2.0 at 2,048 entries, whose lists are longer than a wave), whatever the number
-//    of parents, out of the bounds 45 more; a batch that does not fit the chip at once takes that several times;
+//    of parents, out of the bounds 45 more (several parents: 90 either way); a batch that does not fit the chip at once takes that several times;
 //  - scoring ahead: the documents' bytes at 5 TB/s, 0.4 ns a document at least; all documents of a corpus that the last-level
 //    cache holds, at 16 TB/s from the second query on;
 //  - k_search with bounds: 80, per iteration 5.5 with one parent (6.6 from 90 queries on), 13.6 with four, 18 with sixteen (0.45 of that on 3,000
@@ -795,8 +795,8 @@ int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, co
 //    while the chip is full (0.24 without bounds).
 // One query of 100,000 documents, pool 128: 867 -> 254 us (all scored ahead: the scores 92, the lines 11, the walk 137);
 // 37 of 120,011, pool 512: 3.17 -> 0.93 ms (out of the bounds: these 0.10 ms, the lines 0.01, the scores 0.14, the walk 0.63).  Where the walk would not be an eighth faster by this count (a fifth with more parents, for which
-// the 60, the 80 and the 6.6 were not measured), k_search stays:
-// 300 queries with a pool of 128, 1.2 and 1.6 ms.  16 queries of 60,000 documents of 128 columns, pool 32: 293 and 178 us, 64 of 100,000 of 768, pool 128: 1,067 and 647.
+// the 60, the 80, the 6.6 and the 45 were not measured), k_search stays:
+// 16 queries of 20,000 documents of 768 columns, pool 128, four parents: 482 and 316 us. 300 queries with a pool of 128, 1.2 and 1.6 ms.  16 queries of 60,000 documents of 128 columns, pool 32: 293 and 178 us, 64 of 100,000 of 768, pool 128: 1,067 and 647.
 // A way whose lists would not hold what enters them is not taken: a query whose list is full is searched twice (43,000 documents, degree 32,
 // 3 queries, pool 2,048: 10.9 ms by k_search, 13.3 scored ahead, 4.3 out of the bounds; degree 64, pool 3,600: 14.8, 29.0 and 7.9).  Documents that are
 // met enter while they score at least the last line that the pool has filled, taking those met for any of the corpus; what leaves as a parent
@@ -818,7 +818,7 @@ ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t wi
     const bool single = width == 1;
     const double walk = (single ? 60.0 : 90.0) + beam * (1.1 + std::max(0, beam - 512) * 6e-4) * ceil(q / (256.0 * std::max(1.0, per_cu)));
     const double table = ap_bound_cost(ix, nq);
-    const double out_of_bounds = walk + 45.0 + table + q * first * n * std::max(0.4e-3, row / 5e6);
+    const double out_of_bounds = walk + (single ? 45.0 : 0.0) + table + q * first * n * std::max(0.4e-3, row / 5e6);
     const double all = walk + n * row / 5e6 + (q - 1) * n * std::max(0.16e-3, row / (n * row <= 2e8 ? 16e6 : 7.5e6));
     const double near = std::min(1.2, std::max(0.4, 0.45 + 0.36 * log10(n / 3000.0)));
     const double other = bounds ? table + (single ? 80.0 : 0.0) + std::max(iters * near * (5.5 + (single ? 0.012 * std::min(q, 90.0) : std::min(2.7 * (width - 1), 12.5))), q * met * 0.09e-3)

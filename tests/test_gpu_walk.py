@@ -200,3 +200,19 @@ def test_walks_whose_lists_would_not_hold_what_enters_them(debug_knobs, degree, 
     assert third[1] != third[2] and max(third[3]) == 0 < min(third[1] + third[2])
     assert third[0] == third[way], third
     ix.close()
+
+
+def test_the_plans_choice_with_several_parents(debug_knobs):
+    """16 queries with four parents, where the cost model has the walk out of the bounds just a fifth faster than the search."""
+    n, nq, rng = 20_000, 16, np.random.default_rng(4)
+    w = make_workload("tiny", seed=4, n=n, nq=nq, dim=768, vocab=30_522, sp=("fixed", 100), tx=("fixed", 60))
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    ix = B.Index.import_graph(docs, B.build_params(64, n_entry=16), rng.integers(0, n, (n, 64)).astype(np.int32), rng.permutation(n)[:16].astype(np.int32))
+    got, third = {}, {}
+    for mode in (1, 2, 3, 0):
+        debug_knobs("search_walk", mode)
+        got[mode] = _searches(ix, qs, None, [(10, 128, 4)])
+        third[mode] = ix.search_stats(nq)[0][:, 2].clone()
+    assert all(torch.equal(a, b) for mode in (2, 3, 0) for a, b in zip(got[1], got[mode]))
+    assert torch.equal(third[0], third[2]) and not torch.equal(third[0], third[1]) and (third[2] > 0).any()
+    ix.close()
