@@ -884,6 +884,26 @@ int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, 
     return AP_OK;
 }
 
+// LDS of a search's arrays.  k: of the secondary pool, with keywords.
+static size_t ap_search_lds(int32_t L, bool kw, int32_t k, bool big_tables, int32_t nt, int32_t cmax, int32_t icap) {
+    const bool pipe = !kw && !big_tables && nt >= 512;   // the large-pool path: entering keys in the candidates' space, a bitmap of the pool
+    const int32_t nxtw = !pipe && cmax > nt ? cmax : 0;
+    return (size_t)(L + (pipe ? 1 : 2) * cmax + nxtw + (kw ? cmax + k : 0)) * 8 + (size_t)cmax * 16 +
+           (size_t)(big_tables ? ApQTab<true>::SLOTS : ApQTab<false>::SLOTS) * 8 + (pipe ? (size_t)((L + 63) / 64) * 8 : 0) + (pipe && icap ? 8 + (size_t)icap * 4 : 0);
+}
+// Workgroup size (plain search): four waves as long as the LDS holds at least five workgroups per CU; a pool
+// that leaves room for two to four gets eight waves, one that fills the CU alone sixteen (measured: each is the
+// fastest in its range).
+static int32_t ap_search_threads(int32_t L, int32_t cmax) {
+    const size_t per_cu = (size_t)160 * 1024 / ap_search_lds(L, false, 0, false, 256, cmax, 0);
+    return per_cu > AP_SEARCH_NT512_AT ? 256 : per_cu > AP_SEARCH_NT1024_AT ? 512 : 1024;
+}
+// Whether a plain search may take a floor below which neighbours wait: where it ends by itself, in large pools.  In small ones (256 threads) what
+// it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
+static bool ap_search_waits(const ap_index *ix, int32_t beam, int32_t width, int32_t max_iters) {
+    return max_iters == 0 && !ix->deleted && g_ap_debug.search_floor != 1 && ap_search_threads(beam, std::max(ix->params.n_entry, width * ix->params.degree)) >= 512;
+}
+
 // The launch itself.  Q: the queries (any view with f32 dense rows); w_dev / w_stride: device weights, one triple
 // per query (stride 3) or one for all (stride 0).  kw_terms == NULL: the plain search; otherwise the
 // keyword-constrained one.  The queries run in slabs of ws.slab, one launch each, that share the workspace.
@@ -937,21 +957,12 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
     g.bound_col = ix->bd_mem ? ix->bd_col + ix->corpus.sp_vocab : nullptr;
     g.bound_bits = ix->bd_bits;
     g.tx_vocab = ix->corpus.tx_vocab;
-    auto lds_bytes = [&](int32_t nt, int32_t cmax, int32_t icap) {
-        const bool pipe = !kw && !big_tables && nt >= 512;   // the large-pool path: entering keys in the candidates' space, a bitmap of the pool
-        const int32_t nxtw = !pipe && cmax > nt ? cmax : 0;
-        return (size_t)(g.L + (pipe ? 1 : 2) * cmax + nxtw + (kw ? cmax + g.k : 0)) * 8 + (size_t)cmax * 16 +
-               (size_t)(big_tables ? ApQTab<true>::SLOTS : ApQTab<false>::SLOTS) * 8 + (pipe ? (size_t)((g.L + 63) / 64) * 8 : 0) + (pipe && icap ? 8 + (size_t)icap * 4 : 0);
-    };
-    // Workgroup size (plain search): four waves as long as the LDS holds at least five workgroups per CU; a pool
-    // that leaves room for two to four gets eight waves, one that fills the CU alone sixteen (measured: each is the
-    // fastest in its range).
+    auto lds_bytes = [&](int32_t nt, int32_t cmax, int32_t icap) { return ap_search_lds(beam, kw, kw ? k : 0, big_tables, nt, cmax, icap); };
     const int64_t at_once = std::min(ws.slab, nq);
     int32_t nt = 256;
     g.icap = 0;
     if (!kw && !big_tables) {
-        const size_t per_cu = (size_t)160 * 1024 / lds_bytes(256, g.cmax, 0);
-        nt = per_cu > AP_SEARCH_NT512_AT ? 256 : per_cu > AP_SEARCH_NT1024_AT ? 512 : 1024;
+        nt = ap_search_threads(beam, g.cmax);
         // A pool that fills the CU alone because of the candidates beside it: their descriptors and keys take 28 bytes each, their ids 4,
         // and what gets past the bounds is a few dozen an iteration.  Listed and scored AP_SEARCH_LISTED at a time, two queries
         // of eight waves share the CU, and one reads while the other ranks and merges.  2,000 queries of 500,000 bf16 documents,
@@ -1005,9 +1016,7 @@ static int ap_search_launch(const ap_index *ix, const ApSearchWs &ws, const ApVe
         else if (!kw && !visited_fit(128) && visited_fit(256)) most = bf16 && ix->docs.dim > 512 ? 0 : !bf16 && ix->docs.dim > 512 ? 16 : 19;
         if (at_once * 10 > four * least && at_once * 10 <= four * most && at_once <= slots(128, lds_bytes(128, g.cmax, 0))) nt = 128;
     }
-    // A floor below which neighbours wait: where a search ends by itself, in large pools.  In small ones (256 threads) what
-    // it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
-    g.bound_floor = ws.bound.table && ws.bound.marks && nt >= 512 && max_iters == 0 && g_ap_debug.search_floor != 1 ? reinterpret_cast<const float4 *>(ws.bound.floor) : nullptr;
+    g.bound_floor = ws.bound.table && ws.bound.marks ? reinterpret_cast<const float4 *>(ws.bound.floor) : nullptr;   // the caller asked for marks: ap_search_waits
     g.marks = ws.bound.marks;
     g.nxtw = nt <= 256 && g.cmax > nt ? g.cmax : 0;
     g.vis_lds = visited_fit(nt) ? 1 : 0;
@@ -1087,7 +1096,7 @@ static int ap_search_impl(ap_index *ix, const ap_queries *q, const float *per_qu
     ApSearchWs ws;
     const bool bounds = ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters);
     const ApWalkPlan plan = kw_terms ? ApWalkPlan() : ap_walk_plan(ix, q->nq, p->beam, p->search_width, p->max_iters, bounds, true);
-    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, bounds, plan, !kw_terms && !ix->deleted && p->max_iters == 0));
+    AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, bounds, plan, !kw_terms && ap_search_waits(ix, p->beam, p->search_width, p->max_iters)));
     return ap_search_launch(ix, ws, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, p->k, p->beam, p->max_iters,
                             p->search_width, kw_terms, kw_stride, kw_flags, false, out_ids, out_scores, (hipStream_t)stream);
 }

@@ -31,3 +31,31 @@ def test_marked_floors(debug_knobs, n, width, beam):
     for key in got:
         assert all(torch.equal(a, b) for a, b in zip(got[1, 0], got[key])), key
     ix.close()
+
+
+# pools that two, four and eight waves search
+@pytest.mark.parametrize("nq,beam,threads", [(2400, 64, 128), (1500, 256, 256), (1500, 1200, 512)])
+def test_marks_are_laid_out_where_a_floor_is_taken(debug_knobs, nq, beam, threads):
+    """A search with a limit of iterations takes no floor: what a small pool's search takes of memory is no more than that."""
+    n = 30_000
+    w = make_workload("tiny", seed=1, n=n, nq=nq, dim=64, sp=("fixed", 8), tx=("fixed", 8))
+    rng = np.random.default_rng(1)
+    docs, qs = B.DeviceVecs(w.docs), B.DeviceVecs(w.queries)
+    graph, entry = rng.integers(0, n, (n, 64)).astype(np.int32), rng.permutation(n)[:16].astype(np.int32)
+    debug_knobs("search_bounds", 2)
+    debug_knobs("search_walk", 1)
+    took = []
+    for iters in (1, 0):
+        ix = B.Index.import_graph(docs, B.build_params(64, n_entry=16), graph, entry)
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        before = torch.cuda.mem_get_info()[0]
+        ix.search_batch(qs, 10, beam, max_iters=iters, search_width=1 if threads < 512 else 16)
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        took.append(before - torch.cuda.mem_get_info()[0])
+        print(beam, iters, ix.search_form(), took, flush=True)
+        assert ix.search_form()["threads"] == threads
+        ix.close()
+    words = nq * (n // 32) * 8   # bytes of the marks
+    assert took[1] - took[0] < words // 2 if threads < 512 else took[1] - took[0] > words // 2
