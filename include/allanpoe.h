@@ -363,6 +363,10 @@ int ap_build_scored(const ap_index *index, uint64_t *out, void *stream);
  * f16 (the candidates are then scored again in f32), 0 = f32. */
 int ap_build_seed_bf16(const ap_index *index, int32_t *out);
 
+/* Bytes of scratch that a construction of n documents holds from its start to its end and its stages take one after the other (host
+ * uint64): at most 64 MiB; a stage that needs more makes its own while it runs. */
+int ap_build_shared_bytes(const ap_build_params *params, int64_t n, uint64_t *out);
+
 /* Whether the rounds of the last construction or insertion that gave this index told candidates apart by packed lists
  * (host int32): 1 = yes, 0 = every candidate's record was read. */
 int ap_build_packed(const ap_index *index, int32_t *out);

@@ -2888,14 +2888,20 @@ struct BuildBufs {
     }
 };
 
-// Bytes of the scratch that a construction's stages after ingest take one after the other: those of the refinement, the assembly and the
-// entry points, and of the exact seed lists and the neighbourhood similarities where they are small.
+// Bytes of the scratch that a construction's stages after ingest take one after the other: those of the exact seed lists, the refinement,
+// the neighbourhood similarities, the assembly and the entry points, of each where it is small.  (Of 8.8 million documents the assembly alone takes
+// 1.1 GB, which the buffers of the seed sweep have use for.)
 static size_t build_work_bytes(const ap_build_params &p, int64_t n) {
-    const size_t K = (size_t)p.knn_k, N = (size_t)n, seed = (N + AP_TILE - 1) / AP_TILE * AP_TILE * N * 4, pm = N * K * K * 4;
-    size_t most = std::max({N * 12, N * (size_t)(p.degree / 4) * 8, (size_t)p.n_entry * 4});
-    if (seed <= AP_WORK_BYTES) most = std::max(most, seed);
-    if (pm <= AP_WORK_BYTES) most = std::max(most, pm);
+    const size_t K = (size_t)p.knn_k, N = (size_t)n;
+    const size_t stages[] = {(N + AP_TILE - 1) / AP_TILE * AP_TILE * N * 4, N * 12, N * K * K * 4, N * (size_t)(p.degree / 4) * 8, (size_t)p.n_entry * 4};
+    size_t most = 0;
+    for (size_t s : stages) if (s <= AP_WORK_BYTES) most = std::max(most, s);
     return most;
+}
+extern "C" int ap_build_shared_bytes(const ap_build_params *params, int64_t n, uint64_t *out) {
+    AP_REQUIRE(params && out && n >= 1, "NULL argument, or no documents");
+    *out = build_work_bytes(*params, n);
+    return AP_OK;
 }
 
 static int build_impl(ap_index *ix, hipStream_t st, BuildBufs &b) {

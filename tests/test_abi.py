@@ -64,3 +64,17 @@ def test_debug_settings_are_named_and_bounded():
     assert b"no_such_setting" in lib.ap_last_error()
     assert lib.ap_debug_set(b"seed_buffer_cap", C.c_int64(-5)) == -1
     assert lib.ap_debug_set(None, C.c_int64(0)) == -1
+
+
+@pytest.mark.parametrize("degree", [4, 64, 128])
+def test_scratch_held_through_a_construction_is_bounded(degree):
+    """The seed stage sizes its buffers by the memory that is left: what the other stages share takes at most 64 MiB of it."""
+    out, bp = C.c_uint64(0), B.build_params(degree)
+    held = {}
+    for n in (1, 100, 2_000, 65_536, 524_288, 524_289, 8_800_000, 1 << 30):
+        assert B.lib().ap_build_shared_bytes(C.byref(bp), C.c_int64(n), C.byref(out)) == 0
+        held[n] = out.value
+    assert all(0 < b <= 64 << 20 for b in held.values()), held
+    assert held[2_000] >= 2_000 * 2_000 * 4                                  # the exact seed lists' scores
+    assert held[524_288] >= (524_288 * 128 if degree == 64 else 12 * 524_288)   # 16 places of 8 bytes a document at degree 64
+    assert B.lib().ap_build_shared_bytes(None, C.c_int64(5), C.byref(out)) == -1
