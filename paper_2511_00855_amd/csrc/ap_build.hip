@@ -1735,11 +1735,14 @@ extern "C" int ap_stage_refine(const ap_index *ix, int32_t K, int32_t S, int32_t
 // 32 x 32 blocks that reach the triangle: three, two, two and three a wave, the roles going round with the node so that
 // the SIMDs of a CU get the same work.  Same products in the same order as the full tile, so the same bits.  Bound by the gather of the rows (bf16
 // rows: 10.7 -> 9.5 ms for 200,000 documents of 1,024 columns); for f32 rows it was the f32 matrix instructions, at a sixteenth of the bf16
-// rate.  A f32 value is the sum of three bf16 values, each the rounding of what the ones before it leave, and of the nine products of two such sums six
-// matter: what the other three add lies 2^-26 below the product, a quarter of what rounding it to f32 takes off.  So a tile on the diagonal is
-// split while it goes to LDS and takes six bf16 instructions for sixteen columns where f32 ones take eight at twice the cycles each.
-// 100,000 documents of 768 columns: 17.1 -> 9.7 ms.  Largest and root mean square error against 64 bits, of |a||b|: 1.8e-7 and 1.8e-8 -> 1.4e-7 and
-// 1.5e-8 (768 Gaussian columns), 1.26e-6 and 2.7e-7 -> 9.3e-7 and 2.0e-7 (768 positive ones); smaller too at 96, 260 and 1,024 columns.
+// rate.  A f32 value is the sum of three bf16 values, each the rounding of what the ones before it leave.  So a tile on the diagonal is split while it goes to LDS
+// and takes eight bf16 instructions for sixteen columns where f32 ones take eight at twice the cycles each: all products of two such sums but the smallest, which
+// lies 2^-34 below the value.  The bf16 instruction cuts off what it adds to a sum below the sum's last place instead of rounding it, so that a sum that takes every product
+// loses more than f32 instructions do where few columns are not zero (one: 5.9e-8 and 1.3e-7 of |a||b|, twelve of 768: 1.6e-7 and 4.2e-7).  Therefore the
+// products of the first parts, each exact, are summed by 32 columns from zero on and added by the vector unit, which rounds, and the others have a sum of their own.
+// 100,000 documents of 768 columns: 17.0 -> 11.8 ms.  Largest and root mean square error against 64 bits, of |a||b|, with f32 instructions and so:
+// 1.6e-7 and 1.8e-8, 3.4e-8 and 3.6e-9 (768 Gaussian columns); 1.6e-6 and 3.5e-7, 3.1e-7 and 7.0e-8 (768 positive ones); one column that is not zero 5.9e-8 and 2.5e-8
+// either way, three 1.2e-7 and 2.1e-8, 1.1e-7 and 1.5e-8, twelve 1.6e-7 and 1.9e-8, 1.0e-7 and 0.9e-8; smaller too at 4, 16, 96, 260 and 1,024 columns.
 // Not where a norm says that values may overflow as bf16 (beyond 1e15) or that a rounding's rest may get lost among the smallest numbers (below
 // 1e-12), nor with an infinity or a NaN: those neighbourhoods take the f32 instructions.
 #define AP_GD_STRIDE (AP_BK + 8)   // bf16 elements: 80-byte rows, of which eight lanes' 16-byte reads meet every bank once
@@ -1753,7 +1756,7 @@ __device__ __forceinline__ void ap_split_bf16(float x, float y, uint32_t (&part)
     }
 }
 template <int DT>
-__global__ __launch_bounds__(256) void k_gram_dense(const void *dense, const float *__restrict__ norm, int32_t dim, int32_t K, const int32_t *__restrict__ knn,
+__global__ __launch_bounds__(256, DT == AP_F32 ? 2 : 1) void k_gram_dense(const void *dense, const float *__restrict__ norm, int32_t dim, int32_t K, const int32_t *__restrict__ knn,
                                                     const int32_t *__restrict__ node_ids, int64_t x0,
                                                     float *__restrict__ pm /* chunk x K x K */) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[ApTileLds<DT>::BYTES];
@@ -1811,7 +1814,15 @@ __global__ __launch_bounds__(256) void k_gram_dense(const void *dense, const flo
 #pragma unroll
             for (int p = 0; p < 3; p++) f[p] = __builtin_bit_cast(ap_bf16x8, *reinterpret_cast<const uint4 *>(at + p * PLANE));
         };
-        constexpr int TA[6] = {1, 2, 0, 1, 0, 0}, TB[6] = {1, 0, 2, 0, 1, 0};   // the smallest products first
+        constexpr int N = 7, TA[N] = {1, 2, 1, 2, 0, 1, 0}, TB[N] = {2, 1, 1, 0, 2, 0, 1};   // the smaller products, the smallest first
+        ap_f32x16 rest[2][2];   // their sum
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) rest[a][b][r] = 0.f;
+        const ap_f32x16 none = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (int32_t k0 = 0; k0 < dim; k0 += AP_BK) {
             __syncthreads();
             const bool inside = k0 + (int)(threadIdx.x & 7) * 4 < dim;
@@ -1828,28 +1839,36 @@ __global__ __launch_bounds__(256) void k_gram_dense(const void *dense, const flo
             __syncthreads();
             if (k0 + AP_BK < dim) ap_tile_load<DT>(dense, dim, ra, k0 + AP_BK, va);
             if (!any) continue;
+            auto multiply = [&](const uint16_t *px, const uint16_t *py, ap_f32x16 &to, ap_f32x16 &low) {
+                ap_f32x16 first = none;
 #pragma unroll
-            for (int kk = 0; kk < AP_BK; kk += 16) {
-                ap_bf16x8 a0[3], c1[3], b0[3];
-                read(pa + kk, a0);
-                read(pc + kk, c1);
-                if (corner) {
+                for (int kk = 0; kk < AP_BK; kk += 16) {
+                    ap_bf16x8 x[3], y[3];
+                    read(px + kk, x);
+                    read(py + kk, y);
 #pragma unroll
-                    for (int t = 0; t < 6; t++) {
-                        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[TA[t]], a0[TB[t]], acc[0][0], 0, 0, 0);
-                        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1[TA[t]], a0[TB[t]], acc[1][0], 0, 0, 0);
-                        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1[TA[t]], c1[TB[t]], acc[1][1], 0, 0, 0);
-                    }
-                } else {
-                    read(pb + kk, b0);
-#pragma unroll
-                    for (int t = 0; t < 6; t++) {
-                        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[TA[t]], b0[TB[t]], acc[0][0], 0, 0, 0);
-                        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[TA[t]], c1[TB[t]], acc[0][1], 0, 0, 0);
-                    }
+                    for (int t = 0; t < N; t++) low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[TA[t]], y[TB[t]], low, 0, 0, 0);
+                    first = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], first, 0, 0, 0);
                 }
+#pragma unroll
+                for (int r = 0; r < 16; r++) to[r] += first[r];
+                __builtin_amdgcn_sched_barrier(0);   // one block after the other: two at a time spill
+            };
+            if (corner) {
+                multiply(pa, pa, acc[0][0], rest[0][0]);
+                multiply(pc, pa, acc[1][0], rest[1][0]);
+                multiply(pc, pc, acc[1][1], rest[1][1]);
+            } else {
+                multiply(pa, pb, acc[0][0], rest[0][0]);
+                multiply(pa, pc, acc[0][1], rest[0][1]);
             }
         }
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) acc[a][b][r] += rest[a][b][r];
     }
     if (DT == AP_F32 && odd) {
         float *lA = reinterpret_cast<float *>(lds);
