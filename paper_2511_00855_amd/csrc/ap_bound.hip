@@ -81,8 +81,9 @@ __global__ __launch_bounds__(1024) void k_bd_pick(const int32_t *__restrict__ df
 // A tile's postings: the tail entries of AP_BOUND_QT consecutive documents, grouped by a hash of their terms.  An entry is
 // (term << 8 | document in the tile, value bits); terms of both vocabularies count through and stay below AP_BOUND_VOCAB.
 // The tile's entries begin where its documents' lists do (both vocabularies' offsets together), start[b] is where those of
-// bucket b do behind that.  One block per tile; the order within a bucket is left to chance: a term has one entry per
-// document, so no sum depends on it.
+// bucket b do behind that.  One block per tile; the order within a bucket is left to chance, and with it the order in which the terms of a query are
+// added to a document's entry: bounds, and the counters of what they keep from being scored, may differ by a last place between two ingests of a corpus.
+// That an entry is an upper bound does not depend on it, so ids and scores do not.
 static_assert(AP_BOUND_VOCAB <= (int64_t)1 << 24 && AP_BOUND_QT == 256, "a term and a document of a tile share a word");
 __device__ __forceinline__ uint32_t ap_bound_bucket(uint32_t t, int bits) { return (t * 0x9E3779B1u) >> (32 - bits); }
 __device__ __forceinline__ void ap_bd_post(const ApVecs &D, int64_t tile, int32_t nsp, const int32_t *__restrict__ col, int bits, uint32_t *__restrict__ start,
@@ -577,7 +578,8 @@ __device__ __forceinline__ float2 ap_bound_dnorm(float2 dn) {
 // many terms.  1,000 queries: 707 -> 480 us; 4,000 of some 150 terms, 80,000 documents of 1,024 bf16 columns: 5.5 -> 3.0 ms.
 // Tile order: an XCD takes the document tiles in groups of two and walks each group's query tiles, so that a group's
 // documents and the queries stay in its L2 while they are used.  Groups of four leave some XCDs a group more than others: 4,000 queries of 20,000 documents
-// (79 tiles) 425 us, 367 by two, 359 by one; 10,000 of 100,000 4.1 ms, 3.9 and 4.2.
+// (79 tiles) 425 us, 367 by two, 359 by one; 10,000 of 100,000 4.1 ms, 3.9 and 4.2.  By how many tiles the longest XCD's share grows: by four at most three more than by one,
+// by two at most one, a tenth of the share at 79 tiles and a fiftieth at 391, where the reuse of the queries' columns is worth eight hundredths.
 #define AP_BOUND_GROUP 2
 __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict__ qm, const float *__restrict__ qc, int32_t nq, int32_t q_tiles,
                                                       const uint16_t *__restrict__ dense, int32_t dense_ld, int32_t n_dense,
@@ -713,7 +715,8 @@ __global__ __launch_bounds__(1024) void k_bound_table(const uint16_t *__restrict
 // 64 a stage), a wave 32 documents, whose columns go straight to the matrix unit: a lane reads 64 consecutive bytes of a chunk, half a line, so
 // that the instruction's eight columns are other ones than in the tile above, the same on both sides.  Two chunks are on their way while two are multiplied.
 // 8 waves share 256 documents and their postings.  One query of 100,000 documents of 1,280 columns: 156 us by the tile of 256 queries, 54 so
-// (4.7 TB/s); 37 of 120,011 of 1,536: 175 and 104; 64: 97 and 110; from 65 on the tile takes less than two passes.
+// (4.7 TB/s); 37 of 120,011 of 1,536: 175 and 104.  64 queries, the whole of an exact top-k: 219 and 183 us of 100,000 documents of 1,280 columns, 235 and 196 of 120,011
+// of 1,536, 129 and 110 of 20,000 of 1,280, 91 and 84 of 5,000 of 640; from 65 on the tile takes less than two passes.
 #define AP_BOUND_FEW_STRIDE (256 + 16)   // bytes of a query's two chunks in LDS
 template <int A>
 __global__ __launch_bounds__(512, 4) void k_bound_few(const uint16_t *__restrict__ qm, const float *__restrict__ qc, int32_t nq, const uint16_t *__restrict__ dense,

@@ -585,7 +585,7 @@ __global__ void k_scatter_rows(const int32_t *__restrict__ list, int64_t nlist, 
 // like an overflowing row of the one-sided sweep.  The lists are the exact ones either way.
 // rounded (f32 rows): thresholds and sweep take the rows rounded to f16, at eight times the matrix rate, and the few candidates that the
 // rounding leaves open are scored in f32 (k_rescore_buf).  The lists are the same bits.  100,000 rows of 768 columns, K = 128: 82.7 ms with
-// f32 products (71 of them the sweep), 23 ms rounded (9.4 the sweep); 96 columns: 23.4 and 11.5 ms.
+// f32 products (71 of them the sweep), 20.9 ms rounded (9.4 the sweep); 96 columns: 23.4 and 9.9 ms.
 // *done = false (and AP_OK): not applicable here (shape, memory; rounded: norms that differ too much, or rows too much alike for the
 // rounding to tell them apart, which a sample of rows says before the sweep); the caller takes the next sweep.  Rows with a mean cosine of 0.8,
 // 100,000 x 768, K = 128: 84.5 ms, the f32 sweep alone 83.8, and 100 with the rounded sweep in front of it.

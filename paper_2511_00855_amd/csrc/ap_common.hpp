@@ -154,7 +154,7 @@ struct ApWork {
     size_t bytes = 0;
     template <typename T> T *take(size_t count) const { return count * sizeof(T) <= bytes ? static_cast<T *>(mem) : nullptr; }
 };
-#define AP_WORK_BYTES ((size_t)64 << 20)   // scratch beyond that is not held through the stages that do not need it
+#define AP_WORK_BYTES ((size_t)64 << 20)   // a construction's stage that needs more makes its own
 
 // Debug settings (ap_debug_set): 0 = the library's own choice.  They exist so that tests can drive small inputs
 // through the code paths of large ones; nothing here changes a result.

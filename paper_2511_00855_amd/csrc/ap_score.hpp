@@ -19,10 +19,6 @@ struct ApVisited {
         else old = __hip_atomic_fetch_or(g + (v >> 5), bit, __ATOMIC_RELAXED, AP_VIS_SCOPE);
         return (old & bit) != 0u;
     }
-    __device__ __forceinline__ bool test(int32_t v) const {
-        const uint32_t w = l ? l[v >> 5] : __hip_atomic_load(g + (v >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return ((w >> (v & 31)) & 1u) != 0u;
-    }
 };
 
 // Pool keys.  Plain search: ap_make_key (30-bit id, bit 0 = "not yet expanded").
