@@ -304,7 +304,7 @@ ApWalkPlan ap_walk_plan(const ap_index *ix, int64_t nq, int32_t beam, int32_t wi
 int ap_walk_launch(const ap_index *ix, const ApWalk &walk, uint32_t *visited, const ApVecs &Q, const float *w, int32_t w_stride, int32_t k, int32_t beam,
                    int32_t width, int32_t *counts, int32_t *out_ids, float *out_scores, hipStream_t st);
 double ap_bound_cost(const ap_index *ix, int64_t nq);
-bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters);
+bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters, bool keywords = false);
 // address, on the current device, of the static workspace of ap_search_batch_noalloc (looked up once per device)
 int ap_static_scratch(void **out);
 // the plain search with an arbitrary query view and device weights (ap_search.hip); big_tables: the queries are as long

@@ -815,20 +815,22 @@ double ap_bound_cost(const ap_index *ix, int64_t nq) {
 //        16          2.. 4   3.. 4   4.. 8   5.. 9   6..12   8..15
 //    and 10 to 20 at degree 64 with pools of 128, where it no longer matters (one query 2.53 and 0.79 ms).  1,000 queries of 100,000 f32 documents at degree 16, pool 16:
 //    0.32 ms without bounds, 0.67 with them; 24 at degree 64, pool 10: 0.47 and 0.23;
+//  - with keywords, whose parents have half as many edges again, 0.26 to 0.41 ns a document and 0.30 to 0.71 us an edge that an iteration of 200 to 1,000 queries has (4,000
+//    queries of 60,000 bf16 documents at degree 64, pool 16: 2.84 ms without bounds, 1.99 with them; 1,000 of 128 f32 columns at degree 32, pool 10: 0.66 and 0.48);
 //  - more where documents have long lists, which a search without bounds reads (1,254 entries, 768 f32 columns, degree 64: 2.4 to 3.5 ns a document, and an
 //    iteration of one query 80 us, of 24 to 1,000 190 to 240).  4,000 queries of 100,000 such documents, pools of 10, 16 and 24: 9.2, 13.1 and 19.2 ms
 //    without bounds, 5.0, 5.4 and 6.0 with them.
-bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters) {
+bool ap_bound_pays(const ap_index *ix, int64_t nq, int32_t beam, int32_t width, int32_t max_iters, bool keywords) {
     if (!ix->bd_mem || g_ap_debug.search_bounds == 1 || nq < 1) return false;
     const double n = (double)ix->docs.n;
     if ((double)AP_BOUND_WS_BYTES / (4.0 * n) < (double)std::min<int64_t>(nq, 256)) return false;   // slabs too small to fill the chip
     if (g_ap_debug.search_bounds == 2) return true;
     double iters = (double)beam / width;
     if (max_iters > 0) iters = std::min(iters, (double)max_iters);
-    const double reached = n * (1.0 - exp(-iters * width * (double)ix->params.degree / n));
-    const double iteration = std::min(40.0, 12.0 + 4.0 * log2((double)nq)) * std::min(1.0, pow(ix->params.degree / 64.0, 1.25));
+    const double edges = ix->params.degree * (keywords ? 1.5 : 1.0), reached = n * (1.0 - exp(-iters * width * edges / n));
+    const double iteration = std::min(40.0, 12.0 + 4.0 * log2((double)nq)) * pow(std::min(edges, 96.0) / 64.0, 1.25);
     const double lists = ap_list_share(ix);
-    return std::max((double)nq * reached * 0.22e-3 * (1.5 * lists - 0.5), iters * iteration * lists) > ap_bound_cost(ix, nq);
+    return std::max((double)nq * reached * (keywords ? 0.35e-3 : 0.22e-3) * (1.5 * lists - 0.5), iters * iteration * lists) > ap_bound_cost(ix, nq);
 }
 
 // Queries per slab when `cap_words` words are available: as many as fit, then evened out over the slabs.
@@ -1094,7 +1096,7 @@ static int ap_search_impl(ap_index *ix, const ap_queries *q, const float *per_qu
     if (q->nq == 0) return AP_OK;
     const ApVecs Q{q->nq, ix->docs.dim, q->dense, q->sp_indptr, q->sp_idx, q->sp_val, q->tx_indptr, q->tx_idx, q->tx_cnt};
     ApSearchWs ws;
-    const bool bounds = ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters);
+    const bool bounds = ap_bound_pays(ix, q->nq, p->beam, p->search_width, p->max_iters, kw_terms && !(kw_flags & AP_KW_NO_EDGES));
     const ApWalkPlan plan = kw_terms ? ApWalkPlan() : ap_walk_plan(ix, q->nq, p->beam, p->search_width, p->max_iters, bounds, true);
     AP_TRY(ap_search_reserve(ix, q->nq, (hipStream_t)stream, &ws, bounds, plan, !kw_terms && ap_search_waits(ix, p->beam, p->search_width, p->max_iters)));
     return ap_search_launch(ix, ws, Q, per_query_w ? per_query_w : ix->w_dev, per_query_w ? 3 : 0, p->k, p->beam, p->max_iters,

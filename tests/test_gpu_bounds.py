@@ -643,3 +643,22 @@ def test_small_pools_by_the_length_of_the_lists(debug_knobs, terms, mode):
     counts = _way(debug_knobs, ix, qs, 6)
     assert torch.equal(counts[0], counts[mode])
     ix.close()
+
+
+def test_small_pools_with_keywords(debug_knobs):
+    """With keywords an iteration has half as many edges again: bounds pay from smaller pools on."""
+    n, nq, degree, beam, rng = 40_960, 1024, 32, 6, np.random.default_rng(3)
+    plain, qs = _plain_corpus(rng, n, nq, 64, 10_000, 20, 12, degree)
+    sem, _, _, entry = plain.export_graph()
+    edges = torch.randint(0, n, (n, degree // 2), generator=torch.Generator().manual_seed(3)).to(torch.int32)
+    ix = B.Index.import_graph(plain.docs, B.build_params(degree, n_entry=16), sem, entry, edges, torch.full((n,), degree // 2, dtype=torch.int32))
+    assert torch.equal(_way(debug_knobs, ix, qs, beam)[0], _way(debug_knobs, ix, qs, beam)[1])   # without keywords they do not
+    kw = torch.randint(0, 10_000, (nq, 2), generator=torch.Generator().manual_seed(4)).to(torch.int32)
+    got, counts = {}, {}
+    for mode in (1, 2, 0):
+        debug_knobs("search_bounds", mode)
+        got[mode] = [t.clone().view(torch.int32) for t in ix.search_batch_keywords(qs, 5, beam, kw)]
+        counts[mode] = ix.search_stats(nq)[0][:, 2].clone()
+    assert all(torch.equal(a, b) for mode in (2, 0) for a, b in zip(got[1], got[mode]))
+    assert torch.equal(counts[0], counts[2]) and not torch.equal(counts[0], counts[1])
+    ix.close(); plain.close()
