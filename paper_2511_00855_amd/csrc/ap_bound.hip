@@ -897,9 +897,12 @@ __global__ __launch_bounds__(1024) void k_bound_floor(const float *__restrict__ 
 // The floors of the slab's queries for a pool of `beam` entries: as if the documents a search meets were drawn at random,
 // with a quarter of the pool on top; they are better than that, so the pool's last score usually ends above it.  The lower ones, which four and sixteen
 // times as many documents reach, serve the first iterations.
-int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st) {
+double ap_bound_floor_share(const ap_index *ix, int32_t beam) {
     const double n = (double)ix->docs.n, met = n * (1.0 - exp(-(double)beam * ix->params.degree / n));
-    const float share = (float)(g_ap_debug.search_floor == 2 ? 0.002 : std::min(1.0, 1.25 * beam / met));
+    return g_ap_debug.search_floor == 2 ? 0.002 : std::min(1.0, 1.25 * beam / met);
+}
+int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st) {
+    const float share = (float)ap_bound_floor_share(ix, beam);
     hipLaunchKernelGGL(k_bound_floor, dim3((unsigned)nq), dim3(1024), 0, st, b.table, b.ld, ix->docs.n, make_float4(share, 4.f * share, 16.f * share, 0.f),
                        reinterpret_cast<float4 *>(b.floor), b.marks, (ix->docs.n + 31) / 32);
     AP_CHECK_HIP(hipGetLastError());

@@ -295,6 +295,7 @@ static inline int ap_bound_make_room(const ap_index *ix, hipStream_t st, T **p, 
 int ap_bound_reserve(const ap_index *ix, int64_t nq, int64_t least, size_t cap, int tables, hipStream_t st, ApBound *b);
 int ap_bound_fill(const ap_index *ix, const ApBound &b, const ApVecs &Q, const float *w, int32_t w_stride, int64_t q0, int64_t nq,
                   const int32_t *kw_terms, int32_t kw_stride, hipStream_t st);
+double ap_bound_floor_share(const ap_index *ix, int32_t beam);
 int ap_bound_floors(const ap_index *ix, const ApBound &b, int64_t nq, int32_t beam, hipStream_t st);
 // sizes the workspace an index owns (grow only, capped) for a call of nq queries (ap_search.hip); marks: the search may take a floor (k_search)
 int ap_search_reserve(ap_index *ix, int32_t nq, hipStream_t st, ApSearchWs *ws, bool bounds, const ApWalkPlan &plan = ApWalkPlan(), bool marks = false);

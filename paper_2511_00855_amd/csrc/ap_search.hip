@@ -901,9 +901,9 @@ static int32_t ap_search_threads(int32_t L, int32_t cmax) {
     return per_cu > AP_SEARCH_NT512_AT ? 256 : per_cu > AP_SEARCH_NT1024_AT ? 512 : 1024;
 }
 // Whether a plain search may take a floor below which neighbours wait: where it ends by itself, in large pools.  In small ones (256 threads) what
-// it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.
+// it keeps from being scored is little -- 590 instead of 730 documents at beam 128 -- and its code costs more.  A pool for (nearly) all documents has no floor.
 static bool ap_search_waits(const ap_index *ix, int32_t beam, int32_t width, int32_t max_iters) {
-    return max_iters == 0 && !ix->deleted && g_ap_debug.search_floor != 1 && ap_search_threads(beam, std::max(ix->params.n_entry, width * ix->params.degree)) >= 512;
+    return max_iters == 0 && !ix->deleted && g_ap_debug.search_floor != 1 && ap_bound_floor_share(ix, beam) < 1.0 && ap_search_threads(beam, std::max(ix->params.n_entry, width * ix->params.degree)) >= 512;
 }
 
 // The launch itself.  Q: the queries (any view with f32 dense rows); w_dev / w_stride: device weights, one triple
